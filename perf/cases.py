@@ -1,0 +1,373 @@
+"""The work that is timed: calls of the public entry points over the range of sizes they are used at.
+
+A case is a dict of plain values.  `call` names the entry point:
+  step         GMeta.meta_step, sparse meta-gradient as a coalesced row list
+  step_table   GMeta.meta_step, sparse meta-gradient added into a table-shaped accumulator (tasks in waves)
+  train        GMeta.meta_train: several iterations in one call, parameters updated in place
+  train_table  GMeta.meta_train_step_table: one iteration with the table-shaped accumulator, parameters updated in place
+  group        GMeta.group_batch: one-task batches assembled from a flat stream of records
+The other keys are the model (n_fields, rows, emb_dim, hidden, dtype), the batch (tasks, support, query, sizes, bag_max,
+zipf, private) and the method (inner_steps, order, adapt_rows).  Shapes are those of synth/configs.py, with fewer tasks or
+smaller tables where three whole states would not fit one GPU, and ragged or odd ones between them.
+"""
+import functools
+import math
+from types import SimpleNamespace
+
+import numpy as np
+import torch
+
+from paper_2401_04338_amd import GMeta
+
+N_DENSE = 13
+INNER_LR = 0.01
+OUTER_LR = 1e-4
+LABEL_RATE = 0.2
+
+
+def _case(name, call, **kw):
+    c = dict(name=name, call=call, tasks=4, n_fields=8, rows=1000, emb_dim=16, hidden="64-32", dtype="fp32", support=32,
+             query=32, sizes="equal", bag_max=1, zipf=0.0, private=0, inner_steps=1, order=2, adapt_rows=1, batches=1, waves=1)
+    c.update(kw)
+    return c
+
+
+def listed():
+    return [
+        # The smallest call: a handful of tasks, fp32, one lookup per bag.  Latency and launch count.
+        _case("step_tiny_fp32", "step"),
+        # The ordinary fp32 call: tens of tasks, multi-hot bags, skewed rows.
+        _case("step_small_fp32", "step", tasks=64, n_fields=26, rows=100_000, emb_dim=32, hidden="256-128", support=128,
+              query=128, bag_max=8, zipf=1.05),
+        # fp32 with nothing round: ragged tasks, odd widths, several first-order inner steps.
+        _case("step_ragged_fp32", "step", tasks=37, n_fields=11, rows=7_001, emb_dim=16, hidden="100-52", support=45, query=61,
+              sizes="ragged", bag_max=5, zipf=1.1, inner_steps=2, order=1),
+        # A few tasks with the widest model: adapting a model to new users as they come.
+        _case("step_few_bf16", "step", tasks=3, n_fields=64, rows=1 << 17, emb_dim=64, hidden="1024-512-256", dtype="bf16",
+              support=512, query=512, bag_max=32, zipf=1.05),
+        # The ordinary bf16 call: hundreds of tasks, three second-order inner steps.
+        _case("step_medium_bf16", "step", tasks=512, n_fields=26, rows=1_000_000, emb_dim=64, hidden="512-256", dtype="bf16",
+              support=256, query=256, bag_max=20, zipf=1.1, inner_steps=3),
+        # The same model, first order, with tasks of no round size.
+        _case("step_first_order_bf16", "step", tasks=201, n_fields=26, rows=300_007, emb_dim=64, hidden="512-256", dtype="bf16",
+              support=150, query=243, sizes="ragged", bag_max=20, zipf=1.1, inner_steps=3, order=1),
+        # Cold start: many small tasks of very uneven size, some fields with rows of the task's own.
+        _case("step_coldstart_bf16", "step", tasks=700, n_fields=40, rows=350_000, emb_dim=64, hidden="1024-512-256",
+              dtype="bf16", support=32, query=32, sizes="lognormal", bag_max=10, zipf=1.2, private=4, inner_steps=2),
+        # Dense-only inner adaptation: the inner loop reads the embeddings as they are.
+        _case("step_dense_only_bf16", "step", tasks=128, n_fields=26, rows=300_000, emb_dim=64, hidden="512-256", dtype="bf16",
+              support=256, query=256, bag_max=20, zipf=1.1, inner_steps=1, adapt_rows=0),
+        # The largest: the widest model with the longest bags, tasks in waves, table-shaped sparse output.
+        _case("step_large_bf16", "step_table", tasks=256, n_fields=64, rows=1 << 19, emb_dim=64, hidden="1024-512-256",
+              dtype="bf16", support=512, query=512, bag_max=32, zipf=1.05, waves=2),
+        # Sustained training: several iterations in one call, the next batch's index side prepared meanwhile.
+        _case("train_loop_bf16", "train", tasks=96, n_fields=26, rows=200_000, emb_dim=64, hidden="512-256", dtype="bf16",
+              support=256, query=256, bag_max=20, zipf=1.1, inner_steps=1, batches=4),
+        # One iteration of the large model's training with the table-shaped accumulator.
+        _case("train_table_bf16", "train_table", tasks=48, n_fields=64, rows=1 << 17, emb_dim=64, hidden="1024-512-256",
+              dtype="bf16", support=512, query=512, bag_max=32, zipf=1.05),
+        # The step before the hot path: a flat stream of records grouped into one-task batches and split.
+        _case("group_stream", "group", tasks=256, n_fields=26, rows=1_000_000, emb_dim=64, hidden="512-256", dtype="bf16",
+              support=128, query=128, sizes="ragged", bag_max=20, zipf=1.1),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _draw_once(rng):
+    kind = rng.choice(["fp32", "fp32", "fp32", "bf16", "bf16", "bf16", "bf16", "cold", "large", "large", "train", "train_table", "group"])
+    if kind == "fp32":
+        c = _case("", "step", tasks=_log(rng, 2, 64), n_fields=rng.randint(4, 26), rows=_log(rng, 500, 100_000),
+                  emb_dim=rng.choice([16, 32]), hidden=rng.choice(["64-32", "100-52", "256-128", "200-72", "128"]),
+                  support=_log(rng, 8, 128), query=_log(rng, 8, 128), sizes=rng.choice(["equal", "ragged"]),
+                  bag_max=rng.randint(1, 8), zipf=rng.choice([0.0, 1.05, 1.1]), inner_steps=rng.choice([1, 1, 2]),
+                  order=rng.choice([1, 2, 2]))
+    elif kind == "bf16":
+        c = _case("", "step", tasks=_log(rng, 3, 512), n_fields=rng.randint(16, 64), rows=_log(rng, 20_000, 1_000_000), emb_dim=64,
+                  hidden=rng.choice(["512-256", "512-256", "1024-512-256", "640-192"]), dtype="bf16", support=_log(rng, 40, 512),
+                  query=_log(rng, 40, 512), sizes=rng.choice(["equal", "ragged"]), bag_max=rng.randint(4, 32),
+                  zipf=rng.choice([1.05, 1.1]), inner_steps=rng.choice([1, 2, 3]), order=rng.choice([1, 2, 2]),
+                  adapt_rows=rng.choice([1, 1, 1, 0]))
+    elif kind == "cold":
+        c = _case("", "step", tasks=_log(rng, 60, 700), n_fields=rng.randint(20, 40), rows=_log(rng, 50_000, 350_000), emb_dim=64,
+                  hidden=rng.choice(["1024-512-256", "512-256"]), dtype="bf16", sizes="lognormal", bag_max=rng.randint(3, 10),
+                  zipf=1.2, private=4, inner_steps=2)
+    elif kind in ("large", "train_table"):
+        c = _case("", "step_table" if kind == "large" else "train_table", tasks=_log(rng, 16, 256), n_fields=rng.randint(32, 64),
+                  rows=_log(rng, 1 << 16, 1 << 19), emb_dim=64, hidden="1024-512-256", dtype="bf16", support=_log(rng, 200, 512),
+                  query=_log(rng, 200, 512), bag_max=rng.randint(8, 32), zipf=1.05, sizes=rng.choice(["equal", "ragged"]),
+                  waves=rng.choice([1, 2]) if kind == "large" else 1)
+    elif kind == "train":
+        c = _case("", "train", tasks=_log(rng, 16, 128), n_fields=rng.randint(16, 26), rows=_log(rng, 50_000, 200_000), emb_dim=64,
+                  hidden="512-256", dtype="bf16", support=_log(rng, 100, 256), query=_log(rng, 100, 256), bag_max=rng.randint(4, 20),
+                  zipf=1.1, inner_steps=rng.choice([1, 2]), batches=rng.randint(2, 4))
+    else:
+        c = _case("", "group", tasks=_log(rng, 16, 512), n_fields=rng.randint(8, 40), rows=_log(rng, 10_000, 1_000_000), emb_dim=64,
+                  hidden="512-256", dtype="bf16", support=_log(rng, 16, 128), query=_log(rng, 16, 128), sizes="ragged",
+                  bag_max=rng.randint(1, 20), zipf=1.1)
+    del c["name"]
+    return c
+
+
+def _cost(case):
+    w = work(case)
+    return w["bytes"] / 4e12 + w["flops"] / 5e14
+
+
+def _memory(case):
+    """Rough device bytes of a state: per-task parameters, activations, index lists, pair counts, tables and outputs."""
+    d = _dims(case)
+    n_theta = sum(a * b for a, b in zip(d[:-1], d[1:]))
+    T = case["tasks"] / case["waves"]
+    S = T * (case["support"] + case["query"])
+    lookups = S * case["n_fields"] * (case["bag_max"] + 1) / 2
+    return (T * n_theta * (8 + 2 * case["inner_steps"]) + S * d[0] * (14 + 2 * case["inner_steps"]) + lookups * 40 +
+            T * case["n_fields"] * 3 * case["support"] * case["query"] + 2.0 * case["n_fields"] * case["rows"] * case["emb_dim"] * 4)
+
+
+def draw(rng):
+    limit = _cost(listed()[8])
+    while True:
+        c = _draw_once(rng)
+        if _cost(c) <= limit and _memory(c) <= 6e10:
+            return c
+
+
+# ---------------------------------------------------------------------------------------------- inputs
+def _dims(case):
+    return [case["n_fields"] * case["emb_dim"] + N_DENSE] + [int(h) for h in case["hidden"].split("-")] + [1]
+
+
+def _seed(case, seed):
+    return (seed * 1_000_003 + 7_919 * case["tasks"] + 104_729 * case["n_fields"] + case["rows"]) & 0x7FFFFFFF
+
+
+def _task_sizes(case, rng):
+    """[tasks, 2] samples per task and set."""
+    T, base = case["tasks"], np.array([case["support"], case["query"]], dtype=np.float64)
+    if case["sizes"] == "equal":
+        s = np.tile(base, (T, 1))
+    elif case["sizes"] == "ragged":      # uniform between half and one and a half times the mean, capped at 512
+        s = np.rint(base * rng.uniform(0.5, 1.5, size=(T, 2))).clip(1, 512)
+    else:                                # log-normal around a median of 64 samples per task, split 1:1
+        h = np.rint(np.exp(math.log(32) + rng.standard_normal(T))).clip(1, 1024)
+        s = np.stack([h, h], axis=1)
+    return s.astype(np.int64)
+
+
+@functools.lru_cache(maxsize=4)
+def _zipf_cdf(rows, s):
+    c = np.cumsum(np.arange(1, rows + 1, dtype=np.float64) ** -s)
+    return torch.from_numpy(c / c[-1]).to("cuda")
+
+
+def _rows_of(case, field, task, gen):
+    """Row numbers for lookups of the given fields and tasks: uniform, bounded Zipf with the hot ranks spread over the
+    table, or (the first `private` fields) uniform in a block of the task's own."""
+    R = case["rows"]
+    u = torch.rand(field.numel(), dtype=torch.float64, device="cuda", generator=gen)
+    if case["zipf"] > 0:
+        rank = torch.searchsorted(_zipf_cdf(R, case["zipf"]), u, right=True).clamp_(max=R - 1)
+        mult = 2_654_435_761 % R | 1
+        while math.gcd(mult, R) != 1:
+            mult += 2
+        row = (rank * mult + field * (R // 3 + 1)) % R
+    else:
+        row = (u * R).long().clamp_(max=R - 1)
+    if case["private"]:
+        block = max(1, R // case["tasks"])
+        own = (task * block + (u * block).long().clamp_(max=block - 1)).clamp_(max=R - 1)
+        row = torch.where(field < case["private"], own, row)
+    return row.to(torch.int32)
+
+
+def _bag_lengths(case, n, gen):
+    """[n, fields] lookups per bag, uniform in 1..bag_max.  The record stream's are drawn without replacement inside a
+    record (every record holds equally many lookups in all), so that the sizes of what comes back depend on the case alone."""
+    F, most = case["n_fields"], case["bag_max"]
+    if case["call"] != "group":
+        return torch.randint(1, most + 1, (n, F), device="cuda", generator=gen)
+    order = torch.rand(n, F, device="cuda", generator=gen).argsort(dim=1)
+    return order % most + 1
+
+
+def _make_set(case, sizes, gen):
+    F = case["n_fields"]
+    toff = np.zeros(len(sizes) + 1, dtype=np.int64)
+    np.cumsum(sizes, out=toff[1:])
+    n = int(toff[-1])
+    lens = _bag_lengths(case, n, gen).reshape(-1)
+    bag_offsets = torch.zeros(n * F + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(lens, 0, out=bag_offsets[1:])
+    task_of = torch.repeat_interleave(torch.arange(len(sizes), device="cuda"), torch.as_tensor(sizes, device="cuda"))
+    parts, step = [], max(1, (1 << 24) // (F * case["bag_max"]))
+    for lo in range(0, n, step):
+        hi = min(n, lo + step)
+        bag = torch.repeat_interleave(torch.arange(lo * F, hi * F, device="cuda"), lens[lo * F: hi * F])
+        parts.append(_rows_of(case, bag % F, task_of[bag // F], gen))
+    return SimpleNamespace(task_offsets=toff, bag_offsets=bag_offsets,
+                           indices=torch.cat(parts) if parts else torch.zeros(0, dtype=torch.int32, device="cuda"),
+                           dense=torch.randn(n, N_DENSE, device="cuda", generator=gen),
+                           labels=(torch.rand(n, device="cuda", generator=gen) < LABEL_RATE).float())
+
+
+def _make_batch(case, rng, gen):
+    sizes = _task_sizes(case, np.random.default_rng(case["tasks"]) if case["call"] == "group" else rng)
+    return _make_set(case, sizes[:, 0], gen), _make_set(case, sizes[:, 1], gen)
+
+
+def _make_params(case, gen):
+    d = _dims(case)
+    return SimpleNamespace(
+        emb=torch.randn(case["n_fields"] * case["rows"], case["emb_dim"], device="cuda", generator=gen).mul_(0.05),
+        W=[torch.randn(a, b, device="cuda", generator=gen) / math.sqrt(a) for a, b in zip(d[:-1], d[1:])],
+        b=[torch.rand(b, device="cuda", generator=gen) * 0.2 - 0.1 for b in d[1:]])
+
+
+def _list_capacity(case):
+    """Rows a batch's list may hold: what such batches are expected to look up, and a margin."""
+    total = case["n_fields"] * case["rows"]
+    return min(total, int(_distinct(case) * (2.0 if case["sizes"] == "lognormal" else 1.2)) + 1000)
+
+
+def _context(case, batches):
+    args = (case["n_fields"], [case["rows"]] * case["n_fields"], case["emb_dim"], N_DENSE, _dims(case), int(case["dtype"] == "bf16"))
+    probe = GMeta(*args, workspace_bytes=1 << 20)
+    need, lists = 0, 0
+    for s, q in batches:
+        T = -(-case["tasks"] // case["waves"])
+        share = T / case["tasks"] * (1.0 if case["waves"] == 1 else 1.2 if case["sizes"] == "ragged" else 1.03)
+        sizes = [int(x * share) + 1 for x in (len(s.labels), len(q.labels), s.indices.numel(), q.indices.numel())]
+        need = max(need, probe.workspace_bytes(T, *sizes, case["inner_steps"], case["order"]))
+        lists = max(lists, min(s.indices.numel() + q.indices.numel(), case["n_fields"] * case["rows"]) * (case["emb_dim"] * 4 + 8))
+    probe.close()
+    ws = int(need * 1.02) + (8 << 20)
+    if case["call"] == "train":      # beside the step: the meta-gradient lists and a second batch's index structures
+        ws += 2 * lists + int(need * 0.35) + (64 << 20)
+    if case["call"] == "group":
+        ws = 64 * (len(batches[0][0].labels) + len(batches[0][1].labels)) * case["n_fields"] + (8 << 20)
+    ctx = GMeta(*args, workspace_bytes=ws)
+    if case["waves"] > 1:
+        ctx.configure("max_wave_tasks", -(-case["tasks"] // case["waves"]))
+    if not case["adapt_rows"]:
+        ctx.configure("adapt_rows", 0)
+    return ctx
+
+
+def _flat_stream(case, batch, rng):
+    """The batch's records as they arrive from a log: tasks interleaved, two batches per task."""
+    s, q = batch
+    task = np.concatenate([np.repeat(np.arange(case["tasks"]), np.diff(x.task_offsets)) for x in batch])
+    batch_id = np.repeat([0, 1], [len(s.labels), len(q.labels)])
+    order = rng.permutation(len(task))
+    bag_offsets = torch.cat([s.bag_offsets, q.bag_offsets[1:] + s.bag_offsets[-1]])
+    return SimpleNamespace(task=task[order], batch_id=batch_id[order], bag_offsets=bag_offsets,
+                           indices=torch.cat([s.indices, q.indices]), dense=torch.cat([s.dense, q.dense]),
+                           labels=torch.cat([s.labels, q.labels]))
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(_seed(case, seed))
+    rng = np.random.default_rng(_seed(case, seed))
+    st = SimpleNamespace(case=case)
+    st.batches = [_make_batch(case, rng, gen) for _ in range(case["batches"])]
+    st.ctx = _context(case, st.batches)
+    if case["call"] == "group":
+        st.stream = _flat_stream(case, st.batches[0], rng)
+        st.batches = None
+        return st
+    st.params = _make_params(case, gen)
+    if case["call"] == "step":
+        st.out = st.ctx.alloc_outputs(case["tasks"], _list_capacity(case))
+        st.out["emb_rows"].zero_()       # (what lies behind the listed rows is compared too)
+        st.out["emb_grad"].zero_()
+    elif case["call"] in ("step_table", "train_table"):
+        st.table = torch.zeros_like(st.params.emb)
+        st.out = st.ctx.alloc_outputs(case["tasks"], 0)
+    else:
+        st.losses = torch.zeros(case["batches"], device="cuda")
+    return st
+
+
+def run(st):
+    c, ctx = st.case, st.ctx
+    K, order = c["inner_steps"], c["order"]
+    if c["call"] == "group":
+        r = st.stream
+        sets = ctx.group_batch(r.task, r.batch_id, r.bag_offsets, r.indices, r.dense, r.labels, 1, 2)
+        return [[s.task_offsets, s.bag_offsets, s.indices, s.dense, s.labels] for s in sets]
+    if c["call"] == "step":
+        o = ctx.meta_step(*st.batches[0], st.params, INNER_LR, K, order, out=st.out)
+        return [o["loss"], o["task_loss"], o["dW"], o["db"], o["n_emb_rows"], o["emb_rows"], o["emb_grad"]]
+    if c["call"] == "step_table":
+        o = ctx.meta_step(*st.batches[0], st.params, INNER_LR, K, order, out=st.out, emb_grad_table=st.table)
+        return [o["loss"], o["task_loss"], o["dW"], o["db"], st.table]
+    if c["call"] == "train":
+        ctx.meta_train(st.batches, st.params, INNER_LR, K, order, OUTER_LR, losses=st.losses)
+        return [st.losses, st.params.W, st.params.b, st.params.emb]
+    ctx.meta_train_step_table(*st.batches[0], st.params, INNER_LR, K, order, OUTER_LR, st.table, loss=st.out["loss"],
+                              task_loss=st.out["task_loss"])
+    return [st.out["loss"], st.out["task_loss"], st.params.W, st.params.b, st.params.emb]
+
+
+# ---------------------------------------------------------------------------------------------- what a pass has to do
+@functools.lru_cache(maxsize=256)
+def _expected_distinct(rows, zipf, lookups):
+    """Expected number of distinct rows of one table among that many lookups."""
+    if zipf <= 0:
+        return rows * -math.expm1(-lookups / rows)
+    p = np.arange(1, rows + 1, dtype=np.float64) ** -zipf
+    return float(-np.expm1(-(lookups / p.sum()) * p).sum())
+
+
+def _distinct(case):
+    """Expected number of table rows a batch looks up."""
+    lookups = int(sum(_mean_samples(case)) * case["tasks"] * (case["bag_max"] + 1) / 2)
+    return ((case["n_fields"] - case["private"]) * _expected_distinct(case["rows"], case["zipf"], lookups) +
+            case["private"] * _expected_distinct(case["rows"], 0.0, lookups))
+
+
+def _mean_samples(case):
+    if case["sizes"] == "lognormal":
+        return 2 * [32 * math.exp(0.5)]
+    return [case["support"], case["query"]]
+
+
+def work(case):
+    """Operands once, outputs once: table rows looked up, indices, offsets, dense features, labels, parameters in; gradients
+    (or updated parameters) out.  Products of the MLP: forward, backward and weight gradient of every inner step and of
+    the query pass, and for second order the tangent of each (two products where the primal has one)."""
+    T, F, D = case["tasks"], case["n_fields"], case["emb_dim"]
+    S, Q = (T * x for x in _mean_samples(case))
+    lookups = (S + Q) * F * (case["bag_max"] + 1) / 2
+    batch_bytes = lookups * 4 + (S + Q) * (F * 8 + N_DENSE * 4 + 4)
+    if case["call"] == "group":
+        return {"bytes": 2.0 * batch_bytes + (S + Q) * 16, "flops": 0.0}
+    d = _dims(case)
+    n_theta = sum(a * b + b for a, b in zip(d[:-1], d[1:]))
+    n_w = sum(a * b for a, b in zip(d[:-1], d[1:]))
+    distinct = _distinct(case)
+    row = D * 4.0
+    sparse = distinct * (row + row + 8) if case["call"] == "step" else distinct * 3 * row
+    flops = 6.0 * n_w * (S * case["inner_steps"] + Q) + lookups * D
+    if case["order"] == 2:
+        flops += 12.0 * n_w * S * case["inner_steps"]
+    n = case["batches"]
+    return {"bytes": n * (batch_bytes + sparse + 8.0 * n_theta), "flops": n * flops}
+
+
+def tolerance(case):
+    """Four times what was measured against the float64 reference on the same inputs.
+
+    fp32: 1e-7 (rel) and 3e-6 (max) where every ReLU gate falls the same way, but 9e-4 and 0.04 in the one batch of six
+    (37 ragged tasks) where a pre-activation within rounding of zero takes the other side and moves one sample's
+    gradients.  bf16: up to 5e-3 and 0.7, against float64 sums on the same bf16-rounded operands: operands that round
+    the other way and the gates these move; a row that one sample looks up shows all of it.  Updated parameters show
+    an update's difference times its share of the parameter, about 1.5e-2.  Grouping moves bits."""
+    if case["call"] == "group":
+        return "exact"
+    if case["call"] in ("train", "train_table"):
+        return {"rel": 1e-3, "max": 0.05}
+    return {"rel": 0.02, "max": 0.99} if case["dtype"] == "bf16" else {"rel": 4e-3, "max": 0.15}
