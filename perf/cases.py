@@ -238,9 +238,10 @@ def _context(case, batches):
     need, lists = 0, 0
     for s, q in batches:
         T = -(-case["tasks"] // case["waves"])
-        share = T / case["tasks"] * (1.0 if case["waves"] == 1 else 1.2 if case["sizes"] == "ragged" else 1.03)
-        sizes = [int(x * share) + 1 for x in (len(s.labels), len(q.labels), s.indices.numel(), q.indices.numel())]
-        need = max(need, probe.workspace_bytes(T, *sizes, case["inner_steps"], case["order"]))
+        share = 1.0 if case["waves"] == 1 else T / case["tasks"] * (1.2 if case["sizes"] == "ragged" else 1.0)
+        samples = [min(math.ceil(len(x.labels) * share), max(512 * T, len(x.labels) // case["waves"])) for x in (s, q)]
+        nnz = [math.ceil(x.indices.numel() * share * (1.0 if case["waves"] == 1 else 1.02)) for x in (s, q)]
+        need = max(need, probe.workspace_bytes(T, *samples, *nnz, case["inner_steps"], case["order"]))
         lists = max(lists, min(s.indices.numel() + q.indices.numel(), case["n_fields"] * case["rows"]) * (case["emb_dim"] * 4 + 8))
     probe.close()
     ws = int(need * 1.02) + (8 << 20)
