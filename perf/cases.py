@@ -269,17 +269,24 @@ def _flat_stream(case, batch, rng):
                            labels=torch.cat([s.labels, q.labels]))
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
     gen = torch.Generator(device="cuda").manual_seed(_seed(case, seed))
     rng = np.random.default_rng(_seed(case, seed))
     st = SimpleNamespace(case=case)
     st.batches = [_make_batch(case, rng, gen) for _ in range(case["batches"])]
-    st.ctx = _context(case, st.batches)
     if case["call"] == "group":
         st.stream = _flat_stream(case, st.batches[0], rng)
+    else:
+        st.params = _make_params(case, gen)
+    return st
+
+
+def prepare(case, seed):
+    st = _inputs(case, seed)
+    st.ctx = _context(case, st.batches)
+    if case["call"] == "group":
         st.batches = None
         return st
-    st.params = _make_params(case, gen)
     if case["call"] == "step":
         st.out = st.ctx.alloc_outputs(case["tasks"], _list_capacity(case))
         st.out["emb_rows"].zero_()       # (what lies behind the listed rows is compared too)
@@ -311,6 +318,110 @@ def run(st):
     ctx.meta_train_step_table(*st.batches[0], st.params, INNER_LR, K, order, OUTER_LR, st.table, loss=st.out["loss"],
                               task_loss=st.out["task_loss"])
     return [st.out["loss"], st.out["task_loss"], st.params.W, st.params.b, st.params.emb]
+
+
+# ---------------------------------------------------------------------------------------------- the same in 64 bits
+def _segment_sums(values, index, offsets):
+    """Sums of values[index[offsets[i]: offsets[i + 1]]], in pieces of 64: a frequent row's list is long."""
+    n = index.numel()
+    cuts = torch.unique(torch.cat([offsets, torch.arange(0, n, 64, device="cuda")]))
+    cuts = cuts[cuts <= n]
+    pieces = torch.nn.functional.embedding_bag(index, values, cuts, mode="sum", include_last_offset=True)
+    place = torch.searchsorted(cuts, offsets)
+    return torch.nn.functional.embedding_bag(torch.arange(len(pieces), device="cuda"), pieces, place, mode="sum",
+                                             include_last_offset=True)
+
+
+class _Pool(torch.autograd.Function):
+    """Sum-pooling as the linear map that it is; lists = (forward index, offsets, transposed index, offsets)."""
+    @staticmethod
+    def forward(ctx, x, lists):
+        ctx.lists = lists
+        return _segment_sums(x, lists[0], lists[1])
+
+    @staticmethod
+    def backward(ctx, g):
+        return _Pool.apply(g.contiguous(), ctx.lists[2:] + ctx.lists[:2]), None
+
+
+def _task_lookups(case, s, t):
+    """Global row and bag offsets of one task's lookups, its dense features and labels."""
+    lo, hi, F = int(s.task_offsets[t]), int(s.task_offsets[t + 1]), case["n_fields"]
+    off = s.bag_offsets[lo * F: hi * F + 1]
+    first, last = int(off[0]), int(off[-1])
+    off = off - first
+    field = torch.repeat_interleave(torch.arange((hi - lo) * F, device="cuda") % F, off[1:] - off[:-1])
+    return s.indices[first:last].long() + field * case["rows"], off, s.dense[lo:hi].double(), s.labels[lo:hi].double()
+
+
+def _lists(index, offsets, n_rows):
+    bag = torch.repeat_interleave(torch.arange(len(offsets) - 1, device="cuda"), offsets[1:] - offsets[:-1])
+    rows, order = torch.sort(index, stable=True)
+    return index, offsets, bag[order], torch.searchsorted(rows, torch.arange(n_rows + 1, device="cuda"))
+
+
+def _loss64(emb, W, b, lists, dense, labels):
+    a = torch.cat([_Pool.apply(emb, lists).reshape(len(labels), -1), dense], dim=1)
+    for l, (w, x) in enumerate(zip(W, b)):
+        a = a @ w + x
+        a = torch.relu(a) if l + 1 < len(W) else a
+    return torch.nn.functional.binary_cross_entropy_with_logits(a[:, 0], labels)
+
+
+def _meta_gradient64(case, batch, emb, W, b):
+    """Task losses, dense gradients and the table-shaped sparse gradient, task by task by automatic differentiation."""
+    n = len(W)
+    W0, b0 = [[x.detach().requires_grad_() for x in p] for p in (W, b)]
+    dense_grads = [torch.zeros_like(x) for x in W0 + b0]
+    table, losses, second = torch.zeros_like(emb), [], case["order"] == 2
+    for t in range(case["tasks"]):
+        (rs, os, ds, ys), (rq, oq, dq, yq) = (_task_lookups(case, s, t) for s in batch)
+        rows, local = torch.unique(torch.cat([rs, rq]), return_inverse=True)
+        ls, lq = _lists(local[:len(rs)], os, len(rows)), _lists(local[len(rs):], oq, len(rows))
+        e0 = emb[rows].requires_grad_()
+        e, Wk, bk = e0, W0, b0
+        for _ in range(case["inner_steps"]):
+            g = torch.autograd.grad(_loss64(e, Wk, bk, ls, ds, ys), [e, *Wk, *bk], create_graph=second)
+            g = g if second else [x.detach() for x in g]
+            e = e - INNER_LR * g[0] if case["adapt_rows"] else e
+            Wk = [x - INNER_LR * y for x, y in zip(Wk, g[1: 1 + n])]
+            bk = [x - INNER_LR * y for x, y in zip(bk, g[1 + n:])]
+        loss = _loss64(e, Wk, bk, lq, dq, yq)
+        g = torch.autograd.grad(loss, [e0, *W0, *b0])
+        table.index_add_(0, rows, g[0])
+        for x, y in zip(dense_grads, g[1:]):
+            x += y
+        losses.append(loss.detach())
+    return torch.stack(losses), dense_grads[:n], dense_grads[n:], table
+
+
+def exact(case, seed):
+    if case["call"] == "group":
+        return None
+    st = _inputs(case, seed)
+    emb, W, b = st.params.emb.double(), [x.double() for x in st.params.W], [x.double() for x in st.params.b]
+    totals = []
+    for batch in st.batches:
+        task_loss, dW, db, table = _meta_gradient64(case, batch, emb, W, b)
+        totals.append(task_loss.sum().reshape(1))
+        if case["call"] in ("train", "train_table"):
+            for x, g in zip([emb, *W, *b], [table, *dW, *db]):
+                x.sub_(g, alpha=OUTER_LR)
+    if case["call"] == "train":
+        return [torch.cat(totals), W, b, emb]
+    if case["call"] == "train_table":
+        return [totals[0], task_loss, W, b, emb]
+    if case["call"] == "step_table":
+        return [totals[0], task_loss, dW, db, table]
+    seen = torch.zeros(len(emb), dtype=torch.bool, device="cuda")
+    for s in st.batches[0]:
+        F, lens = case["n_fields"], s.bag_offsets[1:] - s.bag_offsets[:-1]
+        field = torch.repeat_interleave(torch.arange(len(lens), device="cuda") % F, lens)
+        seen[s.indices.long() + field * case["rows"]] = True
+    rows = seen.nonzero()[:, 0]
+    grad = torch.zeros(_list_capacity(case), case["emb_dim"], dtype=torch.float64, device="cuda")
+    grad[:len(rows)] = table[rows]
+    return [totals[0], task_loss, dW, db, None, None, grad]
 
 
 # ---------------------------------------------------------------------------------------------- what a pass has to do
