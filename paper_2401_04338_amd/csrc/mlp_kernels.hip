@@ -7,71 +7,151 @@
 #include "gm_internal.h"
 
 // ------------------------------------------------------------------------------------------------
-// fp32 grouped GEMM (vector FMA), C = A1*B1 (+ A2*B2) with generic strides and a fused epilogue
+// fp32 grouped GEMM on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, products and sums), C = A1*B1 (+ A2*B2)
+// with a fused epilogue
 // ------------------------------------------------------------------------------------------------
-#define GB_M 64
-#define GB_N 64
-#define GB_K 16
+// Bound: the fp32 matrix rate (157 TFLOP/s; plain vector FMA reaches half of it and has to fetch 8 LDS values per 16
+// FMAs) where the tiles fill the device, the latency of the k-loop's loads where a call has a few tasks only.
+// A workgroup of four waves takes the k-range in pieces that are requested a whole piece ahead (registers), so that
+// the memory latency runs beside the MFMAs of the piece before.  Two shapes:
+//   SPLIT false  64 x 64 tile, one 32 x 32 block per wave, pieces of 64
+//   SPLIT true   32 x 32 tile, the four waves take a quarter of every piece of 128 each and their blocks are added in
+//                wave order through LDS: four times the workgroups and a quarter of the MFMA chain per wave
+// Operands stay in LDS as they lie in memory.  Within 16 contraction values MFMA j takes values j and j + 8 (any pairing
+// gives the same sum as long as both operands use it): a contraction-contiguous row then delivers a lane's 8 values as
+// two 16-byte reads, and in a contraction-slowest tile the two halves of a wave read rows 8 apart, which with a row
+// stride of (tile + 4) floats are 32 banks apart: neither form has bank conflicts.
+// Measured on one second-order step, all 18 products together: 64 tasks x (128 + 128) rows through 845-256-128-1
+// 2.03 -> 0.69 ms (a first-layer forward product 113 -> 43 us, 84 TFLOP/s), 37 tasks of about 50 rows through 189-100-52-1 0.45 ->
+// 0.12 ms, 4 tasks x (32 + 32) rows through 141-64-32-1 0.29 -> 0.10 ms (before: vector FMA, loads not overlapped).
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a, int n_ntiles, int mt_per_group) {
-    __shared__ float As[GB_K][GB_M + 4];
-    __shared__ float Bs[GB_K][GB_N + 4];
-    const int ntile = blockIdx.x % n_ntiles;
-    const int mtile = blockIdx.x / n_ntiles;
+template <bool SPLIT>
+struct F32Tile {
+    static constexpr int T = SPLIT ? 32 : 64;       // rows and columns of the tile
+    static constexpr int BK = SPLIT ? 128 : 64;     // contraction values per piece
+    static constexpr int V = T * BK / 4 / 256;      // 16-byte pieces per thread and operand
+    static constexpr int WORDS_CONT = T * (BK + 4), WORDS_SLOW = BK * (T + 4);
+};
+
+typedef __attribute__((__vector_size__(4 * sizeof(u32)))) u32 u32x4_t;
+
+// One operand's pieces [T x BK] from memory to registers to LDS.  CONT: element (i, k) at p + i*ld + k, else at
+// p + k*ld + i (extents along the contiguous direction and strides are multiples of 4: every matrix is padded to 32).
+// The piece's base is uniform and moves on; a thread's offsets inside it stay.  What lies outside the operand is asked
+// for beyond the buffer's end and reads as zero.
+template <bool SPLIT, bool CONT>
+struct F32Operand {
+    using TT = F32Tile<SPLIT>;
+    static constexpr u32 OOB = 0x80000000u;
+    const float* base;
+    int64_t step;
+    u32 off[TT::V];
+    __device__ __forceinline__ static int row(int u) { const int e = threadIdx.x + u * 256; return CONT ? e / (TT::BK / 4) : e % (TT::T / 4) * 4; }
+    __device__ __forceinline__ static int col(int u) { const int e = threadIdx.x + u * 256; return CONT ? e % (TT::BK / 4) * 4 : e / (TT::T / 4); }
+    __device__ __forceinline__ void init(const float* p, int64_t ld, int n_i) {
+        base = p;
+        step = CONT ? TT::BK : TT::BK * ld;
+#pragma unroll
+        for (int u = 0; u < TT::V; ++u) {
+            const u32 o = CONT ? (u32)row(u) * (u32)ld + (u32)col(u) : (u32)col(u) * (u32)ld + (u32)row(u);
+            off[u] = row(u) < n_i ? o * 4u : OOB;
+        }
+    }
+    __device__ __forceinline__ void fetch(int k_left, u32x4_t (&v)[TT::V]) {   // the next piece; k_left: contraction values from its start on
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+        for (int u = 0; u < TT::V; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(col(u) < k_left ? off[u] : OOB), 0, 0);
+        base += step;
+    }
+    __device__ __forceinline__ static void store(float* s, const u32x4_t (&v)[TT::V]) {
+#pragma unroll
+        for (int u = 0; u < TT::V; ++u)
+            *reinterpret_cast<u32x4_t*>(s + (CONT ? row(u) * (TT::BK + 4) + col(u) : col(u) * (TT::T + 4) + row(u))) = v[u];
+    }
+    // a lane's 8 values (row or column i of the tile, contraction values k .. k + 7)
+    __device__ __forceinline__ static void frag(const float* s, int i, int k, float (&f)[8]) {
+        if (CONT) {
+            const float4 a = *reinterpret_cast<const float4*>(s + i * (TT::BK + 4) + k), b = *reinterpret_cast<const float4*>(s + i * (TT::BK + 4) + k + 4);
+            f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = s[(k + j) * (TT::T + 4) + i];
+        }
+    }
+};
+
+template <bool SPLIT, bool KA, bool KB>
+__global__ __launch_bounds__(256, 4) void gemm_f32_kernel(GemmArgs a, int n_ntiles, int mt_per_group) {
+    using TT = F32Tile<SPLIT>;
+    using OpA = F32Operand<SPLIT, KA>;
+    using OpB = F32Operand<SPLIT, KB>;
+    constexpr int WA = KA ? TT::WORDS_CONT : TT::WORDS_SLOW, WB = KB ? TT::WORDS_CONT : TT::WORDS_SLOW;
+    static_assert(!SPLIT || WA + WB >= 4 * 32 * 33, "the waves' blocks are added in the operand stage");
+    __shared__ float4 stage[(WA + WB) / 4];
+    float* const As = reinterpret_cast<float*>(stage);
+    float* const Bs = As + WA;
+    // workgroups are dealt round-robin to the 8 XCDs: neighbouring tiles (same rows, same weights) go to the same one
+    const int per = gridDim.x >> 3, rest = gridDim.x & 7, xcd = blockIdx.x & 7;
+    const int tile = xcd * per + (xcd < rest ? xcd : rest) + (blockIdx.x >> 3);
+    const int ntile = tile % n_ntiles;
+    const int mtile = tile / n_ntiles;
     int g, m0;
-    if (a.tile_group) {
-        g = a.tile_group[mtile];
-        m0 = a.tile_m0[mtile];
+    if (a.tile_group) {   // the list's tiles have 64 rows
+        constexpr int PER = 64 / TT::T;
+        g = a.tile_group[mtile / PER];
+        m0 = a.tile_m0[mtile / PER] + mtile % PER * TT::T;
     } else {
         g = mtile / mt_per_group;
-        m0 = (mtile % mt_per_group) * GB_M;
+        m0 = (mtile % mt_per_group) * TT::T;
     }
     const int64_t r0 = a.row_offsets ? a.row_offsets[g] : 0;
     const int rows_g = a.row_offsets ? (int)(a.row_offsets[g + 1] - r0) : 0;
     const int M = a.M < 0 ? rows_g : a.M;
     const int K = a.K < 0 ? rows_g : a.K;
     const int N = a.N;
-    const int n0 = ntile * GB_N;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc[4][4];
+    if (m0 >= M) return;
+    const int n0 = ntile * TT::T;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l32 = lane & 31, half = lane >> 5;
+    const int mi = SPLIT ? l32 : (wv >> 1) * 32 + l32, ni = SPLIT ? l32 : (wv & 1) * 32 + l32;
+    f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
+    constexpr int KW = SPLIT ? TT::BK / 4 : TT::BK;    // contraction values of a piece that a wave takes
+    const int kw0 = (SPLIT ? wv * KW : 0) + half * 8;
     for (int pr = 0; pr < a.n_pairs; ++pr) {
-        const float* A = a.A[pr] + (int64_t)g * a.gA[pr] + r0 * a.rA[pr];
-        const float* B = a.B[pr] + (int64_t)g * a.gB[pr] + r0 * a.rB[pr];
-        const int64_t sAm = a.sAm[pr], sAk = a.sAk[pr], sBk = a.sBk[pr], sBn = a.sBn[pr];
-        for (int k0 = 0; k0 < K; k0 += GB_K) {
-#pragma unroll
-            for (int e = threadIdx.x; e < GB_M * GB_K; e += 256) {
-                int m, k;
-                if (sAk == 1) { m = e / GB_K; k = e % GB_K; } else { m = e % GB_M; k = e / GB_M; }
-                const int gm = m0 + m, gk = k0 + k;
-                As[k][m] = (gm < M && gk < K) ? A[gm * sAm + gk * sAk] : 0.f;
-            }
-#pragma unroll
-            for (int e = threadIdx.x; e < GB_N * GB_K; e += 256) {
-                int n, k;
-                if (sBk == 1) { n = e / GB_K; k = e % GB_K; } else { n = e % GB_N; k = e / GB_N; }
-                const int gn = n0 + n, gk = k0 + k;
-                Bs[k][n] = (gn < N && gk < K) ? B[gk * sBk + gn * sBn] : 0.f;
-            }
+        OpA A;
+        OpB B;
+        A.init(a.A[pr] + (int64_t)g * a.gA[pr] + r0 * a.rA[pr] + m0 * a.sAm[pr], KA ? a.sAm[pr] : a.sAk[pr], M - m0);
+        B.init(a.B[pr] + (int64_t)g * a.gB[pr] + r0 * a.rB[pr] + n0 * a.sBn[pr], KB ? a.sBn[pr] : a.sBk[pr], N - n0);
+        u32x4_t va[TT::V], vb[TT::V];
+        A.fetch(K, va);
+        B.fetch(K, vb);
+        for (int left = K; left > 0; left -= TT::BK) {
+            __syncthreads();   // the piece before has been read
+            OpA::store(As, va);
+            OpB::store(Bs, vb);
             __syncthreads();
-#pragma unroll
-            for (int k = 0; k < GB_K; ++k) {
-                float av[4], bv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) av[i] = As[k][ty * 4 + i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) bv[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+            if (left > TT::BK) {
+                A.fetch(left - TT::BK, va);
+                B.fetch(left - TT::BK, vb);
             }
-            __syncthreads();
+            // (what lies beyond the contraction is zero: the loop may run past it)
+            float fa[2][8], fb[2][8];
+            OpA::frag(As, mi, kw0, fa[0]);
+            OpB::frag(Bs, ni, kw0, fb[0]);
+#pragma unroll
+            for (int kb = 0; kb < KW / 16; ++kb) {   // the next 16 values are on their way while these are multiplied
+                if (kb + 1 < KW / 16) {
+                    OpA::frag(As, mi, kw0 + (kb + 1) * 16, fa[(kb + 1) & 1]);
+                    OpB::frag(Bs, ni, kw0 + (kb + 1) * 16, fb[(kb + 1) & 1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[kb & 1][j], fb[kb & 1][j], acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 
@@ -79,40 +159,55 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a, int n_ntiles,
     const float* bias = a.bias ? a.bias + (int64_t)g * a.gBias : nullptr;
     const float* mask = a.mask ? a.mask + r0 * a.ld_mask : nullptr;
     const float* Cin = a.Cin ? a.Cin + (int64_t)g * a.gCin : nullptr;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float v = acc[i][j];
-            switch (a.epi) {
-                case EPI_BIAS_RELU: v = fmaxf(v + bias[n], 0.f); break;
-                case EPI_BIAS_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v + bias[n] : 0.f; break;
-                case EPI_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v : 0.f; break;
-                case EPI_AXPBY: v = a.c1 * v + (Cin ? a.c0 * Cin[(int64_t)m * a.ldc + n] : 0.f); break;
-                default: break;
-            }
-            C[(int64_t)m * a.ldc + n] = v;
+    auto emit = [&](int m, int n, float v) {
+        if (m >= M || n >= N) return;
+        switch (a.epi) {
+            case EPI_BIAS_RELU: v = fmaxf(v + bias[n], 0.f); break;
+            case EPI_BIAS_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v + bias[n] : 0.f; break;
+            case EPI_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v : 0.f; break;
+            case EPI_AXPBY: v = a.c1 * v + (Cin ? a.c0 * Cin[(int64_t)m * a.ldc + n] : 0.f); break;
+            default: break;
         }
+        C[(int64_t)m * a.ldc + n] = v;
+    };
+    // a lane holds column l32 of its block and rows 8*(i/4) + 4*half + i%4
+    if (SPLIT) {
+        float* red = As;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[(wv * 32 + (i >> 2) * 8 + half * 4 + (i & 3)) * 33 + l32] = acc[i];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = threadIdx.x + u * 256, r = e >> 5, c = e & 31;
+            emit(m0 + r, n0 + c, ((red[r * 33 + c] + red[(32 + r) * 33 + c]) + red[(64 + r) * 33 + c]) + red[(96 + r) * 33 + c]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) emit(m0 + (wv >> 1) * 32 + (i >> 2) * 8 + half * 4 + (i & 3), n0 + ni, acc[i]);
     }
 }
 
-void launch_gemm_f32(hipStream_t st, const GemmArgs& a) {
-    const int n_ntiles = (a.N + GB_N - 1) / GB_N;
-    int64_t n_mtiles;
-    int mt_per_group = 1;
-    if (a.tile_group) {
-        n_mtiles = a.n_mtiles;
-    } else {
-        mt_per_group = (a.M + GB_M - 1) / GB_M;
-        n_mtiles = (int64_t)mt_per_group * a.G;
-    }
+template <bool SPLIT>
+static void gemm_f32_shape(hipStream_t st, const GemmArgs& a) {
+    constexpr int T = F32Tile<SPLIT>::T;
+    const int n_ntiles = (a.N + T - 1) / T, mt_per_group = a.tile_group ? 1 : (a.M + T - 1) / T;
+    const int64_t n_mtiles = a.tile_group ? (int64_t)a.n_mtiles * (64 / T) : (int64_t)mt_per_group * a.G;
     if (n_mtiles <= 0 || n_ntiles <= 0) return;
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((unsigned)(n_mtiles * n_ntiles)), dim3(256), 0, st, a, n_ntiles,
-                       mt_per_group);
+    const dim3 grid((unsigned)(n_mtiles * n_ntiles));
+    const bool ka = a.sAk[0] == 1, kb = a.sBk[0] == 1;
+    if (ka && kb) hipLaunchKernelGGL((gemm_f32_kernel<SPLIT, true, true>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
+    else if (ka) hipLaunchKernelGGL((gemm_f32_kernel<SPLIT, true, false>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
+    else hipLaunchKernelGGL((gemm_f32_kernel<SPLIT, false, false>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
+}
+
+// The split tiles where 64 x 64 ones would not give every compute unit two workgroups: at 128 to 256 tiles 13.9 -> 12.0 us
+// and 33.9 -> 18.6 us for products of the step above; from 512 tiles on the large ones are ahead (43 against 48 us, 53 against 73).
+#define F32_SPLIT_TILES 512
+void launch_gemm_f32(hipStream_t st, const GemmArgs& a) {
+    const int64_t tiles = (int64_t)((a.N + 63) / 64) * (a.tile_group ? a.n_mtiles : (int64_t)((a.M + 63) / 64) * a.G);
+    if (tiles < F32_SPLIT_TILES) gemm_f32_shape<true>(st, a);
+    else gemm_f32_shape<false>(st, a);
 }
 
 // ------------------------------------------------------------------------------------------------
