@@ -295,13 +295,24 @@ void launch_gemm_bf16_bkmajor(hipStream_t st, const GemmBArgs& a, int bm, int bn
 void launch_convert_weights(hipStream_t st, const float* src, int64_t g_src, int G, int rows, int cols, bf16_t* w,
                             bf16_t* wT, int64_t g_dst);
 
-// out[g*g_out + n] = c0*in[g*g_in + n] + c1 * sum_{s in group g} (X1[s,n]*w1[s] + X2[s,n]*w2[s])
-void launch_task_colsum(hipStream_t st, int G, const int32_t* row_offsets, int N, const float* X1,
-                        const float* w1, const float* X2, const float* w2, int64_t ldx, float* out,
-                        int64_t g_out, const float* in, int64_t g_in, float c0, float c1);
-void launch_task_colsum_bf(hipStream_t st, int G, const int32_t* row_offsets, int N, const bf16_t* X1,
-                           const float* w1, const bf16_t* X2, const float* w2, int64_t ldx, float* out,
-                           int64_t g_out, const float* in, int64_t g_in, float c0, float c1);
+// out[g*g_out + n] = c0*in[g*g_in + n] + c1 * sum_{s in group g} (X1[s,n]*w1[s] + X2[s,n]*w2[s]), several such sums over
+// the same groups of rows at once.  N == 1: X1 is fp32 (no X2, no weights).  Otherwise N and ldx are multiples of 32, rows
+// are 16-byte aligned and of the launch's type.  G at most 32768.
+enum { COL_JOBS = 12 };   // sums per launch
+struct ColJob {
+    int N, block0;            // (block0 is set by the launcher)
+    const void* X1; const float* w1;   // w null: ones
+    const void* X2; const float* w2;   // X2 null: no second term
+    int64_t ldx;
+    float* out; int64_t g_out;
+    const float* in; int64_t g_in;     // null: nothing is added
+    float c0, c1;
+};
+struct ColJobs {
+    int n;
+    ColJob job[COL_JOBS];
+};
+void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offsets, const ColJob* list, int n);
 // z[s] = a[s,:].w_g + b_g (+ ta[s,:].w_g + a[s,:].tw_g + tb_g when tangent)
 struct LastFwdArgs {
     int64_t n; int N; int64_t ld;       // rows (padded), width of the last hidden layer, its leading dimension

@@ -971,23 +971,28 @@ static void dense_tn(gm_ctx* c, const Grp& g, int l, int np, const Act* a0, cons
     dense_tn_n(c, g, l, np, as, ds, out, in, in_stride, c0, c1, write_f32);
 }
 
-static void colsum(gm_ctx* c, const Grp& g, int N, const Act* X1, const float* w1, const Act* X2, const float* w2,
-                   float* out, int64_t g_out, const float* in, int64_t g_in, float c0, float c1) {
-    // algorithmic bytes: every operand row once (and its per-row weights), one output row per task (read back when updated)
-    Prof p(c, "task_colsum", (double)g.rows * N * (c->mlp_dtype ? 2.0 : 4.0) * (X2 ? 2 : 1) + 4.0 * g.rows * ((w1 ? 1 : 0) + (w2 ? 1 : 0)) +
-                                 4.0 * g.G * N * (in ? 2 : 1), 0);
-    if (c->mlp_dtype == 0)
-        launch_task_colsum(c->stream, g.G, g.row_off, N, X1->f, w1, X2 ? X2->f : nullptr, w2, X1->ld, out, g_out, in, g_in,
-                           c0, c1);
-    else
-        launch_task_colsum_bf(c->stream, g.G, g.row_off, N, X1->b, w1, X2 ? X2->b : nullptr, w2, X1->ld, out, g_out, in,
-                              g_in, c0, c1);
-}
-static void colsum_f32(gm_ctx* c, const Grp& g, int N, const float* X1, int64_t ldx, float* out, int64_t g_out,
-                       const float* in, int64_t g_in, float c0, float c1) {
-    Prof p(c, "task_colsum", 4.0 * g.rows * N + 4.0 * g.G * N * (in ? 2 : 1), 0);
-    launch_task_colsum(c->stream, g.G, g.row_off, N, X1, nullptr, nullptr, nullptr, ldx, out, g_out, in, g_in, c0, c1);
-}
+// The per-task column sums of one pass, collected and launched together.
+struct ColSums {
+    gm_ctx* c;
+    const Grp& g;
+    std::vector<ColJob> jobs;
+    double bytes = 0;   // algorithmic: every operand row once (and its per-row weights), one output row per task (read back when updated)
+    void add(int N, const Act* X1, const float* w1, const Act* X2, const float* w2, float* out, int64_t g_out, const float* in,
+             int64_t g_in, float c0, float c1) {
+        bytes += (double)g.rows * N * (c->mlp_dtype ? 2.0 : 4.0) * (X2 ? 2 : 1) + 4.0 * g.rows * ((w1 ? 1 : 0) + (w2 ? 1 : 0)) +
+                 4.0 * g.G * N * (in ? 2 : 1);
+        auto data = [&](const Act* x) { return c->mlp_dtype ? (const void*)x->b : (const void*)x->f; };
+        jobs.push_back(ColJob{N, 0, data(X1), w1, X2 ? data(X2) : nullptr, w2, X1->ld, out, g_out, in, g_in, c0, c1});
+    }
+    void add_scalar(const float* x, float* out, int64_t g_out, const float* in, int64_t g_in, float c0, float c1) {   // one value per row
+        bytes += 4.0 * g.rows + 4.0 * g.G * (in ? 2 : 1);
+        jobs.push_back(ColJob{1, 0, x, nullptr, nullptr, nullptr, 1, out, g_out, in, g_in, c0, c1});
+    }
+    void launch() {
+        Prof p(c, "task_colsum", bytes, 0);
+        launch_task_colsum(c->stream, c->mlp_dtype, g.G, g.row_off, jobs.data(), (int)jobs.size());
+    }
+};
 
 static const void* act_ptr(const gm_ctx* c, const Act& a) { return c->mlp_dtype ? (const void*)a.b : (const void*)a.f; }
 static void* act_ptr(const gm_ctx* c, Act& a) { return c->mlp_dtype ? (void*)a.b : (void*)a.f; }
@@ -1047,11 +1052,14 @@ static void forward_backward(gm_ctx* c, const Grp& g, const float* labels, const
 // gradients), one product per step accumulated in the matrix cores, from the shared fp32 theta: no per-task fp32
 // master of a weight matrix is written or read (it was most of what a step of small tasks moved); biases and the
 // last layer keep their per-task fp32 chain (in, in_stride).
+// loss / task_loss: the rows' losses, summed per task along with the rest.
 static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const float* in, int64_t in_stride, float c0,
                        float c1, float* wL_copy, bool write_f32 = true, const Grp* coarse = nullptr,
-                       Theta* coarse_out = nullptr, const std::vector<Pass>* hist = nullptr, const float* in0 = nullptr) {
+                       Theta* coarse_out = nullptr, const std::vector<Pass>* hist = nullptr, const float* in0 = nullptr,
+                       const float* loss = nullptr, float* task_loss = nullptr) {
     const int L = c->L;
     const int64_t nt = out.sf;
+    ColSums sums{c, g};
     for (int l = 1; l < L; ++l) {
         const Act* prev = l == 1 ? p.X : &(*p.A)[l - 1];
         if (coarse) dense_tn(c, *coarse, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, *coarse_out, nullptr, 0, 0.f, c1);
@@ -1065,13 +1073,14 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
             }
             dense_tn_n(c, g, l, np, as, ds, out, in0, 0, c0, c1, false);
         } else dense_tn(c, g, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, out, in, in_stride, c0, c1, write_f32);
-        colsum(c, g, c->ld[l], &(*p.Dl)[l], nullptr, nullptr, nullptr, out.f + c->offb[l], nt, in ? in + c->offb[l] : nullptr,
-               in_stride, c0, c1);
+        sums.add(c->ld[l], &(*p.Dl)[l], nullptr, nullptr, nullptr, out.f + c->offb[l], nt, in ? in + c->offb[l] : nullptr,
+                 in_stride, c0, c1);
     }
     const Act* prev = L == 1 ? p.X : &(*p.A)[L - 1];
-    colsum(c, g, c->ld[L - 1], prev, p.dL, nullptr, nullptr, out.f + c->offW[L], nt, in ? in + c->offW[L] : nullptr,
-           in_stride, c0, c1);
-    colsum_f32(c, g, 1, p.dL, 1, out.f + c->offb[L], nt, in ? in + c->offb[L] : nullptr, in_stride, c0, c1);
+    sums.add(c->ld[L - 1], prev, p.dL, nullptr, nullptr, out.f + c->offW[L], nt, in ? in + c->offW[L] : nullptr, in_stride, c0, c1);
+    sums.add_scalar(p.dL, out.f + c->offb[L], nt, in ? in + c->offb[L] : nullptr, in_stride, c0, c1);
+    if (loss) sums.add_scalar(loss, task_loss, 1, nullptr, 0, 0.f, 1.f);
+    sums.launch();
     if (wL_copy)
         (void)hipMemcpy2DAsync(wL_copy, c->ld[L - 1] * sizeof(float), out.f + c->offW[L], nt * sizeof(float),
                                c->ld[L - 1] * sizeof(float), g.G, hipMemcpyDeviceToDevice, c->stream);
@@ -1119,8 +1128,9 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
             launch_last_bwd(st, c->mlp_dtype, g.rows, c->ld[L - 1], c->ld[L - 1], c->ld[L - 1], g.row_task, w.tdL, s.wL,
                             s.wL_stride, s.dL, vwL, nt, act_ptr(c, s.A[L - 1]), act_ptr(c, w.TD[L - 1]), nullptr);
     }
-    colsum(c, g, c->ld[L - 1], tprev, s.dL, prev, w.tdL, v.f + c->offW[L], nt, v.f + c->offW[L], nt, 1.f, -alpha);
-    colsum_f32(c, g, 1, w.tdL, 1, v.f + c->offb[L], nt, v.f + c->offb[L], nt, 1.f, -alpha);
+    ColSums sums{c, g};   // (biases and the last layer's direction: nothing below reads them)
+    sums.add(c->ld[L - 1], tprev, s.dL, prev, w.tdL, v.f + c->offW[L], nt, v.f + c->offW[L], nt, 1.f, -alpha);
+    sums.add_scalar(w.tdL, v.f + c->offb[L], nt, v.f + c->offb[L], nt, 1.f, -alpha);
     Theta vout = v;
     if (!refresh_v_copies) vout.b = nullptr;
     for (int l = L - 1; l >= 1; --l) {
@@ -1133,8 +1143,9 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
             else dense_tn(c, *coarse, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], w.vsum, nullptr, 0, 0.f, 1.f);
         } else if (l == 1 && !tx) dense_tn(c, g, l, 1, a_prev, &w.TD[l], nullptr, nullptr, vout, v.f, nt, 1.f, -alpha);
         else dense_tn(c, g, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], vout, v.f, nt, 1.f, -alpha);
-        colsum(c, g, c->ld[l], &w.TD[l], nullptr, nullptr, nullptr, v.f + c->offb[l], nt, v.f + c->offb[l], nt, 1.f, -alpha);
+        sums.add(c->ld[l], &w.TD[l], nullptr, nullptr, nullptr, v.f + c->offb[l], nt, v.f + c->offb[l], nt, 1.f, -alpha);
     }
+    sums.launch();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2019,15 +2030,14 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         if (table && FD > 0 && !gxs_self_init) launch_fill_f32(st, w.GX, d.Ps * (int64_t)FD, 0.f);
         Pass pq{&Xq, &w.Aq, &w.Dq, w.dLq, w.zq};
         forward_backward(c, gq, labels_q, pq, th, thf, thf_stride, w.loss_q, F > 0 ? gxq : nullptr);
-        colsum_f32(c, gq, 1, w.loss_q, 1, task_loss + wp.t0, 1, nullptr, 0, 0.f, 1.f);
         // The query gradient w.r.t. theta' per task starts the second-order chain; without a chain it is only summed
         // over the tasks, so it is taken over runs of tasks straight away.
         const int n_coarse = coarse_group_count(c, Tw, std::min(d.Ps, d.Pq));
         Grp gs_coarse = gs, gq_coarse = gq;
         gs_coarse.row_off = w.coarse_off_s; gs_coarse.G = n_coarse;
         gq_coarse.row_off = w.coarse_off_q; gq_coarse.G = n_coarse;
-        if (second) theta_grad(c, gq, pq, w.v, nullptr, 0, 0.f, 1.f, nullptr);
-        else theta_grad(c, gq, pq, w.v, nullptr, 0, 0.f, 1.f, nullptr, true, &gq_coarse, &w.vsum);
+        theta_grad(c, gq, pq, w.v, nullptr, 0, 0.f, 1.f, nullptr, true, second ? nullptr : &gq_coarse, second ? nullptr : &w.vsum,
+                   nullptr, nullptr, w.loss_q, task_loss + wp.t0);
 
         // second-order chain back through the inner steps: v_k = v_{k+1} - alpha H_k v_{k+1}
         if (second) {
