@@ -17,22 +17,44 @@ __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(
 // ------------------------------------------------------------------------------------------------
 // prefetch + sum pooling: x[s, f*D:(f+1)*D] = sum over bag(s,f) of emb[field_base[f] + index]
 // ------------------------------------------------------------------------------------------------
-__global__ void gather_pool_kernel(int F, int D, int LG, const int64_t* __restrict__ field_base,
-                                   const int64_t* __restrict__ bag_offsets, const int32_t* __restrict__ indices,
-                                   const float* __restrict__ emb, int64_t sample0, int64_t n_bags,
-                                   const int32_t* __restrict__ row_map, int32_t row_base, float* x, int ldx,
-                                   bf16_t* x_bf) {
+// One launch takes both sets: sample u of the launch is sample u of the first set or u - n0 of the second, and the last
+// blocks write the dense features and the zero padding behind the pooled fields.
+struct PoolArgs {
+    int F, D, LG, n_dense, ldx;
+    unsigned pool_blocks;
+    const int64_t* field_base;
+    const float4* emb;
+    PoolSet set[2];
+};
+
+__device__ __forceinline__ void pool_tail(const PoolArgs& a) {
+    const int FD = a.F * a.D, tail = a.ldx - FD;
+    const int64_t i = (int64_t)(blockIdx.x - a.pool_blocks) * blockDim.x + threadIdx.x, n0 = a.set[0].n_samples;
+    if (i >= (n0 + a.set[1].n_samples) * tail) return;
+    int64_t s = i / tail;
+    const int c = (int)(i - s * tail);
+    const PoolSet& S = a.set[s >= n0];
+    if (s >= n0) s -= n0;
+    const float v = (S.dense && c < a.n_dense) ? S.dense[(S.sample0 + s) * a.n_dense + c] : 0.f;
+    const int64_t o = (int64_t)(S.row_map[s] - S.row_base) * a.ldx + FD + c;
+    if (S.x) S.x[o] = v;
+    if (S.x_bf) S.x_bf[o] = f2bf(v);
+}
+
+__global__ __launch_bounds__(256) void gather_pool_kernel(PoolArgs a) {
+    if (blockIdx.x >= a.pool_blocks) { pool_tail(a); return; }
+    const int LG = a.LG, F = a.F;
     const int groups_per_block = blockDim.x / LG;
     const int g_in_block = threadIdx.x / LG, l = threadIdx.x % LG;
-    if (g_in_block >= groups_per_block) return;
-    const int64_t n_groups = (int64_t)gridDim.x * groups_per_block;
-    const float4* emb4 = reinterpret_cast<const float4*>(emb);
+    const int64_t n_groups = (int64_t)a.pool_blocks * groups_per_block, n0 = a.set[0].n_samples, n_bags = (n0 + a.set[1].n_samples) * F;
     for (int64_t bag = (int64_t)blockIdx.x * groups_per_block + g_in_block; bag < n_bags; bag += n_groups) {
-        const int64_t s = bag / F;
+        int64_t s = bag / F;
         const int f = (int)(bag - s * F);
-        const int64_t gb = sample0 * F + bag;
-        const int64_t p0 = bag_offsets[gb], p1 = bag_offsets[gb + 1];
-        const int64_t fb = field_base[f];
+        const PoolSet& S = a.set[s >= n0];
+        if (s >= n0) s -= n0;
+        const int64_t gb = (S.sample0 + s) * F + f;
+        const int64_t p0 = S.bag_offsets[gb], p1 = S.bag_offsets[gb + 1];
+        const int64_t fb = a.field_base[f];
         // the order of the sums is gather_pool_xcd_kernel's, bit for bit: eight lookups at a time, the first four into
         // one chain and the next four into the other (one chain when a lane group is narrower than eight lanes)
         float4 acc0 = make_float4(0.f, 0.f, 0.f, 0.f), acc1 = acc0;
@@ -40,15 +62,15 @@ __global__ void gather_pool_kernel(int F, int D, int LG, const int64_t* __restri
         for (int64_t p = p0; p < p1; p += 8) {
             float4 v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = p + j < p1 ? emb4[(fb + indices[p + j]) * LG + l] : zero;
+            for (int j = 0; j < 8; ++j) v[j] = p + j < p1 ? a.emb[(fb + S.indices[p + j]) * LG + l] : zero;
             acc0 = add4(add4(add4(add4(acc0, v[0]), v[1]), v[2]), v[3]);
             if (LG >= 8) acc1 = add4(add4(add4(add4(acc1, v[4]), v[5]), v[6]), v[7]);
             else acc0 = add4(add4(add4(add4(acc0, v[4]), v[5]), v[6]), v[7]);
         }
         const float4 acc = add4(acc0, acc1);
-        const int64_t o = (int64_t)(row_map[s] - row_base) * ldx + (int64_t)f * D + l * 4;
-        if (x) *reinterpret_cast<float4*>(x + o) = acc;
-        if (x_bf) store_bf4(x_bf + o, acc);
+        const int64_t o = (int64_t)(S.row_map[s] - S.row_base) * a.ldx + (int64_t)f * a.D + l * 4;
+        if (S.x) *reinterpret_cast<float4*>(S.x + o) = acc;
+        if (S.x_bf) store_bf4(S.x_bf + o, acc);
     }
 }
 
@@ -60,46 +82,49 @@ __global__ void gather_pool_kernel(int F, int D, int LG, const int64_t* __restri
 // this kernel is bound by.  (The lookups of a bag are summed in two interleaved chains of four, a fixed order.)  Indices
 // and the fp32 outputs stream past once: they are read and written with the non-temporal hint, which leaves L2 to the
 // rows (measured: 2-3 %; whether all XCDs sweep one field range together or each its own eighth makes no difference).
-__global__ void gather_pool_xcd_kernel(int F, int D, int LG, const int64_t* __restrict__ field_base,
-                                       const int64_t* __restrict__ bag_offsets, const int32_t* __restrict__ indices,
-                                       const float* __restrict__ emb, int64_t sample0, int64_t n_samples,
-                                       const int32_t* __restrict__ row_map, int32_t row_base, float* x, int ldx,
-                                       bf16_t* x_bf) {
+// A field's support and query samples follow each other, so that its rows are fetched for both sets at once.
+// Measured: 201 tasks of about (150 + 243) samples x 26 fields, bags of 1..20, 0.67 ms in two launches -> 0.63 ms; 128 tasks x (512 + 512)
+// samples x 64 fields, bags of 1..32, 3.63 -> 3.62 ms, 9.8 TB/s of rows.
+__global__ __launch_bounds__(256) void gather_pool_xcd_kernel(PoolArgs a) {
+    if (blockIdx.x >= a.pool_blocks) { pool_tail(a); return; }
+    const int LG = a.LG, F = a.F;
     const int groups_per_block = blockDim.x / LG;
     const int g_in_block = threadIdx.x / LG, l = threadIdx.x % LG;
-    if (g_in_block >= groups_per_block) return;
-    const int xcd = blockIdx.x & 7, bi = blockIdx.x >> 3, nbx = gridDim.x >> 3;
-    const float4* emb4 = reinterpret_cast<const float4*>(emb);
-    // work items of this XCD: pairs [lo, hi) of the field-major list (pair = field * n_samples + sample)
-    const int64_t n_pairs = n_samples * F;
-    const int64_t lo = n_pairs * xcd / 8, hi = n_pairs * (xcd + 1) / 8;
-    const int64_t stride = (int64_t)nbx * groups_per_block;
+    const int xcd = blockIdx.x & 7, bi = blockIdx.x >> 3, nbx = a.pool_blocks >> 3;
+    // work items of this XCD: pairs [lo, hi) of the field-major list (pair = field * samples + sample; fewer than 2^32)
+    const u32 n0 = (u32)a.set[0].n_samples, n = n0 + (u32)a.set[1].n_samples;
+    const int64_t n_pairs = (int64_t)n * F;
+    const int64_t hi = n_pairs * (xcd + 1) / 8, stride = (int64_t)nbx * groups_per_block;
+    int64_t it = n_pairs * xcd / 8 + (int64_t)bi * groups_per_block + g_in_block;
+    if (it >= hi) return;
+    int f = (int)(it / n);
+    u32 u = (u32)(it - (int64_t)f * n);
     // A bag is a chain of dependent reads (offsets -> indices -> rows).  The chain of the NEXT bag is started before
     // the rows of this one are summed: its offsets and its first LG indices (one per lane of the group, handed round
     // by lane shuffles) are in registers when its turn comes, and up to 8 row reads are in flight per lane.
-    int64_t it = lo + (int64_t)bi * groups_per_block + g_in_block;
-    int64_t p0 = 0, p1 = 0;
-    int32_t idx_l = 0;
-    if (it < hi) {
-        const int f = (int)(it / n_samples);
-        const int64_t gb = (sample0 + (it - (int64_t)f * n_samples)) * F + f;
-        p0 = bag_offsets[gb]; p1 = bag_offsets[gb + 1];
-        if (p0 + l < p1) idx_l = __builtin_nontemporal_load(indices + p0 + l);
-    }
-    for (; it < hi; it += stride) {
-        const int f = (int)(it / n_samples);
-        const int64_t s = it - (int64_t)f * n_samples;
-        const int64_t fb = field_base[f];
+    int64_t p0, p1;
+    int32_t idx_l;
+    auto open_bag = [&](int bf, u32 bu) {
+        const bool second = bu >= n0;
+        const int64_t* bo = second ? a.set[1].bag_offsets : a.set[0].bag_offsets;
+        const int32_t* ix = second ? a.set[1].indices : a.set[0].indices;
+        const int64_t gb = ((second ? a.set[1].sample0 - n0 : a.set[0].sample0) + bu) * F + bf;
+        p0 = bo[gb]; p1 = bo[gb + 1];
+        idx_l = (p0 + l < p1) ? __builtin_nontemporal_load(ix + p0 + l) : 0;
+    };
+    open_bag(f, u);
+    while (true) {
+        const bool second = u >= n0;
+        const int32_t* indices = second ? a.set[1].indices : a.set[0].indices;
+        const int64_t fb = a.field_base[f];
         const int64_t c0 = p0, c1 = p1;
         int32_t cur_idx = idx_l;
         // next bag's offsets and first indices
-        const int64_t itn = it + stride;
-        if (itn < hi) {
-            const int fn = (int)(itn / n_samples);
-            const int64_t gbn = (sample0 + (itn - (int64_t)fn * n_samples)) * F + fn;
-            p0 = bag_offsets[gbn]; p1 = bag_offsets[gbn + 1];
-            idx_l = (p0 + l < p1) ? __builtin_nontemporal_load(indices + p0 + l) : 0;
-        }
+        it += stride;
+        int fn = f;
+        int64_t un = (int64_t)u + stride;
+        while (un >= (int64_t)n) { un -= n; ++fn; }
+        if (it < hi) open_bag(fn, (u32)un);
         float4 acc0 = make_float4(0.f, 0.f, 0.f, 0.f), acc1 = acc0;
         for (int64_t base = c0; base < c1; base += LG) {
             if (base > c0) cur_idx = (base + l < c1) ? __builtin_nontemporal_load(indices + base + l) : 0;
@@ -110,35 +135,27 @@ __global__ void gather_pool_xcd_kernel(int F, int D, int LG, const int64_t* __re
                 for (int j = 0; j < 8; ++j) {
                     const int jj = j0 + j;
                     const int32_t r = __shfl(cur_idx, jj < LG ? jj : 0, LG);
-                    v[j] = jj < m ? emb4[(fb + r) * LG + l] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    v[j] = jj < m ? a.emb[(fb + r) * LG + l] : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
                 acc0 = add4(add4(add4(add4(acc0, v[0]), v[1]), v[2]), v[3]);
                 acc1 = add4(add4(add4(add4(acc1, v[4]), v[5]), v[6]), v[7]);
             }
         }
         const float4 acc = add4(acc0, acc1);
-        const int64_t o = (int64_t)(row_map[s] - row_base) * ldx + (int64_t)f * D + l * 4;
+        const u32 s = second ? u - n0 : u;
+        const int32_t row = second ? a.set[1].row_map[s] - a.set[1].row_base : a.set[0].row_map[s] - a.set[0].row_base;
+        const int64_t o = (int64_t)row * a.ldx + (int64_t)f * a.D + l * 4;
+        float* x = second ? a.set[1].x : a.set[0].x;
+        bf16_t* x_bf = second ? a.set[1].x_bf : a.set[0].x_bf;
         if (x) {
             __builtin_nontemporal_store(acc.x, x + o); __builtin_nontemporal_store(acc.y, x + o + 1);
             __builtin_nontemporal_store(acc.z, x + o + 2); __builtin_nontemporal_store(acc.w, x + o + 3);
         }
         if (x_bf) store_bf4(x_bf + o, acc);
+        if (it >= hi) break;
+        f = fn;
+        u = (u32)un;
     }
-}
-
-// dense features and zero padding behind the pooled fields
-__global__ void dense_tail_kernel(int FD, int n_dense, const float* __restrict__ dense, int64_t sample0,
-                                  int64_t n_samples, const int32_t* __restrict__ row_map, int32_t row_base, float* x,
-                                  int ldx, bf16_t* x_bf) {
-    const int tail = ldx - FD;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_samples * tail) return;
-    const int64_t s = i / tail;
-    const int c = (int)(i - s * tail);
-    const float v = (dense && c < n_dense) ? dense[(sample0 + s) * n_dense + c] : 0.f;
-    const int64_t o = (int64_t)(row_map[s] - row_base) * ldx + FD + c;
-    if (x) x[o] = v;
-    if (x_bf) x_bf[o] = f2bf(v);
 }
 
 static inline unsigned pool_grid(int64_t n_bags, int groups_per_block) {
@@ -149,24 +166,16 @@ static inline unsigned pool_grid(int64_t n_bags, int groups_per_block) {
     return (unsigned)nb;
 }
 
-void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t* field_base,
-                        const int64_t* bag_offsets, const int32_t* indices, const float* dense, const float* emb,
-                        int64_t sample0, int64_t n_samples, const int32_t* row_map, int32_t row_base, float* x, int ldx,
-                        bf16_t* x_bf) {
-    if (n_samples <= 0) return;
-    const int LG = D / 4;
-    const int64_t n_bags = n_samples * F;
-    if (n_bags > 0 && F >= 8 && n_bags >= (1 << 14)) {
-        const unsigned grid = pool_grid(n_bags, 256 / LG) / 8 * 8;
-        hipLaunchKernelGGL(gather_pool_xcd_kernel, dim3(grid), dim3(256), 0, st, F, D, LG, field_base, bag_offsets,
-                           indices, emb, sample0, n_samples, row_map, row_base, x, ldx, x_bf);
-    } else if (n_bags > 0)
-        hipLaunchKernelGGL(gather_pool_kernel, dim3(pool_grid(n_bags, 256 / LG)), dim3(256), 0, st, F, D, LG, field_base,
-                           bag_offsets, indices, emb, sample0, n_bags, row_map, row_base, x, ldx, x_bf);
-    const int64_t nt = n_samples * (ldx - F * D);
-    if (nt > 0)
-        hipLaunchKernelGGL(dense_tail_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, F * D, n_dense, dense,
-                           sample0, n_samples, row_map, row_base, x, ldx, x_bf);
+void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t* field_base, const float* emb, int ldx,
+                        const PoolSet& s0, const PoolSet& s1) {
+    const int64_t n = s0.n_samples + s1.n_samples, n_bags = n * F;
+    if (n <= 0) return;
+    PoolArgs a{F, D, F > 0 ? D / 4 : 1, n_dense, ldx, 0, field_base, reinterpret_cast<const float4*>(emb), {s0, s1}};
+    const bool by_xcd = n_bags > 0 && F >= 8 && n_bags >= (1 << 14);
+    if (n_bags > 0) a.pool_blocks = by_xcd ? pool_grid(n_bags, 256 / a.LG) / 8 * 8 : pool_grid(n_bags, 256 / a.LG);
+    const unsigned grid = a.pool_blocks + (unsigned)((n * (ldx - F * D) + 255) / 256);
+    if (by_xcd) hipLaunchKernelGGL(gather_pool_xcd_kernel, dim3(grid), dim3(256), 0, st, a);
+    else if (grid > 0) hipLaunchKernelGGL(gather_pool_kernel, dim3(grid), dim3(256), 0, st, a);
 }
 
 // dense and pad columns of every (padded) row: copied from x_base, or zero

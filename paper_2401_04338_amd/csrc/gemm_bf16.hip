@@ -651,36 +651,3 @@ void launch_gemm_bf16_timed(hipStream_t st, const GemmBArgs& a, bool kb) {   // 
     else launch_pipe<false, false, EPI_MASK | EP_CB, true>(st, a);
 }
 #endif
-
-// fp32 padded weights [rows, cols] -> bf16 W [rows, cols] and W^T [cols, rows], per group
-__global__ void convert_weights_kernel(const float* __restrict__ src, int64_t g_src, int rows, int cols, bf16_t* w,
-                                       bf16_t* wT, int64_t g_dst) {
-    __shared__ float tile[32][33];
-    const int g = blockIdx.z;
-    const float* s = src + (int64_t)g * g_src;
-    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 256 threads: 8 rows at a time
-    for (int i = ty; i < 32; i += 8) {
-        const int r = r0 + i, c = c0 + tx;
-        const float v = (r < rows && c < cols) ? s[(int64_t)r * cols + c] : 0.f;
-        tile[i][tx] = v;
-        if (w && r < rows && c < cols) w[(int64_t)g * g_dst + (int64_t)r * cols + c] = f2bf(v);
-    }
-    __syncthreads();
-    if (!wT) return;
-    for (int i = ty; i < 32; i += 8) {
-        const int c = c0 + i, r = r0 + tx;
-        if (c < cols && r < rows) wT[(int64_t)g * g_dst + (int64_t)c * rows + r] = f2bf(tile[tx][i]);
-    }
-}
-
-void launch_convert_weights(hipStream_t st, const float* src, int64_t g_src, int G, int rows, int cols, bf16_t* w,
-                            bf16_t* wT, int64_t g_dst) {
-    if (G <= 0 || rows <= 0 || cols <= 0) return;
-    for (int g0 = 0; g0 < G; g0 += 32768) {
-        const int gc = (G - g0) < 32768 ? (G - g0) : 32768;
-        hipLaunchKernelGGL(convert_weights_kernel, dim3((cols + 31) / 32, (rows + 31) / 32, gc), dim3(256), 0, st,
-                           src + (int64_t)g0 * g_src, g_src, rows, cols, w ? w + (int64_t)g0 * g_dst : nullptr,
-                           wT ? wT + (int64_t)g0 * g_dst : nullptr, g_dst);
-    }
-}

@@ -35,12 +35,13 @@ struct SetView {
     int64_t n_samples;           // samples of the whole set
 };
 
-// uniform_rows: the number of rows every table has, or -1 when the tables differ in size
+// (clears the status words first.)  uniform_rows: the number of rows every table has, or -1 when the tables differ in size
 void launch_tf_count(hipStream_t st, int F, int t0, int Tw, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status);
 void launch_scan_u32(hipStream_t st, const u32* in, u32* out, int64_t n, u32* tmp /* >= n/1024+2048 */,
                      u32* total /* may be null */);
 size_t scan_tmp_words(int64_t n);
+void launch_scan_u32_pair(hipStream_t st, const u32* in0, u32* out0, const u32* in1, u32* out1, int64_t n, u32* tmp);   // two scans of one length
 
 struct TfSortArgs {
     int F, t0, Tw;
@@ -145,10 +146,16 @@ void launch_segments(hipStream_t st, const u32* sorted_keys, int64_t n, u32* fla
                      int64_t capacity, int64_t* n_rows_out, u32* status);
 
 // ------------------------------------------------------------------ embedding kernels
-void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t* field_base,
-                        const int64_t* bag_offsets, const int32_t* indices, const float* dense,
-                        const float* emb, int64_t sample0, int64_t n_samples, const int32_t* row_map,
-                        int32_t row_base, float* x /* may be null */, int ldx, bf16_t* x_bf /* may be null */);
+struct PoolSet {
+    const int64_t* bag_offsets; const int32_t* indices; const float* dense;   // the whole set's
+    int64_t sample0, n_samples;     // samples [sample0, sample0 + n_samples) are pooled
+    const int32_t* row_map; int32_t row_base;   // x row of each of them: row_map[i] - row_base
+    float* x;                       // null: only x_bf
+    bf16_t* x_bf;                   // null: only x
+};
+// pooled fields, dense features and zero padding of every sample of two sets, one launch
+void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t* field_base, const float* emb, int ldx,
+                        const PoolSet& s0, const PoolSet& s1);
 // Two-hop row arithmetic per (task, field): G[slot] = sum of Z over the slot's lookups (hop 1), then
 // y_out[bag] = y_in[bag] + c * sum over the bag's lookups of G[slot] (hop 2), for up to two sets of bags.
 struct TwoHopOut {
@@ -292,8 +299,6 @@ void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn = 128);
 void launch_gemm_bf16_kmajor(hipStream_t st, const GemmBArgs& a, int tile = 128);   // tile: 128, or 256 (N % 256 == 0)
 // A contraction-contiguous as in launch_gemm_bf16, B stored contraction-slowest (element (k, n) at ... + k*ldb + n)
 void launch_gemm_bf16_bkmajor(hipStream_t st, const GemmBArgs& a, int bm, int bn = 128);
-void launch_convert_weights(hipStream_t st, const float* src, int64_t g_src, int G, int rows, int cols, bf16_t* w,
-                            bf16_t* wT, int64_t g_dst);
 
 // out[g*g_out + n] = c0*in[g*g_in + n] + c1 * sum_{s in group g} (X1[s,n]*w1[s] + X2[s,n]*w2[s]), several such sums over
 // the same groups of rows at once.  N == 1: X1 is fp32 (no X2, no weights).  Otherwise N and ldx are multiples of 32, rows
@@ -313,34 +318,73 @@ struct ColJobs {
     ColJob job[COL_JOBS];
 };
 void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offsets, const ColJob* list, int n);
-// z[s] = a[s,:].w_g + b_g (+ ta[s,:].w_g + a[s,:].tw_g + tb_g when tangent)
-struct LastFwdArgs {
+// z[s] = a[s,:].w_g + b_g (+ ta[s,:].w_g + a[s,:].tw_g + tb_g when tangent); widths and strides are multiples of 32
+struct LastArgs {
     int64_t n; int N; int64_t ld;       // rows (padded), width of the last hidden layer, its leading dimension
-    int bf16;                           // activations a / ta are bf16 (else fp32)
+    int bf16;                           // activations a / ta and d are bf16 (else fp32)
     const int32_t* row_task;            // [n] task of every row
     const int32_t* row_offsets;         // [G+1] first (padded) row of each task
     const int32_t* real_offsets;        // [G+1] first sample of each task (labels are indexed by sample)
     const void* a; const void* ta;      // ta null: plain forward
     const float* w; int64_t gW; const float* b;      // w + g*gW [N], b + g*gW scalar
     const float* tw; int64_t gTW; const float* tb;
-    const float* labels; const float* z_in;          // tangent: z of the primal pass
+    const float* labels; const float *z_in, *delta_in;   // tangent: z and delta of the primal pass
     float* z_out; float* delta_out; float* loss_out; // plain: z, (sigma-y)/N_g, bce/N_g
                                                      // tangent: delta_out = sigma'(z) * tz / N_g
+    void* d;   // null, or the delta of the last hidden layer: (delta_out*w (+ delta_in*tw)) * (a > 0)
 };
-void launch_last_fwd(hipStream_t st, const LastFwdArgs& a);
-void launch_last_bwd(hipStream_t st, int bf16, int64_t n, int N, int64_t ld_a, int64_t ld_d, const int32_t* row_task,
-                     const float* dl, const float* w, int64_t gW, const float* dl2, const float* w2, int64_t gW2,
-                     const void* act, void* d, float* d_f32);
-void launch_reduce_tasks(hipStream_t st, const float* v, int64_t ld, int G, int64_t n, float* out, int accumulate,
-                         float scale = 1.f);
-void launch_fill_sample_task(hipStream_t st, const int32_t* row_offsets, int G, int32_t* sample_task);
-void launch_pack_weights(hipStream_t st, const float* W, int din, int dout, int ld_in, int ld_out, float* dst);
-void launch_unpack_weights(hipStream_t st, const float* src, int din, int dout, int ld_out, float* W);
+void launch_last_layer(hipStream_t st, const LastArgs& a);
+void launch_input_delta(hipStream_t st, int64_t n, int N, const int32_t* row_task, const float* dl, const float* w, int64_t gW,
+                        const float* dl2, const float* w2, int64_t gW2, float* d);
+enum { REDUCE_PIECES = 16 };   // pieces of theta per launch
+struct ReducePiece {
+    int64_t j0, n;    // theta[j0 .. j0 + n), multiples of 32
+    int G, Gsum;      // rows of v / of vsum that are added
+    int block0;       // set by the launcher
+};
+struct ReduceArgs {
+    const float *v, *vsum;
+    int64_t ld;       // of both
+    float scale;      // of vsum's sum
+    float* out; int accumulate;
+    int n;            // (n and piece are set by the launcher)
+    ReducePiece piece[REDUCE_PIECES];
+};
+void launch_reduce_tasks(hipStream_t st, const ReduceArgs& base, const ReducePiece* list, int n);
+struct ExpandJob {
+    const int64_t* off64;    // [G+1] one of the two
+    const int32_t* off32;
+    const int32_t* first;    // [G] or null
+    int32_t* out;
+};
+struct ExpandJobs { int n; ExpandJob job[4]; };
+void launch_expand_tasks(hipStream_t st, int G, const ExpandJobs& jobs);
+enum { MATRIX_JOBS = 12 };   // matrices per launch
+struct MatrixJob {
+    const float* src; int src_rows, src_cols, ld_src;
+    float* dst; bf16_t* dst_bf; int rows, cols, ld_dst;   // dst_bf may be null
+    int block0;              // set by the launcher
+};
+struct MatrixJobs { int n; MatrixJob job[MATRIX_JOBS]; };
+void launch_copy_matrices(hipStream_t st, const MatrixJob* list, int n);
 void launch_axpy(hipStream_t st, int64_t n, float a, const float* x, float* y);  // y += a*x
 void launch_axpy_clear(hipStream_t st, int64_t n, float a, float* x, float* y);  // y += a*x, x = 0 (n % 4 == 0, 16-byte aligned)
 void launch_sum_to_scalar(hipStream_t st, const float* x, int n, float* out, int accumulate);
 void launch_fill_u32(hipStream_t st, u32* p, int64_t n, u32 v);
 void launch_fill_f32(hipStream_t st, float* p, int64_t n, float v);
+enum { ZERO_JOBS = 4 };
+struct ZeroJobs { int n; u32* p[ZERO_JOBS]; int64_t words[ZERO_JOBS]; };
+void launch_zero(hipStream_t st, const ZeroJobs& z);   // several arrays in one launch
+// zeroes the pad rows of row-padded buffers: rows [off[g] + real rows of g, off[g + 1]) of every task g
+enum { PAD_JOBS = 8 };
+struct PadJobs {
+    int n;
+    char* p[PAD_JOBS];
+    int row_bytes[PAD_JOBS];   // multiples of 64
+    int set[PAD_JOBS];         // which set's rows
+    const int32_t *off[2], *real[2];   // [G + 1] first padded row / first sample of each task, per set
+};
+void launch_zero_pad_rows(hipStream_t st, int G, const PadJobs& z);
 
 // ------------------------------------------------------------------ on-box ceilings (measurement only)
 void launch_stream_copy(hipStream_t st, const void* src, void* dst, int64_t bytes);

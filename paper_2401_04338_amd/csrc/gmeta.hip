@@ -345,14 +345,21 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.row_off_q = ar.get<int32_t>(d.Tw + 1);
     w.real_off_s = ar.get<int32_t>(d.Tw + 1);
     w.real_off_q = ar.get<int32_t>(d.Tw + 1);
-    w.sample_task_s = ar.get<int32_t>(d.Ss + 1);
-    w.sample_task_q = ar.get<int32_t>(d.Sq + 1);
-    w.row_task_s = ar.get<int32_t>(d.Ps + 1);
-    w.row_task_q = ar.get<int32_t>(d.Pq + 1);
     w.tile_g_s = ar.get<int32_t>(d.mt_s + 1);
     w.tile_m_s = ar.get<int32_t>(d.mt_s + 1);
     w.tile_g_q = ar.get<int32_t>(d.mt_q + 1);
     w.tile_m_q = ar.get<int32_t>(d.mt_q + 1);
+    w.coarse_off_s = ar.get<int32_t>(COARSE_GROUPS + 1);
+    w.coarse_off_q = ar.get<int32_t>(COARSE_GROUPS + 1);
+    w.task_path = ar.get<u32>(d.Tw + 1);
+    w.pair_off_ss = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
+    w.pair_off_qs = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
+    w.pair_off_sq = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
+    // (down to here: filled by setup_wave, in one copy)
+    w.sample_task_s = ar.get<int32_t>(d.Ss + 1);
+    w.sample_task_q = ar.get<int32_t>(d.Sq + 1);
+    w.row_task_s = ar.get<int32_t>(d.Ps + 1);
+    w.row_task_q = ar.get<int32_t>(d.Pq + 1);
     w.cnt_s = ar.get<u32>(TF + 1);
     w.base_s = ar.get<u32>(TF + 1);
     w.cnt_q = ar.get<u32>(TF + 1);
@@ -375,17 +382,7 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
         w.tmid_keys = ar.get<u32>(d.nnz_s + d.nnz_q + 1);
         w.tmid_vals = ar.get<u32>(d.nnz_s + d.nnz_q + 1);
     }
-    w.coarse_off_s = ar.get<int32_t>(COARSE_GROUPS + 1);
-    w.coarse_off_q = ar.get<int32_t>(COARSE_GROUPS + 1);
-    w.pair_mat = nullptr;
-    w.pair_off_ss = w.pair_off_qs = w.pair_off_sq = nullptr;
-    w.task_path = ar.get<u32>(d.Tw + 1);
-    if (d.pair) {
-        w.pair_off_ss = ar.get<int64_t>(d.Tw + 1);
-        w.pair_off_qs = ar.get<int64_t>(d.Tw + 1);
-        w.pair_off_sq = ar.get<int64_t>(d.Tw + 1);
-        w.pair_mat = ar.get<uint8_t>(d.pair_bytes + 64);
-    }
+    w.pair_mat = d.pair ? ar.get<uint8_t>(d.pair_bytes + 64) : nullptr;
 }
 
 // activations, per-task parameters and gradient buffers of a wave
@@ -1016,24 +1013,22 @@ static void forward_backward(gm_ctx* c, const Grp& g, const float* labels, const
     }
     const float* wL = thf + c->offW[L];
     {
-        // algorithmic bytes: the last hidden activations read twice (logit; mask of the backward pass), the delta of the
-        // last hidden layer written, 20 bytes of per-row scalars (label, logit, delta, loss, task)
+        // algorithmic bytes: the last hidden activations read, the delta of the last hidden layer written, 20 bytes of
+        // per-row scalars (label, logit, delta, loss, task)
         const double esz_l = c->mlp_dtype ? 2.0 : 4.0;
-        Prof pr(c, "last_layer", (double)g.rows * c->ld[L - 1] * esz_l * (L > 1 ? 3 : 1) + 20.0 * g.rows + (L == 1 && dX ? 4.0 * g.rows * c->FD : 0.0), 0);
-        LastFwdArgs f;
+        Prof pr(c, "last_layer", (double)g.rows * c->ld[L - 1] * esz_l * (L > 1 ? 2 : 1) + 20.0 * g.rows + (L == 1 && dX ? 4.0 * g.rows * c->FD : 0.0), 0);
+        LastArgs f;
         memset(&f, 0, sizeof f);
         f.n = g.rows; f.N = c->ld[L - 1]; f.ld = c->ld[L - 1]; f.bf16 = c->mlp_dtype;
         f.row_task = g.row_task; f.row_offsets = g.row_off; f.real_offsets = g.real_off;
         f.a = act_ptr(c, *prev); f.w = wL; f.gW = thf_stride; f.b = thf + c->offb[L];
         f.labels = labels; f.z_out = p.zL; f.delta_out = p.dL; f.loss_out = loss_out;
-        launch_last_fwd(st, f);
+        if (L > 1) f.d = act_ptr(c, (*p.Dl)[L - 1]);
+        launch_last_layer(st, f);
         if (L == 1) {
-            if (dX) launch_last_bwd(st, 0, g.rows, c->FD, c->ld[0], c->FD, g.row_task, p.dL, wL, thf_stride, nullptr, nullptr,
-                                    0, nullptr, nullptr, dX);
+            if (dX) launch_input_delta(st, g.rows, c->FD, g.row_task, p.dL, wL, thf_stride, nullptr, nullptr, 0, dX);
             return;
         }
-        launch_last_bwd(st, c->mlp_dtype, g.rows, c->ld[L - 1], c->ld[L - 1], c->ld[L - 1], g.row_task, p.dL, wL,
-                        thf_stride, nullptr, nullptr, 0, act_ptr(c, (*p.A)[L - 1]), act_ptr(c, (*p.Dl)[L - 1]), nullptr);
     }
     for (int l = L - 1; l >= 1; --l) {
         if (l == 1) {
@@ -1109,24 +1104,20 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
     }
     const float* vwL = v.f + c->offW[L];
     {
-        // (tangent pass: activations and their tangents read, the mask read, the tangent delta written)
+        // (tangent pass: activations and their tangents read, the tangent delta written)
         const double esz_l = c->mlp_dtype ? 2.0 : 4.0;
-        Prof pr(c, "last_layer", (double)g.rows * c->ld[L - 1] * esz_l * (L > 1 ? 4 : 2) + 24.0 * g.rows + (L == 1 ? 4.0 * g.rows * c->FD : 0.0), 0);
-        LastFwdArgs f;
+        Prof pr(c, "last_layer", (double)g.rows * c->ld[L - 1] * esz_l * (L > 1 ? 3 : 2) + 24.0 * g.rows + (L == 1 ? 4.0 * g.rows * c->FD : 0.0), 0);
+        LastArgs f;
         memset(&f, 0, sizeof f);
         f.n = g.rows; f.N = c->ld[L - 1]; f.ld = c->ld[L - 1]; f.bf16 = c->mlp_dtype;
         f.row_task = g.row_task; f.row_offsets = g.row_off; f.real_offsets = g.real_off;
         f.a = act_ptr(c, *prev); f.ta = act_ptr(c, *tprev); f.w = s.wL; f.gW = s.wL_stride; f.b = nullptr;
         f.tw = vwL; f.gTW = nt; f.tb = v.f + c->offb[L];
-        f.z_in = s.zL; f.delta_out = w.tdL;
-        launch_last_fwd(st, f);
+        f.z_in = s.zL; f.delta_in = s.dL; f.delta_out = w.tdL;
         // tangent of the backward pass, top layer first; each layer's direction is consumed before it is updated
-        if (L == 1)
-            launch_last_bwd(st, 0, g.rows, c->FD, c->ld[0], c->FD, g.row_task, w.tdL, s.wL, s.wL_stride, s.dL, vwL, nt,
-                            nullptr, nullptr, w.dX);
-        else
-            launch_last_bwd(st, c->mlp_dtype, g.rows, c->ld[L - 1], c->ld[L - 1], c->ld[L - 1], g.row_task, w.tdL, s.wL,
-                            s.wL_stride, s.dL, vwL, nt, act_ptr(c, s.A[L - 1]), act_ptr(c, w.TD[L - 1]), nullptr);
+        if (L > 1) f.d = act_ptr(c, w.TD[L - 1]);
+        launch_last_layer(st, f);
+        if (L == 1) launch_input_delta(st, g.rows, c->FD, g.row_task, w.tdL, s.wL, s.wL_stride, s.dL, vwL, nt, w.dX);
     }
     ColSums sums{c, g};   // (biases and the last layer's direction: nothing below reads them)
     sums.add(c->ld[L - 1], tprev, s.dL, prev, w.tdL, v.f + c->offW[L], nt, v.f + c->offW[L], nt, 1.f, -alpha);
@@ -1163,13 +1154,6 @@ __global__ void gather_task_lookup_offsets(const int64_t* toff, const int64_t* b
     if (t <= T) out[t] = bag_offsets[toff[t] * F];
 }
 
-// prow[s] = padded row of sample s (whole set): prow_off[t] + (s - toff[t])
-__global__ void fill_prow_kernel(const int64_t* toff, const int32_t* prow_off, int32_t* prow) {
-    const int t = blockIdx.x;
-    const int64_t lo = toff[t], hi = toff[t + 1];
-    for (int64_t s = lo + threadIdx.x; s < hi; s += blockDim.x) prow[s] = prow_off[t] + (int32_t)(s - lo);
-}
-
 static void build_tiles(const std::vector<int64_t>& poff, int t0, int t1, int bm, std::vector<int32_t>& row_off,
                         std::vector<int32_t>& tg, std::vector<int32_t>& tm) {
     row_off.clear(); tg.clear(); tm.clear();
@@ -1185,11 +1169,32 @@ static void build_tiles(const std::vector<int64_t>& poff, int t0, int t1, int bm
     row_off.push_back((int32_t)(poff[t1] - base));
 }
 
-static int upload_i32(gm_ctx* c, int32_t* dst, const std::vector<int32_t>& v) {
-    if (v.empty()) return GM_OK;
-    HIPCHK(c, hipMemcpyAsync(dst, v.data(), v.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-    return GM_OK;
-}
+// What a call sends to the device lives here until the stream has taken it.
+struct HostImages {
+    hipStream_t st = nullptr;
+    std::vector<std::vector<char>> held;
+    ~HostImages() { if (!held.empty()) (void)hipStreamSynchronize(st); }
+};
+// Arrays that lie side by side in the workspace, sent in one copy (a copy of a few hundred bytes costs what a launch does).
+struct Upload {
+    char* dev;
+    std::vector<char> host;
+    template <typename T>
+    void put(T* dst, const T* src, size_t n) {
+        const size_t off = (size_t)(reinterpret_cast<char*>(dst) - dev);
+        if (host.size() < off + n * sizeof(T)) host.resize(off + n * sizeof(T));
+        if (n > 0) memcpy(host.data() + off, src, n * sizeof(T));
+    }
+    template <typename T>
+    void put(T* dst, const std::vector<T>& v) { put(dst, v.data(), v.size()); }
+    int send(gm_ctx* c, HostImages& keep) {
+        keep.st = c->stream;
+        keep.held.push_back(std::move(host));
+        const std::vector<char>& v = keep.held.back();
+        if (!v.empty()) HIPCHK(c, hipMemcpyAsync(dev, v.data(), v.size(), hipMemcpyHostToDevice, c->stream));
+        return GM_OK;
+    }
+};
 
 struct Batch {  // host-side description of one call
     int T;
@@ -1198,6 +1203,7 @@ struct Batch {  // host-side description of one call
     std::vector<int64_t> ls, lq;          // lookup offsets per task (filled when several waves are needed)
     bool table = false;                   // table-shaped sparse output: every wave sorts and reduces its own lookups
     BatchBufs b;
+    HostImages images;
 };
 
 // The lookups of samples [s0, s1) of the support set and [q0, q1) of the query set, ordered by global row and cut into
@@ -1312,7 +1318,6 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
     if (F == 0 || Tw == 0) return GM_OK;
     const int64_t TF = (int64_t)Tw * F;
     SetView vs = make_view(B.sup, B.b.toff_s, wp.s0, wp.ls0), vq = make_view(B.qry, B.b.toff_q, wp.q0, wp.lq0);
-    launch_fill_u32(st, c->d_status, ST_WORDS, 0);
     {
         Prof p(c, "tf_count", 8.0 * ((wp.s1 - wp.s0) + (wp.q1 - wp.q0)) * F + 4.0 * ((wp.ls1 - wp.ls0) + (wp.lq1 - wp.lq0)), 0);
         launch_tf_count(st, F, wp.t0, Tw, vs, vq, c->d_field_base, B.sup->nnz, B.qry->nnz, uniform_rows(c), w.cnt_s, w.cnt_q, c->d_status);
@@ -1332,8 +1337,7 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
     if (cap > tf_sort_max_cap())
         return fail(c, GM_ERR_CAPACITY, "a (task, field) has %u lookups in one set; the limit is %d", hs[ST_MAX_TF],
                     tf_sort_max_cap());
-    launch_scan_u32(st, w.cnt_s, w.base_s, TF, w.scan_tmp, nullptr);
-    launch_scan_u32(st, w.cnt_q, w.base_q, TF, w.scan_tmp, nullptr);
+    launch_scan_u32_pair(st, w.cnt_s, w.base_s, w.cnt_q, w.base_q, TF, w.scan_tmp);
     const double tf_bytes = 12.0 * ((wp.ls1 - wp.ls0) + (wp.lq1 - wp.lq0));
     // ---- the dictionaries read off the row order of the wave's lookups
     bool join = jr && jr->so && c->index_path != 1;
@@ -1565,20 +1569,19 @@ static int begin_batch(gm_ctx* c, Batch& B, Arena& ar, int64_t capacity, bool ne
     if (ar.overflow || (dense_ar && dense_ar->overflow))
         return fail(c, GM_ERR_WORKSPACE, "workspace too small for the batch-level buffers (%zu needed)", ar.off);
     hipStream_t st = c->stream;
-    HIPCHK(c, hipMemcpyAsync(B.b.toff_s, B.sup->task_offsets, (T + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    HIPCHK(c, hipMemcpyAsync(B.b.toff_q, B.qry->task_offsets, (T + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
     std::vector<int32_t> ps(B.poff_s.begin(), B.poff_s.end()), pq(B.poff_q.begin(), B.poff_q.end());
-    int rc;
-    if ((rc = upload_i32(c, B.b.prow_off_s, ps)) || (rc = upload_i32(c, B.b.prow_off_q, pq))) return rc;
-    if (T > 0) {
-        hipLaunchKernelGGL(fill_prow_kernel, dim3(T), dim3(256), 0, st, B.b.toff_s, B.b.prow_off_s, B.b.prow_s);
-        hipLaunchKernelGGL(fill_prow_kernel, dim3(T), dim3(256), 0, st, B.b.toff_q, B.b.prow_off_q, B.b.prow_q);
-    }
-    HIPCHK(c, hipStreamSynchronize(st));  // the host vectors above go out of scope
+    Upload up{reinterpret_cast<char*>(B.b.toff_s), {}};
+    up.put(B.b.toff_s, B.sup->task_offsets, T + 1);
+    up.put(B.b.toff_q, B.qry->task_offsets, T + 1);
+    up.put(B.b.prow_off_s, ps);
+    up.put(B.b.prow_off_q, pq);
+    int rc = up.send(c, B.images);
+    if (rc != GM_OK) return rc;
+    launch_expand_tasks(st, T, ExpandJobs{2, {{B.b.toff_s, nullptr, B.b.prow_off_s, B.b.prow_s}, {B.b.toff_q, nullptr, B.b.prow_off_q, B.b.prow_q}}});
     return GM_OK;
 }
 
-static int setup_wave(gm_ctx* c, const Batch& B, const WavePlan& wp, int bm, int K, WaveBufs& w, const WaveDims& d, Grp& gs,
+static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, WaveBufs& w, const WaveDims& d, Grp& gs,
                       Grp& gq) {
     hipStream_t st = c->stream;
     std::vector<int32_t> ro_s, tg_s, tm_s, ro_q, tg_q, tm_q, re_s, re_q;
@@ -1596,28 +1599,21 @@ static int setup_wave(gm_ctx* c, const Batch& B, const WavePlan& wp, int bm, int
         co_s.push_back(ro_s[t]);
         co_q.push_back(ro_q[t]);
     }
-    int rc;
-    if ((rc = upload_i32(c, w.coarse_off_s, co_s)) || (rc = upload_i32(c, w.coarse_off_q, co_q))) return rc;
-    if ((rc = upload_i32(c, w.row_off_s, ro_s)) || (rc = upload_i32(c, w.row_off_q, ro_q)) ||
-        (rc = upload_i32(c, w.real_off_s, re_s)) || (rc = upload_i32(c, w.real_off_q, re_q)) ||
-        (rc = upload_i32(c, w.tile_g_s, tg_s)) || (rc = upload_i32(c, w.tile_m_s, tm_s)) ||
-        (rc = upload_i32(c, w.tile_g_q, tg_q)) || (rc = upload_i32(c, w.tile_m_q, tm_q)))
-        return rc;
+    Upload up{reinterpret_cast<char*>(w.row_off_s), {}};
+    up.put(w.row_off_s, ro_s); up.put(w.row_off_q, ro_q);
+    up.put(w.real_off_s, re_s); up.put(w.real_off_q, re_q);
+    up.put(w.tile_g_s, tg_s); up.put(w.tile_m_s, tm_s);
+    up.put(w.tile_g_q, tg_q); up.put(w.tile_m_q, tm_q);
+    up.put(w.coarse_off_s, co_s); up.put(w.coarse_off_q, co_q);
     std::vector<int64_t> po_ss, po_qs, po_sq;
     std::vector<u32> path;
     pair_layout(c, B, wp, K, d.pair_ss, d.pair_sq, &po_ss, &po_qs, &po_sq, &path);
-    if (!path.empty())
-        HIPCHK(c, hipMemcpyAsync(w.task_path, path.data(), path.size() * sizeof(u32), hipMemcpyHostToDevice, st));
-    if (d.pair) {
-        HIPCHK(c, hipMemcpyAsync(w.pair_off_ss, po_ss.data(), po_ss.size() * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        HIPCHK(c, hipMemcpyAsync(w.pair_off_qs, po_qs.data(), po_qs.size() * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        HIPCHK(c, hipMemcpyAsync(w.pair_off_sq, po_sq.data(), po_sq.size() * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    }
-    launch_fill_sample_task(st, w.real_off_s, d.Tw, w.sample_task_s);
-    launch_fill_sample_task(st, w.real_off_q, d.Tw, w.sample_task_q);
-    launch_fill_sample_task(st, w.row_off_s, d.Tw, w.row_task_s);
-    launch_fill_sample_task(st, w.row_off_q, d.Tw, w.row_task_q);
-    HIPCHK(c, hipStreamSynchronize(st));  // host vectors go out of scope
+    up.put(w.task_path, path);
+    if (d.pair) { up.put(w.pair_off_ss, po_ss); up.put(w.pair_off_qs, po_qs); up.put(w.pair_off_sq, po_sq); }
+    const int rc = up.send(c, B.images);
+    if (rc != GM_OK) return rc;
+    launch_expand_tasks(st, d.Tw, ExpandJobs{4, {{nullptr, w.real_off_s, nullptr, w.sample_task_s}, {nullptr, w.real_off_q, nullptr, w.sample_task_q},
+                                                 {nullptr, w.row_off_s, nullptr, w.row_task_s}, {nullptr, w.row_off_q, nullptr, w.row_task_q}}});
     gs = Grp{w.row_off_s, w.real_off_s, w.row_task_s, w.tile_g_s, w.tile_m_s, d.mt_s, d.Tw, bm, d.Ps};
     gq = Grp{w.row_off_q, w.real_off_q, w.row_task_q, w.tile_g_q, w.tile_m_q, d.mt_q, d.Tw, bm, d.Pq};
     return GM_OK;
@@ -1757,14 +1753,15 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     ValEnc enc = kPlainVals;     // how the values that travel with the row keys name their bags
 
     // meta theta in the padded internal layout (and its bf16 operand copies); accumulators
+    std::vector<MatrixJob> mats;
     for (int l = 1; l <= L; ++l) {
-        launch_pack_weights(st, params->W[l - 1], c->dims[l - 1], c->dims[l], c->ld[l - 1], c->ld[l], b.theta0.f + c->offW[l]);
-        launch_pack_weights(st, params->b[l - 1], 1, c->dims[l], 1, (int)(l == L ? 32 : c->ld[l]), b.theta0.f + c->offb[l]);
-        if (bf && l < L)
-            launch_convert_weights(st, b.theta0.f + c->offW[l], 0, 1, c->ld[l - 1], c->ld[l], b.theta0.b + c->offWb[l],
-                                   nullptr, 0);
+        mats.push_back(MatrixJob{params->W[l - 1], c->dims[l - 1], c->dims[l], c->dims[l], b.theta0.f + c->offW[l],
+                                 bf && l < L ? b.theta0.b + c->offWb[l] : nullptr, c->ld[l - 1], c->ld[l], c->ld[l], 0});
+        mats.push_back(MatrixJob{params->b[l - 1], 1, c->dims[l], c->dims[l], b.theta0.f + c->offb[l], nullptr, 1,
+                                 l == L ? 32 : c->ld[l], 32, 0});
     }
-    launch_fill_f32(st, b.g_theta, nt, 0.f);
+    launch_copy_matrices(st, mats.data(), (int)mats.size());
+    bool theta_summed = false;   // the first wave's sums are stored, later waves' added
     // Gradient w.r.t. the pooled inputs: the query rows are written whole by the outer backward pass; the support rows
     // are the second-order chain's sum, which starts from zero unless its first product stores instead of adding.
     const bool gxs_self_init = order == 2 && K > 0 && bf && L > 1;
@@ -1834,13 +1831,9 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         const int32_t rb_s = (int32_t)wp.ps0, rb_q = (int32_t)wp.pq0;
         const bool second = order == 2 && K > 0;
 
-        // a1: one prefetch pass for both sets (pad rows stay zero; without pad rows nothing needs clearing: every
-        // real row is written whole, pooled fields by the gather and dense / pad columns by the tail kernels)
+        // a1: one prefetch pass for both sets.  Every real row is written whole (pooled fields, dense and pad columns); only
+        // the pad rows of what the row arithmetic writes real rows of are cleared.
         const bool padded = d.Ps != d.Ss || d.Pq != d.Sq;
-        if (padded) {
-            launch_fill_f32(st, w.Xs0, d.Ps * ld0, 0.f);
-            launch_fill_f32(st, w.Xq0, d.Pq * ld0, 0.f);
-        }
         Act X0s;  // step-0 support input
         X0s.ld = ld0;
         if (bf) X0s = K > 0 ? w.steps[0].X : Act();
@@ -1848,21 +1841,27 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         {
             const double lookups = (double)(d.nnz_s + d.nnz_q), bags = (double)(d.Ss + d.Sq) * F;
             Prof p(c, "gather_pool", lookups * (4.0 * D + 4) + bags * (4.0 * D + 8 + (bf ? 2.0 * D : 0)), 0);
-            if (bf && X0s.b && padded) zero_bf16(st, X0s.b, d.Ps * ld0);
-            if (bf && padded) zero_bf16(st, w.Xq.b, d.Pq * ld0);
-            launch_gather_pool(st, F, D, c->n_dense, c->d_field_base, sup->bag_offsets, sup->indices, sup->dense,
-                               params->emb, wp.s0, d.Ss, rows_s, rb_s, w.Xs0, ld0, bf ? X0s.b : nullptr);
-            launch_gather_pool(st, F, D, c->n_dense, c->d_field_base, qry->bag_offsets, qry->indices, qry->dense,
-                               params->emb, wp.q0, d.Sq, rows_q, rb_q, w.Xq0, ld0, (bf && K == 0) ? w.Xq.b : nullptr);
+            launch_gather_pool(st, F, D, c->n_dense, c->d_field_base, params->emb, ld0,
+                               PoolSet{sup->bag_offsets, sup->indices, sup->dense, wp.s0, d.Ss, rows_s, rb_s, w.Xs0, bf ? X0s.b : nullptr},
+                               PoolSet{qry->bag_offsets, qry->indices, qry->dense, wp.q0, d.Sq, rows_q, rb_q, w.Xq0, (bf && K == 0) ? w.Xq.b : nullptr});
+        }
+        if (padded) {
+            PadJobs pj;
+            memset(&pj, 0, sizeof pj);
+            pj.off[0] = w.row_off_s; pj.off[1] = w.row_off_q; pj.real[0] = w.real_off_s; pj.real[1] = w.real_off_q;
+            auto pad = [&](void* p, int elem, int set) {
+                if (!p) return;
+                pj.p[pj.n] = static_cast<char*>(p); pj.row_bytes[pj.n] = ld0 * elem; pj.set[pj.n] = set;
+                if (++pj.n == PAD_JOBS) { launch_zero_pad_rows(st, Tw, pj); pj.n = 0; }
+            };
+            pad(w.Xs0, 4, 0); pad(w.Xq0, 4, 1);
+            pad(X0s.b, 2, 0); pad(w.Xq.b, 2, 1); pad(w.Xs_scratch.b, 2, 0);
+            for (size_t k = 1; k < w.steps.size(); ++k) pad(w.steps[k].X.b, 2, 0);
+            if (second) { pad(w.TX.b, 2, 0); pad(w.TX.f, 4, 0); pad(w.TXf, 4, 0); }
+            launch_zero_pad_rows(st, Tw, pj);
         }
         // the pooled direction: its dense and pad columns are zero (dense features are not parameters)
-        if (second && padded) {
-            if (w.TX.b) zero_bf16(st, w.TX.b, d.Ps * ld0);
-            if (w.TX.f) launch_fill_f32(st, w.TX.f, d.Ps * ld0, 0.f);
-            if (w.TXf) launch_fill_f32(st, w.TXf, d.Ps * ld0, 0.f);
-        } else if (second) {
-            launch_copy_tail(st, FD, nullptr, d.Ps, bf ? w.TXf : w.TX.f, ld0, w.TX.b);
-        }
+        if (second) launch_copy_tail(st, FD, nullptr, d.Ps, bf ? w.TXf : w.TX.f, ld0, w.TX.b);
 
         // The wave's offsets and indices are validated.  Ordering the lookups by row needs nothing else: it runs on the
         // side stream from here on -- beside the dense phase, which is bound by memory traffic, not beside the index
@@ -1996,12 +1995,10 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 float* xs_next = nullptr;
                 if (more) {
                     xs_next = bf ? w.Xs0 : Xn.f;  // bf16: the fp32 master is updated in place
-                    if (bf && padded) zero_bf16(st, Xn.b, d.Ps * ld0);
                 }
                 const bool last = !more;
                 TwoHopOut os = hop_out(true, xs_cur, xs_next, more && bf ? Xn.b : nullptr, -alpha);
                 TwoHopOut oq = hop_out(false, w.Xq0, w.Xq0, (bf && last) ? Xq.b : nullptr, -alpha);
-                if (bf && last && padded) zero_bf16(st, Xq.b, d.Pq * ld0);
                 two_hop(true, w.dX, more ? &os : nullptr, &oq);
                 if (more) {
                     launch_copy_tail(st, FD, xs_cur, d.Ps, bf ? nullptr : (xs_next != xs_cur ? xs_next : nullptr), ld0, bf ? Xn.b : nullptr);
@@ -2070,23 +2067,19 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 }
             }
         }
-        // cross-task reduction of the dense part (tasks of the wave in order, waves in order)
+        // cross-task reduction of the dense part (tasks of the wave in order, waves in order).  vsum: the weight matrices'
+        // part summed over runs of tasks -- the chain's last step, or (first order) all of it
         {
             Prof p(c, "reduce_tasks", 4.0 * (second ? Tw : n_coarse) * nt, 0);
-            if (second) {
-                launch_reduce_tasks(st, w.v.f, nt, Tw, nt, b.g_theta, 1, 1.f);
-                for (int l = 1; l < L; ++l)   // the last step's weight-matrix part, summed over runs of tasks
-                    launch_reduce_tasks(st, w.vsum.f + c->offW[l], nt, n_coarse, (int64_t)c->ld[l - 1] * c->ld[l],
-                                        b.g_theta + c->offW[l], 1, -alpha);
-            } else {   // weight matrices of the hidden layers from the runs of tasks, the rest from the tasks
-                for (int l = 1; l < L; ++l) {
-                    launch_reduce_tasks(st, w.vsum.f + c->offW[l], nt, n_coarse, c->offb[l] - c->offW[l],
-                                        b.g_theta + c->offW[l], 1, 1.f);
-                    launch_reduce_tasks(st, w.v.f + c->offb[l], nt, Tw, c->offW[l + 1] - c->offb[l], b.g_theta + c->offb[l], 1,
-                                        1.f);
-                }
-                launch_reduce_tasks(st, w.v.f + c->offW[L], nt, Tw, nt - c->offW[L], b.g_theta + c->offW[L], 1, 1.f);
+            ReduceArgs ra{w.v.f, w.vsum.f, nt, second ? -alpha : 1.f, b.g_theta, theta_summed, 0, {}};
+            std::vector<ReducePiece> pieces;
+            for (int l = 1; l < L; ++l) {
+                pieces.push_back(ReducePiece{c->offW[l], c->offb[l] - c->offW[l], second ? Tw : 0, n_coarse, 0});
+                pieces.push_back(ReducePiece{c->offb[l], c->offW[l + 1] - c->offb[l], Tw, 0, 0});
             }
+            pieces.push_back(ReducePiece{c->offW[L], nt - c->offW[L], Tw, 0, 0});
+            launch_reduce_tasks(st, ra, pieces.data(), (int)pieces.size());
+            theta_summed = true;
         }
         // table-shaped sparse output: the wave's lookups are ordered by row and every row's sum is added to its row of
         // the table (rows are distinct within a wave; waves follow each other on the stream)
@@ -2108,10 +2101,14 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     }
 
     // outputs: dense meta-gradient, loss, coalesced sparse meta-gradient
+    if (!theta_summed) launch_fill_f32(st, b.g_theta, nt, 0.f);   // no tasks
+    mats.clear();
     for (int l = 1; l <= L; ++l) {
-        launch_unpack_weights(st, b.g_theta + c->offW[l], c->dims[l - 1], c->dims[l], c->ld[l], out->dW[l - 1]);
-        launch_unpack_weights(st, b.g_theta + c->offb[l], 1, c->dims[l], c->dims[l], out->db[l - 1]);
+        mats.push_back(MatrixJob{b.g_theta + c->offW[l], c->dims[l - 1], c->dims[l], c->ld[l], out->dW[l - 1], nullptr, c->dims[l - 1],
+                                 c->dims[l], c->dims[l], 0});
+        mats.push_back(MatrixJob{b.g_theta + c->offb[l], 1, c->dims[l], c->dims[l], out->db[l - 1], nullptr, 1, c->dims[l], c->dims[l], 0});
     }
+    launch_copy_matrices(st, mats.data(), (int)mats.size());
     launch_sum_to_scalar(st, task_loss, T, loss, 0);
     // (a batch whose segments were cut inside its wave keeps the status words of that: the row count, the capacity flag)
     if (!pre && !list_ordered) launch_fill_u32(st, c->d_status, ST_WORDS, 0);
@@ -2140,6 +2137,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     rc = side_list ? (hipStreamSynchronize(st) == hipSuccess ? GM_OK : fail(c, GM_ERR_HIP, "stream synchronisation failed"))
                    : read_status(c, hs);
     if (rc != GM_OK) return rc;
+    B.images.held.clear();   // (the stream has been drained)
     HIPCHK(c, hipGetLastError());
     prof_drain(c);
     if (hs[ST_CAPACITY])
@@ -2371,6 +2369,7 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
     }
     u32 hs[ST_WORDS];
     if ((rc = read_status(c, hs))) return rc;
+    B.images.held.clear();
     HIPCHK(c, hipGetLastError());
     if (hs[ST_CAPACITY])
         return fail(c, GM_ERR_CAPACITY, "internal: %u rows touched exceed the list capacity %lld", hs[ST_NROWS], (long long)capacity);
@@ -2682,9 +2681,9 @@ extern "C" int gm_gather_pool(gm_ctx* c, int32_t T, const gm_set* set, const flo
     if (ar.overflow) return fail(c, GM_ERR_WORKSPACE, "workspace too small");
     HIPCHK(c, hipMemcpyAsync(toff, set->task_offsets, (T + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
     // validate before the gather trusts offsets and indices
-    launch_fill_u32(st, c->d_status, ST_WORDS, 0);
     SetView v = make_view(set, toff, 0, 0);
-    if (c->F > 0 && T > 0)
+    if (c->F == 0 || T == 0) launch_fill_u32(st, c->d_status, ST_WORDS, 0);
+    else
         launch_tf_count(st, c->F, 0, T, v, v, c->d_field_base, set->nnz, set->nnz, uniform_rows(c), cnt, cnt + (int64_t)T * c->F + 1, c->d_status);
     u32 hs[ST_WORDS];
     rc = read_status(c, hs);
@@ -2706,8 +2705,8 @@ extern "C" int gm_gather_pool(gm_ctx* c, int32_t T, const gm_set* set, const flo
         int32_t* ident = ar.get<int32_t>(n);
         hipLaunchKernelGGL(iota_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, ident, n);
         Prof p(c, "gather_pool", 0, 0);
-        launch_gather_pool(st, c->F, c->D, c->n_dense, c->d_field_base, set->bag_offsets, set->indices, set->dense, emb, s0,
-                           n, ident, 0, xp, ld0, nullptr);
+        launch_gather_pool(st, c->F, c->D, c->n_dense, c->d_field_base, emb, ld0,
+                           PoolSet{set->bag_offsets, set->indices, set->dense, s0, n, ident, 0, xp, nullptr}, PoolSet{});
         hipLaunchKernelGGL(strip_pad_kernel, dim3((unsigned)((n * d0 + 255) / 256)), dim3(256), 0, st, xp, n, ld0, d0,
                            x + s0 * d0);
     }
@@ -2796,6 +2795,7 @@ extern "C" int gm_index_prep(gm_ctx* c, int32_t T, const gm_set* sup, const gm_s
     u32 hs[ST_WORDS];
     rc = read_status(c, hs);
     if (rc != GM_OK) return rc;
+    B.images.held.clear();   // (the stream has been drained)
     HIPCHK(c, hipGetLastError());
     prof_drain(c);
     if (hs[ST_CAPACITY])

@@ -110,8 +110,7 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
 void launch_tf_count(hipStream_t st, int F, int t0, int Tw, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status) {
     if (Tw <= 0) return;
-    launch_fill_u32(st, cnt_sup, (int64_t)Tw * F, 0u);
-    if (cnt_qry != cnt_sup) launch_fill_u32(st, cnt_qry, (int64_t)Tw * F, 0u);
+    launch_zero(st, ZeroJobs{3, {status, cnt_sup, cnt_qry}, {ST_WORDS, (int64_t)Tw * F, cnt_qry != cnt_sup ? (int64_t)Tw * F : 0}});
     // enough workgroups to fill the chip whatever the number of tasks in the wave
     const int split = Tw >= 2048 ? 1 : (Tw >= 512 ? 4 : 8);
     hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, split), dim3(256), 2 * F * sizeof(u32), st, F, t0, sup, qry, field_base,
@@ -207,7 +206,59 @@ __global__ void scan_add_kernel(u32* out, int64_t n, const u32* block_offsets) {
         if (base + i < n) out[base + i] += o;
 }
 
-__global__ void copy_u32_kernel(const u32* src, u32* dst) { *dst = *src; }
+// One workgroup scans the whole array, 16384 values at a time: up to SCAN_ONE values that is faster than a launch per
+// level.  Measured: 2304 values, 8.8 us in three launches -> 3.9 us in one.
+#define SCAN_ONE 32768
+struct ScanPair { const u32* in[2]; u32* out[2]; };   // blockIdx.x picks one
+__global__ __launch_bounds__(1024) void scan_one_kernel(ScanPair p, int64_t n, u32* total) {
+    __shared__ int sh[1024 / WAVE + 2];
+    const u32* in = p.in[blockIdx.x];
+    u32* out = p.out[blockIdx.x];
+    const bool wide = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+    u32 carry = 0;
+    for (int64_t base0 = 0; base0 < n; base0 += 16384) {
+        const int64_t base = base0 + (int64_t)threadIdx.x * 16;
+        u32 v[16];
+        u32 sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (wide && base + 4 * q + 4 <= n) {
+                const uint4 x = *reinterpret_cast<const uint4*>(in + base + 4 * q);
+                v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+            } else {
+#pragma unroll
+                for (int k = 4 * q; k < 4 * q + 4; ++k) v[k] = base + k < n ? in[base + k] : 0u;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) sum += v[k];
+        int all;
+        u32 run = carry + (u32)block_excl_scan((int)sum, sh, &all);
+        carry += (u32)all;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32 o[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { o[k] = run; run += v[4 * q + k]; }
+            if (wide && base + 4 * q + 4 <= n) *reinterpret_cast<uint4*>(out + base + 4 * q) = make_uint4(o[0], o[1], o[2], o[3]);
+            else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (base + 4 * q + k < n) out[base + 4 * q + k] = o[k];
+            }
+        }
+        __syncthreads();   // the scan's scratch is used again
+    }
+    if (total && threadIdx.x == 0) *total = carry;
+}
+void launch_scan_u32_pair(hipStream_t st, const u32* in0, u32* out0, const u32* in1, u32* out1, int64_t n, u32* tmp) {
+    if (n > 0 && n <= SCAN_ONE) {
+        hipLaunchKernelGGL(scan_one_kernel, dim3(2), dim3(1024), 0, st, ScanPair{{in0, in1}, {out0, out1}}, n, (u32*)nullptr);
+        return;
+    }
+    launch_scan_u32(st, in0, out0, n, tmp, nullptr);
+    launch_scan_u32(st, in1, out1, n, tmp, nullptr);
+}
 
 size_t scan_tmp_words(int64_t n) {
     size_t w = 0;
@@ -226,12 +277,12 @@ void launch_scan_u32(hipStream_t st, const u32* in, u32* out, int64_t n, u32* tm
         if (total) launch_fill_u32(st, total, 1, 0);
         return;
     }
-    const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
-    hipLaunchKernelGGL(scan_block_kernel, dim3((unsigned)nb), dim3(SCAN_NT), 0, st, in, out, n, tmp);
-    if (nb == 1) {
-        if (total) hipLaunchKernelGGL(copy_u32_kernel, dim3(1), dim3(1), 0, st, tmp, total);
+    if (n <= SCAN_ONE) {
+        hipLaunchKernelGGL(scan_one_kernel, dim3(1), dim3(1024), 0, st, ScanPair{{in, nullptr}, {out, nullptr}}, n, total);
         return;
     }
+    const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+    hipLaunchKernelGGL(scan_block_kernel, dim3((unsigned)nb), dim3(SCAN_NT), 0, st, in, out, n, tmp);
     u32* next = tmp + (nb + 63) / 64 * 64;
     launch_scan_u32(st, tmp, tmp, nb, next, total);
     hipLaunchKernelGGL(scan_add_kernel, dim3((unsigned)nb), dim3(SCAN_NT), 0, st, out, n, tmp);
@@ -1012,12 +1063,11 @@ size_t radix_hist_words(int64_t n, int extra_tiles) {
 template <int BITS, bool BYTASK>
 static void radix_pass(hipStream_t st, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
                        const TaskOf& tk, const SegTab& seg) {
-    // ranges: at most one partly filled tile per range beyond the tiles of the whole list; the count table is cleared
-    // first, since the tiles past the last range's write nothing into it
+    // ranges: at most one partly filled tile per range beyond the tiles of the whole list (the tiles past the last range's
+    // write nothing into the count table: what the table holds there stands behind every count and moves none's place)
     const int nblk = (int)((n + RS_TILE - 1) / RS_TILE) + seg.n_seg;
     u32* scan_tmp = hist + ((size_t)512 * nblk + 63) / 64 * 64;
     const dim3 grid((nblk + 7) / 8 * 8);
-    if (seg.n_seg) launch_fill_u32(st, hist, (int64_t)(1 << BITS) * nblk, 0u);
     hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK>), grid, dim3(RS_NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
     launch_scan_u32(st, hist, hist, (int64_t)(1 << BITS) * nblk, scan_tmp, nullptr);
     hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK>), grid, dim3(RS_NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
@@ -1295,6 +1345,27 @@ void launch_segments(hipStream_t st, const u32* sorted_keys, int64_t n, u32* fla
 }
 
 // ------------------------------------------------------------------------------------------------
+__global__ void zero_kernel(ZeroJobs z) {
+    u32* p = z.p[blockIdx.y];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < z.words[blockIdx.y]; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0u;
+}
+void launch_zero(hipStream_t st, const ZeroJobs& z) {
+    int64_t most = 0;
+    for (int i = 0; i < z.n; ++i) most = std::max(most, z.words[i]);
+    if (most <= 0) return;
+    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)std::min<int64_t>((most + 255) / 256, 4096), z.n), dim3(256), 0, st, z);
+}
+__global__ void zero_pad_rows_kernel(PadJobs z) {
+    const int g = blockIdx.x, set = z.set[blockIdx.y], bytes = z.row_bytes[blockIdx.y];
+    const int n_real = z.real[set][g + 1] - z.real[set][g], r0 = z.off[set][g] + n_real, n_pad = z.off[set][g + 1] - r0;
+    uint4* p = reinterpret_cast<uint4*>(z.p[blockIdx.y] + (int64_t)r0 * bytes);
+    const int n = n_pad * (bytes / 16);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+void launch_zero_pad_rows(hipStream_t st, int G, const PadJobs& z) {
+    if (G <= 0 || z.n <= 0) return;
+    hipLaunchKernelGGL(zero_pad_rows_kernel, dim3(G, z.n), dim3(256), 0, st, z);
+}
 __global__ void fill_u32_kernel(u32* p, int64_t n, u32 v) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;

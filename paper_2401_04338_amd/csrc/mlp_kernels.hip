@@ -360,7 +360,7 @@ void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offs
 }
 
 // ------------------------------------------------------------------------------------------------
-// last layer (d_L = 1) fused with the sigmoid / binary cross-entropy: one wavefront per row.
+// last layer (d_L = 1) fused with the sigmoid / binary cross-entropy and the delta of the layer below it
 // Rows may be padded per task: row r of task g is sample real_offsets[g] + (r - row_offsets[g]) when that
 // is below real_offsets[g+1]; pad rows get delta = 0 and loss = 0.
 // ------------------------------------------------------------------------------------------------
@@ -384,10 +384,23 @@ __device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// lpr: lanes per row, a power of two (64: one row per wave; fewer when 8 columns per lane cover the row with less,
-// so that a wave takes 64 / lpr rows at once)
+__device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8]) {
+    *reinterpret_cast<uint4*>(p) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+}
+__device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
+    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
+}
+
+// lpr: lanes per row, a power of two: 8 columns per lane and step (width and strides are multiples of 32, rows 16-byte
+// aligned: every activation is padded to 32 columns).  The row's logit and delta are known to all of its lanes, which then
+// write the delta of the last hidden layer, d[s, n] = (delta * w_n (+ delta' * w'_n in the tangent pass)) * (a[s, n] > 0),
+// from the activations they just read (cache hits).  Bound: HBM with many rows -- the activations are read once instead
+// of twice -- and the launch with few.
+// Measured: the three passes of a step of 4 tasks x (32 + 32) rows, 32 units, fp32, 20.8 us in six launches (logits and
+// deltas apart) -> 12.2 us in three; the seven of 512 tasks x (256 + 256) rows, 256 units, bf16, 0.37 ms.
 template <typename T>
-__global__ void last_fwd_kernel(LastFwdArgs a, int lpr) {
+__global__ __launch_bounds__(256) void last_layer_kernel(LastArgs a, int lpr) {
     const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t s = gt / lpr;
     const int lane = (int)(gt % lpr);
@@ -395,84 +408,88 @@ __global__ void last_fwd_kernel(LastFwdArgs a, int lpr) {
     const int g = a.row_task[s];
     const int r_in = (int)(s - a.row_offsets[g]);
     const int n_real = a.real_offsets[g + 1] - a.real_offsets[g];
+    T* const d = a.d ? reinterpret_cast<T*>(a.d) + s * a.ld : nullptr;
     if (r_in >= n_real) {  // pad row
         if (lane == 0) {
             a.delta_out[s] = 0.f;
             if (a.z_out) a.z_out[s] = 0.f;
             if (a.loss_out) a.loss_out[s] = 0.f;
         }
+        const float zero[8] = {};
+        if (d)
+            for (int n = lane * 8; n < a.N; n += lpr * 8) store8(d + n, zero);
         return;
     }
     const float* w = a.w + (int64_t)g * a.gW;
+    const float* tw = a.ta ? a.tw + (int64_t)g * a.gTW : nullptr;
     const T* x = reinterpret_cast<const T*>(a.a) + s * a.ld;
+    const T* tx = a.ta ? reinterpret_cast<const T*>(a.ta) + s * a.ld : nullptr;
     float acc = 0.f;
-    // bf16 rows whose width and stride are multiples of 8: 16-byte loads (pad columns hold zeros on both sides)
-    const bool vec = sizeof(T) == 2 && (a.N % 8 == 0) && (a.ld % 8 == 0) && (a.gW % 4 == 0) && (!a.ta || a.gTW % 4 == 0) &&
-                     reinterpret_cast<uintptr_t>(a.w) % 16 == 0 && (!a.ta || reinterpret_cast<uintptr_t>(a.tw) % 16 == 0);
-    if (vec) {
-        const bf16_t* xb = reinterpret_cast<const bf16_t*>(x);
-        const bf16_t* txb = a.ta ? reinterpret_cast<const bf16_t*>(a.ta) + s * a.ld : nullptr;
-        const float* tw = a.ta ? a.tw + (int64_t)g * a.gTW : nullptr;
-        for (int n = lane * 8; n < a.N; n += lpr * 8) {
-            float xv[8], wv[8];
-            load8(xb + n, xv);
-            load8(w + n, wv);
-            if (!a.ta) {
+    for (int n = lane * 8; n < a.N; n += lpr * 8) {
+        float xv[8], wv[8];
+        load8(x + n, xv);
+        load8(w + n, wv);
+        if (!tx) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) acc = fmaf(xv[k], wv[k], acc);
-            } else {
-                float tv[8], twv[8];
-                load8(txb + n, tv);
-                load8(tw + n, twv);
+            for (int k = 0; k < 8; ++k) acc = fmaf(xv[k], wv[k], acc);
+        } else {
+            float tv[8], twv[8];
+            load8(tx + n, tv);
+            load8(tw + n, twv);
 #pragma unroll
-                for (int k = 0; k < 8; ++k) acc += tv[k] * wv[k] + xv[k] * twv[k];
-            }
+            for (int k = 0; k < 8; ++k) acc += tv[k] * wv[k] + xv[k] * twv[k];
         }
-    } else if (!a.ta) {
-        for (int n = lane; n < a.N; n += 64) acc = fmaf(ldf(x, n), w[n], acc);
-    } else {
-        const T* tx = reinterpret_cast<const T*>(a.ta) + s * a.ld;
-        const float* tw = a.tw + (int64_t)g * a.gTW;
-        for (int n = lane; n < a.N; n += 64) acc += ldf(tx, n) * w[n] + ldf(x, n) * tw[n];
     }
-    for (int d = lpr >> 1; d > 0; d >>= 1) acc += __shfl_xor(acc, d, 64);   // within the row's lanes
-    if (lane != 0) return;
+    for (int m = lpr >> 1; m > 0; m >>= 1) acc += __shfl_xor(acc, m, 64);   // within the row's lanes: all of them hold the sum
     const float inv_n = 1.f / (float)n_real;
-    if (!a.ta) {
-        const float z = acc + a.b[(int64_t)g * a.gW];
+    const float z = tx ? a.z_in[s] : acc + a.b[(int64_t)g * a.gW];
+    const float e = __expf(-fabsf(z));
+    const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
+    float delta, delta2 = 0.f;
+    if (!tx) {
         const float y = a.labels[a.real_offsets[g] + r_in];
-        const float e = __expf(-fabsf(z));
-        const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-        if (a.z_out) a.z_out[s] = z;
-        a.delta_out[s] = (sig - y) * inv_n;
-        if (a.loss_out) a.loss_out[s] = (fmaxf(z, 0.f) - y * z + log1pf(e)) * inv_n;
+        delta = (sig - y) * inv_n;
+        if (lane == 0) {
+            if (a.z_out) a.z_out[s] = z;
+            if (a.loss_out) a.loss_out[s] = (fmaxf(z, 0.f) - y * z + log1pf(e)) * inv_n;
+        }
     } else {
-        const float tz = acc + a.tb[(int64_t)g * a.gTW];
-        const float z = a.z_in[s];
-        const float e = __expf(-fabsf(z));
-        const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-        a.delta_out[s] = sig * (1.f - sig) * tz * inv_n;
+        delta = sig * (1.f - sig) * (acc + a.tb[(int64_t)g * a.gTW]) * inv_n;
+        delta2 = a.delta_in[s];
+    }
+    if (lane == 0) a.delta_out[s] = delta;
+    if (!d) return;
+    for (int n = lane * 8; n < a.N; n += lpr * 8) {
+        float xv[8], wv[8], v[8];
+        load8(x + n, xv);
+        load8(w + n, wv);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = delta * wv[k];
+        if (tx) {
+            load8(tw + n, wv);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] += delta2 * wv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (!(xv[k] > 0.f)) v[k] = 0.f;
+        store8(d + n, v);
     }
 }
 
-void launch_last_fwd(hipStream_t st, const LastFwdArgs& a) {
+void launch_last_layer(hipStream_t st, const LastArgs& a) {
     if (a.n <= 0) return;
     int lpr = 64;
-    // the 16-byte path of the kernel (same conditions) reads 8 columns per lane: narrow rows need fewer lanes
-    if (a.bf16 && a.N % 8 == 0 && a.ld % 8 == 0 && a.gW % 4 == 0 && (!a.ta || a.gTW % 4 == 0) &&
-        reinterpret_cast<uintptr_t>(a.w) % 16 == 0 && (!a.ta || reinterpret_cast<uintptr_t>(a.tw) % 16 == 0)) {
-        while (lpr > 8 && (lpr / 2) * 8 >= a.N) lpr /= 2;
-    }
+    while (lpr > 4 && (lpr / 2) * 8 >= a.N) lpr /= 2;
     const dim3 grid((unsigned)((a.n * lpr + 255) / 256));
-    if (a.bf16) hipLaunchKernelGGL(last_fwd_kernel<bf16_t>, grid, dim3(256), 0, st, a, lpr);
-    else hipLaunchKernelGGL(last_fwd_kernel<float>, grid, dim3(256), 0, st, a, lpr);
+    if (a.bf16) hipLaunchKernelGGL(last_layer_kernel<bf16_t>, grid, dim3(256), 0, st, a, lpr);
+    else hipLaunchKernelGGL(last_layer_kernel<float>, grid, dim3(256), 0, st, a, lpr);
 }
 
-template <typename T>
-__global__ void last_bwd_kernel(int64_t n, int N, int64_t ld_a, int64_t ld_d, const int32_t* __restrict__ row_task,
-                                const float* __restrict__ dl, const float* __restrict__ w, int64_t gW,
-                                const float* __restrict__ dl2, const float* __restrict__ w2, int64_t gW2,
-                                const T* __restrict__ act, T* d, float* d_f32) {
+// A model without hidden layers: the gradient w.r.t. the pooled inputs, d[s, c] = dl[s]*w_g[c] (+ dl2[s]*w2_g[c]), c < N
+__global__ void input_delta_kernel(int64_t n, int N, const int32_t* __restrict__ row_task, const float* __restrict__ dl,
+                                   const float* __restrict__ w, int64_t gW, const float* __restrict__ dl2,
+                                   const float* __restrict__ w2, int64_t gW2, float* d) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n * N) return;
     const int64_t s = i / N;
@@ -480,127 +497,111 @@ __global__ void last_bwd_kernel(int64_t n, int N, int64_t ld_a, int64_t ld_d, co
     const int g = row_task[s];
     float v = dl[s] * w[(int64_t)g * gW + c];
     if (dl2) v += dl2[s] * w2[(int64_t)g * gW2 + c];
-    if (act && !(ldf(act, s * ld_a + c) > 0.f)) v = 0.f;
-    if (d) stf(d, s * ld_d + c, v);
-    if (d_f32) d_f32[s * ld_d + c] = v;
+    d[i] = v;
 }
-
-// bf16 rows, 8 columns per thread (N, strides and the weight strides allow 16-byte accesses)
-__global__ void last_bwd_vec_kernel(int64_t n, int N, int64_t ld_a, int64_t ld_d, const int32_t* __restrict__ row_task,
-                                    const float* __restrict__ dl, const float* __restrict__ w, int64_t gW,
-                                    const float* __restrict__ dl2, const float* __restrict__ w2, int64_t gW2,
-                                    const bf16_t* __restrict__ act, bf16_t* d, float* d_f32) {
-    const int per_row = N / 8;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * per_row) return;
-    const int64_t s = i / per_row;
-    const int c = (int)(i - s * per_row) * 8;
-    const int g = row_task[s];
-    float wv[8], v[8];
-    load8(w + (int64_t)g * gW + c, wv);
-    const float a1 = dl[s];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = a1 * wv[k];
-    if (dl2) {
-        load8(w2 + (int64_t)g * gW2 + c, wv);
-        const float a2 = dl2[s];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] += a2 * wv[k];
-    }
-    if (act) {
-        float av[8];
-        load8(act + s * ld_a + c, av);
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (!(av[k] > 0.f)) v[k] = 0.f;
-    }
-    if (d) *reinterpret_cast<uint4*>(d + s * ld_d + c) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
-    if (d_f32) {
-        *reinterpret_cast<float4*>(d_f32 + s * ld_d + c) = make_float4(v[0], v[1], v[2], v[3]);
-        *reinterpret_cast<float4*>(d_f32 + s * ld_d + c + 4) = make_float4(v[4], v[5], v[6], v[7]);
-    }
-}
-
-// d[s,n] = (dl[s]*w_g[n] (+ dl2[s]*w2_g[n])) * (act[s,n] > 0); act null: no mask.  Output in the
-// activation type (d) and/or fp32 (d_f32).
-void launch_last_bwd(hipStream_t st, int bf16, int64_t n, int N, int64_t ld_a, int64_t ld_d, const int32_t* row_task,
-                     const float* dl, const float* w, int64_t gW, const float* dl2, const float* w2, int64_t gW2,
-                     const void* act, void* d, float* d_f32) {
+void launch_input_delta(hipStream_t st, int64_t n, int N, const int32_t* row_task, const float* dl, const float* w, int64_t gW,
+                        const float* dl2, const float* w2, int64_t gW2, float* d) {
     if (n <= 0 || N <= 0) return;
-    const dim3 grid((unsigned)((n * N + 255) / 256));
-    if (bf16 && N % 8 == 0 && ld_a % 8 == 0 && ld_d % 8 == 0 && gW % 4 == 0 && (!dl2 || gW2 % 4 == 0) &&
-        reinterpret_cast<uintptr_t>(w) % 16 == 0 && (!w2 || reinterpret_cast<uintptr_t>(w2) % 16 == 0))
-        hipLaunchKernelGGL(last_bwd_vec_kernel, dim3((unsigned)((n * (N / 8) + 255) / 256)), dim3(256), 0, st, n, N, ld_a, ld_d,
-                           row_task, dl, w, gW, dl2, w2, gW2, (const bf16_t*)act, (bf16_t*)d, d_f32);
-    else if (bf16)
-        hipLaunchKernelGGL(last_bwd_kernel<bf16_t>, grid, dim3(256), 0, st, n, N, ld_a, ld_d, row_task, dl, w, gW, dl2,
-                           w2, gW2, (const bf16_t*)act, (bf16_t*)d, d_f32);
-    else
-        hipLaunchKernelGGL(last_bwd_kernel<float>, grid, dim3(256), 0, st, n, N, ld_a, ld_d, row_task, dl, w, gW, dl2, w2,
-                           gW2, (const float*)act, (float*)d, d_f32);
+    hipLaunchKernelGGL(input_delta_kernel, dim3((unsigned)((n * N + 255) / 256)), dim3(256), 0, st, n, N, row_task, dl, w, gW,
+                       dl2, w2, gW2, d);
 }
 
 // ------------------------------------------------------------------------------------------------
-// cross-task reduction of the dense meta-gradient (Alg. 1, global back-propagation on theta; Sec. 2.1.3):
-// out[j] (+)= sum_g v[g, j], tasks added in task order; with a scale other than 1: out[j] (+)= scale * (sum_g v[g, j])
+// cross-task reduction of the dense meta-gradient (Alg. 1, global back-propagation on theta; Sec. 2.1.3), the pieces of
+// theta in one launch: out[j] (+)= sum_g v[g, j] + scale * sum_r vsum[r, j], tasks (and runs of tasks) added in order
 // ------------------------------------------------------------------------------------------------
-__global__ void reduce_tasks_kernel(const float* __restrict__ v, int64_t ld, int G, int64_t n, float* out,
-                                    int accumulate, float scale) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    // eight tasks' values are requested before the first is added (the order of the sum stays the task order)
-    float acc = (accumulate && scale == 1.f) ? out[j] : 0.f;
-    int g = 0;
-    for (; g + 8 <= G; g += 8) {
-        float x[8];
+// Bound: HBM (the tasks' gradients once).  A thread takes four consecutive values of a piece (offsets and lengths are
+// multiples of 32) and requests eight tasks' before it adds the first.
+__global__ __launch_bounds__(256) void reduce_tasks_kernel(ReduceArgs a) {
+    int pi = 0;
+    while (pi + 1 < a.n && (int)blockIdx.x >= a.piece[pi + 1].block0) ++pi;
+    const ReducePiece& p = a.piece[pi];
+    const int64_t i = ((int64_t)((int)blockIdx.x - p.block0) * 256 + threadIdx.x) * 4;
+    if (i >= p.n) return;
+    const int64_t j = p.j0 + i;
+    float4* out = reinterpret_cast<float4*>(a.out + j);
+    float4 acc = a.accumulate ? *out : make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](const float* v, int G, float4 sum) {
+        int g = 0;
+        for (; g + 8 <= G; g += 8) {
+            float4 x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = v[(int64_t)(g + u) * ld + j];
+            for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const float4*>(v + (int64_t)(g + u) * a.ld + j);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += x[u];
+            for (int u = 0; u < 8; ++u) { sum.x += x[u].x; sum.y += x[u].y; sum.z += x[u].z; sum.w += x[u].w; }
+        }
+        for (; g < G; ++g) {
+            const float4 x = *reinterpret_cast<const float4*>(v + (int64_t)g * a.ld + j);
+            sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
+        }
+        return sum;
+    };
+    if (p.G > 0) acc = add(a.v, p.G, acc);
+    if (p.Gsum > 0) {
+        const float4 s = add(a.vsum, p.Gsum, make_float4(0.f, 0.f, 0.f, 0.f));
+        acc.x += a.scale * s.x; acc.y += a.scale * s.y; acc.z += a.scale * s.z; acc.w += a.scale * s.w;
     }
-    for (; g < G; ++g) acc += v[(int64_t)g * ld + j];
-    out[j] = scale == 1.f ? acc : (accumulate ? out[j] : 0.f) + scale * acc;
+    *out = acc;
 }
 
-void launch_reduce_tasks(hipStream_t st, const float* v, int64_t ld, int G, int64_t n, float* out, int accumulate,
-                         float scale) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(reduce_tasks_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, v, ld, G, n, out,
-                       accumulate, scale);
+void launch_reduce_tasks(hipStream_t st, const ReduceArgs& base, const ReducePiece* list, int n) {
+    for (int i0 = 0; i0 < n; i0 += REDUCE_PIECES) {
+        ReduceArgs a = base;
+        a.n = std::min(n - i0, (int)REDUCE_PIECES);
+        int blocks = 0;
+        for (int i = 0; i < a.n; ++i) {
+            a.piece[i] = list[i0 + i];
+            a.piece[i].block0 = blocks;
+            blocks += (int)((a.piece[i].n + 1023) / 1024);
+        }
+        if (blocks > 0) hipLaunchKernelGGL(reduce_tasks_kernel, dim3(blocks), dim3(256), 0, st, a);
+    }
 }
 
-__global__ void fill_sample_task_kernel(const int32_t* row_offsets, int32_t* sample_task) {
+// Per-row tables from per-task offsets, several at once: row off[g] + i of task g gets g, or first[g] + i
+__global__ void expand_tasks_kernel(ExpandJobs jobs) {
+    const ExpandJob& j = jobs.job[blockIdx.y];
     const int g = blockIdx.x;
-    for (int s = row_offsets[g] + threadIdx.x; s < row_offsets[g + 1]; s += blockDim.x) sample_task[s] = g;
+    const int64_t lo = j.off64 ? j.off64[g] : j.off32[g], hi = j.off64 ? j.off64[g + 1] : j.off32[g + 1];
+    for (int64_t s = lo + threadIdx.x; s < hi; s += blockDim.x) j.out[s] = j.first ? j.first[g] + (int32_t)(s - lo) : g;
 }
-void launch_fill_sample_task(hipStream_t st, const int32_t* row_offsets, int G, int32_t* sample_task) {
-    if (G <= 0) return;
-    hipLaunchKernelGGL(fill_sample_task_kernel, dim3(G), dim3(256), 0, st, row_offsets, sample_task);
+void launch_expand_tasks(hipStream_t st, int G, const ExpandJobs& jobs) {
+    if (G <= 0 || jobs.n <= 0) return;
+    hipLaunchKernelGGL(expand_tasks_kernel, dim3(G, jobs.n), dim3(256), 0, st, jobs);
 }
 
-// W [din, dout] row-major  <->  padded [ld_in, ld_out] (pad rows / columns zero)
-__global__ void pack_weights_kernel(const float* W, int din, int dout, int ld_in, int ld_out, float* dst) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)ld_in * ld_out) return;
-    const int r = (int)(i / ld_out), c = (int)(i % ld_out);
-    dst[i] = (r < din && c < dout) ? W[(int64_t)r * dout + c] : 0.f;
+// Matrices between row-major and padded form, all layers' in one launch (the launch is what bounds it): dst [rows, cols]
+// with leading dimension ld_dst takes src [src_rows, src_cols] with ld_src and zeros around it, and a bf16 copy
+__global__ __launch_bounds__(256) void copy_matrices_kernel(MatrixJobs jobs) {
+    int ji = 0;
+    while (ji + 1 < jobs.n && (int)blockIdx.x >= jobs.job[ji + 1].block0) ++ji;
+    const MatrixJob& m = jobs.job[ji];
+    const int64_t e0 = (int64_t)((int)blockIdx.x - m.block0) * 1024, n = (int64_t)m.rows * m.cols;
+    const int r0 = (int)(e0 / m.cols);
+    const u32 c0 = (u32)(e0 - (int64_t)r0 * m.cols);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const u32 o = c0 + threadIdx.x + u * 256, dr = o / (u32)m.cols;
+        if (e0 + threadIdx.x + u * 256 >= n) break;
+        const int64_t r = r0 + (int64_t)dr;
+        const int c = (int)(o - dr * (u32)m.cols);
+        const float v = r < m.src_rows && c < m.src_cols ? m.src[r * m.ld_src + c] : 0.f;
+        m.dst[r * m.ld_dst + c] = v;
+        if (m.dst_bf) m.dst_bf[r * m.ld_dst + c] = f2bf(v);
+    }
 }
-void launch_pack_weights(hipStream_t st, const float* W, int din, int dout, int ld_in, int ld_out, float* dst) {
-    const int64_t n = (int64_t)ld_in * ld_out;
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, din, dout, ld_in,
-                       ld_out, dst);
-}
-__global__ void unpack_weights_kernel(const float* src, int din, int dout, int ld_out, float* W) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)din * dout) return;
-    const int r = (int)(i / dout), c = (int)(i % dout);
-    W[i] = src[(int64_t)r * ld_out + c];
-}
-void launch_unpack_weights(hipStream_t st, const float* src, int din, int dout, int ld_out, float* W) {
-    const int64_t n = (int64_t)din * dout;
-    if (n <= 0) return;
-    hipLaunchKernelGGL(unpack_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, din, dout,
-                       ld_out, W);
+void launch_copy_matrices(hipStream_t st, const MatrixJob* list, int n) {
+    for (int i0 = 0; i0 < n; i0 += MATRIX_JOBS) {
+        MatrixJobs a;
+        a.n = std::min(n - i0, (int)MATRIX_JOBS);
+        int64_t blocks = 0;
+        for (int i = 0; i < a.n; ++i) {
+            a.job[i] = list[i0 + i];
+            a.job[i].block0 = (int)blocks;
+            blocks += ((int64_t)a.job[i].rows * a.job[i].cols + 1023) / 1024;
+        }
+        if (blocks > 0) hipLaunchKernelGGL(copy_matrices_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+    }
 }
 
 __global__ void axpy_kernel(int64_t n, float a, const float* __restrict__ x, float* y) {
