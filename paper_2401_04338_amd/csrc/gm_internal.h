@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 typedef uint32_t u32;
 typedef uint64_t u64;
 typedef uint16_t bf16_t;  // raw bfloat16 bits
@@ -220,15 +222,26 @@ struct PairHopOut {
     float c;
 };
 struct PairHopArgs {
-    int F, D, row_blocks, n_out, n_work;      // row_blocks, n_out (enabled out sets) and n_work (workgroups) are set by the launcher
+    int F, D;
     const uint8_t* mat;
     const int32_t *in_real_off, *in_row_off;  // the in set
     const float* Z;                           // [rows, ldz], the (field f) block at column f*D
     int64_t ldz;
-    PairHopOut out[2];
+    PairHopOut out[2];                        // support, query
     const u32* task_path;                     // [Tw] only tasks flagged 1 are touched
+    const int32_t* small; int n_small;        // tasks of at most 64 rows in both sets
+    const int32_t* tiles;                     // set by the launcher
 };
-void launch_pair_hop(hipStream_t st, PairHopArgs a, int Tw, int max_out_rows);
+// The work of a hop over the tasks of a wave, by the outputs asked for: the small tasks, and the tiles of 256 out-rows of the
+// others as eight lists (one per XCD; nine offsets, then the entries: task, which enabled output << 16, tile << 17).
+enum { HOP_BOTH = 0, HOP_SUPPORT = 1, HOP_QUERY = 2 };
+struct HopTask { int32_t t, ns, nq; };        // (task numbers below 65536, rows below 2^22)
+struct HopPlan {
+    std::vector<int32_t> small, tiles[3];
+    int longest[3] = {0, 0, 0};               // entries of the longest of the eight lists
+};
+HopPlan hop_plan(const std::vector<HopTask>& tasks);
+void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3], const int longest[3]);
 void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_rows, float* x_out, int ldx, bf16_t* x_bf);
 
 // keys: the sorted row keys; scan: exclusive scan of their segment-head flags and n_rows: the number of segments

@@ -256,7 +256,7 @@ enum { COARSE_GROUPS = 32 };   // most runs of tasks (gm_configure "coarse_group
 
 struct WaveBufs {
     int32_t *row_off_s, *row_off_q, *real_off_s, *real_off_q;
-    int32_t *sample_task_s, *sample_task_q, *row_task_s, *row_task_q;
+    int32_t *row_task_s, *row_task_q;
     int32_t *tile_g_s, *tile_m_s, *tile_g_q, *tile_m_q;
     u32 *cnt_s, *base_s, *cnt_q, *base_q, *n_slots, *scan_tmp;
     u32* slot_rows;
@@ -283,6 +283,8 @@ struct WaveBufs {
     // pair-count matrices of the wave (null when the sparse kernel does the row arithmetic)
     uint8_t* pair_mat;
     int64_t *pair_off_ss, *pair_off_qs, *pair_off_sq;
+    int32_t *hop_small = nullptr, *hop_tiles[3] = {nullptr, nullptr, nullptr};   // the hops' work lists (HopPlan)
+    int hop_longest[3] = {0, 0, 0}, n_hop_small = 0;
     u32* task_path;   // [Tw] 1: pair-count path, 0: sparse kernel (the counting kernel clears it on overflow)
     // table-shaped sparse output only: the wave's own gradient buffer (support rows, then query rows) and sort
     float* GX = nullptr;
@@ -298,6 +300,7 @@ struct WaveDims {
     bool any_sparse = false;               // some task of the wave takes the sparse kernel
     bool pair_ss = false, pair_sq = false; // which kinds besides query x support
     int64_t pair_bytes = 0;
+    int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of all tasks (an upper bound on the hops' work lists)
     bool table = false;                    // the sparse gradient is reduced wave by wave into a table-shaped output
 };
 
@@ -355,9 +358,10 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.pair_off_ss = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_qs = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_sq = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
+    w.hop_small = d.pair ? ar.get<int32_t>(d.Tw + 1) : nullptr;
+    for (int k = 0; k < 3; ++k)
+        w.hop_tiles[k] = d.pair ? ar.get<int32_t>(9 + (k == HOP_QUERY ? 0 : d.hop_tiles_s) + (k == HOP_SUPPORT ? 0 : d.hop_tiles_q)) : nullptr;
     // (down to here: filled by setup_wave, in one copy)
-    w.sample_task_s = ar.get<int32_t>(d.Ss + 1);
-    w.sample_task_q = ar.get<int32_t>(d.Sq + 1);
     w.row_task_s = ar.get<int32_t>(d.Ps + 1);
     w.row_task_q = ar.get<int32_t>(d.Pq + 1);
     w.cnt_s = ar.get<u32>(TF + 1);
@@ -736,6 +740,8 @@ extern "C" size_t gm_workspace_bytes(const gm_model_desc* model, int32_t n_tasks
             d.pair = true;
             d.pair_ss = inner_steps >= 2;
             d.pair_sq = order == 2;
+            d.hop_tiles_s = n_tasks * ((ns + 255) / 256);
+            d.hop_tiles_q = n_tasks * ((nq + 255) / 256);
             d.pair_bytes = (int64_t)n_tasks * c.F * ((d.pair_ss ? ps * ps : 0) + pq * ps * (d.pair_sq ? 2 : 1));
         }
     }
@@ -1460,8 +1466,11 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
     WaveDims d;
     d.table = B.table;
     for (int t = p.t0; t < p.t1; ++t) {
-        if (task_pair_ok(c, B, t, K)) d.pair = true;
-        else d.any_sparse = true;
+        if (task_pair_ok(c, B, t, K)) {
+            d.pair = true;
+            d.hop_tiles_s += (B.sup->task_offsets[t + 1] - B.sup->task_offsets[t] + 255) / 256;
+            d.hop_tiles_q += (B.qry->task_offsets[t + 1] - B.qry->task_offsets[t] + 255) / 256;
+        } else d.any_sparse = true;
     }
     if (d.pair) {
         d.pair_ss = K >= 2;
@@ -1610,10 +1619,21 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
     pair_layout(c, B, wp, K, d.pair_ss, d.pair_sq, &po_ss, &po_qs, &po_sq, &path);
     up.put(w.task_path, path);
     if (d.pair) { up.put(w.pair_off_ss, po_ss); up.put(w.pair_off_qs, po_qs); up.put(w.pair_off_sq, po_sq); }
+    if (d.pair) {
+        std::vector<HopTask> tasks;
+        for (int t = 0; t < d.Tw; ++t)
+            if (path[t]) tasks.push_back(HopTask{t, re_s[t + 1] - re_s[t], re_q[t + 1] - re_q[t]});
+        const HopPlan plan = hop_plan(tasks);
+        w.n_hop_small = (int)plan.small.size();
+        up.put(w.hop_small, plan.small);
+        for (int k = 0; k < 3; ++k) {
+            w.hop_longest[k] = plan.longest[k];
+            up.put(w.hop_tiles[k], plan.tiles[k]);
+        }
+    }
     const int rc = up.send(c, B.images);
     if (rc != GM_OK) return rc;
-    launch_expand_tasks(st, d.Tw, ExpandJobs{4, {{nullptr, w.real_off_s, nullptr, w.sample_task_s}, {nullptr, w.real_off_q, nullptr, w.sample_task_q},
-                                                 {nullptr, w.row_off_s, nullptr, w.row_task_s}, {nullptr, w.row_off_q, nullptr, w.row_task_q}}});
+    launch_expand_tasks(st, d.Tw, ExpandJobs{2, {{nullptr, w.row_off_s, nullptr, w.row_task_s}, {nullptr, w.row_off_q, nullptr, w.row_task_q}}});
     gs = Grp{w.row_off_s, w.real_off_s, w.row_task_s, w.tile_g_s, w.tile_m_s, d.mt_s, d.Tw, bm, d.Ps};
     gq = Grp{w.row_off_q, w.real_off_q, w.row_task_q, w.tile_g_q, w.tile_m_q, d.mt_q, d.Tw, bm, d.Pq};
     return GM_OK;
@@ -1933,8 +1953,9 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 };
                 if (o0) fill(pa.out[0], *o0, true);
                 if (o1) fill(pa.out[1], *o1, false);
+                pa.small = w.hop_small; pa.n_small = w.n_hop_small;
                 Prof p(c, "pair_hop", alg_bytes, 0);
-                launch_pair_hop(st, pa, Tw, max_bags);
+                launch_pair_hop(st, pa, w.hop_tiles, w.hop_longest);
             }
             if (!any_sparse) return;
             TwoHopArgs a;

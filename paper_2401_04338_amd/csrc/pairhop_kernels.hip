@@ -17,6 +17,8 @@
 // as it would in an fp32 loop.
 //
 // Counts above 255 or tasks too large for this path are handled by the sparse two-hop kernel instead.
+#include <algorithm>
+
 #include "gm_internal.h"
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 ph_short8;
@@ -311,12 +313,21 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 // ------------------------------------------------------------------------------------------------
 // the hop: Y = Y_in + c * M * Z on MFMA 32x32x16 (bf16 operands, fp32 accumulation)
 //
-// One workgroup of 4 waves owns (task, field, DS columns, 256 out-rows); each wave owns 64 of the rows
-// (two 32-row strips).  Z is staged 64 rows at a time: split into its three bf16 pieces and stored
-// contraction-contiguous per column, so that a B fragment is one 16-byte LDS read.  M is read
-// straight from memory: within a 64-wide chunk the lane half h contracts columns [32h, 32h+32) of the
-// chunk (the contraction index may be enumerated in any order as long as A and B agree), which makes
-// a lane's share of a strip 32 contiguous bytes of one row of M.
+// Z is staged 64 rows at a time: split into its three bf16 pieces and stored contraction-contiguous per column, so that
+// a B fragment is one 16-byte LDS read.  M is read straight from memory: within a 64-wide chunk the lane half h contracts
+// columns [32h, 32h+32) of the chunk (the contraction index may be enumerated in any order as long as A and B agree),
+// which makes a lane's share of a strip 32 contiguous bytes of one row of M.
+//
+// Bound: HBM (M, Z, Y read, Y written) for tasks of 256 rows; with uneven or small tasks it was workgroups that had
+// nothing to do, waves that multiplied rows of no one and one XCD with the large tasks.  So the work is a list made from the
+// task sizes (hop_plan):
+//   tasks of at most 64 rows in both sets   one workgroup per (task, field, DS columns) takes both outputs from one staged Z
+//   the others                              tiles of 256 out-rows; a last tile of at most 128 (64) rows gives every wave one
+//                                           strip of 32 rows (and half the columns).  The tasks are dealt to the XCDs by
+//                                           size, largest first, a task's tiles to one XCD (they read the same rows of Z).
+// Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
+// 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
+// (256 + 256) rows x 26 fields 6.7 -> 6.6 ms, 4.8 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
 // ------------------------------------------------------------------------------------------------
 #define PH_KC 64
 
@@ -336,76 +347,36 @@ __device__ __forceinline__ void ph_cvt4(u32 x, u32& lo, u32& hi) {
 // one group) and the staging writes (every fourth column, one group) spread over all banks.
 __device__ __forceinline__ int ph_key(int col) { return ((col >> 1) + (col >> 4)) & 7; }
 
+// One workgroup's share of a 64-row chunk of Z: DS/16 rows of four columns per thread.
 template <int DS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_hop_kernel(PairHopArgs a) {
-    constexpr int NCT = DS / 32;      // 32-column tiles
-    constexpr int CG = DS / 4;        // float4 column groups of a row of Z
-    constexpr int RPT = CG / 4;       // rows of the 64-row chunk staged per thread (256 threads)
-    __shared__ __attribute__((aligned(16))) bf16_t zs[2 * 3 * DS * PH_KC];
-    // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2): re-number them so that the
-    // workgroups of one (task, field, column slice) -- both out sets, all row blocks: they read the same rows of
-    // Z -- are consecutive on one XCD.
-    const int nsl = a.D / DS;
-    const int per_xcd = gridDim.x >> 3;
-    const int wid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (wid >= a.n_work) return;
-    const int nz = a.n_out * a.row_blocks, fx = a.F * nsl;
-    const int zi = wid % nz, rest = wid / nz;
-    const int fs = rest % fx, t = rest / fx;
-    const int f = fs / nsl, sl = fs - f * nsl;
-    const int o = zi / a.row_blocks, rb = zi - o * a.row_blocks;
-    const PairHopOut& out = a.out[o];
-    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t];
-    const int n_out = out.real_off[t + 1] - out.real_off[t];
-    if (rb * 256 >= n_out || !a.task_path[t]) return;
-    const int colsP = pad64(n_in), rowsP = pad64(n_out);
-    const uint8_t* M = a.mat + out.mat_off[t] + (size_t)f * rowsP * colsP;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
-    const int row_w = rb * 256 + wv * 64;             // first out-row of this wave
-    const bool wave_on = row_w < n_out;               // both strips then lie inside the padded matrix
-    const int cg = threadIdx.x % CG, rg = threadIdx.x / CG;
-    const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
-    const float* Zt = a.Z + (int64_t)a.in_row_off[t] * a.ldz + colz + cg * 4;
-    // a wave without rows multiplies rows 0..63 (valid memory) and stores nothing: the loop stays free of branches
-    const uint8_t* Mw = M + (size_t)((wave_on ? row_w : 0) + ln) * colsP + h * 32;
-
-    int wr_off[4];   // element offsets of this thread's staging writes, per column of its float4
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc) {
-        const int col = cg * 4 + cc, k0 = rg * RPT;
-        wr_off[cc] = col * PH_KC + (((k0 >> 3) ^ ph_key(col)) << 3) + (k0 & 7);
-    }
-    int rd_key[NCT];
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) rd_key[ct] = ph_key(ct * 32 + ln);
-
-    ph_float16 acc[2][NCT];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[s][ct][v] = 0.f;
-
+struct HopStage {
+    static constexpr int CG = DS / 4;        // float4 column groups of a row of Z
+    static constexpr int RPT = CG / 4;       // rows of the 64-row chunk staged per thread (256 threads)
+    static constexpr int WORDS = 3 * DS * PH_KC;   // bf16 values of a staged chunk
+    int rg, wr_off[4];   // element offsets of this thread's staging writes, per column of its float4
+    const float* Zt;
+    int64_t ldz;
+    int n_in;
     float4 z[RPT];
-    uint4 araw[2][2], anext[2][2];
-    auto load_z = [&](int kc) {
+    __device__ __forceinline__ HopStage(const float* Z0, int64_t ldz_, int n_in_) : ldz(ldz_), n_in(n_in_) {
+        const int cg = threadIdx.x % CG;
+        rg = threadIdx.x / CG;
+        Zt = Z0 + cg * 4;
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) {
+            const int col = cg * 4 + cc, k0 = rg * RPT;
+            wr_off[cc] = col * PH_KC + (((k0 >> 3) ^ ph_key(col)) << 3) + (k0 & 7);
+        }
+    }
+    __device__ __forceinline__ void load(int kc) {
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {   // branch-free: a row beyond the task reads the task's last row and is zeroed
             const int row = kc + rg * RPT + r;
-            z[r] = *reinterpret_cast<const float4*>(Zt + (int64_t)min(row, n_in - 1) * a.ldz);
+            z[r] = *reinterpret_cast<const float4*>(Zt + (int64_t)min(row, n_in - 1) * ldz);
         }
-    };
-    auto load_a = [&](int kc, uint4 (&dst)[2][2]) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const uint4* src = reinterpret_cast<const uint4*>(Mw + (size_t)(s * 32) * colsP + kc);
-            dst[s][0] = src[0];
-            dst[s][1] = src[1];
-        }
-    };
-    // splits the staged rows into their three bf16 pieces and writes them into one LDS buffer
-    auto stage = [&](bf16_t* buf, int kc) {
+    }
+    // splits the loaded rows into their three bf16 pieces and writes them into an LDS buffer
+    __device__ __forceinline__ void store(bf16_t* buf, int kc) const {
         u32 p0[4][RPT], p1[4][RPT], p2[4][RPT];  // [column][row]: the three pieces as fp32 bit patterns
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
@@ -435,103 +406,266 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                 *reinterpret_cast<u32*>(d2) = ph_pack_hi(p2[cc][0], p2[cc][1]);
             }
         }
+    }
+};
+
+// one staged chunk times NS strips of counts, for NC column tiles from column tile ct0 on
+template <int DS, int NS, int NC>
+__device__ __forceinline__ void hop_multiply(const bf16_t* zb, const uint4 (&araw)[NS][2], int ct0, ph_float16 (&acc)[NS][NC]) {
+    const int lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        ph_short8 af[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint4 q = araw[s][ks >> 1];
+            const u32 b0 = (ks & 1) ? q.z : q.x, b1 = (ks & 1) ? q.w : q.y;
+            u32 w0, w1, w2, w3;
+            ph_cvt4(b0, w0, w1);
+            ph_cvt4(b1, w2, w3);
+            const uint4 packed = make_uint4(w0, w1, w2, w3);
+            af[s] = __builtin_bit_cast(ph_short8, packed);
+        }
+        ph_short8 bfrag[NC][3];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int col = (ct0 + c) * 32 + ln;
+            const bf16_t* src = zb + col * PH_KC + (((h * 4 + ks) ^ ph_key(col)) << 3);
+#pragma unroll
+            for (int sp = 0; sp < 3; ++sp) bfrag[c][sp] = *reinterpret_cast<const ph_short8*>(src + sp * DS * PH_KC);
+        }
+#pragma unroll
+        for (int sp = 2; sp >= 0; --sp)  // smallest pieces first
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    acc[s][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s], bfrag[c][sp], acc[s][c], 0, 0, 0);
+    }
+}
+
+// Rows [row0, row0 + 32) and one column tile of the output; D layout of the 32x32 tile: register v of lane (ln, h) is
+// row 8*(v/4) + 4*h + v%4, column ln.  (y_in may be y_out: a tile's loads are issued together, ahead of its stores.)
+__device__ __forceinline__ void hop_read_y(const PairHopOut& out, int64_t base, int row0, int n_out, float (&y)[16]) {
+    const int h = (threadIdx.x & 63) >> 5, ld = (int)out.ld;
+    const float* src = out.y_in ? out.y_in + base : nullptr;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int rl = 8 * (v >> 2) + 4 * h + (v & 3);
+        y[v] = (src && row0 + rl < n_out) ? src[rl * ld] : 0.f;
+    }
+}
+__device__ __forceinline__ void hop_write_y(const PairHopOut& out, int64_t base, int row0, int n_out, const float (&y)[16], const ph_float16& acc) {
+    const int h = (threadIdx.x & 63) >> 5, ld = (int)out.ld;
+    float* yo = out.y_out ? out.y_out + base : nullptr;
+    bf16_t* yb = out.y_bf ? out.y_bf + base : nullptr;
+    const float c = out.c;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int rl = 8 * (v >> 2) + 4 * h + (v & 3);
+        if (row0 + rl >= n_out) continue;
+        const float r = y[v] + c * acc[v];
+        if (yo) yo[rl * ld] = r;
+        if (yb) yb[rl * ld] = f2bf(r);
+    }
+}
+
+// A tile of up to 64 * NS * 2 out-rows from row0 on.  NS strips per wave, NC column tiles per wave: with fewer than all of
+// them the waves lie side by side along the columns.
+template <int DS, int NS, int NC>
+__device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M, const float* Z0, int64_t ldz, int n_in, int n_out, int row0,
+                                         int64_t row_base, int64_t colz, bf16_t* zs) {
+    constexpr int WC = DS / 32 / NC;   // waves along the columns
+    const int colsP = pad64(n_in);
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
+    const int ct0 = (wv % WC) * NC, row_w = row0 + (wv / WC) * 32 * NS;   // first out-row of this wave
+    const bool wave_on = row_w < n_out;               // its strips then lie inside the padded matrix
+    const uint8_t* Mw = M + (size_t)(row_w + ln) * colsP + h * 32;
+    HopStage<DS> st(Z0, ldz, n_in);
+    ph_float16 acc[NS][NC];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[s][c][v] = 0.f;
+    uint4 araw[NS][2], anext[NS][2];
+    auto load_a = [&](int kc, uint4 (&dst)[NS][2]) {
+        if (!wave_on) return;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint4* src = reinterpret_cast<const uint4*>(Mw + (size_t)(s * 32) * colsP + kc);
+            dst[s][0] = src[0];
+            dst[s][1] = src[1];
+        }
     };
     // Two LDS buffers: while chunk c is multiplied out of one, chunk c+1 (loaded during the multiplication) is
     // split into the other; one barrier per chunk.
     if (colsP > 0) {
-        load_z(0);
+        st.load(0);
         load_a(0, araw);
-        stage(zs, 0);
+        st.store(zs, 0);
     }
     __syncthreads();
     int cur = 0;
     for (int kc = 0; kc < colsP; kc += PH_KC) {
-        const int kn = kc + PH_KC < colsP ? kc + PH_KC : kc;   // the last chunk loads itself again: no branches
-        load_z(kn);
-        load_a(kn, anext);
-        __builtin_amdgcn_sched_barrier(0);   // the loads above are consumed only after the multiplication below
-        const bf16_t* zb = zs + cur * (3 * DS * PH_KC);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            ph_short8 af[2];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const uint4 q = araw[s][ks >> 1];
-                const u32 b0 = (ks & 1) ? q.z : q.x, b1 = (ks & 1) ? q.w : q.y;
-                u32 w0, w1, w2, w3;
-                ph_cvt4(b0, w0, w1);
-                ph_cvt4(b1, w2, w3);
-                const uint4 packed = make_uint4(w0, w1, w2, w3);
-                af[s] = __builtin_bit_cast(ph_short8, packed);
-            }
-            ph_short8 bfrag[NCT][3];
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) {
-                const bf16_t* src = zb + (ct * 32 + ln) * PH_KC + (((h * 4 + ks) ^ rd_key[ct]) << 3);
-#pragma unroll
-                for (int sp = 0; sp < 3; ++sp) bfrag[ct][sp] = *reinterpret_cast<const ph_short8*>(src + sp * DS * PH_KC);
-            }
-#pragma unroll
-            for (int sp = 2; sp >= 0; --sp)  // smallest pieces first
-#pragma unroll
-                for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-                    for (int s = 0; s < 2; ++s)
-                        acc[s][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s], bfrag[ct][sp], acc[s][ct], 0, 0, 0);
+        const int kn = kc + PH_KC;
+        if (kn < colsP) {
+            st.load(kn);
+            load_a(kn, anext);
         }
+        __builtin_amdgcn_sched_barrier(0);   // the loads above are consumed only after the multiplication below
+        if (wave_on) hop_multiply<DS, NS, NC>(zs + cur * HopStage<DS>::WORDS, araw, ct0, acc);
         __builtin_amdgcn_sched_barrier(0);
-        cur ^= 1;
-        stage(zs + cur * (3 * DS * PH_KC), kn);
+        if (kn < colsP) {
+            cur ^= 1;
+            st.store(zs + cur * HopStage<DS>::WORDS, kn);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) { araw[s][0] = anext[s][0]; araw[s][1] = anext[s][1]; }
-        __syncthreads();
+            for (int s = 0; s < NS; ++s) { araw[s][0] = anext[s][0]; araw[s][1] = anext[s][1]; }
+            __syncthreads();
+        }
     }
     if (!wave_on) return;
-    // D layout of the 32x32 tile: register v of lane (ln, h) is row 8*(v/4) + 4*h + v%4, column ln
-    const int64_t base = ((int64_t)out.row_off[t] + row_w) * out.ld + colz + ln;
-    const float* yin = out.y_in ? out.y_in + base : nullptr;
-    float* yout = out.y_out ? out.y_out + base : nullptr;
-    bf16_t* ybf = out.y_bf ? out.y_bf + base : nullptr;
-    const int ldo = (int)out.ld;
-    const float cc = out.c;
-    // y_in may be y_out: the loads of a 32x32 tile are issued together, ahead of its stores
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) {
-            float yv[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int rl = s * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                yv[v] = (yin && row_w + rl < n_out) ? yin[rl * ldo + ct * 32] : 0.f;
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int rl = s * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (row_w + rl >= n_out) continue;
-                const int idx = rl * ldo + ct * 32;
-                const float y = yv[v] + cc * acc[s][ct][v];
-                if (yout) yout[idx] = y;
-                if (ybf) ybf[idx] = f2bf(y);
-            }
+        for (int c = 0; c < NC; ++c) {
+            float y[16];
+            const int r = row_w + s * 32;
+            const int64_t base = (row_base + r) * out.ld + colz + (ct0 + c) * 32 + ln;
+            hop_read_y(out, base, r, n_out, y);
+            hop_write_y(out, base, r, n_out, y, acc[s][c]);
         }
 }
 
-void launch_pair_hop(hipStream_t st, PairHopArgs a, int Tw, int max_out_rows) {
-    if (Tw <= 0 || a.F <= 0 || max_out_rows <= 0) return;
-    int n_out = 0;
-    PairHopOut packed[2];
+template <int DS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_hop_kernel(PairHopArgs a) {
+    constexpr int NCT = DS / 32;      // 32-column tiles
+    __shared__ __attribute__((aligned(16))) bf16_t zs[2 * HopStage<DS>::WORDS];
+    // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, the fields of one entry in a row
+    const int nsl = a.D / DS, fx = a.F * nsl;
+    const int xcd = blockIdx.x & 7, k = (int)(blockIdx.x >> 3), e = a.tiles[xcd] + k / fx;
+    if (e >= a.tiles[xcd + 1]) return;
+    const u32 entry = (u32)a.tiles[9 + e];
+    const int t = (int)(entry & 0xFFFFu), o = (int)((entry >> 16) & 1u), row0 = (int)(entry >> 17) * 256;
+    if (!a.task_path[t]) return;
+    const int fs = k % fx, f = fs / nsl, sl = fs - f * nsl;
+    const PairHopOut& out = a.out[o];
+    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], n_out = out.real_off[t + 1] - out.real_off[t];
+    const uint8_t* M = a.mat + out.mat_off[t] + (size_t)f * pad64(n_out) * pad64(n_in);
+    const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
+    const float* Z0 = a.Z + (int64_t)a.in_row_off[t] * a.ldz + colz;
+    const int64_t row_base = out.row_off[t];
+    if (n_out - row0 > 128) hop_tile<DS, 2, NCT>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
+    else if (n_out - row0 > 64) hop_tile<DS, 1, NCT>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
+    else hop_tile<DS, 1, 1>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
+}
+
+// Tasks of at most 64 rows in both sets: one chunk of Z, at most two strips per output.  What is bound here is the chain of
+// dependent reads (task -> offsets -> M, Z and Y -> LDS), so everything is requested at once and half the LDS and registers
+// of the large tiles let twice as many workgroups run side by side.
+template <int DS>
+__global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
+    constexpr int NCT = DS / 32;
+    __shared__ __attribute__((aligned(16))) bf16_t zs[HopStage<DS>::WORDS];
+    const int nsl = a.D / DS, fx = a.F * nsl;
+    const int per_xcd = gridDim.x >> 3, wid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);   // neighbouring fields on one XCD
+    if (wid >= a.n_small * fx) return;
+    const int t = a.small[wid / fx], fs = wid % fx, f = fs / nsl, sl = fs - f * nsl;
+    if (!a.task_path[t]) return;
+    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t];
+    const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
+    const int row_w = (wv >> 1) * 32, ct = wv & 1;
+    uint4 araw[2][1][2];
+    float y[2][16];
+    int n_out[2];
+    int64_t base[2];
+    bool on[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        on[o] = false;
+        n_out[o] = 0;
+        base[o] = 0;
+        if (!a.out[o].enabled) continue;
+        n_out[o] = a.out[o].real_off[t + 1] - a.out[o].real_off[t];
+        on[o] = row_w < n_out[o] && ct < NCT;
+        if (!on[o]) continue;
+        base[o] = ((int64_t)a.out[o].row_off[t] + row_w) * a.out[o].ld + colz + ct * 32 + ln;
+        if (n_in > 0) {
+            const uint4* src = reinterpret_cast<const uint4*>(a.mat + a.out[o].mat_off[t] + ((size_t)f * 64 + row_w + ln) * 64 + h * 32);
+            araw[o][0][0] = src[0];
+            araw[o][0][1] = src[1];
+        }
+    }
+    if (n_in > 0) {
+        HopStage<DS> st(a.Z + (int64_t)a.in_row_off[t] * a.ldz + colz, a.ldz, n_in);
+        st.load(0);
+        st.store(zs, 0);
+    }
+#pragma unroll
     for (int o = 0; o < 2; ++o)
-        if (a.out[o].enabled) packed[n_out++] = a.out[o];
-    if (n_out == 0) return;
-    for (int o = 0; o < n_out; ++o) a.out[o] = packed[o];
-    a.row_blocks = (max_out_rows + 255) / 256;
-    a.n_out = n_out;
+        if (on[o]) hop_read_y(a.out[o], base[o], row_w, n_out[o], y[o]);
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        if (!on[o]) continue;
+        ph_float16 acc[1][1];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+        if (n_in > 0) hop_multiply<DS, 1, 1>(zs, araw[o], ct, acc);
+        hop_write_y(a.out[o], base[o], row_w, n_out[o], y[o], acc[0][0]);
+    }
+}
+
+HopPlan hop_plan(const std::vector<HopTask>& tasks) {
+    HopPlan p;
+    std::vector<HopTask> large;
+    for (const HopTask& t : tasks) {
+        if (std::max(t.ns, t.nq) <= 64) p.small.push_back(t.t);
+        else large.push_back(t);
+    }
+    // largest first, there and back over the XCDs: equal numbers of tasks and nearly equal work on each
+    std::stable_sort(large.begin(), large.end(), [](const HopTask& a, const HopTask& b) { return (int64_t)(a.ns + a.nq) > (int64_t)(b.ns + b.nq); });
+    for (int kind = 0; kind < 3; ++kind) {
+        std::vector<int32_t> of[8];
+        for (size_t i = 0; i < large.size(); ++i) {
+            const int x = (int)(i & 8 ? 7 - (i & 7) : i & 7);
+            for (int o = 0; o < 2; ++o) {
+                if (kind != HOP_BOTH && kind != (o ? HOP_QUERY : HOP_SUPPORT)) continue;
+                const int slot = kind == HOP_BOTH ? o : 0;   // the place of the output among those enabled
+                const int n = o ? large[i].nq : large[i].ns;
+                for (int rb = 0; rb * 256 < n; ++rb) of[x].push_back((int32_t)((u32)large[i].t | ((u32)slot << 16) | ((u32)rb << 17)));
+            }
+        }
+        std::vector<int32_t>& l = p.tiles[kind];
+        l.assign(9, 0);
+        for (int x = 0; x < 8; ++x) {
+            l[x + 1] = l[x] + (int32_t)of[x].size();
+            p.longest[kind] = std::max(p.longest[kind], (int)of[x].size());
+        }
+        for (int x = 0; x < 8; ++x) l.insert(l.end(), of[x].begin(), of[x].end());
+    }
+    return p;
+}
+
+void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3], const int longest[3]) {
+    const int kind = a.out[0].enabled ? (a.out[1].enabled ? HOP_BOTH : HOP_SUPPORT) : HOP_QUERY;
+    if (a.F <= 0 || !(a.out[0].enabled || a.out[1].enabled)) return;
+    if (kind == HOP_QUERY) {
+        a.out[0] = a.out[1];
+        a.out[1].enabled = 0;
+    }
+    a.tiles = tiles[kind];
     const int ds = a.D % 64 == 0 ? 64 : 32;
-    const int64_t n_work = (int64_t)a.F * (a.D / ds) * Tw * n_out * a.row_blocks;
-    if (n_work >= ((int64_t)1 << 31) - 8) return;   // cannot happen within the library's own limits on a call
-    a.n_work = (int)n_work;
-    const unsigned grid = (unsigned)((n_work + 7) / 8 * 8);
-    if (ds == 64) hipLaunchKernelGGL(pair_hop_kernel<64>, dim3(grid), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(pair_hop_kernel<32>, dim3(grid), dim3(256), 0, st, a);
+    const int64_t fx = (int64_t)a.F * (a.D / ds), n_large = 8 * fx * longest[kind], n_small = (fx * a.n_small + 7) / 8 * 8;
+    if (n_large >= ((int64_t)1 << 31) || n_small >= ((int64_t)1 << 31)) return;   // cannot happen within the library's own limits on a call
+    if (n_large > 0) {
+        if (ds == 64) hipLaunchKernelGGL(pair_hop_kernel<64>, dim3((unsigned)n_large), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(pair_hop_kernel<32>, dim3((unsigned)n_large), dim3(256), 0, st, a);
+    }
+    if (n_small > 0) {
+        if (ds == 64) hipLaunchKernelGGL(pair_hop_small_kernel<64>, dim3((unsigned)n_small), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(pair_hop_small_kernel<32>, dim3((unsigned)n_small), dim3(256), 0, st, a);
+    }
 }

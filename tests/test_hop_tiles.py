@@ -1,0 +1,42 @@
+"""The row hops at the edges of their tiles: task sizes around 64, 128 and 256 rows in either set, tasks with an empty
+support set, more than eight tasks (the lists of the XCDs), one and two column tiles per row and rows of several slices."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from tests.helpers import small_cfg
+from tests.test_gpu_parity import TOL_FP32, _compare_step, _inputs, gm  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _cut(s, sizes, F):
+    """The first sizes[t] samples of every task."""
+    keep = np.concatenate([np.arange(a, a + n) for a, n in zip(s.task_offsets[:-1], sizes)]).astype(np.int64)
+    off = s.bag_offsets.numpy()
+    lens = off[1:] - off[:-1]
+    bags = (keep[:, None] * F + np.arange(F)).reshape(-1)
+    idx = np.concatenate([np.arange(off[b], off[b + 1]) for b in bags]) if len(bags) else np.zeros(0, np.int64)
+    return dataclasses.replace(s, task_offsets=np.concatenate([[0], np.cumsum(sizes)]).astype(s.task_offsets.dtype),
+                               bag_offsets=torch.from_numpy(np.concatenate([[0], np.cumsum(lens[bags])])), indices=s.indices[torch.from_numpy(idx)],
+                               dense=s.dense[torch.from_numpy(keep)], labels=s.labels[torch.from_numpy(keep)])
+
+
+@pytest.mark.parametrize("D,bf,ns,nq", [
+    (64, 0, [1, 64, 63, 64, 32, 33, 2, 31, 7, 64], [64, 1, 63, 64, 33, 32, 2, 31, 64, 64]),
+    (64, 0, [65, 64, 128, 129, 1, 192, 3, 66, 127, 193], [64, 65, 129, 128, 193, 1, 128, 3, 66, 127]),
+    (32, 0, [257, 10, 256, 255, 64, 65, 300, 130], [10, 257, 255, 256, 65, 64, 130, 300]),
+    (128, 0, [70, 5, 200], [5, 70, 129]),
+    (64, 1, [320, 64, 65, 9, 40], [33, 64, 257, 130, 40])])
+def test_tile_edges(gm, D, bf, ns, nq):  # noqa: F811
+    F = 3
+    cfg = small_cfg(n_tasks=len(ns), n_fields=F, emb_dim=D, rows_per_field=60, n_support=max(ns), n_query=max(nq), bag_max=3,
+                    layer_dims=(F * D + 5, 40, 1), mlp_dtype=bf)
+    sup, qry, params = _inputs(cfg, emb_std=0.3)
+    sup, qry = _cut(sup, ns, F), _cut(qry, nq, F)
+    ctx = gm.from_config(cfg, workspace_bytes=1 << 29)
+    ctx.configure("row_path", 2)
+    _compare_step(cfg, ctx, sup, qry, params, 2, 2, 2e-2 if bf else TOL_FP32, f"rows of {D}, {ns} / {nq}", operand="bf16" if bf else "fp64")
+    ctx.close()
