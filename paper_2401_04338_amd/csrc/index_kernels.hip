@@ -2,6 +2,8 @@
 // inner-loop row update and the overlap join of Sec. 2.1.2, and the global (field,row) ordering that
 // routes the sparse meta-gradient (Alg. 1, global back-propagation on xi).  Everything here has exactly
 // one correct answer and is compared bit-exactly with the CPU oracle.
+#include <algorithm>
+
 #include "gm_internal.h"
 
 #define WAVE 64
@@ -84,9 +86,13 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
         }
         if (uniform_rows >= 0 && n > 0) {   // (offsets outside [0, nnz] are flagged above; the range read here is clamped)
             const int64_t q0 = min(max(v.bag_offsets[s_lo * F], (int64_t)0), nnz), q1 = min(max(v.bag_offsets[s_hi * F], q0), nnz);
-            for (int64_t p = q0 + (int64_t)blockIdx.y * blockDim.x + threadIdx.x; p < q1; p += (int64_t)gridDim.y * blockDim.x) {
-                const int32_t r = v.indices[p];
-                if (r < 0 || r >= uniform_rows) bad = true;
+            const int64_t step = (int64_t)gridDim.y * blockDim.x;
+            for (int64_t p = q0 + (int64_t)blockIdx.y * blockDim.x + threadIdx.x; p < q1; p += 4 * step) {
+                int32_t r[4];   // four reads in flight (past the end: the first one's index again)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) r[k] = v.indices[p + k * step < q1 ? p + k * step : p];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) bad |= r[k] < 0 || r[k] >= uniform_rows;
             }
         }
     }
@@ -107,12 +113,14 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
     if (too_large) atomicOr(&status[ST_TOO_LARGE], 1u);
 }
 
-void launch_tf_count(hipStream_t st, int F, int t0, int Tw, SetView sup, SetView qry, const int64_t* field_base,
+void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t bags_per_task, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status) {
     if (Tw <= 0) return;
     launch_zero(st, ZeroJobs{3, {status, cnt_sup, cnt_qry}, {ST_WORDS, (int64_t)Tw * F, cnt_qry != cnt_sup ? (int64_t)Tw * F : 0}});
-    // enough workgroups to fill the chip whatever the number of tasks in the wave
-    const int split = Tw >= 2048 ? 1 : (Tw >= 512 ? 4 : 8);
+    // A task's bags are split over workgroups of two bags per thread, down to 4096 workgroups in all: fewer leave the chip
+    // idle with few tasks (3 tasks x 65536 bags in 24 workgroups 244 us, in 384 39 us), more only add their
+    // 2 F atomics each.
+    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(bags_per_task / 512, 4096 / Tw));
     hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, split), dim3(256), 2 * F * sizeof(u32), st, F, t0, sup, qry, field_base,
                        nnz_sup, nnz_qry, uniform_rows, cnt_sup, cnt_qry, status);
 }
@@ -746,21 +754,26 @@ __global__ __launch_bounds__(256) void field_offsets_kernel(int F, int Tw, const
 }
 
 // first key and first tile of every field's range, and what a key of the field has in front of its row number
-__global__ void field_table_kernel(int F, const u32* tot, const int64_t* field_base, int tile_keys, u32* key_pos, u32* tile_base,
-                                   u32* key_sub) {
-    if (threadIdx.x || blockIdx.x) return;
+__global__ __launch_bounds__(256) void field_table_kernel(int F, const u32* tot, const int64_t* field_base, int tile_keys, u32* key_pos, u32* tile_base,
+                                                          u32* key_sub) {
+    __shared__ int sh[8];
     u32 k = 0, tl = 0;
-    for (int f = 0; f < F; ++f) {
-        key_pos[f] = k;
-        tile_base[f] = tl;
-        key_sub[f] = (u32)field_base[f];
-        const u32 nf = tot[f] + tot[F + f];
-        k += nf;
-        tl += (nf + (u32)tile_keys - 1) / (u32)tile_keys;
+    for (int f0 = 0; f0 <= F; f0 += 256) {   // (entry F: the ends)
+        const int f = f0 + (int)threadIdx.x;
+        const u32 nf = f < F ? tot[f] + tot[F + f] : 0u;
+        int n_keys, n_tiles;
+        const u32 kx = (u32)block_excl_scan((int)nf, sh, &n_keys);
+        __syncthreads();
+        const u32 tx = (u32)block_excl_scan((int)((nf + (u32)tile_keys - 1) / (u32)tile_keys), sh, &n_tiles);
+        __syncthreads();
+        if (f <= F) {
+            key_pos[f] = k + kx;
+            tile_base[f] = tl + tx;
+            key_sub[f] = f < F ? (u32)field_base[f] : 0u;
+        }
+        k += (u32)n_keys;
+        tl += (u32)n_tiles;
     }
-    key_pos[F] = k;
-    tile_base[F] = tl;
-    key_sub[F] = 0u;
 }
 
 #define BKF_CH 1024   // bags of a task staged at a time
@@ -853,7 +866,7 @@ void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables) {
     u32* key_sub = tile_base + (a.F + 1);
     u32* tot = key_sub + (a.F + 1);
     hipLaunchKernelGGL(field_offsets_kernel, dim3(a.F), dim3(256), 0, st, a.F, a.Tw, a.cnt_s, a.cnt_q, a.fm_off_s, a.fm_off_q, tot);
-    hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(64), 0, st, a.F, tot, a.field_base, RS_TILE_KEYS, key_pos, tile_base, key_sub);
+    hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(256), 0, st, a.F, tot, a.field_base, RS_TILE_KEYS, key_pos, tile_base, key_sub);
     a.key_pos = key_pos;
     a.tot = tot;
     hipLaunchKernelGGL(build_keys_fm_kernel, dim3(a.F, a.Tw, 2), dim3(256), 0, st, a);
