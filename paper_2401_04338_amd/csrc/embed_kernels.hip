@@ -207,7 +207,10 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 // borders leaves one partial sum per chunk that a second pass adds in chunk order.  The cutting depends
 // only on positions, so the order of every sum is fixed.
 // ------------------------------------------------------------------------------------------------
-#define SEG_CH 64
+#define SEG_CH 64         // positions per chunk
+#define SEG_CH_SMALL 16   // ... of a short list of narrow rows, where 64 leave the device idle and a lane group of D/4 <= 4 lanes
+#define SEG_SMALL_N 32768 //     walking its chunk 4 positions at a time (2048 lookups of 16 columns: 23 -> 8 us)
+static inline int seg_chunk(int64_t n, int D) { return n <= SEG_SMALL_N && D <= 16 ? SEG_CH_SMALL : SEG_CH; }
 
 // One lane group (LG = D/4 lanes, a float4 of the row each) walks one chunk.  The chunk's metadata is read LG positions
 // at a time, one position per lane (coalesced), and handed round the group by lane shuffles; the head flags of
@@ -215,7 +218,7 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 // follows from the head flags at the chunk's two borders, so no segment table is read here.
 template <int LG>
 __global__ void __launch_bounds__(256)
-seg_reduce_chunks_kernel(int D, int F, ValEnc enc, const u32* __restrict__ keys, const u32* __restrict__ scan,
+seg_reduce_chunks_kernel(int D, int F, int ch, ValEnc enc, const u32* __restrict__ keys, const u32* __restrict__ scan,
                          const int64_t* __restrict__ n_rows, int64_t capacity, int64_t n,
                          const u32* __restrict__ sorted_vals, const float* __restrict__ gx, float* emb_grad,
                          float* partial, float* table) {
@@ -224,12 +227,12 @@ seg_reduce_chunks_kernel(int D, int F, ValEnc enc, const u32* __restrict__ keys,
     const int g_in_block = threadIdx.x / LG, l = threadIdx.x % LG;
     const int group_lane0 = (threadIdx.x % 64) / LG * LG;   // the group's first lane inside its wave
     const int64_t n_valid = table ? 0 : min(*n_rows, capacity);
-    const int64_t n_chunks = (n + SEG_CH - 1) / SEG_CH;
+    const int64_t n_chunks = (n + ch - 1) / ch;
     const int64_t n_groups = (int64_t)gridDim.x * GPB;
     const float4* gx4 = reinterpret_cast<const float4*>(gx);
     for (int64_t c = (int64_t)blockIdx.x * GPB + g_in_block; c < n_chunks; c += n_groups) {
-        const int64_t cb = c * SEG_CH;
-        const int cnt = (int)min((int64_t)SEG_CH, n - cb);
+        const int64_t cb = c * ch;
+        const int cnt = (int)min((int64_t)ch, n - cb);
         // borders: does the chunk's last run go on in the next chunk; which segment does position cb lie in
         const bool goes_on = (cb + cnt < n) && keys[cb + cnt] == keys[cb + cnt - 1];
         int64_t seg = table ? 0 : (int64_t)scan[cb] - 1;     // + 1 at every head, the one at cb included
@@ -309,17 +312,17 @@ seg_reduce_chunks_kernel(int D, int F, ValEnc enc, const u32* __restrict__ keys,
 // One lane group per CHUNK: if the chunk's last run begins inside the chunk and goes on past it, this group adds
 // the pieces the following chunks left (each of them starts with the same key) in chunk order.  Every such
 // segment is the last one of exactly one chunk.
-__global__ void seg_reduce_join_kernel(int D, int LG, const u32* __restrict__ keys, const u32* __restrict__ scan,
+__global__ void seg_reduce_join_kernel(int D, int LG, int ch, const u32* __restrict__ keys, const u32* __restrict__ scan,
                                        const int64_t* __restrict__ n_rows, int64_t capacity, int64_t n,
                                        const float* __restrict__ partial, float* emb_grad, float* table) {
     const int groups_per_block = blockDim.x / LG;
     const int g_in_block = threadIdx.x / LG, l = threadIdx.x % LG;
     if (g_in_block >= groups_per_block) return;
     const int64_t n_valid = table ? 0 : min(*n_rows, capacity);
-    const int64_t n_chunks = (n + SEG_CH - 1) / SEG_CH;
+    const int64_t n_chunks = (n + ch - 1) / ch;
     const int64_t n_groups = (int64_t)gridDim.x * groups_per_block;
     for (int64_t c = (int64_t)blockIdx.x * groups_per_block + g_in_block; c + 1 < n_chunks; c += n_groups) {
-        const int64_t cb = c * SEG_CH, ce = cb + SEG_CH;   // not the last chunk, so it is full and ce < n
+        const int64_t cb = c * ch, ce = cb + ch;   // not the last chunk, so it is full and ce < n
         const u32 key = keys[ce - 1];
         if (keys[ce] != key) continue;                     // the run ends with the chunk
         if (cb > 0 && keys[cb - 1] == key) continue;       // began in an earlier chunk, which adds it up
@@ -330,7 +333,7 @@ __global__ void seg_reduce_join_kernel(int D, int LG, const u32* __restrict__ ke
         }
         // c1: the last chunk that starts with the key.  Most segments end in chunk c + 1, a hot row's spans
         // thousands: gallop forward in doubling steps, then bisect (the keys are sorted).
-        auto starts_with_key = [&](int64_t cc) { return cc < n_chunks && keys[cc * SEG_CH] == key; };
+        auto starts_with_key = [&](int64_t cc) { return cc < n_chunks && keys[cc * ch] == key; };
         int64_t c1 = c + 1, step = 1;
         while (starts_with_key(c1 + step)) {
             c1 += step;
@@ -361,17 +364,17 @@ __global__ void seg_reduce_join_kernel(int D, int LG, const u32* __restrict__ ke
     }
 }
 
-size_t seg_reduce_partial_floats(int64_t n, int D) { return (size_t)((n + SEG_CH - 1) / SEG_CH) * 2 * D + 16; }
+size_t seg_reduce_partial_floats(int64_t n, int D) { return (size_t)((n + seg_chunk(n, D) - 1) / seg_chunk(n, D)) * 2 * D + 16; }
 
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows, int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
                        float* emb_grad, float* partial, float* table) {
     if (n <= 0 || capacity <= 0) return;
-    const int LG = D / 4;
-    const int64_t n_chunks = (n + SEG_CH - 1) / SEG_CH;
+    const int LG = D / 4, ch = seg_chunk(n, D);
+    const int64_t n_chunks = (n + ch - 1) / ch;
     const dim3 grid(pool_grid(n_chunks, 256 / LG));
 #define SEG_CHUNKS(LG_)                                                                                              \
     case LG_:                                                                                                        \
-        hipLaunchKernelGGL(seg_reduce_chunks_kernel<LG_>, grid, dim3(256), 0, st, D, F, enc, keys, scan, n_rows, capacity, n, \
+        hipLaunchKernelGGL(seg_reduce_chunks_kernel<LG_>, grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
                            sorted_vals, gx, emb_grad, partial, table);                                               \
         break;
     switch (LG) {
@@ -379,7 +382,7 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
         default: return;   // emb_dim is a power of two in 4..256 (checked when the context is made)
     }
 #undef SEG_CHUNKS
-    hipLaunchKernelGGL(seg_reduce_join_kernel, dim3(pool_grid(n_chunks, 256 / LG)), dim3(256), 0, st, D, LG, keys, scan,
+    hipLaunchKernelGGL(seg_reduce_join_kernel, dim3(pool_grid(n_chunks, 256 / LG)), dim3(256), 0, st, D, LG, ch, keys, scan,
                        n_rows, capacity, n, partial, emb_grad, table);
 }
 

@@ -231,17 +231,21 @@ struct PairHopArgs {
     PairHopOut out[2];                        // support, query
     const u32* task_path;                     // [Tw] only tasks flagged 1 are touched
     const int32_t* small; int n_small;        // tasks of at most 64 rows in both sets
+    int run;                                  // (field, slice)s per entry of the lists
     const int32_t* tiles;                     // set by the launcher
 };
 // The work of a hop over the tasks of a wave, by the outputs asked for: the small tasks, and the tiles of 256 out-rows of the
-// others as eight lists (one per XCD; nine offsets, then the entries: task, which enabled output << 16, tile << 17).
+// others as eight lists (one per XCD; nine offsets, then the entries: task, which enabled output << 16, tile << 17, run << 19).
 enum { HOP_BOTH = 0, HOP_SUPPORT = 1, HOP_QUERY = 2 };
-struct HopTask { int32_t t, ns, nq; };        // (task numbers below 65536, rows below 2^22)
+struct HopTask { int32_t t, ns, nq; };        // (task numbers below 65536, at most 1024 rows)
 struct HopPlan {
     std::vector<int32_t> small, tiles[3];
     int longest[3] = {0, 0, 0};               // entries of the longest of the eight lists
+    int run = 1;                              // (field, slice)s per entry
 };
-HopPlan hop_plan(const std::vector<HopTask>& tasks);
+int hop_slices(int F, int D);                 // (field, slice of columns)s of a row
+int64_t hop_entries(int64_t tiles, int fx);   // most entries of a list over so many tiles of 256 rows
+HopPlan hop_plan(const std::vector<HopTask>& tasks, int fx);
 void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3], const int longest[3]);
 void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_rows, float* x_out, int ldx, bf16_t* x_bf);
 
@@ -382,6 +386,7 @@ struct MatrixJob {
 struct MatrixJobs { int n; MatrixJob job[MATRIX_JOBS]; };
 void launch_copy_matrices(hipStream_t st, const MatrixJob* list, int n);
 void launch_axpy(hipStream_t st, int64_t n, float a, const float* x, float* y);  // y += a*x
+void launch_scale(hipStream_t st, int64_t n, float a, const float* x, float* y);  // y = a*x
 void launch_axpy_clear(hipStream_t st, int64_t n, float a, float* x, float* y);  // y += a*x, x = 0 (n % 4 == 0, 16-byte aligned)
 void launch_sum_to_scalar(hipStream_t st, const float* x, int n, float* out, int accumulate);
 void launch_fill_u32(hipStream_t st, u32* p, int64_t n, u32 v);

@@ -284,7 +284,7 @@ struct WaveBufs {
     uint8_t* pair_mat;
     int64_t *pair_off_ss, *pair_off_qs, *pair_off_sq;
     int32_t *hop_small = nullptr, *hop_tiles[3] = {nullptr, nullptr, nullptr};   // the hops' work lists (HopPlan)
-    int hop_longest[3] = {0, 0, 0}, n_hop_small = 0;
+    int hop_longest[3] = {0, 0, 0}, hop_run = 1, n_hop_small = 0;
     u32* task_path;   // [Tw] 1: pair-count path, 0: sparse kernel (the counting kernel clears it on overflow)
     // table-shaped sparse output only: the wave's own gradient buffer (support rows, then query rows) and sort
     float* GX = nullptr;
@@ -358,9 +358,11 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.pair_off_ss = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_qs = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_sq = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
+    const int fx = hop_slices(F, c->D);
     w.hop_small = d.pair ? ar.get<int32_t>(d.Tw + 1) : nullptr;
     for (int k = 0; k < 3; ++k)
-        w.hop_tiles[k] = d.pair ? ar.get<int32_t>(9 + (k == HOP_QUERY ? 0 : d.hop_tiles_s) + (k == HOP_SUPPORT ? 0 : d.hop_tiles_q)) : nullptr;
+        w.hop_tiles[k] = d.pair ? ar.get<int32_t>(9 + (k == HOP_QUERY ? 0 : hop_entries(d.hop_tiles_s, fx)) + (k == HOP_SUPPORT ? 0 : hop_entries(d.hop_tiles_q, fx)))
+                                : nullptr;
     // (down to here: filled by setup_wave, in one copy)
     w.row_task_s = ar.get<int32_t>(d.Ps + 1);
     w.row_task_q = ar.get<int32_t>(d.Pq + 1);
@@ -1623,8 +1625,9 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
         std::vector<HopTask> tasks;
         for (int t = 0; t < d.Tw; ++t)
             if (path[t]) tasks.push_back(HopTask{t, re_s[t + 1] - re_s[t], re_q[t + 1] - re_q[t]});
-        const HopPlan plan = hop_plan(tasks);
+        const HopPlan plan = hop_plan(tasks, hop_slices(c->F, c->D));
         w.n_hop_small = (int)plan.small.size();
+        w.hop_run = plan.run;
         up.put(w.hop_small, plan.small);
         for (int k = 0; k < 3; ++k) {
             w.hop_longest[k] = plan.longest[k];
@@ -1784,7 +1787,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     bool theta_summed = false;   // the first wave's sums are stored, later waves' added
     // Gradient w.r.t. the pooled inputs: the query rows are written whole by the outer backward pass; the support rows
     // are the second-order chain's sum, which starts from zero unless its first product stores instead of adding.
-    const bool gxs_self_init = order == 2 && K > 0 && bf && L > 1;
+    const bool gxs_self_init = order == 2 && K > 0;
     if (FD > 0 && !table && !gxs_self_init) launch_fill_f32(st, b.GX, Ps_tot * (int64_t)FD, 0.f);
     float* task_loss = out->task_loss ? out->task_loss : b.task_loss;
 
@@ -1953,7 +1956,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 };
                 if (o0) fill(pa.out[0], *o0, true);
                 if (o1) fill(pa.out[1], *o1, false);
-                pa.small = w.hop_small; pa.n_small = w.n_hop_small;
+                pa.small = w.hop_small; pa.n_small = w.n_hop_small; pa.run = w.hop_run;
                 Prof p(c, "pair_hop", alg_bytes, 0);
                 launch_pair_hop(st, pa, w.hop_tiles, w.hop_longest);
             }
@@ -2078,8 +2081,9 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                          k == 0 ? &gs_coarse : nullptr);
                 if (F > 0) {
                     if (!fused_gx) {
-                        Prof p(c, "axpy_gx", 12.0 * d.Ps * FD, 0);
-                        launch_axpy(st, d.Ps * (int64_t)FD, -alpha, w.dX, gxs);
+                        Prof p(c, "axpy_gx", (k == K - 1 ? 8.0 : 12.0) * d.Ps * FD, 0);
+                        if (k == K - 1) launch_scale(st, d.Ps * (int64_t)FD, -alpha, w.dX, gxs);
+                        else launch_axpy(st, d.Ps * (int64_t)FD, -alpha, w.dX, gxs);
                     }
                     if (k > 0 && adapt) {
                         TwoHopOut os = hop_out(true, txf, txf, w.TX.b, -alpha);

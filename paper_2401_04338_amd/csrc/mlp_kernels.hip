@@ -608,6 +608,13 @@ __global__ void axpy_kernel(int64_t n, float a, const float* __restrict__ x, flo
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         y[i] += a * x[i];
 }
+__global__ void scale_kernel(int64_t n, float a, const float* __restrict__ x, float* y) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) y[i] = a * x[i];
+}
+void launch_scale(hipStream_t st, int64_t n, float a, const float* x, float* y) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(scale_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, st, n, a, x, y);
+}
 // y += a * x and x = 0 in one pass (the table-shaped sparse meta-gradient applied to the tables and cleared for the next
 // iteration); 16 bytes per lane
 __global__ void axpy_clear_kernel(int64_t n4, float a, float4* x, float4* y) {

@@ -324,7 +324,8 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 //   tasks of at most 64 rows in both sets   one workgroup per (task, field, DS columns) takes both outputs from one staged Z
 //   the others                              tiles of 256 out-rows; a last tile of at most 128 (64) rows gives every wave one
 //                                           strip of 32 rows (and half the columns).  The tasks are dealt to the XCDs by
-//                                           size, largest first, a task's tiles to one XCD (they read the same rows of Z).
+//                                           size, largest first, a task's tiles to one XCD (they read the same rows of Z);
+//                                           a few tasks are dealt in runs of fields.
 // Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
 // 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
 // (256 + 256) rows x 26 fields 6.7 -> 6.6 ms, 4.8 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
@@ -544,12 +545,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     __shared__ __attribute__((aligned(16))) bf16_t zs[2 * HopStage<DS>::WORDS];
     // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, the fields of one entry in a row
     const int nsl = a.D / DS, fx = a.F * nsl;
-    const int xcd = blockIdx.x & 7, k = (int)(blockIdx.x >> 3), e = a.tiles[xcd] + k / fx;
+    const int xcd = blockIdx.x & 7, k = (int)(blockIdx.x >> 3), e = a.tiles[xcd] + k / a.run;
     if (e >= a.tiles[xcd + 1]) return;
     const u32 entry = (u32)a.tiles[9 + e];
-    const int t = (int)(entry & 0xFFFFu), o = (int)((entry >> 16) & 1u), row0 = (int)(entry >> 17) * 256;
-    if (!a.task_path[t]) return;
-    const int fs = k % fx, f = fs / nsl, sl = fs - f * nsl;
+    const int t = (int)(entry & 0xFFFFu), o = (int)((entry >> 16) & 1u), row0 = (int)((entry >> 17) & 3u) * 256;
+    const int fs = (int)(entry >> 19) * a.run + k % a.run, f = fs / nsl, sl = fs - f * nsl;
+    if (fs >= fx || !a.task_path[t]) return;
     const PairHopOut& out = a.out[o];
     const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], n_out = out.real_off[t + 1] - out.real_off[t];
     const uint8_t* M = a.mat + out.mat_off[t] + (size_t)f * pad64(n_out) * pad64(n_in);
@@ -618,26 +619,37 @@ __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
     }
 }
 
-HopPlan hop_plan(const std::vector<HopTask>& tasks) {
+int hop_slices(int F, int D) { return F * (D / (D % 64 == 0 ? 64 : 32)); }
+// With fewer than eight large tasks for every XCD the XCDs take runs of HOP_RUN (field, slice)s of a task instead of whole
+// tasks (3 tasks x (512 + 512) rows x 64 fields, two hops: 180 -> 93 us).
+enum { HOP_RUN = 8, HOP_WHOLE_TASKS = 64 };
+int64_t hop_entries(int64_t tiles, int fx) { return std::max(tiles, std::min<int64_t>(tiles, (HOP_WHOLE_TASKS - 1) * 4) * ((fx + HOP_RUN - 1) / HOP_RUN)); }
+
+HopPlan hop_plan(const std::vector<HopTask>& tasks, int fx) {
     HopPlan p;
     std::vector<HopTask> large;
     for (const HopTask& t : tasks) {
         if (std::max(t.ns, t.nq) <= 64) p.small.push_back(t.t);
         else large.push_back(t);
     }
+    const bool whole = large.size() >= HOP_WHOLE_TASKS || fx > HOP_RUN << 13;   // (13 bits hold a run's number)
+    p.run = whole ? fx : (int)HOP_RUN;
+    const int runs = (fx + p.run - 1) / p.run;
     // largest first, there and back over the XCDs: equal numbers of tasks and nearly equal work on each
     std::stable_sort(large.begin(), large.end(), [](const HopTask& a, const HopTask& b) { return (int64_t)(a.ns + a.nq) > (int64_t)(b.ns + b.nq); });
     for (int kind = 0; kind < 3; ++kind) {
         std::vector<int32_t> of[8];
-        for (size_t i = 0; i < large.size(); ++i) {
-            const int x = (int)(i & 8 ? 7 - (i & 7) : i & 7);
-            for (int o = 0; o < 2; ++o) {
-                if (kind != HOP_BOTH && kind != (o ? HOP_QUERY : HOP_SUPPORT)) continue;
-                const int slot = kind == HOP_BOTH ? o : 0;   // the place of the output among those enabled
-                const int n = o ? large[i].nq : large[i].ns;
-                for (int rb = 0; rb * 256 < n; ++rb) of[x].push_back((int32_t)((u32)large[i].t | ((u32)slot << 16) | ((u32)rb << 17)));
+        size_t unit = 0;
+        for (const HopTask& t : large)
+            for (int r = 0; r < runs; ++r, ++unit) {
+                const int x = (int)(unit & 8 ? 7 - (unit & 7) : unit & 7);
+                for (int o = 0; o < 2; ++o) {
+                    if (kind != HOP_BOTH && kind != (o ? HOP_QUERY : HOP_SUPPORT)) continue;
+                    const u32 slot = kind == HOP_BOTH ? o : 0;   // the place of the output among those enabled
+                    const int n = o ? t.nq : t.ns;
+                    for (int rb = 0; rb * 256 < n; ++rb) of[x].push_back((int32_t)((u32)t.t | (slot << 16) | ((u32)rb << 17) | ((u32)r << 19)));
+                }
             }
-        }
         std::vector<int32_t>& l = p.tiles[kind];
         l.assign(9, 0);
         for (int x = 0; x < 8; ++x) {
@@ -658,7 +670,7 @@ void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3
     }
     a.tiles = tiles[kind];
     const int ds = a.D % 64 == 0 ? 64 : 32;
-    const int64_t fx = (int64_t)a.F * (a.D / ds), n_large = 8 * fx * longest[kind], n_small = (fx * a.n_small + 7) / 8 * 8;
+    const int64_t fx = (int64_t)a.F * (a.D / ds), n_large = 8 * (int64_t)a.run * longest[kind], n_small = (fx * a.n_small + 7) / 8 * 8;
     if (n_large >= ((int64_t)1 << 31) || n_small >= ((int64_t)1 << 31)) return;   // cannot happen within the library's own limits on a call
     if (n_large > 0) {
         if (ds == 64) hipLaunchKernelGGL(pair_hop_kernel<64>, dim3((unsigned)n_large), dim3(256), 0, st, a);

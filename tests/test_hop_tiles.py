@@ -40,3 +40,14 @@ def test_tile_edges(gm, D, bf, ns, nq):  # noqa: F811
     ctx.configure("row_path", 2)
     _compare_step(cfg, ctx, sup, qry, params, 2, 2, 2e-2 if bf else TOL_FP32, f"rows of {D}, {ns} / {nq}", operand="bf16" if bf else "fp64")
     ctx.close()
+
+
+@pytest.mark.parametrize("tasks,fields", [(2, 17), (64, 3)])   # runs of eight fields with one left over; the first batch dealt by whole tasks
+def test_runs_of_fields(gm, tasks, fields):  # noqa: F811
+    cfg = small_cfg(n_tasks=tasks, n_fields=fields, emb_dim=32, rows_per_field=60, n_support=66, n_query=65, bag_max=2,
+                    layer_dims=(fields * 32 + 5, 24, 1))
+    sup, qry, params = _inputs(cfg, emb_std=0.3)
+    ctx = gm.from_config(cfg, workspace_bytes=1 << 29)
+    ctx.configure("row_path", 2)
+    _compare_step(cfg, ctx, sup, qry, params, 2, 2, TOL_FP32, f"{tasks} tasks x {fields} fields")
+    ctx.close()
