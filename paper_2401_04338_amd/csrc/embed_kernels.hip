@@ -39,6 +39,8 @@ __device__ __forceinline__ void pool_tail(const PoolArgs& a) {
     const int64_t o = (int64_t)(S.row_map[s] - S.row_base) * a.ldx + FD + c;
     if (S.x) S.x[o] = v;
     if (S.x_bf) S.x_bf[o] = f2bf(v);
+    if (S.zero) S.zero[o] = 0.f;
+    if (S.zero_bf) S.zero_bf[o] = 0;
 }
 
 __global__ __launch_bounds__(256) void gather_pool_kernel(PoolArgs a) {
@@ -178,14 +180,14 @@ void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t
     else if (grid > 0) hipLaunchKernelGGL(gather_pool_kernel, dim3(grid), dim3(256), 0, st, a);
 }
 
-// dense and pad columns of every (padded) row: copied from x_base, or zero
+// dense and pad columns of every (padded) row, copied from x_base
 __global__ void copy_tail_kernel(int FD, const float* x_base, int64_t n_rows, float* x_out, int ldx, bf16_t* x_bf) {
     const int tail = ldx - FD;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_rows * tail) return;
     const int64_t s = i / tail;
     const int c = (int)(i - s * tail);
-    const float v = x_base ? x_base[s * ldx + FD + c] : 0.f;
+    const float v = x_base[s * ldx + FD + c];
     if (x_out) x_out[s * ldx + FD + c] = v;
     if (x_bf) x_bf[s * ldx + FD + c] = f2bf(v);
 }

@@ -155,6 +155,8 @@ struct PoolSet {
     const int32_t* row_map; int32_t row_base;   // x row of each of them: row_map[i] - row_base
     float* x;                       // null: only x_bf
     bf16_t* x_bf;                   // null: only x
+    float* zero = nullptr;          // buffers of the same rows whose dense and pad columns become zero (may be null)
+    bf16_t* zero_bf = nullptr;
 };
 // pooled fields, dense features and zero padding of every sample of two sets, one launch
 void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t* field_base, const float* emb, int ldx,
@@ -282,10 +284,13 @@ struct GemmArgs {
     int epi;
     const float* bias; int64_t gBias;           // bias + g*gBias + n
     const float* mask; int64_t ld_mask;         // mask + (r0+m)*ld_mask + n
-    const float* Cin; int64_t gCin;             // Cin + g*gCin + m*ldc + n   (EPI_AXPBY)
+    const float* Cin; int64_t gCin, rCin;       // Cin + g*gCin + r0(g)*rCin + m*ldc + n   (EPI_AXPBY)
     float c0, c1;
 };
-void launch_gemm_f32(hipStream_t st, const GemmArgs& a);
+void launch_gemm_f32(hipStream_t st, const GemmArgs& a);   // A contraction-contiguous
+enum { GEMM_LIST = 4 };   // products per launch
+struct GemmList { int n; GemmArgs job[GEMM_LIST]; int block0[GEMM_LIST]; };
+void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n);   // both operands contraction-slowest, M fixed, K the group's rows
 
 // bf16 operands, both stored contraction-contiguous: C[M,N] = sum_p A_p[M,K] * Bt_p[N,K]^T
 #define GEMM_MAX_PAIRS 4   // products accumulated into one output (the pipelined kernel takes at most two)
@@ -383,12 +388,16 @@ struct MatrixJob {
     float* dst; bf16_t* dst_bf; int rows, cols, ld_dst;   // dst_bf may be null
     int block0;              // set by the launcher
 };
-struct MatrixJobs { int n; MatrixJob job[MATRIX_JOBS]; };
-void launch_copy_matrices(hipStream_t st, const MatrixJob* list, int n);
+struct MatrixJobs {
+    int n;
+    MatrixJob job[MATRIX_JOBS];
+    const float* sum_src; int sum_n, sum_block; float* sum_dst;
+};
+void launch_copy_matrices(hipStream_t st, const MatrixJob* list, int n /* at least 1 */, const float* sum_src = nullptr, int sum_n = 0,
+                          float* sum_dst = nullptr);   // sum_dst: *sum_dst = sum of sum_src too
 void launch_axpy(hipStream_t st, int64_t n, float a, const float* x, float* y);  // y += a*x
 void launch_scale(hipStream_t st, int64_t n, float a, const float* x, float* y);  // y = a*x
 void launch_axpy_clear(hipStream_t st, int64_t n, float a, float* x, float* y);  // y += a*x, x = 0 (n % 4 == 0, 16-byte aligned)
-void launch_sum_to_scalar(hipStream_t st, const float* x, int n, float* out, int accumulate);
 void launch_fill_u32(hipStream_t st, u32* p, int64_t n, u32 v);
 void launch_fill_f32(hipStream_t st, float* p, int64_t n, float v);
 enum { ZERO_JOBS = 4 };

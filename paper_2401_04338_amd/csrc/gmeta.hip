@@ -853,8 +853,8 @@ static void dense_nn(gm_ctx* c, const Grp& g, int l, int np, const Act* in0, con
 }
 
 // out[rows, ld_{l-1}] = mask .* sum_p d_p[rows, ld_l] * W_p,l^T ; for l == 1: dX[rows, FD] fp32, no mask
-// dX (layer 1 only): the fp32 gradient w.r.t. the pooled input.  bf16 mode can also accumulate it, scaled, into
-// gx_acc (gx_acc += gx_scale * dX, or = with gx_init) in the same pass; with write_dx = false only that is stored.
+// dX (layer 1 only): the fp32 gradient w.r.t. the pooled input.  With write_dx = false it goes, scaled, into gx_acc instead
+// (gx_acc += gx_scale * dX, or = with gx_init); bf16 mode can do both in the same pass.
 static void dense_nt(gm_ctx* c, const Grp& g, int l, int np, const Act* d0, const Theta* th0, const Act* d1,
                      const Theta* th1, const Act* mask, Act* out, float* dX, float* gx_acc = nullptr, float gx_scale = 0.f,
                      bool write_dx = true, bool gx_init = false) {
@@ -880,7 +880,10 @@ static void dense_nt(gm_ctx* c, const Grp& g, int l, int np, const Act* d0, cons
         }
         a.M = -1; a.N = N; a.K = K;
         a.tile_group = g.tile_g; a.tile_m0 = g.tile_m; a.n_mtiles = g.n_mtiles;
-        if (dX) { a.C = dX; a.ldc = N; a.rC = N; a.epi = EPI_NONE; }
+        if (dX && !write_dx) {   // straight into the sum
+            a.C = gx_acc; a.ldc = N; a.rC = N; a.epi = EPI_AXPBY; a.c1 = gx_scale;
+            if (!gx_init) { a.Cin = gx_acc; a.rCin = N; a.c0 = 1.f; }
+        } else if (dX) { a.C = dX; a.ldc = N; a.rC = N; a.epi = EPI_NONE; }
         else { a.C = out->f; a.ldc = N; a.rC = N; a.epi = EPI_MASK; a.mask = mask->f; a.ld_mask = mask->ld; }
         launch_gemm_f32(c->stream, a);
     } else {
@@ -931,8 +934,9 @@ static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
 }
 
 // out_g[ld_{l-1}, ld_l] = c0*in_g + c1 * sum_p a_p[rows_g, ld_{l-1}]^T d_p[rows_g, ld_l]  (and its bf16 copies)
+// later (fp32): the product is added to this list, for one launch with others that depend on nothing of each other
 static void dense_tn_n(gm_ctx* c, const Grp& g, int l, int np, const Act* const* as, const Act* const* ds, Theta& out,
-                       const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true) {
+                       const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true, std::vector<GemmArgs>* later = nullptr) {
     const int M = c->ld[l - 1], N = c->ld[l];
     {
         const double esz = c->mlp_dtype ? 2.0 : 4.0;
@@ -949,7 +953,8 @@ static void dense_tn_n(gm_ctx* c, const Grp& g, int l, int np, const Act* const*
             }
             a.C = out.f + c->offW[l]; a.ldc = N; a.gC = out.sf; a.M = M; a.N = N; a.K = -1;
             a.epi = EPI_AXPBY; a.Cin = in ? in + c->offW[l] : nullptr; a.gCin = in_stride; a.c0 = c0; a.c1 = c1;
-            launch_gemm_f32(c->stream, a);
+            if (later) later->push_back(a);
+            else launch_gemm_f32_wgrads(c->stream, &a, 1);
         } else {
             GemmBArgs a;
             memset(&a, 0, sizeof a);
@@ -970,10 +975,11 @@ static void dense_tn_n(gm_ctx* c, const Grp& g, int l, int np, const Act* const*
 }
 
 static void dense_tn(gm_ctx* c, const Grp& g, int l, int np, const Act* a0, const Act* d0, const Act* a1, const Act* d1,
-                     Theta& out, const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true) {
+                     Theta& out, const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true,
+                     std::vector<GemmArgs>* later = nullptr) {
     const Act* as[2] = {a0, a1};
     const Act* ds[2] = {d0, d1};
-    dense_tn_n(c, g, l, np, as, ds, out, in, in_stride, c0, c1, write_f32);
+    dense_tn_n(c, g, l, np, as, ds, out, in, in_stride, c0, c1, write_f32, later);
 }
 
 // The per-task column sums of one pass, collected and launched together.
@@ -1063,9 +1069,10 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
     const int L = c->L;
     const int64_t nt = out.sf;
     ColSums sums{c, g};
+    std::vector<GemmArgs> later;
     for (int l = 1; l < L; ++l) {
         const Act* prev = l == 1 ? p.X : &(*p.A)[l - 1];
-        if (coarse) dense_tn(c, *coarse, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, *coarse_out, nullptr, 0, 0.f, c1);
+        if (coarse) dense_tn(c, *coarse, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, *coarse_out, nullptr, 0, 0.f, c1, true, &later);
         else if (hist) {
             const Act* as[GEMM_MAX_PAIRS];
             const Act* ds[GEMM_MAX_PAIRS];
@@ -1075,9 +1082,13 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
                 ds[j] = &(*(*hist)[j].Dl)[l];
             }
             dense_tn_n(c, g, l, np, as, ds, out, in0, 0, c0, c1, false);
-        } else dense_tn(c, g, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, out, in, in_stride, c0, c1, write_f32);
+        } else dense_tn(c, g, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, out, in, in_stride, c0, c1, write_f32, &later);
         sums.add(c->ld[l], &(*p.Dl)[l], nullptr, nullptr, nullptr, out.f + c->offb[l], nt, in ? in + c->offb[l] : nullptr,
                  in_stride, c0, c1);
+    }
+    if (!later.empty()) {
+        Prof pr(c, "gemm_wgrad", 0, 0);   // (its bytes and operations are counted layer by layer)
+        launch_gemm_f32_wgrads(c->stream, later.data(), (int)later.size());
     }
     const Act* prev = L == 1 ? p.X : &(*p.A)[L - 1];
     sums.add(c->ld[L - 1], prev, p.dL, nullptr, nullptr, out.f + c->offW[L], nt, in ? in + c->offW[L] : nullptr, in_stride, c0, c1);
@@ -1131,6 +1142,7 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
     sums.add(c->ld[L - 1], tprev, s.dL, prev, w.tdL, v.f + c->offW[L], nt, v.f + c->offW[L], nt, 1.f, -alpha);
     sums.add_scalar(w.tdL, v.f + c->offb[L], nt, v.f + c->offb[L], nt, 1.f, -alpha);
     Theta vout = v;
+    std::vector<GemmArgs> later;   // (fp32: the loop's products read every layer's direction before any is updated)
     if (!refresh_v_copies) vout.b = nullptr;
     for (int l = L - 1; l >= 1; --l) {
         if (l == 1) dense_nt(c, g, l, 2, &w.TD[l], &s.th, &s.Dl[l], &v, nullptr, nullptr, w.dX, gx_acc, -alpha, need_dx || !gx_acc, gx_init);
@@ -1138,11 +1150,15 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
         const Act* ta_prev = l == 1 ? &w.TX : &w.TA[l - 1];
         const Act* a_prev = l == 1 ? &s.X : &s.A[l - 1];
         if (coarse) {
-            if (l == 1 && !tx) dense_tn(c, *coarse, l, 1, a_prev, &w.TD[l], nullptr, nullptr, w.vsum, nullptr, 0, 0.f, 1.f);
-            else dense_tn(c, *coarse, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], w.vsum, nullptr, 0, 0.f, 1.f);
-        } else if (l == 1 && !tx) dense_tn(c, g, l, 1, a_prev, &w.TD[l], nullptr, nullptr, vout, v.f, nt, 1.f, -alpha);
-        else dense_tn(c, g, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], vout, v.f, nt, 1.f, -alpha);
+            if (l == 1 && !tx) dense_tn(c, *coarse, l, 1, a_prev, &w.TD[l], nullptr, nullptr, w.vsum, nullptr, 0, 0.f, 1.f, true, &later);
+            else dense_tn(c, *coarse, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], w.vsum, nullptr, 0, 0.f, 1.f, true, &later);
+        } else if (l == 1 && !tx) dense_tn(c, g, l, 1, a_prev, &w.TD[l], nullptr, nullptr, vout, v.f, nt, 1.f, -alpha, true, &later);
+        else dense_tn(c, g, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], vout, v.f, nt, 1.f, -alpha, true, &later);
         sums.add(c->ld[l], &w.TD[l], nullptr, nullptr, nullptr, v.f + c->offb[l], nt, v.f + c->offb[l], nt, 1.f, -alpha);
+    }
+    if (!later.empty()) {
+        Prof pr(c, "gemm_wgrad", 0, 0);
+        launch_gemm_f32_wgrads(st, later.data(), (int)later.size());
     }
     sums.launch();
 }
@@ -1865,7 +1881,8 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             const double lookups = (double)(d.nnz_s + d.nnz_q), bags = (double)(d.Ss + d.Sq) * F;
             Prof p(c, "gather_pool", lookups * (4.0 * D + 4) + bags * (4.0 * D + 8 + (bf ? 2.0 * D : 0)), 0);
             launch_gather_pool(st, F, D, c->n_dense, c->d_field_base, params->emb, ld0,
-                               PoolSet{sup->bag_offsets, sup->indices, sup->dense, wp.s0, d.Ss, rows_s, rb_s, w.Xs0, bf ? X0s.b : nullptr},
+                               PoolSet{sup->bag_offsets, sup->indices, sup->dense, wp.s0, d.Ss, rows_s, rb_s, w.Xs0, bf ? X0s.b : nullptr,
+                                       second ? (bf ? w.TXf : w.TX.f) : nullptr, second ? w.TX.b : nullptr},   // (dense features are not parameters: their direction is zero)
                                PoolSet{qry->bag_offsets, qry->indices, qry->dense, wp.q0, d.Sq, rows_q, rb_q, w.Xq0, (bf && K == 0) ? w.Xq.b : nullptr});
         }
         if (padded) {
@@ -1883,9 +1900,6 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             if (second) { pad(w.TX.b, 2, 0); pad(w.TX.f, 4, 0); pad(w.TXf, 4, 0); }
             launch_zero_pad_rows(st, Tw, pj);
         }
-        // the pooled direction: its dense and pad columns are zero (dense features are not parameters)
-        if (second) launch_copy_tail(st, FD, nullptr, d.Ps, bf ? w.TXf : w.TX.f, ld0, w.TX.b);
-
         // The wave's offsets and indices are validated.  Ordering the lookups by row needs nothing else: it runs on the
         // side stream from here on -- beside the dense phase, which is bound by memory traffic, not beside the index
         // kernels above, which are bound by the same things as the sort -- and is joined before the segment reduction
@@ -2075,7 +2089,8 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             for (int k = K - 1; k >= 0; --k) {
                 const StepState& s = w.steps[k];
                 // bf16 with hidden layers: the layer-1 product adds -alpha * dX to the gradient buffer itself
-                const bool fused_gx = bf && L > 1 && F > 0;
+                // (fp32 does so when nothing else reads dX)
+                const bool fused_gx = L > 1 && F > 0 && (bf || !(k > 0 && adapt));
                 // (the chain's first step starts that sum: the buffer's support rows need no clearing)
                 hvp_step(c, gs, s, w, alpha, k > 0, fused_gx ? gxs : nullptr, k > 0 && adapt, k == K - 1, adapt,
                          k == 0 ? &gs_coarse : nullptr);
@@ -2133,8 +2148,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                                  c->dims[l], c->dims[l], 0});
         mats.push_back(MatrixJob{b.g_theta + c->offb[l], 1, c->dims[l], c->dims[l], out->db[l - 1], nullptr, 1, c->dims[l], c->dims[l], 0});
     }
-    launch_copy_matrices(st, mats.data(), (int)mats.size());
-    launch_sum_to_scalar(st, task_loss, T, loss, 0);
+    launch_copy_matrices(st, mats.data(), (int)mats.size(), task_loss, T, loss);
     // (a batch whose segments were cut inside its wave keeps the status words of that: the row count, the capacity flag)
     if (!pre && !list_ordered) launch_fill_u32(st, c->d_status, ST_WORDS, 0);
     if (table) {
