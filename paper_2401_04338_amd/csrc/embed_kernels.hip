@@ -210,9 +210,18 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 // only on positions, so the order of every sum is fixed.
 // ------------------------------------------------------------------------------------------------
 #define SEG_CH 64         // positions per chunk
-#define SEG_CH_SMALL 16   // ... of a short list of narrow rows, where 64 leave the device idle and a lane group of D/4 <= 4 lanes
-#define SEG_SMALL_N 32768 //     walking its chunk 4 positions at a time (2048 lookups of 16 columns: 23 -> 8 us)
-static inline int seg_chunk(int64_t n, int D) { return n <= SEG_SMALL_N && D <= 16 ? SEG_CH_SMALL : SEG_CH; }
+#define SEG_SMALL_N 32768 // Short lists of narrow rows take chunks of 16 or 32, as the room for their partial rows allows: 64 leave the
+                          // device idle and a lane group of D/4 <= 4 lanes walking its chunk 4 positions at a time (2048 lookups of
+                          // 16 columns: 23 -> 8 us).  The chunk follows from n, F and D alone.
+static size_t seg_floats(int64_t n, int D, int ch) { return (size_t)((n + ch - 1) / ch) * 2 * D + 16; }
+size_t seg_reduce_partial_floats(int64_t n, int D) { return seg_floats(n, D, SEG_CH); }
+static int seg_chunk(int64_t n, int F, int D) {
+    if (n > SEG_SMALL_N || D > 16) return SEG_CH;
+    const size_t room = (size_t)n + radix_hist_words(n, F) + seg_floats(n, D, SEG_CH);   // at least this, see launch_seg_reduce
+    for (int ch = 16; ch < SEG_CH; ch *= 2)
+        if (seg_floats(n, D, ch) <= room) return ch;
+    return SEG_CH;
+}
 
 // One lane group (LG = D/4 lanes, a float4 of the row each) walks one chunk.  The chunk's metadata is read LG positions
 // at a time, one position per lane (coalesced), and handed round the group by lane shuffles; the head flags of
@@ -366,12 +375,10 @@ __global__ void seg_reduce_join_kernel(int D, int LG, int ch, const u32* __restr
     }
 }
 
-size_t seg_reduce_partial_floats(int64_t n, int D) { return (size_t)((n + seg_chunk(n, D) - 1) / seg_chunk(n, D)) * 2 * D + 16; }
-
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows, int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
                        float* emb_grad, float* partial, float* table) {
     if (n <= 0 || capacity <= 0) return;
-    const int LG = D / 4, ch = seg_chunk(n, D);
+    const int LG = D / 4, ch = seg_chunk(n, F, D);
     const int64_t n_chunks = (n + ch - 1) / ch;
     const dim3 grid(pool_grid(n_chunks, 256 / LG));
 #define SEG_CHUNKS(LG_)                                                                                              \

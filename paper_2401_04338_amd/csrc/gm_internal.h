@@ -232,13 +232,14 @@ struct PairHopArgs {
     int64_t ldz;
     PairHopOut out[2];                        // support, query
     const u32* task_path;                     // [Tw] only tasks flagged 1 are touched
-    const int32_t* small; int n_small;        // tasks of at most 64 rows in both sets
+    const int32_t* small; int n_small;        // tasks of at most HOP_SMALL rows in both sets
     int run;                                  // (field, slice)s per entry of the lists
     const int32_t* tiles;                     // set by the launcher
 };
 // The work of a hop over the tasks of a wave, by the outputs asked for: the small tasks, and the tiles of 256 out-rows of the
 // others as eight lists (one per XCD; nine offsets, then the entries: task, which enabled output << 16, tile << 17, run << 19).
 enum { HOP_BOTH = 0, HOP_SUPPORT = 1, HOP_QUERY = 2 };
+enum { HOP_SMALL = 64 };
 struct HopTask { int32_t t, ns, nq; };        // (task numbers below 65536, at most 1024 rows)
 struct HopPlan {
     std::vector<int32_t> small, tiles[3];
@@ -255,7 +256,7 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 // (both as launch_segments left them; neither is read when the output is table-shaped)
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows,
                        int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
-                       float* emb_grad, float* partial /* seg_reduce_partial_floats(n, D) */,
+                       float* emb_grad, float* partial /* seg_reduce_partial_floats(n, D), for D <= 16 with n + radix_hist_words(n, F) more */,
                        float* table /* null, or [all rows, D]: every segment is ADDED to its row instead of listed */);
 size_t seg_reduce_partial_floats(int64_t n, int D);
 void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows, const float* grad,

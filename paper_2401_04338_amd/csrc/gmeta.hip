@@ -300,7 +300,7 @@ struct WaveDims {
     bool any_sparse = false;               // some task of the wave takes the sparse kernel
     bool pair_ss = false, pair_sq = false; // which kinds besides query x support
     int64_t pair_bytes = 0;
-    int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of all tasks (an upper bound on the hops' work lists)
+    int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of the tasks beyond HOP_SMALL (the hops' work lists)
     bool table = false;                    // the sparse gradient is reduced wave by wave into a table-shaped output
 };
 
@@ -330,14 +330,18 @@ static Theta alloc_theta(const gm_ctx* c, Arena& ar, int Tw, bool need_f) {
 static void alloc_sort(const gm_ctx* c, Arena& ar, SortBufs& so, int64_t nnz, int64_t max_segs, size_t extra_hist_words,
                        bool need_gx) {
     so.keys = ar.get<u32>(nnz + 1);
-    so.vals = ar.get<u32>(nnz + 1);
     so.keys_tmp = ar.get<u32>(nnz + 1);
-    so.vals_tmp = ar.get<u32>(nnz + 1);
+    so.vals = ar.get<u32>(nnz + 1);   // (vals .. vals_tmp: seg_room)
     so.hist = ar.get<u32>(radix_hist_words(nnz, c->F) + extra_hist_words);
     so.scan_tmp = ar.get<u32>(scan_tmp_words(nnz));
     so.seg_start = ar.get<u32>(std::min(nnz, max_segs) + 2);
     so.seg_partial = need_gx ? ar.get<float>(seg_reduce_partial_floats(nnz, c->D)) : nullptr;
+    so.vals_tmp = ar.get<u32>(nnz + 1);
 }
+// Room for the segment reduction's partial rows.  Nothing of the sort but its result and the flags' scan (keys_tmp) is read
+// any more by then: the unused values, the digit counts and what lies beside them are one stretch with seg_partial, so narrow
+// rows can be cut into short chunks without more workspace.
+static float* seg_room(const gm_ctx* c, const SortBufs& so) { return c->D <= 16 ? reinterpret_cast<float*>(std::min(so.hist, so.vals_tmp)) : so.seg_partial; }
 
 // What depends on the indices only (row dictionaries, overlap join, pair-count matrices, and with the table-shaped
 // output the wave's own sort buffers): a batch's can be prepared while another batch computes.
@@ -359,10 +363,12 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.pair_off_qs = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_sq = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     const int fx = hop_slices(F, c->D);
-    w.hop_small = d.pair ? ar.get<int32_t>(d.Tw + 1) : nullptr;
-    for (int k = 0; k < 3; ++k)
-        w.hop_tiles[k] = d.pair ? ar.get<int32_t>(9 + (k == HOP_QUERY ? 0 : hop_entries(d.hop_tiles_s, fx)) + (k == HOP_SUPPORT ? 0 : hop_entries(d.hop_tiles_q, fx)))
-                                : nullptr;
+    if (d.pair) {
+        const int64_t es = hop_entries(d.hop_tiles_s, fx), eq = hop_entries(d.hop_tiles_q, fx);
+        const int64_t words[4] = {d.Tw + 1, 9 + es + eq, 9 + es, 9 + eq};
+        w.hop_small = ar.get<int32_t>(words[0] + words[1] + words[2] + words[3]);
+        for (int k = 0; k < 3; ++k) w.hop_tiles[k] = (k ? w.hop_tiles[k - 1] : w.hop_small) + words[k];
+    }
     // (down to here: filled by setup_wave, in one copy)
     w.row_task_s = ar.get<int32_t>(d.Ps + 1);
     w.row_task_q = ar.get<int32_t>(d.Pq + 1);
@@ -742,8 +748,10 @@ extern "C" size_t gm_workspace_bytes(const gm_model_desc* model, int32_t n_tasks
             d.pair = true;
             d.pair_ss = inner_steps >= 2;
             d.pair_sq = order == 2;
-            d.hop_tiles_s = n_tasks * ((ns + 255) / 256);
-            d.hop_tiles_q = n_tasks * ((nq + 255) / 256);
+            if (std::max(ns, nq) > HOP_SMALL) {
+                d.hop_tiles_s = n_tasks * ((ns + 255) / 256);
+                d.hop_tiles_q = n_tasks * ((nq + 255) / 256);
+            }
             d.pair_bytes = (int64_t)n_tasks * c.F * ((d.pair_ss ? ps * ps : 0) + pq * ps * (d.pair_sq ? 2 : 1));
         }
     }
@@ -1486,8 +1494,11 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
     for (int t = p.t0; t < p.t1; ++t) {
         if (task_pair_ok(c, B, t, K)) {
             d.pair = true;
-            d.hop_tiles_s += (B.sup->task_offsets[t + 1] - B.sup->task_offsets[t] + 255) / 256;
-            d.hop_tiles_q += (B.qry->task_offsets[t + 1] - B.qry->task_offsets[t] + 255) / 256;
+            const int64_t ns = B.sup->task_offsets[t + 1] - B.sup->task_offsets[t], nq = B.qry->task_offsets[t + 1] - B.qry->task_offsets[t];
+            if (std::max(ns, nq) > HOP_SMALL) {
+                d.hop_tiles_s += (ns + 255) / 256;
+                d.hop_tiles_q += (nq + 255) / 256;
+            }
         } else d.any_sparse = true;
     }
     if (d.pair) {
@@ -2132,7 +2143,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             {
                 Prof p(c, "seg_reduce", (double)nw * (4.0 * D + 4), 0);
                 launch_seg_reduce(st, D, F, ordered ? enc : kPlainVals, w.so.keys, w.so.keys_tmp, nullptr, nw, nw, w.so.vals, w.GX,
-                                  nullptr, w.so.seg_partial, table);
+                                  nullptr, seg_room(c, w.so), table);
             }
             if (side_table) HIPCHK(c, hipEventRecord(c->ev_main, st));
         } else if (ordered) {
@@ -2159,7 +2170,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         if (F > 0) {
             Prof p(c, "seg_reduce", (double)nnz * (4.0 * D + 4), 0);
             launch_seg_reduce(st, D, F, (pre || list_ordered) ? enc : kPlainVals, b.so.keys, b.so.keys_tmp, out->n_emb_rows, capacity, nnz,
-                              b.so.vals, b.GX, out->emb_grad, b.so.seg_partial, nullptr);
+                              b.so.vals, b.GX, out->emb_grad, seg_room(c, b.so), nullptr);
         }
     }
     if (pre && no_sync) return GM_OK;   // the caller drains the stream; a prepared batch has passed every check already

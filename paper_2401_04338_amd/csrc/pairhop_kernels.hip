@@ -629,7 +629,7 @@ HopPlan hop_plan(const std::vector<HopTask>& tasks, int fx) {
     HopPlan p;
     std::vector<HopTask> large;
     for (const HopTask& t : tasks) {
-        if (std::max(t.ns, t.nq) <= 64) p.small.push_back(t.t);
+        if (std::max(t.ns, t.nq) <= HOP_SMALL) p.small.push_back(t.t);
         else large.push_back(t);
     }
     const bool whole = large.size() >= HOP_WHOLE_TASKS || fx > HOP_RUN << 13;   // (13 bits hold a run's number)
