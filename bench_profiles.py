@@ -23,11 +23,11 @@ import sqlite3
 
 # regular expressions over kernel names for each kernel family that bench.py reports (launches of one family are averaged)
 FAMILIES = {
-    "pair_hop": r"pair_hop_kernel",
+    "pair_hop": r"pair_hop_(small_)?kernel",
     "pair_count": r"pair_count_kernel",
     "two_hop": r"two_hop_kernel",
     "seg_reduce": r"seg_reduce_(chunks|join)_kernel",
-    "gather_pool": r"gather_pool(_xcd)?_kernel|dense_tail_kernel",
+    "gather_pool": r"gather_pool(_xcd)?_kernel",
     # radix_*_kernel<BITS, BYTASK>: the pass by task belongs to the per-(task, field) dictionaries (with the join that reads
     # them off the ordered list), the passes by row key to the ordering of the lookups by row
     "tf_sort": r"tf_sort_kernel|tf_join_kernel|radix_(hist|scatter)_kernel<\d+, true>",
@@ -36,13 +36,13 @@ FAMILIES = {
     "task_colsum": r"task_colsum_kernel",
     "reduce_tasks": r"reduce_tasks_kernel",
     "axpy_gx": r"axpy_kernel",
-    "last_layer": r"last_fwd_kernel|last_bwd",
+    "last_layer": r"last_layer_kernel",
     # gemm_bf16_kernel<BM, BN, DB, KA, KB, EP>: which operand is read contraction-slowest tells the product's kind;
     # gemm_bf16_pipe_kernel<KA, KB, EP, ..>: the pipelined 256 x 256 kernel, the same two flags
     "gemm_wgrad": r"gemm_bf16_kernel<\d+, \d+, false, true, true|gemm_bf16_pipe_kernel<true, true",
     "gemm_fwd": r"gemm_bf16_kernel<\d+, \d+, false, false, true|gemm_bf16_pipe_kernel<false, true",
     "gemm_bwd": r"gemm_bf16_kernel<\d+, \d+, false, false, false|gemm_bf16_pipe_kernel<false, false",
-    "gemm_f32 (all launches)": r"gemm_f32_kernel",
+    "gemm_f32 (all launches)": r"gemm_f32_(wgrads_)?kernel",
 }
 
 
