@@ -798,7 +798,7 @@ static int read_status(gm_ctx* c, u32* host) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// dense operators on handles (fp32: vector-FMA GEMM; bf16: MFMA GEMM)
+// dense operators on handles (MFMA GEMMs: fp32 or bf16 operands)
 // ------------------------------------------------------------------------------------------------
 struct Grp {  // grouping of one set's rows by task inside the wave
     const int32_t *row_off, *real_off, *row_task;
