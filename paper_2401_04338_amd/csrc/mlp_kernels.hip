@@ -7,31 +7,39 @@
 #include "gm_internal.h"
 
 // ------------------------------------------------------------------------------------------------
-// fp32 grouped GEMM on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, products and sums), C = A1*B1 (+ A2*B2)
+// fp32 grouped GEMM on the matrix cores (fp32 operands, products and sums), C = A1*B1 (+ A2*B2)
 // with a fused epilogue
 // ------------------------------------------------------------------------------------------------
 // Bound: the fp32 matrix rate (157 TFLOP/s; plain vector FMA reaches half of it and has to fetch 8 LDS values per 16
 // FMAs) where the tiles fill the device, the latency of the k-loop's loads where a call has a few tasks only.
 // A workgroup of four waves takes the k-range in pieces that are requested a whole piece ahead (registers), so that
 // the memory latency runs beside the MFMAs of the piece before.  Two shapes:
-//   SPLIT false  64 x 64 tile, one 32 x 32 block per wave, pieces of 64
-//   SPLIT true   32 x 32 tile, the four waves take a quarter of every piece of 128 each and their blocks are added in
-//                wave order through LDS: four times the workgroups and a quarter of the MFMA chain per wave
-// Operands stay in LDS as they lie in memory.  Within 16 contraction values MFMA j takes values j and j + 8 (any pairing
-// gives the same sum as long as both operands use it): a contraction-contiguous row then delivers a lane's 8 values as
-// two 16-byte reads, and in a contraction-slowest tile the two halves of a wave read rows 8 apart, which with a row
-// stride of (tile + 4) floats are 32 banks apart: neither form has bank conflicts.
+//   SMALL false  64 x 64 tile, 2 x 2 blocks of 16 x 16 per wave, pieces of 64
+//   SMALL true   32 x 32 tile, one block per wave, pieces of 128: four times the workgroups and a quarter of the MFMA time
+// ORDER OF THE SUMS: v_mfma_f32_16x16x4_f32 adds its four products one after the other, each a fused multiply-add rounded
+// to fp32 (measured: the same bits as an fmaf chain in ascending k, denormals included), and every MFMA takes the next four
+// contraction values.  So an output has the bits of the plain loop over k whatever the tile: a task's results do not depend
+// on how many tasks share its launch.
+// Operands stay in LDS as they lie in memory; lane group q of the four reads contraction value 4 j + q for MFMA j.
+// Contraction-contiguous rows are 4 floats longer than a piece and contraction-slowest rows change places in blocks of 16
+// columns from one to the next: in both forms the 64 lanes read 64 different banks.
 // Measured on one second-order step, all 18 products together: 64 tasks x (128 + 128) rows through 845-256-128-1
-// 2.03 -> 0.69 ms (a first-layer forward product 113 -> 43 us, 84 TFLOP/s), 37 tasks of about 50 rows through 189-100-52-1 0.45 ->
-// 0.12 ms, 4 tasks x (32 + 32) rows through 141-64-32-1 0.29 -> 0.10 ms (before: vector FMA, loads not overlapped).
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+// 2.03 -> 0.69 ms, 37 tasks of about 50 rows through 189-100-52-1 0.45 -> 0.12 ms, 4 tasks x (32 + 32) rows through
+// 141-64-32-1 0.29 -> 0.10 ms (before: vector FMA, loads not overlapped).  Small tiles whose waves share the contraction and
+// 32 x 32 blocks in the large ones take the same time (0.69 ms), but add in orders of their own.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-template <bool SPLIT>
+template <bool SMALL>
 struct F32Tile {
-    static constexpr int T = SPLIT ? 32 : 64;       // rows and columns of the tile
-    static constexpr int BK = SPLIT ? 128 : 64;     // contraction values per piece
+    static constexpr int R = SMALL ? 1 : 2;         // a wave's blocks of 16 rows, and of 16 columns
+    static constexpr int T = 32 * R;                // rows and columns of the tile
+    static constexpr int BK = SMALL ? 128 : 64;     // contraction values per piece
     static constexpr int V = T * BK / 4 / 256;      // 16-byte pieces per thread and operand
-    static constexpr int WORDS_CONT = T * (BK + 4), WORDS_SLOW = BK * (T + 4);
+    static constexpr int LD_CONT = BK + 4, LD_SLOW = T;
+    static constexpr int WORDS_CONT = T * LD_CONT, WORDS_SLOW = BK * LD_SLOW;
+    static constexpr int NJ = SMALL ? 8 : 4;        // values of a lane that are read ahead, per block
+    // column i of contraction-slowest row k: blocks of 16 columns exchanged
+    __device__ __forceinline__ static int swap(int k, int i) { return i ^ (SMALL ? (k & 2) << 3 : (k & 3) << 4); }
 };
 
 typedef __attribute__((__vector_size__(4 * sizeof(u32)))) u32 u32x4_t;
@@ -40,9 +48,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(u32)))) u32 u32x4_t;
 // p + k*ld + i (extents along the contiguous direction and strides are multiples of 4: every matrix is padded to 32).
 // The piece's base is uniform and moves on; a thread's offsets inside it stay.  What lies outside the operand is asked
 // for beyond the buffer's end and reads as zero.
-template <bool SPLIT, bool CONT>
+template <bool SMALL, bool CONT>
 struct F32Operand {
-    using TT = F32Tile<SPLIT>;
+    using TT = F32Tile<SMALL>;
     static constexpr u32 OOB = 0x80000000u;
     const float* base;
     int64_t step;
@@ -67,28 +75,26 @@ struct F32Operand {
     __device__ __forceinline__ static void store(float* s, const u32x4_t (&v)[TT::V]) {
 #pragma unroll
         for (int u = 0; u < TT::V; ++u)
-            *reinterpret_cast<u32x4_t*>(s + (CONT ? row(u) * (TT::BK + 4) + col(u) : col(u) * (TT::T + 4) + row(u))) = v[u];
+            *reinterpret_cast<u32x4_t*>(s + (CONT ? row(u) * TT::LD_CONT + col(u) : col(u) * TT::LD_SLOW + TT::swap(col(u), row(u)))) = v[u];
     }
-    // a lane's 8 values (row or column i of the tile, contraction values k .. k + 7)
-    __device__ __forceinline__ static void frag(const float* s, int i, int k, float (&f)[8]) {
-        if (CONT) {
-            const float4 a = *reinterpret_cast<const float4*>(s + i * (TT::BK + 4) + k), b = *reinterpret_cast<const float4*>(s + i * (TT::BK + 4) + k + 4);
-            f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-        } else {
+    // a lane's values of the next NJ MFMAs (contraction values from k on): row or column i of the tile, q the lane group
+    __device__ __forceinline__ static void frag(const float* s, int i, int k, int q, float (&f)[TT::R][TT::NJ]) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) f[j] = s[(k + j) * (TT::T + 4) + i];
+        for (int r = 0; r < TT::R; ++r) {
+            const float* p = CONT ? s + (i + r * 16) * TT::LD_CONT + k + q : s + (k + q) * TT::LD_SLOW + TT::swap(q, i + r * 16);
+#pragma unroll
+            for (int j = 0; j < TT::NJ; ++j) f[r][j] = p[j * 4 * (CONT ? 1 : TT::LD_SLOW)];
         }
     }
 };
 
 // block, n_blocks: the workgroup's number among those of this product
-template <bool SPLIT, bool KA, bool KB>
+template <bool SMALL, bool KA, bool KB>
 __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& a, int n_ntiles, int mt_per_group, int block, int n_blocks) {
-    using TT = F32Tile<SPLIT>;
-    using OpA = F32Operand<SPLIT, KA>;
-    using OpB = F32Operand<SPLIT, KB>;
+    using TT = F32Tile<SMALL>;
+    using OpA = F32Operand<SMALL, KA>;
+    using OpB = F32Operand<SMALL, KB>;
     constexpr int WA = KA ? TT::WORDS_CONT : TT::WORDS_SLOW, WB = KB ? TT::WORDS_CONT : TT::WORDS_SLOW;
-    static_assert(!SPLIT || WA + WB >= 4 * 32 * 33, "the waves' blocks are added in the operand stage");
     __shared__ float4 stage[(WA + WB) / 4];
     float* const As = reinterpret_cast<float*>(stage);
     float* const Bs = As + WA;
@@ -113,14 +119,13 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& a, int n_ntiles, i
     const int N = a.N;
     if (m0 >= M) return;
     const int n0 = ntile * TT::T;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l32 = lane & 31, half = lane >> 5;
-    const int mi = SPLIT ? l32 : (wv >> 1) * 32 + l32, ni = SPLIT ? l32 : (wv & 1) * 32 + l32;
-    f32x16 acc;
+    constexpr int R = TT::R, NJ = TT::NJ;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, li = lane & 15, q = lane >> 4;
+    const int mb = (wv >> 1) * 16 * R, nb = (wv & 1) * 16 * R;
+    f32x4 acc[R][R];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int i = 0; i < R * R * 4; ++i) acc[i / 4 / R][i / 4 % R][i % 4] = 0.f;
 
-    constexpr int KW = SPLIT ? TT::BK / 4 : TT::BK;    // contraction values of a piece that a wave takes
-    const int kw0 = (SPLIT ? wv * KW : 0) + half * 8;
     for (int pr = 0; pr < a.n_pairs; ++pr) {
         OpA A;
         OpB B;
@@ -139,18 +144,23 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& a, int n_ntiles, i
                 B.fetch(left - TT::BK, vb);
             }
             // (what lies beyond the contraction is zero: the loop may run past it)
-            float fa[2][8], fb[2][8];
-            OpA::frag(As, mi, kw0, fa[0]);
-            OpB::frag(Bs, ni, kw0, fb[0]);
+            float fa[2][R][NJ], fb[2][R][NJ];
+            OpA::frag(As, mb + li, 0, q, fa[0]);
+            OpB::frag(Bs, nb + li, 0, q, fb[0]);
+            constexpr int STEPS = TT::BK / 4 / NJ;
 #pragma unroll
-            for (int kb = 0; kb < KW / 16; ++kb) {   // the next 16 values are on their way while these are multiplied
-                if (kb + 1 < KW / 16) {
-                    OpA::frag(As, mi, kw0 + (kb + 1) * 16, fa[(kb + 1) & 1]);
-                    OpB::frag(Bs, ni, kw0 + (kb + 1) * 16, fb[(kb + 1) & 1]);
+            for (int kb = 0; kb < STEPS; ++kb) {   // the next values are on their way while these are multiplied
+                if (kb + 1 < STEPS) {
+                    OpA::frag(As, mb + li, (kb + 1) * 4 * NJ, q, fa[(kb + 1) & 1]);
+                    OpB::frag(Bs, nb + li, (kb + 1) * 4 * NJ, q, fb[(kb + 1) & 1]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[kb & 1][j], fb[kb & 1][j], acc, 0, 0, 0);
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int c = 0; c < R; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[kb & 1][r][j], fb[kb & 1][c][j], acc[r][c], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -160,69 +170,61 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& a, int n_ntiles, i
     const float* bias = a.bias ? a.bias + (int64_t)g * a.gBias : nullptr;
     const float* mask = a.mask ? a.mask + r0 * a.ld_mask : nullptr;
     const float* Cin = a.Cin ? a.Cin + (int64_t)g * a.gCin + r0 * a.rCin : nullptr;
-    auto emit = [&](int m, int n, float v) {
+    auto emit = [&](int m, int n, float v) {   // (fmaf: the same rounding in every instance)
         if (m >= M || n >= N) return;
         switch (a.epi) {
             case EPI_BIAS_RELU: v = fmaxf(v + bias[n], 0.f); break;
             case EPI_BIAS_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v + bias[n] : 0.f; break;
             case EPI_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v : 0.f; break;
-            case EPI_AXPBY: v = a.c1 * v + (Cin ? a.c0 * Cin[(int64_t)m * a.ldc + n] : 0.f); break;
+            case EPI_AXPBY: v = fmaf(a.c1, v, Cin ? a.c0 * Cin[(int64_t)m * a.ldc + n] : 0.f); break;
             default: break;
         }
         C[(int64_t)m * a.ldc + n] = v;
     };
-    // a lane holds column l32 of its block and rows 8*(i/4) + 4*half + i%4
-    if (SPLIT) {
-        float* red = As;
-        __syncthreads();
+    // a lane holds column li and rows 4 q .. 4 q + 3 of a block
 #pragma unroll
-        for (int i = 0; i < 16; ++i) red[(wv * 32 + (i >> 2) * 8 + half * 4 + (i & 3)) * 33 + l32] = acc[i];
-        __syncthreads();
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = threadIdx.x + u * 256, r = e >> 5, c = e & 31;
-            emit(m0 + r, n0 + c, ((red[r * 33 + c] + red[(32 + r) * 33 + c]) + red[(64 + r) * 33 + c]) + red[(96 + r) * 33 + c]);
-        }
-    } else {
+        for (int c = 0; c < R; ++c)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) emit(m0 + (wv >> 1) * 32 + (i >> 2) * 8 + half * 4 + (i & 3), n0 + ni, acc[i]);
-    }
+            for (int i = 0; i < 4; ++i) emit(m0 + mb + r * 16 + q * 4 + i, n0 + nb + c * 16 + li, acc[r][c][i]);
 }
 
-template <bool SPLIT, bool KA, bool KB>
+template <bool SMALL, bool KA, bool KB>
 __global__ __launch_bounds__(256, 4) void gemm_f32_kernel(GemmArgs a, int n_ntiles, int mt_per_group) {
-    gemm_f32_tile<SPLIT, KA, KB>(a, n_ntiles, mt_per_group, (int)blockIdx.x, (int)gridDim.x);
+    gemm_f32_tile<SMALL, KA, KB>(a, n_ntiles, mt_per_group, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Weight gradients of several layers in one launch: they are independent, and with a handful of tasks each of them is one
 // launch's latency long (4 tasks x (32 + 32) rows through 141-64-32: the three passes of a step 34.7 us in six launches, 20.8 us in three).
-template <bool SPLIT>
+template <bool SMALL>
 __global__ __launch_bounds__(256, 4) void gemm_f32_wgrads_kernel(GemmList l) {
     int i = 0;
     while (i + 1 < l.n && (int)blockIdx.x >= l.block0[i + 1]) ++i;
     const GemmArgs& a = l.job[i];
-    constexpr int T = F32Tile<SPLIT>::T;
-    gemm_f32_tile<SPLIT, false, false>(a, (a.N + T - 1) / T, (a.M + T - 1) / T, (int)blockIdx.x - l.block0[i],
+    constexpr int T = F32Tile<SMALL>::T;
+    gemm_f32_tile<SMALL, false, false>(a, (a.N + T - 1) / T, (a.M + T - 1) / T, (int)blockIdx.x - l.block0[i],
                                        (i + 1 < l.n ? l.block0[i + 1] : (int)gridDim.x) - l.block0[i]);
 }
 
-template <bool SPLIT>
+template <bool SMALL>
 static void gemm_f32_shape(hipStream_t st, const GemmArgs& a) {
-    constexpr int T = F32Tile<SPLIT>::T;
+    constexpr int T = F32Tile<SMALL>::T;
     const int n_ntiles = (a.N + T - 1) / T, mt_per_group = a.tile_group ? 1 : (a.M + T - 1) / T;
     const int64_t n_mtiles = a.tile_group ? (int64_t)a.n_mtiles * (64 / T) : (int64_t)mt_per_group * a.G;
     if (n_mtiles <= 0 || n_ntiles <= 0) return;
     const dim3 grid((unsigned)(n_mtiles * n_ntiles));
-    if (a.sBk[0] == 1) hipLaunchKernelGGL((gemm_f32_kernel<SPLIT, true, true>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
-    else hipLaunchKernelGGL((gemm_f32_kernel<SPLIT, true, false>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
+    if (a.sBk[0] == 1) hipLaunchKernelGGL((gemm_f32_kernel<SMALL, true, true>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
+    else hipLaunchKernelGGL((gemm_f32_kernel<SMALL, true, false>), grid, dim3(256), 0, st, a, n_ntiles, mt_per_group);
 }
 
-// The split tiles where 64 x 64 ones would not give every compute unit two workgroups: at 128 to 256 tiles 13.9 -> 12.0 us
-// and 33.9 -> 18.6 us for products of the step above; from 512 tiles on the large ones are ahead (43 against 48 us, 53 against 73).
-#define F32_SPLIT_TILES 512
+// The small tiles where 64 x 64 ones would not give every compute unit two workgroups.  The forward and the backward products
+// of 269-256-1, 128 rows a task, three passes, small against large: 64 tiles 45 / 34 against 60 / 47 us, 256 tiles 63 / 47
+// against 61 / 49, 512 tiles 104 / 74 against 87 / 69.  Either way the results have the same bits.
+#define F32_SMALL_TILES 512
 void launch_gemm_f32(hipStream_t st, const GemmArgs& a) {
     const int64_t tiles = (int64_t)((a.N + 63) / 64) * (a.tile_group ? a.n_mtiles : (int64_t)((a.M + 63) / 64) * a.G);
-    if (tiles < F32_SPLIT_TILES) gemm_f32_shape<true>(st, a);
+    if (tiles < F32_SMALL_TILES) gemm_f32_shape<true>(st, a);
     else gemm_f32_shape<false>(st, a);
 }
 void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n) {
@@ -234,15 +236,15 @@ void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n) {
             l.job[i] = list[i0 + i];
             tiles64 = std::max(tiles64, (int64_t)((l.job[i].M + 63) / 64) * ((l.job[i].N + 63) / 64) * l.job[i].G);   // (the largest decides)
         }
-        const bool split = tiles64 < F32_SPLIT_TILES;
-        const int T = split ? 32 : 64;
+        const bool small = tiles64 < F32_SMALL_TILES;
+        const int T = small ? 32 : 64;
         int64_t blocks = 0;
         for (int i = 0; i < l.n; ++i) {
             l.block0[i] = (int)blocks;
             blocks += (int64_t)((l.job[i].M + T - 1) / T) * ((l.job[i].N + T - 1) / T) * l.job[i].G;
         }
         if (blocks <= 0) continue;
-        if (split) hipLaunchKernelGGL(gemm_f32_wgrads_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, l);
+        if (small) hipLaunchKernelGGL(gemm_f32_wgrads_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, l);
         else hipLaunchKernelGGL(gemm_f32_wgrads_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, l);
     }
 }
