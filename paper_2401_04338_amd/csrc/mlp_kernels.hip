@@ -250,76 +250,67 @@ void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// element access in either activation type
-// ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ float ldf(const float* p, int64_t i) { return p[i]; }
-__device__ __forceinline__ float ldf(const bf16_t* p, int64_t i) { return bf2f(p[i]); }
-__device__ __forceinline__ void stf(float* p, int64_t i, float v) { p[i] = v; }
-__device__ __forceinline__ void stf(bf16_t* p, int64_t i, float v) { p[i] = f2bf(v); }
-
-// ------------------------------------------------------------------------------------------------
 // per-task column sums (bias gradients, last-layer weight gradient, per-task mean loss), all those of a pass in one launch:
 // out[g,n] = c0*in[g,n] + c1 * sum_{s in g} ( X1[s,n]*w1[s] + X2[s,n]*w2[s] ), rows summed in a fixed order
 // ------------------------------------------------------------------------------------------------
 // Bound: HBM with many tasks; with a few the chain of dependent row batches of one workgroup, and the launches
-// themselves.  A workgroup of 16 waves takes one task and one block of columns of one job.  A lane owns 16 bytes of
-// columns (8 bf16 or 4 fp32); rows narrower than a wave's 64 lanes are taken several at a time.  The waves take the
+// themselves.  A workgroup of 16 waves takes one task and one block of columns of one job.
+// bf16: a lane owns 16 bytes of columns; rows narrower than a wave's 64 lanes are taken several at a time.  The waves take the
 // rows round-robin in batches of UB independent loads; lanes that share columns are added first, then the waves in wave
-// order.  The partition depends on the job's width alone: results do not depend on how the tasks are cut into waves.
-// Measured: the 16 launches of a step of 3 tasks x (512 + 512) rows through 1024-512-256 hidden units 0.37 -> 0.03 ms
+// order.  fp32: four chains per column (rows 8 c .. 8 c + 7 of every 32, one after the other), which are added in order; four
+// waves take the chains of 64 columns, a lane one column, sixteen rows requested at once.  (The task's thetas, and with
+// them which side of zero a hidden unit falls on, follow from these sums: in fp32 their order stays whatever the launch.)
+// Either partition depends on the job's width alone: results do not depend on how the tasks are cut into waves.
+// Measured: the 16 launches of a step of 3 tasks x (512 + 512) rows through 1024-512-256 hidden units, bf16, 0.37 -> 0.03 ms
 // in 3 launches (4 waves and a launch per sum before); 512 tasks x 256 rows through 512-256, 28 launches, 0.62 -> 0.60 ms in 7.
-template <typename T>
-struct ColVec;
-template <>
-struct ColVec<float> {
-    static constexpr int N = 4;
-    typedef float4 Raw;
-    __device__ static void open(const Raw& x, float (&v)[4]) { v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; }
-};
-template <>
-struct ColVec<bf16_t> {
-    static constexpr int N = 8;
-    typedef uint4 Raw;
-    __device__ static void open(const Raw& x, float (&v)[8]) {
+enum { COLSUM_WAVES = 16 };
+
+// the job of a workgroup
+__device__ __forceinline__ const ColJob& colsum_job(const ColJobs& jobs) {
+    int ji = 0;
+    while (ji + 1 < jobs.n && (int)blockIdx.x >= jobs.job[ji + 1].block0) ++ji;
+    return jobs.job[ji];
+}
+__device__ __forceinline__ void colsum_store(const ColJob& j, int n, float sum) {
+    const int g = blockIdx.y;
+    j.out[(int64_t)g * j.g_out + n] = j.c1 * sum + (j.in ? j.c0 * j.in[(int64_t)g * j.g_in + n] : 0.f);
+}
+
+// rows r0 .. r1 of one column block, this wave's share; the lane's columns start at n of rows r0 + sub, r0 + sub + rpi, ...
+template <bool TWO>
+__device__ __forceinline__ void colsum_rows(const ColJob& j, int64_t r0, int64_t r1, int wv, int rpi, int sub, int n, float (&acc)[8]) {
+    constexpr int UB = TWO ? 4 : 8;
+    const bf16_t *X1 = reinterpret_cast<const bf16_t*>(j.X1) + n, *X2 = reinterpret_cast<const bf16_t*>(j.X2) + n;
+    auto open = [](const uint4& x, float (&v)[8]) {
         const u32 w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             v[2 * k] = __builtin_bit_cast(float, w[k] << 16);
             v[2 * k + 1] = __builtin_bit_cast(float, w[k] & 0xFFFF0000u);
         }
-    }
-};
-
-enum { COLSUM_WAVES = 16 };
-
-// rows r0 .. r1 of one column block, this wave's share; the lane's columns start at n of rows r0 + sub, r0 + sub + rpi, ...
-template <typename T, bool TWO>
-__device__ __forceinline__ void colsum_rows(const ColJob& j, int64_t r0, int64_t r1, int wv, int rpi, int sub, int n, float (&acc)[ColVec<T>::N]) {
-    typedef typename ColVec<T>::Raw Raw;
-    constexpr int V = ColVec<T>::N, UB = TWO ? 4 : 8;
-    const T *X1 = reinterpret_cast<const T*>(j.X1) + n, *X2 = reinterpret_cast<const T*>(j.X2) + n;
+    };
     for (int64_t s0 = r0 + (int64_t)wv * UB * rpi; s0 < r1; s0 += (int64_t)COLSUM_WAVES * UB * rpi) {
-        Raw x1[UB], x2[TWO ? UB : 1];
+        uint4 x1[UB], x2[TWO ? UB : 1];
         float f1[UB], f2[TWO ? UB : 1];
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
             const int64_t s = s0 + u * rpi + sub;
             const bool ok = s < r1;
             const int64_t sc = ok ? s : r0;
-            x1[u] = *reinterpret_cast<const Raw*>(X1 + sc * j.ldx);
+            x1[u] = *reinterpret_cast<const uint4*>(X1 + sc * j.ldx);
             f1[u] = ok ? (j.w1 ? j.w1[sc] : 1.f) : 0.f;
             if (TWO) {
-                x2[u] = *reinterpret_cast<const Raw*>(X2 + sc * j.ldx);
+                x2[u] = *reinterpret_cast<const uint4*>(X2 + sc * j.ldx);
                 f2[u] = ok ? (j.w2 ? j.w2[sc] : 1.f) : 0.f;
             }
         }
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
-            float a[V], b[V];
-            ColVec<T>::open(x1[u], a);
-            if (TWO) ColVec<T>::open(x2[u], b);
+            float a[8], b[8];
+            open(x1[u], a);
+            if (TWO) open(x2[u], b);
 #pragma unroll
-            for (int k = 0; k < V; ++k) {
+            for (int k = 0; k < 8; ++k) {
                 float v = a[k] * f1[u];
                 if (TWO) v += b[k] * f2[u];
                 acc[k] += v;
@@ -328,13 +319,10 @@ __device__ __forceinline__ void colsum_rows(const ColJob& j, int64_t r0, int64_t
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_kernel(const int32_t* __restrict__ row_offsets, ColJobs jobs) {
-    constexpr int V = ColVec<T>::N;
+__global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_bf16_kernel(const int32_t* __restrict__ row_offsets, ColJobs jobs) {
+    constexpr int V = 8;
     __shared__ float part[COLSUM_WAVES - 1][64 * V];
-    int ji = 0;
-    while (ji + 1 < jobs.n && (int)blockIdx.x >= jobs.job[ji + 1].block0) ++ji;
-    const ColJob& j = jobs.job[ji];
+    const ColJob& j = colsum_job(jobs);
     const int g = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t r0 = row_offsets[g], r1 = row_offsets[g + 1];
     float acc[V];
@@ -350,7 +338,7 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_kernel(const in
             float sum = acc[0];
 #pragma unroll
             for (int w = 0; w < COLSUM_WAVES - 1; ++w) sum += part[w][0];
-            j.out[(int64_t)g * j.g_out] = j.c1 * sum + (j.in ? j.c0 * j.in[(int64_t)g * j.g_in] : 0.f);
+            colsum_store(j, 0, sum);
         }
         return;
     }
@@ -358,8 +346,8 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_kernel(const in
     while (lpr > 1 && (lpr / 2) * V >= j.N) lpr /= 2;
     const int sub = lane / lpr, n = (((int)blockIdx.x - j.block0) * 64 + lane % lpr) * V;
     if (n < j.N) {
-        if (j.X2) colsum_rows<T, true>(j, r0, r1, wv, 64 / lpr, sub, n, acc);
-        else colsum_rows<T, false>(j, r0, r1, wv, 64 / lpr, sub, n, acc);
+        if (j.X2) colsum_rows<true>(j, r0, r1, wv, 64 / lpr, sub, n, acc);
+        else colsum_rows<false>(j, r0, r1, wv, 64 / lpr, sub, n, acc);
     }
     for (int d = 32; d >= lpr; d >>= 1)
 #pragma unroll
@@ -375,13 +363,74 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_kernel(const in
             float sum = acc[k];
 #pragma unroll
             for (int w = 0; w < COLSUM_WAVES - 1; ++w) sum += part[w][k * 64 + lane];
-            j.out[(int64_t)g * j.g_out + n + k] = j.c1 * sum + (j.in ? j.c0 * j.in[(int64_t)g * j.g_in + n + k] : 0.f);
+            colsum_store(j, n + k, sum);
         }
     }
 }
 
+// one chain of one column: rows r0 + 8 * chain .. + 7 of every 32
+template <bool TWO>
+__device__ __forceinline__ float colsum_chain(const ColJob& j, int64_t r0, int64_t r1, int chain, int n) {
+    const float *X1 = reinterpret_cast<const float*>(j.X1) + n, *X2 = reinterpret_cast<const float*>(j.X2) + n;
+    float acc = 0.f;
+    for (int64_t s0 = r0 + chain * 8; s0 < r1; s0 += 64) {
+        float x1[16], f1[16], x2[TWO ? 16 : 1], f2[TWO ? 16 : 1];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int64_t s = s0 + (u < 8 ? u : u + 24);
+            const bool ok = s < r1;
+            const int64_t sc = ok ? s : r0;
+            x1[u] = X1[sc * j.ldx];
+            f1[u] = ok ? (j.w1 ? j.w1[sc] : 1.f) : 0.f;
+            if (TWO) {
+                x2[u] = X2[sc * j.ldx];
+                f2[u] = ok ? (j.w2 ? j.w2[sc] : 1.f) : 0.f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+#pragma clang fp contract(off)   // (a product is rounded before it is added, in both forms)
+            float v = x1[u] * f1[u];
+            if (TWO) v = fmaf(x2[u], f2[u], v);
+            acc += v;
+        }
+    }
+    return acc;
+}
+
+__global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_f32_kernel(const int32_t* __restrict__ row_offsets, ColJobs jobs) {
+    __shared__ float part[64 * COLSUM_WAVES];
+    const ColJob& j = colsum_job(jobs);
+    const int g = blockIdx.y, tid = threadIdx.x;
+    const int64_t r0 = row_offsets[g], r1 = row_offsets[g + 1];
+    if (j.N == 1) {   // one value per row: read by all lanes, added by four
+        const float* X = reinterpret_cast<const float*>(j.X1);
+        float acc = 0.f;
+        for (int64_t s0 = r0; s0 < r1; s0 += 64 * COLSUM_WAVES) {
+            __syncthreads();   // the values before have been added
+            part[tid] = s0 + tid < r1 ? X[(s0 + tid) * j.ldx] : 0.f;
+            __syncthreads();
+            const int n = (int)min(r1 - s0, (int64_t)(64 * COLSUM_WAVES));
+            if (tid < 4)
+                for (int b = tid * 8; b < n; b += 32)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) acc += part[b + u];
+        }
+        const float a1 = __shfl(acc, 1, 64), a2 = __shfl(acc, 2, 64), a3 = __shfl(acc, 3, 64);
+        if (tid == 0) colsum_store(j, 0, ((acc + a1) + a2) + a3);
+        return;
+    }
+    const int lane = tid & 63, chain = (tid >> 6) & 3, group = tid >> 8;
+    const int n = (((int)blockIdx.x - j.block0) * (COLSUM_WAVES / 4) + group) * 64 + lane;
+    float acc = 0.f;
+    if (n < j.N) acc = j.X2 ? colsum_chain<true>(j, r0, r1, chain, n) : colsum_chain<false>(j, r0, r1, chain, n);
+    part[tid] = acc;
+    __syncthreads();
+    if (chain == 0 && n < j.N) colsum_store(j, n, ((acc + part[tid + 64]) + part[tid + 128]) + part[tid + 192]);
+}
+
 void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offsets, const ColJob* list, int n) {
-    const int cols = 64 * (bf16 ? ColVec<bf16_t>::N : ColVec<float>::N);
+    const int cols = bf16 ? 64 * 8 : 64 * (COLSUM_WAVES / 4);   // of a workgroup
     for (int i0 = 0; i0 < n; i0 += COL_JOBS) {
         ColJobs jobs;
         jobs.n = std::min(n - i0, (int)COL_JOBS);
@@ -393,8 +442,8 @@ void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offs
         }
         if (G <= 0 || blocks <= 0) continue;
         const dim3 grid(blocks, G), block(64 * COLSUM_WAVES);
-        if (bf16) hipLaunchKernelGGL(task_colsum_kernel<bf16_t>, grid, block, 0, st, row_offsets, jobs);
-        else hipLaunchKernelGGL(task_colsum_kernel<float>, grid, block, 0, st, row_offsets, jobs);
+        if (bf16) hipLaunchKernelGGL(task_colsum_bf16_kernel, grid, block, 0, st, row_offsets, jobs);
+        else hipLaunchKernelGGL(task_colsum_f32_kernel, grid, block, 0, st, row_offsets, jobs);
     }
 }
 
@@ -409,7 +458,8 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-__device__ __forceinline__ void load8(const bf16_t* p, float (&v)[8]) {
+// 16 bytes of columns of a row in either activation type (and as many fp32 weights)
+__device__ __forceinline__ void load_cols(const bf16_t* p, float (&v)[8]) {
     const uint4 x = *reinterpret_cast<const uint4*>(p);
     const u32 w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
@@ -418,28 +468,32 @@ __device__ __forceinline__ void load8(const bf16_t* p, float (&v)[8]) {
         v[2 * k + 1] = __builtin_bit_cast(float, w[k] & 0xFFFF0000u);
     }
 }
-__device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
+__device__ __forceinline__ void load_cols(const float* p, float (&v)[8]) {
     const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
-
-__device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8]) {
+__device__ __forceinline__ void load_cols(const float* p, float (&v)[4]) {
+    const float4 a = *reinterpret_cast<const float4*>(p);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+}
+__device__ __forceinline__ void store_cols(bf16_t* p, const float (&v)[8]) {
     *reinterpret_cast<uint4*>(p) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
 }
-__device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
+__device__ __forceinline__ void store_cols(float* p, const float (&v)[4]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
 
-// lpr: lanes per row, a power of two: 8 columns per lane and step (width and strides are multiples of 32, rows 16-byte
-// aligned: every activation is padded to 32 columns).  The row's logit and delta are known to all of its lanes, which then
-// write the delta of the last hidden layer, d[s, n] = (delta * w_n (+ delta' * w'_n in the tangent pass)) * (a[s, n] > 0),
-// from the activations they just read (cache hits).  Bound: HBM with many rows -- the activations are read once instead
-// of twice -- and the launch with few.
+// lpr: lanes per row, a power of two; 16 bytes of columns per lane and step (width and strides are multiples of 32, rows
+// 16-byte aligned: every activation is padded to 32 columns).  fp32: 16 lanes hold 64 partial sums, one for every column modulo
+// 64, and add them in halves (a fixed order, whatever the row's width).  The row's logit and delta are known to all of its
+// lanes, which then write the delta of the last hidden layer, d[s, n] = (delta * w_n (+ delta' * w'_n in the tangent pass))
+// * (a[s, n] > 0), from the activations they just read (cache hits).  Bound: HBM with many rows -- the activations are read
+// once instead of twice -- and the launch with few.
 // Measured: the three passes of a step of 4 tasks x (32 + 32) rows, 32 units, fp32, 20.8 us in six launches (logits and
 // deltas apart) -> 12.2 us in three; the seven of 512 tasks x (256 + 256) rows, 256 units, bf16, 0.37 ms.
 template <typename T>
 __global__ __launch_bounds__(256) void last_layer_kernel(LastArgs a, int lpr) {
+    constexpr int V = 16 / sizeof(T), SUMS = sizeof(T) == 4 ? 4 : 1;   // columns per lane and step, partial sums per lane
     const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t s = gt / lpr;
     const int lane = (int)(gt % lpr);
@@ -454,32 +508,39 @@ __global__ __launch_bounds__(256) void last_layer_kernel(LastArgs a, int lpr) {
             if (a.z_out) a.z_out[s] = 0.f;
             if (a.loss_out) a.loss_out[s] = 0.f;
         }
-        const float zero[8] = {};
+        const float zero[V] = {};
         if (d)
-            for (int n = lane * 8; n < a.N; n += lpr * 8) store8(d + n, zero);
+            for (int n = lane * V; n < a.N; n += lpr * V) store_cols(d + n, zero);
         return;
     }
     const float* w = a.w + (int64_t)g * a.gW;
     const float* tw = a.ta ? a.tw + (int64_t)g * a.gTW : nullptr;
     const T* x = reinterpret_cast<const T*>(a.a) + s * a.ld;
     const T* tx = a.ta ? reinterpret_cast<const T*>(a.ta) + s * a.ld : nullptr;
-    float acc = 0.f;
-    for (int n = lane * 8; n < a.N; n += lpr * 8) {
-        float xv[8], wv[8];
-        load8(x + n, xv);
-        load8(w + n, wv);
+    float sums[SUMS] = {};
+    for (int n = lane * V; n < a.N; n += lpr * V) {
+        float xv[V], wv[V];
+        load_cols(x + n, xv);
+        load_cols(w + n, wv);
         if (!tx) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) acc = fmaf(xv[k], wv[k], acc);
+            for (int k = 0; k < V; ++k) sums[k % SUMS] = fmaf(xv[k], wv[k], sums[k % SUMS]);
         } else {
-            float tv[8], twv[8];
-            load8(tx + n, tv);
-            load8(tw + n, twv);
+            float tv[V], twv[V];
+            load_cols(tx + n, tv);
+            load_cols(tw + n, twv);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) acc += tv[k] * wv[k] + xv[k] * twv[k];
+            for (int k = 0; k < V; ++k) sums[k % SUMS] += tv[k] * wv[k] + xv[k] * twv[k];
         }
     }
-    for (int m = lpr >> 1; m > 0; m >>= 1) acc += __shfl_xor(acc, m, 64);   // within the row's lanes: all of them hold the sum
+    for (int m = lpr >> 1; m > 0; m >>= 1)   // within the row's lanes: all of them hold the sum
+#pragma unroll
+        for (int k = 0; k < SUMS; ++k) sums[k] += __shfl_xor(sums[k], m, 64);
+#pragma unroll
+    for (int h = SUMS / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int k = 0; k < h; ++k) sums[k] += sums[k + h];
+    const float acc = sums[0];
     const float inv_n = 1.f / (float)n_real;
     const float z = tx ? a.z_in[s] : acc + a.b[(int64_t)g * a.gW];
     const float e = __expf(-fabsf(z));
@@ -498,28 +559,28 @@ __global__ __launch_bounds__(256) void last_layer_kernel(LastArgs a, int lpr) {
     }
     if (lane == 0) a.delta_out[s] = delta;
     if (!d) return;
-    for (int n = lane * 8; n < a.N; n += lpr * 8) {
-        float xv[8], wv[8], v[8];
-        load8(x + n, xv);
-        load8(w + n, wv);
+    for (int n = lane * V; n < a.N; n += lpr * V) {
+        float xv[V], wv[V], v[V];
+        load_cols(x + n, xv);
+        load_cols(w + n, wv);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = delta * wv[k];
+        for (int k = 0; k < V; ++k) v[k] = delta * wv[k];
         if (tx) {
-            load8(tw + n, wv);
+            load_cols(tw + n, wv);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] += delta2 * wv[k];
+            for (int k = 0; k < V; ++k) v[k] += delta2 * wv[k];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+        for (int k = 0; k < V; ++k)
             if (!(xv[k] > 0.f)) v[k] = 0.f;
-        store8(d + n, v);
+        store_cols(d + n, v);
     }
 }
 
 void launch_last_layer(hipStream_t st, const LastArgs& a) {
     if (a.n <= 0) return;
-    int lpr = 64;
-    while (lpr > 4 && (lpr / 2) * 8 >= a.N) lpr /= 2;
+    int lpr = a.bf16 ? 64 : 16;
+    while (a.bf16 && lpr > 4 && (lpr / 2) * 8 >= a.N) lpr /= 2;
     const dim3 grid((unsigned)((a.n * lpr + 255) / 256));
     if (a.bf16) hipLaunchKernelGGL(last_layer_kernel<bf16_t>, grid, dim3(256), 0, st, a, lpr);
     else hipLaunchKernelGGL(last_layer_kernel<float>, grid, dim3(256), 0, st, a, lpr);
