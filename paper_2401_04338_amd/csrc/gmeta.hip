@@ -252,6 +252,10 @@ struct SortBufs {
     float* seg_partial = nullptr;
 };
 
+// Most tasks of a wave: they are one grid dimension of several kernels (the column sums put them in y), and the hops' work
+// lists and the pass by task keep a task's number in 16 bits.
+enum { MAX_WAVE_TASKS = 32768 };
+static int most_wave_tasks(const gm_ctx* c) { return c->max_wave_tasks > 0 ? std::min<int>(c->max_wave_tasks, MAX_WAVE_TASKS) : MAX_WAVE_TASKS; }
 enum { COARSE_GROUPS = 32 };   // most runs of tasks (gm_configure "coarse_groups" says how many are used)
 
 struct WaveBufs {
@@ -622,7 +626,7 @@ extern "C" int gm_configure(gm_ctx* c, const char* key, int64_t value) {
         return GM_OK;
     }
     if (!strcmp(key, "max_wave_tasks")) {
-        if (value < 0 || value > 32768) return fail(c, GM_ERR_ARG, "max_wave_tasks must be in [0, 32768]");
+        if (value < 0 || value > MAX_WAVE_TASKS) return fail(c, GM_ERR_ARG, "max_wave_tasks must be in [0, %d]", (int)MAX_WAVE_TASKS);
         c->max_wave_tasks = (int)value;
         return GM_OK;
     }
@@ -1549,10 +1553,8 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         have_offsets = true;
         return GM_OK;
     };
-    // Waves of (nearly) equal numbers of tasks: the fewest waves whose every wave fits.  A wave's tasks are one grid
-    // dimension of several kernels, hence the cap.
-    int max_per = std::min(std::max(T, 1), 32768);
-    if (c->max_wave_tasks > 0) max_per = std::min(max_per, c->max_wave_tasks);
+    // Waves of (nearly) equal numbers of tasks: the fewest waves whose every wave fits.
+    const int max_per = std::min(std::max(T, 1), most_wave_tasks(c));
     int n_waves = (std::max(T, 1) + max_per - 1) / max_per;
     while (true) {
         const int per = (std::max(T, 1) + n_waves - 1) / n_waves;
@@ -2450,8 +2452,8 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
         const gm_set *s = &support[i], *q = &query[i];
         if (n_tasks[i] < 0 || !s->task_offsets || !q->task_offsets || s->nnz < 0 || q->nnz < 0 || s->n_samples < 0 || q->n_samples < 0 ||
             s->task_offsets[n_tasks[i]] != s->n_samples || q->task_offsets[n_tasks[i]] != q->n_samples ||
-            s->nnz + q->nnz >= ((int64_t)1 << 31)) {
-            overlapped = false;   // (the per-iteration call reports what is wrong)
+            s->nnz + q->nnz >= ((int64_t)1 << 31) || n_tasks[i] > most_wave_tasks(c)) {
+            overlapped = false;   // (the per-iteration call takes the tasks in waves, or reports what is wrong)
             break;
         }
         const int64_t cap = c->F > 0 ? std::min<int64_t>(s->nnz + q->nnz, c->field_base[c->F]) : 0;

@@ -94,3 +94,34 @@ def test_train_loop_stops_at_a_bad_batch():
     # the context keeps working
     ctx.meta_train(batches[:2], loop, cfg.inner_lr, 1, 2, 0.05)
     ctx.close()
+
+
+def _dense_only_batch(T, n_dense, dev, seed):
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    toff = np.arange(T + 1, dtype=np.int64)
+    none = dict(bag_offsets=torch.zeros(1, dtype=torch.int64, device=dev), indices=torch.zeros(0, dtype=torch.int32, device=dev))
+    return tuple(SetData(toff, none["bag_offsets"], none["indices"], torch.randn(T, n_dense, device=dev, generator=gen),
+                         (torch.rand(T, device=dev, generator=gen) < 0.5).float()) for _ in range(2))
+
+
+# a batch of more tasks than a wave may hold (65535: the most blocks in a grid's y), and one cut by "max_wave_tasks"
+@pytest.mark.parametrize("tasks,per_wave", [(65536, 0), (32769, 0), (300, 128)])
+def test_train_loop_with_more_tasks_than_a_wave(tasks, per_wave):
+    from paper_2401_04338_amd import GMeta
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda", 0)
+    dims = [5, 4, 1]
+    gen = torch.Generator(device=dev).manual_seed(1)
+    params = Params(torch.zeros(0, 4, device=dev), [torch.randn(a, b, device=dev, generator=gen) for a, b in zip(dims[:-1], dims[1:])],
+                    [torch.randn(b, device=dev, generator=gen) for b in dims[1:]])
+    batches = [_dense_only_batch(tasks, 5, dev, 7 + i) for i in range(2)]
+    ctx = GMeta(0, [], 4, 5, dims, 0, workspace_bytes=6 << 30)   # (holds the loop's two batches as one wave each)
+    ctx.configure("max_wave_tasks", per_wave)
+    one, loop = _clone(params, dev), _clone(params, dev)
+    want = [float(ctx.meta_train_step(s, q, one, 0.05, 1, 2, 1e-4).item()) for s, q in batches]
+    losses = ctx.meta_train(batches, loop, 0.05, 1, 2, 1e-4)
+    assert ctx.iterations_done == 2 and [float(x) for x in losses.cpu()] == want
+    _same_params(loop, one)
+    assert all(torch.isfinite(w).all() for w in loop.W)
+    ctx.close()
