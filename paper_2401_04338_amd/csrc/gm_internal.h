@@ -237,7 +237,8 @@ struct PairHopArgs {
     const int32_t* tiles;                     // set by the launcher
 };
 // The work of a hop over the tasks of a wave, by the outputs asked for: the small tasks, and the tiles of 256 out-rows of the
-// others as eight lists (one per XCD; nine offsets, then the entries: task, which enabled output << 16, tile << 17, run << 19).
+// others as eight lists (one per XCD; nine offsets, then the entries: task, number among its entries << 16, run << 19).  A task
+// has one entry per tile (at most eight) and run of fields, back to back; together they stand for run x tiles workgroups.
 enum { HOP_BOTH = 0, HOP_SUPPORT = 1, HOP_QUERY = 2 };
 enum { HOP_SMALL = 64 };
 struct HopTask { int32_t t, ns, nq; };        // (task numbers below 65536, at most 1024 rows)

@@ -324,11 +324,14 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 //   tasks of at most 64 rows in both sets   one workgroup per (task, field, DS columns) takes both outputs from one staged Z
 //   the others                              tiles of 256 out-rows; a last tile of at most 128 (64) rows gives every wave one
 //                                           strip of 32 rows (and half the columns).  The tasks are dealt to the XCDs by
-//                                           size, largest first, a task's tiles to one XCD (they read the same rows of Z);
+//                                           size, largest first, a task's tiles to one XCD and there field by field (both
+//                                           outputs and all row blocks of a field read the same Z, which L2 still holds);
 //                                           a few tasks are dealt in runs of fields.
 // Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
 // 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
 // (256 + 256) rows x 26 fields 6.7 -> 6.6 ms, 4.8 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
+// Fetched by the two hops of 256 tasks x (512 + 512) rows x 64 fields: 19.6 GB with a tile's fields first, 15.5 GB with a field's tiles
+// first, by the six of 512 tasks x (256 + 256) rows x 26 fields 20.1 and 19.0 GB (the time is the same within 0.3 %).
 // ------------------------------------------------------------------------------------------------
 #define PH_KC 64
 
@@ -543,16 +546,21 @@ template <int DS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_hop_kernel(PairHopArgs a) {
     constexpr int NCT = DS / 32;      // 32-column tiles
     __shared__ __attribute__((aligned(16))) bf16_t zs[2 * HopStage<DS>::WORDS];
-    // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, the fields of one entry in a row
+    // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, a run of one task's fields in a row and
+    // for every field all of the task's tiles
     const int nsl = a.D / DS, fx = a.F * nsl;
     const int xcd = blockIdx.x & 7, k = (int)(blockIdx.x >> 3), e = a.tiles[xcd] + k / a.run;
     if (e >= a.tiles[xcd + 1]) return;
     const u32 entry = (u32)a.tiles[9 + e];
-    const int t = (int)(entry & 0xFFFFu), o = (int)((entry >> 16) & 1u), row0 = (int)((entry >> 17) & 3u) * 256;
-    const int fs = (int)(entry >> 19) * a.run + k % a.run, f = fs / nsl, sl = fs - f * nsl;
-    if (fs >= fx || !a.task_path[t]) return;
+    const int t = (int)(entry & 0xFFFFu);
+    if (!a.task_path[t]) return;
+    const int n0 = a.out[0].real_off[t + 1] - a.out[0].real_off[t], n1 = a.out[1].enabled ? a.out[1].real_off[t + 1] - a.out[1].real_off[t] : 0;
+    const int nt0 = (n0 + 255) >> 8, nt = nt0 + ((n1 + 255) >> 8);
+    const int u = (int)((entry >> 16) & 7u) * a.run + k % a.run, tile = u % nt, o = tile >= nt0, row0 = (o ? tile - nt0 : tile) * 256;
+    const int fs = (int)(entry >> 19) * a.run + u / nt, f = fs / nsl, sl = fs - f * nsl;
+    if (fs >= fx) return;
     const PairHopOut& out = a.out[o];
-    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], n_out = out.real_off[t + 1] - out.real_off[t];
+    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], n_out = o ? n1 : n0;
     const uint8_t* M = a.mat + out.mat_off[t] + (size_t)f * pad64(n_out) * pad64(n_in);
     const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
     const float* Z0 = a.Z + (int64_t)a.in_row_off[t] * a.ldz + colz;
@@ -643,12 +651,10 @@ HopPlan hop_plan(const std::vector<HopTask>& tasks, int fx) {
         for (const HopTask& t : large)
             for (int r = 0; r < runs; ++r, ++unit) {
                 const int x = (int)(unit & 8 ? 7 - (unit & 7) : unit & 7);
-                for (int o = 0; o < 2; ++o) {
-                    if (kind != HOP_BOTH && kind != (o ? HOP_QUERY : HOP_SUPPORT)) continue;
-                    const u32 slot = kind == HOP_BOTH ? o : 0;   // the place of the output among those enabled
-                    const int n = o ? t.nq : t.ns;
-                    for (int rb = 0; rb * 256 < n; ++rb) of[x].push_back((int32_t)((u32)t.t | (slot << 16) | ((u32)rb << 17) | ((u32)r << 19)));
-                }
+                u32 nt = 0;   // the task's tiles: as many entries, which share its (tile, field)s
+                if (kind != HOP_QUERY) nt += (u32)(t.ns + 255) / 256;
+                if (kind != HOP_SUPPORT) nt += (u32)(t.nq + 255) / 256;
+                for (u32 j = 0; j < nt; ++j) of[x].push_back((int32_t)((u32)t.t | (j << 16) | ((u32)r << 19)));
             }
         std::vector<int32_t>& l = p.tiles[kind];
         l.assign(9, 0);

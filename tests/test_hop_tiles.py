@@ -1,5 +1,6 @@
 """The row hops at the edges of their tiles: task sizes around 64, 128 and 256 rows in either set, tasks with an empty
-support set, more than eight tasks (the lists of the XCDs), one and two column tiles per row and rows of several slices."""
+support set, more than eight tasks (the lists of the XCDs), one and two column tiles per row and rows of several slices,
+tasks of up to 1024 rows (four tiles and a run of fields beyond the first)."""
 import dataclasses
 
 import numpy as np
@@ -24,15 +25,15 @@ def _cut(s, sizes, F):
                                dense=s.dense[torch.from_numpy(keep)], labels=s.labels[torch.from_numpy(keep)])
 
 
-@pytest.mark.parametrize("D,bf,ns,nq", [
-    (64, 0, [1, 64, 63, 64, 32, 33, 2, 31, 7, 64], [64, 1, 63, 64, 33, 32, 2, 31, 64, 64]),
-    (64, 0, [65, 64, 128, 129, 1, 192, 3, 66, 127, 193], [64, 65, 129, 128, 193, 1, 128, 3, 66, 127]),
-    (32, 0, [257, 10, 256, 255, 64, 65, 300, 130], [10, 257, 255, 256, 65, 64, 130, 300]),
-    (128, 0, [70, 5, 200], [5, 70, 129]),
-    (64, 1, [320, 64, 65, 9, 40], [33, 64, 257, 130, 40])])
-def test_tile_edges(gm, D, bf, ns, nq):  # noqa: F811
-    F = 3
-    cfg = small_cfg(n_tasks=len(ns), n_fields=F, emb_dim=D, rows_per_field=60, n_support=max(ns), n_query=max(nq), bag_max=3,
+@pytest.mark.parametrize("F,D,bf,ns,nq", [
+    (3, 64, 0, [1, 64, 63, 64, 32, 33, 2, 31, 7, 64], [64, 1, 63, 64, 33, 32, 2, 31, 64, 64]),
+    (3, 64, 0, [65, 64, 128, 129, 1, 192, 3, 66, 127, 193], [64, 65, 129, 128, 193, 1, 128, 3, 66, 127]),
+    (3, 32, 0, [257, 10, 256, 255, 64, 65, 300, 130], [10, 257, 255, 256, 65, 64, 130, 300]),
+    (3, 128, 0, [70, 5, 200], [5, 70, 129]),
+    (3, 64, 1, [320, 64, 65, 9, 40], [33, 64, 257, 130, 40]),
+    (9, 32, 0, [513, 30, 1024, 769, 200], [1024, 31, 513, 100, 768])])
+def test_tile_edges(gm, F, D, bf, ns, nq):  # noqa: F811
+    cfg = small_cfg(n_tasks=len(ns), n_fields=F, emb_dim=D, rows_per_field=60, n_support=max(ns), n_query=max(nq), bag_max=3 if F < 9 else 1,
                     layer_dims=(F * D + 5, 40, 1), mlp_dtype=bf)
     sup, qry, params = _inputs(cfg, emb_std=0.3)
     sup, qry = _cut(sup, ns, F), _cut(qry, nq, F)
