@@ -945,50 +945,66 @@ static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
     return n;
 }
 
-// out_g[ld_{l-1}, ld_l] = c0*in_g + c1 * sum_p a_p[rows_g, ld_{l-1}]^T d_p[rows_g, ld_l]  (and its bf16 copies)
-// later (fp32): the product is added to this list, for one launch with others that depend on nothing of each other
-static void dense_tn_n(gm_ctx* c, const Grp& g, int l, int np, const Act* const* as, const Act* const* ds, Theta& out,
-                       const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true, std::vector<GemmArgs>* later = nullptr) {
-    const int M = c->ld[l - 1], N = c->ld[l];
-    {
-        const double esz = c->mlp_dtype ? 2.0 : 4.0;
-        const double out_b = c->mlp_dtype ? ((write_f32 || !out.b) ? 4.0 : 0.0) + (out.b ? 2.0 : 0.0) : 4.0;
-        const double by = (double)np * g.rows * (M + N) * esz + (double)g.G * M * N * (out_b + ((in && in_stride) ? 4.0 : 0.0));
-        Prof p(c, "gemm_wgrad", by, 2.0 * g.rows * N * M * np);
-        if (c->mlp_dtype == 0) {
-            GemmArgs a;
-            memset(&a, 0, sizeof a);
-            a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = np;
-            for (int i = 0; i < np; ++i) {
-                a.A[i] = as[i]->f; a.sAm[i] = 1; a.sAk[i] = M; a.rA[i] = M;
-                a.B[i] = ds[i]->f; a.sBk[i] = N; a.sBn[i] = 1; a.rB[i] = N;
-            }
-            a.C = out.f + c->offW[l]; a.ldc = N; a.gC = out.sf; a.M = M; a.N = N; a.K = -1;
-            a.epi = EPI_AXPBY; a.Cin = in ? in + c->offW[l] : nullptr; a.gCin = in_stride; a.c0 = c0; a.c1 = c1;
-            if (later) later->push_back(a);
-            else launch_gemm_f32_wgrads(c->stream, &a, 1);
-        } else {
-            GemmBArgs a;
-            memset(&a, 0, sizeof a);
-            a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = np;
-            for (int i = 0; i < np; ++i) {   // activations and deltas as they are stored: [rows, width]
-                a.A[i] = as[i]->b; a.lda[i] = M; a.rA[i] = M;
-                a.B[i] = ds[i]->b; a.ldb[i] = N; a.rB[i] = N;
-            }
-            if (write_f32 || !out.b) { a.Cf = out.f + c->offW[l]; a.ldcf = N; a.gCf = out.sf; }
-            a.M = M; a.N = N; a.K = -1;
-            if (out.b) {  // the bf16 operand copy of W
-                a.Cb = out.b + c->offWb[l]; a.ldcb = N; a.gCb = out.sb;
-            }
-            a.epi = EPI_AXPBY; a.Cin = in ? in + c->offW[l] : nullptr; a.gCin = in_stride; a.ldcin = N; a.c0 = c0; a.c1 = c1;
-            launch_gemm_bf16_kmajor(c->stream, a, wgrad_wide_ok(c, M, N, g.rows, g.G) ? 256 : 128);
+// fp32 weight gradients of one pass that depend on nothing of each other, collected and launched together
+struct WGrads {
+    std::vector<GemmArgs> list;
+    std::vector<double> bytes, flops;   // algorithmic, of every product
+    void add(const GemmArgs& a, double by, double fl) { list.push_back(a); bytes.push_back(by); flops.push_back(fl); }
+    void launch(gm_ctx* c) {
+        for (size_t i0 = 0; i0 < list.size(); i0 += GEMM_LIST) {
+            const size_t i1 = std::min(list.size(), i0 + (size_t)GEMM_LIST);
+            double by = 0, fl = 0;
+            for (size_t i = i0; i < i1; ++i) { by += bytes[i]; fl += flops[i]; }
+            Prof p(c, "gemm_wgrad", by, fl);
+            launch_gemm_f32_wgrads(c->stream, list.data() + i0, (int)(i1 - i0));
         }
+    }
+};
+
+// out_g[ld_{l-1}, ld_l] = c0*in_g + c1 * sum_p a_p[rows_g, ld_{l-1}]^T d_p[rows_g, ld_l]  (and its bf16 copies)
+// later: where an fp32 product goes instead of a launch of its own
+static void dense_tn_n(gm_ctx* c, const Grp& g, int l, int np, const Act* const* as, const Act* const* ds, Theta& out,
+                       const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true, WGrads* later = nullptr) {
+    const int M = c->ld[l - 1], N = c->ld[l];
+    const double esz = c->mlp_dtype ? 2.0 : 4.0;
+    const double out_b = c->mlp_dtype ? ((write_f32 || !out.b) ? 4.0 : 0.0) + (out.b ? 2.0 : 0.0) : 4.0;
+    const double by = (double)np * g.rows * (M + N) * esz + (double)g.G * M * N * (out_b + ((in && in_stride) ? 4.0 : 0.0));
+    const double fl = 2.0 * g.rows * N * M * np;
+    if (c->mlp_dtype == 0) {
+        GemmArgs a;
+        memset(&a, 0, sizeof a);
+        a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = np;
+        for (int i = 0; i < np; ++i) {
+            a.A[i] = as[i]->f; a.sAm[i] = 1; a.sAk[i] = M; a.rA[i] = M;
+            a.B[i] = ds[i]->f; a.sBk[i] = N; a.sBn[i] = 1; a.rB[i] = N;
+        }
+        a.C = out.f + c->offW[l]; a.ldc = N; a.gC = out.sf; a.M = M; a.N = N; a.K = -1;
+        a.epi = EPI_AXPBY; a.Cin = in ? in + c->offW[l] : nullptr; a.gCin = in_stride; a.c0 = c0; a.c1 = c1;
+        WGrads alone;
+        (later ? *later : alone).add(a, by, fl);
+        alone.launch(c);
+    } else {
+        Prof p(c, "gemm_wgrad", by, fl);
+        GemmBArgs a;
+        memset(&a, 0, sizeof a);
+        a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = np;
+        for (int i = 0; i < np; ++i) {   // activations and deltas as they are stored: [rows, width]
+            a.A[i] = as[i]->b; a.lda[i] = M; a.rA[i] = M;
+            a.B[i] = ds[i]->b; a.ldb[i] = N; a.rB[i] = N;
+        }
+        if (write_f32 || !out.b) { a.Cf = out.f + c->offW[l]; a.ldcf = N; a.gCf = out.sf; }
+        a.M = M; a.N = N; a.K = -1;
+        if (out.b) {  // the bf16 operand copy of W
+            a.Cb = out.b + c->offWb[l]; a.ldcb = N; a.gCb = out.sb;
+        }
+        a.epi = EPI_AXPBY; a.Cin = in ? in + c->offW[l] : nullptr; a.gCin = in_stride; a.ldcin = N; a.c0 = c0; a.c1 = c1;
+        launch_gemm_bf16_kmajor(c->stream, a, wgrad_wide_ok(c, M, N, g.rows, g.G) ? 256 : 128);
     }
 }
 
 static void dense_tn(gm_ctx* c, const Grp& g, int l, int np, const Act* a0, const Act* d0, const Act* a1, const Act* d1,
                      Theta& out, const float* in, int64_t in_stride, float c0, float c1, bool write_f32 = true,
-                     std::vector<GemmArgs>* later = nullptr) {
+                     WGrads* later = nullptr) {
     const Act* as[2] = {a0, a1};
     const Act* ds[2] = {d0, d1};
     dense_tn_n(c, g, l, np, as, ds, out, in, in_stride, c0, c1, write_f32, later);
@@ -1081,7 +1097,7 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
     const int L = c->L;
     const int64_t nt = out.sf;
     ColSums sums{c, g};
-    std::vector<GemmArgs> later;
+    WGrads later;
     for (int l = 1; l < L; ++l) {
         const Act* prev = l == 1 ? p.X : &(*p.A)[l - 1];
         if (coarse) dense_tn(c, *coarse, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, *coarse_out, nullptr, 0, 0.f, c1, true, &later);
@@ -1098,10 +1114,7 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
         sums.add(c->ld[l], &(*p.Dl)[l], nullptr, nullptr, nullptr, out.f + c->offb[l], nt, in ? in + c->offb[l] : nullptr,
                  in_stride, c0, c1);
     }
-    if (!later.empty()) {
-        Prof pr(c, "gemm_wgrad", 0, 0);   // (its bytes and operations are counted layer by layer)
-        launch_gemm_f32_wgrads(c->stream, later.data(), (int)later.size());
-    }
+    later.launch(c);
     const Act* prev = L == 1 ? p.X : &(*p.A)[L - 1];
     sums.add(c->ld[L - 1], prev, p.dL, nullptr, nullptr, out.f + c->offW[L], nt, in ? in + c->offW[L] : nullptr, in_stride, c0, c1);
     sums.add_scalar(p.dL, out.f + c->offb[L], nt, in ? in + c->offb[L] : nullptr, in_stride, c0, c1);
@@ -1154,7 +1167,7 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
     sums.add(c->ld[L - 1], tprev, s.dL, prev, w.tdL, v.f + c->offW[L], nt, v.f + c->offW[L], nt, 1.f, -alpha);
     sums.add_scalar(w.tdL, v.f + c->offb[L], nt, v.f + c->offb[L], nt, 1.f, -alpha);
     Theta vout = v;
-    std::vector<GemmArgs> later;   // (fp32: the loop's products read every layer's direction before any is updated)
+    WGrads later;   // (fp32: the loop's products read every layer's direction before any is updated)
     if (!refresh_v_copies) vout.b = nullptr;
     for (int l = L - 1; l >= 1; --l) {
         if (l == 1) dense_nt(c, g, l, 2, &w.TD[l], &s.th, &s.Dl[l], &v, nullptr, nullptr, w.dX, gx_acc, -alpha, need_dx || !gx_acc, gx_init);
@@ -1168,10 +1181,7 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
         else dense_tn(c, g, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], vout, v.f, nt, 1.f, -alpha, true, &later);
         sums.add(c->ld[l], &w.TD[l], nullptr, nullptr, nullptr, v.f + c->offb[l], nt, v.f + c->offb[l], nt, 1.f, -alpha);
     }
-    if (!later.empty()) {
-        Prof pr(c, "gemm_wgrad", 0, 0);
-        launch_gemm_f32_wgrads(st, later.data(), (int)later.size());
-    }
+    later.launch(c);
     sums.launch();
 }
 

@@ -17,6 +17,28 @@ def test_more_than_one_gpu_is_refused_with_a_message():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("bf,layers", [(0, 2), (0, 6), (1, 2)])
+def test_timed_launches_of_the_weight_gradients(bf, layers):
+    """The timing report's launches, bytes and operations of the weight gradients: in fp32 a pass's products share launches
+    of at most four, in bf16 each has its own."""
+    from paper_2401_04338_amd import GMeta
+    from tests.helpers import small_cfg
+    from tests.test_gpu_parity import _inputs, _params_dev, _to_dev
+    cfg = small_cfg(n_tasks=3, n_support=16, n_query=8, layer_dims=(17,) + (40,) * layers + (1,), mlp_dtype=bf)
+    sup, qry, params = _inputs(cfg)
+    ctx = GMeta.from_config(cfg, workspace_bytes=1 << 28)
+    ctx.profile(True)
+    ctx.meta_step(_to_dev(sup, ctx.device), _to_dev(qry, ctx.device), _params_dev(params, ctx.device), cfg.inner_lr, 1, 2)
+    r = ctx.profile_report()["gemm_wgrad"]
+    ctx.close()
+    assert r["launches"] == 3 * (layers if bf else -(-layers // 4))   # inner step, query set, tangent pass
+    width = 32 * 64 + (layers - 1) * 64 * 64   # products' outputs, padded
+    # one product per row of either set; in the tangent pass two (the first layer's second only where rows are adapted further)
+    least = 2.0 * width * (3 * 16 + 3 * 8 + 3 * 16)
+    assert least <= r["flops"] <= least + 2.0 * width * 3 * 16 and r["bytes"] > 0
+
+
+@pytest.mark.gpu
 def test_json_line_of_a_small_run():
     """The smallest config, a few steps: one JSON line on stdout with every field of the contract, the roofline of the
     dominant kernel family and the oracle timed beside it."""
