@@ -264,7 +264,7 @@ def main():
 
     # The prefetch reads hot rows from the caches: its logical bytes (4 D per lookup) can exceed what HBM delivers.  Its
     # fraction of the roofline is therefore taken on the COMPULSORY bytes of a launch: every distinct row once, the
-    # indices, the offsets and the pooled outputs (counted here for the first wave of tasks of each set).
+    # indices, the offsets and the pooled outputs (counted here for the first wave of tasks).
     for f in fams:
         if f["kernel"] != "gather_pool" or cfg.n_fields == 0:
             continue
@@ -364,17 +364,17 @@ def measured_traffic(workload, family, launches_per_step, n_tasks, tasks_per_wav
 
 
 def compulsory_gather_bytes(cfg, sup, qry, n_tasks):
-    """Bytes one prefetch launch cannot avoid moving, averaged over the two launches (support, query) of the first
-    n_tasks tasks: distinct table rows * 4 D + 4 per lookup + 8 per bag + the pooled rows written (fp32, and the bf16
-    operand copy when the MLP runs on bf16 operands)."""
+    """Bytes the prefetch of the first n_tasks tasks cannot avoid moving (one launch takes both sets): distinct table rows
+    of both sets * 4 D + 4 per lookup + 8 per bag + the pooled rows written (fp32, and the bf16 operand copy when the MLP
+    runs on bf16 operands)."""
     import torch
     F, R, D = cfg.n_fields, cfg.rows_per_field, cfg.emb_dim
     ld0 = -(-cfg.layer_dims[0] // 32) * 32
     total = 0.0
+    mark = torch.zeros(cfg.total_rows, dtype=torch.bool, device=sup.indices.device)
     for sd in (sup, qry):
         s1 = int(sd.task_offsets[n_tasks])
         lo, hi = int(sd.bag_offsets[0].item()), int(sd.bag_offsets[s1 * F].item())
-        mark = torch.zeros(cfg.total_rows, dtype=torch.bool, device=sd.indices.device)
         step_bags = max(1, (1 << 24) // max(cfg.bag_max, 1))
         for b0 in range(0, s1 * F, step_bags):      # in pieces: the per-lookup field ids are 8 bytes each
             b1 = min(s1 * F, b0 + step_bags)
@@ -382,10 +382,8 @@ def compulsory_gather_bytes(cfg, sup, qry, n_tasks):
             lens = offs[1:] - offs[:-1]
             field = (torch.arange(b0, b1, device=lens.device) % F).repeat_interleave(lens)
             mark[sd.indices[int(offs[0].item()): int(offs[-1].item())].long() + field * R] = True
-        distinct = int(mark.sum().item())
-        del mark
-        total += distinct * 4.0 * D + (hi - lo) * 4.0 + s1 * F * 8.0 + s1 * ld0 * (4.0 + (2.0 if cfg.mlp_dtype else 0.0))
-    return total / 2.0
+        total += (hi - lo) * 4.0 + s1 * F * 8.0 + s1 * ld0 * (4.0 + (2.0 if cfg.mlp_dtype else 0.0))
+    return total + int(mark.sum().item()) * 4.0 * D
 
 
 def outer_update_timing(cfg, params, out, ws):

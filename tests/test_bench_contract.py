@@ -4,7 +4,9 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -14,6 +16,24 @@ def test_more_than_one_gpu_is_refused_with_a_message():
                        timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_compulsory_bytes_of_the_prefetch():
+    """Both sets in one launch: a row that both look up is counted once, lookups, bags and pooled rows of either add up."""
+    sys.path.insert(0, ROOT)
+    from bench import compulsory_gather_bytes
+    from synth.generate import SetData
+    from tests.helpers import small_cfg
+    cfg = small_cfg(n_tasks=2, n_fields=2, emb_dim=4, rows_per_field=10, n_dense=5, layer_dims=(13, 8, 1), mlp_dtype=1)
+
+    def one(task_offsets, lens, idx):
+        n = task_offsets[-1]
+        return SetData(np.array(task_offsets), torch.tensor([0] + list(np.cumsum(lens))), torch.tensor(idx, dtype=torch.int32),
+                       torch.zeros(n, 5), torch.zeros(n))
+    sup = one([0, 2, 3], [1, 2, 1, 0, 1, 1], [3, 5, 6, 3, 9, 9])      # task 0: rows (0,3) (1,5) (1,6)
+    qry = one([0, 1, 2], [2, 1, 1, 1], [3, 4, 5, 0, 0])               # task 0: rows (0,3) (0,4) (1,5)
+    rows, lookups, bags, samples = 4, 4 + 3, 4 + 2, 2 + 1
+    assert compulsory_gather_bytes(cfg, sup, qry, 1) == rows * 16 + lookups * 4 + bags * 8 + samples * 32 * 6
 
 
 @pytest.mark.gpu
