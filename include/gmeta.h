@@ -124,7 +124,8 @@ int gm_meta_step(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_s
                  float* loss, gm_grads* out);
 
 /* gm_meta_step for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc): same arguments, same results, but every intermediate buffer lives in a static
+ * harnesses that forbid hipMalloc): same arguments, same results (where the scratch takes the tasks in other waves than
+ * the workspace: as "max_wave_tasks" below says), but every intermediate buffer lives in a static
  * device array of GM_STATIC_SCRATCH_MIB MiB that is part of the library's code object (each GPU the library runs on
  * holds its copy until the process ends) instead of the context's workspace, and the call allocates and frees
  * nothing on the device.  The caller still passes inputs and outputs; ctx must have been created before (gm_create
@@ -278,7 +279,11 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               best; 1..32 = that many.  Another grouping adds the same per-task terms in another order
  *               (fp32 rounding).
  *   "max_wave_tasks": most tasks processed at a time (0 = as many as the workspace holds).  Tasks are independent
- *               (Alg. 1): a call runs them in waves of nearly equal size, the fewest that fit the workspace.
+ *               (Alg. 1): a call runs them in waves of nearly equal size, the fewest that fit the workspace.  Losses,
+ *               row lists and row gradients are identical however the tasks are cut into waves, the bias gradients and
+ *               the last layer's too; the hidden layers' weight gradients are summed over other runs of tasks (see
+ *               "coarse_groups"), a wave with a bag or a (task, field) beyond the pair matrices' limits takes the other
+ *               row arithmetic whole ("row_path"), and with emb_grad_table every wave adds its own sums to a row.
  *   "pair_tile_rows": most out-rows of a pair-count matrix that the counting kernel holds in LDS at a time
  *               (0 = as many as fit); identical results.
  * Unknown keys or values give GM_ERR_ARG. */

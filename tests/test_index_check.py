@@ -1,0 +1,45 @@
+"""The check of the indices (all that stands before the gathers) finds one bad index wherever it lies.  Tables of one size:
+a workgroup's threads read four indices a trip, `step` = 256 x (workgroups of the task) apart, so the places are the ends of
+each of the four, of the trip after and of the list.  Tables of different sizes: bag by bag.  gm_index_prep checks and does
+not gather."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_parity import gm  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+F, ROWS = 2, 50
+
+
+def _set(samples, bag):
+    n = samples * F
+    return SimpleNamespace(n_samples=samples, task_offsets=np.array([0, samples], dtype=np.int64), labels=torch.zeros(samples, device="cuda:0"),
+                           bag_offsets=torch.arange(0, (n + 1) * bag, bag, dtype=torch.int64, device="cuda:0"), nnz=n * bag,
+                           indices=torch.arange(n * bag, dtype=torch.int32, device="cuda:0") % ROWS, dense=torch.zeros(samples, 1, device="cuda:0"))
+
+
+@pytest.mark.parametrize("uneven", [0, 1])
+@pytest.mark.parametrize("samples,bag,split", [(100, 6, 1), (300, 5, 2), (700, 9, 5)])   # (split: bags of both sets / 512)
+def test_one_bad_index(gm, samples, bag, split, uneven):  # noqa: F811
+    from paper_2401_04338_amd import GMetaError
+    step, n = 256 * split, samples * F * bag
+    assert split == max(1, 2 * samples * F // 512) and n > 4 * step
+    ctx = gm(F, [ROWS, ROWS + uneven], 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 26)
+    sets = [_set(samples, bag), _set(samples, bag)]
+    ctx.index_prep(*sets)
+    for s in sets:
+        for at in sorted({k * step + d for k in range(5) for d in (-1, 0, 1)} - {-1} | {n - 1}):
+            if at >= n:
+                continue
+            good = int(s.indices[at])
+            for bad in (-1, ROWS + uneven):
+                s.indices[at] = bad
+                with pytest.raises(GMetaError) as e:
+                    ctx.index_prep(*sets)
+                assert e.value.code == -2, (at, bad)
+            s.indices[at] = good
+    ctx.index_prep(*sets)
+    ctx.close()
