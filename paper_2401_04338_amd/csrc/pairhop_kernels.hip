@@ -324,14 +324,16 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 //   tasks of at most 64 rows in both sets   one workgroup per (task, field, DS columns) takes both outputs from one staged Z
 //   the others                              tiles of 256 out-rows; a last tile of at most 128 (64) rows gives every wave one
 //                                           strip of 32 rows (and half the columns).  The tasks are dealt to the XCDs by
-//                                           size, largest first, a task's tiles to one XCD and there field by field (both
-//                                           outputs and all row blocks of a field read the same Z, which L2 still holds);
+//                                           size, largest first, a task's tiles to one XCD (all of a field's read the same Z);
 //                                           a few tasks are dealt in runs of fields.
 // Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
 // 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
-// (256 + 256) rows x 26 fields 6.7 -> 6.6 ms, 4.8 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
-// Fetched by the two hops of 256 tasks x (512 + 512) rows x 64 fields: 19.6 GB with a tile's fields first, 15.5 GB with a field's tiles
-// first, by the six of 512 tasks x (256 + 256) rows x 26 fields 20.1 and 19.0 GB (the time is the same within 0.3 %).
+// (256 + 256) rows x 26 fields 6.7 -> 6.5 ms, 4.7 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
+// Inside a run of fields the tiles come first, field by field, where a task has more than two of them: Z is read that often, and
+// the others of a field find it in L2 (two hops of 256 tasks x (512 + 512) rows x 64 fields, four tiles each, fetch 15.5 GB instead
+// of 19.6 and take 5.03 instead of 5.30 ms on one card, 4.97 against 5.15 on another).  One or two tiles: the fields come first, a
+// tile's pieces of the same rows one after the other (six hops of 512 tasks x (256 + 256) rows x 26 fields, two tiles each, 6.52 ms;
+// tiles first they fetch 19.0 GB instead of 20.1 but take 6.59).
 // ------------------------------------------------------------------------------------------------
 #define PH_KC 64
 
@@ -546,25 +548,40 @@ template <int DS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_hop_kernel(PairHopArgs a) {
     constexpr int NCT = DS / 32;      // 32-column tiles
     __shared__ __attribute__((aligned(16))) bf16_t zs[2 * HopStage<DS>::WORDS];
-    // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, a run of one task's fields in a row and
-    // for every field all of the task's tiles
+    // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, all (tile, field)s of one task's run in a row
     const int nsl = a.D / DS, fx = a.F * nsl;
     const int xcd = blockIdx.x & 7, k = (int)(blockIdx.x >> 3), e = a.tiles[xcd] + k / a.run;
     if (e >= a.tiles[xcd + 1]) return;
     const u32 entry = (u32)a.tiles[9 + e];
     const int t = (int)(entry & 0xFFFFu);
-    if (!a.task_path[t]) return;
-    const int n0 = a.out[0].real_off[t + 1] - a.out[0].real_off[t], n1 = a.out[1].enabled ? a.out[1].real_off[t + 1] - a.out[1].real_off[t] : 0;
-    const int nt0 = (n0 + 255) >> 8, nt = nt0 + ((n1 + 255) >> 8);
-    const int u = (int)((entry >> 16) & 7u) * a.run + k % a.run, tile = u % nt, o = tile >= nt0, row0 = (o ? tile - nt0 : tile) * 256;
-    const int fs = (int)(entry >> 19) * a.run + u / nt, f = fs / nsl, sl = fs - f * nsl;
+    // (both outputs' values are asked for at once: which of them is meant follows from their sizes)
+    const u32 on = a.task_path[t];
+    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], in_row = a.in_row_off[t];
+    int n[2], row_off[2];
+    int64_t mat_off[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        n[o] = a.out[o].real_off[t + 1] - a.out[o].real_off[t];
+        row_off[o] = a.out[o].row_off[t];
+        mat_off[o] = a.out[o].mat_off[t];
+    }
+    if (!on) return;
+    const int nt0 = (n[0] + 255) >> 8, nt = nt0 + (a.out[1].enabled ? (n[1] + 255) >> 8 : 0);
+    int tile = (int)((entry >> 16) & 7u), i = k % a.run;   // (tile, field) in the run, fields first
+    if (nt > 2) {                                           // tiles first
+        const int u = tile * a.run + i;
+        i = u / nt;
+        tile = u - i * nt;
+    }
+    const int o = tile >= nt0, row0 = (o ? tile - nt0 : tile) * 256;
+    const int fs = (int)(entry >> 19) * a.run + i, f = fs / nsl, sl = fs - f * nsl;
     if (fs >= fx) return;
     const PairHopOut& out = a.out[o];
-    const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], n_out = o ? n1 : n0;
-    const uint8_t* M = a.mat + out.mat_off[t] + (size_t)f * pad64(n_out) * pad64(n_in);
+    const int n_out = o ? n[1] : n[0];
+    const uint8_t* M = a.mat + (o ? mat_off[1] : mat_off[0]) + (size_t)f * pad64(n_out) * pad64(n_in);
     const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
-    const float* Z0 = a.Z + (int64_t)a.in_row_off[t] * a.ldz + colz;
-    const int64_t row_base = out.row_off[t];
+    const float* Z0 = a.Z + (int64_t)in_row * a.ldz + colz;
+    const int64_t row_base = o ? row_off[1] : row_off[0];
     if (n_out - row0 > 128) hop_tile<DS, 2, NCT>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
     else if (n_out - row0 > 64) hop_tile<DS, 1, NCT>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
     else hop_tile<DS, 1, 1>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
@@ -670,8 +687,9 @@ HopPlan hop_plan(const std::vector<HopTask>& tasks, int fx) {
 void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3], const int longest[3]) {
     const int kind = a.out[0].enabled ? (a.out[1].enabled ? HOP_BOTH : HOP_SUPPORT) : HOP_QUERY;
     if (a.F <= 0 || !(a.out[0].enabled || a.out[1].enabled)) return;
-    if (kind == HOP_QUERY) {
-        a.out[0] = a.out[1];
+    if (kind == HOP_QUERY) a.out[0] = a.out[1];
+    if (kind != HOP_BOTH) {   // (its arrays are read all the same)
+        a.out[1] = a.out[0];
         a.out[1].enabled = 0;
     }
     a.tiles = tiles[kind];
