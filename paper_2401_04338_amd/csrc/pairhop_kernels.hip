@@ -329,11 +329,10 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 // Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
 // 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
 // (256 + 256) rows x 26 fields 6.7 -> 6.5 ms, 4.7 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
-// Inside a run of fields the tiles come first, field by field, where a task has more than two of them: Z is read that often, and
-// the others of a field find it in L2 (two hops of 256 tasks x (512 + 512) rows x 64 fields, four tiles each, fetch 15.5 GB instead
-// of 19.6 and take 5.03 instead of 5.30 ms on one card, 4.97 against 5.15 on another).  One or two tiles: the fields come first, a
-// tile's pieces of the same rows one after the other (six hops of 512 tasks x (256 + 256) rows x 26 fields, two tiles each, 6.52 ms;
-// tiles first they fetch 19.0 GB instead of 20.1 but take 6.59).
+// Inside a run of fields the tiles come first, field by field, where an output has several: they find the field's Z in L2 (two hops
+// of 256 tasks x (512 + 512) rows x 64 fields, two tiles each, fetch 15.5 GB instead of 19.6; eleven runs of a side 4.86..5.12 against
+// 5.05..5.35 ms).  With one tile per output the fields come first, a tile's pieces of the same rows one after the other (six hops of
+// 512 tasks x (256 + 256) rows x 26 fields 6.35..6.57 ms; tiles first they fetch 19.0 GB instead of 20.1 and take 1-2 % longer).
 // ------------------------------------------------------------------------------------------------
 #define PH_KC 64
 
@@ -566,9 +565,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         mat_off[o] = a.out[o].mat_off[t];
     }
     if (!on) return;
-    const int nt0 = (n[0] + 255) >> 8, nt = nt0 + (a.out[1].enabled ? (n[1] + 255) >> 8 : 0);
+    const int nt0 = (n[0] + 255) >> 8, nt1 = a.out[1].enabled ? (n[1] + 255) >> 8 : 0, nt = nt0 + nt1;
     int tile = (int)((entry >> 16) & 7u), i = k % a.run;   // (tile, field) in the run, fields first
-    if (nt > 2) {                                           // tiles first
+    if (nt0 > 1 || nt1 > 1) {                               // tiles first
         const int u = tile * a.run + i;
         i = u / nt;
         tile = u - i * nt;
