@@ -2639,6 +2639,13 @@ static std::vector<int32_t> record_order(const int64_t* task, const int64_t* bat
     const uint64_t t0 = (uint64_t)*mt.first, b0 = (uint64_t)*mb.first, t_span = (uint64_t)*mt.second - t0, b_span = (uint64_t)*mb.second - b0;
     auto bits_of = [](uint64_t span) { int b = 0; while (b < 64 && (span >> b)) ++b; return b; };
     const int tb = bits_of(t_span), bb = bits_of(b_span);
+    // Few records with numbers far apart are compared: every pass also walks its digits' table.  256 records of one batch each,
+    // 63-bit task numbers, 3 us (27 us by digits), 1024 20 (48), 2048 80 (67); 31-bit ones, 512 7.2 (7.4), 1024 22 (15).
+    auto table = [](int bits) { const int passes = (bits + 12) / 13; return passes ? (int64_t)passes << ((bits + passes - 1) / passes) : 0; };
+    if ((tb + bb <= 64 ? table(tb + bb) : table(tb) + table(bb)) > 24 * n) {
+        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return task[a] != task[b] ? task[a] < task[b] : batch_id[a] < batch_id[b]; });
+        return order;
+    }
     std::vector<uint64_t> key((size_t)n);
     auto sort_by_key = [&](int bits) {   // key[i]: of record i
         const int passes = (bits + 12) / 13, width = passes ? (bits + passes - 1) / passes : 0;

@@ -1,5 +1,6 @@
 """The order of grouped records over the spans of the numbers they are ordered by (none, one digit, several, more than 64 bits
-together), streams of zero and one record, and a workspace that holds one of the two sets only."""
+together; either side of the line between comparing and counting digits), streams of zero and one record, and a workspace that
+holds one of the two sets only."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,8 @@ I64 = np.iinfo(np.int64)
 @pytest.mark.parametrize("n,lo,hi,b_hi,share,ws", [
     (0, 0, 1, 1, (1, 2), 1 << 24), (1, 5, 6, 1, (1, 2), 1 << 24), (300, 7, 8, 1, (2, 3), 1 << 24), (999, -3, 8192, 2, (1, 2), 1 << 24),
     (1000, 0, 40, 9000, (0, 1), 1 << 24), (1000, I64.min, I64.max, 1, (1, 1), 1 << 24), (1000, I64.min, I64.max, 50, (1, 2), 1 << 24),
-    (60000, 0, 300, 3, (1, 2), 1 << 20)])
+    (60000, 0, 300, 3, (1, 2), 1 << 20), (4000, I64.min, I64.max, 1, (1, 1), 1 << 24), (4000, I64.min, I64.max, 50, (1, 2), 1 << 24),
+    (200, 0, 1 << 31, 1, (1, 2), 1 << 24), (600, 0, 1 << 31, 1, (1, 2), 1 << 24), (40, -5, 1 << 40, 3, (1, 2), 1 << 24)])
 def test_orders(n, lo, hi, b_hi, share, ws):
     from paper_2401_04338_amd import GMeta
     F = 4
