@@ -132,13 +132,15 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
     }
 }
 
-void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t bags_per_task, SetView sup, SetView qry, const int64_t* field_base,
+void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status) {
     if (Tw <= 0) return;
     launch_zero(st, ZeroJobs{3, {status, cnt_sup, cnt_qry}, {ST_WORDS, (int64_t)Tw * F, cnt_qry != cnt_sup ? (int64_t)Tw * F : 0}});
     // A task's bags are split over workgroups of two bags per thread, down to 4096 workgroups in all: fewer leave the chip
     // idle with few tasks (3 tasks x 65536 bags in 24 workgroups 244 us, in 384 21 us), more only add their 2 F atomics each.
-    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(bags_per_task / 512, 4096 / Tw));
+    // The largest task decides: the others' spare workgroups have nothing to add, and it alone would be the launch's time
+    // (one task of 2048 + 2048 samples and 299 of 2 + 2, 40 fields: 67 us, 589 with the average task's split).
+    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(most_bags / 512, 4096 / Tw));
     hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, split), dim3(256), 2 * F * sizeof(u32), st, F, t0, sup, qry, field_base,
                        nnz_sup, nnz_qry, uniform_rows, cnt_sup, cnt_qry, status);
 }

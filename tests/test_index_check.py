@@ -43,3 +43,26 @@ def test_one_bad_index(gm, samples, bag, split, uneven):  # noqa: F811
             s.indices[at] = good
     ctx.index_prep(*sets)
     ctx.close()
+
+
+@pytest.mark.parametrize("uneven", [0, 1])
+def test_one_bad_index_beside_small_tasks(gm, uneven):  # noqa: F811
+    """The largest task decides how many workgroups every task gets: here five, of which the one-sample tasks fill none."""
+    from paper_2401_04338_amd import GMetaError
+    sizes = [1] * 20 + [700] + [1] * 20
+    ctx = gm(F, [ROWS, ROWS + uneven], 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 26)
+    sets = [_set(sum(sizes), 9), _set(sum(sizes), 9)]
+    for s in sets:
+        s.task_offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    ctx.index_prep(*sets)
+    per = F * 9
+    for s in sets:
+        for at in (0, 19 * per, 20 * per, 20 * per + 1280, 20 * per + 4 * 1280 - 1, 720 * per - 1, 720 * per, s.nnz - 1):
+            good = int(s.indices[at])
+            s.indices[at] = -1
+            with pytest.raises(GMetaError) as e:
+                ctx.index_prep(*sets)
+            assert e.value.code == -2, at
+            s.indices[at] = good
+    ctx.index_prep(*sets)
+    ctx.close()
