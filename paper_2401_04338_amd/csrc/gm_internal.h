@@ -342,7 +342,7 @@ struct ColJobs {
     int n;
     ColJob job[COL_JOBS];
 };
-void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offsets, const ColJob* list, int n);
+void launch_task_colsum(hipStream_t st, int bf16, int G, int most_rows, const int32_t* row_offsets, const ColJob* list, int n);   // most_rows: of one group
 // z[s] = a[s,:].w_g + b_g (+ ta[s,:].w_g + a[s,:].tw_g + tb_g when tangent); widths and strides are multiples of 32
 struct LastArgs {
     int64_t n; int N; int64_t ld;       // rows (padded), width of the last hidden layer, its leading dimension

@@ -809,6 +809,7 @@ struct Grp {  // grouping of one set's rows by task inside the wave
     const int32_t *tile_g, *tile_m;
     int n_mtiles, G, bm;
     int64_t rows;  // padded rows of the set in the wave
+    int most_rows; // of one task
 };
 
 
@@ -1029,7 +1030,7 @@ struct ColSums {
     }
     void launch() {
         Prof p(c, "task_colsum", bytes, 0);
-        launch_task_colsum(c->stream, c->mlp_dtype, g.G, g.row_off, jobs.data(), (int)jobs.size());
+        launch_task_colsum(c->stream, c->mlp_dtype, g.G, g.most_rows, g.row_off, jobs.data(), (int)jobs.size());
     }
 };
 
@@ -1684,8 +1685,9 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
     const int rc = up.send(c, B.images);
     if (rc != GM_OK) return rc;
     launch_expand_tasks(st, d.Tw, ExpandJobs{2, {{nullptr, w.row_off_s, nullptr, w.row_task_s}, {nullptr, w.row_off_q, nullptr, w.row_task_q}}});
-    gs = Grp{w.row_off_s, w.real_off_s, w.row_task_s, w.tile_g_s, w.tile_m_s, d.mt_s, d.Tw, bm, d.Ps};
-    gq = Grp{w.row_off_q, w.real_off_q, w.row_task_q, w.tile_g_q, w.tile_m_q, d.mt_q, d.Tw, bm, d.Pq};
+    auto most = [](const std::vector<int32_t>& off) { int32_t m = 0; for (size_t t = 1; t < off.size(); ++t) m = std::max(m, off[t] - off[t - 1]); return (int)m; };
+    gs = Grp{w.row_off_s, w.real_off_s, w.row_task_s, w.tile_g_s, w.tile_m_s, d.mt_s, d.Tw, bm, d.Ps, most(ro_s)};
+    gq = Grp{w.row_off_q, w.real_off_q, w.row_task_q, w.tile_g_q, w.tile_m_q, d.mt_q, d.Tw, bm, d.Pq, most(ro_q)};
     return GM_OK;
 }
 

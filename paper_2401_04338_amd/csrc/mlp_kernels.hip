@@ -254,7 +254,7 @@ void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n) {
 // out[g,n] = c0*in[g,n] + c1 * sum_{s in g} ( X1[s,n]*w1[s] + X2[s,n]*w2[s] ), rows summed in a fixed order
 // ------------------------------------------------------------------------------------------------
 // Bound: HBM with many tasks; with a few the chain of dependent row batches of one workgroup, and the launches
-// themselves.  A workgroup of 16 waves takes one task and one block of columns of one job.
+// themselves.  A workgroup (bf16: of up to 16 waves, fp32: of four) takes one task and one block of columns of one job.
 // bf16: a lane owns 16 bytes of columns; rows narrower than a wave's 64 lanes are taken several at a time.  The waves take the
 // rows round-robin in batches of UB independent loads; lanes that share columns are added first, then the waves in wave
 // order.  fp32: four chains per column (rows 8 c .. 8 c + 7 of every 32, one after the other), which are added in order; four
@@ -263,7 +263,7 @@ void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n) {
 // Either partition depends on the job's width alone: results do not depend on how the tasks are cut into waves.
 // Measured: the 16 launches of a step of 3 tasks x (512 + 512) rows through 1024-512-256 hidden units, bf16, 0.37 -> 0.03 ms
 // in 3 launches (4 waves and a launch per sum before); 512 tasks x 256 rows through 512-256, 28 launches, 0.62 -> 0.60 ms in 7.
-enum { COLSUM_WAVES = 16 };
+enum { COLSUM_WAVES = 16, COLSUM_WAVES_F32 = 4 };   // of a workgroup, at most
 
 // the job of a workgroup
 __device__ __forceinline__ const ColJob& colsum_job(const ColJobs& jobs) {
@@ -319,9 +319,11 @@ __device__ __forceinline__ void colsum_rows(const ColJob& j, int64_t r0, int64_t
     }
 }
 
-__global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_bf16_kernel(const int32_t* __restrict__ row_offsets, ColJobs jobs) {
+// WAVES: of the sixteen that the rows are dealt to, those that have rows in some task
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void task_colsum_bf16_kernel(const int32_t* __restrict__ row_offsets, ColJobs jobs) {
     constexpr int V = 8;
-    __shared__ float part[COLSUM_WAVES - 1][64 * V];
+    __shared__ float part[WAVES > 1 ? WAVES - 1 : 1][64 * V];
     const ColJob& j = colsum_job(jobs);
     const int g = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t r0 = row_offsets[g], r1 = row_offsets[g + 1];
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_bf16_kernel(con
         if (threadIdx.x == 0) {
             float sum = acc[0];
 #pragma unroll
-            for (int w = 0; w < COLSUM_WAVES - 1; ++w) sum += part[w][0];
+            for (int w = 0; w < WAVES - 1; ++w) sum += part[w][0];
             colsum_store(j, 0, sum);
         }
         return;
@@ -362,7 +364,7 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_bf16_kernel(con
         for (int k = 0; k < V; ++k) {
             float sum = acc[k];
 #pragma unroll
-            for (int w = 0; w < COLSUM_WAVES - 1; ++w) sum += part[w][k * 64 + lane];
+            for (int w = 0; w < WAVES - 1; ++w) sum += part[w][k * 64 + lane];
             colsum_store(j, n + k, sum);
         }
     }
@@ -398,19 +400,21 @@ __device__ __forceinline__ float colsum_chain(const ColJob& j, int64_t r0, int64
     return acc;
 }
 
-__global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_f32_kernel(const int32_t* __restrict__ row_offsets, ColJobs jobs) {
-    __shared__ float part[64 * COLSUM_WAVES];
+// chains: of every column, those that have rows in some task (1, 2 or 4): the waves beyond them take further columns
+__global__ __launch_bounds__(64 * COLSUM_WAVES_F32) void task_colsum_f32_kernel(const int32_t* __restrict__ row_offsets, int chains, ColJobs jobs) {
+    constexpr int NT = 64 * COLSUM_WAVES_F32;
+    __shared__ float part[NT];
     const ColJob& j = colsum_job(jobs);
     const int g = blockIdx.y, tid = threadIdx.x;
     const int64_t r0 = row_offsets[g], r1 = row_offsets[g + 1];
     if (j.N == 1) {   // one value per row: read by all lanes, added by four
         const float* X = reinterpret_cast<const float*>(j.X1);
         float acc = 0.f;
-        for (int64_t s0 = r0; s0 < r1; s0 += 64 * COLSUM_WAVES) {
+        for (int64_t s0 = r0; s0 < r1; s0 += NT) {
             __syncthreads();   // the values before have been added
             part[tid] = s0 + tid < r1 ? X[(s0 + tid) * j.ldx] : 0.f;
             __syncthreads();
-            const int n = (int)min(r1 - s0, (int64_t)(64 * COLSUM_WAVES));
+            const int n = (int)min(r1 - s0, (int64_t)NT);
             if (tid < 4)
                 for (int b = tid * 8; b < n; b += 32)
 #pragma unroll
@@ -420,30 +424,50 @@ __global__ __launch_bounds__(64 * COLSUM_WAVES) void task_colsum_f32_kernel(cons
         if (tid == 0) colsum_store(j, 0, ((acc + a1) + a2) + a3);
         return;
     }
-    const int lane = tid & 63, chain = (tid >> 6) & 3, group = tid >> 8;
-    const int n = (((int)blockIdx.x - j.block0) * (COLSUM_WAVES / 4) + group) * 64 + lane;
+    const int lane = tid & 63, wv = tid >> 6, chain = wv & (chains - 1), group = wv / chains;
+    const int n = (((int)blockIdx.x - j.block0) * (COLSUM_WAVES_F32 / chains) + group) * 64 + lane;
     float acc = 0.f;
     if (n < j.N) acc = j.X2 ? colsum_chain<true>(j, r0, r1, chain, n) : colsum_chain<false>(j, r0, r1, chain, n);
-    part[tid] = acc;
-    __syncthreads();
-    if (chain == 0 && n < j.N) colsum_store(j, n, ((acc + part[tid + 64]) + part[tid + 128]) + part[tid + 192]);
+    if (chains > 1) {
+        part[tid] = acc;
+        __syncthreads();
+        if (chain == 0)
+            for (int w = 1; w < chains; ++w) acc += part[tid + w * 64];
+    }
+    if (chain == 0 && n < j.N) colsum_store(j, n, acc);
 }
 
-void launch_task_colsum(hipStream_t st, int bf16, int G, const int32_t* row_offsets, const ColJob* list, int n) {
-    const int cols = bf16 ? 64 * 8 : 64 * (COLSUM_WAVES / 4);   // of a workgroup
+// most_rows: of the largest task.  Waves that no task has rows for are not launched (they would only add zeros, so the results
+// are the same; 1024 threads for every task before): 20000 tasks x (1 + 1) rows, 32 units, fp32, 0.81 -> 0.15 ms a step; 5000 tasks x (2 + 2)
+// rows, 256-128, bf16, 0.48 -> 0.09 ms; 512 tasks x (128 + 128) rows, 1024-512, fp32, 0.36 -> 0.37 ms.
+void launch_task_colsum(hipStream_t st, int bf16, int G, int most_rows, const int32_t* row_offsets, const ColJob* list, int n) {
+    int chains = 1;
+    while (chains < 4 && chains * 8 < most_rows) chains *= 2;
+    const int cols = bf16 ? 64 * 8 : 64 * (COLSUM_WAVES_F32 / chains);   // of a workgroup
     for (int i0 = 0; i0 < n; i0 += COL_JOBS) {
         ColJobs jobs;
         jobs.n = std::min(n - i0, (int)COL_JOBS);
-        int blocks = 0;
+        int blocks = 0, waves = 1;
         for (int i = 0; i < jobs.n; ++i) {
-            jobs.job[i] = list[i0 + i];
-            jobs.job[i].block0 = blocks;
-            blocks += (jobs.job[i].N + cols - 1) / cols;
+            ColJob& j = jobs.job[i];
+            j = list[i0 + i];
+            j.block0 = blocks;
+            blocks += (j.N + cols - 1) / cols;
+            int first = 64;   // rows that a wave of the bf16 kernel starts with
+            if (j.N > 1) {
+                first = j.X2 ? 4 : 8;
+                for (int lanes = 64; lanes > 1 && lanes / 2 * 8 >= j.N; lanes /= 2) first *= 2;
+            }
+            while (waves < COLSUM_WAVES && waves * first < most_rows) waves *= 2;
         }
         if (G <= 0 || blocks <= 0) continue;
-        const dim3 grid(blocks, G), block(64 * COLSUM_WAVES);
-        if (bf16) hipLaunchKernelGGL(task_colsum_bf16_kernel, grid, block, 0, st, row_offsets, jobs);
-        else hipLaunchKernelGGL(task_colsum_f32_kernel, grid, block, 0, st, row_offsets, jobs);
+        const dim3 grid(blocks, G), block(64 * (bf16 ? waves : (int)COLSUM_WAVES_F32));
+        if (!bf16) hipLaunchKernelGGL(task_colsum_f32_kernel, grid, block, 0, st, row_offsets, chains, jobs);
+        else if (waves == 1) hipLaunchKernelGGL(task_colsum_bf16_kernel<1>, grid, block, 0, st, row_offsets, jobs);
+        else if (waves == 2) hipLaunchKernelGGL(task_colsum_bf16_kernel<2>, grid, block, 0, st, row_offsets, jobs);
+        else if (waves == 4) hipLaunchKernelGGL(task_colsum_bf16_kernel<4>, grid, block, 0, st, row_offsets, jobs);
+        else if (waves == 8) hipLaunchKernelGGL(task_colsum_bf16_kernel<8>, grid, block, 0, st, row_offsets, jobs);
+        else hipLaunchKernelGGL(task_colsum_bf16_kernel<COLSUM_WAVES>, grid, block, 0, st, row_offsets, jobs);
     }
 }
 

@@ -1,5 +1,5 @@
 """The per-task column sums: more sums than one launch takes, rows that end inside a wave's batch, widths of several
-column blocks and widths that leave lanes of a row group empty."""
+column blocks and widths that leave lanes of a row group empty, tasks with rows for some of the waves only."""
 import pytest
 
 from tests.helpers import small_cfg
@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bf,tasks,rows,hidden", [(0, 2, 3, (12,) * 13), (0, 3, 129, (300, 40)), (0, 2, 513, (9,)),
-                                                  (1, 3, 65, (600, 72)), (1, 2, 133, (40,))])
+                                                  (1, 3, 65, (600, 72)), (1, 2, 133, (40,)),
+                                                  (0, 5, 8, (300, 40)), (0, 5, 16, (300, 40)), (1, 5, 4, (600, 72)), (1, 5, 31, (600, 72))])
 def test_partitions(gm, bf, tasks, rows, hidden):  # noqa: F811
     cfg = small_cfg(n_tasks=tasks, n_support=rows, n_query=max(1, rows - 2), layer_dims=(17,) + hidden + (1,), mlp_dtype=bf)
     sup, qry, params = _inputs(cfg, emb_std=0.3)

@@ -55,7 +55,7 @@ def test_logits(gm, n_dense):  # noqa: F811
     assert np.max(np.abs(got["task_loss"][:T] - np.log1p(np.exp(z)))) < 1e-5
 
 
-@pytest.mark.parametrize("rows", [1, 8, 31, 33, 129, 1023, 1500])
+@pytest.mark.parametrize("rows", [1, 8, 9, 16, 17, 31, 33, 129, 257, 1023, 1500])
 def test_column_sums(gm, rows):  # noqa: F811
     """Four chains, rows 8 c .. 8 c + 7 of every 32 in chain c, every product rounded before it is added; then the chains in
     order.  With zero weights a row's delta is (1/2 - label) / rows."""
@@ -72,3 +72,20 @@ def test_column_sums(gm, rows):  # noqa: F811
     got = _step(gm, [rows], x, y, np.zeros(n_dense))
     assert np.array_equal(got["dW"][D:, 0], want[:-1])
     assert np.array_equal(got["db"], want[-1:])
+
+
+@pytest.mark.parametrize("bf", [0, 1])
+@pytest.mark.parametrize("rows", [1, 4, 5, 8, 9, 16, 17, 33, 64, 65])
+def test_a_large_task_beside(gm, bf, rows):  # noqa: F811
+    """How many waves a launch of the sums has follows from the wave's largest task; what a small task gets from it does not."""
+    rng = np.random.default_rng(rows)
+    n_dense, big = 60, 200
+    dims = [D + n_dense, 600, 40, 1]
+    x, y = rng.standard_normal((rows + big, n_dense)).astype(np.float32), (rng.random(rows + big) < 0.5).astype(np.float32)
+    params = SimpleNamespace(emb=torch.zeros(3, D, device="cuda:0"), b=[torch.tensor(rng.standard_normal(n), dtype=torch.float32, device="cuda:0") for n in dims[1:]],
+                             W=[torch.tensor(rng.standard_normal((a, b)) / 4, dtype=torch.float32, device="cuda:0") for a, b in zip(dims[:-1], dims[1:])])
+    ctx = gm(1, [3], D, n_dense, dims, bf, workspace_bytes=1 << 28)
+    alone, beside = _set([rows], x[:rows], y[:rows]), _set([rows, big], x, y)
+    a, b = (ctx.meta_step(s, s, params, 0.1, 2, 1) for s in (alone, beside))
+    assert torch.equal(a["task_loss"][:1], b["task_loss"][:1])
+    ctx.close()
