@@ -31,7 +31,8 @@ def _cut(s, sizes, F):
     (3, 32, 0, [257, 10, 256, 255, 64, 65, 300, 130], [10, 257, 255, 256, 65, 64, 130, 300]),
     (3, 128, 0, [70, 5, 200], [5, 70, 129]),
     (3, 64, 1, [320, 64, 65, 9, 40], [33, 64, 257, 130, 40]),
-    (9, 32, 0, [513, 30, 1024, 769, 200], [1024, 31, 513, 100, 768])])
+    (9, 32, 0, [513, 30, 1024, 769, 200], [1024, 31, 513, 100, 768]),
+    (9, 32, 0, [512, 1024, 449, 768, 448, 256], [768, 256, 512, 450, 512, 512])])   # (tiles of equal height first; not with 448 rows)
 def test_tile_edges(gm, F, D, bf, ns, nq):  # noqa: F811
     cfg = small_cfg(n_tasks=len(ns), n_fields=F, emb_dim=D, rows_per_field=60, n_support=max(ns), n_query=max(nq), bag_max=3 if F < 9 else 1,
                     layer_dims=(F * D + 5, 40, 1), mlp_dtype=bf)
