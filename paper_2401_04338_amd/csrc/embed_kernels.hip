@@ -227,14 +227,16 @@ static int seg_chunk(int64_t n, int F, int D) {
 // at a time, one position per lane (coalesced), and handed round the group by lane shuffles; the head flags of
 // the LG positions come back as one ballot word.  Whether a run began before the chunk or continues past it
 // follows from the head flags at the chunk's two borders, so no segment table is read here.
-template <int LG>
+// CH: the chunk's length, 0 where `short_ch` says it
+template <int LG, int CH>
 __global__ void __launch_bounds__(256)
-seg_reduce_chunks_kernel(int D, int F, int ch, ValEnc enc, const u32* __restrict__ keys, const u32* __restrict__ scan,
+seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __restrict__ keys, const u32* __restrict__ scan,
                          const int64_t* __restrict__ n_rows, int64_t capacity, int64_t n,
                          const u32* __restrict__ sorted_vals, const float* __restrict__ gx, float* emb_grad,
                          float* partial, float* table) {
     constexpr int GPB = 256 / LG;            // lane groups per workgroup
     constexpr int U = LG < 8 ? LG : 8;       // row loads in flight per lane
+    const int ch = CH ? CH : short_ch;
     const int g_in_block = threadIdx.x / LG, l = threadIdx.x % LG;
     const int group_lane0 = (threadIdx.x % 64) / LG * LG;   // the group's first lane inside its wave
     const int64_t n_valid = table ? 0 : min(*n_rows, capacity);
@@ -381,14 +383,22 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
     const int LG = D / 4, ch = seg_chunk(n, F, D);
     const int64_t n_chunks = (n + ch - 1) / ch;
     const dim3 grid(pool_grid(n_chunks, 256 / LG));
-#define SEG_CHUNKS(LG_)                                                                                              \
+    // (the long chunk is a constant of its kernels: 100 tasks x (300 + 300) rows of 32 columns 99 us with a variable length, 90 with 64)
+#define SEG_CHUNKS(LG_, CH_)                                                                                         \
     case LG_:                                                                                                        \
-        hipLaunchKernelGGL(seg_reduce_chunks_kernel<LG_>, grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
+        hipLaunchKernelGGL((seg_reduce_chunks_kernel<LG_, CH_>), grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
                            sorted_vals, gx, emb_grad, partial, table);                                               \
         break;
-    switch (LG) {
-        SEG_CHUNKS(1) SEG_CHUNKS(2) SEG_CHUNKS(4) SEG_CHUNKS(8) SEG_CHUNKS(16) SEG_CHUNKS(32) SEG_CHUNKS(64)
-        default: return;   // emb_dim is a power of two in 4..256 (checked when the context is made)
+    if (ch == SEG_CH) {
+        switch (LG) {
+            SEG_CHUNKS(1, SEG_CH) SEG_CHUNKS(2, SEG_CH) SEG_CHUNKS(4, SEG_CH) SEG_CHUNKS(8, SEG_CH) SEG_CHUNKS(16, SEG_CH) SEG_CHUNKS(32, SEG_CH) SEG_CHUNKS(64, SEG_CH)
+            default: return;   // emb_dim is a power of two in 4..256 (checked when the context is made)
+        }
+    } else {
+        switch (LG) {
+            SEG_CHUNKS(1, 0) SEG_CHUNKS(2, 0) SEG_CHUNKS(4, 0)   // (short chunks: at most 16 columns)
+            default: return;
+        }
     }
 #undef SEG_CHUNKS
     hipLaunchKernelGGL(seg_reduce_join_kernel, dim3(pool_grid(n_chunks, 256 / LG)), dim3(256), 0, st, D, LG, ch, keys, scan,
