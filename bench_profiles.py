@@ -3,7 +3,8 @@
 beside bench.py; no part of the library).
 
   python bench_profiles.py trace <results.db> [--top N] --bench-args '<bench.py arguments of the profiled run>'
-      per-kernel totals of a `rocprofv3 --kernel-trace --stats` run (the rocpd database it writes)
+      per-kernel totals of a `rocprofv3 --kernel-trace --stats` run (the rocpd database it writes); --call NAME instead of
+      --bench-args: the run made passes of that call of perf/cases.py (command in the summary's header)
   python bench_profiles.py hbm --fetch F.csv --write W.csv --copy-gib G --workload NAME --steps N [--json OUT.json]
       HBM bytes per launch and kernel family from a `--pmc FETCH_SIZE` run and a `--pmc WRITE_SIZE` run of
       `bench.py --ceilings` (both counters are KiB per dispatch; the stream_copy_kernel dispatches of gm_ceilings, which
@@ -47,7 +48,7 @@ FAMILIES = {
 
 
 def _is_framework(name: str) -> bool:
-    return name.startswith("void at::") or "at::native" in name or "rocprim" in name or "hipcub" in name
+    return name.startswith("void at::") or "at::native" in name or "rocprim" in name or "hipcub" in name or "compute_cuda_kernel" in name
 
 
 def trace(a):
@@ -65,9 +66,15 @@ def trace(a):
             ours.append((name.split("(")[0].replace("void ", ""), calls, total, avg))
     tot = sum(r[2] for r in ours)
     ba = a.bench_args or "<bench arguments>"
-    print("# rocprofv3 kernel trace of gm_meta_step (per-kernel totals over the whole run: warm-up, timed and event-timed steps)")
-    print(f"# command (from /tmp, TMPDIR=/tmp): rocprofv3 --kernel-trace --stats -d <out> -o <name> -- python3 /root/repo/bench.py {ba}")
-    print(f"# summary made with: python bench_profiles.py trace <out>/<name>_results.db --top {a.top} --bench-args '{ba}'")
+    if a.call:
+        print(f"# rocprofv3 kernel trace of {a.passes} passes of perf/cases.py's {a.call} (per-kernel totals, all passes)")
+        print("# command (from /tmp, TMPDIR=/tmp, PYTHONPATH=/root/repo): rocprofv3 --kernel-trace --stats -d <out> -o <name> -- python3 -c \"import perf.cases as p; "
+              f"s = p.prepare(next(c for c in p.listed() if c['name'] == '{a.call}'), 1); r = [p.run(s) for _ in range({a.passes})]\"")
+        print(f"# library kernels: {sum(r[1] for r in ours) / a.passes:.1f} launches and {tot / a.passes:.1f} us a pass (summed kernel times)")
+    else:
+        print("# rocprofv3 kernel trace of gm_meta_step (per-kernel totals over the whole run: warm-up, timed and event-timed steps)")
+        print(f"# command (from /tmp, TMPDIR=/tmp): rocprofv3 --kernel-trace --stats -d <out> -o <name> -- python3 /root/repo/bench.py {ba}")
+        print(f"# summary made with: python bench_profiles.py trace <out>/<name>_results.db --top {a.top} --bench-args '{ba}'")
     print(f"{'kernel':56s} {'calls':>6s} {'total_us':>10s} {'avg_us':>10s}   share_of_library_time")
     for name, calls, total, avg in ours[:a.top]:
         print(f"{name[:56]:56s} {calls:6d} {total:10.1f} {avg:10.2f} {100.0 * total / tot:8.2f}%")
@@ -173,6 +180,8 @@ def main():
     t.add_argument("db")
     t.add_argument("--top", type=int, default=40)
     t.add_argument("--bench-args", default="")
+    t.add_argument("--call", default=None, help="name of the call in perf/cases.py that the run made")
+    t.add_argument("--passes", type=int, default=10, help="passes that the run made of it")
     h = sub.add_parser("hbm")
     h.add_argument("--fetch", required=True)
     h.add_argument("--write", required=True)
