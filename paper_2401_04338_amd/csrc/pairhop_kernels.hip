@@ -328,9 +328,9 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 //                                           a few tasks are dealt in runs of fields.
 // Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
 // 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
-// (256 + 256) rows x 26 fields 6.7 -> 6.5 ms, 4.7 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
+// (256 + 256) rows x 26 fields 6.7 -> 6.5 ms, 4.6 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
 // Inside a run of fields the tiles come first, field by field, where an output has several of equal height: they find the field's Z
-// in L2 (two hops of 256 tasks x (512 + 512) rows x 64 fields, two tiles each, fetch 15.5 GB instead of 19.6; eleven runs of a side
+// in L2 (two hops of 256 tasks x (512 + 512) rows x 64 fields, two tiles each, fetch 15.4 GB instead of 19.6; eleven runs of a side
 // 4.86..5.12 against 5.05..5.35 ms).  Otherwise the fields come first.  With one tile per output a tile's pieces of the same rows follow
 // each other (six hops of 512 tasks x (256 + 256) rows x 26 fields 6.35..6.57 ms; tiles first they fetch 19.0 GB instead of 20.1 and
 // take 1-2 % longer).  With a short last tile, high and low ones in turn would fall on the same compute units again and again: the
