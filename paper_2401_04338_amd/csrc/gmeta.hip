@@ -1541,11 +1541,21 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
     return d;
 }
 
+// Row tile of the forward and backward products: by the tasks' average size, but smaller where the first layer's tiles would
+// leave compute units without one (the contraction of a tile is a serial chain whatever its size).
 static int pick_bm(const gm_ctx* c, const Batch& B) {
     if (B.T == 0) return 64;
     const int64_t avg = (B.poff_s[B.T] + B.poff_q[B.T]) / (2 * (int64_t)B.T);
     if (!c->mlp_dtype) return 64;
-    return avg >= 192 ? 256 : (avg >= 96 ? 128 : 64);
+    int bm = avg >= 192 ? 256 : (avg >= 96 ? 128 : 64);
+    auto tiles = [&](int rows) {
+        int64_t m = 0;
+        for (int t = 0; t < B.T; ++t) m += (B.poff_s[t + 1] - B.poff_s[t] + rows - 1) / rows;
+        const int cols = gemm_bn(c, rows, c->ld[1], c->ld[0]);
+        return m * ((c->ld[1] + cols - 1) / cols);
+    };
+    while (bm > 64 && tiles(bm) < c->n_cus) bm /= 2;
+    return bm;
 }
 
 // splits the tasks into waves that fit `avail` bytes of workspace

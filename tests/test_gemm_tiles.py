@@ -1,0 +1,56 @@
+"""bf16 products: the same bits whichever row tile a batch's size selects.  A few tasks of their own (small tiles) and the same
+tasks at the head of a larger batch (larger tiles), rows and widths that are no multiples of a tile."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_parity import gm  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+F, D, NDENSE, OWN = 4, 32, 5, 2048   # table rows of a task's own, half of them for each set
+
+
+def _sets(sizes, which):
+    """Every task draws from a generator of its own (task t is the same in every batch) and looks every row up once, so that a
+    row's gradient is one sample's."""
+    parts = []
+    for t, n in enumerate(sizes):
+        rng = np.random.default_rng([which, t])
+        lens = rng.integers(1, 4, size=n * F)
+        field = np.repeat(np.arange(n * F) % F, lens)
+        idx = np.zeros(len(field), dtype=np.int64)
+        for f in range(F):
+            idx[field == f] = rng.permutation(OWN // 2)[:(field == f).sum()] + t * OWN + which * (OWN // 2)
+        parts.append((lens, idx, rng.standard_normal((n, NDENSE)), rng.random(n) < 0.3))
+    lens, idx, dense, labels = (np.concatenate(x) for x in zip(*parts))
+    dev = "cuda:0"
+    return SimpleNamespace(task_offsets=np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64),
+                           bag_offsets=torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64, device=dev),
+                           indices=torch.tensor(idx, dtype=torch.int32, device=dev), dense=torch.tensor(dense, dtype=torch.float32, device=dev),
+                           labels=torch.tensor(labels, dtype=torch.float32, device=dev))
+
+
+@pytest.mark.parametrize("hidden,rows,many", [((264, 136), (201, 257), 150), ((264, 136), (101, 131), 90), ((512, 256), (256, 300), 140),
+                                              ((1024, 264, 40), (195, 193), 70)])
+@pytest.mark.parametrize("K", [1, 3])
+def test_row_tiles(gm, hidden, rows, many, K):  # noqa: F811
+    dims = [F * D + NDENSE, *hidden, 1]
+    gen = torch.Generator("cuda").manual_seed(5)
+    params = SimpleNamespace(emb=torch.randn(F * OWN * many, D, device="cuda", generator=gen) * 0.3,
+                             W=[torch.randn(a, b, device="cuda", generator=gen) / a ** 0.5 for a, b in zip(dims[:-1], dims[1:])],
+                             b=[torch.randn(b, device="cuda", generator=gen) * 0.1 for b in dims[1:]])
+    got = []
+    for T in (2, many):
+        sizes = [rows[t % 2] for t in range(T)]
+        ctx = gm(F, [OWN * many] * F, D, NDENSE, dims, 1, workspace_bytes=3 << 30)
+        out = ctx.meta_step(_sets(sizes, 0), _sets(sizes, 1), params, 0.1, K, 2)
+        n = int(out["n_emb_rows"].item())
+        r = out["emb_rows"][:n]
+        mine = r % (OWN * many) < 2 * OWN   # rows of the first two tasks
+        got.append((out["task_loss"][:2].clone(), r[mine], out["emb_grad"][:n][mine]))
+        ctx.close()
+    assert len(got[0][1]) > 0 and float(got[0][2].abs().max()) > 0
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
