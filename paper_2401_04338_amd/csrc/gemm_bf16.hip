@@ -151,15 +151,26 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
     }
 }
 
-// Four waves, 2 along m and 2 along n: a wave's share of a BM x BN tile is BM / 2 x BN / 2.
-template <int BM, int BN, bool DB, bool KA, bool KB, int EP>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBArgs a, int n_ntiles, int mt_per_group, int n_tiles) {
-    constexpr int WN = 2;   // waves along n
-    constexpr int NT = 2 * WN * 64;              // threads
-    constexpr int MI = BM / 64, NI = BN / (32 * WN);  // 32x32 blocks per wave in each direction
+// WM waves along m and WN along n: a wave's share of a BM x BN tile is BM / WM x BN / WN.
+//
+// Bound: contractions of a few hundred (weights of a task's own, a task's rows) leave a tile four to sixteen steps, so what a
+// workgroup waits for -- its first operands, a barrier's last wave, the epilogue's loads -- has to be hidden by the other
+// waves of its compute unit.  Eight waves with a quarter of the accumulators of four, operands through buffer loads (no branch
+// around a load, addresses once per product) and DEPTH tiles in registers on their way: 256 x 128 tiles of four waves held a
+// compute unit alone.  More than one tile ahead costs waves and pays only where compute units have a workgroup each.
+// Measured against four waves of plain loads (products of 512 tasks of 256 rows, layers 1677-512-256): backward with the
+// gradient stored 398 -> 387 us, hidden layer 125 -> 116, weight gradients over runs of tasks 575 -> 452, per task (four waves
+// there: what they write is the bound, and wider stores of a wave help) 532 -> 496; 3 tasks of 512 rows, 4109-1024-512-256,
+// 64-row tiles: forward 47 -> 26 us a layer.
+typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, int n_ntiles, int mt_per_group, int n_tiles) {
+    constexpr int NT = WM * WN * 64;                          // threads
+    constexpr int MI = BM / (32 * WM), NI = BN / (32 * WN);   // 32x32 blocks per wave in each direction
     extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    constexpr int LDA_K = BM + GPADK, LDB_K = BN + GPADK;  // KM: LDS row strides of the [GK][BM] and [GK][BN] tiles
-    constexpr int TILE = (KA ? GK * LDA_K : BM * GLD) + (KB ? GK * LDB_K : BN * GLD);  // elements of one operand stage
+    constexpr int LDA_K = BM + GPADK, LDB_K = BN + GPADK;  // LDS row strides of contraction-slowest tiles [GK][BM] and [GK][BN]
+    constexpr int A_ELEMS = KA ? GK * LDA_K : BM * GLD;    // LDS elements of the A tile; the B tile follows
+    constexpr int TILE = A_ELEMS + (KB ? GK * LDB_K : BN * GLD);
 
     // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Re-number them so that
     // consecutive tiles -- the n-tiles of one row block, then the next row block of the same task, which
@@ -185,7 +196,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBArgs a, int n_ntile
     const int n0 = ntile * BN;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / WN) * (BM / 2), wn0 = (wave % WN) * (BN / WN);
+    const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
     const int l32 = lane & 31, lhi = lane >> 5;
 
     f32x16 acc[MI][NI];
@@ -199,61 +210,69 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBArgs a, int n_ntile
     // global -> register staging: 16-byte chunks, 8 chunks per tile row
     constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;  // chunks per thread
     constexpr int CR = NT / 8;                          // tile rows covered by one chunk round
-    uint4 ra[CA], rb[CB];
+    constexpr int RA = NT / (BM / 8), RB = NT / (BN / 8);   // rows of a contraction-slowest tile covered by one round
+    u32x4 ra[DEPTH][CA], rb[DEPTH][CB];
     const int crow = tid >> 3, ccol = (tid & 7) * 8;     // chunk c = tid + NT*i: row = crow + CR*i, k = ccol
+    const int arow = tid / (BM / 8), acol = (tid % (BM / 8)) * 8, brow = tid / (BN / 8), bcol = (tid % (BN / 8)) * 8;
 
-    const int kt_per_pair = (K + GK - 1) / GK;
-    const int n_kt = kt_per_pair * a.n_pairs;
-
-    constexpr int A_ELEMS = KA ? GK * LDA_K : BM * GLD;   // LDS elements of the A tile; the B tile follows
-    auto load_tile = [&](int kt) {
-        const int pr = kt / kt_per_pair;
-        const int k0 = (kt - pr * kt_per_pair) * GK;
-        const bf16_t* A = a.A[pr] + (int64_t)g * a.gA[pr] + r0 * a.rA[pr];
-        const bf16_t* B = a.B[pr] + (int64_t)g * a.gB[pr] + r0 * a.rB[pr];
-        const int64_t lda = a.lda[pr], ldb = a.ldb[pr];
+    const int n_kt = (K + GK - 1) / GK * a.n_pairs;
+    // Operand tiles come through buffer loads: what lies outside the operand reads as zero without a branch, also whole tiles
+    // past the last one.  (The tile's first row is in the base address: offsets stay far below 32 bits.)
+    const u32 OOB = 1u << 30;    // (beyond any tile: a tile's 256 rows of less than 2^21 columns; row steps added to it stay below 2^31)
+    // (the product's operands are taken from the arguments once per product: a scalar load in every tile is a wait in every tile)
+    int pr = -1, k0 = 0;         // product and contraction offset of the next tile to be requested
+    const bf16_t *A = nullptr, *B = nullptr;
+    u32 la = 0, lb = 0;
+    int left_a = 0, left_b = 0;  // rows of the operand from its base on
+    auto open_product = [&]() {
+        const bool on = ++pr < a.n_pairs;
+        const int p = on ? pr : 0;
+        const int64_t lda = a.lda[p], ldb = a.ldb[p];
+        A = a.A[p] + (int64_t)g * a.gA[p] + r0 * a.rA[p] + (KA ? 0 : (int64_t)m0 * lda);
+        B = a.B[p] + (int64_t)g * a.gB[p] + r0 * a.rB[p] + (KB ? 0 : (int64_t)n0 * ldb);
+        la = (u32)lda * 2u;
+        lb = (u32)ldb * 2u;
+        left_a = on ? (KA ? K : min(M - m0, BM)) : 0;
+        left_b = on ? (KB ? K : min(N - n0, BN)) : 0;
+        k0 = 0;
+    };
+    open_product();
+    auto load_tile = [&](u32x4 (&da)[CA], u32x4 (&db)[CB]) {
+        const __amdgpu_buffer_rsrc_t qa = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)((u32)(KA ? min(left_a, GK) : left_a) * la), 0x00020000);
+        const __amdgpu_buffer_rsrc_t qb = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)((u32)(KB ? min(left_b, GK) : left_b) * lb), 0x00020000);
         const bool kok = k0 + ccol < K;
-        if constexpr (KA) {  // contraction slowest: 16-byte chunks along m, chunk c = tid + NT*i of row c / (BM/8)
+        {
+            const bool ok = KA ? m0 + acol < M : kok;
+            const u32 o = !ok ? OOB : KA ? (u32)arow * la + (u32)(m0 + acol) * 2u : (u32)crow * la + (u32)(k0 + ccol) * 2u;
 #pragma unroll
-            for (int i = 0; i < CA; ++i) {
-                const int ch = tid + NT * i, kr = ch / (BM / 8), mc = (ch % (BM / 8)) * 8;
-                ra[i] = (k0 + kr < K && m0 + mc < M) ? *reinterpret_cast<const uint4*>(A + (int64_t)(k0 + kr) * lda + m0 + mc)
-                                                     : make_uint4(0, 0, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < CA; ++i) {
-                const int m = m0 + crow + CR * i;
-                ra[i] = (kok && m < M) ? *reinterpret_cast<const uint4*>(A + (int64_t)m * lda + k0 + ccol) : make_uint4(0, 0, 0, 0);
-            }
+            for (int i = 0; i < CA; ++i) da[i] = __builtin_amdgcn_raw_buffer_load_b128(qa, (int)(o + (u32)((KA ? RA : CR) * i) * la), 0, 0);
         }
-        if constexpr (KB) {
+        {
+            const bool ok = KB ? n0 + bcol < N : kok;
+            const u32 o = !ok ? OOB : KB ? (u32)brow * lb + (u32)(n0 + bcol) * 2u : (u32)crow * lb + (u32)(k0 + ccol) * 2u;
 #pragma unroll
-            for (int i = 0; i < CB; ++i) {
-                const int ch = tid + NT * i, kr = ch / (BN / 8), nc = (ch % (BN / 8)) * 8;
-                rb[i] = (k0 + kr < K && n0 + nc < N) ? *reinterpret_cast<const uint4*>(B + (int64_t)(k0 + kr) * ldb + n0 + nc)
-                                                     : make_uint4(0, 0, 0, 0);
-            }
+            for (int i = 0; i < CB; ++i) db[i] = __builtin_amdgcn_raw_buffer_load_b128(qb, (int)(o + (u32)((KB ? RB : CR) * i) * lb), 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // (tiles are requested in the order they are waited for)
+        k0 += GK;
+        if (k0 >= K) {
+            open_product();
         } else {
-#pragma unroll
-            for (int i = 0; i < CB; ++i) {
-                const int n = n0 + crow + CR * i;
-                rb[i] = (kok && n < N) ? *reinterpret_cast<const uint4*>(B + (int64_t)n * ldb + k0 + ccol) : make_uint4(0, 0, 0, 0);
-            }
+            // (never negative: past the last product nothing is left, however many tiles are asked for)
+            if constexpr (KA) { A += (u64)GK * (la / 2u); left_a = max(left_a - GK, 0); }
+            if constexpr (KB) { B += (u64)GK * (lb / 2u); left_b = max(left_b - GK, 0); }
         }
     };
-    auto store_tile = [&](bf16_t* stage) {
+    auto store_tile = [&](bf16_t* stage, const u32x4 (&da)[CA], const u32x4 (&db)[CB]) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) {
-            const int ch = tid + NT * i;
-            if constexpr (KA) *reinterpret_cast<uint4*>(stage + (ch / (BM / 8)) * LDA_K + (ch % (BM / 8)) * 8) = ra[i];
-            else *reinterpret_cast<uint4*>(stage + (crow + CR * i) * GLD + ccol) = ra[i];
+            if constexpr (KA) *reinterpret_cast<u32x4*>(stage + (arow + RA * i) * LDA_K + acol) = da[i];
+            else *reinterpret_cast<u32x4*>(stage + (crow + CR * i) * GLD + ccol) = da[i];
         }
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
-            const int ch = tid + NT * i;
-            if constexpr (KB) *reinterpret_cast<uint4*>(stage + A_ELEMS + (ch / (BN / 8)) * LDB_K + (ch % (BN / 8)) * 8) = rb[i];
-            else *reinterpret_cast<uint4*>(stage + A_ELEMS + (crow + CR * i) * GLD + ccol) = rb[i];
+            if constexpr (KB) *reinterpret_cast<u32x4*>(stage + A_ELEMS + (brow + RB * i) * LDB_K + bcol) = db[i];
+            else *reinterpret_cast<u32x4*>(stage + A_ELEMS + (crow + CR * i) * GLD + ccol) = db[i];
         }
     };
     // 8 contraction values of one column of a contraction-slowest tile: two transposing LDS reads
@@ -290,33 +309,31 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBArgs a, int n_ntile
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
         }
     };
+    // (not __syncthreads: that would also wait for the tiles on their way)
+    auto barrier = [&]() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
 
-    if (DB) {
-        // two LDS stages: the next tile is fetched to registers while this one feeds the MFMAs and is parked in the
-        // other stage afterwards; one barrier per tile
-        if (n_kt > 0) {
-            load_tile(0);
-            store_tile(smem);
+    // DEPTH tiles are on their way from memory at any time, in registers; NS LDS stages.  With one stage two barriers a tile:
+    // everyone has read the last one before it is overwritten.  With two, a wave that passed the barrier of tile kt has read
+    // tile kt - 1, which tile kt + 1 overwrites.
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load_tile(ra[d], rb[d]);
+    for (int kt0 = 0; kt0 < n_kt; kt0 += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (kt0 + d >= n_kt) break;
+            bf16_t* stage = smem + (NS == 2 ? (kt0 + d) & 1 : 0) * TILE;
+            if (NS == 1 && kt0 + d > 0) barrier();
+            store_tile(stage, ra[d], rb[d]);
+            load_tile(ra[d], rb[d]);
+            barrier();
+            compute(stage);
         }
-        __syncthreads();
-        for (int kt = 0; kt < n_kt; ++kt) {
-            const bool more = kt + 1 < n_kt;
-            if (more) load_tile(kt + 1);
-            compute(smem + (kt & 1) * TILE);
-            if (more) store_tile(smem + ((kt + 1) & 1) * TILE);
-            __syncthreads();
-        }
-    } else {
-        if (n_kt > 0) load_tile(0);
-        for (int kt = 0; kt < n_kt; ++kt) {
-            __syncthreads();  // previous tile fully consumed
-            store_tile(smem);
-            __syncthreads();
-            if (kt + 1 < n_kt) load_tile(kt + 1);  // overlaps with the MFMAs below
-            compute(smem);
-        }
-        __syncthreads();  // every wave is done with the operand tiles
     }
+    barrier();   // every wave is done with the operand tiles
 
     gemm_epilogue<BM, BN, MI, NI, EP>(a, acc, smem, g, r0, m0, n0, M, N, wm0, wn0, lane, wave);
 }
@@ -335,8 +352,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBArgs a, int n_ntile
 //           requested, MFMAs of step 3
 // Operand tiles come through buffer loads: a row, column or whole tile outside the operand reads as zero without a
 // branch, so the loop body is straight-line code.  A is stored contraction-contiguous; B either way (KB).
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-
 #ifdef GEMM_TIMING
 __device__ unsigned long long g_gemm_ts[4 * 16384];
 void gemm_timing_fetch(unsigned long long* host, int n) { (void)hipMemcpyFromSymbol(host, HIP_SYMBOL(g_gemm_ts), sizeof(unsigned long long) * n); }
@@ -578,30 +593,31 @@ static void launch_pipe(hipStream_t st, const GemmBArgs& a) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
 }
 
-template <int BM, int BN, bool KA, bool KB, int EP>
+template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP>
 static void launch_variant(hipStream_t st, const GemmBArgs& a) {
     int n_ntiles, mt_per_group;
     int64_t n_tiles;
     tile_counts(a, BM, BN, n_ntiles, mt_per_group, n_tiles);
     if (n_tiles <= 0) return;
-    size_t shmem = ((KA ? (size_t)GK * (BM + GPADK) : (size_t)BM * GLD) + (KB ? (size_t)GK * (BN + GPADK) : (size_t)BN * GLD)) * sizeof(bf16_t);
-    const size_t epi = (size_t)4 * 32 * (BN / 2 + 4) * sizeof(float);  // the epilogue's strips, one per wave
+    size_t shmem = ((KA ? (size_t)GK * (BM + GPADK) : (size_t)BM * GLD) + (KB ? (size_t)GK * (BN + GPADK) : (size_t)BN * GLD)) * sizeof(bf16_t) * NS;
+    const size_t epi = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);  // the epilogue's strips, one per wave
     if (shmem < epi) shmem = epi;
-    auto kern = gemm_bf16_kernel<BM, BN, false, KA, KB, EP>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, DEPTH, NS, KA, KB, EP>;
     if (shmem > 48 * 1024) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
 }
 
 // Tile shapes of one operand form.  bm: row tile the caller built its (tile_group, tile_m0) lists for (64, 128 or
-// 256); bn: 128, or 256 (with bm = 256: the pipelined 256 x 256 kernel).  Measured on the benchmark shapes: one LDS
-// stage with register prefetch beats two stages for the smaller tiles (occupancy).
+// 256); bn: 128, or 256 (with bm = 256: the pipelined 256 x 256 kernel).  64-row tiles keep two tiles on their way and two LDS
+// stages (3 tasks of 512 rows: a layer's forward 23.1 us, with four tiles and four waves 24.9); for the others one of each
+// leaves room for more workgroups (512 tasks of 256 rows: a backward launch 387 us, 518 with two tiles on their way).
 template <bool KB, int EP>
 static void launch_rows_form(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
     if (bm == 256 && bn == 256) launch_pipe<false, KB, EP>(st, a);
-    else if (bm == 256) launch_variant<256, 128, false, KB, EP>(st, a);
-    else if (bm == 128) launch_variant<128, 128, false, KB, EP>(st, a);
-    else launch_variant<64, 128, false, KB, EP_RUNTIME>(st, a);
+    else if (bm == 256) launch_variant<256, 128, 4, 2, 1, 1, false, KB, EP>(st, a);
+    else if (bm == 128) launch_variant<128, 128, 2, 4, 1, 1, false, KB, EP>(st, a);
+    else launch_variant<64, 128, 2, 4, 2, 2, false, KB, EP>(st, a);
 }
 
 // backward form: both operands contraction-contiguous
@@ -622,7 +638,8 @@ void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
 template <int EP>
 static void launch_kmajor_tile(hipStream_t st, const GemmBArgs& a, int tile) {
     if (tile == 256) launch_pipe<true, true, EP>(st, a);
-    else launch_variant<128, 128, true, true, EP>(st, a);
+    // (eight waves where only sums over runs of tasks are written: a long contraction; else four)
+    else launch_variant<128, 128, 2, EP == (EPI_AXPBY | EP_CF) ? 4 : 2, 1, 1, true, true, EP>(st, a);
 }
 void launch_gemm_bf16_kmajor(hipStream_t st, const GemmBArgs& a, int tile) {
     if (a.n_pairs > 2) tile = 128;   // (the pipelined kernel keeps two operand descriptors)
@@ -632,7 +649,7 @@ void launch_gemm_bf16_kmajor(hipStream_t st, const GemmBArgs& a, int tile) {
         case EPI_AXPBY | EP_CF | EP_CIN: launch_kmajor_tile<EPI_AXPBY | EP_CF | EP_CIN>(st, a, tile); break;
         case EPI_AXPBY | EP_CF | EP_CB | EP_CIN: launch_kmajor_tile<EPI_AXPBY | EP_CF | EP_CB | EP_CIN>(st, a, tile); break;
         case EPI_AXPBY | EP_CB | EP_CIN: launch_kmajor_tile<EPI_AXPBY | EP_CB | EP_CIN>(st, a, tile); break;
-        default: launch_variant<128, 128, true, true, EP_RUNTIME>(st, a); break;
+        default: launch_variant<128, 128, 2, 2, 1, 1, true, true, EP_RUNTIME>(st, a); break;
     }
 }
 
