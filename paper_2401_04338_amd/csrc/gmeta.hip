@@ -1916,6 +1916,10 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         // a1: one prefetch pass for both sets.  Every real row is written whole (pooled fields, dense and pad columns); only
         // the pad rows of what the row arithmetic writes real rows of are cleared.
         const bool padded = d.Ps != d.Ss || d.Pq != d.Sq;
+        // bf16: the fp32 input is kept only where a row update still adds to it -- the support set's from the second inner step on
+        const bool hops = F > 0 && adapt && K > 0, q_once = bf && !hops;
+        float* const xs_f32 = bf && !(hops && K > 1) ? nullptr : w.Xs0;
+        float* const xq_f32 = q_once ? nullptr : w.Xq0;
         Act X0s;  // step-0 support input
         X0s.ld = ld0;
         if (bf) X0s = K > 0 ? w.steps[0].X : Act();
@@ -1924,9 +1928,9 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             const double lookups = (double)(d.nnz_s + d.nnz_q), bags = (double)(d.Ss + d.Sq) * F;
             Prof p(c, "gather_pool", lookups * (4.0 * D + 4) + bags * (4.0 * D + 8 + (bf ? 2.0 * D : 0)), 0);
             launch_gather_pool(st, F, D, c->n_dense, c->d_field_base, params->emb, ld0,
-                               PoolSet{sup->bag_offsets, sup->indices, sup->dense, wp.s0, d.Ss, rows_s, rb_s, w.Xs0, bf ? X0s.b : nullptr,
+                               PoolSet{sup->bag_offsets, sup->indices, sup->dense, wp.s0, d.Ss, rows_s, rb_s, xs_f32, bf ? X0s.b : nullptr,
                                        second ? (bf ? w.TXf : w.TX.f) : nullptr, second ? w.TX.b : nullptr},   // (dense features are not parameters: their direction is zero)
-                               PoolSet{qry->bag_offsets, qry->indices, qry->dense, wp.q0, d.Sq, rows_q, rb_q, w.Xq0, (bf && K == 0) ? w.Xq.b : nullptr});
+                               PoolSet{qry->bag_offsets, qry->indices, qry->dense, wp.q0, d.Sq, rows_q, rb_q, xq_f32, q_once ? w.Xq.b : nullptr});
         }
         if (padded) {
             PadJobs pj;
@@ -1937,7 +1941,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 pj.p[pj.n] = static_cast<char*>(p); pj.row_bytes[pj.n] = ld0 * elem; pj.set[pj.n] = set;
                 if (++pj.n == PAD_JOBS) { launch_zero_pad_rows(st, Tw, pj); pj.n = 0; }
             };
-            pad(w.Xs0, 4, 0); pad(w.Xq0, 4, 1);
+            pad(xs_f32, 4, 0); pad(xq_f32, 4, 1);
             pad(X0s.b, 2, 0); pad(w.Xq.b, 2, 1); pad(w.Xs_scratch.b, 2, 0);
             for (size_t k = 1; k < w.steps.size(); ++k) pad(w.steps[k].X.b, 2, 0);
             if (second) { pad(w.TX.b, 2, 0); pad(w.TX.f, 4, 0); pad(w.TXf, 4, 0); }
@@ -2077,9 +2081,10 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 if (more) {
                     xs_next = bf ? w.Xs0 : Xn.f;  // bf16: the fp32 master is updated in place
                 }
+                // (bf16: of the last update of a set only the operand copy is read)
                 const bool last = !more;
-                TwoHopOut os = hop_out(true, xs_cur, xs_next, more && bf ? Xn.b : nullptr, -alpha);
-                TwoHopOut oq = hop_out(false, w.Xq0, w.Xq0, (bf && last) ? Xq.b : nullptr, -alpha);
+                TwoHopOut os = hop_out(true, xs_cur, bf && k + 2 == K ? nullptr : xs_next, more && bf ? Xn.b : nullptr, -alpha);
+                TwoHopOut oq = hop_out(false, w.Xq0, bf && last ? nullptr : w.Xq0, (bf && last) ? Xq.b : nullptr, -alpha);
                 two_hop(true, w.dX, more ? &os : nullptr, &oq);
                 if (more) {
                     launch_copy_tail(st, FD, xs_cur, d.Ps, bf ? nullptr : (xs_next != xs_cur ? xs_next : nullptr), ld0, bf ? Xn.b : nullptr);
@@ -2101,7 +2106,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
 
         if ((rc = join_pairs())) return rc;   // (no inner step took a row hop)
         // outer forward/backward on the query set with the adapted parameters
-        if (bf && K > 0) launch_copy_tail(st, (F > 0 && adapt) ? FD : 0, w.Xq0, d.Pq, nullptr, ld0, Xq.b);
+        if (bf && hops) launch_copy_tail(st, FD, w.Xq0, d.Pq, nullptr, ld0, Xq.b);
         // gradient w.r.t. the pooled inputs: the wave's rows of the batch-wide buffer, or the wave's own buffer
         float* gxs = table ? w.GX : b.GX + wp.ps0 * (int64_t)FD;
         float* gxq = table ? w.GX + d.Ps * (int64_t)FD : b.GX + (Ps_tot + wp.pq0) * (int64_t)FD;
@@ -2126,7 +2131,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             }
             if (F > 0 && adapt) {
                 // direction on the support rows = query gradient routed through the rows both sets share
-                TwoHopOut os = hop_out(true, nullptr, txf, w.TX.b, 1.f);
+                TwoHopOut os = hop_out(true, nullptr, bf && K == 1 ? nullptr : txf, w.TX.b, 1.f);
                 two_hop(false, gxq, &os, nullptr);
             }
             for (int k = K - 1; k >= 0; --k) {
@@ -2144,7 +2149,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                         else launch_axpy(st, d.Ps * (int64_t)FD, -alpha, w.dX, gxs);
                     }
                     if (k > 0 && adapt) {
-                        TwoHopOut os = hop_out(true, txf, txf, w.TX.b, -alpha);
+                        TwoHopOut os = hop_out(true, txf, bf && k == 1 ? nullptr : txf, w.TX.b, -alpha);
                         two_hop(true, w.dX, &os, nullptr);
                     }
                 }
