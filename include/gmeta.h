@@ -146,7 +146,8 @@ int gm_meta_step_static(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, con
  * params: as for gm_meta_step, but the DEVICE arrays it points to are written (emb, every W_l, every b_l).
  * loss: DEVICE scalar, the step's sum_t L^Query_t (before the update).  task_loss: DEVICE [T] or NULL.
  * The meta-gradient lists live in the context's workspace (rows * (4 D + 8) bytes on top of what the step
- * needs, rows = min(lookups, table rows); GM_ERR_WORKSPACE if that does not fit).  The row-list form of the
+ * needs, rows = min(lookups, table rows); GM_ERR_WORKSPACE if that does not fit) and are written when the tasks run in
+ * several waves; one wave's reduction adds to the tables itself, the same values.  The row-list form of the
  * sparse gradient is used, so each set must hold fewer than 2^31 lookups.  Errors as gm_meta_step; on an
  * error nothing has been updated. */
 int gm_meta_train_step(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_set* query,
@@ -157,7 +158,8 @@ int gm_meta_train_step(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, cons
  * meta-gradient is accumulated, wave of tasks by wave of tasks, in emb_grad_table -- DEVICE [all table rows, D]
  * fp32, 16-byte aligned, ALL ZERO on entry -- and then applied to the tables in one streaming pass
  * (emb -= outer_lr * table) that also clears the buffer: it is all zero again on return, ready for the next
- * iteration.  Everything else as gm_meta_train_step (Alg. 1: the step, then both global back-propagation steps
+ * iteration.  Tasks that run as one wave need no accumulator: their reduction adds to the tables itself (the same values)
+ * and the buffer is left as it is.  Everything else as gm_meta_train_step (Alg. 1: the step, then both global back-propagation steps
  * applied with step size beta); the workspace only has to hold the dense meta-gradient beside the step. */
 int gm_meta_train_step_table(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_set* query,
                              const gm_params* params, float inner_lr, int32_t inner_steps, int32_t order,
@@ -174,7 +176,7 @@ int gm_meta_train_step_table(gm_ctx* ctx, int32_t n_tasks, const gm_set* support
  * before its update; n_done: HOST, iterations applied when the call returns (all of them on GM_OK; on an error the
  * failing iteration and the ones after it have not been applied), or NULL.
  * The overlap needs every batch to run as one wave of tasks and the workspace to hold, beside the dense buffers of
- * one batch, the index structures of two batches and the meta-gradient lists; otherwise the iterations simply run one
+ * one batch, the index structures of two batches (no meta-gradient lists: a wave's rows are updated by its reduction); otherwise the iterations simply run one
  * after the other (same results).  The "overlap_sort" / "overlap_pairs" settings are ignored during the call. */
 int gm_meta_train(gm_ctx* ctx, int32_t n_iters, const int32_t* n_tasks, const gm_set* support, const gm_set* query,
                   const gm_params* params, float inner_lr, int32_t inner_steps, int32_t order, float outer_lr,

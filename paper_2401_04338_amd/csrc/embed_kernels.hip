@@ -13,6 +13,7 @@ __device__ __forceinline__ void store_bf4(bf16_t* dst, float4 v) {
 }
 
 __device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+__device__ __forceinline__ float4 fma4(float s, float4 a, float4 b) { return make_float4(fmaf(s, a.x, b.x), fmaf(s, a.y, b.y), fmaf(s, a.z, b.z), fmaf(s, a.w, b.w)); }
 
 // ------------------------------------------------------------------------------------------------
 // prefetch + sum pooling: x[s, f*D:(f+1)*D] = sum over bag(s,f) of emb[field_base[f] + index]
@@ -233,7 +234,7 @@ __global__ void __launch_bounds__(256)
 seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __restrict__ keys, const u32* __restrict__ scan,
                          const int64_t* __restrict__ n_rows, int64_t capacity, int64_t n,
                          const u32* __restrict__ sorted_vals, const float* __restrict__ gx, float* emb_grad,
-                         float* partial, float* table) {
+                         float* partial, float* table, float scale) {
     constexpr int GPB = 256 / LG;            // lane groups per workgroup
     constexpr int U = LG < 8 ? LG : 8;       // row loads in flight per lane
     const int ch = CH ? CH : short_ch;
@@ -273,7 +274,7 @@ seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __re
             else if (continues) dst = partial + (c * 2 + 1) * D;
             else if (table) {  // table-shaped output: added to the segment's row (rows of one call are distinct)
                 float4* tp = reinterpret_cast<float4*>(table + (int64_t)run_key * D + l * 4);
-                *tp = add4(*tp, acc);
+                *tp = fma4(scale, acc, *tp);
                 return;
             } else {
                 if (seg >= n_valid) return;
@@ -336,7 +337,7 @@ seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __re
 template <int LG>
 __global__ __launch_bounds__(256) void seg_reduce_join_kernel(int ch, const u32* __restrict__ keys, const u32* __restrict__ scan,
                                                               const int64_t* __restrict__ n_rows, int64_t capacity, int64_t n,
-                                                              const float* __restrict__ partial, float* emb_grad, float* table) {
+                                                              const float* __restrict__ partial, float* emb_grad, float* table, float scale) {
     constexpr int GPB = 256 / LG, D = 4 * LG, ROUND = GPB * JOIN_U;
     __shared__ float4 stage[ROUND * LG];
     __shared__ int64_t list_c[JOIN_LIST], list_row[JOIN_LIST];
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(256) void seg_reduce_join_kernel(int ch, const u32*
     auto piece = [&](int64_t c, int which) { return *reinterpret_cast<const float4*>(partial + (c * 2 + which) * D + l * 4); };
     auto finish = [&](int64_t row, float4 acc) {
         float4* dst = reinterpret_cast<float4*>((table ? table : emb_grad) + row * D + l * 4);
-        *dst = table ? add4(*dst, acc) : acc;
+        *dst = table ? fma4(scale, acc, *dst) : acc;
     };
     for (int64_t c = (int64_t)blockIdx.x * GPB + g_in_block; c + 1 < n_chunks; c += n_groups) {
         const int64_t cb = c * ch, ce = cb + ch;   // not the last chunk, so it is full and ce < n
@@ -442,13 +443,13 @@ __global__ __launch_bounds__(256) void seg_reduce_join_kernel(int ch, const u32*
         }
         if (threadIdx.x < D) {
             float* dst = (table ? table : emb_grad) + list_row[i] * D + threadIdx.x;
-            *dst = table ? *dst + acc : acc;
+            *dst = table ? fmaf(scale, acc, *dst) : acc;
         }
     }
 }
 
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows, int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
-                       float* emb_grad, float* partial, float* table) {
+                       float* emb_grad, float* partial, float* table, float scale) {
     if (n <= 0 || capacity <= 0) return;
     const int LG = D / 4, ch = seg_chunk(n, F, D);
     const int64_t n_chunks = (n + ch - 1) / ch;
@@ -457,7 +458,7 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
 #define SEG_CHUNKS(LG_, CH_)                                                                                         \
     case LG_:                                                                                                        \
         hipLaunchKernelGGL((seg_reduce_chunks_kernel<LG_, CH_>), grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
-                           sorted_vals, gx, emb_grad, partial, table);                                               \
+                           sorted_vals, gx, emb_grad, partial, table, scale);                                               \
         break;
     if (ch == SEG_CH) {
         switch (LG) {
@@ -473,7 +474,7 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
 #undef SEG_CHUNKS
 #define SEG_JOIN(LG_)                                                                                                \
     case LG_:                                                                                                        \
-        hipLaunchKernelGGL(seg_reduce_join_kernel<LG_>, grid, dim3(256), 0, st, ch, keys, scan, n_rows, capacity, n, partial, emb_grad, table); \
+        hipLaunchKernelGGL(seg_reduce_join_kernel<LG_>, grid, dim3(256), 0, st, ch, keys, scan, n_rows, capacity, n, partial, emb_grad, table, scale); \
         break;
     switch (LG) { SEG_JOIN(1) SEG_JOIN(2) SEG_JOIN(4) SEG_JOIN(8) SEG_JOIN(16) SEG_JOIN(32) SEG_JOIN(64) default: break; }
 #undef SEG_JOIN

@@ -258,7 +258,7 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows,
                        int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
                        float* emb_grad, float* partial /* seg_reduce_partial_floats(n, D), for D <= 16 with n + radix_hist_words(n, F) more */,
-                       float* table /* null, or [all rows, D]: every segment is ADDED to its row instead of listed */);
+                       float* table /* null, or [all rows, D]: scale * every segment is ADDED to its row instead of listed */, float scale);
 size_t seg_reduce_partial_floats(int64_t n, int D);
 void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows, const float* grad,
                         int64_t n_rows, float scale);

@@ -1761,7 +1761,7 @@ static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& 
 // Everything of a one-wave batch with the row-list output that depends on its indices only, prepared ahead of the step
 // (by gm_meta_train, on the second stream, while the previous batch computes): validated offsets and indices, padded
 // row numbers, tile lists, per-(task, field) dictionaries and overlap join, pair-count matrices, the batch-wide order
-// of the lookups by row and its segments.  The buffers live in an arena of their own.
+// of the lookups by row.  The buffers live in an arena of their own.
 struct Prepared {
     Batch B;
     WavePlan wp;
@@ -1774,11 +1774,20 @@ struct Prepared {
     ValEnc enc = kPlainVals;   // how the values of the ordered lookups name their bags
 };
 
+// Global back-propagation on xi (Alg. 1) as part of a step: emb[row] += scale * (the row's gradient) straight from the segment
+// reduction.  Only a batch of one wave of tasks can (`done`): the next wave's prefetch reads the tables.
+struct EmbUpdate {
+    float* emb;
+    float scale;
+    bool done = false;
+};
+
 // The step.  pre: null, or the batch's index side prepared beforehand (one wave, row-list output); no_sync: return with
 // the work enqueued and the stream not drained (the caller synchronises and reads nothing from the host side but the
-// stream's error state; only with pre).
+// stream's error state; only with pre).  up: see EmbUpdate (where done, no list is written and no table-shaped output touched).
 static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set* qry, const gm_params* params, float alpha,
-                          int32_t K, int32_t order, float* loss, gm_grads* out, Prepared* pre, bool no_sync) {
+                          int32_t K, int32_t order, float* loss, gm_grads* out, Prepared* pre, bool no_sync,
+                          EmbUpdate* up = nullptr) {
     if (!c) return GM_ERR_ARG;
     if (T < 0 || K < 0 || (order != 1 && order != 2)) return fail(c, GM_ERR_ARG, "bad n_tasks / inner_steps / order");
     if (!out) return fail(c, GM_ERR_ARG, "null outputs");
@@ -1825,6 +1834,10 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     BatchBufs& b = B.b;
     const int64_t Ps_tot = B.poff_s[T];
     const size_t wave_mark = ar.off;
+    const bool apply = up && F > 0 && plans.size() == 1;
+    float* const row_table = apply ? up->emb : table;        // where the segment reduction adds rows (null: it lists them)
+    const float row_scale = apply ? up->scale : 1.f;
+    int64_t* const n_list = apply ? nullptr : out->n_emb_rows;   // (null: no list)
     struct SideGuard {   // whatever way this call ends, nothing of it is left running on the side stream
         gm_ctx* c;
         bool active = false;
@@ -1881,7 +1894,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                                              (u32)(0 - (uint64_t)wp.ps0), (u32)((uint64_t)d.Ps - (uint64_t)wp.pq0)}
                                  : whole_batch_range(B);
                 jr.n_sup_rows = d.Ps; jr.n_qry_rows = d.Pq;
-                if (!table) { jr.emb_rows = out->emb_rows; jr.capacity = capacity; jr.n_rows = out->n_emb_rows; }
+                if (!table) { jr.emb_rows = out->emb_rows; jr.capacity = capacity; jr.n_rows = n_list; }
                 jr.pair_only = d.pair && !d.any_sparse;
             }
             rc = run_index_wave(c, B, wp, w, &tf_cap, &max_bag, &max_tf, &jr);
@@ -1968,7 +1981,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             side.active = true;
             side_list = true;
             launch_fill_u32(c->side, c->d_status_side, ST_WORDS, 0);
-            global_order(c, B, b.so, whole_batch_range(B), out->emb_rows, nullptr, capacity, out->n_emb_rows, true);
+            global_order(c, B, b.so, whole_batch_range(B), out->emb_rows, nullptr, capacity, n_list, true);
             HIPCHK(c, hipEventRecord(c->ev_side, c->side));
         }
         // row arithmetic of one (task, field) at a time, through LDS (no row table in HBM)
@@ -2180,7 +2193,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             {
                 Prof p(c, "seg_reduce", (double)nw * (4.0 * D + 4), 0);
                 launch_seg_reduce(st, D, F, ordered ? enc : kPlainVals, w.so.keys, w.so.keys_tmp, nullptr, nw, nw, w.so.vals, w.GX,
-                                  nullptr, seg_room(c, w.so), table);
+                                  nullptr, seg_room(c, w.so), row_table, row_scale);
             }
             if (side_table) HIPCHK(c, hipEventRecord(c->ev_main, st));
         } else if (ordered) {
@@ -2203,13 +2216,14 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         launch_fill_u32(st, reinterpret_cast<u32*>(out->n_emb_rows), 2, 0u);
     } else {
         if (side_list) HIPCHK(c, hipStreamWaitEvent(st, c->ev_side, 0));
-        else if (!pre && !list_ordered) global_order(c, B, b.so, whole_batch_range(B), out->emb_rows, nullptr, capacity, out->n_emb_rows);
+        else if (!pre && !list_ordered) global_order(c, B, b.so, whole_batch_range(B), out->emb_rows, nullptr, capacity, n_list);
         if (F > 0) {
             Prof p(c, "seg_reduce", (double)nnz * (4.0 * D + 4), 0);
-            launch_seg_reduce(st, D, F, (pre || list_ordered) ? enc : kPlainVals, b.so.keys, b.so.keys_tmp, out->n_emb_rows, capacity, nnz,
-                              b.so.vals, b.GX, out->emb_grad, seg_room(c, b.so), nullptr);
+            launch_seg_reduce(st, D, F, (pre || list_ordered) ? enc : kPlainVals, b.so.keys, b.so.keys_tmp, n_list, apply ? nnz : capacity, nnz,
+                              b.so.vals, b.GX, out->emb_grad, seg_room(c, b.so), row_table, row_scale);
         }
     }
+    if (up) up->done = apply;
     if (pre && no_sync) return GM_OK;   // the caller drains the stream; a prepared batch has passed every check already
     u32 hs[ST_WORDS];
     memset(hs, 0, sizeof hs);
@@ -2300,17 +2314,18 @@ extern "C" int gm_meta_train_step(gm_ctx* c, int32_t T, const gm_set* sup, const
     out.emb_rows = rows; out.emb_grad = grad; out.n_emb_rows = n_rows; out.emb_rows_capacity = capacity;
     out.task_loss = task_loss;
     c->ws_bytes = static_cast<size_t>(top - c->ws);
-    const int rc = gm_meta_step(c, T, sup, qry, params, alpha, K, order, loss, &out);
+    EmbUpdate xi{const_cast<float*>(params->emb), -beta};
+    const int rc = meta_step_impl(c, T, sup, qry, params, alpha, K, order, loss, &out, nullptr, false, &xi);
     c->ws_bytes = full;
     if (rc != GM_OK) return rc;
     hipStream_t st = c->stream;
     int64_t h_rows = 0;
-    HIPCHK(c, hipMemcpyAsync(&h_rows, n_rows, sizeof h_rows, hipMemcpyDeviceToHost, st));
+    if (!xi.done) HIPCHK(c, hipMemcpyAsync(&h_rows, n_rows, sizeof h_rows, hipMemcpyDeviceToHost, st));
     for (int l = 0; l < L; ++l) {
         launch_axpy(st, (int64_t)c->dims[l] * c->dims[l + 1], -beta, dW[l], const_cast<float*>(params->W[l]));
         launch_axpy(st, c->dims[l + 1], -beta, db[l], const_cast<float*>(params->b[l]));
     }
-    HIPCHK(c, hipStreamSynchronize(st));
+    if (!xi.done) HIPCHK(c, hipStreamSynchronize(st));
     if (c->F > 0 && h_rows > 0) {
         Prof p(c, "scatter_add", (double)h_rows * (12.0 * D + 8), 0);
         launch_scatter_add(st, D, const_cast<float*>(params->emb), rows, grad, h_rows, -beta);
@@ -2321,8 +2336,10 @@ extern "C" int gm_meta_train_step(gm_ctx* c, int32_t T, const gm_set* sup, const
     return GM_OK;
 }
 
-// The same iteration with the sparse meta-gradient accumulated in a table-shaped buffer of the caller's (any number of
-// lookups, tasks in waves) and applied to the tables in one streaming pass that clears the buffer again.
+// The same iteration for any number of lookups.  Tasks in several waves: the sparse meta-gradient is accumulated in a
+// table-shaped buffer of the caller's and applied to the tables in one streaming pass that clears the buffer again.  One wave:
+// the segment reduction adds to the tables itself and the buffer stays as it is, all zero (48 tasks x (512 + 512) rows, 64
+// tables of 131,072 rows: that pass over 4 GB was 1.2 ms of 13.7).
 extern "C" int gm_meta_train_step_table(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set* qry, const gm_params* params,
                                         float alpha, int32_t K, int32_t order, float beta, float* loss, float* task_loss,
                                         float* emb_grad_table) {
@@ -2357,7 +2374,8 @@ extern "C" int gm_meta_train_step_table(gm_ctx* c, int32_t T, const gm_set* sup,
     out.n_emb_rows = reinterpret_cast<int64_t*>(top + dense_bytes);   // (0 with the table-shaped output)
     out.task_loss = task_loss;
     c->ws_bytes = static_cast<size_t>(top - c->ws);
-    const int rc = gm_meta_step(c, T, sup, qry, params, alpha, K, order, loss, &out);
+    EmbUpdate xi{const_cast<float*>(params->emb), -beta};
+    const int rc = meta_step_impl(c, T, sup, qry, params, alpha, K, order, loss, &out, nullptr, false, &xi);
     c->ws_bytes = full;
     if (rc != GM_OK) return rc;
     hipStream_t st = c->stream;
@@ -2365,7 +2383,7 @@ extern "C" int gm_meta_train_step_table(gm_ctx* c, int32_t T, const gm_set* sup,
         launch_axpy(st, (int64_t)c->dims[l] * c->dims[l + 1], -beta, dW[l], const_cast<float*>(params->W[l]));
         launch_axpy(st, c->dims[l + 1], -beta, db[l], const_cast<float*>(params->b[l]));
     }
-    if (c->F > 0) {
+    if (c->F > 0 && !xi.done) {
         const int64_t n = c->field_base[c->F] * (int64_t)D;   // (D is a multiple of 4)
         Prof p(c, "table_update", 16.0 * n, 0);
         launch_axpy_clear(st, n, -beta, emb_grad_table, const_cast<float*>(params->emb));
@@ -2398,7 +2416,7 @@ static WavePlan whole_batch_plan(const Batch& B) {
     return p;
 }
 // bytes of the index side and of the dense side of a batch run as ONE wave of tasks
-static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order, int64_t capacity,
+static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order,
                            size_t* index_bytes, size_t* dense_bytes) {
     Batch B;
     host_layout(c, B, T, sup, qry);
@@ -2408,7 +2426,7 @@ static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_s
     ia.cap = da.cap = ~(size_t)0 >> 1;
     BatchBufs b;
     WaveBufs w;
-    alloc_batch_index(c, ia, b, T, sup->n_samples, qry->n_samples, sup->nnz + qry->nnz, capacity, true);
+    alloc_batch_index(c, ia, b, T, sup->n_samples, qry->n_samples, sup->nnz + qry->nnz, 0, true);
     alloc_wave_index(c, ia, w, d);
     alloc_batch_dense(c, da, b, T, B.poff_s[T], B.poff_q[T], true);
     alloc_wave_dense(c, da, w, d, K, order);
@@ -2417,8 +2435,7 @@ static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_s
 }
 
 // The index side of one batch, on the context's current stream, into the arena `ia`.
-static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, const gm_set* qry, int K, int order,
-                         int64_t capacity, int64_t* emb_rows, int64_t* n_rows, Prepared& P) {
+static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, const gm_set* qry, int K, int order, Prepared& P) {
     int rc = check_set(c, sup, T, "support");
     if (rc != GM_OK) return rc;
     rc = check_set(c, qry, T, "query");
@@ -2427,7 +2444,7 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
     JoinReq jr;
     Batch& B = P.B;
     B.T = T; B.sup = sup; B.qry = qry; B.table = false;
-    if ((rc = begin_batch(c, B, ia, capacity, true, nullptr))) return rc;
+    if ((rc = begin_batch(c, B, ia, 0, true, nullptr))) return rc;
     P.bm = pick_bm(c, B);
     P.wp = whole_batch_plan(B);
     if (sup->nnz + qry->nnz >= ((int64_t)1 << 31)) return fail(c, GM_ERR_WORKSPACE, "the batch does not run as one wave of tasks");
@@ -2440,7 +2457,6 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
             jr.so = &B.b.so;
             jr.range = whole_batch_range(B);
             jr.n_sup_rows = P.d.Ps; jr.n_qry_rows = P.d.Pq;
-            jr.emb_rows = emb_rows; jr.capacity = capacity; jr.n_rows = n_rows;
             jr.pair_only = P.d.pair && !P.d.any_sparse;
         }
         if ((rc = run_index_wave(c, B, P.wp, P.w, &P.tf_cap, &P.max_bag, &P.max_tf, &jr))) return rc;
@@ -2452,14 +2468,11 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
     }
     if (!jr.used) {
         launch_fill_u32(c->stream, c->d_status, ST_WORDS, 0);
-        global_order(c, B, B.b.so, whole_batch_range(B), emb_rows, nullptr, capacity, n_rows);
+        global_order(c, B, B.b.so, whole_batch_range(B), nullptr, nullptr, 0, nullptr);
     }
-    u32 hs[ST_WORDS];
-    if ((rc = read_status(c, hs))) return rc;
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     B.images.held.clear();
     HIPCHK(c, hipGetLastError());
-    if (hs[ST_CAPACITY])
-        return fail(c, GM_ERR_CAPACITY, "internal: %u rows touched exceed the list capacity %lld", hs[ST_NROWS], (long long)capacity);
     return GM_OK;
 }
 
@@ -2478,10 +2491,8 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
     HIPCHK(c, hipSetDevice(c->device));
     const int L = c->L, D = c->D;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    // what the overlapped loop needs: two index arenas, the meta-gradient lists (row lists twice: the next batch's is
-    // written while this batch's is still being applied), and the dense side of the largest batch
+    // what the overlapped loop needs: two index arenas, the dense meta-gradient and the dense side of the largest batch
     bool overlapped = true;
-    int64_t cap_max = 0;
     size_t idx_max = 0, dense_max = 0;
     for (int i = 0; i < n_iters; ++i) {
         const gm_set *s = &support[i], *q = &query[i];
@@ -2491,16 +2502,14 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
             overlapped = false;   // (the per-iteration call takes the tasks in waves, or reports what is wrong)
             break;
         }
-        const int64_t cap = c->F > 0 ? std::min<int64_t>(s->nnz + q->nnz, c->field_base[c->F]) : 0;
-        cap_max = std::max(cap_max, cap);
         size_t ib, db;
-        one_wave_bytes(c, n_tasks[i], s, q, K, order, cap, &ib, &db);
+        one_wave_bytes(c, n_tasks[i], s, q, K, order, &ib, &db);
         idx_max = std::max(idx_max, up(ib) + 4096);
         dense_max = std::max(dense_max, db);
     }
     int64_t n_dense = 0;
     for (int l = 0; l < L; ++l) n_dense += (int64_t)(c->dims[l] + 1) * c->dims[l + 1];
-    const size_t top = up((size_t)n_dense * 4) + 2 * up((size_t)cap_max * 8) + up((size_t)cap_max * std::max(D, 1) * 4) + 2 * 256 + 256;
+    const size_t top = up((size_t)n_dense * 4) + 2 * 256;
     if (overlapped && c->persistent + dense_max + 2 * idx_max + top + (1 << 20) > c->ws_bytes) overlapped = false;
     if (!overlapped) {   // one iteration after the other (several waves of tasks, or a workspace for one batch only)
         for (int i = 0; i < n_iters; ++i) {
@@ -2513,13 +2522,7 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
     const size_t full = c->ws_bytes;
     char* const top_p = c->ws + (full - top) / 256 * 256;
     float* dense = reinterpret_cast<float*>(top_p);
-    int64_t* rows[2];
-    rows[0] = reinterpret_cast<int64_t*>(top_p + up((size_t)n_dense * 4));
-    rows[1] = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(rows[0]) + up((size_t)cap_max * 8));
-    float* grad = reinterpret_cast<float*>(reinterpret_cast<char*>(rows[1]) + up((size_t)cap_max * 8));
-    int64_t* n_rows[2];
-    n_rows[0] = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(grad) + up((size_t)cap_max * std::max(D, 1) * 4));
-    n_rows[1] = n_rows[0] + 32;
+    int64_t* const n_rows = reinterpret_cast<int64_t*>(top_p + up((size_t)n_dense * 4));   // (no list: not written)
     char* const idx_p[2] = {top_p - 2 * idx_max, top_p - idx_max};
     const size_t dense_end = static_cast<size_t>(idx_p[0] - c->ws);
     std::vector<float*> dW(L), db(L);
@@ -2542,9 +2545,8 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
     auto prepare = [&](int i, bool on_side) -> int {
         Arena ia;
         ia.base = idx_p[i & 1]; ia.cap = idx_max; ia.off = 0;
-        const int64_t cap = c->F > 0 ? std::min<int64_t>(support[i].nnz + query[i].nnz, c->field_base[c->F]) : 0;
         if (on_side) { std::swap(c->stream, c->side); std::swap(c->d_status, c->d_status_side); }
-        const int rc = prepare_batch(c, ia, n_tasks[i], &support[i], &query[i], K, order, cap, rows[i & 1], n_rows[i & 1], P[i & 1]);
+        const int rc = prepare_batch(c, ia, n_tasks[i], &support[i], &query[i], K, order, P[i & 1]);
         if (on_side) { std::swap(c->stream, c->side); std::swap(c->d_status, c->d_status_side); }
         return rc;
     };
@@ -2554,43 +2556,27 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
         gm_grads out;
         memset(&out, 0, sizeof out);
         out.dW = dW.data(); out.db = db.data();
-        out.emb_rows = rows[i & 1]; out.emb_grad = grad; out.n_emb_rows = n_rows[i & 1];
-        out.emb_rows_capacity = c->F > 0 ? std::min<int64_t>(support[i].nnz + query[i].nnz, c->field_base[c->F]) : 0;
+        out.n_emb_rows = n_rows;
+        EmbUpdate xi{const_cast<float*>(params->emb), -beta};
         c->ws_bytes = dense_end;
-        rc = meta_step_impl(c, n_tasks[i], &support[i], &query[i], params, alpha, K, order, losses + i, &out, &P[i & 1], true);
+        rc = meta_step_impl(c, n_tasks[i], &support[i], &query[i], params, alpha, K, order, losses + i, &out, &P[i & 1], true, &xi);
         c->ws_bytes = full;
         if (rc != GM_OK) { (void)hipStreamSynchronize(st); return rc; }
-        int64_t h_rows = 0;
-        HIPCHK(c, hipMemcpyAsync(&h_rows, n_rows[i & 1], sizeof h_rows, hipMemcpyDeviceToHost, st));
-        // the next batch's index side, on the second stream, while this batch computes; its row list replaces the one of
-        // batch i-1, whose update (enqueued before this batch's step) must have been applied: ev_main marks that point
-        int rc_next = GM_OK;
-        if (i + 1 < n_iters) {
-            HIPCHK(c, hipStreamWaitEvent(c->side, c->ev_main, 0));
-            rc_next = prepare(i + 1, true);
-        }
-        HIPCHK(c, hipStreamSynchronize(st));
-        HIPCHK(c, hipGetLastError());
-        prof_drain(c);
-        // the two global back-propagation steps with the outer step size (Alg. 1), in place
+        // the two global back-propagation steps with the outer step size (Alg. 1), in place: xi's by the step itself
         for (int l = 0; l < L; ++l) {
             launch_axpy(st, (int64_t)c->dims[l] * c->dims[l + 1], -beta, dW[l], const_cast<float*>(params->W[l]));
             launch_axpy(st, c->dims[l + 1], -beta, db[l], const_cast<float*>(params->b[l]));
         }
-        if (c->F > 0 && h_rows > 0) {
-            Prof p(c, "scatter_add", (double)h_rows * (12.0 * D + 8), 0);
-            launch_scatter_add(st, D, const_cast<float*>(params->emb), rows[i & 1], grad, h_rows, -beta);
-        }
-        HIPCHK(c, hipEventRecord(c->ev_main, st));
+        // the next batch's index side, on the second stream, while this batch computes, in the arena of batch i-1, which the
+        // host has waited for
+        int rc_next = GM_OK;
+        if (i + 1 < n_iters) rc_next = prepare(i + 1, true);
+        HIPCHK(c, hipStreamSynchronize(st));
+        HIPCHK(c, hipGetLastError());
+        prof_drain(c);
         if (n_done) *n_done = i + 1;
-        if (rc_next != GM_OK) {
-            (void)hipStreamSynchronize(st);
-            return rc_next;
-        }
+        if (rc_next != GM_OK) return rc_next;
     }
-    HIPCHK(c, hipStreamSynchronize(st));
-    HIPCHK(c, hipGetLastError());
-    prof_drain(c);
     return GM_OK;
 }
 

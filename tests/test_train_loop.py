@@ -125,3 +125,35 @@ def test_train_loop_with_more_tasks_than_a_wave(tasks, per_wave):
     _same_params(loop, one)
     assert all(torch.isfinite(w).all() for w in loop.W)
     ctx.close()
+
+
+@pytest.mark.parametrize("dim,rows,bf", [(4, 3, 0), (32, 700, 0), (64, 5, 1), (256, 40, 0)])
+@pytest.mark.parametrize("waves", [1, 2])
+def test_update_of_the_rows_inside_the_step(dim, rows, bf, waves):
+    """One wave of tasks: the segment reduction adds to the tables itself.  The parameters are those of the step's list applied
+    by gm_scatter_add, bit for bit; several waves take the list, or the caller's table-shaped buffer, as before."""
+    from paper_2401_04338_amd import GMeta
+    cfg = SMALL.with_(n_tasks=12, n_support=50, n_query=40, n_fields=3, emb_dim=dim, rows_per_field=rows, bag_max=9,
+                      layer_dims=(3 * dim + 13, 32, 1), inner_lr=0.05, mlp_dtype=bf)
+    beta, K, order, dev = 0.02, 1, 2, torch.device("cuda", 0)
+    params = make_params(cfg, "cpu", emb_std=0.1)
+    s, q = make_batch(cfg, 0, dev)
+    ctx = GMeta.from_config(cfg, workspace_bytes=1 << 30)
+    ctx.configure("max_wave_tasks", -(-cfg.n_tasks // waves))
+    want = _clone(params, dev)
+    out = ctx.meta_step(s, q, want, cfg.inner_lr, K, order)
+    n = int(out["n_emb_rows"].item())
+    ctx.scatter_add(want.emb, out["emb_rows"][:n].contiguous(), out["emb_grad"][:n].contiguous(), -beta)
+    got = _clone(params, dev)
+    loss = ctx.meta_train_step(s, q, got, cfg.inner_lr, K, order, beta)
+    assert float(loss.item()) == float(out["loss"].item())
+    assert torch.equal(got.emb, want.emb)
+    by_table, table = _clone(params, dev), torch.zeros(3 * rows, dim, device=dev)
+    ctx.meta_train_step_table(s, q, by_table, cfg.inner_lr, K, order, beta, table)
+    assert not table.any()
+    if waves == 1:
+        _same_params(by_table, got)
+    else:      # (two sums per row, added: fp32 rounding of at most three additions more)
+        moved = (want.emb - params.emb.to(dev)).abs().max()
+        assert (by_table.emb - got.emb).abs().max() <= 1e-5 * moved + 2 * torch.finfo(torch.float32).eps * want.emb.abs().max()
+    ctx.close()
