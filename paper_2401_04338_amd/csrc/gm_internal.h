@@ -202,7 +202,7 @@ struct PairCountArgs {
     int F;
     const int32_t *real_off_s, *real_off_q;   // [Tw+1] first sample of each task (relative to the wave)
     const int32_t *row_off_s, *row_off_q;     // [Tw+1] first row of each task in the activation buffers
-    const u32 *base_s, *base_q, *cnt_q, *n_slots;   // per (task, field)
+    const u32 *base_s, *base_q, *cnt_s, *cnt_q, *n_slots;   // per (task, field)
     const int32_t *slot_start, *qseg_lo, *qseg_hi;
     const int2 *sup_sorted, *qry_sorted;
     const int64_t *off_ss, *off_qs, *off_sq;  // [Tw] byte offset of the task's first matrix of each kind

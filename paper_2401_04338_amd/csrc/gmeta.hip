@@ -1719,7 +1719,7 @@ static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& 
     memset(&pa, 0, sizeof pa);
     pa.F = F;
     pa.real_off_s = w.real_off_s; pa.real_off_q = w.real_off_q; pa.row_off_s = w.row_off_s; pa.row_off_q = w.row_off_q;
-    pa.base_s = w.base_s; pa.base_q = w.base_q; pa.cnt_q = w.cnt_q; pa.n_slots = w.n_slots;
+    pa.base_s = w.base_s; pa.base_q = w.base_q; pa.cnt_s = w.cnt_s; pa.cnt_q = w.cnt_q; pa.n_slots = w.n_slots;
     pa.slot_start = w.slot_start; pa.qseg_lo = w.qseg_lo; pa.qseg_hi = w.qseg_hi;
     pa.sup_sorted = w.sup_sorted; pa.qry_sorted = w.qry_sorted;
     pa.off_ss = w.pair_off_ss; pa.off_qs = w.pair_off_qs; pa.off_sq = w.pair_off_sq;

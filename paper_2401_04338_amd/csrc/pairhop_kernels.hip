@@ -33,7 +33,7 @@ __host__ __device__ __forceinline__ int pad64(int n) { return (n + 63) & ~63; }
 // number of times bag b looks row u up.  Under a skewed row distribution a few hot rows carry nearly all
 // of the pairs (a row looked up a times by one set and b times by the other adds a*b of them), and LDS
 // atomics retire only about one lane per cycle, so the hot rows do not go through pair-by-pair atomics:
-// PC_HB hot rows at a time, their count vectors are laid out densely ([bags, PC_HB] bytes, one atomic per
+// a batch of HB hot rows at a time, their count vectors are laid out densely ([bags, HB] bytes, one atomic per
 // lookup) and multiplied on the matrix cores as 8-bit integers (v_mfma_i32_32x32x32_i8: a count is at
 // most the bag's length, which this path limits to 127; sums are exact in 32 bits).
 // Only the remaining rows (fewer than PC_HOT lookups from either set, at most 9 pairs each) are counted
@@ -43,22 +43,45 @@ __host__ __device__ __forceinline__ int pad64(int n) { return (n + 63) & ~63; }
 // The kernel is bound by latency, not by arithmetic, so everything it walks more than once is staged in
 // LDS when the workgroup starts: the bag of every lookup of both lists (16 bits each) and one record per
 // row with pairs (hot: the bounds of its two lookup ranges; cold: packed starts and sizes).  After that
-// only LDS is read until the matrix is written out.
+// only LDS is read until the matrix is written out.  Hot rows are numbered in the lists' order and every lookup
+// of one carries its number within its batch beside its bag, so that a batch is one range of each list that all
+// threads walk side by side; a wave per row waited for the hottest one, three barriers for every 32 rows.  The
+// count blocks lie where the tile will: with 64 rows a batch they take no more LDS than it.
+// Measured, one launch (before: 32 rows a batch, a wave per row and batch, one workgroup per compute unit): 512 tasks of 256 + 256
+// rows x 26 fields, bags of 1..20, two kinds 2.14 -> 1.21 ms; 201 tasks of 75..225 + 122..365 rows 0.63 -> 0.37; 128 tasks of
+// 512 + 512 rows x 64 fields, bags of 1..32 3.38 -> 2.30 (1.0 ms of it the time its 4.3 GB take to write); 3 of them 111 -> 78 us.
+// Tried: a bag's further lookups of a row found beside the first and only those added, the first ones stored: the second pass
+// costs more than the atomics it saves (2.30 -> 2.65).
 // ------------------------------------------------------------------------------------------------
 #define PC_TPW 4          // MFMA tiles per wave: a workgroup of NT threads covers NT / 16 tiles per row tile
 #define PC_SMALL_ROWS 128 // samples per set of a 'small' task: 16 tiles, four waves
 #define PC_SMALL_N 1984   // lookups per set of a 'small' (task, field)
-#define PC_HB 32     // hot rows per matrix-core batch (one MFMA contraction step)
-#define PC_HBS 48    // bytes per bag in a count block (16-byte fragment reads; 12 words spread them over the banks)
+#define PC_TWO_LDS (PAIR_LDS_BYTES / 2)   // LDS of a workgroup that shares its compute unit with another
 #define PC_HOT 4     // a row is hot when one of the two sets looks it up at least this often
+// bytes per bag in a count block of hb rows (16-byte fragment reads; 12 or 20 words spread them over the banks)
+__host__ __device__ constexpr int pc_stride(int hb) { return hb + 16; }
+// LDS of one row tile of R out-rows: the byte cells, or the count blocks of a batch that come before them
+__host__ __device__ __forceinline__ size_t pc_tile_bytes(int R, int colsP, int hb) {
+    const size_t cells = (size_t)colsP * (R + 4), counts = (size_t)(R + colsP) * pc_stride(hb);
+    return cells > counts ? cells : counts;
+}
 
 typedef int pc_int4 __attribute__((ext_vector_type(4)));
 typedef int pc_int16 __attribute__((ext_vector_type(16)));
 
-template <int NT>
+// (LDS only: the matrices' stores go on behind it)
+__device__ __forceinline__ void pc_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// HBITS: log2 of the hot rows of a batch; a lookup's 16 bits hold its bag in the lower 15 - HBITS
+template <int NT, int HBITS>
 __global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
+    constexpr int HB = 1 << HBITS, HBS = pc_stride(HB), BAG_BITS = 15 - HBITS, BAG_MASK = (1 << BAG_BITS) - 1;
     extern __shared__ __attribute__((aligned(16))) u32 pc_lds[];
-    __shared__ int sh_nhot, sh_ncold;
+    __shared__ int sh_ncold, sh_wave_hot[2][NT / 64];
     const int f = blockIdx.x, t = blockIdx.y;
     const bool qs = blockIdx.z == 1;   // 0: support x support, 1: query x support (and its transpose)
     if (!qs && !a.want_ss) return;
@@ -71,7 +94,7 @@ __global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
     if (colsP == 0 || rowsP == 0) return;
     const u32 B = a.base_s[tf], Bq = a.base_q[tf];
     const int nu = (int)a.n_slots[tf];
-    const int n_in_entries = a.slot_start[B + tf + nu] - (int)B;
+    const int n_in_entries = (int)a.cnt_s[tf];
     const int n_out_entries = qs ? (int)a.cnt_q[tf] : n_in_entries;
     if (a.cls) {   // uneven tasks: the small (task, field)s have a launch of their own, with small workgroups
         const bool small = max(ns, nq) <= PC_SMALL_ROWS && max(n_in_entries, n_out_entries) <= a.small_n;
@@ -80,62 +103,82 @@ __global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
     // LDS, from the end (6 * n_max bytes): the bag of every out lookup and of every in lookup (16 bits each, in the
     // order of the row-sorted lists; one array when both sets are the support set), then the records: hot rows
     // from the front (two words: in range, out range), cold rows with pairs from the back (one word).
-    // From the start: the tile of R out-rows, TRANSPOSED, one byte per cell: cell (i, j) at j * ldT + i with
-    // ldT = R + 4 (an odd number of words: the MFMA result, the transposed read-out and the atomics all spread
-    // over the banks); then the two dense count blocks of a batch, [R] and [colsP] bags of PC_HBS bytes.
+    // From the start: the two dense count blocks of a batch, [R] and [colsP] bags of HBS bytes (one block when both sets
+    // are the support set); then in their place the tile of R out-rows, TRANSPOSED, one byte per cell: cell (i, j) at
+    // j * ldT + i with ldT = R + 4 (an odd number of words: the MFMA result, the transposed read-out and the atomics all
+    // spread over the banks).
     const int nmax = a.n_max;                                  // a multiple of 8
     uint16_t* out_rows = reinterpret_cast<uint16_t*>(pc_lds) + (a.lds_bytes / 2 - nmax);
     uint16_t* in_rows = qs ? out_rows - nmax : out_rows;
     const int RW = qs ? nmax / 2 : nmax;                       // record words
     u32* recs = reinterpret_cast<u32*>(in_rows) - RW;
-    if (threadIdx.x == 0) { sh_nhot = 0; sh_ncold = 0; }
-    __syncthreads();
-    {
-        // eight loads in flight per thread and list: the workgroup has the compute unit to itself, so nothing else hides
-        // the latency of these first reads
-        auto stage_rows = [&](const int2* list, int n_entries, int row0, uint16_t* dst) {
-            for (int e0 = threadIdx.x; e0 < n_entries; e0 += 8 * NT) {
-                int r[8];
+    if (threadIdx.x == 0) sh_ncold = 0;
+    // The first lookups of both lists are on their way while the rows are classified: eight loads per thread and list, as the
+    // workgroup has little company on its compute unit to hide the latency of these first reads.
+    const int2 *in_list = a.sup_sorted + B, *out_list = a.qry_sorted + Bq;   // {row, slot}, slot-sorted
+    int2 in_first[8], out_first[8];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) r[q] = list[min(e0 + q * NT, n_entries - 1)].x;
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    if (e0 + q * NT < n_entries) dst[e0 + q * NT] = (uint16_t)(r[q] - row0);
-            }
-        };
-        stage_rows(a.sup_sorted + B, n_in_entries, a.row_off_s[t], in_rows);   // {row, slot}, slot-sorted
-        if (qs) stage_rows(a.qry_sorted + Bq, n_out_entries, a.row_off_q[t], out_rows);
+    for (int q = 0; q < 8; ++q) {
+        in_first[q] = out_first[q] = make_int2(0, -1);
+        if ((int)threadIdx.x + q * NT < n_in_entries) in_first[q] = in_list[threadIdx.x + q * NT];
+        if (qs && (int)threadIdx.x + q * NT < n_out_entries) out_first[q] = out_list[threadIdx.x + q * NT];
     }
-    for (int u0 = threadIdx.x; u0 < nu; u0 += 4 * NT) {   // (the loads of four rows in flight per thread)
-        int lo_[4], hi_[4], lo2_[4], hi2_[4];
+    uint8_t* const mark = reinterpret_cast<uint8_t*>(pc_lds);   // [nu] 0, or HB | the row's number within its batch of hot rows (where the tile will be)
+    pc_barrier();
+    int nhot = 0;                                              // (the same in all threads)
+    for (int ub = 0; ub < nu; ub += 4 * NT) {                  // four rows per thread, their bounds in flight together
+        const int u0 = ub + 4 * (int)threadIdx.x;
+        int lo_[5], lo2_[4], hi2_[4];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) lo_[q] = a.slot_start[B + tf + min(u0 + q, nu)] - (int)B;
+        if (qs) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                lo2_[q] = a.qseg_lo[B + min(u0 + q, nu - 1)] - (int)Bq;
+                hi2_[q] = a.qseg_hi[B + min(u0 + q, nu - 1)] - (int)Bq;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { lo2_[q] = lo_[q]; hi2_[q] = lo_[q + 1]; }
+        }
+        // hot rows numbered in list order: those of the waves before this one, of the lanes before this one, the thread's own
+        bool hot[4];
+        int k = nhot, mine = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int u = min(u0 + q * NT, nu - 1);
-            lo_[q] = a.slot_start[B + tf + u] - (int)B;
-            hi_[q] = a.slot_start[B + tf + u + 1] - (int)B;
-            lo2_[q] = lo_[q]; hi2_[q] = hi_[q];
-            if (qs) { lo2_[q] = a.qseg_lo[B + u] - (int)Bq; hi2_[q] = a.qseg_hi[B + u] - (int)Bq; }
+            const int na = lo_[q + 1] - lo_[q], nb = hi2_[q] - lo2_[q];
+            hot[q] = u0 + q < nu && na > 0 && nb > 0 && (na >= PC_HOT || nb >= PC_HOT);
+            const unsigned long long in_wave = __ballot(hot[q]);
+            k += __popcll(in_wave & ((1ull << lane) - 1ull));
+            mine += __popcll(in_wave);
+        }
+        int* const counts = sh_wave_hot[(ub / (4 * NT)) & 1];  // (two sets in turn: one barrier each)
+        if (lane == 0) counts[wv] = mine;
+        pc_barrier();
+        for (int w = 0; w < NT / 64; ++w) {
+            const int c = counts[w];
+            if (w < wv) k += c;
+            nhot += c;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (u0 + q * NT >= nu) continue;
-            const int lo = lo_[q], hi = hi_[q], lo2 = lo2_[q], hi2 = hi2_[q];
-            const int na = hi - lo, nb = hi2 - lo2;
-            if (na <= 0 || nb <= 0) continue;
-            if (na >= PC_HOT || nb >= PC_HOT) {
-                const int k = atomicAdd(&sh_nhot, 1);
+            if (u0 + q >= nu) continue;
+            const int na = lo_[q + 1] - lo_[q], nb = hi2_[q] - lo2_[q];
+            mark[u0 + q] = hot[q] ? (uint8_t)(HB | (k & (HB - 1))) : (uint8_t)0;
+            if (hot[q]) {
                 if (2 * k + 1 < RW) {
-                    recs[2 * k] = (u32)lo | ((u32)hi << 16);
-                    recs[2 * k + 1] = (u32)lo2 | ((u32)hi2 << 16);
+                    recs[2 * k] = (u32)lo_[q] | ((u32)lo_[q + 1] << 16);
+                    recs[2 * k + 1] = (u32)lo2_[q] | ((u32)hi2_[q] << 16);
                 }
-            } else {
-                const int k = atomicAdd(&sh_ncold, 1);
-                if (k < RW) recs[RW - 1 - k] = (u32)lo | ((u32)lo2 << 14) | ((u32)na << 28) | ((u32)nb << 30);
+                ++k;
+            } else if (na > 0 && nb > 0) {
+                const int kc = atomicAdd(&sh_ncold, 1);
+                if (kc < RW) recs[RW - 1 - kc] = (u32)lo_[q] | ((u32)lo2_[q] << 14) | ((u32)na << 28) | ((u32)nb << 30);
             }
         }
     }
-    __syncthreads();
-    const int nhot = sh_nhot, ncold = sh_ncold;
+    pc_barrier();
+    const int ncold = sh_ncold;
     if (2 * nhot + ncold > RW) {   // the records do not fit (they may have overwritten each other): sparse kernel
         if (threadIdx.x == 0) {
             a.task_path[t] = 0u;
@@ -144,72 +187,106 @@ __global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
         return;
     }
     const size_t budget = (size_t)a.lds_bytes - 6 * (size_t)nmax;
-    int R = min(rowsP, a.max_tile_rows);   // at most 64 MFMA tiles per row tile
-    while (R > 32 && ((size_t)colsP * (R + 4) + (size_t)(R + colsP) * PC_HBS > budget || R * colsP > NT * 64)) R -= 32;
-    if ((size_t)colsP * (R + 4) + (size_t)(R + colsP) * PC_HBS > budget) {   // not even 32 rows fit: sparse kernel
+    int R = min(rowsP, a.max_tile_rows);   // at most NT / 16 MFMA tiles per row tile
+    while (R > 32 && (pc_tile_bytes(R, colsP, HB) > budget || R * colsP > NT * 64)) R -= 32;
+    if (pc_tile_bytes(R, colsP, HB) > budget) {   // not even 32 rows fit: sparse kernel
         if (threadIdx.x == 0) {
             a.task_path[t] = 0u;
             a.status[ST_PAIR_OVF] = 1u;
         }
         return;
     }
+    // the lists: every lookup's bag, and where its row is hot the row's number within its batch
+    auto stage = [&](const int2* list, const int2 (&first)[8], int n, int row0, uint16_t* dst) {
+        auto put = [&](int e, int2 v) { dst[e] = (uint16_t)((v.x - row0) | (v.y >= 0 ? (int)mark[v.y] << BAG_BITS : 0)); };
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if ((int)threadIdx.x + q * NT < n) put(threadIdx.x + q * NT, first[q]);
+        for (int e0 = threadIdx.x + 8 * NT; e0 < n; e0 += 8 * NT) {
+            int2 v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = list[min(e0 + q * NT, n - 1)];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (e0 + q * NT < n) put(e0 + q * NT, v[q]);
+        }
+    };
+    stage(in_list, in_first, n_in_entries, a.row_off_s[t], in_rows);
+    if (qs) stage(out_list, out_first, n_out_entries, a.row_off_q[t], out_rows);
     const int ldT = R + 4;
     uint8_t* tile = reinterpret_cast<uint8_t*>(pc_lds);
-    uint8_t* c_out = tile + (size_t)colsP * ldT;   // colsP * ldT is a multiple of 16
-    uint8_t* c_in = c_out + R * PC_HBS;
+    uint8_t* c_in = tile;
+    uint8_t* c_block = tile + (size_t)colsP * HBS;   // of the out bags, where they are another set's
     uint8_t* M = a.mat + (qs ? a.off_qs[t] : a.off_ss[t]) + (size_t)f * rowsP * colsP;
     uint8_t* Mt = (qs && a.want_sq) ? a.mat + a.off_sq[t] + (size_t)f * colsP * rowsP : nullptr;  // [colsP rows][rowsP cols]
     const int tiles_c = colsP / 32;
     bool ovf = false;
     for (int i0 = 0; i0 < rowsP; i0 += R) {
         const int rows_here = min(R, rowsP - i0);
-        const int n_tiles = (rows_here / 32) * tiles_c;
-        int my_tr[PC_TPW], my_tc[PC_TPW];
+        // A wave's four tiles are two pairs side by side: two by two where the tile rows are even in number, so that every
+        // fragment read feeds two products.
+        const int pairs_c = tiles_c / 2, tile_rows = rows_here / 32;
+        const bool square = (tile_rows & 1) == 0;
+        int my_tr[2], my_tc[2];      // of each pair: its tile row, its first tile column
 #pragma unroll
-        for (int q = 0; q < PC_TPW; ++q) {
-            const int tt = wv * PC_TPW + q;
-            my_tr[q] = tt < n_tiles ? tt / tiles_c : -1;
-            my_tc[q] = tt - (tt / tiles_c) * tiles_c;
+        for (int p = 0; p < 2; ++p) {
+            const int unit = square ? wv : 2 * wv + p, r = unit / pairs_c * (square ? 2 : 1) + (square ? p : 0);
+            my_tr[p] = r < tile_rows ? r : -1;
+            my_tc[p] = unit % pairs_c * 2;
         }
         pc_int16 acc[PC_TPW];
 #pragma unroll
         for (int q = 0; q < PC_TPW; ++q)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[q][v] = 0;
-        for (int hb = 0; hb < nhot; hb += PC_HB) {
-            __syncthreads();   // the previous batch's fragments (or the previous tile) have been read
-            for (int i = threadIdx.x; i < (R + colsP) * PC_HBS / 16; i += NT)   // both count blocks, contiguous
-                reinterpret_cast<uint4*>(c_out)[i] = make_uint4(0u, 0u, 0u, 0u);
-            __syncthreads();
-            // one atomic per lookup (a count is at most the bag's length); a wave per hot row
-            for (int hx = wv; hx < PC_HB && hb + hx < nhot; hx += NT / 64) {
-                const u32 r0 = recs[2 * (hb + hx)], r1 = recs[2 * (hb + hx) + 1];
-                const u32 inc = 1u << (8 * (hx & 3));
-                for (int e = (int)(r0 & 0xFFFFu) + lane; e < (int)(r0 >> 16); e += 64)
-                    atomicAdd(reinterpret_cast<u32*>(c_in) + (((int)in_rows[e] * PC_HBS + hx) >> 2), inc);
-                for (int e = (int)(r1 & 0xFFFFu) + lane; e < (int)(r1 >> 16); e += 64) {
-                    const int i = (int)out_rows[e] - i0;
-                    if ((unsigned)i < (unsigned)rows_here) atomicAdd(reinterpret_cast<u32*>(c_out) + ((i * PC_HBS + hx) >> 2), inc);
-                }
-            }
-            __syncthreads();
+        const uint8_t* c_out = qs ? c_block : c_in + (size_t)i0 * HBS;
+        for (int hb = 0; hb < nhot; hb += HB) {
+            pc_barrier();   // the previous batch's fragments (or the previous tile) have been read
+            for (int i = threadIdx.x; i < (colsP + (qs ? rows_here : 0)) * HBS / 16; i += NT)   // both count blocks, contiguous
+                reinterpret_cast<uint4*>(c_in)[i] = make_uint4(0u, 0u, 0u, 0u);
+            pc_barrier();
+            // one atomic per lookup (a count is at most the bag's length)
+            auto count = [&](const uint16_t* list, int lo, int hi, uint8_t* block, int first, int rows) {
+                for (int e0 = lo + (int)threadIdx.x; e0 < hi; e0 += 4 * NT) {
+                    u32 v[4];
 #pragma unroll
-            for (int q = 0; q < PC_TPW; ++q) {
-                if (my_tr[q] >= 0) {
-                    const pc_int4 qa = *reinterpret_cast<const pc_int4*>(c_out + (my_tr[q] * 32 + ln) * PC_HBS + h * 16);
-                    const pc_int4 qb = *reinterpret_cast<const pc_int4*>(c_in + (my_tc[q] * 32 + ln) * PC_HBS + h * 16);
-                    acc[q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(qa, qb, acc[q], 0, 0, 0);
+                    for (int q = 0; q < 4; ++q) v[q] = e0 + q * NT < hi ? list[e0 + q * NT] : 0u;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int i = (int)(v[q] & BAG_MASK) - first, k = (int)(v[q] >> BAG_BITS) & (HB - 1);
+                        if ((v[q] & 0x8000u) && (unsigned)i < (unsigned)rows)
+                            atomicAdd(reinterpret_cast<u32*>(block) + ((i * HBS + k) >> 2), 1u << (8 * (k & 3)));
+                    }
+                }
+            };
+            const int last = min(hb + HB, nhot) - 1;
+            count(in_rows, (int)(recs[2 * hb] & 0xFFFFu), (int)(recs[2 * last] >> 16), c_in, 0, colsP);
+            if (qs) count(out_rows, (int)(recs[2 * hb + 1] & 0xFFFFu), (int)(recs[2 * last + 1] >> 16), c_block, i0, rows_here);
+            pc_barrier();
+            if (my_tr[0] >= 0) {
+#pragma unroll
+                for (int kk = 0; kk < HB; kk += 32) {
+                    auto frag = [&](const uint8_t* block, int tile_no) { return *reinterpret_cast<const pc_int4*>(block + (tile_no * 32 + ln) * HBS + kk + h * 16); };
+                    pc_int4 qb[2] = {frag(c_in, my_tc[0]), frag(c_in, my_tc[0] + 1)};
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        if (my_tr[p] < 0) continue;
+                        if (p == 1 && !square) { qb[0] = frag(c_in, my_tc[1]); qb[1] = frag(c_in, my_tc[1] + 1); }
+                        const pc_int4 qa = frag(c_out, my_tr[p]);
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) acc[2 * p + c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(qa, qb[c], acc[2 * p + c], 0, 0, 0);
+                    }
                 }
             }
         }
         // ---- the hot part becomes the tile's initial content (every cell of the tile's rows is written); a lane
         //      holds four consecutive rows of one column: one word of the transposed tile.  255 stands for
         //      "255 or more" and is reported when the tile is read out.
-        __syncthreads();   // the previous tile has been read out
+        pc_barrier();   // the previous tile has been read out, and the last batch's counts
 #pragma unroll
         for (int q = 0; q < PC_TPW; ++q) {
-            if (my_tr[q] >= 0) {
-                uint8_t* col = tile + (size_t)(my_tc[q] * 32 + ln) * ldT + my_tr[q] * 32 + 4 * h;
+            if (my_tr[q >> 1] >= 0) {
+                uint8_t* col = tile + (size_t)((my_tc[q >> 1] + (q & 1)) * 32 + ln) * ldT + my_tr[q >> 1] * 32 + 4 * h;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const u32 b0 = min((u32)acc[q][4 * g + 0], 255u), b1 = min((u32)acc[q][4 * g + 1], 255u);
@@ -218,55 +295,70 @@ __global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
                 }
             }
         }
-        __syncthreads();
+        pc_barrier();
         // ---- the other rows, pair by pair; a cell that was at 254 or more before an increment may have
         //      wrapped: reported
         for (int k = threadIdx.x; k < ncold; k += NT) {
             const u32 r = recs[RW - 1 - k];
             const int lo = (int)(r & 0x3FFFu), lo2 = (int)((r >> 14) & 0x3FFFu), na = (int)((r >> 28) & 3u), nb = (int)(r >> 30);
-            for (int y = 0; y < nb; ++y) {
-                const int i = (int)out_rows[lo2 + y] - i0;
-                if ((unsigned)i >= (unsigned)rows_here) continue;
-                const int sh = 8 * (i & 3);
-                for (int x = 0; x < na; ++x) {
-                    const int j = (int)in_rows[lo + x];
-                    const u32 old = atomicAdd(&pc_lds[(j * ldT + i) >> 2], 1u << sh);
-                    ovf |= ((old >> sh) & 0xFFu) >= 254u;
-                }
+            int i[3], j[3];        // (at most three lookups from either set: all reads, then all atomics in flight)
+#pragma unroll
+            for (int y = 0; y < 3; ++y) {
+                i[y] = y < nb ? (int)out_rows[lo2 + y] - i0 : -1;
+                j[y] = y < na ? (int)in_rows[lo + y] : 0;
             }
+            u32 old[3][3];
+#pragma unroll
+            for (int y = 0; y < 3; ++y)
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    old[y][x] = 0u;
+                    if ((unsigned)i[y] < (unsigned)rows_here && x < na) {
+                        const int sh = 8 * (i[y] & 3);
+                        old[y][x] = atomicAdd(&pc_lds[(j[x] * ldT + i[y]) >> 2], 1u << sh) >> sh;
+                    }
+                }
+#pragma unroll
+            for (int y = 0; y < 3; ++y)
+#pragma unroll
+                for (int x = 0; x < 3; ++x) ovf |= (old[y][x] & 0xFFu) >= 254u;
         }
-        __syncthreads();
-        // ---- rows [i0, i0 + rows_here) of M.  A thread takes a 4 x 4 block of cells: four words of the transposed tile
-        //      (four rows of one column each), turned in registers into four words of M (four columns of one row each).
-        //      Of a wave, 16 lanes lie along the columns and 4 along the rows: the tile reads then spread over all
-        //      banks (a column step moves 4 banks, a row step 1), and every row gets 64 contiguous bytes per store.
+        pc_barrier();
+        // ---- rows [i0, i0 + rows_here) of M.  A thread takes 4 rows x 8 columns: eight words of the transposed tile (four rows
+        //      of one column each), turned in registers into four pairs of words of M.  Of a wave, 8 lanes lie along the
+        //      columns and 8 along the rows: every lane has a bank of its own, and every row gets 64 contiguous bytes per store.
         {
-            const int jl = lane & 15, il = lane >> 4;
-            const int pj_n = colsP / 64, n_patches = pj_n * (rows_here / 16);
+            const int jl = lane & 7, il = lane >> 3;
+            const int pj_n = colsP / 64, n_patches = pj_n * (rows_here / 32);
             for (int wq = wv; wq < n_patches; wq += NT / 64) {
                 const int pj = wq % pj_n, pi = wq / pj_n;
-                const int j4 = (pj * 16 + jl) * 4, i4 = (pi * 4 + il) * 4;
-                const u32 ca = *reinterpret_cast<const u32*>(tile + (j4 + 0) * ldT + i4), cb = *reinterpret_cast<const u32*>(tile + (j4 + 1) * ldT + i4);
-                const u32 cc = *reinterpret_cast<const u32*>(tile + (j4 + 2) * ldT + i4), cd = *reinterpret_cast<const u32*>(tile + (j4 + 3) * ldT + i4);
-                // a byte of 255: some byte of the complement is zero
-                const u32 na_ = ~ca, nb_ = ~cb, nc_ = ~cc, nd_ = ~cd;
-                ovf |= (((na_ - 0x01010101u) & ca & 0x80808080u) | ((nb_ - 0x01010101u) & cb & 0x80808080u) |
-                        ((nc_ - 0x01010101u) & cc & 0x80808080u) | ((nd_ - 0x01010101u) & cd & 0x80808080u)) != 0u;
-                const u32 t0 = __builtin_amdgcn_perm(cb, ca, 0x05010400u), t1 = __builtin_amdgcn_perm(cb, ca, 0x07030602u);
-                const u32 u0 = __builtin_amdgcn_perm(cd, cc, 0x05010400u), u1 = __builtin_amdgcn_perm(cd, cc, 0x07030602u);
-                u32* dst = reinterpret_cast<u32*>(M + (size_t)(i0 + i4) * colsP + j4);
-                const size_t rw = (size_t)colsP / 4;
-                dst[0] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
-                dst[rw] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
-                dst[2 * rw] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
-                dst[3 * rw] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
+                const int j8 = (pj * 8 + jl) * 8, i4 = (pi * 8 + il) * 4;
+                u32 w[8];
+#pragma unroll
+                for (int x = 0; x < 8; ++x) w[x] = *reinterpret_cast<const u32*>(tile + (j8 + x) * ldT + i4);
+#pragma unroll
+                for (int x = 0; x < 8; ++x) ovf |= ((~w[x] - 0x01010101u) & w[x] & 0x80808080u) != 0u;   // a byte of 255: some byte of the complement is zero
+                u32 o[4][2];
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    const u32 t0 = __builtin_amdgcn_perm(w[4 * x + 1], w[4 * x], 0x05010400u), t1 = __builtin_amdgcn_perm(w[4 * x + 1], w[4 * x], 0x07030602u);
+                    const u32 u0 = __builtin_amdgcn_perm(w[4 * x + 3], w[4 * x + 2], 0x05010400u), u1 = __builtin_amdgcn_perm(w[4 * x + 3], w[4 * x + 2], 0x07030602u);
+                    o[0][x] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
+                    o[1][x] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
+                    o[2][x] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
+                    o[3][x] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
+                }
+                uint8_t* dst = M + (size_t)(i0 + i4) * colsP + j8;
+#pragma unroll
+                for (int y = 0; y < 4; ++y) *reinterpret_cast<uint2*>(dst + (size_t)y * colsP) = make_uint2(o[y][0], o[y][1]);
             }
         }
         if (Mt) {  // the transpose is the tile as it lies: row j holds columns [i0, i0 + rows_here)
-            const int gpr = rows_here / 4;
+            const int gpr = rows_here / 16;
             for (int w = threadIdx.x; w < colsP * gpr; w += NT) {
-                const int j = w / gpr, i4 = (w - j * gpr) * 4;
-                *reinterpret_cast<u32*>(Mt + (size_t)j * rowsP + i0 + i4) = *reinterpret_cast<const u32*>(tile + j * ldT + i4);
+                const int j = w / gpr, i16 = (w - j * gpr) * 16;
+                const u32* src = reinterpret_cast<const u32*>(tile + j * ldT + i16);
+                *reinterpret_cast<uint4*>(Mt + (size_t)j * rowsP + i0 + i16) = make_uint4(src[0], src[1], src[2], src[3]);
             }
         }
     }
@@ -278,17 +370,22 @@ __global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
 
 // max_tf: the most lookups any (task, field) of the wave has in one set; max_rows: the most samples any
 // counted task has in one set
-template <int NT>
+// LDS of a launch: what the largest (task, field) needs for one tile of as many rows as NT threads take
+static size_t pc_lds_need(int NT, int HBITS, int n_max, int max_rows, int max_tile_rows) {
+    const int P = pad64(max_rows > 0 ? max_rows : 1);
+    const int R = std::max(32, std::min({P, max_tile_rows, NT * 64 / P / 32 * 32}));
+    return 6 * (size_t)n_max + std::max(pc_tile_bytes(R, P, 1 << HBITS), (size_t)n_max) + 64;   // (a mark per row to begin with)
+}
+static int pc_n_max(int max_tf) { return (max_tf + 7) / 8 * 8 + 8; }
+
+template <int NT, int HBITS>
 static void launch_pair_count_nt(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int max_rows) {
-    a.n_max = (max_tf + 7) / 8 * 8 + 8;
-    // LDS: what the largest (task, field) needs for one tile of all its rows, or all there is
-    const size_t P = (size_t)pad64(max_rows > 0 ? max_rows : 1);
-    const size_t R = P < (size_t)a.max_tile_rows ? P : (size_t)a.max_tile_rows;
-    size_t need = 6 * (size_t)a.n_max + P * (R + 4) + (R + P) * PC_HBS + 64;
-    if (need > PAIR_LDS_BYTES) need = PAIR_LDS_BYTES;
+    a.n_max = pc_n_max(max_tf);
+    const size_t need = std::min<size_t>(pc_lds_need(NT, HBITS, a.n_max, max_rows, a.max_tile_rows), PAIR_LDS_BYTES);
     a.lds_bytes = (int)(need / 16 * 16);
-    (void)hipFuncSetAttribute((const void*)pair_count_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, PAIR_LDS_BYTES);
-    hipLaunchKernelGGL(pair_count_kernel<NT>, dim3(a.F, Tw, 2), dim3(NT), (size_t)a.lds_bytes, st, a);
+    auto kern = pair_count_kernel<NT, HBITS>;
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PAIR_LDS_BYTES);
+    hipLaunchKernelGGL(kern, dim3(a.F, Tw, 2), dim3(NT), (size_t)a.lds_bytes, st, a);
 }
 
 // max_rows / min_rows: the most / fewest samples any counted task has in one set (the larger of its two sets)
@@ -296,17 +393,24 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
     if (Tw <= 0 || a.F <= 0) return;
     a.max_tile_rows = max_tile_rows > 0 ? (max_tile_rows + 31) / 32 * 32 : 1 << 20;
     a.small_n = PC_SMALL_N;
+    // Eight waves where a compute unit's LDS then holds two workgroups, whose phases hide each other's latency; else sixteen,
+    // which take twice the rows a tile.
+    auto larger = [&]() {
+        if (max_rows > 512) launch_pair_count_nt<1024, 5>(st, a, Tw, max_tf, max_rows);   // (a bag's number takes ten bits)
+        else if (pc_lds_need(512, 6, pc_n_max(max_tf), max_rows, a.max_tile_rows) <= PC_TWO_LDS) launch_pair_count_nt<512, 6>(st, a, Tw, max_tf, max_rows);
+        else launch_pair_count_nt<1024, 6>(st, a, Tw, max_tf, max_rows);
+    };
     if (max_rows <= PC_SMALL_ROWS && max_tf <= PC_SMALL_N) {   // every task is small
         a.cls = 0;
-        launch_pair_count_nt<256>(st, a, Tw, max_tf, max_rows);
+        launch_pair_count_nt<256, 6>(st, a, Tw, max_tf, max_rows);
     } else if (max_rows > 2 * PC_SMALL_ROWS && min_rows <= PC_SMALL_ROWS && (int64_t)Tw * a.F >= 32) {   // uneven: two launches, each workgroup checks its class
         a.cls = 1;
-        launch_pair_count_nt<256>(st, a, Tw, max_tf < PC_SMALL_N ? max_tf : PC_SMALL_N, PC_SMALL_ROWS);
+        launch_pair_count_nt<256, 6>(st, a, Tw, max_tf < PC_SMALL_N ? max_tf : PC_SMALL_N, PC_SMALL_ROWS);
         a.cls = 2;
-        launch_pair_count_nt<1024>(st, a, Tw, max_tf, max_rows);
+        larger();
     } else {
         a.cls = 0;
-        launch_pair_count_nt<1024>(st, a, Tw, max_tf, max_rows);
+        larger();
     }
 }
 

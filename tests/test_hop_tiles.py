@@ -53,3 +53,18 @@ def test_runs_of_fields(gm, tasks, fields):  # noqa: F811
     ctx.configure("row_path", 2)
     _compare_step(cfg, ctx, sup, qry, params, 2, 2, TOL_FP32, f"{tasks} tasks x {fields} fields")
     ctx.close()
+
+
+@pytest.mark.parametrize("rows,samples,bag,zipf", [(64, 120, 8, 0.0), (65, 200, 6, 0.0), (130, 256, 9, 0.0), (129, 300, 9, 0.0), (700, 512, 12, 1.05),
+                                                   (5000, 250, 20, 0.6), (33, 700, 3, 0.0)])
+@pytest.mark.parametrize("K", [1, 2])
+def test_batches_of_hot_rows(gm, rows, samples, bag, zipf, K):  # noqa: F811
+    """Rows that both sets look up often: one batch of the counting kernel exactly full, one row over, several batches and tiles
+    of out-rows, more distinct rows than a workgroup has threads, sets of more than 512 samples."""
+    cfg = small_cfg(n_tasks=3, n_fields=2, emb_dim=32, rows_per_field=rows, n_support=samples, n_query=samples - 30, bag_max=bag, zipf_s=zipf,
+                    layer_dims=(2 * 32 + 5, 24, 1))
+    sup, qry, params = _inputs(cfg, emb_std=0.3)
+    ctx = gm.from_config(cfg, workspace_bytes=1 << 29)
+    ctx.configure("row_path", 2)
+    _compare_step(cfg, ctx, sup, qry, params, K, 2, TOL_FP32, f"{rows} rows, {samples} samples, bags of {bag}")
+    ctx.close()
