@@ -102,3 +102,54 @@ def test_group_batch_op_bit_exact(case):
     _same(got_s.numpy(), ref_s)
     _same(got_q.numpy(), ref_q)
     ctx.close()
+
+
+def _numpy_groups(F, st, num, den):
+    """The same sets by sorting: (task, batch) ascending, stream order inside a batch, the first ceil(n num / den) to the support."""
+    order = np.lexsort((np.arange(len(st["task"])), st["batch_id"], st["task"]))
+    key = np.stack([st["task"][order], st["batch_id"][order]])
+    head = np.flatnonzero(np.concatenate([[True], (key[:, 1:] != key[:, :-1]).any(axis=0)])) if len(order) else np.zeros(0, np.int64)
+    m = np.diff(np.concatenate([head, [len(order)]]))
+    k = -(-m * num // den)
+    rank = np.arange(len(order)) - np.repeat(head, m)
+    is_sup = rank < np.repeat(k, m)
+    out = []
+    for sel, sizes in ((is_sup, k), (~is_sup, m - k)):
+        p = order[sel]
+        lens = np.diff(st["bag_offsets"]).reshape(-1, F)[p].reshape(-1)
+        starts = st["bag_offsets"][:-1].reshape(-1, F)[p].reshape(-1)
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        idx = st["indices"][np.repeat(starts - off[:-1], lens) + np.arange(off[-1])]
+        out.append(dict(task_offsets=np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64), bag_offsets=off, indices=idx,
+                        dense=st["dense"][p], labels=st["labels"][p]))
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,tasks,batches,t_lo,b_lo,num,den", [
+    (32767, 37, 2, 0, 0, 1, 2), (32768, 37, 2, 0, 0, 1, 2), (40011, 700, 3, 4093, -2, 2, 3),      # host / device order; numbers across a power of two, below zero
+    (33000, 1, 1, 5, 9, 1, 2), (50000, 4096, 2, -4096, 1 << 40, 1, 3),                             # one batch; all 13 bits
+    (9000, 9000, 1, 0, 0, 1, 2), (10000, 50, 2, -(1 << 62), 0, 0, 1), (30, 4, 2, 100, 7, 1, 1)])  # more bits; no support set; no query set
+@pytest.mark.parametrize("room", ["all", "no_sort", "one_set"])
+def test_orders_on_host_and_device(n, tasks, batches, t_lo, b_lo, num, den, room):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2401_04338_amd import GMeta
+    rng = np.random.default_rng(n + tasks)
+    F, cfg = 2, small_cfg(n_fields=2)
+    lens = rng.integers(0, 4, size=n * F)
+    st = dict(task=t_lo + rng.integers(0, tasks, size=n), batch_id=b_lo + rng.integers(0, batches, size=n),
+              bag_offsets=np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), indices=rng.integers(0, 40, size=lens.sum()).astype(np.int32),
+              dense=rng.standard_normal((n, cfg.n_dense)).astype(np.float32), labels=rng.integers(0, 2, size=n).astype(np.float32))
+    # what both sets need is 4 n (1 + F) and small scan buffers; 64 KiB hold neither them nor the sort from 9000 records on
+    ws = {"all": 1 << 26, "no_sort": 4 * n * (1 + F) + (96 << 10), "one_set": 4 * n * (1 + F) - (n // 2)}[room]
+    ctx = GMeta.from_config(cfg, workspace_bytes=max(ws, 1 << 16))
+    dev = ctx.device
+    try:
+        got = ctx.group_batch(st["task"], st["batch_id"], *(torch.from_numpy(st[k]).to(dev) for k in ("bag_offsets", "indices", "dense", "labels")), num, den)
+    except Exception as e:   # a set of its own may not fit the smallest workspace (all records in one set)
+        assert room == "one_set" and num in (0, den) and "workspace" in str(e)
+        return
+    for g, want in zip(got, _numpy_groups(F, st, num, den)):
+        _same(g.numpy(), want)
+    ctx.close()
