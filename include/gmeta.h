@@ -276,6 +276,12 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               second-order chain anyway): no per-task fp32 copy of a weight matrix is written or read; 0 = every
  *               step updates a per-task fp32 master (theta_{k+1} = theta_k - alpha * gradient_k).  The same values up
  *               to fp32 rounding before the bf16 operand copy is taken.
+ *   "chain_factors": bf16 operands, second order: the chain's direction on a task's hidden layers (the query gradient, less
+ *               alpha times a Hessian-vector product per step) is a sum of products of the passes' inputs and deltas over the
+ *               task's rows: 0 (default) = written as a matrix per task, or, where tasks are small (row tiles of 64, up to
+ *               four inner steps) and that costs less, kept as these factors and multiplied with them; 1 = always matrices;
+ *               2 = factors wherever they can be.  The factors' path does not round the direction to bf16 (the thin products
+ *               keep 16 significant bits) and adds its part of the meta-gradient over runs of tasks.
  *   "coarse_groups": number of runs of consecutive tasks for those products: 0 (default) = 16, or, when the first
  *               layer's product takes the wide tiles, the count in [12, 16] whose tiles fill the device's last round
  *               best; 1..32 = that many.  Another grouping adds the same per-task terms in another order

@@ -71,7 +71,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
     const float* Cin = has_cin ? a.Cin + (int64_t)g * a.gCin : nullptr;
     float* Cf = fl.cf ? a.Cf + (int64_t)g * a.gCf + r0 * a.rCf : nullptr;
     float* Cacc = has_acc ? a.Cacc + r0 * a.rCacc : nullptr;
-    bf16_t* Cb = fl.cb ? a.Cb + (int64_t)g * a.gCb + r0 * a.rCb : nullptr;
+    bf16_t* Cb = fl.cb ? a.Cb + (int64_t)g * a.gCb + r0 * a.rCb + (fl.epi == EPI_SPLIT ? (int64_t)blockIdx.y * a.ext.slot : 0) : nullptr;
     constexpr int SW = NI * 32, ELD = SW + 4;      // strip width, LDS row stride (floats)
     constexpr int LPR = SW / 4, RPI = 64 / LPR;    // lanes per strip row, rows per pass
     float* E = reinterpret_cast<float*>(smem) + wave * (32 * ELD);
@@ -140,11 +140,21 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
                 *reinterpret_cast<float4*>(Cacc + (int64_t)m * a.ldcacc + n) =
                     make_float4(ci.x + a.cacc * x.x, ci.y + a.cacc * x.y, ci.z + a.cacc * x.z, ci.w + a.cacc * x.w);
             }
+            if (fl.epi == EPI_SPLIT) {
+                const float c = a.ext.c[blockIdx.y];
+                x = make_float4(c * x.x, c * x.y, c * x.z, c * x.w);
+            }
             if (fl.cb) {
                 uint2 pk;
                 pk.x = f2bf2(x.x, x.y);
                 pk.y = f2bf2(x.z, x.w);
                 *reinterpret_cast<uint2*>(Cb + (int64_t)m * a.ldcb + n) = pk;
+                if (fl.epi == EPI_SPLIT) {
+                    uint2 lo;
+                    lo.x = f2bf2(x.x - bf2f((bf16_t)(pk.x & 0xffffu)), x.y - bf2f((bf16_t)(pk.x >> 16)));
+                    lo.y = f2bf2(x.z - bf2f((bf16_t)(pk.y & 0xffffu)), x.w - bf2f((bf16_t)(pk.y >> 16)));
+                    *reinterpret_cast<uint2*>(Cb + (int64_t)m * a.ldcb + a.ext.ld + n) = lo;
+                }
             }
         }
         asm volatile("" ::: "memory");   // (no block barrier: it would also wait for the strip's global stores to land)
@@ -163,49 +173,25 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
 // there: what they write is the bound, and wider stores of a wave help) 532 -> 496; 3 tasks of 512 rows, 4109-1024-512-256,
 // 64-row tiles: forward 47 -> 26 us a layer.
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, int n_ntiles, int mt_per_group, int n_tiles) {
+// One product of a sum: its operands from the tile's first row (or, contraction-slowest, from the group's first row) on, row
+// strides in bytes, contraction length.  on false: nothing is read.
+struct GemmOp {
+    const bf16_t *A, *B;
+    u32 la, lb;
+    int K;
+    bool on;
+};
+// acc += the products open(0), open(1), .. of the tile at (m0, n0) of an M x N result, n_kt tiles of 64 contraction values in all.
+template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, class Open>
+__device__ __forceinline__ void gemm_tiles(f32x16 (&acc)[BM / (32 * WM)][BN / (32 * WN)], bf16_t* smem, int M, int N, int m0, int n0, int n_kt, Open&& open) {
     constexpr int NT = WM * WN * 64;                          // threads
     constexpr int MI = BM / (32 * WM), NI = BN / (32 * WN);   // 32x32 blocks per wave in each direction
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
     constexpr int LDA_K = BM + GPADK, LDB_K = BN + GPADK;  // LDS row strides of contraction-slowest tiles [GK][BM] and [GK][BN]
     constexpr int A_ELEMS = KA ? GK * LDA_K : BM * GLD;    // LDS elements of the A tile; the B tile follows
     constexpr int TILE = A_ELEMS + (KB ? GK * LDB_K : BN * GLD);
-
-    // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Re-number them so that
-    // consecutive tiles -- the n-tiles of one row block, then the next row block of the same task, which
-    // read the same rows and the same weights -- run on the same XCD.
-    const int per_xcd = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile >= n_tiles) return;
-    const int ntile = tile % n_ntiles;
-    const int mtile = tile / n_ntiles;
-    int g, m0;
-    if (a.tile_group) {
-        g = a.tile_group[mtile];
-        m0 = a.tile_m0[mtile];
-    } else {
-        g = mtile / mt_per_group;
-        m0 = (mtile % mt_per_group) * BM;
-    }
-    const int64_t r0 = a.row_offsets[g];
-    const int rows_g = (int)(a.row_offsets[g + 1] - r0);
-    const int M = a.M < 0 ? rows_g : a.M;
-    const int K = a.K < 0 ? rows_g : a.K;
-    const int N = a.N;
-    const int n0 = ntile * BN;
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
     const int l32 = lane & 31, lhi = lane >> 5;
-
-    f32x16 acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     // global -> register staging: 16-byte chunks, 8 chunks per tile row
     constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;  // chunks per thread
@@ -215,52 +201,44 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, in
     const int crow = tid >> 3, ccol = (tid & 7) * 8;     // chunk c = tid + NT*i: row = crow + CR*i, k = ccol
     const int arow = tid / (BM / 8), acol = (tid % (BM / 8)) * 8, brow = tid / (BN / 8), bcol = (tid % (BN / 8)) * 8;
 
-    const int n_kt = (K + GK - 1) / GK * a.n_pairs;
     // Operand tiles come through buffer loads: what lies outside the operand reads as zero without a branch, also whole tiles
     // past the last one.  (The tile's first row is in the base address: offsets stay far below 32 bits.)
     const u32 OOB = 1u << 30;    // (beyond any tile: a tile's 256 rows of less than 2^21 columns; row steps added to it stay below 2^31)
     // (the product's operands are taken from the arguments once per product: a scalar load in every tile is a wait in every tile)
     int pr = -1, k0 = 0;         // product and contraction offset of the next tile to be requested
-    const bf16_t *A = nullptr, *B = nullptr;
-    u32 la = 0, lb = 0;
+    GemmOp op;
     int left_a = 0, left_b = 0;  // rows of the operand from its base on
     auto open_product = [&]() {
-        const bool on = ++pr < a.n_pairs;
-        const int p = on ? pr : 0;
-        const int64_t lda = a.lda[p], ldb = a.ldb[p];
-        A = a.A[p] + (int64_t)g * a.gA[p] + r0 * a.rA[p] + (KA ? 0 : (int64_t)m0 * lda);
-        B = a.B[p] + (int64_t)g * a.gB[p] + r0 * a.rB[p] + (KB ? 0 : (int64_t)n0 * ldb);
-        la = (u32)lda * 2u;
-        lb = (u32)ldb * 2u;
-        left_a = on ? (KA ? K : min(M - m0, BM)) : 0;
-        left_b = on ? (KB ? K : min(N - n0, BN)) : 0;
+        op = open(++pr);
+        left_a = op.on ? (KA ? op.K : min(M - m0, BM)) : 0;
+        left_b = op.on ? (KB ? op.K : min(N - n0, BN)) : 0;
         k0 = 0;
     };
     open_product();
     auto load_tile = [&](u32x4 (&da)[CA], u32x4 (&db)[CB]) {
-        const __amdgpu_buffer_rsrc_t qa = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)((u32)(KA ? min(left_a, GK) : left_a) * la), 0x00020000);
-        const __amdgpu_buffer_rsrc_t qb = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)((u32)(KB ? min(left_b, GK) : left_b) * lb), 0x00020000);
-        const bool kok = k0 + ccol < K;
+        const __amdgpu_buffer_rsrc_t qa = __builtin_amdgcn_make_buffer_rsrc((void*)op.A, 0, (int)((u32)(KA ? min(left_a, GK) : left_a) * op.la), 0x00020000);
+        const __amdgpu_buffer_rsrc_t qb = __builtin_amdgcn_make_buffer_rsrc((void*)op.B, 0, (int)((u32)(KB ? min(left_b, GK) : left_b) * op.lb), 0x00020000);
+        const bool kok = k0 + ccol < op.K;
         {
             const bool ok = KA ? m0 + acol < M : kok;
-            const u32 o = !ok ? OOB : KA ? (u32)arow * la + (u32)(m0 + acol) * 2u : (u32)crow * la + (u32)(k0 + ccol) * 2u;
+            const u32 o = !ok ? OOB : KA ? (u32)arow * op.la + (u32)(m0 + acol) * 2u : (u32)crow * op.la + (u32)(k0 + ccol) * 2u;
 #pragma unroll
-            for (int i = 0; i < CA; ++i) da[i] = __builtin_amdgcn_raw_buffer_load_b128(qa, (int)(o + (u32)((KA ? RA : CR) * i) * la), 0, 0);
+            for (int i = 0; i < CA; ++i) da[i] = __builtin_amdgcn_raw_buffer_load_b128(qa, (int)(o + (u32)((KA ? RA : CR) * i) * op.la), 0, 0);
         }
         {
             const bool ok = KB ? n0 + bcol < N : kok;
-            const u32 o = !ok ? OOB : KB ? (u32)brow * lb + (u32)(n0 + bcol) * 2u : (u32)crow * lb + (u32)(k0 + ccol) * 2u;
+            const u32 o = !ok ? OOB : KB ? (u32)brow * op.lb + (u32)(n0 + bcol) * 2u : (u32)crow * op.lb + (u32)(k0 + ccol) * 2u;
 #pragma unroll
-            for (int i = 0; i < CB; ++i) db[i] = __builtin_amdgcn_raw_buffer_load_b128(qb, (int)(o + (u32)((KB ? RB : CR) * i) * lb), 0, 0);
+            for (int i = 0; i < CB; ++i) db[i] = __builtin_amdgcn_raw_buffer_load_b128(qb, (int)(o + (u32)((KB ? RB : CR) * i) * op.lb), 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);   // (tiles are requested in the order they are waited for)
         k0 += GK;
-        if (k0 >= K) {
+        if (k0 >= op.K) {
             open_product();
         } else {
             // (never negative: past the last product nothing is left, however many tiles are asked for)
-            if constexpr (KA) { A += (u64)GK * (la / 2u); left_a = max(left_a - GK, 0); }
-            if constexpr (KB) { B += (u64)GK * (lb / 2u); left_b = max(left_b - GK, 0); }
+            if constexpr (KA) { op.A += (u64)GK * (op.la / 2u); left_a = max(left_a - GK, 0); }
+            if constexpr (KB) { op.B += (u64)GK * (op.lb / 2u); left_b = max(left_b - GK, 0); }
         }
     };
     auto store_tile = [&](bf16_t* stage, const u32x4 (&da)[CA], const u32x4 (&db)[CB]) {
@@ -333,7 +311,76 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, in
             compute(stage);
         }
     }
+}
+
+// XT: the products of the argument's `ext` list are added to the ordinary ones (see GemmExt).
+template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP, bool XT>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, int n_ntiles, int mt_per_group, int n_tiles) {
+    constexpr int MI = BM / (32 * WM), NI = BN / (32 * WN);   // 32x32 blocks per wave in each direction
+    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+
+    // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Re-number them so that
+    // consecutive tiles -- the n-tiles of one row block, then the next row block of the same task, which
+    // read the same rows and the same weights -- run on the same XCD.
+    const int per_xcd = gridDim.x >> 3;
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= n_tiles) return;
+    const int ntile = tile % n_ntiles;
+    const int mtile = tile / n_ntiles;
+    int g, m0;
+    if (a.tile_group) {
+        g = a.tile_group[mtile];
+        m0 = a.tile_m0[mtile];
+    } else {
+        g = mtile / mt_per_group;
+        m0 = (mtile % mt_per_group) * BM;
+    }
+    const int64_t r0 = a.row_offsets[g];
+    const int rows_g = (int)(a.row_offsets[g + 1] - r0);
+    const int M = a.M < 0 ? rows_g : a.M;
+    const int K = a.K < 0 ? rows_g : a.K;
+    constexpr bool SPLIT = EP == (EPI_SPLIT | EP_CB);   // the columns are rows of B, those of the group in another set
+    const int e = SPLIT ? (int)blockIdx.y : 0;
+    const int64_t r0b = SPLIT ? a.ext.rows[e][g] : r0;
+    const int N = SPLIT ? (int)(a.ext.rows[e][g + 1] - r0b) : a.N;
+    const int n0 = ntile * BN;
+    if (SPLIT && n0 >= N) return;
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    // (not __syncthreads: that would also wait for the tiles on their way)
+    auto barrier = [&]() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    gemm_tiles<BM, BN, WM, WN, DEPTH, NS, KA, KB>(acc, smem, M, N, m0, n0, (K + GK - 1) / GK * a.n_pairs, [&](int pr) {
+        const bool on = pr < a.n_pairs;
+        const int p = on ? pr : 0;
+        const int64_t lda = a.lda[p], ldb = a.ldb[p];
+        return GemmOp{a.A[p] + (int64_t)g * a.gA[p] + r0 * a.rA[p] + (KA ? 0 : (int64_t)m0 * lda),
+                      (SPLIT ? a.ext.Q[e] : a.B[p] + (int64_t)g * a.gB[p]) + r0b * a.rB[p] + (KB ? 0 : (int64_t)n0 * ldb), (u32)lda * 2u, (u32)ldb * 2u, K, on};
+    });
     barrier();   // every wave is done with the operand tiles
+    if constexpr (XT) {
+        const GemmExt& x = a.ext;
+        int n_kt = 0;
+        for (int e = 0; e < x.n; ++e) n_kt += 2 * ((x.rows[e][g + 1] - x.rows[e][g] + GK - 1) / GK);
+        gemm_tiles<BM, BN, WM, WN, DEPTH, NS, false, true>(acc, smem, M, N, m0, n0, n_kt, [&](int pr) {
+            const bool on = pr < 2 * x.n;
+            const int e = on ? pr >> 1 : 0;
+            const int64_t f0 = x.rows[e][g];
+            return GemmOp{x.S[e] + (r0 + m0) * 2 * x.ld + (pr & 1) * x.ld, x.Q[e] + f0 * x.ldq, (u32)x.ld * 4u, (u32)x.ldq * 2u, (int)(x.rows[e][g + 1] - f0), on};
+        });
+        barrier();
+    }
 
     gemm_epilogue<BM, BN, MI, NI, EP>(a, acc, smem, g, r0, m0, n0, M, N, wm0, wn0, lane, wave);
 }
@@ -567,7 +614,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_pipe_kernel(GemmBArgs a, int n_
 }
 
 static void tile_counts(const GemmBArgs& a, int BM, int BN, int& n_ntiles, int& mt_per_group, int64_t& n_tiles) {
-    n_ntiles = (a.N + BN - 1) / BN;
+    n_ntiles = ((a.N < 0 ? a.most_n : a.N) + BN - 1) / BN;
     int64_t n_mtiles;
     mt_per_group = 1;
     if (a.tile_group) {
@@ -593,28 +640,31 @@ static void launch_pipe(hipStream_t st, const GemmBArgs& a) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
 }
 
-template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP>
+template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP, bool XT = false>
 static void launch_variant(hipStream_t st, const GemmBArgs& a) {
     int n_ntiles, mt_per_group;
     int64_t n_tiles;
     tile_counts(a, BM, BN, n_ntiles, mt_per_group, n_tiles);
     if (n_tiles <= 0) return;
-    size_t shmem = ((KA ? (size_t)GK * (BM + GPADK) : (size_t)BM * GLD) + (KB ? (size_t)GK * (BN + GPADK) : (size_t)BN * GLD)) * sizeof(bf16_t) * NS;
+    size_t shmem = ((KA ? (size_t)GK * (BM + GPADK) : (size_t)BM * GLD) + (KB || XT ? (size_t)GK * (BN + GPADK) : (size_t)BN * GLD)) * sizeof(bf16_t) * NS;
     const size_t epi = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);  // the epilogue's strips, one per wave
     if (shmem < epi) shmem = epi;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, DEPTH, NS, KA, KB, EP>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, DEPTH, NS, KA, KB, EP, XT>;
     if (shmem > 48 * 1024) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WM * WN), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
+    hipLaunchKernelGGL(kern, dim3(grid, a.epi == EPI_SPLIT ? a.ext.n : 1), dim3(64 * WM * WN), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
 }
 
 // Tile shapes of one operand form.  bm: row tile the caller built its (tile_group, tile_m0) lists for (64, 128 or
-// 256); bn: 128, or 256 (with bm = 256: the pipelined 256 x 256 kernel).  64-row tiles keep two tiles on their way and two LDS
+// 256); bn: 128, or 256 (with bm = 256: the pipelined 256 x 256 kernel).  With further products (a.ext: many small tasks) one tile on
+// its way and one stage leave room for more workgroups (700 tasks of a median 32 rows: a forward launch 424 -> 410 us, their thin
+// products 227 -> 208); other 64-row tiles keep two tiles on their way and two LDS
 // stages (3 tasks of 512 rows: a layer's forward 23.1 us, with four tiles and four waves 24.9); for the others one of each
 // leaves room for more workgroups (512 tasks of 256 rows: a backward launch 387 us, 518 with two tiles on their way).
 template <bool KB, int EP>
 static void launch_rows_form(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
-    if (bm == 256 && bn == 256) launch_pipe<false, KB, EP>(st, a);
+    if (a.ext.n > 0) launch_variant<64, 128, 2, 4, 1, 1, false, KB, EP, true>(st, a);   // (bm is 64)
+    else if (bm == 256 && bn == 256) launch_pipe<false, KB, EP>(st, a);
     else if (bm == 256) launch_variant<256, 128, 4, 2, 1, 1, false, KB, EP>(st, a);
     else if (bm == 128) launch_variant<128, 128, 2, 4, 1, 1, false, KB, EP>(st, a);
     else launch_variant<64, 128, 2, 4, 2, 2, false, KB, EP>(st, a);
@@ -627,6 +677,7 @@ void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
         case EPI_NONE | EP_CF: launch_rows_form<false, EPI_NONE | EP_CF>(st, a, bm, bn); break;
         case EPI_NONE | EP_CF | EP_CACC: launch_rows_form<false, EPI_NONE | EP_CF | EP_CACC>(st, a, bm, bn); break;
         case EPI_NONE | EP_CACC: launch_rows_form<false, EPI_NONE | EP_CACC>(st, a, bm, bn); break;
+        case EPI_SPLIT | EP_CB: launch_variant<64, 64, 2, 2, 1, 1, false, false, EPI_SPLIT | EP_CB>(st, a); break;
         default: launch_rows_form<false, EP_RUNTIME>(st, a, bm, bn); break;
     }
 }

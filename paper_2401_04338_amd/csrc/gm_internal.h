@@ -264,7 +264,7 @@ void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows
                         int64_t n_rows, float scale);
 
 // ------------------------------------------------------------------ MLP kernels
-enum { EPI_NONE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_MASK = 2, EPI_MASK = 3, EPI_AXPBY = 4 };
+enum { EPI_NONE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_MASK = 2, EPI_MASK = 3, EPI_AXPBY = 4, EPI_SPLIT = 5 };   // SPLIT: c1 * value as bf16, and what that leaves as another
 
 struct GemmArgs {
     // up to two products accumulated: C = A1*B1 (+ A2*B2)
@@ -296,6 +296,18 @@ void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n);   // b
 
 // bf16 operands, both stored contraction-contiguous: C[M,N] = sum_p A_p[M,K] * Bt_p[N,K]^T
 #define GEMM_MAX_PAIRS 4   // products accumulated into one output (the pipelined kernel takes at most two)
+// Further products of a sum: S_e * Q_e, contracted over the rows that the group has in a set (`rows`): S_e [rows of the result,
+// 2 * ld], the rows' upper parts, then at column ld their lower parts; Q_e [rows of the set, ldq].
+// With EPI_SPLIT: the products that make them, one for every entry: c_e * A * Q_e^T, the columns being the group's rows of that
+// set, goes to Cb + e * slot.
+enum { GEMM_EXT = 7 };
+struct GemmExt {
+    int n;
+    const bf16_t *S[GEMM_EXT], *Q[GEMM_EXT];
+    const int32_t* rows[GEMM_EXT];
+    float c[GEMM_EXT];
+    int64_t ld, ldq, slot;
+};
 struct GemmBArgs {
     const bf16_t* A[GEMM_MAX_PAIRS];
     const bf16_t* B[GEMM_MAX_PAIRS];
@@ -317,6 +329,8 @@ struct GemmBArgs {
     bf16_t* Cb; int64_t ldcb, gCb, rCb;    // bf16 output
     float* Cacc; int64_t ldcacc, rCacc; float cacc;  // Cacc[(r0 + m)*ldcacc + n] += cacc * value (not with EPI_AXPBY + Cin)
     int cacc_init;                                   // 1: Cacc is not read, = cacc * value (first term of a sum)
+    int most_n;                            // N -1 (EPI_SPLIT): most columns of a product
+    GemmExt ext;                           // (64-row tiles only)
 };
 void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn = 128);   // bn = 256 (with bm = 256): the pipelined 256 x 256 kernel
 // same product with both operands stored contraction-slowest: A_p element (k, m) at A + g*gA + r0*rA + k*lda + m,

@@ -82,6 +82,7 @@ struct gm_ctx {
     int adapt_rows = 1;   // 0: the inner loop adapts the dense parameters only (embedding rows are read, not updated)
     int gemm_tile_n = 0;
     int wgrad_wide = 1;      // weight gradients over runs of tasks in 256 x 256 tiles where the shape allows
+    int chain_factors = 0;   // the second-order chain's direction on a task's hidden layers: 0 by size, 1 matrices, 2 factors where they can be (see factor_rows)
     int theta_from_meta = 1; // bf16, second order, several inner steps: a step's weights from theta and all steps' gradients
     int coarse_groups = 0;   // runs of tasks for the products only summed over tasks (0: chosen by shape)
     int n_cus = 256;
@@ -228,11 +229,30 @@ struct Act {  // one activation-shaped buffer [rows, ld] in the type(s) the GEMM
     bf16_t* b = nullptr;   // bf16 mode: [rows, ld]
     int ld = 0;
 };
+// The second-order chain's direction on the hidden layers' weights, for small tasks, as what it is made of: c * P^T Q of some
+// passes over the task's rows, P a pass's inputs of the layer and Q its deltas.  X * V is then the sum of c * (X P^T) Q, two thin
+// products contracted over the task's rows (the first kept as two bf16 parts, 16 significant bits; V itself would be rounded
+// to 8), and no task's direction is written, rounded, read or summed: with a few dozen rows a task that traffic was half a step.
+// (The weights theta' themselves stay matrices: their bf16 rounding decides ReLU gates.)
+struct Factor {
+    const Act* X;                       // P of layer 1 (null: none)
+    const std::vector<Act>*A, *D;       // P of layer l > 1: A[l - 1]; Q: D[l]
+    bool query;                         // whose rows
+    float c;
+};
+struct FactorRoom {                     // where the thin products' results go
+    bf16_t* S = nullptr;                // slots of [rows, 2 * ld], upper and lower parts
+    int64_t slot = 0;
+    int ld = 0;
+    const int32_t *rows_s = nullptr, *rows_q = nullptr;
+    int most_s = 0, most_q = 0;         // rows of the largest task
+};
 struct Theta {  // parameters as the GEMMs read them; stride 0 = shared by all tasks
     float* f = nullptr;
     int64_t sf = 0;
     bf16_t* b = nullptr;
     int64_t sb = 0;
+    const std::vector<Factor>* fac = nullptr;   // the hidden layers' weights as factors (b is null)
 };
 
 struct StepState {  // what one inner step leaves behind for the second-order pass
@@ -283,6 +303,10 @@ struct WaveBufs {
     float *dLq, *zq;
     Act TX;
     std::vector<Act> TA, TD;
+    // factors: what every step of the second-order chain leaves (TX, TA, TD of step k are TXk[k], ..)
+    std::vector<Act> TXk;
+    std::vector<std::vector<Act>> TAk, TDk;
+    FactorRoom room;
     float* tdL;
     // pair-count matrices of the wave (null when the sparse kernel does the row arithmetic)
     uint8_t* pair_mat;
@@ -306,7 +330,9 @@ struct WaveDims {
     int64_t pair_bytes = 0;
     int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of the tasks beyond HOP_SMALL (the hops' work lists)
     bool table = false;                    // the sparse gradient is reduced wave by wave into a table-shaped output
+    int factor_ld = 0;                     // > 0: the chain's direction stays factors (see Factor); rows of the largest task of the batch
 };
+static int factor_slots(int K) { return 2 * K - 1; }   // most factors of the direction: the query pass's, two of every later step
 
 static Act alloc_act(const gm_ctx* c, Arena& ar, int64_t rows, int ld) {
     Act a;
@@ -412,7 +438,8 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.TXf = (second && bf) ? ar.get<float>(d.Ps * ld0) : nullptr;
     w.dX = ar.get<float>(std::max(d.Ps, d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
     w.loss_q = ar.get<float>(d.Pq + 1);
-    w.v = alloc_theta(c, ar, d.Tw, true);
+    const bool factors = d.factor_ld > 0;
+    w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
     w.vsum = Theta{ar.get<float>((int64_t)std::max(16, c->coarse_groups) * c->n_theta), c->n_theta, nullptr, 0};
     if (!second) w.v.b = nullptr;  // the direction is a GEMM operand only in the second-order pass
     w.Xs_scratch = Act();
@@ -469,6 +496,22 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
             w.TD[l] = alloc_act(c, ar, d.Ps, c->ld[l]);
         }
         w.tdL = ar.get<float>(d.Ps + 1);
+    }
+    w.TXk.clear(); w.TAk.clear(); w.TDk.clear();
+    if (factors) {
+        for (int k = 0; k < K; ++k) {   // (the last step's are the ones above)
+            if (k == K - 1) { w.TXk.push_back(w.TX); w.TAk.push_back(w.TA); w.TDk.push_back(w.TD); break; }
+            w.TXk.push_back(alloc_act(c, ar, d.Ps, ld0));
+            w.TAk.emplace_back(L);
+            w.TDk.emplace_back(L);
+            for (int l = 1; l < L; ++l) {
+                w.TAk[k][l] = alloc_act(c, ar, d.Ps, c->ld[l]);
+                w.TDk[k][l] = alloc_act(c, ar, d.Ps, c->ld[l]);
+            }
+        }
+        w.room.ld = round_up(d.factor_ld, 64);
+        w.room.slot = std::max(d.Ps, d.Pq) * 2 * w.room.ld;
+        w.room.S = ar.get<bf16_t>(w.room.slot * factor_slots(K) + 8);
     }
     if (d.table) {
         w.GX = ar.get<float>((d.Ps + d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
@@ -598,6 +641,11 @@ extern "C" int gm_configure(gm_ctx* c, const char* key, int64_t value) {
     if (!strcmp(key, "wgrad_wide")) {
         if (value != 0 && value != 1) return fail(c, GM_ERR_ARG, "wgrad_wide must be 0 or 1");
         c->wgrad_wide = (int)value;
+        return GM_OK;
+    }
+    if (!strcmp(key, "chain_factors")) {
+        if (value < 0 || value > 2) return fail(c, GM_ERR_ARG, "chain_factors must be 0, 1 or 2");
+        c->chain_factors = (int)value;
         return GM_OK;
     }
     if (!strcmp(key, "theta_from_meta")) {
@@ -810,7 +858,12 @@ struct Grp {  // grouping of one set's rows by task inside the wave
     int n_mtiles, G, bm;
     int64_t rows;  // padded rows of the set in the wave
     int most_rows; // of one task
+    const FactorRoom* room = nullptr;
+    bool whole = false;  // all rows as one group (the tasks have the weights in common)
 };
+// The same rows as one group for products with shared weights: tiles then run over the tasks' borders (bf16; 700 tasks of a
+// median 32 rows, a first-layer product of the first step 0.76 -> 0.27 ms; 201 tasks of 75..225 rows 0.15 -> 0.08).
+static Grp whole_group(const gm_ctx* c, const Grp& g);
 
 
 // column tile of a forward / backward product.  256 selects the pipelined 256 x 256 kernel (256-row tiles, a multiple of
@@ -823,6 +876,35 @@ static int gemm_bn(const gm_ctx* c, int bm, int N, int K) {
 }
 
 // out[rows, ld_l] = epi( sum_p in_p[rows, ld_{l-1}] * W_p,l + bias )
+// The factors of th's layer-l weights, for a product with `in` (forward: in * W, else in * W^T): the thin products with P (Q)
+// are made here, in one launch, the ones with Q (P) are added to a's list.
+static void add_factors(gm_ctx* c, const Grp& g, int l, const Act* in, const Theta* th, bool forward, GemmBArgs& a) {
+    if (!th->fac) return;
+    const FactorRoom* room = g.room;
+    GemmBArgs s;
+    memset(&s, 0, sizeof s);
+    for (const Factor& f : *th->fac) {
+        const Act *P = l == 1 ? f.X : &(*f.A)[l - 1], *Q = &(*f.D)[l];
+        if (!P) continue;
+        if (!forward) std::swap(P, Q);
+        const int e = a.ext.n++;
+        s.ext.n = a.ext.n;
+        s.ext.Q[e] = P->b; s.ext.c[e] = f.c;
+        s.ext.rows[e] = a.ext.rows[e] = f.query ? room->rows_q : room->rows_s;
+        s.most_n = std::max(s.most_n, f.query ? room->most_q : room->most_s);
+        s.ext.ldq = P->ld; a.ext.ldq = Q->ld;
+        a.ext.S[e] = room->S + e * room->slot; a.ext.Q[e] = Q->b;
+    }
+    const int W = in->ld;
+    s.row_offsets = g.row_off; s.G = g.G; s.n_pairs = 1;
+    s.A[0] = in->b; s.lda[0] = W; s.rA[0] = W; s.ldb[0] = W; s.rB[0] = W;
+    s.M = -1; s.N = -1; s.K = W;
+    s.tile_group = g.tile_g; s.tile_m0 = g.tile_m; s.n_mtiles = g.n_mtiles;
+    s.epi = EPI_SPLIT;
+    s.Cb = room->S; s.ldcb = 2 * room->ld; s.rCb = 2 * room->ld; s.ext.ld = a.ext.ld = room->ld; s.ext.slot = room->slot;
+    launch_gemm_bf16(c->stream, s, 64);
+}
+
 static void dense_nn(gm_ctx* c, const Grp& g, int l, int np, const Act* in0, const Theta* th0, const Act* in1,
                      const Theta* th1, const float* bias, int64_t bias_stride, const Act* mask, int epi, Act& out) {
     const int K = c->ld[l - 1], N = c->ld[l];
@@ -852,12 +934,16 @@ static void dense_nn(gm_ctx* c, const Grp& g, int l, int np, const Act* in0, con
     } else {
         GemmBArgs a;
         memset(&a, 0, sizeof a);
-        a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = np;
+        a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = 0;
         for (int i = 0; i < np; ++i) {   // W as stored, [d_in, d_out]: the contraction index is its slow one
-            a.A[i] = ins[i]->b; a.lda[i] = K; a.rA[i] = K;
-            a.B[i] = ths[i]->b + c->offWb[l]; a.ldb[i] = N; a.gB[i] = ths[i]->sb;
+            if (ths[i]->b) {
+                const int p = a.n_pairs++;
+                a.A[p] = ins[i]->b; a.lda[p] = K; a.rA[p] = K;
+                a.B[p] = ths[i]->b + c->offWb[l]; a.ldb[p] = N; a.gB[p] = ths[i]->sb;
+            }
+            add_factors(c, g, l, ins[i], ths[i], true, a);
         }
-        a.Cb = out.b; a.ldcb = N; a.rCb = N; a.M = -1; a.N = N; a.K = K;
+        a.Cb = out.b; a.ldcb = N; a.rCb = N; a.M = g.whole ? (int)g.rows : -1; a.N = N; a.K = K;
         a.tile_group = g.tile_g; a.tile_m0 = g.tile_m; a.n_mtiles = g.n_mtiles;
         a.epi = epi; a.bias = bias; a.gBias = bias_stride;
         if (mask) { a.mask = mask->b; a.ld_mask = mask->ld; }
@@ -902,12 +988,16 @@ static void dense_nt(gm_ctx* c, const Grp& g, int l, int np, const Act* d0, cons
     } else {
         GemmBArgs a;
         memset(&a, 0, sizeof a);
-        a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = np;
+        a.row_offsets = g.row_off; a.G = g.G; a.n_pairs = 0;
         for (int i = 0; i < np; ++i) {
-            a.A[i] = ds[i]->b; a.lda[i] = K; a.rA[i] = K;
-            a.B[i] = ths[i]->b + c->offWb[l]; a.ldb[i] = K; a.gB[i] = ths[i]->sb;
+            if (ths[i]->b) {
+                const int p = a.n_pairs++;
+                a.A[p] = ds[i]->b; a.lda[p] = K; a.rA[p] = K;
+                a.B[p] = ths[i]->b + c->offWb[l]; a.ldb[p] = K; a.gB[p] = ths[i]->sb;
+            }
+            add_factors(c, g, l, ds[i], ths[i], false, a);
         }
-        a.M = -1; a.N = N; a.K = K;
+        a.M = g.whole ? (int)g.rows : -1; a.N = N; a.K = K;
         a.tile_group = g.tile_g; a.tile_m0 = g.tile_m; a.n_mtiles = g.n_mtiles;
         if (dX) {
             if (write_dx) { a.Cf = dX; a.ldcf = N; a.rCf = N; }
@@ -918,6 +1008,21 @@ static void dense_nt(gm_ctx* c, const Grp& g, int l, int np, const Act* d0, cons
         }
         launch_gemm_bf16(c->stream, a, g.bm, gemm_bn(c, g.bm, N, K * np));
     }
+}
+
+static Grp whole_group(const gm_ctx* c, const Grp& g) {
+    int widest = c->ld[0];
+    for (int l = 1; l < c->L; ++l) widest = std::max(widest, c->ld[l]);
+    if (c->L < 2 || g.rows * widest * 2 >= ((int64_t)1 << 31)) return g;   // (an operand's offsets are 32 bits)
+    Grp w = g;
+    w.whole = true;
+    w.G = 1;
+    w.tile_g = w.tile_m = nullptr;
+    w.n_mtiles = 0;
+    w.bm = 256;
+    auto tiles = [&](int bm) { const int bn = gemm_bn(c, bm, c->ld[1], c->ld[0]); return (g.rows + bm - 1) / bm * ((c->ld[1] + bn - 1) / bn); };
+    while (w.bm > 64 && tiles(w.bm) < c->n_cus) w.bm /= 2;
+    return w;
 }
 
 // Weight gradient [M, N] of G groups over `rows` rows in all: the pipelined 256 x 256 tiles pay once the contraction of a
@@ -1050,8 +1155,9 @@ static void forward_backward(gm_ctx* c, const Grp& g, const float* labels, const
     hipStream_t st = c->stream;
     const int L = c->L;
     const Act* prev = p.X;
+    const Grp gd = c->mlp_dtype && th.sb == 0 && thf_stride == 0 ? whole_group(c, g) : g;
     for (int l = 1; l < L; ++l) {
-        dense_nn(c, g, l, 1, prev, &th, nullptr, nullptr, thf + c->offb[l], thf_stride, nullptr, EPI_BIAS_RELU, (*p.A)[l]);
+        dense_nn(c, gd, l, 1, prev, &th, nullptr, nullptr, thf + c->offb[l], thf_stride, nullptr, EPI_BIAS_RELU, (*p.A)[l]);
         prev = &(*p.A)[l];
     }
     const float* wL = thf + c->offW[L];
@@ -1075,9 +1181,9 @@ static void forward_backward(gm_ctx* c, const Grp& g, const float* labels, const
     }
     for (int l = L - 1; l >= 1; --l) {
         if (l == 1) {
-            if (dX) dense_nt(c, g, l, 1, &(*p.Dl)[l], &th, nullptr, nullptr, nullptr, nullptr, dX);
+            if (dX) dense_nt(c, gd, l, 1, &(*p.Dl)[l], &th, nullptr, nullptr, nullptr, nullptr, dX);
         } else {
-            dense_nt(c, g, l, 1, &(*p.Dl)[l], &th, nullptr, nullptr, &(*p.A)[l - 1], &(*p.Dl)[l - 1], nullptr);
+            dense_nt(c, gd, l, 1, &(*p.Dl)[l], &th, nullptr, nullptr, &(*p.A)[l - 1], &(*p.Dl)[l - 1], nullptr);
         }
     }
 }
@@ -1132,8 +1238,9 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
 // layer-1 product itself; need_dx: the tangent of dX is also wanted in w.dX (for the row arithmetic of the next step)
 // coarse (the chain's last step): the weight matrices' part of H v is not folded into every task's v but summed over
 // runs of tasks into w.vsum (unscaled); the caller adds -alpha times their sum to the reduced v
+// fold: -alpha times it is added to what w.vsum holds
 static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, float alpha, bool refresh_v_copies,
-                     float* gx_acc, bool need_dx, bool gx_init, bool tx, const Grp* coarse = nullptr) {
+                     float* gx_acc, bool need_dx, bool gx_init, bool tx, const Grp* coarse = nullptr, bool fold = false) {
     hipStream_t st = c->stream;
     const int L = c->L;
     Theta& v = w.v;
@@ -1176,8 +1283,10 @@ static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, f
         const Act* ta_prev = l == 1 ? &w.TX : &w.TA[l - 1];
         const Act* a_prev = l == 1 ? &s.X : &s.A[l - 1];
         if (coarse) {
-            if (l == 1 && !tx) dense_tn(c, *coarse, l, 1, a_prev, &w.TD[l], nullptr, nullptr, w.vsum, nullptr, 0, 0.f, 1.f, true, &later);
-            else dense_tn(c, *coarse, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], w.vsum, nullptr, 0, 0.f, 1.f, true, &later);
+            const float* in = fold ? w.vsum.f : nullptr;
+            const float c0 = fold ? 1.f : 0.f, c1 = fold ? -alpha : 1.f;
+            if (l == 1 && !tx) dense_tn(c, *coarse, l, 1, a_prev, &w.TD[l], nullptr, nullptr, w.vsum, in, w.vsum.sf, c0, c1, true, &later);
+            else dense_tn(c, *coarse, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], w.vsum, in, w.vsum.sf, c0, c1, true, &later);
         } else if (l == 1 && !tx) dense_tn(c, g, l, 1, a_prev, &w.TD[l], nullptr, nullptr, vout, v.f, nt, 1.f, -alpha, true, &later);
         else dense_tn(c, g, l, 2, ta_prev, &s.Dl[l], a_prev, &w.TD[l], vout, v.f, nt, 1.f, -alpha, true, &later);
         sums.add(c->ld[l], &w.TD[l], nullptr, nullptr, nullptr, v.f + c->offb[l], nt, v.f + c->offb[l], nt, 1.f, -alpha);
@@ -1481,6 +1590,11 @@ static SortRange whole_batch_range(const Batch& B) {
 
 static inline int64_t pad64(int64_t n) { return (n + 63) & ~(int64_t)63; }
 
+// What decides between matrices and factors of the chain's direction (factor_rows): the thin products' rate over padded sizes,
+// the matrices' over bytes, the memory-side cache, and the most rows of a task (a slot of the thin products is that wide).
+static constexpr double FACTOR_RATE = 2.5e14, MATRIX_RATE = 4.5e12, FACTOR_CACHE = 2.56e8;
+enum { FACTOR_MOST_ROWS = 2048 };
+
 // Whether a task's row arithmetic should go through pair-count matrices: the product costs
 // n_out * n_in * D per (task, field) against lookups * D for the sparse kernel, on units that are far
 // faster, so it pays while the task is moderately small.
@@ -1511,9 +1625,38 @@ static int64_t pair_layout(const gm_ctx* c, const Batch& B, const WavePlan& p, i
     return acc;
 }
 
+// Whether the chain's direction stays factors (then: rows of the batch's largest task): where the thin products cost less than
+// writing, reading and summing the matrices, and these do not stay in the memory-side cache anyway.  A rule on the whole batch,
+// so that the waves it is cut into do not change results.
+static int factor_rows(const gm_ctx* c, const Batch& B, int bm, int K, int order) {
+    if (!c->mlp_dtype || order != 2 || K < 1 || factor_slots(K) > GEMM_EXT || c->L < 2 || bm != 64 || c->chain_factors == 1) return 0;
+    double widths = 0, weights = 0;
+    for (int l = 1; l < c->L; ++l) {
+        widths += c->ld[l - 1] + c->ld[l];
+        weights += (double)c->ld[l - 1] * c->ld[l];
+    }
+    double ss = 0, sq = 0, rows = 0;
+    int most = 0;
+    for (int t = 0; t < B.T; ++t) {
+        const int64_t ns = B.poff_s[t + 1] - B.poff_s[t], nq = B.poff_q[t + 1] - B.poff_q[t];
+        most = (int)std::max<int64_t>(most, std::max(ns, nq));
+        rows += (double)std::max(ns, nq);
+        ss += (double)pad64(ns) * (double)pad64(ns);
+        sq += (double)pad64(ns) * (double)pad64(nq);
+    }
+    if (most <= 0 || most > FACTOR_MOST_ROWS) return 0;
+    if (c->chain_factors == 2) return most;
+    // (of every step: the query pass's factor and two of each later step; both directions; the second thin product has two parts)
+    const double flops = 2.0 * 3.0 * widths * (K * (K - 1) * ss + K * sq);
+    const double bytes = weights * B.T * (6.0 + 10.0 * (K - 1) + 4.0 * K + 4.0);   // written, updated, read, summed
+    const double room = rows * (4.0 * round_up(most, 64) * factor_slots(K) + 2.0 * (K - 1) * (c->ld[0] + 2.0 * widths));
+    return flops / FACTOR_RATE < bytes / MATRIX_RATE && weights * B.T * 6.0 > FACTOR_CACHE && room < 2.0 * weights * B.T ? most : 0;
+}
+
 static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, int bm, int K, int order) {
     WaveDims d;
     d.table = B.table;
+    d.factor_ld = factor_rows(c, B, bm, K, order);
     for (int t = p.t0; t < p.t1; ++t) {
         if (task_pair_ok(c, B, t, K)) {
             d.pair = true;
@@ -1926,6 +2069,13 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         const int32_t rb_s = (int32_t)wp.ps0, rb_q = (int32_t)wp.pq0;
         const bool second = order == 2 && K > 0;
 
+        const bool factors = d.factor_ld > 0;
+        if (factors) {
+            w.room.rows_s = w.row_off_s; w.room.rows_q = w.row_off_q;
+            w.room.most_s = gs.most_rows; w.room.most_q = gq.most_rows;
+            gs.room = gq.room = &w.room;
+        }
+
         // a1: one prefetch pass for both sets.  Every real row is written whole (pooled fields, dense and pad columns); only
         // the pad rows of what the row arithmetic writes real rows of are cleared.
         const bool padded = d.Ps != d.Ss || d.Pq != d.Sq;
@@ -2062,6 +2212,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         // bf16, second order, 2..GEMM_MAX_PAIRS inner steps: every step's weights straight from the meta parameters
         // and the gradients of all steps so far (their activations and deltas are kept for the chain anyway)
         const bool from_theta0 = bf && second && K >= 2 && K <= GEMM_MAX_PAIRS && c->theta_from_meta;
+        std::vector<Factor> v_fac;   // of the direction
         const float* thf0 = thf;
         std::vector<Pass> passes;
         for (int k = 0; k < K; ++k) {
@@ -2132,8 +2283,14 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         Grp gs_coarse = gs, gq_coarse = gq;
         gs_coarse.row_off = w.coarse_off_s; gs_coarse.G = n_coarse;
         gq_coarse.row_off = w.coarse_off_q; gq_coarse.G = n_coarse;
-        theta_grad(c, gq, pq, w.v, nullptr, 0, 0.f, 1.f, nullptr, true, second ? nullptr : &gq_coarse, second ? nullptr : &w.vsum,
+        // (factors: the chain's other terms are added to these sums, no task's direction is formed)
+        const bool runs_only = !second || factors;
+        theta_grad(c, gq, pq, w.v, nullptr, 0, 0.f, 1.f, nullptr, true, runs_only ? &gq_coarse : nullptr, runs_only ? &w.vsum : nullptr,
                    nullptr, nullptr, w.loss_q, task_loss + wp.t0);
+        if (factors) {
+            v_fac.push_back(Factor{&Xq, &w.Aq, &w.Dq, true, 1.f});
+            w.v.fac = &v_fac;
+        }
 
         // second-order chain back through the inner steps: v_k = v_{k+1} - alpha H_k v_{k+1}
         if (second) {
@@ -2142,6 +2299,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 if (bf) zero_bf16(st, w.TX.b, d.Ps * ld0);
                 else launch_fill_f32(st, w.TX.f, d.Ps * ld0, 0.f);
             }
+            for (int k = 0; factors && k + 1 < K; ++k) zero_bf16(st, w.TXk[k].b, d.Ps * ld0);   // (the columns and rows that no hop writes)
             if (F > 0 && adapt) {
                 // direction on the support rows = query gradient routed through the rows both sets share
                 TwoHopOut os = hop_out(true, nullptr, bf && K == 1 ? nullptr : txf, w.TX.b, 1.f);
@@ -2149,12 +2307,17 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             }
             for (int k = K - 1; k >= 0; --k) {
                 const StepState& s = w.steps[k];
+                if (factors) { w.TX = w.TXk[k]; w.TA = w.TAk[k]; w.TD = w.TDk[k]; }
                 // bf16 with hidden layers: the layer-1 product adds -alpha * dX to the gradient buffer itself
                 // (fp32 does so when nothing else reads dX)
                 const bool fused_gx = L > 1 && F > 0 && (bf || !(k > 0 && adapt));
                 // (the chain's first step starts that sum: the buffer's support rows need no clearing)
                 hvp_step(c, gs, s, w, alpha, k > 0, fused_gx ? gxs : nullptr, k > 0 && adapt, k == K - 1, adapt,
-                         k == 0 ? &gs_coarse : nullptr);
+                         k == 0 || factors ? &gs_coarse : nullptr, factors);
+                if (factors) {
+                    v_fac.push_back(Factor{adapt && F > 0 ? &w.TXk[k] : nullptr, &w.TAk[k], &s.Dl, false, -alpha});
+                    v_fac.push_back(Factor{&s.X, &s.A, &w.TDk[k], false, -alpha});
+                }
                 if (F > 0) {
                     if (!fused_gx) {
                         Prof p(c, "axpy_gx", (k == K - 1 ? 8.0 : 12.0) * d.Ps * FD, 0);
@@ -2162,7 +2325,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                         else launch_axpy(st, d.Ps * (int64_t)FD, -alpha, w.dX, gxs);
                     }
                     if (k > 0 && adapt) {
-                        TwoHopOut os = hop_out(true, txf, bf && k == 1 ? nullptr : txf, w.TX.b, -alpha);
+                        TwoHopOut os = hop_out(true, txf, bf && k == 1 ? nullptr : txf, factors ? w.TXk[k - 1].b : w.TX.b, -alpha);
                         two_hop(true, w.dX, &os, nullptr);
                     }
                 }
@@ -2171,11 +2334,11 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         // cross-task reduction of the dense part (tasks of the wave in order, waves in order).  vsum: the weight matrices'
         // part summed over runs of tasks -- the chain's last step, or (first order) all of it
         {
-            Prof p(c, "reduce_tasks", 4.0 * (second ? Tw : n_coarse) * nt, 0);
-            ReduceArgs ra{w.v.f, w.vsum.f, nt, second ? -alpha : 1.f, b.g_theta, theta_summed, 0, {}};
+            Prof p(c, "reduce_tasks", 4.0 * (runs_only ? n_coarse : Tw) * nt, 0);
+            ReduceArgs ra{w.v.f, w.vsum.f, nt, runs_only ? 1.f : -alpha, b.g_theta, theta_summed, 0, {}};
             std::vector<ReducePiece> pieces;
             for (int l = 1; l < L; ++l) {
-                pieces.push_back(ReducePiece{c->offW[l], c->offb[l] - c->offW[l], second ? Tw : 0, n_coarse, 0});
+                pieces.push_back(ReducePiece{c->offW[l], c->offb[l] - c->offW[l], runs_only ? 0 : Tw, n_coarse, 0});
                 pieces.push_back(ReducePiece{c->offb[l], c->offW[l + 1] - c->offb[l], Tw, 0, 0});
             }
             pieces.push_back(ReducePiece{c->offW[L], nt - c->offW[L], Tw, 0, 0});
