@@ -38,11 +38,10 @@ FAMILIES = {
     "reduce_tasks": r"reduce_tasks_kernel",
     "axpy_gx": r"axpy_kernel",
     "last_layer": r"last_layer_kernel",
-    # gemm_bf16_kernel<BM, BN, WM, WN, DEPTH, NS, KA, KB, EP>: which operand is read contraction-slowest tells the product's kind;
-    # gemm_bf16_pipe_kernel<KA, KB, EP, ..>: the pipelined 256 x 256 kernel, the same two flags
-    "gemm_wgrad": r"gemm_bf16_kernel<(?:\d+, ){6}true, true|gemm_bf16_pipe_kernel<true, true",
-    "gemm_fwd": r"gemm_bf16_kernel<(?:\d+, ){6}false, true|gemm_bf16_pipe_kernel<false, true",
-    "gemm_bwd": r"gemm_bf16_kernel<(?:\d+, ){6}false, false|gemm_bf16_pipe_kernel<false, false",
+    # gemm_bf16_kernel<BM, BN, WM, WN, DEPTH, NS, KA, KB, EP>: which operand is read contraction-slowest tells the product's kind
+    "gemm_wgrad": r"gemm_bf16_kernel<(?:\d+, ){6}true, true",
+    "gemm_fwd": r"gemm_bf16_kernel<(?:\d+, ){6}false, true",
+    "gemm_bwd": r"gemm_bf16_kernel<(?:\d+, ){6}false, false",
     "gemm_f32 (all launches)": r"gemm_f32_(wgrads_)?kernel",
 }
 
@@ -169,8 +168,7 @@ def mfma(a):
     for _, k, n, ma, mb, pct, ops in sorted(rows, reverse=True):
         print(f"  {k[:60]:60s} {n:10d} {ma:14.4g} {mb:16.4g} {pct:11.1f} {ops:14.4g}")
     print("# gemm_bf16_kernel<BM,BN,WM,WN,DEPTH,NS,KA,KB,EP>: KA,KB = false,true forward products; false,false backward (dA) products;")
-    print("# true,true weight gradients.  gemm_bf16_pipe_kernel<KA,KB,EP,..>: the pipelined 256 x 256 kernel, the same two flags.")
-    print("# EP encodes the fused epilogue of the launch.")
+    print("# true,true weight gradients.  EP encodes the fused epilogue of the launch.")
 
 
 def main():

@@ -51,14 +51,12 @@ struct EpiFlags {
     }
 };
 
-// Epilogue shared by the GEMM kernels.  A lane holds column l32 of each 32x32 block and rows 8*(v/4) + 4*lhi + v%4,
-// which would give 2-byte scattered stores; instead every wave passes its accumulators through LDS one 32-row strip at
-// a time, applies the fused operation on 4 consecutive columns per lane and writes whole row segments.  TRANSPOSED: the
-// accumulators were computed with the operand roles swapped (first MFMA operand = B fragment), so a lane holds ROW l32
-// and four consecutive columns per group of four registers; stored straight from the registers that is 16 bytes per
-// lane in 32 different rows per instruction, which the memory pipeline takes several times longer over than whole
-// row segments (measured on the 256 x 256 tiles: epilogue 32 -> 26 thousand cycles forward, 56 -> 33 backward).
-template <int BM, int BN, int MI, int NI, int EP, bool TRANSPOSED = false>
+// The epilogue.  The first operand of the MFMAs is the B fragment, so a lane holds ROW l32 of each 32x32 block and four
+// consecutive columns per group of four registers; stored straight from the registers that is 16 bytes per lane in 32
+// different rows per instruction, which the memory pipeline takes several times longer over than whole row segments
+// (256 x 256 tiles: 32 -> 26 thousand cycles forward, 56 -> 33 backward).  So every wave passes its accumulators through
+// LDS one 32-row strip at a time, applies the fused operation on 4 consecutive columns per lane and writes whole row segments.
+template <int BM, int BN, int MI, int NI, int EP>
 __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[MI][NI], bf16_t* smem, int g, int64_t r0, int m0,
                                               int n0, int M, int N, int wm0, int wn0, int lane, int wave) {
     const EpiFlags<EP> fl(a);
@@ -96,19 +94,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
             if (ok && has_cin) ci_all[it] = *reinterpret_cast<const float4*>(Cin + (int64_t)m * a.ldcin + n);
             if (ok && has_acc && !a.cacc_init) ci_all[it] = *reinterpret_cast<const float4*>(Cacc + (int64_t)m * a.ldcacc + n);
         }
-        if constexpr (TRANSPOSED) {   // (operand roles swapped in the MFMA: the lane holds row l32, four consecutive columns per q)
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+        for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4*>(E + l32 * ELD + j * 32 + 8 * q + 4 * lhi) =
-                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) E[(8 * (v >> 2) + 4 * lhi + (v & 3)) * ELD + j * 32 + l32] = acc[i][j][v];
-        }
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(E + l32 * ELD + j * 32 + 8 * q + 4 * lhi) =
+                    make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the strip is this wave's own: LDS order within the wave suffices
 #pragma unroll
         for (int it = 0; it < 32 / RPI; ++it) {
@@ -172,6 +163,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
 // gradient stored 398 -> 387 us, hidden layer 125 -> 116, weight gradients over runs of tasks 575 -> 452, per task (four waves
 // there: what they write is the bound, and wider stores of a wave help) 532 -> 496; 3 tasks of 512 rows, 4109-1024-512-256,
 // 64-row tiles: forward 47 -> 26 us a layer.
+//
+// 256 x 256 tiles (256 tasks of 512 rows, layers 4109-1024-512-256: the matrix cores are the bound) have a compute unit to
+// themselves, two waves a SIMD: the waves' order of instructions has to hide what other workgroups hide elsewhere (PIPE below).
+// Against four waves of 128 x 128 each with the same two stages: backward 687 -> 648 us, forward 341 -> 312 and 439 -> 423,
+// weight gradients 616 -> 549 a task, 1107 -> 1080 over runs of tasks.  Eight waves that park the next tile before the first step:
+// backward 682, weight gradients over runs 1222; parked between steps without reading ahead: 662, 1098.
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 // One product of a sum: its operands from the tile's first row (or, contraction-slowest, from the group's first row) on, row
 // strides in bytes, contraction length.  on false: nothing is read.
@@ -189,6 +186,8 @@ __device__ __forceinline__ void gemm_tiles(f32x16 (&acc)[BM / (32 * WM)][BN / (3
     constexpr int LDA_K = BM + GPADK, LDB_K = BN + GPADK;  // LDS row strides of contraction-slowest tiles [GK][BM] and [GK][BN]
     constexpr int A_ELEMS = KA ? GK * LDA_K : BM * GLD;    // LDS elements of the A tile; the B tile follows
     constexpr int TILE = A_ELEMS + (KB ? GK * LDB_K : BN * GLD);
+    constexpr bool PIPE = NS == 2 && DEPTH == 1;   // one workgroup a compute unit: nobody else's products hide its waits
+    static_assert(!PIPE || GK == 64, "four steps a tile");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -264,28 +263,28 @@ __device__ __forceinline__ void gemm_tiles(f32x16 (&acc)[BM / (32 * WM)][BN / (3
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * ld));
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    auto compute = [&](const bf16_t* stage) {
+    auto read_frags = [&](const bf16_t* stage, int kk, bf16x8 (&af)[MI], bf16x8 (&bfr)[NI]) {   // step kk: 16 contraction values
         const bf16_t* As = stage;
         const bf16_t* Bs = stage + A_ELEMS;
 #pragma unroll
-        for (int kk = 0; kk < GK / 16; ++kk) {
-            bf16x8 af[MI], bfr[NI];
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                if constexpr (KA) af[i] = frag(As, LDA_K, wm0 + i * 32, kk * 16);
-                else af[i] = *reinterpret_cast<const bf16x8*>(As + (wm0 + i * 32 + l32) * GLD + kk * 16 + lhi * 8);
-            }
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                if constexpr (KB) bfr[j] = frag(Bs, LDB_K, wn0 + j * 32, kk * 16);
-                else bfr[j] = *reinterpret_cast<const bf16x8*>(Bs + (wn0 + j * 32 + l32) * GLD + kk * 16 + lhi * 8);
-            }
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < MI; ++i) {
+            if constexpr (KA) af[i] = frag(As, LDA_K, wm0 + i * 32, kk * 16);
+            else af[i] = *reinterpret_cast<const bf16x8*>(As + (wm0 + i * 32 + l32) * GLD + kk * 16 + lhi * 8);
         }
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            if constexpr (KB) bfr[j] = frag(Bs, LDB_K, wn0 + j * 32, kk * 16);
+            else bfr[j] = *reinterpret_cast<const bf16x8*>(Bs + (wn0 + j * 32 + l32) * GLD + kk * 16 + lhi * 8);
+        }
+    };
+    auto mfmas = [&](const bf16x8 (&af)[MI], const bf16x8 (&bfr)[NI]) {
+        if constexpr (PIPE) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+        if constexpr (PIPE) __builtin_amdgcn_s_setprio(0);
     };
     // (not __syncthreads: that would also wait for the tiles on their way)
     auto barrier = [&]() {
@@ -294,6 +293,31 @@ __device__ __forceinline__ void gemm_tiles(f32x16 (&acc)[BM / (32 * WM)][BN / (3
         asm volatile("" ::: "memory");
     };
 
+    if constexpr (PIPE) {
+        // the fragments of a step are read while the step before it is multiplied; the next tile is parked in the other stage, and
+        // the one after it requested, between the second and the third step: one barrier a tile
+        load_tile(ra[0], rb[0]);
+        store_tile(smem, ra[0], rb[0]);
+        load_tile(ra[0], rb[0]);
+        barrier();
+        for (int kt = 0; kt < n_kt; ++kt) {
+            const bf16_t* cur = smem + (kt & 1) * TILE;
+            bf16_t* nxt = smem + ((kt + 1) & 1) * TILE;
+            bf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
+            read_frags(cur, 0, a0, b0);
+            read_frags(cur, 1, a1, b1);
+            mfmas(a0, b0);
+            read_frags(cur, 2, a0, b0);
+            mfmas(a1, b1);
+            store_tile(nxt, ra[0], rb[0]);
+            read_frags(cur, 3, a1, b1);
+            load_tile(ra[0], rb[0]);
+            mfmas(a0, b0);
+            mfmas(a1, b1);
+            barrier();
+        }
+        return;
+    }
     // DEPTH tiles are on their way from memory at any time, in registers; NS LDS stages.  With one stage two barriers a tile:
     // everyone has read the last one before it is overwritten.  With two, a wave that passed the barrier of tile kt has read
     // tile kt - 1, which tile kt + 1 overwrites.
@@ -308,7 +332,12 @@ __device__ __forceinline__ void gemm_tiles(f32x16 (&acc)[BM / (32 * WM)][BN / (3
             store_tile(stage, ra[d], rb[d]);
             load_tile(ra[d], rb[d]);
             barrier();
-            compute(stage);
+#pragma unroll
+            for (int kk = 0; kk < GK / 16; ++kk) {
+                bf16x8 af[MI], bfr[NI];
+                read_frags(stage, kk, af, bfr);
+                mfmas(af, bfr);
+            }
         }
     }
 }
@@ -385,234 +414,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, in
     gemm_epilogue<BM, BN, MI, NI, EP>(a, acc, smem, g, r0, m0, n0, M, N, wm0, wn0, lane, wave);
 }
 
-// ------------------------------------------------------------------------------------------------
-// 256 x 256 tiles for products that are bound by the matrix cores (forward and backward products of tasks with
-// hundreds of rows).  Four waves, each owning a 128 x 128 block of the tile (16 accumulator blocks = 256 registers):
-// per contraction step a wave reads 8 operand fragments from LDS for 16 MFMAs, half the LDS traffic per flop of a
-// 128 x 64 block, which is what the smaller tiles are bound by.  One wave per SIMD, so nothing but the instruction
-// order hides latencies: two LDS stages, fragments double-buffered in registers, and within each k-tile
-//   step 0: fragments of step 1 requested, first half of the NEXT tile parked in the other stage, first half of the
-//           tile after it requested from memory, MFMAs of step 0
-//   step 1: the same with the second halves
-//   step 2: fragments of step 3 requested, MFMAs of step 2
-//   step 3: barrier (everyone has read this stage and written the other), fragments of the next tile's step 0
-//           requested, MFMAs of step 3
-// Operand tiles come through buffer loads: a row, column or whole tile outside the operand reads as zero without a
-// branch, so the loop body is straight-line code.  A is stored contraction-contiguous; B either way (KB).
-#ifdef GEMM_TIMING
-__device__ unsigned long long g_gemm_ts[4 * 16384];
-void gemm_timing_fetch(unsigned long long* host, int n) { (void)hipMemcpyFromSymbol(host, HIP_SYMBOL(g_gemm_ts), sizeof(unsigned long long) * n); }
-#endif
-template <bool KA, bool KB, int EP, bool TIMED = false>
-__global__ __launch_bounds__(256) void gemm_bf16_pipe_kernel(GemmBArgs a, int n_ntiles, int mt_per_group, int n_tiles) {
-    constexpr int BM = 256, BN = 256, MI = 4, NI = 4, NT = 256;
-    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-    constexpr int LDB_K = BN + GPADK;   // (also the row stride of a contraction-slowest A tile: BM = BN)
-    constexpr int A_ELEMS = KA ? GK * LDB_K : BM * GLD;
-    constexpr int TILE = A_ELEMS + (KB ? GK * LDB_K : BN * GLD);
-
-    const int per_xcd = gridDim.x >> 3;
-    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile >= n_tiles) return;
-    const int ntile = tile % n_ntiles;
-    const int mtile = tile / n_ntiles;
-    int g, m0;
-    if (a.tile_group) {
-        g = a.tile_group[mtile];
-        m0 = a.tile_m0[mtile];
-    } else {
-        g = mtile / mt_per_group;
-        m0 = (mtile % mt_per_group) * BM;
-    }
-    const int64_t r0 = a.row_offsets[g];
-    const int rows_g = (int)(a.row_offsets[g + 1] - r0);
-    const int M = a.M < 0 ? rows_g : a.M;
-    const int K = a.K < 0 ? rows_g : a.K;
-    const int N = a.N;
-    const int n0 = ntile * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave >> 1) * 128, wn0 = (wave & 1) * 128;
-    const int l32 = lane & 31, lhi = lane >> 5;
-
-    f32x16 acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    const int kt_per_pair = (K + GK - 1) / GK;
-    const int n_kt = kt_per_pair * a.n_pairs;
-
-    // operands of the (up to two) products as buffer resources: an access past the group's matrix returns zero
-    const u32 OOB = 0x7ffffff0u;
-    __amdgpu_buffer_rsrc_t rsA[2], rsB[2];
-    u32 ldA2[2], ldB2[2];
-#pragma unroll
-    for (int p2 = 0; p2 < 2; ++p2) {
-        const int pr = p2 < a.n_pairs ? p2 : 0;
-        const bf16_t* A = a.A[pr] + (int64_t)g * a.gA[pr] + r0 * a.rA[pr];
-        const bf16_t* B = a.B[pr] + (int64_t)g * a.gB[pr] + r0 * a.rB[pr];
-        ldA2[p2] = (u32)a.lda[pr] * 2u;
-        ldB2[p2] = (u32)a.ldb[pr] * 2u;
-        rsA[p2] = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)((u32)(KA ? K : M) * ldA2[p2]), 0x00020000);
-        rsB[p2] = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)((u32)(KB ? K : N) * ldB2[p2]), 0x00020000);
-    }
-    // chunk c = tid + 256 i of a tile: A (and B stored like A): row c / 8, 16 bytes at k = (c % 8) * 8;
-    // B stored contraction-slowest: k-row c / 32, 16 bytes at n = (c % 32) * 8
-    const int crow = tid >> 3, ccol = (tid & 7) * 8;
-    const int kbrow = tid >> 5, kbcol = (tid & 31) * 8;
-    u32x4 ra[8], rb[8];
-    auto gload_half = [&](int h, int lt) {   // chunks 4h .. 4h+3 of tile lt (a tile past the end reads as zero)
-        const int pr = (lt >= kt_per_pair && a.n_pairs > 1) ? 1 : 0;
-        const int k0 = (lt - pr * kt_per_pair) * GK;
-        const __amdgpu_buffer_rsrc_t rA = pr ? rsA[1] : rsA[0];
-        const __amdgpu_buffer_rsrc_t rB = pr ? rsB[1] : rsB[0];
-        const u32 la = pr ? ldA2[1] : ldA2[0], lb = pr ? ldB2[1] : ldB2[0];
-        const bool kok = k0 + ccol < K;
-        if constexpr (KA) {   // (a column past M would read on into the next row: such a chunk is sent out of bounds)
-            const bool mok = m0 + kbcol < M;
-            const u32 a0 = mok ? (u32)(k0 + kbrow) * la + (u32)(m0 + kbcol) * 2u : OOB;
-#pragma unroll
-            for (int i = 4 * h; i < 4 * h + 4; ++i) ra[i] = __builtin_amdgcn_raw_buffer_load_b128(rA, (int)(a0 + (mok ? (u32)(8 * i) * la : 0u)), 0, 0);
-        } else {
-            const u32 a0 = kok ? (u32)(m0 + crow) * la + (u32)(k0 + ccol) * 2u : OOB;
-#pragma unroll
-            for (int i = 4 * h; i < 4 * h + 4; ++i) ra[i] = __builtin_amdgcn_raw_buffer_load_b128(rA, (int)(a0 + (kok ? (u32)(32 * i) * la : 0u)), 0, 0);
-        }
-        if constexpr (KB) {
-            const u32 b0 = (u32)(k0 + kbrow) * lb + (u32)(n0 + kbcol) * 2u;
-#pragma unroll
-            for (int i = 4 * h; i < 4 * h + 4; ++i) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rB, (int)(b0 + (u32)(8 * i) * lb), 0, 0);
-        } else {
-            const u32 b0 = kok ? (u32)(n0 + crow) * lb + (u32)(k0 + ccol) * 2u : OOB;
-#pragma unroll
-            for (int i = 4 * h; i < 4 * h + 4; ++i) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rB, (int)(b0 + (kok ? (u32)(32 * i) * lb : 0u)), 0, 0);
-        }
-    };
-    auto store_half = [&](bf16_t* stage, int h) {
-#pragma unroll
-        for (int i = 4 * h; i < 4 * h + 4; ++i) {
-            if constexpr (KA) *reinterpret_cast<u32x4*>(stage + (kbrow + 8 * i) * LDB_K + kbcol) = ra[i];
-            else *reinterpret_cast<u32x4*>(stage + (crow + 32 * i) * GLD + ccol) = ra[i];
-        }
-#pragma unroll
-        for (int i = 4 * h; i < 4 * h + 4; ++i) {
-            if constexpr (KB) *reinterpret_cast<u32x4*>(stage + A_ELEMS + (kbrow + 8 * i) * LDB_K + kbcol) = rb[i];
-            else *reinterpret_cast<u32x4*>(stage + A_ELEMS + (crow + 32 * i) * GLD + ccol) = rb[i];
-        }
-    };
-    const int tr_off_row = lhi * 8 + ((lane & 15) >> 2), tr_off_col = (lane & 16) + (lane & 3) * 4;
-    auto frag_tr = [&](const bf16_t* tile_, int c0, int k) {
-        const bf16_t* p = tile_ + (k + tr_off_row) * LDB_K + c0 + tr_off_col;
-        typedef s16x4 __attribute__((address_space(3))) * lds_s16x4_ptr;
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p);
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * LDB_K));
-        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-    auto read_frags = [&](const bf16_t* stage, int kk, bf16x8 (&af)[MI], bf16x8 (&bfr)[NI]) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            if constexpr (KA) af[i] = frag_tr(stage, wm0 + i * 32, kk * 16);
-            else af[i] = *reinterpret_cast<const bf16x8*>(stage + (wm0 + i * 32 + l32) * GLD + kk * 16 + lhi * 8);
-        }
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            if constexpr (KB) bfr[j] = frag_tr(stage + A_ELEMS, wn0 + j * 32, kk * 16);
-            else bfr[j] = *reinterpret_cast<const bf16x8*>(stage + A_ELEMS + (wn0 + j * 32 + l32) * GLD + kk * 16 + lhi * 8);
-        }
-    };
-    auto mfmas = [&](const bf16x8 (&af)[MI], const bf16x8 (&bfr)[NI]) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);   // transposed block
-    };
-
-    bf16x8 fa0[MI], fb0[NI], fa1[MI], fb1[NI];
-#ifdef GEMM_TIMING
-    unsigned long long ts0 = 0, ts1 = 0, ts2 = 0;
-    if (TIMED) ts0 = __builtin_readcyclecounter();
-#endif
-    gload_half(0, 0);
-    gload_half(1, 0);
-    store_half(smem, 0);
-    store_half(smem, 1);
-    gload_half(0, 1);
-    gload_half(1, 1);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    read_frags(smem, 0, fa0, fb0);
-#ifdef GEMM_TIMING
-    if (TIMED) ts1 = __builtin_readcyclecounter();
-#endif
-    for (int kt = 0; kt < n_kt; ++kt) {
-        bf16_t* cur = smem + (kt & 1) * TILE;
-        bf16_t* nxt = smem + ((kt + 1) & 1) * TILE;
-        // instruction order of a step: the fragment reads first, then one LDS write or one memory request in the
-        // shadow of every MFMA (0x100 LDS read, 0x200 LDS write, 0x020 memory read, 0x008 MFMA)
-        constexpr int NR = 8 + (KA ? 4 : 0) + (KB ? 4 : 0);   // LDS reads of one set of fragments
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(cur, 1, fa1, fb1);
-        mfmas(fa0, fb0);
-        store_half(nxt, 0);
-        gload_half(0, kt + 2);
-        __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(cur, 2, fa0, fb0);
-        mfmas(fa1, fb1);
-        store_half(nxt, 1);
-        gload_half(1, kt + 2);
-        __builtin_amdgcn_sched_group_barrier(0x100, NR, 1);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-            __builtin_amdgcn_sched_group_barrier(0x200, 1, 1);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        read_frags(cur, 3, fa1, fb1);
-        mfmas(fa0, fb0);
-        __builtin_amdgcn_sched_group_barrier(0x100, NR, 2);
-        __builtin_amdgcn_sched_group_barrier(0x008, 16, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        read_frags(nxt, 0, fa0, fb0);
-        mfmas(fa1, fb1);
-        __builtin_amdgcn_sched_group_barrier(0x100, NR, 3);
-        __builtin_amdgcn_sched_group_barrier(0x008, 16, 3);
-    }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();   // every wave is done with the operand stages (the epilogue reuses them)
-#ifdef GEMM_TIMING
-    if (TIMED) ts2 = __builtin_readcyclecounter();
-#endif
-    gemm_epilogue<BM, BN, MI, NI, EP, true>(a, acc, smem, g, r0, m0, n0, M, N, wm0, wn0, lane, wave);
-#ifdef GEMM_TIMING
-    if (TIMED && tid == 0 && tile < 16384) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        g_gemm_ts[4 * tile] = ts0; g_gemm_ts[4 * tile + 1] = ts1; g_gemm_ts[4 * tile + 2] = ts2;
-        g_gemm_ts[4 * tile + 3] = __builtin_readcyclecounter();
-    }
-#endif
-}
-
 static void tile_counts(const GemmBArgs& a, int BM, int BN, int& n_ntiles, int& mt_per_group, int64_t& n_tiles) {
     n_ntiles = ((a.N < 0 ? a.most_n : a.N) + BN - 1) / BN;
     int64_t n_mtiles;
@@ -624,20 +425,6 @@ static void tile_counts(const GemmBArgs& a, int BM, int BN, int& n_ntiles, int& 
         n_mtiles = (int64_t)mt_per_group * a.G;
     }
     n_tiles = (n_mtiles <= 0 || n_ntiles <= 0) ? 0 : n_mtiles * n_ntiles;
-}
-
-template <bool KA, bool KB, int EP, bool TIMED = false>
-static void launch_pipe(hipStream_t st, const GemmBArgs& a) {
-    constexpr int BM = 256, BN = 256;
-    int n_ntiles, mt_per_group;
-    int64_t n_tiles;
-    tile_counts(a, BM, BN, n_ntiles, mt_per_group, n_tiles);
-    if (n_tiles <= 0) return;
-    const size_t shmem = ((KA ? (size_t)GK * (BM + GPADK) : (size_t)BM * GLD) + (KB ? (size_t)GK * (BN + GPADK) : (size_t)BN * GLD)) * sizeof(bf16_t) * 2;
-    auto kern = gemm_bf16_pipe_kernel<KA, KB, EP, TIMED>;
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    const unsigned grid = (unsigned)((n_tiles + 7) / 8 * 8);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), shmem, st, a, n_ntiles, mt_per_group, (int)n_tiles);
 }
 
 template <int BM, int BN, int WM, int WN, int DEPTH, int NS, bool KA, bool KB, int EP, bool XT = false>
@@ -656,7 +443,7 @@ static void launch_variant(hipStream_t st, const GemmBArgs& a) {
 }
 
 // Tile shapes of one operand form.  bm: row tile the caller built its (tile_group, tile_m0) lists for (64, 128 or
-// 256); bn: 128, or 256 (with bm = 256: the pipelined 256 x 256 kernel).  With further products (a.ext: many small tasks) one tile on
+// 256); bn: 128, or 256 (with bm = 256).  With further products (a.ext: many small tasks) one tile on
 // its way and one stage leave room for more workgroups (700 tasks of a median 32 rows: a forward launch 424 -> 410 us, their thin
 // products 227 -> 208); other 64-row tiles keep two tiles on their way and two LDS
 // stages (3 tasks of 512 rows: a layer's forward 23.1 us, with four tiles and four waves 24.9); for the others one of each
@@ -664,7 +451,7 @@ static void launch_variant(hipStream_t st, const GemmBArgs& a) {
 template <bool KB, int EP>
 static void launch_rows_form(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
     if (a.ext.n > 0) launch_variant<64, 128, 2, 4, 1, 1, false, KB, EP, true>(st, a);   // (bm is 64)
-    else if (bm == 256 && bn == 256) launch_pipe<false, KB, EP>(st, a);
+    else if (bm == 256 && bn == 256) launch_variant<256, 256, 2, 4, 1, 2, false, KB, EP>(st, a);
     else if (bm == 256) launch_variant<256, 128, 4, 2, 1, 1, false, KB, EP>(st, a);
     else if (bm == 128) launch_variant<128, 128, 2, 4, 1, 1, false, KB, EP>(st, a);
     else launch_variant<64, 128, 2, 4, 2, 2, false, KB, EP>(st, a);
@@ -683,17 +470,16 @@ void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
 }
 
 // Weight-gradient form: both operands stored with the contraction index slowest (A [K, M], B [K, N]).  tile: 128, or 256
-// (the pipelined 256 x 256 kernel; N a multiple of 256): worth it when the contraction is thousands of rows long -- per
+// (N a multiple of 256): worth it when the contraction is thousands of rows long -- per
 // task (K = a task's rows, every task writing its own [M, N]) the product is bound by what it writes, and more
 // workgroups per compute unit hide that better than wider tiles.
 template <int EP>
 static void launch_kmajor_tile(hipStream_t st, const GemmBArgs& a, int tile) {
-    if (tile == 256) launch_pipe<true, true, EP>(st, a);
+    if (tile == 256) launch_variant<256, 256, 2, 4, 1, 2, true, true, EP>(st, a);
     // (eight waves where only sums over runs of tasks are written: a long contraction; else four)
     else launch_variant<128, 128, 2, EP == (EPI_AXPBY | EP_CF) ? 4 : 2, 1, 1, true, true, EP>(st, a);
 }
 void launch_gemm_bf16_kmajor(hipStream_t st, const GemmBArgs& a, int tile) {
-    if (a.n_pairs > 2) tile = 128;   // (the pipelined kernel keeps two operand descriptors)
     switch (ep_of(a)) {
         case EPI_AXPBY | EP_CF: launch_kmajor_tile<EPI_AXPBY | EP_CF>(st, a, tile); break;
         case EPI_AXPBY | EP_CF | EP_CB: launch_kmajor_tile<EPI_AXPBY | EP_CF | EP_CB>(st, a, tile); break;
@@ -712,10 +498,3 @@ void launch_gemm_bf16_bkmajor(hipStream_t st, const GemmBArgs& a, int bm, int bn
         default: launch_rows_form<true, EP_RUNTIME>(st, a, bm, bn); break;
     }
 }
-
-#ifdef GEMM_TIMING
-void launch_gemm_bf16_timed(hipStream_t st, const GemmBArgs& a, bool kb) {   // development: per-phase cycle counts of the pipelined kernel
-    if (kb) launch_pipe<false, true, EPI_BIAS_RELU | EP_CB, true>(st, a);
-    else launch_pipe<false, false, EPI_MASK | EP_CB, true>(st, a);
-}
-#endif

@@ -295,7 +295,7 @@ struct GemmList { int n; GemmArgs job[GEMM_LIST]; int block0[GEMM_LIST]; };
 void launch_gemm_f32_wgrads(hipStream_t st, const GemmArgs* list, int n);   // both operands contraction-slowest, M fixed, K the group's rows
 
 // bf16 operands, both stored contraction-contiguous: C[M,N] = sum_p A_p[M,K] * Bt_p[N,K]^T
-#define GEMM_MAX_PAIRS 4   // products accumulated into one output (the pipelined kernel takes at most two)
+#define GEMM_MAX_PAIRS 4   // products accumulated into one output
 // Further products of a sum: S_e * Q_e, contracted over the rows that the group has in a set (`rows`): S_e [rows of the result,
 // 2 * ld], the rows' upper parts, then at column ld their lower parts; Q_e [rows of the set, ldq].
 // With EPI_SPLIT: the products that make them, one for every entry: c_e * A * Q_e^T, the columns being the group's rows of that
@@ -332,7 +332,7 @@ struct GemmBArgs {
     int most_n;                            // N -1 (EPI_SPLIT): most columns of a product
     GemmExt ext;                           // (64-row tiles only)
 };
-void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn = 128);   // bn = 256 (with bm = 256): the pipelined 256 x 256 kernel
+void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn = 128);   // bn = 256: with bm = 256 only
 // same product with both operands stored contraction-slowest: A_p element (k, m) at A + g*gA + r0*rA + k*lda + m,
 // B_p element (k, n) at B + g*gB + r0*rB + k*ldb + n
 void launch_gemm_bf16_kmajor(hipStream_t st, const GemmBArgs& a, int tile = 128);   // tile: 128, or 256 (N % 256 == 0)

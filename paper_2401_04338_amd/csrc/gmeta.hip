@@ -866,9 +866,10 @@ struct Grp {  // grouping of one set's rows by task inside the wave
 static Grp whole_group(const gm_ctx* c, const Grp& g);
 
 
-// column tile of a forward / backward product.  256 selects the pipelined 256 x 256 kernel (256-row tiles, a multiple of
-// 256 columns): it wins where the contraction is long enough to pay for its unhidden prologue and epilogue (one
-// workgroup per compute unit), measured from about 2,048 on; results are identical either way.
+// column tile of a forward / backward product.  256 (256-row tiles, a multiple of 256 columns): it wins where the
+// contraction is long enough to pay for its unhidden prologue and epilogue (one workgroup per compute unit).  512 tasks of 256
+// rows: contraction 1,677, a forward launch 309 us (256 x 128 tiles 364); contraction 256, backward 126 us (115).  Results are
+// identical either way.
 static int gemm_bn(const gm_ctx* c, int bm, int N, int K) {
     if (bm != 256 || N < 256 || N % 256 != 0) return 128;
     if (c->gemm_tile_n) return c->gemm_tile_n;
@@ -1011,9 +1012,7 @@ static void dense_nt(gm_ctx* c, const Grp& g, int l, int np, const Act* d0, cons
 }
 
 static Grp whole_group(const gm_ctx* c, const Grp& g) {
-    int widest = c->ld[0];
-    for (int l = 1; l < c->L; ++l) widest = std::max(widest, c->ld[l]);
-    if (c->L < 2 || g.rows * widest * 2 >= ((int64_t)1 << 31)) return g;   // (an operand's offsets are 32 bits)
+    if (c->L < 2) return g;
     Grp w = g;
     w.whole = true;
     w.G = 1;
@@ -1025,10 +1024,13 @@ static Grp whole_group(const gm_ctx* c, const Grp& g) {
     return w;
 }
 
-// Weight gradient [M, N] of G groups over `rows` rows in all: the pipelined 256 x 256 tiles pay once the contraction of a
-// group is at least 512 rows long (clearly so from thousands of rows on) and the tiles fill the device several times over.
+// Weight gradient [M, N] of G groups over `rows` rows in all: 256 x 256 tiles pay once a group's contraction is some 200
+// rows long and the tiles fill the device several times over.  Dense-only steps of 256 tasks, first layer 1677 x 512, with
+// them and without: 64 rows a task 2.25 / 2.26 ms, 128 4.09 / 4.14, 192 5.51 / 5.58, 256 6.76 / 6.85; 128 tasks, 4109 x 1024: 64
+// rows 3.83 / 3.74, 128 7.04 / 7.01, 192 9.05 / 9.07, 256 10.82 / 10.97.  Narrow layers lose to padded rows of the last tile
+// (512 tasks, 269 x 256, 256 rows: 2.54 / 2.53).
 static bool wgrad_wide_ok(const gm_ctx* c, int M, int N, int64_t rows, int G) {
-    return c->wgrad_wide && c->mlp_dtype && M >= 1024 && N % 256 == 0 && G > 0 && rows / G >= 512 &&
+    return c->wgrad_wide && c->mlp_dtype && M >= 1024 && N % 256 == 0 && G > 0 && rows / G >= 192 &&
            (int64_t)((M + 255) / 256) * (N / 256) * G >= 2 * (int64_t)c->n_cus;
 }
 

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 F, D, NDENSE, OWN = 4, 32, 5, 2048   # table rows of a task's own, half of them for each set
 
 
-def _sets(sizes, which):
+def _sets(sizes, which, F=F):
     """Every task draws from a generator of its own (task t is the same in every batch) and looks every row up once, so that a
     row's gradient is one sample's."""
     parts = []
@@ -52,5 +52,29 @@ def test_row_tiles(gm, hidden, rows, many, K):  # noqa: F811
         got.append((out["task_loss"][:2].clone(), r[mine], out["emb_grad"][:n][mine]))
         ctx.close()
     assert len(got[0][1]) > 0 and float(got[0][2].abs().max()) > 0
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("K", [1, 3, 4])
+def test_weight_gradient_tiles(gm, K):  # noqa: F811
+    """Tasks of about 200 rows under a first layer wide enough for 256 x 256 tiles of its gradients (remainders in both directions
+    and in the contraction, single-row tasks among them): the same bits as in 128 x 128 tiles, one to four products a sum."""
+    f, d, T = 8, 128, 110
+    dims = [f * d + NDENSE, 256, 1]
+    gen = torch.Generator("cuda").manual_seed(6)
+    params = SimpleNamespace(emb=torch.randn(f * OWN * T, d, device="cuda", generator=gen) * 0.3,
+                             W=[torch.randn(a, b, device="cuda", generator=gen) / a ** 0.5 for a, b in zip(dims[:-1], dims[1:])],
+                             b=[torch.randn(b, device="cuda", generator=gen) * 0.1 for b in dims[1:]])
+    sup, qry = (_sets([(193, 256, 257, 1 + w, 319)[t % 5] for t in range(T)], w, f) for w in (0, 1))
+    got = []
+    for wide in (1, 0):
+        ctx = gm(f, [OWN * T] * f, d, NDENSE, dims, 1, workspace_bytes=8 << 30)
+        ctx.configure("wgrad_wide", wide)
+        out = ctx.meta_step(sup, qry, params, 0.1, K, 2)
+        n = int(out["n_emb_rows"].item())
+        got.append([x.clone() for x in (out["task_loss"], *out["dW"], *out["db"], out["emb_grad"][:n])])
+        ctx.close()
+    assert float(got[0][1].abs().max()) > 0
     for a, b in zip(*got):
         assert torch.equal(a, b)
