@@ -1354,12 +1354,14 @@ struct Upload {
     }
 };
 
+enum { PAIR_ROWS = 512, PAIR_ROWS_FEW = 1024 };
 struct Batch {  // host-side description of one call
     int T;
     const gm_set *sup, *qry;
     std::vector<int64_t> poff_s, poff_q;  // padded row offsets per task, whole batch
     std::vector<int64_t> ls, lq;          // lookup offsets per task (filled when several waves are needed)
     bool table = false;                   // table-shaped sparse output: every wave sorts and reduces its own lookups
+    int pair_rows = PAIR_ROWS;            // a task of at most so many rows in each set goes through pair-count matrices
     BatchBufs b;
     HostImages images;
 };
@@ -1603,7 +1605,25 @@ enum { FACTOR_MOST_ROWS = 2048 };
 static bool task_pair_ok(const gm_ctx* c, const Batch& B, int t, int K) {
     if (c->row_path == 1 || K <= 0 || c->F == 0 || c->D % 32 != 0 || !c->adapt_rows) return false;
     const int64_t mx = std::max(B.sup->task_offsets[t + 1] - B.sup->task_offsets[t], B.qry->task_offsets[t + 1] - B.qry->task_offsets[t]);
-    return mx > 0 && mx <= (c->row_path == 2 ? 1024 : 512);
+    return mx > 0 && mx <= (c->row_path == 2 ? (int)PAIR_ROWS_FEW : B.pair_rows);
+}
+
+// A few tasks of 513 to 1024 rows among smaller ones go the others' way: for them alone the sparse kernel would run at every
+// hop, a workgroup a (task, field), as long as the largest takes.  Among 700 tasks of a median 32 rows two of them, 16 launches
+// of 100 us: a step of 28.9 ms takes 27.9.  Where lookups are few (up to three a bag: 32 tasks x 600 rows x 26 fields 2.80 / 2.98
+// ms with matrices; six: 8.67 / 8.39) or the (task, field)s do not fill the device (8 tasks x 700 rows 2.10 / 2.16 ms, 16 tasks
+// 3.55 / 2.82) the sparse kernel is the faster one, and their matrices shall take a fraction of the others' memory.
+static int pair_rows(const gm_ctx* c, const Batch& B) {
+    const double bags = (double)(B.sup->n_samples + B.qry->n_samples) * c->F;
+    if ((double)(B.sup->nnz + B.qry->nnz) < 4.0 * bags || (int64_t)B.T * c->F < c->n_cus) return PAIR_ROWS;
+    double few = 0, others = 0;
+    for (int t = 0; t < B.T; ++t) {
+        const int64_t ns = B.sup->task_offsets[t + 1] - B.sup->task_offsets[t], nq = B.qry->task_offsets[t + 1] - B.qry->task_offsets[t];
+        const int64_t mx = std::max(ns, nq);
+        if (mx > PAIR_ROWS_FEW) continue;
+        (mx > PAIR_ROWS ? few : others) += (double)pad64(ns) * (double)(pad64(ns) + pad64(nq));
+    }
+    return few > 0 && 4.0 * few <= others ? PAIR_ROWS_FEW : PAIR_ROWS;
 }
 
 // Byte offsets of every task's pair-count matrices (kind by kind, fields back to back; nothing for a task
@@ -1727,6 +1747,7 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         have_offsets = true;
         return GM_OK;
     };
+    B.pair_rows = pair_rows(c, B);
     // Waves of (nearly) equal numbers of tasks: the fewest waves whose every wave fits.
     const int max_per = std::min(std::max(T, 1), most_wave_tasks(c));
     int n_waves = (std::max(T, 1) + max_per - 1) / max_per;
@@ -1760,6 +1781,11 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
             if (T == 0) break;
         }
         if (fits) return GM_OK;
+        if (per == 1 && B.pair_rows > PAIR_ROWS) {   // (a large task's matrices may be what does not fit)
+            B.pair_rows = PAIR_ROWS;
+            n_waves = (std::max(T, 1) + max_per - 1) / max_per;
+            continue;
+        }
         if (per == 1) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
         n_waves = std::min(std::max(T, 1), std::max(n_waves + 1, n_waves + n_waves / 16));
     }
@@ -2585,6 +2611,7 @@ static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_s
                            size_t* index_bytes, size_t* dense_bytes) {
     Batch B;
     host_layout(c, B, T, sup, qry);
+    B.pair_rows = pair_rows(c, B);
     const WavePlan p = whole_batch_plan(B);
     const WaveDims d = wave_dims(c, B, p, pick_bm(c, B), K, order);
     Arena ia, da;
@@ -2611,6 +2638,7 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
     B.T = T; B.sup = sup; B.qry = qry; B.table = false;
     if ((rc = begin_batch(c, B, ia, 0, true, nullptr))) return rc;
     P.bm = pick_bm(c, B);
+    B.pair_rows = pair_rows(c, B);
     P.wp = whole_batch_plan(B);
     if (sup->nnz + qry->nnz >= ((int64_t)1 << 31)) return fail(c, GM_ERR_WORKSPACE, "the batch does not run as one wave of tasks");
     P.d = wave_dims(c, B, P.wp, P.bm, K, order);

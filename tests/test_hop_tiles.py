@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from tests.helpers import small_cfg
-from tests.test_gpu_parity import TOL_FP32, _compare_step, _inputs, gm  # noqa: F401
+from tests.test_gpu_parity import TOL_FP32, _compare_step, _inputs, _params_dev, _to_dev, gm  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +68,31 @@ def test_batches_of_hot_rows(gm, rows, samples, bag, zipf, K):  # noqa: F811
     ctx.configure("row_path", 2)
     _compare_step(cfg, ctx, sup, qry, params, K, 2, TOL_FP32, f"{rows} rows, {samples} samples, bags of {bag}")
     ctx.close()
+
+
+@pytest.mark.parametrize("large,bag,matrices", [((600,), 12, True), ((1024, 513), 12, True), ((1025, 600), 12, None), ((600,), 3, False),
+                                                ((1024, 1024, 1024), 12, False)])
+def test_few_large_tasks_among_small_ones(gm, large, bag, matrices):  # noqa: F811
+    """Tasks of more than 512 rows take the others' matrices where they are few and lookups many: then the bits are those of matrices
+    for all (matrices: True), else another order of sums; never more than rounding away from the sparse kernel's."""
+    F, D = 3, 32
+    sizes = [*large, *([200, 250, 193] * 29)]
+    cfg = small_cfg(n_tasks=len(sizes), n_fields=F, emb_dim=D, rows_per_field=500, n_support=max(sizes), n_query=max(sizes), bag_max=bag,
+                    layer_dims=(F * D + 5, 24, 1))
+    sup, qry, params = _inputs(cfg, emb_std=0.3)
+    ctx = gm.from_config(cfg, workspace_bytes=1 << 31)
+    s, q, p = _to_dev(_cut(sup, sizes, F), ctx.device), _to_dev(_cut(qry, sizes, F), ctx.device), _params_dev(params, ctx.device)
+    got = {}
+    for path in (0, 1, 2):
+        if path == 2 and max(sizes) > 1024:
+            continue
+        ctx.configure("row_path", path)
+        out = ctx.meta_step(s, q, p, cfg.inner_lr, 2, 2)
+        n = int(out["n_emb_rows"].item())
+        got[path] = [x.clone() for x in (out["emb_grad"][:n], out["task_loss"][:len(sizes)], *out["dW"])]
+    ctx.close()
+    for a, b in zip(got[0], got[1]):
+        assert float((a - b).norm()) <= TOL_FP32 * float(b.norm())
+    if matrices is not None:
+        same = all(torch.equal(a, b) for a, b in zip(got[0], got[2]))
+        assert same == matrices
