@@ -31,9 +31,9 @@ FAMILIES = {
     "gather_pool": r"gather_pool(_xcd)?_kernel",
     # radix_*_kernel<BITS, BYTASK>: the pass by task belongs to the per-(task, field) dictionaries (with the join that reads
     # them off the ordered list), the passes by row key to the ordering of the lookups by row
-    "tf_sort": r"tf_sort_kernel|tf_join_kernel|radix_(hist|scatter)_kernel<\d+, true>",
+    "tf_sort": r"tf_sort_kernel|tf_join_kernel|radix_(hist|scatter)_kernel<\d+, true",
     "tf_count": r"tf_count_kernel",
-    "global_sort": r"build_keys_kernel|build_keys_fm_kernel|field_(offsets|table)_kernel|radix_(hist|scatter)_kernel<\d+, false>|seg_flags_kernel|seg_emit_kernel",
+    "global_sort": r"build_keys_kernel|build_keys_fm_kernel|field_(offsets|table)_kernel|radix_(hist|scatter)_kernel<\d+, false|seg_flags_kernel|seg_emit_kernel",
     "task_colsum": r"task_colsum_(bf16|f32)_kernel",
     "reduce_tasks": r"reduce_tasks_kernel",
     "axpy_gx": r"axpy_kernel",

@@ -120,7 +120,6 @@ struct SegTab {
     int n_seg;
     const u32 *tile_base, *key_base_pos, *key_sub;
 };
-#define RS_TILE_KEYS 2048   // keys per tile of a radix pass
 // Stable LSD radix sort of (key, val) pairs on the low `bits` bits (of key - key_sub with ranges: every range by
 // itself).  Returns the number of passes: after an odd number the result is in (keys_tmp, vals_tmp), else in (keys, vals).
 int launch_radix_sort(hipStream_t st, u32* keys, u32* vals, u32* keys_tmp, u32* vals_tmp, int64_t n,
@@ -141,7 +140,7 @@ struct FieldKeysArgs {
     u32 *keys, *vals;
     const u32 *key_pos, *tot;        // set by the launcher
 };
-void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables);
+void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n /* lookups of the wave, as the passes are given */);
 SegTab field_seg_tab(int F, u32* tables);
 size_t field_table_words(int F);
 void launch_segments(hipStream_t st, const u32* sorted_keys, int64_t n, u32* flags_scan, u32* scan_tmp,

@@ -796,6 +796,9 @@ __global__ __launch_bounds__(256) void field_table_kernel(int F, const u32* tot,
     }
 }
 
+enum { RS_ITEMS = 8 };   // keys per thread of a radix tile
+static int rs_tile_keys(int64_t n);
+
 #define BKF_CH 1024   // bags of a task staged at a time
 // One workgroup per (field, task, set): the bags (sample, field) of the task, BKF_CH at a time -- their lengths are
 // scanned into LDS, then every lane takes lookups of the piece in order (coalesced writes), finding a lookup's bag
@@ -879,14 +882,14 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
 }
 
 // tables: 3 (F + 1) words (key_pos, tile_base, key_sub), then 2 F words of totals
-void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables) {
+void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n) {
     if (a.F <= 0 || a.Tw <= 0) return;
     u32* key_pos = tables;
     u32* tile_base = key_pos + (a.F + 1);
     u32* key_sub = tile_base + (a.F + 1);
     u32* tot = key_sub + (a.F + 1);
     hipLaunchKernelGGL(field_offsets_kernel, dim3(a.F), dim3(256), 0, st, a.F, a.Tw, a.cnt_s, a.cnt_q, a.fm_off_s, a.fm_off_q, tot);
-    hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(256), 0, st, a.F, tot, a.field_base, RS_TILE_KEYS, key_pos, tile_base, key_sub);
+    hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(256), 0, st, a.F, tot, a.field_base, rs_tile_keys(n), key_pos, tile_base, key_sub);
     a.key_pos = key_pos;
     a.tot = tot;
     hipLaunchKernelGGL(build_keys_fm_kernel, dim3(a.F, a.Tw, 2), dim3(256), 0, st, a);
@@ -894,13 +897,10 @@ void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables) {
 SegTab field_seg_tab(int F, u32* tables) { return SegTab{F, tables + (F + 1), tables, tables + 2 * (F + 1)}; }
 size_t field_table_words(int F) { return (size_t)5 * (F + 1); }
 
-#define RS_NT 256
-#define RS_ITEMS 8
-#define RS_TILE (RS_NT * RS_ITEMS)
-static_assert(RS_TILE == RS_TILE_KEYS, "tile size");
-#define RS_WAVES (RS_NT / WAVE)
-
-// Digits are BITS wide (8 or 9): 25-bit row keys sort in three 9-bit passes instead of four 8-bit ones.
+// Digits are BITS wide (8, or 9 where that saves a pass): 25-bit row keys sort in three 9-bit passes instead of four 8-bit ones.
+// Bound: memory, if enough of it is under way.  All of a thread's RS_ITEMS keys (and their places in the output) are asked for
+// before the first is used: asked for one by one, inside the conditions that guard the list's end, a scatter of 138 million pairs
+// took 740 us and a digit count 267; now 525 and 143 (4.2 and 3.9 TB/s).
 // Tiles are dealt to workgroups so that every XCD (workgroups are spread over the 8 XCDs round-robin) walks one
 // contiguous range of tiles: the pieces that neighbouring tiles write into a digit's output range then meet in one L2.
 __device__ __forceinline__ int rs_tile_of_block(int nblk) {
@@ -929,11 +929,12 @@ struct RsTile {
     size_t hstride;      // ... and the distance between digits
     bool any;
 };
+template <int TILE>
 __device__ __forceinline__ RsTile rs_tile(const SegTab& seg, int tile, int nblk, int64_t n, int nb) {
     RsTile t;
     if (seg.n_seg == 0) {
-        t.k0 = (int64_t)tile * RS_TILE;
-        t.k1 = min(n, t.k0 + RS_TILE);
+        t.k0 = (int64_t)tile * TILE;
+        t.k1 = min(n, t.k0 + TILE);
         t.key_base = 0u;
         t.h0 = (size_t)tile;
         t.hstride = (size_t)nblk;
@@ -948,37 +949,40 @@ __device__ __forceinline__ RsTile rs_tile(const SegTab& seg, int tile, int nblk,
     }
     const u32 tb = seg.tile_base[lo], te = seg.tile_base[lo + 1];
     t.any = (u32)tile < te;       // (tiles past the last range's: nothing to do)
-    t.k0 = (int64_t)seg.key_base_pos[lo] + (int64_t)((u32)tile - tb) * RS_TILE;
-    t.k1 = min((int64_t)seg.key_base_pos[lo + 1], t.k0 + RS_TILE);
+    t.k0 = (int64_t)seg.key_base_pos[lo] + (int64_t)((u32)tile - tb) * TILE;
+    t.k1 = min((int64_t)seg.key_base_pos[lo + 1], t.k0 + TILE);
     t.key_base = seg.key_sub[lo];
     t.hstride = (size_t)(te - tb);
     t.h0 = (size_t)nb * tb + ((u32)tile - tb);
     return t;
 }
 
-template <int BITS, bool BYTASK>
-__global__ void radix_hist_kernel(const u32* src, int64_t n, int shift, u32* hist, int nblk, TaskOf tk, SegTab seg) {
+template <int BITS, bool BYTASK, int NT>
+__global__ __launch_bounds__(NT) void radix_hist_kernel(const u32* src, int64_t n, int shift, u32* hist, int nblk, TaskOf tk, SegTab seg) {
     constexpr int NB = 1 << BITS;
     __shared__ u32 h[NB];
     const int tile = rs_tile_of_block(nblk);
     if (tile >= nblk) return;
-    const RsTile T = rs_tile(seg, tile, nblk, n, NB);
+    const RsTile T = rs_tile<NT * RS_ITEMS>(seg, tile, nblk, n, NB);
     if (!T.any) return;
-    for (int i = threadIdx.x; i < NB; i += RS_NT) h[i] = 0;
+    for (int i = threadIdx.x; i < NB; i += NT) h[i] = 0;
     __syncthreads();
     const int64_t base = T.k0;
     const int64_t n_end = T.k1;
     const int lane = threadIdx.x & (WAVE - 1);
+    u32 item[RS_ITEMS];   // (all of a thread's items are asked for before the first is looked at; past the tile its last one)
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; ++i) item[i] = src[min(base + i * NT + (int64_t)threadIdx.x, n_end - 1)];
 #pragma unroll
     for (int i = 0; i < RS_ITEMS; ++i) {
-        const int64_t idx = base + i * RS_NT + threadIdx.x;
+        const int64_t idx = base + i * NT + threadIdx.x;
         // One atomic per run of equal digits in the wave instead of one per lane.  By task: inside a row the lookups
         // are in input order, i.e. by task, so a hot row gives long runs of one digit, which as one atomic per lane
         // would all queue on one counter.  By key: from the second pass on the keys of a hot row lie next to each
         // other (they share every digit sorted so far), and LDS atomics retire about one lane per cycle.
         const bool valid = idx < n_end;
         u32 d = 0xFFFFFFFFu;
-        if (valid) d = ((BYTASK ? rs_task_of(tk, src[idx]) : src[idx] - T.key_base) >> shift) & (NB - 1);
+        if (valid) d = ((BYTASK ? rs_task_of(tk, item[i]) : item[i] - T.key_base) >> shift) & (NB - 1);
         const u32 dp = __shfl_up(d, 1, WAVE);
         const u64 heads = __ballot(lane == 0 || d != dp);
         if (valid && (lane == 0 || d != dp)) {
@@ -988,37 +992,41 @@ __global__ void radix_hist_kernel(const u32* src, int64_t n, int shift, u32* his
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < NB; i += RS_NT) hist[T.h0 + (size_t)i * T.hstride] = h[i];
+    for (int i = threadIdx.x; i < NB; i += NT) hist[T.h0 + (size_t)i * T.hstride] = h[i];
 }
 
 // Stable scatter: every wave owns a contiguous 1/4 of the tile and ranks its keys round by round (64
 // consecutive keys per round) with ballot matching, so equal digits keep their input order.
-template <int BITS, bool BYTASK>
-__global__ void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, u32* vout, const u32* gofs,
+template <int BITS, bool BYTASK, int NT>
+__global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, u32* vout, const u32* gofs,
                                      int64_t n_all, int shift, int nblk, TaskOf tk, SegTab seg) {
-    constexpr int NB = 1 << BITS, DPT = NB / RS_NT;   // digits per thread in the per-digit phase
-    __shared__ u32 cnt[RS_WAVES][NB];
+    constexpr int NB = 1 << BITS, DPT = NB > NT ? NB / NT : 1;   // digits per thread in the per-digit phase
+    constexpr int TILE = NT * RS_ITEMS, WAVES = NT / WAVE;
+    __shared__ uint16_t cnt[WAVES][NB];
     __shared__ u32 digstart[NB];
-    __shared__ u32 skeys[RS_TILE];
-    __shared__ u32 svals[RS_TILE];
-    __shared__ uint16_t sdig[BYTASK ? RS_TILE : 1];   // the digit of every staged pair (a key names its own)
-    __shared__ int sh_scan[RS_WAVES + 2];
+    __shared__ u32 skeys[TILE];
+    __shared__ u32 svals[TILE];
+    __shared__ uint16_t sdig[BYTASK ? TILE : 1];   // the digit of every staged pair (a key names its own)
+    __shared__ int sh_scan[WAVES + 2];
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
     const int tile = rs_tile_of_block(nblk);
     if (tile >= nblk) return;
-    const RsTile T = rs_tile(seg, tile, nblk, n_all, NB);
+    const RsTile T = rs_tile<TILE>(seg, tile, nblk, n_all, NB);
     if (!T.any) return;
-    for (int i = threadIdx.x; i < RS_WAVES * NB; i += RS_NT) (&cnt[0][0])[i] = 0;
+    for (int i = threadIdx.x; i < WAVES * NB / 2; i += NT) reinterpret_cast<u32*>(&cnt[0][0])[i] = 0;
     __syncthreads();
     const int64_t tile0 = T.k0, n = T.k1;
     u32 key[RS_ITEMS], val[RS_ITEMS], rank[RS_ITEMS], dig[RS_ITEMS];
     const u64 lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
+    for (int r = 0; r < RS_ITEMS; ++r) {   // (as above)
+        const int64_t idx = min(tile0 + (int64_t)w * (WAVE * RS_ITEMS) + r * WAVE + lane, n - 1);
+        key[r] = kin[idx];
+        val[r] = vin[idx];
+    }
+#pragma unroll
     for (int r = 0; r < RS_ITEMS; ++r) {
-        const int64_t idx = tile0 + (int64_t)w * (WAVE * RS_ITEMS) + r * WAVE + lane;
-        const bool valid = idx < n;
-        key[r] = valid ? kin[idx] : 0xFFFFFFFFu;
-        val[r] = valid ? vin[idx] : 0u;
+        const bool valid = tile0 + (int64_t)w * (WAVE * RS_ITEMS) + r * WAVE + lane < n;
         const u32 d = ((BYTASK ? (valid ? rs_task_of(tk, val[r]) : 0u) : key[r] - T.key_base) >> shift) & (NB - 1);
         dig[r] = d;
         u64 peers = __ballot(valid);
@@ -1032,7 +1040,7 @@ __global__ void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, 
         u32 old = 0;
         if (valid && lane == leader) {
             old = cnt[w][d];
-            cnt[w][d] = old + (u32)__popcll(peers);
+            cnt[w][d] = (uint16_t)(old + (u32)__popcll(peers));
         }
         old = __shfl(old, leader, WAVE);
         rank[r] = old + (u32)__popcll(peers & lt_mask);   // (a wave's counters are its own: no barrier between rounds)
@@ -1044,11 +1052,13 @@ __global__ void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, 
 #pragma unroll
     for (int k = 0; k < DPT; ++k) {
         const int d = threadIdx.x * DPT + k;
+        total[k] = 0;
+        if (NB < NT && d >= NB) continue;
         u32 t = 0;
 #pragma unroll
-        for (int ww = 0; ww < RS_WAVES; ++ww) {
+        for (int ww = 0; ww < WAVES; ++ww) {
             const u32 c = cnt[ww][d];
-            cnt[ww][d] = t;
+            cnt[ww][d] = (uint16_t)t;
             t += c;
         }
         total[k] = t;
@@ -1058,7 +1068,8 @@ __global__ void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, 
     u32 ds = (u32)block_excl_scan((int)mine, sh_scan, &tile_count);
 #pragma unroll
     for (int k = 0; k < DPT; ++k) {
-        digstart[threadIdx.x * DPT + k] = ds;
+        const int d = threadIdx.x * DPT + k;
+        if (NB >= NT || d < NB) digstart[d] = ds;
         ds += total[k];
     }
     __syncthreads();
@@ -1074,36 +1085,58 @@ __global__ void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, 
         }
     }
     __syncthreads();
+    u32 at[RS_ITEMS];
 #pragma unroll
     for (int i = 0; i < RS_ITEMS; ++i) {
-        const int pos = i * RS_NT + threadIdx.x;
+        const int pos = min(i * NT + (int)threadIdx.x, tile_count - 1);
+        key[i] = skeys[pos];
+        val[i] = svals[pos];
+        const u32 d = BYTASK ? (u32)sdig[pos] : ((key[i] - T.key_base) >> shift) & (NB - 1);
+        at[i] = gofs[T.h0 + (size_t)d * T.hstride] - digstart[d];
+    }
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; ++i) {
+        const int pos = i * NT + threadIdx.x;
         if (pos < tile_count) {
-            const u32 k = skeys[pos];
-            const u32 d = BYTASK ? (u32)sdig[pos] : ((k - T.key_base) >> shift) & (NB - 1);
-            const size_t dst = (size_t)gofs[T.h0 + (size_t)d * T.hstride] + (pos - digstart[d]);
-            kout[dst] = k;
-            vout[dst] = svals[pos];
+            kout[(size_t)(at[i] + (u32)pos)] = key[i];
+            vout[(size_t)(at[i] + (u32)pos)] = val[i];
         }
     }
 }
 
+// Lists of a million and more are cut into tiles of 512 threads: a digit's run in a tile is twice as long, the count table half
+// as large.  138 million lookups, three passes of 8 bits and one by task, 256 and 512 threads: 3.2 / 2.9 ms.  (Two passes of 10
+// bits instead of the three take 2.05 ms against 2.0, and a table of twice the size.)
+static bool rs_long(int64_t n) { return n >= (int64_t)1 << 20; }
+static int rs_tile_keys(int64_t n) { return (rs_long(n) ? 512 : 256) * RS_ITEMS; }
 // extra_tiles: tiles beyond ceil(n / tile) that a pass over several ranges may need (one per range)
 size_t radix_hist_words(int64_t n, int extra_tiles) {
-    const int64_t nblk = (n + RS_TILE - 1) / RS_TILE + extra_tiles;
+    const int64_t nblk = (n + 256 * RS_ITEMS - 1) / (256 * RS_ITEMS) + extra_tiles;   // (never fewer than a pass has)
     return (size_t)(512 * nblk + 64) + scan_tmp_words(512 * nblk);
 }
 
-template <int BITS, bool BYTASK>
-static void radix_pass(hipStream_t st, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
-                       const TaskOf& tk, const SegTab& seg) {
+template <int BITS, bool BYTASK, int NT>
+static void radix_pass_nt(hipStream_t st, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
+                          const TaskOf& tk, const SegTab& seg) {
     // ranges: at most one partly filled tile per range beyond the tiles of the whole list (the tiles past the last range's
     // write nothing into the count table: what the table holds there stands behind every count and moves none's place)
-    const int nblk = (int)((n + RS_TILE - 1) / RS_TILE) + seg.n_seg;
+    const int nblk = (int)((n + NT * RS_ITEMS - 1) / (NT * RS_ITEMS)) + seg.n_seg;
     u32* scan_tmp = hist + ((size_t)512 * nblk + 63) / 64 * 64;
     const dim3 grid((nblk + 7) / 8 * 8);
-    hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK>), grid, dim3(RS_NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
+    hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK, NT>), grid, dim3(NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
     launch_scan_u32(st, hist, hist, (int64_t)(1 << BITS) * nblk, scan_tmp, nullptr);
-    hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK>), grid, dim3(RS_NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
+    hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK, NT>), grid, dim3(NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
+}
+template <bool BYTASK>
+static void radix_pass(hipStream_t st, int width, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
+                       const TaskOf& tk, const SegTab& seg) {
+    if (rs_long(n)) {
+        if (width <= 8) radix_pass_nt<8, BYTASK, 512>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
+        else radix_pass_nt<9, BYTASK, 512>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
+    } else {
+        if (width <= 8) radix_pass_nt<8, BYTASK, 256>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
+        else radix_pass_nt<9, BYTASK, 256>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
+    }
 }
 
 // Returns the number of passes made: after an odd number the result is in (keys_tmp, vals_tmp).
@@ -1113,13 +1146,11 @@ int launch_radix_sort(hipStream_t st, u32* keys, u32* vals, u32* keys_tmp, u32* 
     const SegTab seg = seg_in ? *seg_in : SegTab{0, nullptr, nullptr, nullptr};
     if (bits < 1) bits = 1;
     if (bits > 32) bits = 32;
-    const int p8 = (bits + 7) / 8, p9 = (bits + 8) / 9;
-    const int width = p9 < p8 ? 9 : 8, passes = p9 < p8 ? p9 : p8;
+    const int passes = (bits + 8) / 9, width = (bits + passes - 1) / passes;
     const TaskOf none{nullptr, nullptr, 0u, 0u, 0, -1};
     u32 *ki = keys, *vi = vals, *ko = keys_tmp, *vo = vals_tmp;
     for (int p = 0; p < passes; ++p) {
-        if (width == 9) radix_pass<9, false>(st, ki, vi, ko, vo, n, width * p, hist, none, seg);
-        else radix_pass<8, false>(st, ki, vi, ko, vo, n, width * p, hist, none, seg);
+        radix_pass<false>(st, width, ki, vi, ko, vo, n, width * p, hist, none, seg);
         u32* t = ki; ki = ko; ko = t;
         t = vi; vi = vo; vo = t;
     }
@@ -1136,13 +1167,11 @@ void launch_task_sort(hipStream_t st, const u32* keys, const u32* vals, u32* mid
     int bits = 1;
     while ((1 << bits) < n_tasks) ++bits;
     const SegTab one{0, nullptr, nullptr, nullptr};
-    if (bits <= 8) {
-        radix_pass<8, true>(st, keys, vals, out_keys, out_vals, n, 0, hist, tk, one);
-    } else if (bits == 9) {
-        radix_pass<9, true>(st, keys, vals, out_keys, out_vals, n, 0, hist, tk, one);
+    if (bits <= 9) {
+        radix_pass<true>(st, bits, keys, vals, out_keys, out_vals, n, 0, hist, tk, one);
     } else {   // (the second pass masks with 8 bits: bits <= 16)
-        radix_pass<8, true>(st, keys, vals, mid_keys, mid_vals, n, 0, hist, tk, one);
-        radix_pass<8, true>(st, mid_keys, mid_vals, out_keys, out_vals, n, 8, hist, tk, one);
+        radix_pass<true>(st, 8, keys, vals, mid_keys, mid_vals, n, 0, hist, tk, one);
+        radix_pass<true>(st, 8, mid_keys, mid_vals, out_keys, out_vals, n, 8, hist, tk, one);
     }
 }
 int task_sort_passes(int n_tasks) { return n_tasks > 512 ? 2 : 1; }

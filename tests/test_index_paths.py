@@ -4,6 +4,8 @@ lookups plus one stable pass by task ("index_path", 2; that row order from one s
 from the fields' ranges sorted by row alone).  All must give the oracle's integer structures bit for bit,
 and a meta step must come out identical whichever built them.
 """
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -114,3 +116,33 @@ def test_row_order_path_refuses_a_row_list_over_several_waves(gm):
     ctx.configure("index_path", 0)
     _compare_step(cfg, ctx, sup, qry, params, 1, 2, TOL_FP32, "row list over several waves, default path")
     ctx.close()
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 4097])      # lookups beyond 2^20, from where on the ordering's tiles are larger
+@pytest.mark.parametrize("rows", [100, 300_000])
+def test_long_lists(gm, extra, rows):
+    """The same dictionaries whichever way a list around the length at which the radix tiles change is ordered, and torch's segments."""
+    T, F, n = 40, 2, (1 << 20) + extra
+    gen = torch.Generator().manual_seed(n + rows)
+
+    def some(lookups, samples=320):
+        cuts = torch.randint(0, lookups + 1, (T * samples * F - 1,), generator=gen).sort().values
+        idx = (torch.rand(lookups, generator=gen) ** 4 * rows).int().clamp(max=rows - 1)
+        off = torch.cat([torch.zeros(1, dtype=torch.int64), cuts, torch.full((1,), lookups)])
+        return SimpleNamespace(task_offsets=np.arange(T + 1, dtype=np.int64) * samples, bag_offsets=off.cuda(), indices=idx.cuda(),
+                               dense=torch.zeros(T * samples, 1, device="cuda"), labels=torch.zeros(T * samples, device="cuda"))
+    sup, qry = some(n // 3), some(n - n // 3)
+    got = []
+    for path, by_field in ((1, 1), (2, 0), (2, 1)):
+        ctx = gm(F, [rows] * F, 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 30)
+        ctx.configure("index_path", path)
+        ctx.configure("sort_fields", by_field)
+        got.append(ctx.index_prep(sup, qry))
+        ctx.close()
+    keys = torch.cat([s.indices.long() + rows * torch.repeat_interleave(torch.arange(len(s.bag_offsets) - 1, device="cuda") % F, s.bag_offsets.diff())
+                      for s in (sup, qry)])
+    want, counts = torch.unique(keys, return_counts=True)
+    for g in got:
+        assert torch.equal(g["emb_rows"], want) and torch.equal(g["seg_counts"], counts)
+        for k in ("slot_counts", "slot_rows", "sup_slot", "qry_slot"):
+            assert torch.equal(g[k], got[0][k]), k
