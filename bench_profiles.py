@@ -27,7 +27,7 @@ FAMILIES = {
     "pair_hop": r"pair_hop_(small_)?kernel",
     "pair_count": r"pair_count_kernel",
     "two_hop": r"two_hop_kernel",
-    "seg_reduce": r"seg_reduce_(chunks|join)_kernel",
+    "seg_reduce": r"seg_reduce_(chunks|hot|hot_list|join)_kernel",
     "gather_pool": r"gather_pool(_xcd)?_kernel",
     # radix_*_kernel<BITS, BYTASK>: the pass by task belongs to the per-(task, field) dictionaries (with the join that reads
     # them off the ordered list), the passes by row key to the ordering of the lookups by row

@@ -257,7 +257,8 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows,
                        int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
                        float* emb_grad, float* partial /* seg_reduce_partial_floats(n, D), for D <= 16 with n + radix_hist_words(n, F) more */,
-                       float* table /* null, or [all rows, D]: scale * every segment is ADDED to its row instead of listed */, float scale);
+                       float* table /* null, or [all rows, D]: scale * every segment is ADDED to its row instead of listed */, float scale,
+                       int64_t gx_rows /* of gx, each of F * D */, u32* room /* radix_hist_words(n, F) words */);
 size_t seg_reduce_partial_floats(int64_t n, int D);
 void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows, const float* grad,
                         int64_t n_rows, float scale);

@@ -2384,7 +2384,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             {
                 Prof p(c, "seg_reduce", (double)nw * (4.0 * D + 4), 0);
                 launch_seg_reduce(st, D, F, ordered ? enc : kPlainVals, w.so.keys, w.so.keys_tmp, nullptr, nw, nw, w.so.vals, w.GX,
-                                  nullptr, seg_room(c, w.so), row_table, row_scale);
+                                  nullptr, seg_room(c, w.so), row_table, row_scale, d.Ps + d.Pq, w.so.hist);
             }
             if (side_table) HIPCHK(c, hipEventRecord(c->ev_main, st));
         } else if (ordered) {
@@ -2411,7 +2411,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         if (F > 0) {
             Prof p(c, "seg_reduce", (double)nnz * (4.0 * D + 4), 0);
             launch_seg_reduce(st, D, F, (pre || list_ordered) ? enc : kPlainVals, b.so.keys, b.so.keys_tmp, n_list, apply ? nnz : capacity, nnz,
-                              b.so.vals, b.GX, out->emb_grad, seg_room(c, b.so), row_table, row_scale);
+                              b.so.vals, b.GX, out->emb_grad, seg_room(c, b.so), row_table, row_scale, Ps_tot + B.poff_q[T], b.so.hist);
         }
     }
     if (up) up->done = apply;

@@ -1,5 +1,8 @@
 """The sparse gradient's sums over short lists of narrow rows: lists whose partial rows leave room for chunks of 16, of 32 (one
 field, about 20000 lookups of 16 columns), and lists beyond 32768 lookups, in chunks of 64; row-list and table-shaped output."""
+from types import SimpleNamespace
+
+import numpy as np
 import pytest
 import torch
 
@@ -42,3 +45,68 @@ def test_long_segments(gm, dim, n_rows, tasks):  # noqa: F811
     m = int(out["n_emb_rows"].item())
     assert torch.equal(table[out["emb_rows"][:m]], out["emb_grad"][:m]), "the same order either way"
     ctx.close()
+
+
+@pytest.mark.parametrize("dim,fields,lookups,mode", [(32, 3, (1 << 22) + 4097, "plain"), (64, 2, (1 << 22) + 255, "ordered"), (128, 1, 1 << 22, "plain"),
+                                                     (64, 2, (1 << 22) - 1, "ordered")])
+def test_chunks_inside_long_segments(gm, dim, fields, lookups, mode):  # noqa: F811
+    """Lists long enough for the chunks inside long segments to be taken in another order (and one just too short): a row with a
+    quarter of a field's lookups, some of thousands, rows of one, a last block that is not full; values in both forms.  A row's sum is
+    64 terms a chunk and then its chunks one after the other, so it is off by at most that many roundings of the sum of magnitudes."""
+    T, R, samples = 150 // fields, 5_000, 512
+    gen = torch.Generator().manual_seed(dim)
+    n = lookups // 2
+
+    def some(n):
+        off = torch.cat([torch.zeros(1, dtype=torch.int64), torch.randint(0, n + 1, (T * samples * fields - 1,), generator=gen).sort().values, torch.full((1,), n)])
+        idx = (torch.rand(n, generator=gen) ** 6 * R).int().clamp(max=R - 1)
+        idx[torch.rand(n, generator=gen) < 0.25] = 7
+        return SimpleNamespace(task_offsets=np.arange(T + 1, dtype=np.int64) * samples, bag_offsets=off.cuda(), indices=idx.cuda(),
+                               dense=torch.randn(T * samples, 1, generator=gen).cuda(), labels=(torch.rand(T * samples, generator=gen) < 0.3).float().cuda())
+    sup, qry = some(lookups - n), some(n)
+    W = torch.randn(fields * dim + 1, 1, generator=gen).cuda() / dim
+    params = SimpleNamespace(emb=torch.randn(fields * R, dim, generator=gen).cuda() * 0.01, W=[W], b=[torch.zeros(1, device="cuda")])
+    ctx = gm(fields, [R] * fields, dim, 1, [fields * dim + 1, 1], 0, workspace_bytes=6 << 30)
+    if mode == "plain":
+        ctx.configure("adapt_rows", 0)
+    else:
+        ctx.configure("index_path", 2)
+    out = ctx.meta_step(sup, qry, params, 0.1, 0 if mode == "plain" else 1, 1)
+    m = int(out["n_emb_rows"].item())
+    got = torch.zeros(fields * R, dim, dtype=torch.float64, device="cuda")
+    got[out["emb_rows"][:m]] = out["emb_grad"][:m].double()
+    table = torch.zeros_like(params.emb)
+    ctx.meta_step(sup, qry, params, 0.1, 0 if mode == "plain" else 1, 1, emb_grad_table=table)
+    ctx.close()
+    assert torch.equal(table.double(), got)
+
+    def pool(s, emb):
+        bag = torch.repeat_interleave(torch.arange(T * samples * fields, device="cuda"), s.bag_offsets.diff())
+        row = s.indices.long() + bag % fields * R
+        return bag, row, torch.zeros(T * samples * fields, dim, dtype=torch.float64, device="cuda").index_add_(0, bag, emb[row])
+    emb, w, b = params.emb.double(), W.double().repeat(1, T).T.contiguous(), torch.zeros(T, dtype=torch.float64, device="cuda")
+    task = torch.arange(T * samples, device="cuda") // samples
+    if mode == "ordered":   # one inner step: a task's rows, weights and bias
+        bag, row, x = pool(sup, emb)
+        x = torch.cat([x.view(T * samples, -1), sup.dense.double()], 1)
+        dz = (torch.sigmoid((x * w[task]).sum(1)) - sup.labels.double()) / samples
+        w1 = w - 0.1 * torch.zeros_like(w).index_add_(0, task, dz[:, None] * x)
+        b = b - 0.1 * torch.zeros_like(b).index_add_(0, task, dz)
+        dx = (dz[:, None] * w[task])[:, :-1].reshape(T * samples * fields, dim)
+        cell = task[bag // fields] * (fields * R) + row
+        own = torch.zeros(T * fields * R, dim, dtype=torch.float64, device="cuda").index_add_(0, cell, dx[bag])
+        own = emb.repeat(T, 1) - 0.1 * own
+        bag, row, _ = pool(qry, emb)
+        xq = torch.zeros(T * samples * fields, dim, dtype=torch.float64, device="cuda").index_add_(0, bag, own[task[bag // fields] * (fields * R) + row])
+        w = w1
+    else:
+        bag, row, xq = pool(qry, emb)
+    xq = torch.cat([xq.view(T * samples, -1), qry.dense.double()], 1)
+    dz = (torch.sigmoid((xq * w[task]).sum(1) + b[task]) - qry.labels.double()) / samples
+    dx = (dz[:, None] * w[task])[:, :-1].reshape(T * samples * fields, dim)
+    want = torch.zeros_like(got).index_add_(0, row, dx[bag])
+    size = torch.zeros_like(got).index_add_(0, row, dx[bag].abs())
+    scale = float((got * want).sum() / (want * want).sum())
+    assert abs(scale * T - 1) < 1e-4 or abs(scale - 1) < 1e-4    # (a mean or a sum over the tasks)
+    terms = 64 + torch.bincount(row, minlength=fields * R).max().item() / 64 + 8 * dim * fields   # (.. and the logit's own terms)
+    assert bool(((got / scale - want).abs() <= terms * 2.0 ** -24 * size + 1e-12).all())
