@@ -26,6 +26,8 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef u32 u32x2 __attribute__((ext_vector_type(2)));
+typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 
 // What an epilogue does is fixed at compile time for the launches the step makes (EP >= 0: bits 0-2 the fused
 // operation, then whether the fp32 output, the bf16 output, the accumulate-into output and the added input exist), so
@@ -56,6 +58,25 @@ struct EpiFlags {
 // different rows per instruction, which the memory pipeline takes several times longer over than whole row segments
 // (256 x 256 tiles: 32 -> 26 thousand cycles forward, 56 -> 33 backward).  So every wave passes its accumulators through
 // LDS one 32-row strip at a time, applies the fused operation on 4 consecutive columns per lane and writes whole row segments.
+// Memory is reached through buffers of the wave's rows: a 32-bit offset per access, nothing done past the last row or column,
+// no branch.  With 64-bit addresses and a test per row these were a third and more of a short product's vector instructions, the
+// multiplications at a quarter of the rate (a wave of a 128 x 128 weight-gradient tile: 678 -> 376), and a strip's reads were
+// waited for with the stores before them.  700 tasks of a median 32 rows 25.7 -> 25.1 ms, 512 of 256 rows 31.8 -> 31.2, 3 of 512
+// rows 1561 -> 1529 us.
+struct EpiBuffer {   // rows [first, first + rows) of a row-major matrix, from column n on; lanes that hold no column touch nothing
+    __amdgpu_buffer_rsrc_t rs;
+    u32 at, ld;      // bytes
+    __device__ __forceinline__ EpiBuffer(const void* p, int64_t row, int64_t ld_elems, int elem, int rows, int er, int n, bool nok) {
+        ld = (u32)ld_elems * (u32)elem;
+        rs = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<const char*>(p) + row * ld_elems * elem), 0, (int)((u32)rows * ld), 0x00020000);
+        at = nok ? (u32)er * ld + (u32)n * (u32)elem : 1u << 31;   // (a wave's 128 rows of less than 2^21 columns stay below 2^30)
+    }
+    __device__ __forceinline__ int off(int r) const { return (int)(at + (u32)r * ld); }
+    __device__ __forceinline__ float4 load4(int r) const { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off(r), 0, 0)); }
+    __device__ __forceinline__ uint2 load2(int r) const { return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, off(r), 0, 0)); }
+    __device__ __forceinline__ void store(int r, float4 v) const { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off(r), 0, 0); }
+    __device__ __forceinline__ void store(int r, uint2 v) const { __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, off(r), 0, 0); }
+};
 template <int BM, int BN, int MI, int NI, int EP>
 __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[MI][NI], bf16_t* smem, int g, int64_t r0, int m0,
                                               int n0, int M, int N, int wm0, int wn0, int lane, int wave) {
@@ -64,53 +85,57 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
     const bool has_bias = (fl.epi == EPI_BIAS_RELU || fl.epi == EPI_BIAS_MASK) && a.bias;
     const bool has_mask = fl.epi == EPI_BIAS_MASK || fl.epi == EPI_MASK;
     const bool has_cin = fl.cin, has_acc = fl.cacc;
-    const float* bias = has_bias ? a.bias + (int64_t)g * a.gBias : nullptr;
-    const bf16_t* mask = has_mask ? a.mask + r0 * a.ld_mask : nullptr;
-    const float* Cin = has_cin ? a.Cin + (int64_t)g * a.gCin : nullptr;
-    float* Cf = fl.cf ? a.Cf + (int64_t)g * a.gCf + r0 * a.rCf : nullptr;
-    float* Cacc = has_acc ? a.Cacc + r0 * a.rCacc : nullptr;
-    bf16_t* Cb = fl.cb ? a.Cb + (int64_t)g * a.gCb + r0 * a.rCb + (fl.epi == EPI_SPLIT ? (int64_t)blockIdx.y * a.ext.slot : 0) : nullptr;
     constexpr int SW = NI * 32, ELD = SW + 4;      // strip width, LDS row stride (floats)
     constexpr int LPR = SW / 4, RPI = 64 / LPR;    // lanes per strip row, rows per pass
+    constexpr int IT = 32 / RPI;
     float* E = reinterpret_cast<float*>(smem) + wave * (32 * ELD);
     const int er = lane / LPR, ec = (lane % LPR) * 4;
-    const int n = n0 + wn0 + ec;
+    const int n = n0 + wn0 + ec, mw = __builtin_amdgcn_readfirstlane(m0 + wm0), rows = __builtin_amdgcn_readfirstlane(max(min(M - mw, MI * 32), 0));   // (uniform, as buffers have to be)
     const bool nok = n < N;
+    auto buffer = [&](const void* p, bool on, int64_t g_off, int64_t row, int64_t ld, int elem) {   // element (mw + r, n) is row r
+        return EpiBuffer(reinterpret_cast<const char*>(p) + (on ? g_off * elem : 0), on ? row + mw : 0, ld, elem, on ? rows : 0, er, n, nok);
+    };
+    const EpiBuffer mask = buffer(a.mask, has_mask, 0, r0, a.ld_mask, 2);
+    const EpiBuffer cin = buffer(a.Cin, has_cin, (int64_t)g * a.gCin, 0, a.ldcin, 4);
+    const EpiBuffer cacc = buffer(a.Cacc, has_acc, r0 * a.rCacc, 0, a.ldcacc, 4);
+    const EpiBuffer cf = buffer(a.Cf, fl.cf, (int64_t)g * a.gCf + r0 * a.rCf, 0, a.ldcf, 4);
+    const EpiBuffer cb = buffer(a.Cb, fl.cb, (int64_t)g * a.gCb + r0 * a.rCb + (fl.epi == EPI_SPLIT ? (int64_t)blockIdx.y * a.ext.slot : 0), 0, a.ldcb, 2);
     float4 bn = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (has_bias && nok) bn = *reinterpret_cast<const float4*>(bias + n);
+    if (has_bias && nok) bn = *reinterpret_cast<const float4*>(a.bias + (int64_t)g * a.gBias + n);
+    // What a strip reads from memory is requested before anything of the strip before it is stored: the outputs may alias the
+    // inputs (an in-place update, element by element), which would otherwise chain every load behind the previous store.
+    const bool read_acc = has_acc && !a.cacc_init;
+    uint2 mk_all[2][IT];
+    float4 ci_all[2][IT];
+    auto request = [&](int i, uint2 (&mk)[IT], float4 (&ci)[IT]) {
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int r = i * 32 + it * RPI;
+            if (has_mask) mk[it] = mask.load2(r);
+            if (has_cin) ci[it] = cin.load4(r);
+            else if (read_acc) ci[it] = cacc.load4(r);
+            else ci[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    request(0, mk_all[0], ci_all[0]);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        // What the strip reads from memory is requested before anything of it is stored: the outputs may alias
-        // the inputs (an in-place update), which would otherwise chain every load behind the previous store.
-        uint2 mk_all[32 / RPI];
-        float4 ci_all[32 / RPI];
-#pragma unroll
-        for (int it = 0; it < 32 / RPI; ++it) {
-            const int m = m0 + wm0 + i * 32 + it * RPI + er;
-            const bool ok = nok && m < M;
-            mk_all[it] = make_uint2(0u, 0u);
-            ci_all[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ok && has_mask) mk_all[it] = *reinterpret_cast<const uint2*>(mask + (int64_t)m * a.ld_mask + n);
-            if (ok && has_cin) ci_all[it] = *reinterpret_cast<const float4*>(Cin + (int64_t)m * a.ldcin + n);
-            if (ok && has_acc && !a.cacc_init) ci_all[it] = *reinterpret_cast<const float4*>(Cacc + (int64_t)m * a.ldcacc + n);
-        }
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<float4*>(E + l32 * ELD + j * 32 + 8 * q + 4 * lhi) =
                     make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+        if (i + 1 < MI) request(i + 1, mk_all[(i + 1) & 1], ci_all[(i + 1) & 1]);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the strip is this wave's own: LDS order within the wave suffices
 #pragma unroll
-        for (int it = 0; it < 32 / RPI; ++it) {
-            const int rr = it * RPI + er;
-            const int m = m0 + wm0 + i * 32 + rr;
-            if (!nok || m >= M) continue;
-            float4 x = *reinterpret_cast<const float4*>(E + rr * ELD + ec);
+        for (int it = 0; it < IT; ++it) {
+            const int r = i * 32 + it * RPI;
+            float4 x = *reinterpret_cast<const float4*>(E + (it * RPI + er) * ELD + ec);
             if (fl.epi == EPI_BIAS_RELU) {
                 x = make_float4(fmaxf(x.x + bn.x, 0.f), fmaxf(x.y + bn.y, 0.f), fmaxf(x.z + bn.z, 0.f), fmaxf(x.w + bn.w, 0.f));
             } else if (has_mask) {
-                const uint2 mk = mk_all[it];
+                const uint2 mk = mk_all[i & 1][it];
                 if (fl.epi == EPI_BIAS_MASK) x = make_float4(x.x + bn.x, x.y + bn.y, x.z + bn.z, x.w + bn.w);
                 // a bf16 is positive iff it is neither zero nor has its sign bit set
                 const u32 h0 = mk.x & 0xffffu, h1 = mk.x >> 16, h2 = mk.y & 0xffffu, h3 = mk.y >> 16;
@@ -119,17 +144,17 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
                 x.z = (h2 != 0 && h2 < 0x8000u) ? x.z : 0.f;
                 x.w = (h3 != 0 && h3 < 0x8000u) ? x.w : 0.f;
             } else if (fl.epi == EPI_AXPBY) {
-                x = make_float4(a.c1 * x.x, a.c1 * x.y, a.c1 * x.z, a.c1 * x.w);
-                if (has_cin) {
-                    const float4 ci = ci_all[it];
-                    x = make_float4(x.x + a.c0 * ci.x, x.y + a.c0 * ci.y, x.z + a.c0 * ci.z, x.w + a.c0 * ci.w);
+                if (has_cin) {   // (fmaf: the same rounding in every instance)
+                    const float4 ci = ci_all[i & 1][it];
+                    x = make_float4(fmaf(a.c1, x.x, a.c0 * ci.x), fmaf(a.c1, x.y, a.c0 * ci.y), fmaf(a.c1, x.z, a.c0 * ci.z), fmaf(a.c1, x.w, a.c0 * ci.w));
+                } else {
+                    x = make_float4(a.c1 * x.x, a.c1 * x.y, a.c1 * x.z, a.c1 * x.w);
                 }
             }
-            if (fl.cf) *reinterpret_cast<float4*>(Cf + (int64_t)m * a.ldcf + n) = x;
+            if (fl.cf) cf.store(r, x);
             if (has_acc) {
-                const float4 ci = ci_all[it];
-                *reinterpret_cast<float4*>(Cacc + (int64_t)m * a.ldcacc + n) =
-                    make_float4(ci.x + a.cacc * x.x, ci.y + a.cacc * x.y, ci.z + a.cacc * x.z, ci.w + a.cacc * x.w);
+                const float4 ci = ci_all[i & 1][it];
+                cacc.store(r, make_float4(fmaf(a.cacc, x.x, ci.x), fmaf(a.cacc, x.y, ci.y), fmaf(a.cacc, x.z, ci.z), fmaf(a.cacc, x.w, ci.w)));
             }
             if (fl.epi == EPI_SPLIT) {
                 const float c = a.ext.c[blockIdx.y];
@@ -139,12 +164,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
                 uint2 pk;
                 pk.x = f2bf2(x.x, x.y);
                 pk.y = f2bf2(x.z, x.w);
-                *reinterpret_cast<uint2*>(Cb + (int64_t)m * a.ldcb + n) = pk;
+                cb.store(r, pk);
                 if (fl.epi == EPI_SPLIT) {
                     uint2 lo;
                     lo.x = f2bf2(x.x - bf2f((bf16_t)(pk.x & 0xffffu)), x.y - bf2f((bf16_t)(pk.x >> 16)));
                     lo.y = f2bf2(x.z - bf2f((bf16_t)(pk.y & 0xffffu)), x.w - bf2f((bf16_t)(pk.y >> 16)));
-                    *reinterpret_cast<uint2*>(Cb + (int64_t)m * a.ldcb + a.ext.ld + n) = lo;
+                    EpiBuffer low = cb;
+                    if (nok) low.at += (u32)a.ext.ld * 2u;
+                    low.store(r, lo);
                 }
             }
         }
@@ -169,7 +196,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
 // Against four waves of 128 x 128 each with the same two stages: backward 687 -> 648 us, forward 341 -> 312 and 439 -> 423,
 // weight gradients 616 -> 549 a task, 1107 -> 1080 over runs of tasks.  Eight waves that park the next tile before the first step:
 // backward 682, weight gradients over runs 1222; parked between steps without reading ahead: 662, 1098.
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 // One product of a sum: its operands from the tile's first row (or, contraction-slowest, from the group's first row) on, row
 // strides in bytes, contraction length.  on false: nothing is read.
 struct GemmOp {
