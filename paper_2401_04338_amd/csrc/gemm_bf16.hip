@@ -26,8 +26,6 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 
 // What an epilogue does is fixed at compile time for the launches the step makes (EP >= 0: bits 0-2 the fused
 // operation, then whether the fp32 output, the bf16 output, the accumulate-into output and the added input exist), so
@@ -58,25 +56,11 @@ struct EpiFlags {
 // different rows per instruction, which the memory pipeline takes several times longer over than whole row segments
 // (256 x 256 tiles: 32 -> 26 thousand cycles forward, 56 -> 33 backward).  So every wave passes its accumulators through
 // LDS one 32-row strip at a time, applies the fused operation on 4 consecutive columns per lane and writes whole row segments.
-// Memory is reached through buffers of the wave's rows: a 32-bit offset per access, nothing done past the last row or column,
+// Memory is reached through buffers of the wave's rows (RowBuffer): a 32-bit offset per access, nothing done past the last row or column,
 // no branch.  With 64-bit addresses and a test per row these were a third and more of a short product's vector instructions, the
 // multiplications at a quarter of the rate (a wave of a 128 x 128 weight-gradient tile: 678 -> 376), and a strip's reads were
 // waited for with the stores before them.  700 tasks of a median 32 rows 25.7 -> 25.1 ms, 512 of 256 rows 31.8 -> 31.2, 3 of 512
 // rows 1561 -> 1529 us.
-struct EpiBuffer {   // rows [first, first + rows) of a row-major matrix, from column n on; lanes that hold no column touch nothing
-    __amdgpu_buffer_rsrc_t rs;
-    u32 at, ld;      // bytes
-    __device__ __forceinline__ EpiBuffer(const void* p, int64_t row, int64_t ld_elems, int elem, int rows, int er, int n, bool nok) {
-        ld = (u32)ld_elems * (u32)elem;
-        rs = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<const char*>(p) + row * ld_elems * elem), 0, (int)((u32)rows * ld), 0x00020000);
-        at = nok ? (u32)er * ld + (u32)n * (u32)elem : 1u << 31;   // (a wave's 128 rows of less than 2^21 columns stay below 2^30)
-    }
-    __device__ __forceinline__ int off(int r) const { return (int)(at + (u32)r * ld); }
-    __device__ __forceinline__ float4 load4(int r) const { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off(r), 0, 0)); }
-    __device__ __forceinline__ uint2 load2(int r) const { return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, off(r), 0, 0)); }
-    __device__ __forceinline__ void store(int r, float4 v) const { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off(r), 0, 0); }
-    __device__ __forceinline__ void store(int r, uint2 v) const { __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, off(r), 0, 0); }
-};
 template <int BM, int BN, int MI, int NI, int EP>
 __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[MI][NI], bf16_t* smem, int g, int64_t r0, int m0,
                                               int n0, int M, int N, int wm0, int wn0, int lane, int wave) {
@@ -93,13 +77,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
     const int n = n0 + wn0 + ec, mw = __builtin_amdgcn_readfirstlane(m0 + wm0), rows = __builtin_amdgcn_readfirstlane(max(min(M - mw, MI * 32), 0));   // (uniform, as buffers have to be)
     const bool nok = n < N;
     auto buffer = [&](const void* p, bool on, int64_t g_off, int64_t row, int64_t ld, int elem) {   // element (mw + r, n) is row r
-        return EpiBuffer(reinterpret_cast<const char*>(p) + (on ? g_off * elem : 0), on ? row + mw : 0, ld, elem, on ? rows : 0, er, n, nok);
+        return RowBuffer(reinterpret_cast<const char*>(p) + (on ? g_off * elem : 0), on ? row + mw : 0, ld, elem, on ? rows : 0, er, n, nok);
     };
-    const EpiBuffer mask = buffer(a.mask, has_mask, 0, r0, a.ld_mask, 2);
-    const EpiBuffer cin = buffer(a.Cin, has_cin, (int64_t)g * a.gCin, 0, a.ldcin, 4);
-    const EpiBuffer cacc = buffer(a.Cacc, has_acc, r0 * a.rCacc, 0, a.ldcacc, 4);
-    const EpiBuffer cf = buffer(a.Cf, fl.cf, (int64_t)g * a.gCf + r0 * a.rCf, 0, a.ldcf, 4);
-    const EpiBuffer cb = buffer(a.Cb, fl.cb, (int64_t)g * a.gCb + r0 * a.rCb + (fl.epi == EPI_SPLIT ? (int64_t)blockIdx.y * a.ext.slot : 0), 0, a.ldcb, 2);
+    const RowBuffer mask = buffer(a.mask, has_mask, 0, r0, a.ld_mask, 2);
+    const RowBuffer cin = buffer(a.Cin, has_cin, (int64_t)g * a.gCin, 0, a.ldcin, 4);
+    const RowBuffer cacc = buffer(a.Cacc, has_acc, r0 * a.rCacc, 0, a.ldcacc, 4);
+    const RowBuffer cf = buffer(a.Cf, fl.cf, (int64_t)g * a.gCf + r0 * a.rCf, 0, a.ldcf, 4);
+    const RowBuffer cb = buffer(a.Cb, fl.cb, (int64_t)g * a.gCb + r0 * a.rCb + (fl.epi == EPI_SPLIT ? (int64_t)blockIdx.y * a.ext.slot : 0), 0, a.ldcb, 2);
     float4 bn = make_float4(0.f, 0.f, 0.f, 0.f);
     if (has_bias && nok) bn = *reinterpret_cast<const float4*>(a.bias + (int64_t)g * a.gBias + n);
     // What a strip reads from memory is requested before anything of the strip before it is stored: the outputs may alias the
@@ -169,7 +153,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
                     uint2 lo;
                     lo.x = f2bf2(x.x - bf2f((bf16_t)(pk.x & 0xffffu)), x.y - bf2f((bf16_t)(pk.x >> 16)));
                     lo.y = f2bf2(x.z - bf2f((bf16_t)(pk.y & 0xffffu)), x.w - bf2f((bf16_t)(pk.y >> 16)));
-                    EpiBuffer low = cb;
+                    RowBuffer low = cb;
                     if (nok) low.at += (u32)a.ext.ld * 2u;
                     low.store(r, lo);
                 }

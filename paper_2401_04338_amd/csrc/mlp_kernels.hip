@@ -160,34 +160,52 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& a, int n_ntiles, i
 #pragma unroll
                     for (int r = 0; r < R; ++r)
 #pragma unroll
-                        for (int c = 0; c < R; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[kb & 1][r][j], fb[kb & 1][c][j], acc[r][c], 0, 0, 0);
+                        for (int c = 0; c < R; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[kb & 1][c][j], fa[kb & 1][r][j], acc[r][c], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
 
-    float* C = a.C + (int64_t)g * a.gC + r0 * a.rC;
-    const float* bias = a.bias ? a.bias + (int64_t)g * a.gBias : nullptr;
-    const float* mask = a.mask ? a.mask + r0 * a.ld_mask : nullptr;
-    const float* Cin = a.Cin ? a.Cin + (int64_t)g * a.gCin + r0 * a.rCin : nullptr;
-    auto emit = [&](int m, int n, float v) {   // (fmaf: the same rounding in every instance)
-        if (m >= M || n >= N) return;
-        switch (a.epi) {
-            case EPI_BIAS_RELU: v = fmaxf(v + bias[n], 0.f); break;
-            case EPI_BIAS_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v + bias[n] : 0.f; break;
-            case EPI_MASK: v = (mask[(int64_t)m * a.ld_mask + n] > 0.f) ? v : 0.f; break;
-            case EPI_AXPBY: v = fmaf(a.c1, v, Cin ? a.c0 * Cin[(int64_t)m * a.ldc + n] : 0.f); break;
-            default: break;
+    // The first operand of the MFMAs is B's, so a lane holds row li of a block and its columns 4 q .. 4 q + 3: 16 bytes an access
+    // (widths and strides are multiples of 4) through a buffer.  Element by element, with 64-bit addresses and a test each, this took
+    // more vector instructions than the products of a short contraction (756 of a wave, now 404): 64 tasks x (128 + 128) rows through
+    // 845-256-128-1 a gradient launch 59 -> 56 us, a forward one 35 -> 32, the step 1277 -> 1230.
+    // All that is read is requested before anything is stored (an update may be in place).
+    const int rows = __builtin_amdgcn_readfirstlane(max(min(M - m0, (int)TT::T), 0));
+    const bool has_bias = a.epi == EPI_BIAS_RELU || a.epi == EPI_BIAS_MASK, has_mask = a.epi == EPI_BIAS_MASK || a.epi == EPI_MASK;
+    const bool axpby = a.epi == EPI_AXPBY, has_cin = axpby && a.Cin;
+    f32x4 in[R][R], bias[R];
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+        const int n = n0 + nb + c * 16 + q * 4;
+        const bool nok = n < N;
+        bias[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (has_bias && nok) bias[c] = *reinterpret_cast<const f32x4*>(a.bias + (int64_t)g * a.gBias + n);
+        const RowBuffer src(has_mask ? a.mask + r0 * a.ld_mask : a.Cin + (int64_t)g * a.gCin + r0 * a.rCin, m0, has_mask ? a.ld_mask : a.ldc, 4,
+                            has_mask || has_cin ? rows : 0, mb + li, n, nok);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            in[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (has_mask || has_cin) in[r][c] = __builtin_bit_cast(f32x4, src.load4(r * 16));
         }
-        C[(int64_t)m * a.ldc + n] = v;
-    };
-    // a lane holds column li and rows 4 q .. 4 q + 3 of a block
+    }
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+    for (int c = 0; c < R; ++c) {
+        const int n = n0 + nb + c * 16 + q * 4;
+        const RowBuffer dst(a.C + (int64_t)g * a.gC + r0 * a.rC, m0, a.ldc, 4, rows, mb + li, n, n < N);
 #pragma unroll
-        for (int c = 0; c < R; ++c)
+        for (int r = 0; r < R; ++r) {
+            float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) emit(m0 + mb + r * 16 + q * 4 + i, n0 + nb + c * 16 + li, acc[r][c][i]);
+            for (int i = 0; i < 4; ++i) {   // (fmaf: the same rounding in every instance)
+                v[i] = has_bias ? acc[r][c][i] + bias[c][i] : acc[r][c][i];
+                if (a.epi == EPI_BIAS_RELU) v[i] = fmaxf(v[i], 0.f);
+                if (has_mask) v[i] = in[r][c][i] > 0.f ? v[i] : 0.f;
+                if (axpby) v[i] = fmaf(a.c1, acc[r][c][i], has_cin ? a.c0 * in[r][c][i] : 0.f);
+            }
+            dst.store(r * 16, make_float4(v[0], v[1], v[2], v[3]));
+        }
+    }
 }
 
 template <bool SMALL, bool KA, bool KB>
