@@ -922,22 +922,29 @@ __device__ __forceinline__ u32 rs_task_of(const TaskOf& m, u32 val) {
 // share of the digit-count table is laid out [digit][tile of the range] behind the shares of the ranges before it, so
 // that ONE exclusive scan over the whole table still yields every (range, digit, tile)'s place in the output; the
 // digit is taken from the key minus the range's key base.  seg.n_seg == 0: one range, the whole list.
+// FEW: few tiles.  The table is [tile][digit] and nobody scans it: every workgroup of the scatter adds up its range's counts itself,
+// beside its first loads (the scan was a launch of one workgroup, RS_FEW_TILES).
 struct RsTile {
     int64_t k0, k1;      // keys of the tile
     u32 key_base;        // subtracted from a key before its digit is taken
     size_t h0;           // count-table index of (digit 0, this tile)
     size_t hstride;      // ... and the distance between digits
+    int64_t pos0;        // the range's first key,
+    int t0, nt;          // first tile and number of tiles
     bool any;
 };
-template <int TILE>
+template <int TILE, bool FEW>
 __device__ __forceinline__ RsTile rs_tile(const SegTab& seg, int tile, int nblk, int64_t n, int nb) {
     RsTile t;
     if (seg.n_seg == 0) {
         t.k0 = (int64_t)tile * TILE;
         t.k1 = min(n, t.k0 + TILE);
         t.key_base = 0u;
-        t.h0 = (size_t)tile;
-        t.hstride = (size_t)nblk;
+        t.h0 = FEW ? (size_t)tile * nb : (size_t)tile;
+        t.hstride = FEW ? 1 : (size_t)nblk;
+        t.pos0 = 0;
+        t.t0 = 0;
+        t.nt = nblk;
         t.any = tile < nblk;
         return t;
     }
@@ -952,18 +959,21 @@ __device__ __forceinline__ RsTile rs_tile(const SegTab& seg, int tile, int nblk,
     t.k0 = (int64_t)seg.key_base_pos[lo] + (int64_t)((u32)tile - tb) * TILE;
     t.k1 = min((int64_t)seg.key_base_pos[lo + 1], t.k0 + TILE);
     t.key_base = seg.key_sub[lo];
-    t.hstride = (size_t)(te - tb);
-    t.h0 = (size_t)nb * tb + ((u32)tile - tb);
+    t.hstride = FEW ? 1 : (size_t)(te - tb);
+    t.h0 = FEW ? (size_t)tile * nb : (size_t)nb * tb + ((u32)tile - tb);
+    t.pos0 = (int64_t)seg.key_base_pos[lo];
+    t.t0 = (int)tb;
+    t.nt = (int)(te - tb);
     return t;
 }
 
-template <int BITS, bool BYTASK, int NT>
+template <int BITS, bool BYTASK, int NT, bool FEW>
 __global__ __launch_bounds__(NT) void radix_hist_kernel(const u32* src, int64_t n, int shift, u32* hist, int nblk, TaskOf tk, SegTab seg) {
     constexpr int NB = 1 << BITS;
     __shared__ u32 h[NB];
     const int tile = rs_tile_of_block(nblk);
     if (tile >= nblk) return;
-    const RsTile T = rs_tile<NT * RS_ITEMS>(seg, tile, nblk, n, NB);
+    const RsTile T = rs_tile<NT * RS_ITEMS, FEW>(seg, tile, nblk, n, NB);
     if (!T.any) return;
     for (int i = threadIdx.x; i < NB; i += NT) h[i] = 0;
     __syncthreads();
@@ -997,7 +1007,7 @@ __global__ __launch_bounds__(NT) void radix_hist_kernel(const u32* src, int64_t 
 
 // Stable scatter: every wave owns a contiguous 1/4 of the tile and ranks its keys round by round (64
 // consecutive keys per round) with ballot matching, so equal digits keep their input order.
-template <int BITS, bool BYTASK, int NT>
+template <int BITS, bool BYTASK, int NT, bool FEW>
 __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, u32* vout, const u32* gofs,
                                      int64_t n_all, int shift, int nblk, TaskOf tk, SegTab seg) {
     constexpr int NB = 1 << BITS, DPT = NB > NT ? NB / NT : 1;   // digits per thread in the per-digit phase
@@ -1008,10 +1018,11 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
     __shared__ u32 svals[TILE];
     __shared__ uint16_t sdig[BYTASK ? TILE : 1];   // the digit of every staged pair (a key names its own)
     __shared__ int sh_scan[WAVES + 2];
+    __shared__ u32 place[FEW ? NB : 1];            // where the tile's keys of a digit go
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
     const int tile = rs_tile_of_block(nblk);
     if (tile >= nblk) return;
-    const RsTile T = rs_tile<TILE>(seg, tile, nblk, n_all, NB);
+    const RsTile T = rs_tile<TILE, FEW>(seg, tile, nblk, n_all, NB);
     if (!T.any) return;
     for (int i = threadIdx.x; i < WAVES * NB / 2; i += NT) reinterpret_cast<u32*>(&cnt[0][0])[i] = 0;
     __syncthreads();
@@ -1023,6 +1034,26 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
         const int64_t idx = min(tile0 + (int64_t)w * (WAVE * RS_ITEMS) + r * WAVE + lane, n - 1);
         key[r] = kin[idx];
         val[r] = vin[idx];
+    }
+    u32 before[DPT], all[DPT];   // FEW: keys of a thread's digits in the range's tiles before this one, in all of them
+    if constexpr (FEW) {
+        static_assert(NB >= NT, "a thread's digits lie next to each other");
+#pragma unroll
+        for (int k = 0; k < DPT; ++k) before[k] = all[k] = 0;
+        for (int t0 = 0; t0 < T.nt; t0 += 8) {
+            u32 c[8][DPT];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int k = 0; k < DPT; ++k) c[u][k] = gofs[(size_t)(T.t0 + min(t0 + u, T.nt - 1)) * NB + threadIdx.x * DPT + k];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int k = 0; k < DPT; ++k) {
+                    if (t0 + u < T.nt) all[k] += c[u][k];
+                    if (T.t0 + t0 + u < tile) before[k] += c[u][k];
+                }
+        }
     }
 #pragma unroll
     for (int r = 0; r < RS_ITEMS; ++r) {
@@ -1066,6 +1097,19 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
     }
     int tile_count;
     u32 ds = (u32)block_excl_scan((int)mine, sh_scan, &tile_count);
+    if constexpr (FEW) {
+        u32 sum = 0;
+        int ignored;
+#pragma unroll
+        for (int k = 0; k < DPT; ++k) sum += all[k];
+        __syncthreads();   // (the scan's scratch is used again)
+        u32 at = (u32)T.pos0 + (u32)block_excl_scan((int)sum, sh_scan, &ignored);
+#pragma unroll
+        for (int k = 0; k < DPT; ++k) {
+            place[threadIdx.x * DPT + k] = at + before[k];
+            at += all[k];
+        }
+    }
 #pragma unroll
     for (int k = 0; k < DPT; ++k) {
         const int d = threadIdx.x * DPT + k;
@@ -1092,7 +1136,7 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
         key[i] = skeys[pos];
         val[i] = svals[pos];
         const u32 d = BYTASK ? (u32)sdig[pos] : ((key[i] - T.key_base) >> shift) & (NB - 1);
-        at[i] = gofs[T.h0 + (size_t)d * T.hstride] - digstart[d];
+        at[i] = (FEW ? place[d] : gofs[T.h0 + (size_t)d * T.hstride]) - digstart[d];
     }
 #pragma unroll
     for (int i = 0; i < RS_ITEMS; ++i) {
@@ -1115,28 +1159,35 @@ size_t radix_hist_words(int64_t n, int extra_tiles) {
     return (size_t)(512 * nblk + 64) + scan_tmp_words(512 * nblk);
 }
 
-template <int BITS, bool BYTASK, int NT>
-static void radix_pass_nt(hipStream_t st, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
+// Up to RS_FEW_TILES tiles (ranges' tiles are counted one by one, so few of them lie in one range) the scatter's workgroups add up
+// the digit counts themselves: a pass is two launches instead of three or five.  Whole steps with the scan's launches and without:
+// 2,048 lookups 389 / 377 us, 134,000 of 11 fields 486 / 467, 461,000 of 20 fields (245 tiles) 590 / 573, 614,000 of 40 fields (340)
+// 804 / 796, 899,000 of 26 fields (465) 853 / 856: from there on what the workgroups read again outweighs a launch.
+#define RS_FEW_TILES 384
+template <int BITS, bool BYTASK, int NT, bool FEW>
+static void radix_pass_nt(hipStream_t st, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist, int nblk,
                           const TaskOf& tk, const SegTab& seg) {
-    // ranges: at most one partly filled tile per range beyond the tiles of the whole list (the tiles past the last range's
-    // write nothing into the count table: what the table holds there stands behind every count and moves none's place)
-    const int nblk = (int)((n + NT * RS_ITEMS - 1) / (NT * RS_ITEMS)) + seg.n_seg;
     u32* scan_tmp = hist + ((size_t)512 * nblk + 63) / 64 * 64;
     const dim3 grid((nblk + 7) / 8 * 8);
-    hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK, NT>), grid, dim3(NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
-    launch_scan_u32(st, hist, hist, (int64_t)(1 << BITS) * nblk, scan_tmp, nullptr);
-    hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK, NT>), grid, dim3(NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
+    hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK, NT, FEW>), grid, dim3(NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
+    if (!FEW) launch_scan_u32(st, hist, hist, (int64_t)(1 << BITS) * nblk, scan_tmp, nullptr);
+    hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK, NT, FEW>), grid, dim3(NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
+}
+template <bool BYTASK, int NT, bool FEW>
+static void radix_pass_width(hipStream_t st, int width, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
+                             int nblk, const TaskOf& tk, const SegTab& seg) {
+    if (width <= 8) radix_pass_nt<8, BYTASK, NT, FEW>(st, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else radix_pass_nt<9, BYTASK, NT, FEW>(st, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
 }
 template <bool BYTASK>
 static void radix_pass(hipStream_t st, int width, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
                        const TaskOf& tk, const SegTab& seg) {
-    if (rs_long(n)) {
-        if (width <= 8) radix_pass_nt<8, BYTASK, 512>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
-        else radix_pass_nt<9, BYTASK, 512>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
-    } else {
-        if (width <= 8) radix_pass_nt<8, BYTASK, 256>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
-        else radix_pass_nt<9, BYTASK, 256>(st, ki, vi, ko, vo, n, shift, hist, tk, seg);
-    }
+    // ranges: at most one partly filled tile per range beyond the tiles of the whole list (the tiles past the last range's
+    // write nothing into the count table: what the table holds there stands behind every count and moves none's place)
+    const int tile = rs_tile_keys(n), nblk = (int)((n + tile - 1) / tile) + seg.n_seg;
+    if (rs_long(n)) radix_pass_width<BYTASK, 512, false>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else if (nblk <= RS_FEW_TILES) radix_pass_width<BYTASK, 256, true>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else radix_pass_width<BYTASK, 256, false>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
 }
 
 // Returns the number of passes made: after an odd number the result is in (keys_tmp, vals_tmp).

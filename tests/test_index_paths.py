@@ -146,3 +146,11 @@ def test_long_lists(gm, extra, rows):
         assert torch.equal(g["emb_rows"], want) and torch.equal(g["seg_counts"], counts)
         for k in ("slot_counts", "slot_rows", "sup_slot", "qry_slot"):
             assert torch.equal(g[k], got[0][k]), k
+
+
+@pytest.mark.parametrize("rows", [300, 200_000])       # one pass of 9 bits, two
+@pytest.mark.parametrize("n", [1, 2048, 2049, 8 * 2048 + 5, 382 * 2048, 382 * 2048 + 1, 384 * 2048, 384 * 2048 + 1])
+def test_few_tiles(gm, n, rows):
+    """Lists of one tile, of several, and around the number of tiles up to which a scatter adds up the digit counts itself (384;
+    two of them for the two fields' ranges where the fields are ordered one by one)."""
+    test_long_lists(gm, n - (1 << 20), rows)
