@@ -1610,9 +1610,10 @@ static bool task_pair_ok(const gm_ctx* c, const Batch& B, int t, int K) {
 
 // A few tasks of 513 to 1024 rows among smaller ones go the others' way: for them alone the sparse kernel would run at every
 // hop, a workgroup a (task, field), as long as the largest takes.  Among 700 tasks of a median 32 rows two of them, 16 launches
-// of 100 us: a step of 28.9 ms takes 27.9.  Where lookups are few (up to three a bag: 32 tasks x 600 rows x 26 fields 2.80 / 2.98
-// ms with matrices; six: 8.67 / 8.39) or the (task, field)s do not fill the device (8 tasks x 700 rows 2.10 / 2.16 ms, 16 tasks
-// 3.55 / 2.82) the sparse kernel is the faster one, and their matrices shall take a fraction of the others' memory.
+// of 100 us: a step of 28.9 ms takes 27.9; four of them (a third of the others' matrices) 28.8 / 27.7; 24 tasks of 700 rows among 30 of
+// 500, 26 fields 9.1 / 7.8 ms, 10 of 1000 among 60 of 300 8.3 / 7.5.  Where lookups are few (up to three a bag: 32 tasks x 600 rows x 26
+// fields 2.80 / 2.98 ms with matrices; six: 8.67 / 8.39) or the (task, field)s do not fill the device (8 tasks x 700 rows x 26 fields 2.10
+// / 2.16 ms; 16 tasks, which do, 3.55 / 2.82) the sparse kernel is the faster one; and they shall take no more memory than the others.
 static int pair_rows(const gm_ctx* c, const Batch& B) {
     const double bags = (double)(B.sup->n_samples + B.qry->n_samples) * c->F;
     if ((double)(B.sup->nnz + B.qry->nnz) < 4.0 * bags || (int64_t)B.T * c->F < c->n_cus) return PAIR_ROWS;
@@ -1623,7 +1624,7 @@ static int pair_rows(const gm_ctx* c, const Batch& B) {
         if (mx > PAIR_ROWS_FEW) continue;
         (mx > PAIR_ROWS ? few : others) += (double)pad64(ns) * (double)(pad64(ns) + pad64(nq));
     }
-    return few > 0 && 4.0 * few <= others ? PAIR_ROWS_FEW : PAIR_ROWS;
+    return few > 0 && few <= others ? PAIR_ROWS_FEW : PAIR_ROWS;
 }
 
 // Byte offsets of every task's pair-count matrices (kind by kind, fields back to back; nothing for a task
@@ -1747,7 +1748,8 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         have_offsets = true;
         return GM_OK;
     };
-    B.pair_rows = pair_rows(c, B);
+    const int few_rows = pair_rows(c, B);
+    B.pair_rows = few_rows;
     // Waves of (nearly) equal numbers of tasks: the fewest waves whose every wave fits.
     const int max_per = std::min(std::max(T, 1), most_wave_tasks(c));
     int n_waves = (std::max(T, 1) + max_per - 1) / max_per;
@@ -1781,12 +1783,12 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
             if (T == 0) break;
         }
         if (fits) return GM_OK;
-        if (per == 1 && B.pair_rows > PAIR_ROWS) {   // (a large task's matrices may be what does not fit)
+        if (B.pair_rows > PAIR_ROWS) {   // (the large tasks' matrices never cost a wave)
             B.pair_rows = PAIR_ROWS;
-            n_waves = (std::max(T, 1) + max_per - 1) / max_per;
             continue;
         }
         if (per == 1) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
+        B.pair_rows = few_rows;
         n_waves = std::min(std::max(T, 1), std::max(n_waves + 1, n_waves + n_waves / 16));
     }
 }

@@ -71,7 +71,7 @@ def test_batches_of_hot_rows(gm, rows, samples, bag, zipf, K):  # noqa: F811
 
 
 @pytest.mark.parametrize("large,bag,matrices", [((600,), 12, True), ((1024, 513), 12, True), ((1025, 600), 12, None), ((600,), 3, False),
-                                                ((1024, 1024, 1024), 12, False)])
+                                                ((1024, 1024, 1024), 12, True), ((1024,) * 6, 12, False)])
 def test_few_large_tasks_among_small_ones(gm, large, bag, matrices):  # noqa: F811
     """Tasks of more than 512 rows take the others' matrices where they are few and lookups many: then the bits are those of matrices
     for all (matrices: True), else another order of sums; never more than rounding away from the sparse kernel's."""
