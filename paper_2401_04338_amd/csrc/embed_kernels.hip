@@ -88,41 +88,49 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(PoolArgs a) {
 // A field's support and query samples follow each other, so that its rows are fetched for both sets at once.
 // Measured: 201 tasks of about (150 + 243) samples x 26 fields, bags of 1..20, 0.67 ms in two launches -> 0.63 ms; 128 tasks x (512 + 512)
 // samples x 64 fields, bags of 1..32, 3.63 -> 3.62 ms, 9.8 TB/s of rows.
+// Where the rows are in L2 the instructions around a read are the bound: the width is a constant of the kernel, the indices of
+// eight reads are handed round together, offsets count from the set's first bag in 32 bits, and what does not depend on the rows
+// (the table's base, the output row) is read a bag ahead of them: 18 million lookups of 64 columns 475 -> 448 us, 72 million 2.10 -> 2.01 ms.
+template <int LG>
 __global__ __launch_bounds__(256) void gather_pool_xcd_kernel(PoolArgs a) {
     if (blockIdx.x >= a.pool_blocks) { pool_tail(a); return; }
-    const int LG = a.LG, F = a.F;
-    const int groups_per_block = blockDim.x / LG;
+    constexpr int GPB = 256 / LG;
+    const int F = a.F;
     const int g_in_block = threadIdx.x / LG, l = threadIdx.x % LG;
     const int xcd = blockIdx.x & 7, bi = blockIdx.x >> 3, nbx = a.pool_blocks >> 3;
     // work items of this XCD: pairs [lo, hi) of the field-major list (pair = field * samples + sample; fewer than 2^32)
     const u32 n0 = (u32)a.set[0].n_samples, n = n0 + (u32)a.set[1].n_samples;
     const int64_t n_pairs = (int64_t)n * F;
-    const int64_t hi = n_pairs * (xcd + 1) / 8, stride = (int64_t)nbx * groups_per_block;
-    int64_t it = n_pairs * xcd / 8 + (int64_t)bi * groups_per_block + g_in_block;
+    const int64_t hi = n_pairs * (xcd + 1) / 8, stride = (int64_t)nbx * GPB;
+    int64_t it = n_pairs * xcd / 8 + (int64_t)bi * GPB + g_in_block;
     if (it >= hi) return;
     int f = (int)(it / n);
     u32 u = (u32)(it - (int64_t)f * n);
+    const int64_t* const bags[2] = {a.set[0].bag_offsets + a.set[0].sample0 * F, a.set[1].bag_offsets + a.set[1].sample0 * F};
     // A bag is a chain of dependent reads (offsets -> indices -> rows).  The chain of the NEXT bag is started before
     // the rows of this one are summed: its offsets and its first LG indices (one per lane of the group, handed round
     // by lane shuffles) are in registers when its turn comes, and up to 8 row reads are in flight per lane.
-    int64_t p0, p1;
-    int32_t idx_l;
+    int64_t p0, p1, base_row;
+    int32_t idx_l, row;
     auto open_bag = [&](int bf, u32 bu) {
         const bool second = bu >= n0;
-        const int64_t* bo = second ? a.set[1].bag_offsets : a.set[0].bag_offsets;
+        const u32 s = second ? bu - n0 : bu;
         const int32_t* ix = second ? a.set[1].indices : a.set[0].indices;
-        const int64_t gb = ((second ? a.set[1].sample0 - n0 : a.set[0].sample0) + bu) * F + bf;
-        p0 = bo[gb]; p1 = bo[gb + 1];
+        const int64_t* bo = (second ? bags[1] : bags[0]) + (u32)(s * (u32)F + (u32)bf);
+        p0 = bo[0]; p1 = bo[1];
+        base_row = a.field_base[bf];
+        row = (second ? a.set[1].row_map : a.set[0].row_map)[s];
         idx_l = (p0 + l < p1) ? __builtin_nontemporal_load(ix + p0 + l) : 0;
     };
     open_bag(f, u);
     while (true) {
         const bool second = u >= n0;
         const int32_t* indices = second ? a.set[1].indices : a.set[0].indices;
-        const int64_t fb = a.field_base[f];
+        const float4* const rows = a.emb + base_row * LG + l;
+        const int64_t o = (int64_t)(row - (second ? a.set[1].row_base : a.set[0].row_base)) * a.ldx + (f * (4 * LG) + l * 4);
         const int64_t c0 = p0, c1 = p1;
         int32_t cur_idx = idx_l;
-        // next bag's offsets and first indices
+        // the next bag
         it += stride;
         int fn = f;
         int64_t un = (int64_t)u + stride;
@@ -133,21 +141,20 @@ __global__ __launch_bounds__(256) void gather_pool_xcd_kernel(PoolArgs a) {
             if (base > c0) cur_idx = (base + l < c1) ? __builtin_nontemporal_load(indices + base + l) : 0;
             const int m = (int)min<int64_t>(LG, c1 - base);
             for (int j0 = 0; j0 < m; j0 += 8) {
+                u32 r[8];
                 float4 v[8];
 #pragma unroll
+                for (int j = 0; j < 8; ++j) r[j] = LG >= 8 || j < LG ? (u32)__shfl(cur_idx, j0 + j, LG) : 0u;
+#pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const int jj = j0 + j;
-                    const int32_t r = __shfl(cur_idx, jj < LG ? jj : 0, LG);
-                    v[j] = jj < m ? a.emb[(fb + r) * LG + l] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if ((LG >= 8 || j < LG) && j0 + j < m) v[j] = rows[(u64)r[j] * LG];
                 }
                 acc0 = add4(add4(add4(add4(acc0, v[0]), v[1]), v[2]), v[3]);
                 acc1 = add4(add4(add4(add4(acc1, v[4]), v[5]), v[6]), v[7]);
             }
         }
         const float4 acc = add4(acc0, acc1);
-        const u32 s = second ? u - n0 : u;
-        const int32_t row = second ? a.set[1].row_map[s] - a.set[1].row_base : a.set[0].row_map[s] - a.set[0].row_base;
-        const int64_t o = (int64_t)row * a.ldx + (int64_t)f * a.D + l * 4;
         float* x = second ? a.set[1].x : a.set[0].x;
         bf16_t* x_bf = second ? a.set[1].x_bf : a.set[0].x_bf;
         if (x) {
@@ -177,8 +184,13 @@ void launch_gather_pool(hipStream_t st, int F, int D, int n_dense, const int64_t
     const bool by_xcd = n_bags > 0 && F >= 8 && n_bags >= (1 << 14);
     if (n_bags > 0) a.pool_blocks = by_xcd ? pool_grid(n_bags, 256 / a.LG) / 8 * 8 : pool_grid(n_bags, 256 / a.LG);
     const unsigned grid = a.pool_blocks + (unsigned)((n * (ldx - F * D) + 255) / 256);
-    if (by_xcd) hipLaunchKernelGGL(gather_pool_xcd_kernel, dim3(grid), dim3(256), 0, st, a);
-    else if (grid > 0) hipLaunchKernelGGL(gather_pool_kernel, dim3(grid), dim3(256), 0, st, a);
+#define POOL_XCD(LG_) case LG_: hipLaunchKernelGGL(gather_pool_xcd_kernel<LG_>, dim3(grid), dim3(256), 0, st, a); break;
+    if (by_xcd) {
+        switch (a.LG) { POOL_XCD(1) POOL_XCD(2) POOL_XCD(4) POOL_XCD(8) POOL_XCD(16) POOL_XCD(32) POOL_XCD(64) default: break; }
+    } else if (grid > 0) {
+        hipLaunchKernelGGL(gather_pool_kernel, dim3(grid), dim3(256), 0, st, a);
+    }
+#undef POOL_XCD
 }
 
 // dense and pad columns of every (padded) row, copied from x_base
