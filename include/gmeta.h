@@ -145,9 +145,9 @@ int gm_meta_step_static(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, con
  *   that a support or query sample looks up.
  * params: as for gm_meta_step, but the DEVICE arrays it points to are written (emb, every W_l, every b_l).
  * loss: DEVICE scalar, the step's sum_t L^Query_t (before the update).  task_loss: DEVICE [T] or NULL.
- * The meta-gradient lists live in the context's workspace (rows * (4 D + 8) bytes on top of what the step
- * needs, rows = min(lookups, table rows); GM_ERR_WORKSPACE if that does not fit) and are written when the tasks run in
- * several waves; one wave's reduction adds to the tables itself, the same values.  The row-list form of the
+ * Tasks that fit the workspace as one wave need no lists: the reduction adds to the tables itself.  For several waves the
+ * meta-gradient lists live in the workspace (rows * (4 D + 8) bytes on top of what the step needs, rows = min(lookups,
+ * table rows); GM_ERR_WORKSPACE if that does not fit), the same values.  The row-list form of the
  * sparse gradient is used, so each set must hold fewer than 2^31 lookups.  Errors as gm_meta_step; on an
  * error nothing has been updated. */
 int gm_meta_train_step(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_set* query,

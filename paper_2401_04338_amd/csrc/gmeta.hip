@@ -2472,6 +2472,53 @@ extern "C" int gm_meta_step_static(gm_ctx* c, int32_t T, const gm_set* sup, cons
     return rc;
 }
 
+static void host_layout(const gm_ctx* c, Batch& B, int T, const gm_set* sup, const gm_set* qry) {
+    B.T = T; B.sup = sup; B.qry = qry; B.table = false;
+    B.poff_s.assign(T + 1, 0);
+    B.poff_q.assign(T + 1, 0);
+    for (int t = 0; t < T; ++t) {
+        B.poff_s[t + 1] = B.poff_s[t] + round_up64(sup->task_offsets[t + 1] - sup->task_offsets[t], c->row_pad);
+        B.poff_q[t + 1] = B.poff_q[t] + round_up64(qry->task_offsets[t + 1] - qry->task_offsets[t], c->row_pad);
+    }
+}
+static WavePlan whole_batch_plan(const Batch& B) {
+    WavePlan p;
+    const int T = B.T;
+    p.t0 = 0; p.t1 = T;
+    p.s0 = 0; p.s1 = B.sup->n_samples; p.q0 = 0; p.q1 = B.qry->n_samples;
+    p.ps0 = 0; p.ps1 = B.poff_s[T]; p.pq0 = 0; p.pq1 = B.poff_q[T];
+    p.ls0 = 0; p.ls1 = B.sup->nnz; p.lq0 = 0; p.lq1 = B.qry->nnz;
+    return p;
+}
+// bytes of the index side and of the dense side of a batch run as ONE wave of tasks
+static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order,
+                           size_t* index_bytes, size_t* dense_bytes) {
+    Batch B;
+    host_layout(c, B, T, sup, qry);
+    B.pair_rows = pair_rows(c, B);
+    const WavePlan p = whole_batch_plan(B);
+    const WaveDims d = wave_dims(c, B, p, pick_bm(c, B), K, order);
+    Arena ia, da;
+    ia.cap = da.cap = ~(size_t)0 >> 1;
+    BatchBufs b;
+    WaveBufs w;
+    alloc_batch_index(c, ia, b, T, sup->n_samples, qry->n_samples, sup->nnz + qry->nnz, 0, true);
+    alloc_wave_index(c, ia, w, d);
+    alloc_batch_dense(c, da, b, T, B.poff_s[T], B.poff_q[T], true);
+    alloc_wave_dense(c, da, w, d, K, order);
+    *index_bytes = ia.off;
+    *dense_bytes = da.off;
+}
+// Whether gm_meta_train_step's batch runs as one wave with `top` bytes at the workspace's end taken (no lists then)
+static bool runs_as_one_wave(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order, size_t top) {
+    if (T < 0 || T > most_wave_tasks(c) || !sup->task_offsets || !qry->task_offsets || sup->n_samples < 0 || qry->n_samples < 0 ||
+        sup->task_offsets[T] != sup->n_samples || qry->task_offsets[T] != qry->n_samples || K < 0 || sup->nnz + qry->nnz >= ((int64_t)1 << 31))
+        return false;   // (several waves, or the step reports what is wrong)
+    size_t index_bytes, dense_bytes;
+    one_wave_bytes(c, T, sup, qry, K, order, &index_bytes, &dense_bytes);
+    return c->persistent + index_bytes + dense_bytes + top + 256 <= c->ws_bytes;
+}
+
 extern "C" int gm_meta_train_step(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set* qry, const gm_params* params,
                                   float alpha, int32_t K, int32_t order, float beta, float* loss, float* task_loss) {
     if (!c) return GM_ERR_ARG;
@@ -2479,11 +2526,13 @@ extern "C" int gm_meta_train_step(gm_ctx* c, int32_t T, const gm_set* sup, const
     if (!params || !params->W || !params->b) return fail(c, GM_ERR_ARG, "null params");
     HIPCHK(c, hipSetDevice(c->device));
     const int L = c->L, D = c->D;
-    // the meta-gradient of this iteration lives at the top of the workspace; the step gets what is below it
-    const int64_t capacity = c->F > 0 ? std::min<int64_t>(sup->nnz + qry->nnz, c->field_base[c->F]) : 0;
+    // the meta-gradient of this iteration lives at the top of the workspace, the step gets what is below it: its dense part, and
+    // where the tasks do not run as one wave (which adds to the tables itself) the row lists
     int64_t n_dense = 0;
     for (int l = 0; l < L; ++l) n_dense += (int64_t)(c->dims[l] + 1) * c->dims[l + 1];
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const bool lists = c->F > 0 && !runs_as_one_wave(c, T, sup, qry, K, order, up((size_t)n_dense * 4) + 256);
+    const int64_t capacity = lists ? std::min<int64_t>(sup->nnz + qry->nnz, c->field_base[c->F]) : 0;
     const size_t need = up((size_t)n_dense * 4) + up((size_t)capacity * 8) + up((size_t)capacity * std::max(D, 1) * 4) + 256;
     if (need + c->persistent + (1 << 20) > c->ws_bytes)
         return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold the meta-gradient (%zu bytes) beside the step", c->ws_bytes, need);
@@ -2590,44 +2639,6 @@ extern "C" int gm_meta_train_step_table(gm_ctx* c, int32_t T, const gm_set* sup,
 // ------------------------------------------------------------------------------------------------
 // several iterations of Alg. 1 in one call, the index side of batch i+1 prepared while batch i computes
 // ------------------------------------------------------------------------------------------------
-static void host_layout(const gm_ctx* c, Batch& B, int T, const gm_set* sup, const gm_set* qry) {
-    B.T = T; B.sup = sup; B.qry = qry; B.table = false;
-    B.poff_s.assign(T + 1, 0);
-    B.poff_q.assign(T + 1, 0);
-    for (int t = 0; t < T; ++t) {
-        B.poff_s[t + 1] = B.poff_s[t] + round_up64(sup->task_offsets[t + 1] - sup->task_offsets[t], c->row_pad);
-        B.poff_q[t + 1] = B.poff_q[t] + round_up64(qry->task_offsets[t + 1] - qry->task_offsets[t], c->row_pad);
-    }
-}
-static WavePlan whole_batch_plan(const Batch& B) {
-    WavePlan p;
-    const int T = B.T;
-    p.t0 = 0; p.t1 = T;
-    p.s0 = 0; p.s1 = B.sup->n_samples; p.q0 = 0; p.q1 = B.qry->n_samples;
-    p.ps0 = 0; p.ps1 = B.poff_s[T]; p.pq0 = 0; p.pq1 = B.poff_q[T];
-    p.ls0 = 0; p.ls1 = B.sup->nnz; p.lq0 = 0; p.lq1 = B.qry->nnz;
-    return p;
-}
-// bytes of the index side and of the dense side of a batch run as ONE wave of tasks
-static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order,
-                           size_t* index_bytes, size_t* dense_bytes) {
-    Batch B;
-    host_layout(c, B, T, sup, qry);
-    B.pair_rows = pair_rows(c, B);
-    const WavePlan p = whole_batch_plan(B);
-    const WaveDims d = wave_dims(c, B, p, pick_bm(c, B), K, order);
-    Arena ia, da;
-    ia.cap = da.cap = ~(size_t)0 >> 1;
-    BatchBufs b;
-    WaveBufs w;
-    alloc_batch_index(c, ia, b, T, sup->n_samples, qry->n_samples, sup->nnz + qry->nnz, 0, true);
-    alloc_wave_index(c, ia, w, d);
-    alloc_batch_dense(c, da, b, T, B.poff_s[T], B.poff_q[T], true);
-    alloc_wave_dense(c, da, w, d, K, order);
-    *index_bytes = ia.off;
-    *dense_bytes = da.off;
-}
-
 // The index side of one batch, on the context's current stream, into the arena `ia`.
 static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, const gm_set* qry, int K, int order, Prepared& P) {
     int rc = check_set(c, sup, T, "support");

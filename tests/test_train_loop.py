@@ -157,3 +157,31 @@ def test_update_of_the_rows_inside_the_step(dim, rows, bf, waves):
         moved = (want.emb - params.emb.to(dev)).abs().max()
         assert (by_table.emb - got.emb).abs().max() <= 1e-5 * moved + 2 * torch.finfo(torch.float32).eps * want.emb.abs().max()
     ctx.close()
+
+
+def test_workspace_without_room_for_the_lists():
+    """Many distinct rows: the row lists take more than a batch's index structures, so between the sizes at which the loop overlaps and at
+    which the lists fit beside one wave, single iterations have to run as one wave without lists to give the loop's bits (40 tasks:
+    other waves would sum the hidden layers' gradients over other runs of tasks)."""
+    from paper_2401_04338_amd import GMeta
+    cfg = SMALL.with_(n_tasks=40, n_support=30, n_query=30, n_fields=6, emb_dim=64, rows_per_field=30000, bag_max=20, zipf_s=0.0,
+                      layer_dims=(6 * 64 + 13, 32, 1), inner_lr=0.05)
+    beta, K, order, dev = 0.02, 1, 2, torch.device("cuda", 0)
+    params = make_params(cfg, "cpu", emb_std=0.1)
+    batches = [make_batch(cfg, it, dev) for it in range(2)]
+    s, q = batches[0]
+    probe = GMeta.from_config(cfg, workspace_bytes=1 << 20)
+    need = probe.workspace_bytes(cfg.n_tasks, s.n_samples, q.n_samples, s.nnz, q.nnz, K, order)
+    probe.close()
+    lists = min(s.nnz + q.nnz, 6 * 30000) * (4 * 64 + 8)
+    for extra in range(12):   # from one wave to room for the loop's two batches and the lists
+        ctx = GMeta.from_config(cfg, workspace_bytes=need + extra * lists // 6)
+        one, loop = _clone(params, dev), _clone(params, dev)
+        ctx.profile(True)
+        for sb, qb in batches:
+            ctx.meta_train_step(sb, qb, one, cfg.inner_lr, K, order, beta)
+        assert "scatter_add" not in ctx.profile_report()   # (no list applied: one wave)
+        ctx.profile(False)
+        ctx.meta_train(batches, loop, cfg.inner_lr, K, order, beta)
+        ctx.close()
+        _same_params(loop, one)
