@@ -291,7 +291,9 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               row lists and row gradients are identical however the tasks are cut into waves, the bias gradients and
  *               the last layer's too; the hidden layers' weight gradients are summed over other runs of tasks (see
  *               "coarse_groups"), a wave with a bag or a (task, field) beyond the pair matrices' limits takes the other
- *               row arithmetic whole ("row_path"), and with emb_grad_table every wave adds its own sums to a row.
+ *               row arithmetic whole ("row_path"), and with emb_grad_table every wave adds its own sums to a row.  (A few
+ *               tasks of 513 to 1,024 samples may take pair matrices too, which the batch alone decides; only where the
+ *               workspace could not hold one of them with its matrices, run by itself, do they take the other row arithmetic.)
  *   "pair_tile_rows": most out-rows of a pair-count matrix that the counting kernel holds in LDS at a time
  *               (0 = as many as fit); identical results.
  * Unknown keys or values give GM_ERR_ARG. */

@@ -1614,6 +1614,8 @@ static bool task_pair_ok(const gm_ctx* c, const Batch& B, int t, int K) {
 // 500, 26 fields 9.1 / 7.8 ms, 10 of 1000 among 60 of 300 8.3 / 7.5.  Where lookups are few (up to three a bag: 32 tasks x 600 rows x 26
 // fields 2.80 / 2.98 ms with matrices; six: 8.67 / 8.39) or the (task, field)s do not fill the device (8 tasks x 700 rows x 26 fields 2.10
 // / 2.16 ms; 16 tasks, which do, 3.55 / 2.82) the sparse kernel is the faster one; and they shall take no more memory than the others.
+// A rule on the batch alone: the two ways add in different orders, and losses and row gradients shall not depend on the workspace,
+// on the waves or on whether training iterations overlap.  (A workspace that cannot hold such a task's matrices at all: plan_waves.)
 static int pair_rows(const gm_ctx* c, const Batch& B) {
     const double bags = (double)(B.sup->n_samples + B.qry->n_samples) * c->F;
     if ((double)(B.sup->nnz + B.qry->nnz) < 4.0 * bags || (int64_t)B.T * c->F < c->n_cus) return PAIR_ROWS;
@@ -1748,11 +1750,11 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         have_offsets = true;
         return GM_OK;
     };
-    const int few_rows = pair_rows(c, B);
-    B.pair_rows = few_rows;
+    B.pair_rows = pair_rows(c, B);
     // Waves of (nearly) equal numbers of tasks: the fewest waves whose every wave fits.
     const int max_per = std::min(std::max(T, 1), most_wave_tasks(c));
-    int n_waves = (std::max(T, 1) + max_per - 1) / max_per;
+    const int fewest = (std::max(T, 1) + max_per - 1) / max_per;
+    int n_waves = fewest;
     while (true) {
         const int per = (std::max(T, 1) + n_waves - 1) / n_waves;
         plans.clear();
@@ -1783,12 +1785,12 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
             if (T == 0) break;
         }
         if (fits) return GM_OK;
-        if (B.pair_rows > PAIR_ROWS) {   // (the large tasks' matrices never cost a wave)
-            B.pair_rows = PAIR_ROWS;
+        if (per == 1) {
+            if (B.pair_rows == PAIR_ROWS) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
+            B.pair_rows = PAIR_ROWS;   // (a large task does not fit with its matrices, not even alone)
+            n_waves = fewest;
             continue;
         }
-        if (per == 1) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
-        B.pair_rows = few_rows;
         n_waves = std::min(std::max(T, 1), std::max(n_waves + 1, n_waves + n_waves / 16));
     }
 }

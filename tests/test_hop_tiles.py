@@ -96,3 +96,48 @@ def test_few_large_tasks_among_small_ones(gm, large, bag, matrices):  # noqa: F8
     if matrices is not None:
         same = all(torch.equal(a, b) for a, b in zip(got[0], got[2]))
         assert same == matrices
+
+
+def _few_large(fields):
+    sizes = [1024, 600, *([200, 250, 193] * 29)]
+    cfg = small_cfg(n_tasks=len(sizes), n_fields=fields, emb_dim=32, rows_per_field=500, n_support=max(sizes), n_query=max(sizes), bag_max=12,
+                    layer_dims=(fields * 32 + 5, 24, 1))
+    sup, qry, params = _inputs(cfg, emb_std=0.3)
+    return cfg, _cut(sup, sizes, fields), _cut(qry, sizes, fields), params
+
+
+def test_few_large_tasks_in_any_workspace(gm):  # noqa: F811
+    """The batch alone decides how a few large tasks' rows are summed: losses and row gradients are the same bits in every workspace,
+    however many waves it takes, and whether training iterations overlap or not."""
+    cfg, sup, qry, params = _few_large(3)
+    dev = torch.device("cuda", 0)
+    s, q, want = _to_dev(sup, dev), _to_dev(qry, dev), None
+    for mib in [1024, *range(420, 110, -12)]:
+        ctx = gm.from_config(cfg, workspace_bytes=mib << 20)
+        p = _params_dev(params, dev)
+        out = ctx.meta_step(s, q, p, cfg.inner_lr, 2, 2)
+        n = int(out["n_emb_rows"].item())
+        got = [out["emb_rows"][:n].clone(), out["emb_grad"][:n].clone(), out["task_loss"][:cfg.n_tasks].clone()]
+        want = want or got
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), f"{mib} MiB"
+        one, loop = _params_dev(params, dev), _params_dev(params, dev)
+        for _ in range(2):
+            ctx.meta_train_step(s, q, one, cfg.inner_lr, 2, 2, 0.01)
+        ctx.meta_train([(s, q)] * 2, loop, cfg.inner_lr, 2, 2, 0.01)
+        ctx.close()
+        assert all(torch.equal(a, b) for a, b in zip([one.emb, *one.W, *one.b], [loop.emb, *loop.W, *loop.b])), f"{mib} MiB"
+
+
+def test_large_task_whose_matrices_do_not_fit(gm):  # noqa: F811
+    """A workspace that holds a large task but not its matrices takes the batch all the same, within rounding."""
+    cfg, sup, qry, params = _few_large(12)
+    dev = torch.device("cuda", 0)
+    s, q, p = _to_dev(sup, dev), _to_dev(qry, dev), _params_dev(params, dev)
+    got = []
+    for mib in (1024, 160):   # (batch-level buffers and the largest task: 132 MiB, with its 47 MiB of matrices 180)
+        ctx = gm.from_config(cfg, workspace_bytes=mib << 20)
+        out = ctx.meta_step(s, q, p, cfg.inner_lr, 2, 2)
+        got.append(out["emb_grad"][:int(out["n_emb_rows"].item())].clone())
+        ctx.close()
+    assert not torch.equal(got[0], got[1])   # (the other row arithmetic)
+    assert float((got[1] - got[0]).norm()) <= TOL_FP32 * float(got[0].norm())
