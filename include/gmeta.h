@@ -176,8 +176,8 @@ int gm_meta_train_step_table(gm_ctx* ctx, int32_t n_tasks, const gm_set* support
  * before its update; n_done: HOST, iterations applied when the call returns (all of them on GM_OK; on an error the
  * failing iteration and the ones after it have not been applied), or NULL.
  * The overlap needs every batch to run as one wave of tasks and the workspace to hold, beside the dense buffers of
- * one batch, the index structures of two batches (no meta-gradient lists: a wave's rows are updated by its reduction); otherwise the iterations simply run one
- * after the other (same results).  The "overlap_sort" / "overlap_pairs" settings are ignored during the call. */
+ * one batch, the index structures of two batches (the pair matrices of one at least; no meta-gradient lists: a wave's rows are
+ * updated by its reduction); otherwise the iterations simply run one after the other (same results).  The "overlap_sort" / "overlap_pairs" settings are ignored during the call. */
 int gm_meta_train(gm_ctx* ctx, int32_t n_iters, const int32_t* n_tasks, const gm_set* support, const gm_set* query,
                   const gm_params* params, float inner_lr, int32_t inner_steps, int32_t order, float outer_lr,
                   float* losses, int32_t* n_done);

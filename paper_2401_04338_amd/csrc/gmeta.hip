@@ -328,6 +328,7 @@ struct WaveDims {
     bool any_sparse = false;               // some task of the wave takes the sparse kernel
     bool pair_ss = false, pair_sq = false; // which kinds besides query x support
     int64_t pair_bytes = 0;
+    bool mat_apart = false;                // the matrices' room belongs to the dense side (gm_meta_train: one batch's at a time)
     int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of the tasks beyond HOP_SMALL (the hops' work lists)
     bool table = false;                    // the sparse gradient is reduced wave by wave into a table-shaped output
     int factor_ld = 0;                     // > 0: the chain's direction stays factors (see Factor); rows of the largest task of the batch
@@ -424,7 +425,7 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
         w.tmid_keys = ar.get<u32>(d.nnz_s + d.nnz_q + 1);
         w.tmid_vals = ar.get<u32>(d.nnz_s + d.nnz_q + 1);
     }
-    w.pair_mat = d.pair ? ar.get<uint8_t>(d.pair_bytes + 64) : nullptr;
+    w.pair_mat = d.pair && !d.mat_apart ? ar.get<uint8_t>(d.pair_bytes + 64) : nullptr;
 }
 
 // activations, per-task parameters and gradient buffers of a wave
@@ -432,6 +433,7 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     const int L = c->L;
     const bool bf = c->mlp_dtype != 0;
     const int ld0 = c->ld[0];
+    if (d.pair && d.mat_apart) w.pair_mat = ar.get<uint8_t>(d.pair_bytes + 64);
     w.Xs0 = ar.get<float>(d.Ps * ld0);
     w.Xq0 = ar.get<float>(d.Pq * ld0);
     const bool second = order == 2 && K > 0;
@@ -1935,8 +1937,8 @@ static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& 
 
 // Everything of a one-wave batch with the row-list output that depends on its indices only, prepared ahead of the step
 // (by gm_meta_train, on the second stream, while the previous batch computes): validated offsets and indices, padded
-// row numbers, tile lists, per-(task, field) dictionaries and overlap join, pair-count matrices, the batch-wide order
-// of the lookups by row.  The buffers live in an arena of their own.
+// row numbers, tile lists, per-(task, field) dictionaries and overlap join, pair-count matrices (unless their room is
+// apart: WaveDims), the batch-wide order of the lookups by row.  The buffers live in an arena of their own.
 struct Prepared {
     Batch B;
     WavePlan wp;
@@ -2058,6 +2060,10 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             gs = pre->gs; gq = pre->gq;
             tf_cap = pre->tf_cap; max_bag = pre->max_bag; max_tf = pre->max_tf;
             pair = pre->pair; any_sparse = pre->any_sparse;
+            if (d.mat_apart) {
+                launch_fill_u32(st, c->d_status, ST_WORDS, 0);
+                if ((rc = count_pairs(c, B, wp, w, d, K, tf_cap, max_bag, max_tf, false, pair, any_sparse, pairs_on_side))) return rc;
+            }
         } else {
             if ((rc = setup_wave(c, B, wp, bm, K, w, d, gs, gq))) return rc;
             // a0: row dictionaries and the overlap join -- read off the row order of the wave's lookups when that order
@@ -2493,13 +2499,14 @@ static WavePlan whole_batch_plan(const Batch& B) {
     return p;
 }
 // bytes of the index side and of the dense side of a batch run as ONE wave of tasks
-static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order,
+static void one_wave_bytes(const gm_ctx* c, int T, const gm_set* sup, const gm_set* qry, int K, int order, bool mat_apart,
                            size_t* index_bytes, size_t* dense_bytes) {
     Batch B;
     host_layout(c, B, T, sup, qry);
     B.pair_rows = pair_rows(c, B);
     const WavePlan p = whole_batch_plan(B);
-    const WaveDims d = wave_dims(c, B, p, pick_bm(c, B), K, order);
+    WaveDims d = wave_dims(c, B, p, pick_bm(c, B), K, order);
+    d.mat_apart = mat_apart;
     Arena ia, da;
     ia.cap = da.cap = ~(size_t)0 >> 1;
     BatchBufs b;
@@ -2517,7 +2524,7 @@ static bool runs_as_one_wave(const gm_ctx* c, int T, const gm_set* sup, const gm
         sup->task_offsets[T] != sup->n_samples || qry->task_offsets[T] != qry->n_samples || K < 0 || sup->nnz + qry->nnz >= ((int64_t)1 << 31))
         return false;   // (several waves, or the step reports what is wrong)
     size_t index_bytes, dense_bytes;
-    one_wave_bytes(c, T, sup, qry, K, order, &index_bytes, &dense_bytes);
+    one_wave_bytes(c, T, sup, qry, K, order, false, &index_bytes, &dense_bytes);
     return c->persistent + index_bytes + dense_bytes + top + 256 <= c->ws_bytes;
 }
 
@@ -2641,8 +2648,8 @@ extern "C" int gm_meta_train_step_table(gm_ctx* c, int32_t T, const gm_set* sup,
 // ------------------------------------------------------------------------------------------------
 // several iterations of Alg. 1 in one call, the index side of batch i+1 prepared while batch i computes
 // ------------------------------------------------------------------------------------------------
-// The index side of one batch, on the context's current stream, into the arena `ia`.
-static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, const gm_set* qry, int K, int order, Prepared& P) {
+// The index side of one batch, on the context's current stream, into the arena `ia`; mat_apart: without the pair-count matrices.
+static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, const gm_set* qry, int K, int order, bool mat_apart, Prepared& P) {
     int rc = check_set(c, sup, T, "support");
     if (rc != GM_OK) return rc;
     rc = check_set(c, qry, T, "query");
@@ -2657,6 +2664,7 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
     P.wp = whole_batch_plan(B);
     if (sup->nnz + qry->nnz >= ((int64_t)1 << 31)) return fail(c, GM_ERR_WORKSPACE, "the batch does not run as one wave of tasks");
     P.d = wave_dims(c, B, P.wp, P.bm, K, order);
+    P.d.mat_apart = mat_apart;
     alloc_wave_index(c, ia, P.w, P.d);
     if (ia.overflow) return fail(c, GM_ERR_WORKSPACE, "the batch's index structures do not fit their arena");
     if (T > 0) {
@@ -2670,7 +2678,7 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
         if ((rc = run_index_wave(c, B, P.wp, P.w, &P.tf_cap, &P.max_bag, &P.max_tf, &jr))) return rc;
         if (jr.used) P.enc = jr.enc;
         bool on_side = false;
-        if ((rc = count_pairs(c, B, P.wp, P.w, P.d, K, P.tf_cap, P.max_bag, P.max_tf, false, P.pair, P.any_sparse, on_side))) return rc;
+        if (!mat_apart && (rc = count_pairs(c, B, P.wp, P.w, P.d, K, P.tf_cap, P.max_bag, P.max_tf, false, P.pair, P.any_sparse, on_side))) return rc;
         if (c->row_path == 2 && P.any_sparse && c->adapt_rows)
             return fail(c, GM_ERR_CAPACITY, "pair-count path forced, but a task, count, bag or (task, field) exceeds its limits");
     }
@@ -2699,9 +2707,11 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
     HIPCHK(c, hipSetDevice(c->device));
     const int L = c->L, D = c->D;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    // what the overlapped loop needs: two index arenas, the dense meta-gradient and the dense side of the largest batch
-    bool overlapped = true;
-    size_t idx_max = 0, dense_max = 0;
+    // What the overlapped loop needs: two index arenas, the dense meta-gradient and the dense side of the largest batch.  Where two
+    // batches' pair-count matrices do not fit, one batch's do: a step then counts its own before it starts (82 uneven tasks, two of
+    // them large, 26 fields: 3.05 ms an iteration with both, 3.26 with one, 3.50 without overlap).
+    bool overlapped = true, apart = false;
+    size_t idx_bytes[2] = {0, 0}, dense_bytes[2] = {0, 0};   // [apart]
     for (int i = 0; i < n_iters; ++i) {
         const gm_set *s = &support[i], *q = &query[i];
         if (n_tasks[i] < 0 || !s->task_offsets || !q->task_offsets || s->nnz < 0 || q->nnz < 0 || s->n_samples < 0 || q->n_samples < 0 ||
@@ -2710,15 +2720,20 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
             overlapped = false;   // (the per-iteration call takes the tasks in waves, or reports what is wrong)
             break;
         }
-        size_t ib, db;
-        one_wave_bytes(c, n_tasks[i], s, q, K, order, &ib, &db);
-        idx_max = std::max(idx_max, up(ib) + 4096);
-        dense_max = std::max(dense_max, db);
+        for (int a = 0; a < 2; ++a) {
+            size_t ib, db;
+            one_wave_bytes(c, n_tasks[i], s, q, K, order, a == 1, &ib, &db);
+            idx_bytes[a] = std::max(idx_bytes[a], up(ib) + 4096);
+            dense_bytes[a] = std::max(dense_bytes[a], db);
+        }
     }
     int64_t n_dense = 0;
     for (int l = 0; l < L; ++l) n_dense += (int64_t)(c->dims[l] + 1) * c->dims[l + 1];
     const size_t top = up((size_t)n_dense * 4) + 2 * 256;
-    if (overlapped && c->persistent + dense_max + 2 * idx_max + top + (1 << 20) > c->ws_bytes) overlapped = false;
+    auto fits = [&](bool a) { return c->persistent + dense_bytes[a] + 2 * idx_bytes[a] + top + (1 << 20) <= c->ws_bytes; };
+    apart = !fits(false);
+    overlapped = overlapped && fits(apart);
+    const size_t idx_max = idx_bytes[apart];
     if (!overlapped) {   // one iteration after the other (several waves of tasks, or a workspace for one batch only)
         for (int i = 0; i < n_iters; ++i) {
             const int rc = gm_meta_train_step(c, n_tasks[i], &support[i], &query[i], params, alpha, K, order, beta, losses + i, nullptr);
@@ -2754,7 +2769,7 @@ extern "C" int gm_meta_train(gm_ctx* c, int32_t n_iters, const int32_t* n_tasks,
         Arena ia;
         ia.base = idx_p[i & 1]; ia.cap = idx_max; ia.off = 0;
         if (on_side) { std::swap(c->stream, c->side); std::swap(c->d_status, c->d_status_side); }
-        const int rc = prepare_batch(c, ia, n_tasks[i], &support[i], &query[i], K, order, P[i & 1]);
+        const int rc = prepare_batch(c, ia, n_tasks[i], &support[i], &query[i], K, order, apart, P[i & 1]);
         if (on_side) { std::swap(c->stream, c->side); std::swap(c->d_status, c->d_status_side); }
         return rc;
     };

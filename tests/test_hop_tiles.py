@@ -108,7 +108,7 @@ def _few_large(fields):
 
 def test_few_large_tasks_in_any_workspace(gm):  # noqa: F811
     """The batch alone decides how a few large tasks' rows are summed: losses and row gradients are the same bits in every workspace,
-    however many waves it takes, and whether training iterations overlap or not."""
+    however many waves it takes, and whether training iterations overlap with both batches' matrices in place, one batch's, or not at all."""
     cfg, sup, qry, params = _few_large(3)
     dev = torch.device("cuda", 0)
     s, q, want = _to_dev(sup, dev), _to_dev(qry, dev), None
@@ -126,6 +126,35 @@ def test_few_large_tasks_in_any_workspace(gm):  # noqa: F811
         ctx.meta_train([(s, q)] * 2, loop, cfg.inner_lr, 2, 2, 0.01)
         ctx.close()
         assert all(torch.equal(a, b) for a, b in zip([one.emb, *one.W, *one.b], [loop.emb, *loop.W, *loop.b])), f"{mib} MiB"
+
+
+def test_loop_stops_at_a_batch_beyond_the_matrices(gm):  # noqa: F811
+    """Matrices forced, a batch beyond their limits after a good one: with both batches' matrices in place, one batch's, or no overlap, the
+    good iteration is applied and the other is not."""
+    from paper_2401_04338_amd import GMetaError
+    dev = torch.device("cuda", 0)
+    sets = []
+    for bag in (12, 200):   # (a matrix takes bags of at most 127)
+        cfg = small_cfg(n_tasks=20, n_fields=3, emb_dim=32, rows_per_field=500, n_support=500, n_query=500, bag_max=12, layer_dims=(3 * 32 + 5, 24, 1))
+        sup, qry, params = _inputs(cfg, emb_std=0.3)
+        if bag > 12:
+            off = sup.bag_offsets.clone()
+            extra = bag - int(off[1])
+            off[1:] += extra
+            sup = dataclasses.replace(sup, bag_offsets=off, indices=torch.cat([torch.zeros(extra, dtype=sup.indices.dtype), sup.indices]))
+        sets.append((_to_dev(sup, dev), _to_dev(qry, dev)))
+    want = None
+    for mib in range(400, 90, -12):
+        ctx = gm.from_config(cfg, workspace_bytes=mib << 20)
+        ctx.configure("row_path", 2)
+        p = _params_dev(params, dev)
+        with pytest.raises(GMetaError) as e:
+            ctx.meta_train(sets, p, cfg.inner_lr, 2, 2, 0.01)
+        assert e.value.code == -3 and ctx.iterations_done == 1, f"{mib} MiB: {e.value}"
+        ctx.close()
+        want = want or p
+        assert torch.equal(p.emb, want.emb), f"{mib} MiB"
+    assert not torch.equal(want.emb, _params_dev(params, dev).emb)
 
 
 def test_large_task_whose_matrices_do_not_fit(gm):  # noqa: F811
