@@ -53,7 +53,8 @@ typedef struct {
     int32_t emb_dim;               /* D, a power of two in 4..256                           */
     int32_t n_dense;               /* dense features per sample                             */
     int32_t n_layers;              /* L                                                     */
-    const int32_t* layer_dims;     /* HOST [L+1] d_0..d_L; d_0 = F*D + n_dense, d_L = 1     */
+    const int32_t* layer_dims;     /* HOST [L+1] d_0..d_L; d_0 = F*D + n_dense, d_L = 1;
+                                      each at most 4,194,304                                */
     int32_t mlp_dtype;             /* 0: fp32 GEMMs; 1: bf16 operands, fp32 accumulation    */
 } gm_model_desc;
 

@@ -212,7 +212,7 @@ __device__ __forceinline__ void gemm_tiles(f32x16 (&acc)[BM / (32 * WM)][BN / (3
 
     // Operand tiles come through buffer loads: what lies outside the operand reads as zero without a branch, also whole tiles
     // past the last one.  (The tile's first row is in the base address: offsets stay far below 32 bits.)
-    const u32 OOB = 1u << 30;    // (beyond any tile: a tile's 256 rows of less than 2^21 columns; row steps added to it stay below 2^31)
+    const u32 OOB = 1u << 31;    // (beyond any tile: 256 rows of at most MAX_WIDTH columns; row steps added to it stay below 2^32)
     // (the product's operands are taken from the arguments once per product: a scalar load in every tile is a wait in every tile)
     int pr = -1, k0 = 0;         // product and contraction offset of the next tile to be requested
     GemmOp op;

@@ -266,6 +266,10 @@ void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows
 // ------------------------------------------------------------------ MLP kernels
 enum { EPI_NONE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_MASK = 2, EPI_MASK = 3, EPI_AXPBY = 4, EPI_SPLIT = 5 };   // SPLIT: c1 * value as bf16, and what that leaves as another
 
+// Widest matrix (columns, padded).  The products reach a tile's rows by 32-bit byte offsets from the first of them and ask for what
+// lies outside from 2^31 on: 256 rows of bf16 or 128 of fp32, at this width 2^31 bytes.
+enum { MAX_WIDTH = 1 << 22 };
+
 typedef u32 u32x2 __attribute__((ext_vector_type(2)));
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
 // What an epilogue reads and writes.
@@ -275,7 +279,7 @@ struct RowBuffer {   // rows [first, first + rows) of a row-major matrix, from c
     __device__ __forceinline__ RowBuffer(const void* p, int64_t row, int64_t ld_elems, int elem, int rows, int er, int n, bool nok) {
         ld = (u32)ld_elems * (u32)elem;
         rs = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<const char*>(p) + row * ld_elems * elem), 0, (int)((u32)rows * ld), 0x00020000);
-        at = nok ? (u32)er * ld + (u32)n * (u32)elem : 1u << 31;   // (a tile's rows of less than 2^21 columns stay below it)
+        at = nok ? (u32)er * ld + (u32)n * (u32)elem : 1u << 31;   // (128 rows of at most MAX_WIDTH columns stay below it)
     }
     __device__ __forceinline__ int off(int r) const { return (int)(at + (u32)r * ld); }
     __device__ __forceinline__ float4 load4(int r) const { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off(r), 0, 0)); }

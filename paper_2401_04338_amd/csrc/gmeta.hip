@@ -200,6 +200,7 @@ static int model_layout(gm_ctx* c, const gm_model_desc* m) {
     c->ld.resize(c->L + 1);
     for (int l = 0; l <= c->L; ++l) {
         if (c->dims[l] <= 0) return fail(c, GM_ERR_ARG, "layer_dims must be positive");
+        if (c->dims[l] > MAX_WIDTH) return fail(c, GM_ERR_ARG, "a layer of %d columns: at most %d", c->dims[l], (int)MAX_WIDTH);
         c->ld[l] = l == c->L ? 1 : round_up(c->dims[l], 32);
     }
     c->offW.assign(c->L + 1, 0);

@@ -52,3 +52,21 @@ def test_workspace_bytes_is_host_only_and_monotone():
     assert 0 < a < b < c
     bad = _model_desc(8, [1000] * 8, 16, 13, [140, 64, 32, 1], 0)   # d_0 != F*D + n_dense
     assert lib.gm_workspace_bytes(C.byref(bad), 4, 128, 128, 1024, 1024, 1, 2) == 0
+
+
+@pytest.mark.parametrize("dims", [[141, 1 << 22, 32, 1], [1 << 22, 64, 1]])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_widest_layer(dims, dtype):
+    """The products address a tile's rows in 32 bits: wider layers are refused, by gm_create too (before it looks for a GPU)."""
+    from paper_2401_04338_amd.binding import _model_desc, load_library
+    import ctypes as C
+    lib = load_library()
+    for wider in (0, 1):
+        d = [n + wider * (n == 1 << 22) for n in dims]
+        desc = _model_desc(8, [1000] * 8, 16, d[0] - 128, d, dtype)
+        assert (lib.gm_workspace_bytes(C.byref(desc), 1, 8, 8, 64, 64, 0, 1) > 0) == (not wider)
+        if wider:
+            ctx = C.c_void_p()
+            assert lib.gm_create(C.byref(ctx), C.byref(desc), 0, None, 1 << 20) == -1
+            assert b"4194304" in lib.gm_last_error(ctx)
+            lib.gm_destroy(ctx)

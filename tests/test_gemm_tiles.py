@@ -78,3 +78,32 @@ def test_weight_gradient_tiles(gm, K):  # noqa: F811
     assert float(got[0][1].abs().max()) > 0
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def test_contraction_of_more_than_two_million(gm):  # noqa: F811
+    """A hidden layer wider than 2^21 and no multiple of a tile's 64 contraction values, its backward product in 256 x 256 tiles: what lies
+    past the last column counts as zero.  Only sixteen columns have weights: the last eight, and the eight of the last row that lie
+    2^30 bytes behind the first row (an offset inside the tile, which once stood for "outside")."""
+    wide, n, d = (1 << 21) + 32, 256, 64
+    gen = torch.Generator("cuda").manual_seed(7)
+    cols = torch.cat([torch.arange(8) + (1 << 29) % wide, torch.arange(8) + wide - 8]).cuda()
+    w1 = torch.randn(F * d, 16, device="cuda", generator=gen) * 0.1
+    params = SimpleNamespace(emb=torch.randn(F * n, d, device="cuda", generator=gen), W=[torch.zeros(F * d, wide, device="cuda"), torch.randn(wide, 1, device="cuda", generator=gen)],
+                             b=[torch.zeros(wide, device="cuda"), torch.zeros(1, device="cuda")])
+    params.W[0][:, cols] = w1
+    y = (torch.arange(n, device="cuda") % 3 == 0).float()
+    empty = SimpleNamespace(task_offsets=np.zeros(2, dtype=np.int64), bag_offsets=torch.zeros(1, dtype=torch.int64, device="cuda"),
+                            indices=torch.zeros(0, dtype=torch.int32, device="cuda"), dense=torch.zeros(0, 0, device="cuda"), labels=torch.zeros(0, device="cuda"))
+    query = SimpleNamespace(task_offsets=np.array([0, n], dtype=np.int64), bag_offsets=torch.arange(n * F + 1, dtype=torch.int64, device="cuda"),
+                            indices=(torch.arange(n * F, device="cuda") // F).int(), dense=torch.zeros(n, 0, device="cuda"), labels=y)   # sample s: row s of every table
+    ctx = gm(F, [n] * F, d, 0, [F * d, wide, 1], 1, workspace_bytes=52 << 30)
+    out = ctx.meta_step(empty, query, params, 0.1, 0, 1)
+    got = out["emb_grad"][:F * n].reshape(F, n, d).permute(1, 0, 2).reshape(n, F * d).clone()
+    ctx.close()
+    bf = lambda t: t.bfloat16().float()   # noqa: E731
+    w, w2 = bf(w1), params.W[1][cols, 0]
+    h = bf(torch.relu(bf(params.emb.reshape(F, n, d).permute(1, 0, 2).reshape(n, F * d)) @ w))
+    delta = bf((torch.sigmoid(h @ w2) - y)[:, None] / n * w2 * (h > 0))
+    want = delta @ w.T
+    worst, largest = (got - want).norm(dim=1).max().item(), want.norm(dim=1).max().item()
+    assert worst <= 2e-2 * largest and largest > 0
