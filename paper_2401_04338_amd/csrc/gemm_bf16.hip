@@ -411,7 +411,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(GemmBArgs a, in
     if constexpr (XT) {
         const GemmExt& x = a.ext;
         int n_kt = 0;
-        for (int e = 0; e < x.n; ++e) n_kt += 2 * ((x.rows[e][g + 1] - x.rows[e][g] + GK - 1) / GK);
+        for (int e = 0; e < x.n; ++e) n_kt += 2 * max((x.rows[e][g + 1] - x.rows[e][g] + GK - 1) / GK, 1);   // (no rows: one tile of zeros)
         gemm_tiles<BM, BN, WM, WN, DEPTH, NS, false, true>(acc, smem, M, N, m0, n0, n_kt, [&](int pr) {
             const bool on = pr < 2 * x.n;
             const int e = on ? pr >> 1 : 0;
