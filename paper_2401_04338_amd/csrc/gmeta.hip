@@ -2994,9 +2994,11 @@ extern "C" int gm_group_batch(gm_ctx* c, int64_t n, int64_t nnz, const int64_t* 
     // query records.  Where (task, batch) takes few bits the batches follow from counts on the host, and the order itself is
     // made on the device from GROUP_DEVICE_N records on, else by the same counting sort on the host; numbers of more bits
     // are sorted on the host.
-    HostImages keep;   // (the stream is drained on every way out)
+    std::vector<int32_t> perm;
+    u32 total[3];      // offsets at the sets' borders
+    HostImages keep;   // (the stream is drained on every way out, before what copies read and write goes)
     keep.st = st;
-    keep.held.resize(2);
+    keep.held.resize(1);
     Arena both;
     both.base = c->ws; both.cap = c->ws_bytes; both.off = c->persistent;
     int32_t* perm_dev = both.get<int32_t>(n + 2);
@@ -3014,7 +3016,6 @@ extern "C" int gm_group_batch(gm_ctx* c, int64_t n, int64_t nnz, const int64_t* 
         sup->task_offsets[T] = nw[0];
         qry->task_offsets[T] = nw[1];
     };
-    std::vector<int32_t> perm;
     bool on_device = false;
     const GroupKeys gk = group_keys(task, batch_id, n);
     if (gk.bits >= 0) {
@@ -3087,7 +3088,8 @@ extern "C" int gm_group_batch(gm_ctx* c, int64_t n, int64_t nnz, const int64_t* 
             scan_dev = ar.get<u32>(scan_tmp_words(nbags + 1));
             if (ar.overflow) return fail(c, GM_ERR_WORKSPACE, "workspace too small for the grouping (%zu bytes needed)", ar.off);
         }
-        u32 total[3] = {0, 0, 0}, hs[ST_WORDS];   // offsets at the sets' borders
+        u32 hs[ST_WORDS];
+        total[0] = total[1] = total[2] = 0;
         if (!on_device && nd_all > 0)
             HIPCHK(c, hipMemcpyAsync(perm_dev, perm.data() + (w0 == 1 ? nw[0] : 0), nd_all * sizeof(int32_t), hipMemcpyHostToDevice, st));
         if (nbags > 0) {
