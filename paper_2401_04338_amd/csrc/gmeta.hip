@@ -879,6 +879,22 @@ static int gemm_bn(const gm_ctx* c, int bm, int N, int K) {
     return K >= 1024 ? 256 : 128;
 }
 
+// Row tile of products of N columns and contraction K whose rows are cut into mtiles(bm) tiles: bm, or smaller where compute units
+// would be left without a tile (the contraction of a tile is a serial chain whatever its size).  256 x 256 tiles become four each,
+// and pay down to half a tile a compute unit: second-order steps of 64 / 72 / 96 / 127 tasks of 256 rows (1677-512-256, 128 / 144 / 192 /
+// 254 tiles) in 256 rows 2.52 / 2.80 / 3.39 / 4.28 ms, in 128 rows 2.47 / 2.81 / 3.42 / 4.37; 16 / 18 / 24 tasks of 512 rows
+// (4109-1024-512-256, 128 / 144 / 192) 3.28 / 3.78 / 4.32 and 3.22 / 3.83 / 4.45; products of shared weights alike (28 x 512 rows, 224
+// tiles, 3.36 / 3.42).  Narrower tiles become two each: 50 / 70 tasks of 256 rows (1677-264-136, 150 / 210 tiles of 256 x 128) 1.96 / 2.43
+// and 1.94 / 2.43; in 128 rows / in 64 20 tasks of 128 rows (160 tiles) 2.73 / 2.67, of 256 rows 1.15 / 1.16.
+template <class MTiles>
+static int row_tile(const gm_ctx* c, int bm, int N, int K, MTiles&& mtiles) {
+    for (; bm > 64; bm /= 2) {
+        const int bn = gemm_bn(c, bm, N, K);
+        if (mtiles(bm) * ((N + bn - 1) / bn) >= (bn == 256 ? c->n_cus / 2 + 1 : c->n_cus)) break;
+    }
+    return bm;
+}
+
 // out[rows, ld_l] = epi( sum_p in_p[rows, ld_{l-1}] * W_p,l + bias )
 // The factors of th's layer-l weights, for a product with `in` (forward: in * W, else in * W^T): the thin products with P (Q)
 // are made here, in one launch, the ones with Q (P) are added to a's list.
@@ -1021,9 +1037,7 @@ static Grp whole_group(const gm_ctx* c, const Grp& g) {
     w.G = 1;
     w.tile_g = w.tile_m = nullptr;
     w.n_mtiles = 0;
-    w.bm = 256;
-    auto tiles = [&](int bm) { const int bn = gemm_bn(c, bm, c->ld[1], c->ld[0]); return (g.rows + bm - 1) / bm * ((c->ld[1] + bn - 1) / bn); };
-    while (w.bm > 64 && tiles(w.bm) < c->n_cus) w.bm /= 2;
+    w.bm = row_tile(c, 256, c->ld[1], c->ld[0], [&](int bm) { return (g.rows + bm - 1) / bm; });
     return w;
 }
 
@@ -1712,21 +1726,16 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
     return d;
 }
 
-// Row tile of the forward and backward products: by the tasks' average size, but smaller where the first layer's tiles would
-// leave compute units without one (the contraction of a tile is a serial chain whatever its size).
+// Row tile of the forward and backward products: by the tasks' average size and how the first layer's tiles fill the device.
 static int pick_bm(const gm_ctx* c, const Batch& B) {
     if (B.T == 0) return 64;
     const int64_t avg = (B.poff_s[B.T] + B.poff_q[B.T]) / (2 * (int64_t)B.T);
     if (!c->mlp_dtype) return 64;
-    int bm = avg >= 192 ? 256 : (avg >= 96 ? 128 : 64);
-    auto tiles = [&](int rows) {
+    return row_tile(c, avg >= 192 ? 256 : (avg >= 96 ? 128 : 64), c->ld[1], c->ld[0], [&](int bm) {
         int64_t m = 0;
-        for (int t = 0; t < B.T; ++t) m += (B.poff_s[t + 1] - B.poff_s[t] + rows - 1) / rows;
-        const int cols = gemm_bn(c, rows, c->ld[1], c->ld[0]);
-        return m * ((c->ld[1] + cols - 1) / cols);
-    };
-    while (bm > 64 && tiles(bm) < c->n_cus) bm /= 2;
-    return bm;
+        for (int t = 0; t < B.T; ++t) m += (B.poff_s[t + 1] - B.poff_s[t] + bm - 1) / bm;
+        return m;
+    });
 }
 
 // splits the tasks into waves that fit `avail` bytes of workspace
