@@ -2,7 +2,7 @@
 //
 // One kernel serves every dense product of the MAML step (G-Meta Alg. 1: inner forward, local
 // back-propagation, outer forward, and the tangent passes of the second-order term):
-//     C_g[M, N] = sum_p  A_p,g[M, K] * B_p,g[K, N]          (p = 1 or 2 products)
+//     C_g[M, N] = sum_p  A_p,g[M, K] * B_p,g[K, N]          (up to GEMM_MAX_PAIRS products, and those of GemmExt)
 // A lane's MFMA fragment is 8 consecutive contraction values.  An operand stored contraction-contiguous
 // delivers them as one 16-byte LDS read; an operand stored with the contraction index slowest (template
 // flags KA / KB) goes to LDS row by row as it lies in memory and the lane collects its 8 values with two
@@ -480,9 +480,8 @@ void launch_gemm_bf16(hipStream_t st, const GemmBArgs& a, int bm, int bn) {
 }
 
 // Weight-gradient form: both operands stored with the contraction index slowest (A [K, M], B [K, N]).  tile: 128, or 256
-// (N a multiple of 256): worth it when the contraction is thousands of rows long -- per
-// task (K = a task's rows, every task writing its own [M, N]) the product is bound by what it writes, and more
-// workgroups per compute unit hide that better than wider tiles.
+// (N a multiple of 256), which the caller takes from some 200 rows of a group on where they fill the device.  In 128 x 128 tiles a
+// product per task (K = a task's rows, every task writing its own [M, N]) is bound by what it writes.
 template <int EP>
 static void launch_kmajor_tile(hipStream_t st, const GemmBArgs& a, int tile) {
     if (tile == 256) launch_variant<256, 256, 2, 4, 1, 2, true, true, EP>(st, a);

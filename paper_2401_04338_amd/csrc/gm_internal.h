@@ -264,7 +264,7 @@ void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows
                         int64_t n_rows, float scale);
 
 // ------------------------------------------------------------------ MLP kernels
-enum { EPI_NONE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_MASK = 2, EPI_MASK = 3, EPI_AXPBY = 4, EPI_SPLIT = 5 };   // SPLIT: c1 * value as bf16, and what that leaves as another
+enum { EPI_NONE = 0, EPI_BIAS_RELU = 1, EPI_BIAS_MASK = 2, EPI_MASK = 3, EPI_AXPBY = 4, EPI_SPLIT = 5 };   // SPLIT: ext.c[e] * value as bf16, and what that leaves as another
 
 // Widest matrix (columns, padded).  The products reach a tile's rows by 32-bit byte offsets from the first of them and ask for what
 // lies outside from 2^31 on: 256 rows of bf16 or 128 of fp32, at this width 2^31 bytes.

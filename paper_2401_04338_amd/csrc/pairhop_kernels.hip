@@ -394,7 +394,8 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
     a.max_tile_rows = max_tile_rows > 0 ? (max_tile_rows + 31) / 32 * 32 : 1 << 20;
     a.small_n = PC_SMALL_N;
     // Eight waves where a compute unit's LDS then holds two workgroups, whose phases hide each other's latency; else sixteen,
-    // which take twice the rows a tile.
+    // which take twice the rows a tile.  A single task of more than 512 rows sends all that share its launch (those of more than
+    // PC_SMALL_ROWS) through sixteen waves and batches of 32 hot rows: its bags' numbers take ten of a lookup's 16 bits.
     auto larger = [&]() {
         if (max_rows > 512) launch_pair_count_nt<1024, 5>(st, a, Tw, max_tf, max_rows);   // (a bag's number takes ten bits)
         else if (pc_lds_need(512, 6, pc_n_max(max_tf), max_rows, a.max_tile_rows) <= PC_TWO_LDS) launch_pair_count_nt<512, 6>(st, a, Tw, max_tf, max_rows);
