@@ -129,7 +129,8 @@ def _numpy_groups(F, st, num, den):
 @pytest.mark.parametrize("n,tasks,batches,t_lo,b_lo,num,den", [
     (32767, 37, 2, 0, 0, 1, 2), (32768, 37, 2, 0, 0, 1, 2), (40011, 700, 3, 4093, -2, 2, 3),      # host / device order; numbers across a power of two, below zero
     (33000, 1, 1, 5, 9, 1, 2), (50000, 4096, 2, -4096, 1 << 40, 1, 3),                             # one batch; all 13 bits
-    (9000, 9000, 1, 0, 0, 1, 2), (10000, 50, 2, -(1 << 62), 0, 0, 1), (30, 4, 2, 100, 7, 1, 1)])  # more bits; no support set; no query set
+    (9000, 9000, 1, 0, 0, 1, 2), (10000, 50, 2, -(1 << 62), 0, 0, 1), (30, 4, 2, 100, 7, 1, 1),    # more bits; no support set; no query set
+    (255, 1000, 1, 0, 0, 1, 2), (256, 1000, 1, 0, 0, 1, 2), (3, 3000, 1, 0, 0, 1, 2)])             # more than four numbers a record, and not; batches of one
 @pytest.mark.parametrize("room", ["all", "no_sort", "one_set"])
 def test_orders_on_host_and_device(n, tasks, batches, t_lo, b_lo, num, den, room):
     if not torch.cuda.is_available():
