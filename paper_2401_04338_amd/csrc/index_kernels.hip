@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
                                      int64_t n_all, int shift, int nblk, TaskOf tk, SegTab seg) {
     constexpr int NB = 1 << BITS, DPT = NB > NT ? NB / NT : 1;   // digits per thread in the per-digit phase
     constexpr int TILE = NT * RS_ITEMS, WAVES = NT / WAVE;
-    __shared__ uint16_t cnt[WAVES][NB];
+    __shared__ __attribute__((aligned(16))) uint16_t cnt[WAVES][NB];   // (cleared four bytes at a time)
     __shared__ u32 digstart[NB];
     __shared__ u32 skeys[TILE];
     __shared__ u32 svals[TILE];
