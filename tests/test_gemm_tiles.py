@@ -56,6 +56,30 @@ def test_row_tiles(gm, hidden, rows, many, K):  # noqa: F811
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("K,order", [(1, 1), (3, 2)])
+def test_forward_and_backward_tiles(gm, K, order):  # noqa: F811
+    """Enough tasks that the products keep 256-row tiles: the same bits in 256 x 256 tiles as in 256 x 128 ones, with rows and contractions
+    that are no multiples of a tile and tasks of one row."""
+    f, T = 8, 150
+    dims = [f * D + NDENSE, 512, 256, 1]
+    gen = torch.Generator("cuda").manual_seed(8)
+    params = SimpleNamespace(emb=torch.randn(f * OWN * T, D, device="cuda", generator=gen) * 0.3,
+                             W=[torch.randn(a, b, device="cuda", generator=gen) / a ** 0.5 for a, b in zip(dims[:-1], dims[1:])],
+                             b=[torch.randn(b, device="cuda", generator=gen) * 0.1 for b in dims[1:]])
+    sup, qry = (_sets([(201, 257, 256, 1 + w, 480)[t % 5] for t in range(T)], w, f) for w in (0, 1))
+    got = []
+    for columns in (128, 256):
+        ctx = gm(f, [OWN * T] * f, D, NDENSE, dims, 1, workspace_bytes=8 << 30)
+        ctx.configure("gemm_tile_n", columns)
+        out = ctx.meta_step(sup, qry, params, 0.1, K, order)
+        n = int(out["n_emb_rows"].item())
+        got.append([x.clone() for x in (out["task_loss"], *out["dW"], *out["db"], out["emb_grad"][:n])])
+        ctx.close()
+    assert float(got[0][-1].abs().max()) > 0
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("K", [1, 3, 4])
 def test_weight_gradient_tiles(gm, K):  # noqa: F811
     """Tasks of about 200 rows under a first layer wide enough for 256 x 256 tiles of its gradients (remainders in both directions
