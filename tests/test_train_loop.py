@@ -24,7 +24,7 @@ def _same_params(a, b):
 
 
 @pytest.mark.parametrize("bf", [0, 1], ids=["fp32", "bf16"])
-@pytest.mark.parametrize("mode", ["overlapped", "fallback"])
+@pytest.mark.parametrize("mode", ["overlapped", "fallback", "serial"])
 def test_train_loop_equals_single_iterations(bf, mode):
     from paper_2401_04338_amd import GMeta
     if not torch.cuda.is_available():
@@ -43,8 +43,8 @@ def test_train_loop_equals_single_iterations(bf, mode):
     probe = GMeta.from_config(cfg, workspace_bytes=1 << 20)
     need = max(probe.workspace_bytes(len(s.task_offsets) - 1, s.n_samples, q.n_samples, s.nnz, q.nnz, K, order) for s, q in batches)
     probe.close()
-    # overlapped: room for two index arenas; fall-back: a workspace that holds one batch and the lists only
-    ws = (1 << 30) if mode == "overlapped" else int(need * 1.15) + (4 << 20)
+    # overlapped: room for two index arenas; fall-back: little more than that; serial: a workspace that holds one batch only
+    ws = {"overlapped": 1 << 30, "fallback": int(need * 1.15) + (4 << 20), "serial": need}[mode]
     ctx = GMeta.from_config(cfg, workspace_bytes=ws)
     one = _clone(params, dev)
     want_losses = [float(ctx.meta_train_step(s, q, one, cfg.inner_lr, K, order, beta).item()) for s, q in batches]
