@@ -552,35 +552,52 @@ __device__ __forceinline__ void hop_multiply(const bf16_t* zb, const uint4 (&ara
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
-                    acc[s][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s], bfrag[c][sp], acc[s][c], 0, 0, 0);
+                    acc[s][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag[c][sp], af[s], acc[s][c], 0, 0, 0);
     }
 }
 
-// Rows [row0, row0 + 32) and one column tile of the output; D layout of the 32x32 tile: register v of lane (ln, h) is
-// row 8*(v/4) + 4*h + v%4, column ln.  (y_in may be y_out: a tile's loads are issued together, ahead of its stores.)
-__device__ __forceinline__ void hop_read_y(const PairHopOut& out, int64_t base, int row0, int n_out, float (&y)[16]) {
-    const int h = (threadIdx.x & 63) >> 5, ld = (int)out.ld;
-    const float* src = out.y_in ? out.y_in + base : nullptr;
+// A wave's 32 x (NC * 32) strips of the output.  The first operand of the MFMAs is the Z fragment, so a lane holds row ln of each
+// 32 x 32 block and four consecutive columns per group of four registers; stored from there, or with the operands the other way
+// round (one row's 32 columns, four bytes a lane), a strip of 64 columns takes 32 reads, 32 stores of fp32 and 32 of two bytes a lane,
+// and the memory pipeline is busy with instructions.  Through LDS, 16 bytes a lane, whole row segments: eight of each.
+// (y_in may be y_out: a strip's reads are asked for together, ahead of its stores.)
+template <int NC>
+struct HopStrip {
+    static constexpr int SW = NC * 32, ELD = SW + 4, LPR = SW / 4, RPI = 64 / LPR, IT = 32 / RPI;   // width, LDS row stride, lanes a row, rows a pass
+    static constexpr int FLOATS = 32 * ELD;   // of LDS, per wave
+    RowBuffer yi, yo, yb;
+    int er, ec;
+    float c;
+    // rows [0, rows) from row `row` on, columns [col, col + SW)
+    __device__ __forceinline__ HopStrip(const PairHopOut& out, int64_t row, int rows, int64_t col)
+        : yi(out.y_in ? out.y_in + col : nullptr, out.y_in ? row : 0, out.ld, 4, out.y_in ? rows : 0, (int)(threadIdx.x & 63) / LPR, (int)(threadIdx.x & 63) % LPR * 4, true),
+          yo(out.y_out ? out.y_out + col : nullptr, out.y_out ? row : 0, out.ld, 4, out.y_out ? rows : 0, (int)(threadIdx.x & 63) / LPR, (int)(threadIdx.x & 63) % LPR * 4, true),
+          yb(out.y_bf ? out.y_bf + col : nullptr, out.y_bf ? row : 0, out.ld, 2, out.y_bf ? rows : 0, (int)(threadIdx.x & 63) / LPR, (int)(threadIdx.x & 63) % LPR * 4, true),
+          er((int)(threadIdx.x & 63) / LPR), ec((int)(threadIdx.x & 63) % LPR * 4), c(out.c) {}
+    __device__ __forceinline__ void request(int r0, float4 (&y)[IT]) const {   // (no input: zeros)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int rl = 8 * (v >> 2) + 4 * h + (v & 3);
-        y[v] = (src && row0 + rl < n_out) ? src[rl * ld] : 0.f;
+        for (int it = 0; it < IT; ++it) y[it] = yi.load4(r0 + it * RPI);
     }
-}
-__device__ __forceinline__ void hop_write_y(const PairHopOut& out, int64_t base, int row0, int n_out, const float (&y)[16], const ph_float16& acc) {
-    const int h = (threadIdx.x & 63) >> 5, ld = (int)out.ld;
-    float* yo = out.y_out ? out.y_out + base : nullptr;
-    bf16_t* yb = out.y_bf ? out.y_bf + base : nullptr;
-    const float c = out.c;
+    __device__ __forceinline__ void park(float* E, const ph_float16 (&acc)[NC]) const {
+        const int ln = threadIdx.x & 31, h = (threadIdx.x & 63) >> 5;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int rl = 8 * (v >> 2) + 4 * h + (v & 3);
-        if (row0 + rl >= n_out) continue;
-        const float r = y[v] + c * acc[v];
-        if (yo) yo[rl * ld] = r;
-        if (yb) yb[rl * ld] = f2bf(r);
+        for (int j = 0; j < NC; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(E + ln * ELD + j * 32 + 8 * q + 4 * h) = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
     }
-}
+    __device__ __forceinline__ void finish(const float* E, int r0, const float4 (&y)[IT]) const {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the strip is this wave's own: LDS order within the wave suffices
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const float4 x = *reinterpret_cast<const float4*>(E + (it * RPI + er) * ELD + ec);
+            const float4 r = make_float4(fmaf(c, x.x, y[it].x), fmaf(c, x.y, y[it].y), fmaf(c, x.z, y[it].z), fmaf(c, x.w, y[it].w));
+            yo.store(r0 + it * RPI, r);
+            yb.store(r0 + it * RPI, make_uint2(f2bf2(r.x, r.y), f2bf2(r.z, r.w)));
+        }
+        asm volatile("" ::: "memory");
+    }
+};
 
 // A tile of up to 64 * NS * 2 out-rows from row0 on.  NS strips per wave, NC column tiles per wave: with fewer than all of
 // them the waves lie side by side along the columns.
@@ -590,7 +607,7 @@ __device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M
     constexpr int WC = DS / 32 / NC;   // waves along the columns
     const int colsP = pad64(n_in);
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
-    const int ct0 = (wv % WC) * NC, row_w = row0 + (wv / WC) * 32 * NS;   // first out-row of this wave
+    const int ct0 = (wv % WC) * NC, row_w = __builtin_amdgcn_readfirstlane(row0 + (wv / WC) * 32 * NS);   // first out-row of this wave
     const bool wave_on = row_w < n_out;               // its strips then lie inside the padded matrix
     const uint8_t* Mw = M + (size_t)(row_w + ln) * colsP + h * 32;
     HopStage<DS> st(Z0, ldz, n_in);
@@ -611,6 +628,8 @@ __device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M
             dst[s][1] = src[1];
         }
     };
+    const HopStrip<NC> strip(out, row_base + row_w, __builtin_amdgcn_readfirstlane(max(min(n_out - row_w, 32 * NS), 0)), colz + __builtin_amdgcn_readfirstlane(ct0 * 32));
+    float4 y[2][HopStrip<NC>::IT];
     // Two LDS buffers: while chunk c is multiplied out of one, chunk c+1 (loaded during the multiplication) is
     // split into the other; one barrier per chunk.
     if (colsP > 0) {
@@ -620,34 +639,31 @@ __device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M
     }
     __syncthreads();
     int cur = 0;
-    for (int kc = 0; kc < colsP; kc += PH_KC) {
-        const int kn = kc + PH_KC;
-        if (kn < colsP) {
-            st.load(kn);
-            load_a(kn, anext);
-        }
+    for (int kn = PH_KC; kn < colsP; kn += PH_KC) {
+        st.load(kn);
+        load_a(kn, anext);
         __builtin_amdgcn_sched_barrier(0);   // the loads above are consumed only after the multiplication below
         if (wave_on) hop_multiply<DS, NS, NC>(zs + cur * HopStage<DS>::WORDS, araw, ct0, acc);
         __builtin_amdgcn_sched_barrier(0);
-        if (kn < colsP) {
-            cur ^= 1;
-            st.store(zs + cur * HopStage<DS>::WORDS, kn);
+        cur ^= 1;
+        st.store(zs + cur * HopStage<DS>::WORDS, kn);
 #pragma unroll
-            for (int s = 0; s < NS; ++s) { araw[s][0] = anext[s][0]; araw[s][1] = anext[s][1]; }
-            __syncthreads();
-        }
+        for (int s = 0; s < NS; ++s) { araw[s][0] = anext[s][0]; araw[s][1] = anext[s][1]; }
+        __syncthreads();
     }
+    strip.request(0, y[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave_on && colsP > 0) hop_multiply<DS, NS, NC>(zs + cur * HopStage<DS>::WORDS, araw, ct0, acc);
+    __syncthreads();   // every wave is done with the staged chunks
     if (!wave_on) return;
+    float* E = reinterpret_cast<float*>(zs) + wv * HopStrip<NC>::FLOATS;
+    static_assert(4 * HopStrip<NC>::FLOATS * 4 <= 2 * HopStage<DS>::WORDS * 2, "the waves' strips fit the staged chunks' LDS");
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            float y[16];
-            const int r = row_w + s * 32;
-            const int64_t base = (row_base + r) * out.ld + colz + (ct0 + c) * 32 + ln;
-            hop_read_y(out, base, r, n_out, y);
-            hop_write_y(out, base, r, n_out, y, acc[s][c]);
-        }
+    for (int s = 0; s < NS; ++s) {
+        strip.park(E, acc[s]);
+        if (s + 1 < NS) strip.request((s + 1) * 32, y[(s + 1) & 1]);
+        strip.finish(E, s * 32, y[s & 1]);
+    }
 }
 
 template <int DS>
@@ -711,21 +727,18 @@ __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
     const int row_w = (wv >> 1) * 32, ct = wv & 1;
     uint4 araw[2][1][2];
-    float y[2][16];
-    int n_out[2];
-    int64_t base[2];
+    float4 y[2][HopStrip<1>::IT];
     bool on[2];
+    auto strip = [&](int o) {
+        const int rows = on[o] ? a.out[o].real_off[t + 1] - a.out[o].real_off[t] - row_w : 0;
+        return HopStrip<1>(a.out[o], (int64_t)a.out[o].row_off[t] + __builtin_amdgcn_readfirstlane(row_w), __builtin_amdgcn_readfirstlane(min(rows, 32)), colz + __builtin_amdgcn_readfirstlane(ct * 32));
+    };
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
         on[o] = false;
-        n_out[o] = 0;
-        base[o] = 0;
         if (!a.out[o].enabled) continue;
-        n_out[o] = a.out[o].real_off[t + 1] - a.out[o].real_off[t];
-        on[o] = row_w < n_out[o] && ct < NCT;
-        if (!on[o]) continue;
-        base[o] = ((int64_t)a.out[o].row_off[t] + row_w) * a.out[o].ld + colz + ct * 32 + ln;
-        if (n_in > 0) {
+        on[o] = row_w < a.out[o].real_off[t + 1] - a.out[o].real_off[t] && ct < NCT;
+        if (on[o] && n_in > 0) {
             const uint4* src = reinterpret_cast<const uint4*>(a.mat + a.out[o].mat_off[t] + ((size_t)f * 64 + row_w + ln) * 64 + h * 32);
             araw[o][0][0] = src[0];
             araw[o][0][1] = src[1];
@@ -738,16 +751,24 @@ __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
     }
 #pragma unroll
     for (int o = 0; o < 2; ++o)
-        if (on[o]) hop_read_y(a.out[o], base[o], row_w, n_out[o], y[o]);
+        if (on[o]) strip(o).request(0, y[o]);
     __syncthreads();
+    ph_float16 acc[2][1][1];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[o][0][0][v] = 0.f;
+        if (on[o] && n_in > 0) hop_multiply<DS, 1, 1>(zs, araw[o], ct, acc[o]);
+    }
+    __syncthreads();   // every wave is done with the staged chunk
+    float* E = reinterpret_cast<float*>(zs) + (NCT == 1 ? wv >> 1 : wv) * HopStrip<1>::FLOATS;
+    static_assert(2 * NCT * HopStrip<1>::FLOATS * 4 <= HopStage<DS>::WORDS * 2, "the strips fit the staged chunk's LDS");
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
         if (!on[o]) continue;
-        ph_float16 acc[1][1];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
-        if (n_in > 0) hop_multiply<DS, 1, 1>(zs, araw[o], ct, acc);
-        hop_write_y(a.out[o], base[o], row_w, n_out[o], y[o], acc[0][0]);
+        const HopStrip<1> sp = strip(o);
+        sp.park(E, acc[o][0]);
+        sp.finish(E, 0, y[o]);
     }
 }
 
