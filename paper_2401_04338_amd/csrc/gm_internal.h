@@ -272,6 +272,7 @@ enum { MAX_WIDTH = 1 << 22 };
 
 typedef u32 u32x2 __attribute__((ext_vector_type(2)));
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+enum { STREAM = 2 };   // hint of a buffer access: non-temporal
 // What an epilogue reads and writes.
 struct RowBuffer {   // rows [first, first + rows) of a row-major matrix, from column n on; lanes that hold no column touch nothing
     __amdgpu_buffer_rsrc_t rs;
@@ -282,10 +283,10 @@ struct RowBuffer {   // rows [first, first + rows) of a row-major matrix, from c
         at = nok ? (u32)er * ld + (u32)n * (u32)elem : 1u << 31;   // (128 rows of at most MAX_WIDTH columns stay below it)
     }
     __device__ __forceinline__ int off(int r) const { return (int)(at + (u32)r * ld); }
-    __device__ __forceinline__ float4 load4(int r) const { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off(r), 0, 0)); }
+    template <int HINT = 0> __device__ __forceinline__ float4 load4(int r) const { return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off(r), 0, HINT)); }
     __device__ __forceinline__ uint2 load2(int r) const { return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, off(r), 0, 0)); }
-    __device__ __forceinline__ void store(int r, float4 v) const { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off(r), 0, 0); }
-    __device__ __forceinline__ void store(int r, uint2 v) const { __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, off(r), 0, 0); }
+    template <int HINT = 0> __device__ __forceinline__ void store(int r, float4 v) const { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off(r), 0, HINT); }
+    template <int HINT = 0> __device__ __forceinline__ void store(int r, uint2 v) const { __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, off(r), 0, HINT); }
 };
 struct GemmArgs {
     // up to two products accumulated: C = A1*B1 (+ A2*B2)

@@ -433,7 +433,7 @@ void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int 
 //                                           a few tasks are dealt in runs of fields.
 // Measured: the four hops of a step of 700 tasks of log-normal size (median 32 + 32 rows) x 40 fields of 64 columns
 // 11.6 -> 1.95 ms, the three of 201 tasks of 75..225 + 122..365 rows x 26 fields 2.34 -> 1.43 ms; the six of 512 tasks x
-// (256 + 256) rows x 26 fields 6.7 -> 6.5 ms, 4.6 TB/s (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
+// (256 + 256) rows x 26 fields 6.7 -> 6.5 ms (before: a grid of (task, output, 256 rows) in task order, 64 rows a wave).
 // Inside a run of fields the tiles come first, field by field, where an output has several of equal height: they find the field's Z
 // in L2 (two hops of 256 tasks x (512 + 512) rows x 64 fields, two tiles each, fetch 15.4 GB instead of 19.6; eleven runs of a side
 // 4.86..5.12 against 5.05..5.35 ms).  Otherwise the fields come first.  With one tile per output a tile's pieces of the same rows follow
@@ -561,6 +561,9 @@ __device__ __forceinline__ void hop_multiply(const bf16_t* zb, const uint4 (&ara
 // round (one row's 32 columns, four bytes a lane), a strip of 64 columns takes 32 reads, 32 stores of fp32 and 32 of two bytes a lane,
 // and the memory pipeline is busy with instructions.  Through LDS, 16 bytes a lane, whole row segments: eight of each.
 // (y_in may be y_out: a strip's reads are asked for together, ahead of its stores.)
+// Y streams past once, read or written: with the non-temporal hint it leaves the caches to the counts, of which a chunk takes half a
+// line at a time, and to Z, which an output's other tiles read again.  The six hops of 512 tasks x (256 + 256) rows x 26 fields
+// 5.25 -> 4.61 ms (hint on the reads and fp32 stores only 4.72; on the counts too 6.1).
 template <int NC>
 struct HopStrip {
     static constexpr int SW = NC * 32, ELD = SW + 4, LPR = SW / 4, RPI = 64 / LPR, IT = 32 / RPI;   // width, LDS row stride, lanes a row, rows a pass
@@ -576,7 +579,7 @@ struct HopStrip {
           er((int)(threadIdx.x & 63) / LPR), ec((int)(threadIdx.x & 63) % LPR * 4), c(out.c) {}
     __device__ __forceinline__ void request(int r0, float4 (&y)[IT]) const {   // (no input: zeros)
 #pragma unroll
-        for (int it = 0; it < IT; ++it) y[it] = yi.load4(r0 + it * RPI);
+        for (int it = 0; it < IT; ++it) y[it] = yi.load4<STREAM>(r0 + it * RPI);
     }
     __device__ __forceinline__ void park(float* E, const ph_float16 (&acc)[NC]) const {
         const int ln = threadIdx.x & 31, h = (threadIdx.x & 63) >> 5;
@@ -592,8 +595,8 @@ struct HopStrip {
         for (int it = 0; it < IT; ++it) {
             const float4 x = *reinterpret_cast<const float4*>(E + (it * RPI + er) * ELD + ec);
             const float4 r = make_float4(fmaf(c, x.x, y[it].x), fmaf(c, x.y, y[it].y), fmaf(c, x.z, y[it].z), fmaf(c, x.w, y[it].w));
-            yo.store(r0 + it * RPI, r);
-            yb.store(r0 + it * RPI, make_uint2(f2bf2(r.x, r.y), f2bf2(r.z, r.w)));
+            yo.store<STREAM>(r0 + it * RPI, r);
+            yb.store<STREAM>(r0 + it * RPI, make_uint2(f2bf2(r.x, r.y), f2bf2(r.z, r.w)));
         }
         asm volatile("" ::: "memory");
     }
