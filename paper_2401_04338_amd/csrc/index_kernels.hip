@@ -43,29 +43,49 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sh, int* total) {
 // ------------------------------------------------------------------------------------------------
 // validation + per-(task, field) lookup counts
 // ------------------------------------------------------------------------------------------------
-// One task per blockIdx.x, its bags dealt to gridDim.y workgroups; cnt_sup / cnt_qry must be zero on entry.
+// One (task, set) per workgroup, or gridDim.z of them where the tasks are few: then cnt_sup / cnt_qry must be zero on entry.
 // A well-formed input that exceeds a size limit of the index kernels (a bag of more than 65,535 lookups, a task of more
 // than 65,536 samples in one set) raises ST_TOO_LARGE, not ST_BAD_INDEX.
 // uniform_rows >= 0: every table has that many rows, so an index is checked without knowing its field: the task's
 // lookups, one contiguous range, are then read by all lanes in order instead of bag by bag.
-__global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const int64_t* field_base,
+// Bound: the two reads and the atomics.  Those that leave the workgroup queue at the memory side (some 30 ns each on one
+// address, about one a nanosecond in all), so there are none but a status word's where a workgroup has its (task, set) for itself,
+// and that one only where the word holds less: 13 workgroups a task, both sets in each, took 93 us for 128 tasks x (256 + 256)
+// samples x 26 fields and 160 us for 128 x (512 + 512) x 64.
+#define TC_NT 1024
+__global__ __launch_bounds__(TC_NT) void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const int64_t* field_base,
                                 int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status) {
-    extern __shared__ u32 sh_cnt[];  // [2F]
-    const int t = blockIdx.x;
-    for (int i = threadIdx.x; i < 2 * F; i += blockDim.x) sh_cnt[i] = 0;
+    extern __shared__ u32 sh_cnt[];  // [F]
+    __shared__ u32 sh_most, sh_longest, sh_flags;
+    const int t = blockIdx.x, set = blockIdx.y;
+    for (int i = threadIdx.x; i < F; i += TC_NT) sh_cnt[i] = 0;
+    if (threadIdx.x == 0) { sh_most = 0; sh_longest = 0; sh_flags = 0; }
     __syncthreads();
     bool bad = false, too_large = false;
     u32 longest = 0;
-    for (int set = 0; set < 2; ++set) {
-        const SetView& v = set ? qry : sup;
-        const int64_t nnz = set ? nnz_qry : nnz_sup;
-        const int64_t s_lo = v.task_offsets[t0 + t], s_hi = v.task_offsets[t0 + t + 1];
-        if (s_hi - s_lo > 65536) too_large = true;
-        const int64_t n = (s_hi - s_lo) * F;
-        for (int64_t i = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.y * blockDim.x) {
-            const int64_t bag = s_lo * F + i;
-            const int f = (int)(i % F);
-            const int64_t p0 = v.bag_offsets[bag], p1 = v.bag_offsets[bag + 1];
+    const SetView& v = set ? qry : sup;
+    const int64_t nnz = set ? nnz_qry : nnz_sup;
+    const int64_t s_lo = v.task_offsets[t0 + t], s_hi = v.task_offsets[t0 + t + 1];
+    if (s_hi - s_lo > 65536) too_large = true;
+    const int64_t n = (s_hi - s_lo) * F, step = (int64_t)gridDim.z * TC_NT, i0 = (int64_t)blockIdx.z * TC_NT + threadIdx.x;
+    const int64_t* bags = v.bag_offsets + s_lo * F;
+    int f = (int)((u32)i0 % (u32)F);   // field of the bag
+    const int f_step = (int)((u32)step % (u32)F);
+    for (int64_t i = i0; i < n; i += 4 * step) {
+        int64_t p[4][2];   // four bags in flight
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t j = i + k * step < n ? i + k * step : i;
+            p[k][0] = bags[j];
+            p[k][1] = bags[j + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (i + k * step >= n) break;
+            const int64_t p0 = p[k][0], p1 = p[k][1];
+            const int f0 = f;
+            f += f_step;
+            if (f >= F) f -= F;
             if (p0 < 0 || p1 < p0 || p1 > nnz) {
                 bad = true;
                 continue;
@@ -75,49 +95,43 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
                 continue;
             }
             if (uniform_rows < 0) {
-                const int64_t R = field_base[f + 1] - field_base[f];
-                for (int64_t p = p0; p < p1; ++p) {
-                    const int32_t r = v.indices[p];
+                const int64_t R = field_base[f0 + 1] - field_base[f0];
+                for (int64_t q = p0; q < p1; ++q) {
+                    const int32_t r = v.indices[q];
                     if (r < 0 || r >= R) bad = true;
                 }
             }
-            atomicAdd(&sh_cnt[set * F + f], (u32)(p1 - p0));
+            atomicAdd(&sh_cnt[f0], (u32)(p1 - p0));
             longest = max(longest, (u32)(p1 - p0));
         }
-        if (uniform_rows >= 0 && n > 0) {   // (offsets outside [0, nnz] are flagged above; the range read here is clamped)
-            const int64_t q0 = min(max(v.bag_offsets[s_lo * F], (int64_t)0), nnz), q1 = min(max(v.bag_offsets[s_hi * F], q0), nnz);
-            const int64_t step = (int64_t)gridDim.y * blockDim.x;
-            for (int64_t p = q0 + (int64_t)blockIdx.y * blockDim.x + threadIdx.x; p < q1; p += 4 * step) {
-                int32_t r[4];   // four reads in flight (past the end: the first one's index again)
+    }
+    if (uniform_rows >= 0 && n > 0) {   // (offsets outside [0, nnz] are flagged above; the range read here is clamped)
+        const int64_t q0 = min(max(bags[0], (int64_t)0), nnz), q1 = min(max(bags[n], q0), nnz);
+        for (int64_t p = q0 + i0; p < q1; p += 8 * step) {
+            int32_t r[8];   // eight reads in flight (past the end: the first one's index again)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) r[k] = v.indices[p + k * step < q1 ? p + k * step : p];
+            for (int k = 0; k < 8; ++k) r[k] = v.indices[p + k * step < q1 ? p + k * step : p];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) bad |= r[k] < 0 || r[k] >= uniform_rows;
-            }
+            for (int k = 0; k < 8; ++k) bad |= r[k] < 0 || r[k] >= uniform_rows;
         }
     }
-    if (t == 0 && blockIdx.y == 0 && threadIdx.x == 0) {  // the ends of both offset arrays
-        if (sup.bag_offsets[0] != 0 || sup.bag_offsets[sup.n_samples * F] != nnz_sup) bad = true;
-        if (qry.bag_offsets[0] != 0 || qry.bag_offsets[qry.n_samples * F] != nnz_qry) bad = true;
-    }
+    if (t == 0 && blockIdx.z == 0 && threadIdx.x == 0)  // the ends of the offset array
+        if (v.bag_offsets[0] != 0 || v.bag_offsets[v.n_samples * F] != nnz) bad = true;
     __syncthreads();
     u32 most = 0;
-    for (int i = threadIdx.x; i < 2 * F; i += blockDim.x) {
+    u32* const cnt = (set ? cnt_qry : cnt_sup) + (size_t)t * F;
+    for (int i = threadIdx.x; i < F; i += TC_NT) {
         const u32 c = sh_cnt[i];
-        if (!c) continue;
-        u32* dst = i < F ? &cnt_sup[(size_t)t * F + i] : &cnt_qry[(size_t)t * F + (i - F)];
-        most = max(most, atomicAdd(dst, c) + c);     // the (task, field)'s count so far: the last adder sees the total
+        if (gridDim.z == 1) {
+            cnt[i] = c;
+            most = max(most, c);
+        } else if (c) most = max(most, atomicAdd(&cnt[i], c) + c);     // the (task, field)'s count so far: the last adder sees the total
     }
-    // one atomic per workgroup and status word: they all queue on the same few addresses (with one per count and wave
-    // 64 tasks x 6656 bags took 56 us, 27 us now)
     for (int d = WAVE / 2; d > 0; d >>= 1) {
         most = max(most, (u32)__shfl_xor((int)most, d, WAVE));
         longest = max(longest, (u32)__shfl_xor((int)longest, d, WAVE));
     }
     const int flags = (__ballot(bad) ? 1 : 0) | (__ballot(too_large) ? 2 : 0);
-    __shared__ u32 sh_most, sh_longest, sh_flags;
-    if (threadIdx.x == 0) { sh_most = 0; sh_longest = 0; sh_flags = 0; }
-    __syncthreads();
     if ((threadIdx.x & (WAVE - 1)) == 0) {
         atomicMax(&sh_most, most);
         atomicMax(&sh_longest, longest);
@@ -125,8 +139,11 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (sh_most) atomicMax(&status[ST_MAX_TF], sh_most);
-        if (sh_longest) atomicMax(&status[ST_MAX_BAG], sh_longest);
+        auto raise = [&](u32 value, int word) {
+            if (value > __hip_atomic_load(&status[word], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&status[word], value);
+        };
+        raise(sh_most, ST_MAX_TF);
+        raise(sh_longest, ST_MAX_BAG);
         if (sh_flags & 1u) atomicOr(&status[ST_BAD_INDEX], 1u);
         if (sh_flags & 2u) atomicOr(&status[ST_TOO_LARGE], 1u);
     }
@@ -135,13 +152,13 @@ __global__ void tf_count_kernel(int F, int t0, SetView sup, SetView qry, const i
 void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status) {
     if (Tw <= 0) return;
-    launch_zero(st, ZeroJobs{3, {status, cnt_sup, cnt_qry}, {ST_WORDS, (int64_t)Tw * F, cnt_qry != cnt_sup ? (int64_t)Tw * F : 0}});
-    // A task's bags are split over workgroups of two bags per thread, down to 4096 workgroups in all: fewer leave the chip
-    // idle with few tasks (3 tasks x 65536 bags in 24 workgroups 244 us, in 384 21 us), more only add their 2 F atomics each.
-    // The largest task decides: the others' spare workgroups have nothing to add, and it alone would be the launch's time
-    // (one task of 2048 + 2048 samples and 299 of 2 + 2, 40 fields: 67 us, 589 with the average task's split).
-    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(most_bags / 512, 4096 / Tw));
-    hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, split), dim3(256), 2 * F * sizeof(u32), st, F, t0, sup, qry, field_base,
+    // A (task, set) is split, down to a bag a thread, while the workgroups are fewer than 128: a few large tasks would leave the chip
+    // idle (3 tasks x 32,768 + 32,768 bags).  The largest task decides: the others' spare workgroups have nothing to add, and it
+    // alone would be the launch's time (one task of 2048 + 2048 samples and 99 of 2 + 2).
+    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(most_bags / TC_NT, 64 / Tw));
+    const int64_t counts = split > 1 ? (int64_t)Tw * F : 0;
+    launch_zero(st, ZeroJobs{split > 1 ? 3 : 1, {status, cnt_sup, cnt_qry}, {ST_WORDS, counts, counts}});
+    hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, 2, split), dim3(TC_NT), F * sizeof(u32), st, F, t0, sup, qry, field_base,
                        nnz_sup, nnz_qry, uniform_rows, cnt_sup, cnt_qry, status);
 }
 
