@@ -135,7 +135,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
                     x = make_float4(a.c1 * x.x, a.c1 * x.y, a.c1 * x.z, a.c1 * x.w);
                 }
             }
-            if (fl.cf) cf.store(r, x);
+            if (fl.cf) cf.store<STREAM>(r, x);
             if (has_acc) {
                 const float4 ci = ci_all[i & 1][it];
                 cacc.store(r, make_float4(fmaf(a.cacc, x.x, ci.x), fmaf(a.cacc, x.y, ci.y), fmaf(a.cacc, x.z, ci.z), fmaf(a.cacc, x.w, ci.w)));
