@@ -143,8 +143,10 @@ struct FieldKeysArgs {
 void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n /* lookups of the wave, as the passes are given */);
 SegTab field_seg_tab(int F, u32* tables);
 size_t field_table_words(int F);
-void launch_segments(hipStream_t st, const u32* sorted_keys, int64_t n, u32* flags_scan, u32* scan_tmp,
-                     int64_t* emb_rows, u32* seg_start, int64_t* seg_counts /* may be null */,
+// chunk_scan: segments that begin in front of every chunk of ch keys; n_rows_out: their number.  With emb_rows or seg_counts:
+// these too (a step's row list is written by launch_seg_reduce).
+void launch_segments(hipStream_t st, const u32* sorted_keys, int64_t n, int ch, u32* chunk_scan, u32* scan_tmp,
+                     int64_t* emb_rows, u32* seg_start, int64_t* seg_counts,
                      int64_t capacity, int64_t* n_rows_out, u32* status);
 
 // ------------------------------------------------------------------ embedding kernels
@@ -252,10 +254,11 @@ HopPlan hop_plan(const std::vector<HopTask>& tasks, int fx);
 void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3], const int longest[3]);
 void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_rows, float* x_out, int ldx, bf16_t* x_bf);
 
-// keys: the sorted row keys; scan: exclusive scan of their segment-head flags and n_rows: the number of segments
+int seg_chunk(int64_t n, int F, int D);   // lookups of the segment reduction's chunks
+// keys: the sorted row keys; chunk_scan: segments before every chunk of seg_chunk keys and n_rows: the number of segments
 // (both as launch_segments left them; neither is read when the output is table-shaped)
-void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows,
-                       int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
+void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* chunk_scan, const int64_t* n_rows,
+                       int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx, int64_t* emb_rows,
                        float* emb_grad, float* partial /* seg_reduce_partial_floats(n, D), for D <= 16 with n + radix_hist_words(n, F) more */,
                        float* table /* null, or [all rows, D]: scale * every segment is ADDED to its row instead of listed */, float scale,
                        int64_t gx_rows /* of gx, each of F * D */, u32* room /* radix_hist_words(n, F) words */);

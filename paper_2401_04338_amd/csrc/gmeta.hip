@@ -1427,8 +1427,8 @@ static int global_order(gm_ctx* c, Batch& B, SortBufs& so, const SortRange& r, i
     // the table-shaped output adds every segment to the row its key names: no segment numbers, no row list
     if ((parts & ORDER_SEGMENTS) && n_rows) {
         p.p.bytes += 4.0 * (double)nnz;   // the sorted keys read once more
-        launch_segments(st, so.keys, nnz, so.keys_tmp, so.scan_tmp, emb_rows, so.seg_start, seg_counts, capacity, n_rows,
-                        status);
+        launch_segments(st, so.keys, nnz, seg_chunk(nnz, F, c->D), so.keys_tmp, so.scan_tmp, emb_rows, so.seg_start, seg_counts, capacity,
+                        n_rows, status);
     }
     return GM_OK;
 }
@@ -2085,7 +2085,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                                              (u32)(0 - (uint64_t)wp.ps0), (u32)((uint64_t)d.Ps - (uint64_t)wp.pq0)}
                                  : whole_batch_range(B);
                 jr.n_sup_rows = d.Ps; jr.n_qry_rows = d.Pq;
-                if (!table) { jr.emb_rows = out->emb_rows; jr.capacity = capacity; jr.n_rows = n_list; }
+                if (!table) { jr.capacity = capacity; jr.n_rows = n_list; }
                 jr.pair_only = d.pair && !d.any_sparse;
             }
             rc = run_index_wave(c, B, wp, w, &tf_cap, &max_bag, &max_tf, &jr);
@@ -2179,7 +2179,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             side.active = true;
             side_list = true;
             launch_fill_u32(c->side, c->d_status_side, ST_WORDS, 0);
-            global_order(c, B, b.so, whole_batch_range(B), out->emb_rows, nullptr, capacity, n_list, true);
+            global_order(c, B, b.so, whole_batch_range(B), nullptr, nullptr, capacity, n_list, true);
             HIPCHK(c, hipEventRecord(c->ev_side, c->side));
         }
         // row arithmetic of one (task, field) at a time, through LDS (no row table in HBM)
@@ -2404,7 +2404,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             {
                 Prof p(c, "seg_reduce", (double)nw * (4.0 * D + 4), 0);
                 launch_seg_reduce(st, D, F, ordered ? enc : kPlainVals, w.so.keys, w.so.keys_tmp, nullptr, nw, nw, w.so.vals, w.GX,
-                                  nullptr, seg_room(c, w.so), row_table, row_scale, d.Ps + d.Pq, w.so.hist);
+                                  nullptr, nullptr, seg_room(c, w.so), row_table, row_scale, d.Ps + d.Pq, w.so.hist);
             }
             if (side_table) HIPCHK(c, hipEventRecord(c->ev_main, st));
         } else if (ordered) {
@@ -2427,11 +2427,11 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         launch_fill_u32(st, reinterpret_cast<u32*>(out->n_emb_rows), 2, 0u);
     } else {
         if (side_list) HIPCHK(c, hipStreamWaitEvent(st, c->ev_side, 0));
-        else if (!pre && !list_ordered) global_order(c, B, b.so, whole_batch_range(B), out->emb_rows, nullptr, capacity, n_list);
+        else if (!pre && !list_ordered) global_order(c, B, b.so, whole_batch_range(B), nullptr, nullptr, capacity, n_list);
         if (F > 0) {
             Prof p(c, "seg_reduce", (double)nnz * (4.0 * D + 4), 0);
             launch_seg_reduce(st, D, F, (pre || list_ordered) ? enc : kPlainVals, b.so.keys, b.so.keys_tmp, n_list, apply ? nnz : capacity, nnz,
-                              b.so.vals, b.GX, out->emb_grad, seg_room(c, b.so), row_table, row_scale, Ps_tot + B.poff_q[T], b.so.hist);
+                              b.so.vals, b.GX, out->emb_rows, out->emb_grad, seg_room(c, b.so), row_table, row_scale, Ps_tot + B.poff_q[T], b.so.hist);
         }
     }
     if (up) up->done = apply;
