@@ -254,7 +254,7 @@ __device__ __forceinline__ bool seg_block_hot(const u32* keys, int64_t b, int64_
 // at a time, one position per lane (coalesced), and handed round the group by lane shuffles; the head flags of
 // the LG positions come back as one ballot word.  Whether a run began before the chunk or continues past it
 // follows from the head flags at the chunk's two borders, so no segment table is read here.
-// What is written goes past the caches (non-temporal), which are the gradient rows': 36 million lookups, 7 million rows listed 1.64 -> 1.52 ms;
+// What is written goes past the caches (non-temporal), which are the gradient rows': 72 million lookups, 7 million rows listed 1.64 -> 1.52 ms;
 // 26 million added to table rows 1.48 -> 1.45.
 // CH: the chunk's length, 0 where `short_ch` says it
 template <int LG, int CH>

@@ -140,7 +140,7 @@ struct FieldKeysArgs {
     u32 *keys, *vals;
     const u32 *key_pos, *tot;        // set by the launcher
 };
-void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n /* lookups of the wave, as the passes are given */);
+void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n /* lookups of the wave, as the passes are given */, int max_bag);
 SegTab field_seg_tab(int F, u32* tables);
 size_t field_table_words(int F);
 // chunk_scan: segments that begin in front of every chunk of ch keys; n_rows_out: their number.  With emb_rows or seg_counts:

@@ -1549,7 +1549,7 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
             fa.cnt_s = w.cnt_s; fa.cnt_q = w.cnt_q; fa.fm_off_s = w.fm_off_s; fa.fm_off_q = w.fm_off_q;
             fa.prow_s = B.b.prow_s; fa.prow_q = B.b.prow_q; fa.row0_s = jr->range.row0_s; fa.row0_q = jr->range.row0_q;
             fa.enc = enc; fa.keys = so.keys; fa.vals = so.vals;
-            launch_build_keys_by_field(st, fa, w.field_tab, nw);
+            launch_build_keys_by_field(st, fa, w.field_tab, nw, (int)hs[ST_MAX_BAG]);
             int64_t max_rows = 1;
             for (int f = 0; f < F; ++f) max_rows = std::max(max_rows, c->field_base[f + 1] - c->field_base[f]);
             const SegTab seg = field_seg_tab(F, w.field_tab);

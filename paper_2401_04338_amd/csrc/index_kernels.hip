@@ -796,15 +796,25 @@ __global__ __launch_bounds__(256) void field_table_kernel(int F, const u32* tot,
 enum { RS_ITEMS = 8 };   // keys per thread of a radix tile
 static int rs_tile_keys(int64_t n);
 
-#define BKF_CH 1024   // bags of a task staged at a time
+#define BKF_CH 1024     // bags of a task staged at a time
+#define BKF_TILE 4096   // their lookups whose bags are written out at a time
+#define BKF_BAG 64      // longest bag for which they are
 // One workgroup per (field, task, set): the bags (sample, field) of the task, BKF_CH at a time -- their lengths are
-// scanned into LDS, then every lane takes lookups of the piece in order (coalesced writes), finding a lookup's bag
-// by bisection of the staged table.
+// scanned into LDS, then every lane takes lookups of the piece in order (coalesced writes).
+// Bound: memory, once a lookup's bag costs little.  SHORT: every bag writes its number to its lookups' places in LDS; a bag of
+// thousands would keep its lane busy, so with longer ones a lookup finds its bag by bisection of the staged table, ten dependent LDS reads
+// (72 million lookups 303 us, written out 270; 138 million of 64 fields 504 and 470; 3 million of three tasks 37 and 20).
+template <bool SHORT>
 __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
     __shared__ u32 sbase[BKF_CH + 1];
-    __shared__ u32 sp0[BKF_CH];
+    __shared__ u32 sp0[BKF_CH], srow[BKF_CH];
+    __shared__ uint16_t bag_of[SHORT ? BKF_TILE : 1];
     __shared__ int sh[8];
-    const int f = blockIdx.x, t = blockIdx.y, set = blockIdx.z;
+    // The fields of a task on one XCD: their bags lie side by side, and their offsets and indices share lines (dealt over all of them
+    // 72 million lookups took 337 us instead of 303).
+    const int per_xcd = (int)(gridDim.x >> 3), id = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (id >= a.F * a.Tw) return;
+    const int t = id / a.F, f = id - t * a.F, set = blockIdx.y;
     const SetView& v = set ? a.qry : a.sup;
     const size_t tf = (size_t)t * a.F + f;
     const u32 n_tf = (set ? a.cnt_q : a.cnt_s)[tf];
@@ -816,19 +826,22 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
     size_t dest = (size_t)a.key_pos[f] + (set ? a.tot[f] : 0u) + (set ? a.fm_off_q : a.fm_off_s)[tf];
     for (int64_t c0 = s_lo; c0 < s_hi; c0 += BKF_CH) {
         const int nb = (int)min<int64_t>(BKF_CH, s_hi - c0);
+        const int per = (nb + 255) >> 8;   // consecutive bags per thread, at most four
+        const int b0 = (int)threadIdx.x * per;
+        u32 len[4];
         __syncthreads();   // the table of the piece before has been read
         {
-            const int b0 = (int)threadIdx.x * 4;   // four consecutive bags per thread
-            u32 len[4], p0r[4];
+            u32 p0r[4];
             u32 sum = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 len[q] = 0; p0r[q] = 0;
-                if (b0 + q < nb) {
+                if (q < per && b0 + q < nb) {
                     const int64_t bag = (c0 + b0 + q) * a.F + f;
                     const int64_t p0 = v.bag_offsets[bag];
                     len[q] = (u32)(v.bag_offsets[bag + 1] - p0);
                     p0r[q] = (u32)(p0 - v.lookup0);
+                    srow[b0 + q] = row0 + (u32)prow[c0 + b0 + q];
                 }
                 sum += len[q];
             }
@@ -836,7 +849,7 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
             u32 run = (u32)block_excl_scan((int)sum, sh, &total);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (b0 + q < nb) {
+                if (q < per && b0 + q < nb) {
                     sbase[b0 + q] = run;
                     sp0[b0 + q] = p0r[q];
                     run += len[q];
@@ -845,32 +858,48 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
         }
         __syncthreads();
         const u32 total = sbase[nb];
-        for (u32 e0 = threadIdx.x; e0 < total; e0 += 4 * 256) {
-            int bag[4];
-            u32 j[4], idx[4];
+        for (u32 s0 = 0; s0 < total; s0 += SHORT ? (u32)BKF_TILE : total) {
+            const u32 s1 = SHORT ? min(total, s0 + (u32)BKF_TILE) : total;
+            if constexpr (SHORT) {
+                if (s0 > 0) __syncthreads();   // the tile before has been read
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const u32 e = e0 + q * 256;
-                bag[q] = 0; j[q] = 0; idx[q] = 0;
-                if (e < total) {
-                    int lo = 0, hi = nb;   // last bag whose first lookup is <= e (empty bags share their successor's)
-                    while (hi - lo > 1) {
-                        const int mid = (lo + hi) >> 1;
-                        if (sbase[mid] <= e) lo = mid;
-                        else hi = mid;
+                for (int q = 0; q < 4; ++q)
+                    if (len[q]) {
+                        const u32 first = sbase[b0 + q], lo = max(first, s0), hi = min(first + len[q], s1);
+                        for (u32 e = lo; e < hi; ++e) bag_of[e - s0] = (uint16_t)(b0 + q);
                     }
-                    bag[q] = lo;
-                    j[q] = e - sbase[lo];
-                    idx[q] = (u32)v.indices[v.lookup0 + sp0[lo] + j[q]];
-                }
+                __syncthreads();
             }
+            for (u32 e0 = s0 + threadIdx.x; e0 < s1; e0 += 4 * 256) {
+                int bag[4];
+                u32 j[4], idx[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const u32 e = e0 + q * 256;
-                if (e < total) {
-                    const u32 row = row0 + (u32)prow[c0 + bag[q]];
-                    a.keys[dest + e] = fb + idx[q];
-                    a.vals[dest + e] = (row << a.enc.rshift) | ((u32)f << a.enc.pshift) | j[q];
+                for (int q = 0; q < 4; ++q) {
+                    const u32 e = e0 + q * 256;
+                    bag[q] = 0; j[q] = 0; idx[q] = 0;
+                    if (e < s1) {
+                        int lo = 0;
+                        if constexpr (SHORT) lo = bag_of[e - s0];
+                        else {
+                            int hi = nb;   // last bag whose first lookup is <= e (empty bags share their successor's)
+                            while (hi - lo > 1) {
+                                const int mid = (lo + hi) >> 1;
+                                if (sbase[mid] <= e) lo = mid;
+                                else hi = mid;
+                            }
+                        }
+                        bag[q] = lo;
+                        j[q] = e - sbase[lo];
+                        idx[q] = (u32)v.indices[v.lookup0 + sp0[lo] + j[q]];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u32 e = e0 + q * 256;
+                    if (e < s1) {
+                        a.keys[dest + e] = fb + idx[q];
+                        a.vals[dest + e] = (srow[bag[q]] << a.enc.rshift) | ((u32)f << a.enc.pshift) | j[q];
+                    }
                 }
             }
         }
@@ -879,7 +908,7 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
 }
 
 // tables: 3 (F + 1) words (key_pos, tile_base, key_sub), then 2 F words of totals
-void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n) {
+void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n, int max_bag) {
     if (a.F <= 0 || a.Tw <= 0) return;
     u32* key_pos = tables;
     u32* tile_base = key_pos + (a.F + 1);
@@ -889,7 +918,9 @@ void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, in
     hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(256), 0, st, a.F, tot, a.field_base, rs_tile_keys(n), key_pos, tile_base, key_sub);
     a.key_pos = key_pos;
     a.tot = tot;
-    hipLaunchKernelGGL(build_keys_fm_kernel, dim3(a.F, a.Tw, 2), dim3(256), 0, st, a);
+    const dim3 grid((unsigned)(((int64_t)a.F * a.Tw + 7) / 8 * 8), 2);
+    if (max_bag <= BKF_BAG) hipLaunchKernelGGL(build_keys_fm_kernel<true>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(build_keys_fm_kernel<false>, grid, dim3(256), 0, st, a);
 }
 SegTab field_seg_tab(int F, u32* tables) { return SegTab{F, tables + (F + 1), tables, tables + 2 * (F + 1)}; }
 size_t field_table_words(int F) { return (size_t)5 * (F + 1); }
@@ -1228,136 +1259,113 @@ int task_sort_passes(int n_tasks) { return n_tasks > 512 ? 2 : 1; }
 // per-(task, field) dictionaries and overlap join read off the (task, field, row) order of the wave's lookups
 // ------------------------------------------------------------------------------------------------
 // One workgroup per (task, field): its lookups are one contiguous run of the ordered list, support lookups before
-// query lookups inside every row.  The run is walked 1024 entries at a time (four consecutive entries per thread);
-// what the entries need from before them -- how many support lookups, how many distinct support rows, and the slot of
-// the row they belong to (none when the support set does not look the row up) -- comes from one block-wide sum scan of
-// two packed counters and one segmented copy scan, carried from one 1024-entry piece to the next.  Writes exactly what
-// tf_sort_kernel writes, for (task, field)s of any size.
-template <bool SLOTS>
-__global__ __launch_bounds__(256) void tf_join_kernel(TfJoinArgs a) {
-    __shared__ int sh_scan[8];
-    __shared__ u32 sh_wstate[4];
+// query lookups inside every row.  The run is walked NT * E entries at a time, a wave's as E rounds of 64 neighbours:
+// what an entry needs from before it -- how many support lookups, how many distinct support rows, and the slot of the row it belongs to
+// (none when the support set does not look the row up) -- are bit counts of the round's ballots, sums of the rounds before and one
+// exchange of the waves' totals a piece.  Writes exactly what tf_sort_kernel writes, for (task, field)s of any size.
+// Bound: memory, if neighbouring entries' stores fall into the same lines and the next piece is asked for ahead.  With four
+// consecutive entries a thread, two block-wide scans and four barriers a piece 72 million lookups took 432 us, 138 million 754; now 317 and
+// 650.  A few long runs (3 tasks x 64 fields of 17,000 entries) are walked by 1024 threads: 57 -> 35 us; short ones a round at a time (37 tasks x
+// 11 fields of 330 entries: four rounds 13 us, one 7.4).
+template <int NT, int E, bool SLOTS>
+__global__ __launch_bounds__(NT) void tf_join_kernel(TfJoinArgs a) {
+    constexpr int NW = NT / WAVE, SPAN = WAVE * E, PIECE = NT * E;
+    __shared__ u32 sh_count[2][NW], sh_state[2][NW];   // a wave's support lookups and distinct support rows (16 bits each); state after it
     const int f = blockIdx.x, t = blockIdx.y;
     const size_t tf = (size_t)t * a.F + f;
     const u32 ns = a.cnt_s[tf], nq = a.cnt_q[tf], B = a.base_s[tf], Bq = a.base_q[tf];
     const u32 n = ns + nq;
-    // The run is read four entries per thread as 16-byte words, from the 16-byte boundary at or before its start: the
-    // `mis` entries in front belong to the (task, field) before and count as absent.
-    const size_t S = (size_t)B + Bq;
-    const u32 mis = (u32)(S & 3);
-    const u32* K = a.keys + (S - mis);
-    const u32* V = a.vals + (S - mis);
-    const u32 n_al = n + mis;
-    const int64_t readable = (a.n_lookups_s + a.n_lookups_q) - (int64_t)(S - mis);   // entries of the list from K on
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const u32 FLAG = 0x80000000u;
+    const u32* K = a.keys + ((size_t)B + Bq);
+    const u32* V = a.vals + ((size_t)B + Bq);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u64 lt = (1ull << lane) - 1ull, le = lt | (1ull << lane);
     const u32 posmask = (1u << a.pshift) - 1u;
     u32 a_carry = 0, u_carry = 0, st_carry = 0;   // the same on every thread
-    for (u32 c0 = 0; c0 < n_al; c0 += 1024) {
-        const u32 j0 = c0 + threadIdx.x * 4;   // position in the aligned run; entry i of the (task, field) is position i + mis
-        u32 k[6], v[5];   // k[0]: the entry before the thread's four, k[5] / v[4]: the one after
-        if ((int64_t)j0 + 4 <= readable) {
-            const uint4 kq = *reinterpret_cast<const uint4*>(K + j0), vq = *reinterpret_cast<const uint4*>(V + j0);
-            k[1] = kq.x; k[2] = kq.y; k[3] = kq.z; k[4] = kq.w;
-            v[0] = vq.x; v[1] = vq.y; v[2] = vq.z; v[3] = vq.w;
-        } else {
+    u32 kn[E + 2], vn[E + 1];   // of the next piece: kn[0] the entry before the wave's first, [1..E] the rounds' own, [E + 1] / vn[E] the entry after its last
+    auto request = [&](u32 c0) {
+        const u32 w0 = c0 + wv * SPAN;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                k[e + 1] = (int64_t)j0 + e < readable ? K[j0 + e] : 0u;
-                v[e] = (int64_t)j0 + e < readable ? V[j0 + e] : 0u;
-            }
+        for (int e = 0; e < E; ++e) {
+            const u32 i = min(w0 + e * 64 + lane, n - 1u);
+            kn[e + 1] = K[i];
+            vn[e] = V[i];
         }
-        // neighbours across threads by lane shuffles; the wave's first and last lanes read theirs
-        k[0] = __shfl_up(k[4], 1, 64);
-        k[5] = __shfl_down(k[1], 1, 64);
-        v[4] = __shfl_down(v[0], 1, 64);
-        if (lane == 0) k[0] = (j0 > 0 && j0 <= n_al) ? K[j0 - 1] : 0u;
-        if (lane == 63) {
-            k[5] = j0 + 4 < n_al ? K[j0 + 4] : 0u;
-            v[4] = j0 + 4 < n_al ? V[j0 + 4] : 0u;
-        }
-        const u32 i0 = j0 - mis;   // (wraps for positions in front of the run: `in` below is false for them)
-        bool in[5];
+        kn[0] = K[min(max(w0, 1u) - 1u, n - 1u)];   // (one address for the wave)
+        kn[E + 1] = K[min(w0 + (u32)SPAN, n - 1u)];
+        vn[E] = V[min(w0 + (u32)SPAN, n - 1u)];
+    };
+    if (n > 0) request(0);
+    int buf = 0;
+    for (u32 c0 = 0; c0 < n; c0 += PIECE, buf ^= 1) {
+        const u32 w0 = c0 + wv * SPAN;
+        u32 k[E + 2], v[E + 1];
 #pragma unroll
-        for (int e = 0; e < 5; ++e) in[e] = j0 + e >= mis && j0 + e < n_al;
-        bool sup[5], head[4];
-        int n_sup = 0, n_sh = 0;
+        for (int e = 0; e < E + 2; ++e) k[e] = kn[e];
 #pragma unroll
-        for (int e = 0; e < 5; ++e) sup[e] = in[e] && (v[e] >> a.rshift) < a.n_sup_rows;
+        for (int e = 0; e < E + 1; ++e) v[e] = vn[e];
+        if (c0 + PIECE < n) request(c0 + PIECE);
+        u64 bs[E], bh[E];   // support lookups, first entries of a row
+        u32 nk[E];          // the key after each entry
+        bool nsup[E];       // and whether it is a support lookup
+        u32 n_sup = 0, n_sh = 0, state = 0x80000000u;   // (none yet: the state from before the wave goes on)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            head[e] = in[e] && (i0 + e == 0 || k[e + 1] != k[e]);
-            n_sup += sup[e] ? 1 : 0;
-            n_sh += (head[e] && sup[e]) ? 1 : 0;
-        }
-        int total;
-        const int excl = block_excl_scan(n_sup | (n_sh << 16), sh_scan, &total);
-        u32 aex = a_carry + ((u32)excl & 0xFFFFu);        // support lookups before the thread's first entry
-        u32 uex = u_carry + ((u32)excl >> 16);            // distinct support rows before it
-        // state of an entry: slot + 1 of its row, 0 when the support set does not look the row up; set at the head of a
-        // run of equal keys and copied along the run
-        u32 stt[4];
-        u32 cur = 0;
-        bool any_head = false;
-        {
-            u32 u = uex;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (head[e]) {
-                    any_head = true;
-                    cur = sup[e] ? u + 1u : 0u;
-                    u += sup[e] ? 1u : 0u;
-                }
-                stt[e] = cur;   // valid from the thread's first head on; before it the incoming state applies
-            }
-        }
-        u32 x = any_head ? (FLAG | cur) : 0u;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const u32 y = __shfl_up(x, d, 64);
-            if (lane >= d && !(x & FLAG)) x = y;
-        }
-        if (lane == 63) sh_wstate[wv] = x;
-        u32 inc = __shfl_up(x, 1, 64);
-        if (lane == 0) inc = 0u;
-        __syncthreads();
-        u32 wave_in = FLAG | st_carry, all = FLAG | st_carry;
-#pragma unroll
-        for (int ww = 0; ww < 4; ++ww) {
-            const u32 s = sh_wstate[ww];
-            if (s & FLAG) {
-                all = s;
-                if (ww < wv) wave_in = s;
-            }
-        }
-        if (!(inc & FLAG)) inc = wave_in;
-        inc &= ~FLAG;
-        {
-            bool seen = false;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                seen = seen || head[e];
-                if (!seen) stt[e] = inc;
-            }
+        for (int e = 0; e < E; ++e) {
+            const u32 i = w0 + e * 64 + lane;
+            const bool in = i < n;
+            u32 pk = __shfl_up(k[e + 1], 1, 64);
+            const u32 last = e == 0 ? k[0] : (u32)__builtin_amdgcn_readlane((int)k[e], 63);
+            if (lane == 0) pk = last;
+            bs[e] = __ballot(in && (v[e] >> a.rshift) < a.n_sup_rows);
+            bh[e] = __ballot(in && (i == 0 || pk != k[e + 1]));
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const u32 i = i0 + e;
-            if (in[e]) {
+        for (int e = 0; e < E; ++e) {
+            nk[e] = __shfl_down(k[e + 1], 1, 64);
+            const u32 next = e == E - 1 ? k[E + 1] : (u32)__builtin_amdgcn_readlane((int)k[e + 2], 0);
+            if (lane == 63) nk[e] = next;
+            const bool after = e == E - 1 ? (v[E] >> a.rshift) < a.n_sup_rows : (bs[e + 1 < E ? e + 1 : e] & 1ull) != 0;
+            nsup[e] = lane == 63 ? after : ((bs[e] >> 1) >> lane) & 1ull;
+            n_sup += (u32)__popcll(bs[e]);
+            n_sh += (u32)__popcll(bs[e] & bh[e]);
+            if (bh[e]) state = (bs[e] >> (63 - __clzll((long long)bh[e]))) & 1ull ? n_sh : 0x40000000u;
+        }
+        if (lane == 0) {
+            sh_count[buf][wv] = n_sup | (n_sh << 16);
+            sh_state[buf][wv] = state;
+        }
+        __syncthreads();   // (the other buffer is the next piece's)
+        u32 ab = a_carry, ub = u_carry, st = st_carry;   // before the wave
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {   // (all waves: the piece's end is carried)
+            if (w == wv) { ab = a_carry; ub = u_carry; st = st_carry; }
+            const u32 cw = sh_count[buf][w], sw = sh_state[buf][w];
+            if (!(sw & 0x80000000u)) st_carry = sw & 0x40000000u ? 0u : u_carry + sw;   // slot + 1 of the last row begun, 0: not a support row
+            a_carry += cw & 0xFFFFu;
+            u_carry += cw >> 16;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const u32 i = w0 + e * 64 + lane;
+            const u64 hs = bs[e] & bh[e], seen = bh[e] & le;
+            const u32 aex = ab + (u32)__popcll(bs[e] & lt);
+            u32 mine = st;
+            if (seen) mine = (bs[e] >> (63 - __clzll((long long)seen))) & 1ull ? ub + (u32)__popcll(hs & le) : 0u;
+            if (i < n) {
                 const u32 key = k[e + 1], val = v[e];
                 const u32 row = val >> a.rshift;
-                const bool next_same = in[e + 1] && k[e + 2] == key;
-                const int32_t slot = (int32_t)stt[e] - 1;
+                const bool sup = (bs[e] >> lane) & 1ull, head = (bh[e] >> lane) & 1ull;
+                const bool next_same = i + 1 < n && nk[e] == key;
+                const int32_t slot = (int32_t)mine - 1;
                 // (every index below is in range when the list is in the stated order; the checks keep a list that is
                 //  not -- a defect elsewhere -- from writing outside the (task, field)'s own ranges)
-                if (sup[e]) {
+                if (sup) {
                     if (slot >= 0 && (u32)slot < ns && aex < ns) {
                         a.sup_sorted[B + aex] = make_int2((int)row, slot);
-                        if (head[e]) {
+                        if (head) {
                             a.slot_rows[B + slot] = key;
                             a.slot_start[B + tf + slot] = (int32_t)(B + aex);
                         }
-                        if (!(next_same && sup[e + 1])) a.qseg_lo[B + slot] = (int32_t)(Bq + (i - aex));
+                        if (!(next_same && nsup[e])) a.qseg_lo[B + slot] = (int32_t)(Bq + (i - aex));
                         if (SLOTS) {
                             const int rel = (int)row - a.row_off_s[t];
                             if (rel >= 0 && rel < a.real_off_s[t + 1] - a.real_off_s[t]) {
@@ -1377,13 +1385,12 @@ __global__ __launch_bounds__(256) void tf_join_kernel(TfJoinArgs a) {
                         }
                     }
                 }
-                if (!next_same && slot >= 0 && (u32)slot < ns) a.qseg_hi[B + slot] = (int32_t)(Bq + (i + 1) - (aex + (sup[e] ? 1u : 0u)));
-                aex += sup[e] ? 1u : 0u;
+                if (!next_same && slot >= 0 && (u32)slot < ns) a.qseg_hi[B + slot] = (int32_t)(Bq + (i + 1) - (aex + (sup ? 1u : 0u)));
             }
+            if (bh[e]) st = (bs[e] >> (63 - __clzll((long long)bh[e]))) & 1ull ? ub + (u32)__popcll(hs) : 0u;
+            ab += (u32)__popcll(bs[e]);
+            ub += (u32)__popcll(hs);
         }
-        a_carry += (u32)total & 0xFFFFu;
-        u_carry += (u32)total >> 16;
-        st_carry = all & ~FLAG;
     }
     if (threadIdx.x == 0) {
         const u32 nu = min(u_carry, ns);
@@ -1394,13 +1401,22 @@ __global__ __launch_bounds__(256) void tf_join_kernel(TfJoinArgs a) {
 
 void launch_tf_join(hipStream_t st, const TfJoinArgs& a) {
     if (a.Tw <= 0 || a.F <= 0) return;
-    if (a.sup_slot) hipLaunchKernelGGL(tf_join_kernel<true>, dim3(a.F, a.Tw), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(tf_join_kernel<false>, dim3(a.F, a.Tw), dim3(256), 0, st, a);
+    const int64_t runs = (int64_t)a.F * a.Tw, n = a.n_lookups_s + a.n_lookups_q;
+    const dim3 grid(a.F, a.Tw);
+#define TF_JOIN(NT_, E_)                                                                                             \
+    do {                                                                                                             \
+        if (a.sup_slot) hipLaunchKernelGGL((tf_join_kernel<NT_, E_, true>), grid, dim3(NT_), 0, st, a);              \
+        else hipLaunchKernelGGL((tf_join_kernel<NT_, E_, false>), grid, dim3(NT_), 0, st, a);                        \
+    } while (0)
+    if (n <= runs * 512) TF_JOIN(256, 1);
+    else if (runs <= 1024 && n > runs * 1024) TF_JOIN(1024, 4);   // (fewer workgroups than the chip holds, with several pieces each)
+    else TF_JOIN(256, 4);
+#undef TF_JOIN
 }
 
 // Segments (runs of equal keys) that begin in front of every chunk of `ch` keys (16, 32 or 64): all that the segment reduction
 // needs to number them, which also writes the row list.  Bound: the keys read once.  A scan of every key's head flag, then a kernel that
-// wrote rows and starts from it, took 520 us for 36 million keys and 125 for 9 million; this 60 and 20.
+// wrote rows and starts from it, took 520 us for 72 million keys and 125 for 18 million; this 95 and 25.
 __device__ __forceinline__ u32 seg_heads(const u32* __restrict__ keys, int64_t base, int64_t n) {   // of the 8 keys from base (a multiple of 8) on; by all lanes of a wave
     const int lane = threadIdx.x & (WAVE - 1);
     u32 k[9];
