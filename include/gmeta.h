@@ -284,7 +284,7 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               2 = factors wherever they can be.  The factors' path does not round the direction to bf16 (the thin products
  *               keep 16 significant bits) and adds its part of the meta-gradient over runs of tasks.
  *   "coarse_groups": number of runs of consecutive tasks for those products: 0 (default) = 16, or, when the first
- *               layer's product takes the wide tiles, the count in [12, 16] whose tiles fill the device's last round
+ *               layer's product takes the wide tiles, the count in [12, 18] whose tiles fill the device's last round
  *               best; 1..32 = that many.  Another grouping adds the same per-task terms in another order
  *               (fp32 rounding).
  *   "max_wave_tasks": most tasks processed at a time (0 = as many as the workspace holds).  Tasks are independent

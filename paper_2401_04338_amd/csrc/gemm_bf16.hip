@@ -486,12 +486,13 @@ template <int EP>
 static void launch_kmajor_tile(hipStream_t st, const GemmBArgs& a, int tile) {
     if (tile == 256) launch_variant<256, 256, 2, 4, 1, 2, true, true, EP>(st, a);
     // (eight waves where only sums over runs of tasks are written: a long contraction; else four)
-    else launch_variant<128, 128, 2, EP == (EPI_AXPBY | EP_CF) ? 4 : 2, 1, 1, true, true, EP>(st, a);
+    else launch_variant<128, 128, 2, (EP & ~EP_CIN) == (EPI_AXPBY | EP_CF) ? 4 : 2, 1, 1, true, true, EP>(st, a);
 }
 void launch_gemm_bf16_kmajor(hipStream_t st, const GemmBArgs& a, int tile) {
     switch (ep_of(a)) {
         case EPI_AXPBY | EP_CF: launch_kmajor_tile<EPI_AXPBY | EP_CF>(st, a, tile); break;
         case EPI_AXPBY | EP_CF | EP_CB: launch_kmajor_tile<EPI_AXPBY | EP_CF | EP_CB>(st, a, tile); break;
+        case EPI_AXPBY | EP_CB: launch_kmajor_tile<EPI_AXPBY | EP_CB>(st, a, tile); break;
         case EPI_AXPBY | EP_CF | EP_CIN: launch_kmajor_tile<EPI_AXPBY | EP_CF | EP_CIN>(st, a, tile); break;
         case EPI_AXPBY | EP_CF | EP_CB | EP_CIN: launch_kmajor_tile<EPI_AXPBY | EP_CF | EP_CB | EP_CIN>(st, a, tile); break;
         case EPI_AXPBY | EP_CB | EP_CIN: launch_kmajor_tile<EPI_AXPBY | EP_CB | EP_CIN>(st, a, tile); break;

@@ -279,6 +279,8 @@ enum { MAX_WAVE_TASKS = 32768 };
 static int most_wave_tasks(const gm_ctx* c) { return c->max_wave_tasks > 0 ? std::min<int>(c->max_wave_tasks, MAX_WAVE_TASKS) : MAX_WAVE_TASKS; }
 enum { COARSE_GROUPS = 32 };   // most runs of tasks (gm_configure "coarse_groups" says how many are used)
 
+static int most_runs(const gm_ctx* c);
+
 struct WaveBufs {
     int32_t *row_off_s, *row_off_q, *real_off_s, *real_off_q;
     int32_t *row_task_s, *row_task_q;
@@ -443,7 +445,7 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.loss_q = ar.get<float>(d.Pq + 1);
     const bool factors = d.factor_ld > 0;
     w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
-    w.vsum = Theta{ar.get<float>((int64_t)std::max(16, c->coarse_groups) * c->n_theta), c->n_theta, nullptr, 0};
+    w.vsum = Theta{ar.get<float>((int64_t)most_runs(c) * c->n_theta), c->n_theta, nullptr, 0};
     if (!second) w.v.b = nullptr;  // the direction is a GEMM operand only in the second-order pass
     w.Xs_scratch = Act();
     if (K > 1 && !second) {
@@ -1046,28 +1048,44 @@ static Grp whole_group(const gm_ctx* c, const Grp& g) {
 // them and without: 64 rows a task 2.25 / 2.26 ms, 128 4.09 / 4.14, 192 5.51 / 5.58, 256 6.76 / 6.85; 128 tasks, 4109 x 1024: 64
 // rows 3.83 / 3.74, 128 7.04 / 7.01, 192 9.05 / 9.07, 256 10.82 / 10.97.  Narrow layers lose to padded rows of the last tile
 // (512 tasks, 269 x 256, 256 rows: 2.54 / 2.53).
+// Long contractions (runs of tasks) also take them where the tiles fill the compute units' rounds: 512 tasks of 256 rows, 1677 x 512, two
+// products, 16 runs in 128 x 128 tiles (896) 691 us, 18 runs in 256 x 256 ones (252) 445; 128 tasks, one product, 89 and 71.
+enum { WIDE_LONG = 1024 };
+static constexpr double WIDE_FILL = 0.85;
+static bool wgrad_wide_shape(const gm_ctx* c, int M, int N) { return c->mlp_dtype && M >= 1024 && N % 256 == 0; }
+static double round_fill(const gm_ctx* c, int64_t tiles) { return (double)tiles / (double)((tiles + c->n_cus - 1) / c->n_cus * c->n_cus); }
 static bool wgrad_wide_ok(const gm_ctx* c, int M, int N, int64_t rows, int G) {
-    return c->wgrad_wide && c->mlp_dtype && M >= 1024 && N % 256 == 0 && G > 0 && rows / G >= 192 &&
-           (int64_t)((M + 255) / 256) * (N / 256) * G >= 2 * (int64_t)c->n_cus;
+    if (!c->wgrad_wide || !wgrad_wide_shape(c, M, N) || G <= 0 || rows / G < 192) return false;
+    const int64_t tiles = (int64_t)((M + 255) / 256) * (N / 256) * G;
+    return tiles >= 2 * (int64_t)c->n_cus || (rows / G >= WIDE_LONG && round_fill(c, tiles) >= WIDE_FILL);
 }
 
 // Runs of consecutive tasks that the products only summed over tasks are taken over.  16, unless the first layer's
-// product then runs in 256 x 256 tiles, one workgroup per compute unit: the count in [12, 16] whose tiles fill the
-// last round over the compute units best (the larger count on a tie).
+// product can run in 256 x 256 tiles, one workgroup per compute unit: the count in [12, 18] whose tiles fill the
+// last round over the compute units best, the largest run counted (the larger count on a tie).
+enum { MOST_RUNS = 18 };
+static int most_runs(const gm_ctx* c) { return std::max(c->coarse_groups, c->L > 1 && wgrad_wide_shape(c, c->ld[0], c->ld[1]) ? (int)MOST_RUNS : 16); }
 static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
     if (c->coarse_groups) return std::min(Tw, c->coarse_groups);
     int n = std::min(Tw, 16);
-    if (n < 16 || c->L < 1) return n;
-    const int M = c->ld[0], N = c->ld[1];
-    if (!wgrad_wide_ok(c, M, N, rows, 16) || rows / 16 < 2048) return n;
-    const int64_t per = (int64_t)((M + 255) / 256) * (N / 256);
+    if (n < 16 || c->L < 2 || !wgrad_wide_shape(c, c->ld[0], c->ld[1]) || rows / MOST_RUNS < WIDE_LONG) return n;
+    const int64_t per = (int64_t)((c->ld[0] + 255) / 256) * (c->ld[1] / 256);
     double best = -1.0;
-    for (int k = 12; k <= 16; ++k) {
-        const int64_t tiles = per * k, rounds = (tiles + c->n_cus - 1) / c->n_cus;
-        const double fill = (double)tiles / (double)(rounds * c->n_cus);
-        if (fill >= best) { best = fill; n = k; }
+    for (int k = 12; k <= std::min<int>(MOST_RUNS, Tw); ++k) {
+        const double fill = round_fill(c, per * k), score = fill * ((double)Tw / k) / ((Tw + k - 1) / k);
+        if (fill >= WIDE_FILL && score >= best) { best = score; n = k; }
     }
     return n;
+}
+
+// Whether the query gradient, where the second-order chain's direction starts, is summed over runs of tasks beside being written per
+// task as the chain's bf16 operand, instead of being written in fp32 per task and read again for the sum: one inner step (the chain's
+// next product is summed over runs anyway), and the extra product costs less than eight bytes a weight and task: 128 tasks of 256 rows
+// (1677-512-256) 165 + 41 us to write, 113 to sum, and with the bf16 operand and the runs 102 + 19, 71 + 34, 16; 128 tasks of 512 rows
+// (4109-1024-512-256) 1240 and 490 us against 970, 797 and 63 -- there the product costs more.  The rates are what these show.
+static constexpr double RUNS_RATE = 7.5e14, RUNS_BYTES = 6.6e12;
+static bool query_runs(const gm_ctx* c, int Tw, int64_t rows_q, int n_runs, int K, int order) {
+    return c->mlp_dtype && order == 2 && K == 1 && c->L > 1 && 8.0 * (Tw - n_runs) / RUNS_BYTES > 2.0 * (double)rows_q / RUNS_RATE;
 }
 
 // fp32 weight gradients of one pass that depend on nothing of each other, collected and launched together
@@ -1209,7 +1227,8 @@ static void forward_backward(gm_ctx* c, const Grp& g, const float* labels, const
 
 // out = c0*in + c1 * (gradient of the pass w.r.t. theta), per task; out.b (if any) gets the bf16 operand copies.
 // coarse / coarse_out: the hidden layers' weight matrices are summed over runs of tasks instead (c1 times the gradient,
-// nothing added), for a caller that only wants their sum over the tasks; biases and the last layer stay per task.
+// nothing added), for a caller that only wants their sum over the tasks -- and, where out has room for bf16 operands, those per
+// task; biases and the last layer stay per task.
 // hist / in0 (bf16 operands, an inner step of a second-order call): the passes of all inner steps so far, this one
 // last, and the meta parameters.  The step's weight matrices are then written as theta - alpha * (sum of the steps'
 // gradients), one product per step accumulated in the matrix cores, from the shared fp32 theta: no per-task fp32
@@ -1226,7 +1245,10 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
     WGrads later;
     for (int l = 1; l < L; ++l) {
         const Act* prev = l == 1 ? p.X : &(*p.A)[l - 1];
-        if (coarse) dense_tn(c, *coarse, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, *coarse_out, nullptr, 0, 0.f, c1, true, &later);
+        if (coarse) {
+            dense_tn(c, *coarse, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, *coarse_out, nullptr, 0, 0.f, c1, true, &later);
+            if (out.b) dense_tn(c, g, l, 1, prev, &(*p.Dl)[l], nullptr, nullptr, out, nullptr, 0, 0.f, c1, false);
+        }
         else if (hist) {
             const Act* as[GEMM_MAX_PAIRS];
             const Act* ds[GEMM_MAX_PAIRS];
@@ -2332,7 +2354,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         gs_coarse.row_off = w.coarse_off_s; gs_coarse.G = n_coarse;
         gq_coarse.row_off = w.coarse_off_q; gq_coarse.G = n_coarse;
         // (factors: the chain's other terms are added to these sums, no task's direction is formed)
-        const bool runs_only = !second || factors;
+        const bool runs_only = !second || factors || query_runs(c, Tw, d.Pq, n_coarse, K, order);
         theta_grad(c, gq, pq, w.v, nullptr, 0, 0.f, 1.f, nullptr, true, runs_only ? &gq_coarse : nullptr, runs_only ? &w.vsum : nullptr,
                    nullptr, nullptr, w.loss_q, task_loss + wp.t0);
         if (factors) {
@@ -2361,7 +2383,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 const bool fused_gx = L > 1 && F > 0 && (bf || !(k > 0 && adapt));
                 // (the chain's first step starts that sum: the buffer's support rows need no clearing)
                 hvp_step(c, gs, s, w, alpha, k > 0, fused_gx ? gxs : nullptr, k > 0 && adapt, k == K - 1, adapt,
-                         k == 0 || factors ? &gs_coarse : nullptr, factors);
+                         k == 0 || factors ? &gs_coarse : nullptr, runs_only);
                 if (factors) {
                     v_fac.push_back(Factor{adapt && F > 0 ? &w.TXk[k] : nullptr, &w.TAk[k], &s.Dl, false, -alpha});
                     v_fac.push_back(Factor{&s.X, &s.A, &w.TDk[k], false, -alpha});
