@@ -224,6 +224,11 @@ void launch_copy_tail(hipStream_t st, int FD, const float* x_base, int64_t n_row
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 load_once(const float* p) { return __builtin_bit_cast(float4, __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p))); }
+__device__ __forceinline__ float4 only(float4 x, u32 keep) {   // x or zeros, by a mask of all bits or none (a condition becomes branches around every read)
+    uint4 b = __builtin_bit_cast(uint4, x);
+    b.x &= keep; b.y &= keep; b.z &= keep; b.w &= keep;
+    return __builtin_bit_cast(float4, b);
+}
 __device__ __forceinline__ void store_once(float* p, float4 v) { __builtin_nontemporal_store(__builtin_bit_cast(f32x4, v), reinterpret_cast<f32x4*>(p)); }
 
 #define SEG_CH 64         // positions per chunk
@@ -256,13 +261,15 @@ __device__ __forceinline__ bool seg_block_hot(const u32* keys, int64_t b, int64_
 // follows from the head flags at the chunk's two borders, so no segment table is read here.
 // What is written goes past the caches (non-temporal), which are the gradient rows': 72 million lookups, 7 million rows listed 1.64 -> 1.52 ms;
 // 26 million added to table rows 1.48 -> 1.45.
-// CH: the chunk's length, 0 where `short_ch` says it
-template <int LG, int CH>
+// CH: the chunk's length, 0 where `short_ch` says it.  ZERO: places of gx below `zero` are zeros: a chunk reads one and the same of the `others` + 1 behind
+// them in their stead and does not look at it (a first-order gradient has nothing for the support set's lookups: 201 tasks of 75..225 + 122..365 rows, 22 million lookups, their zeros filled in (27 us)
+// and read 492 + 195 us in the two kernels, 403 + 127 so; the hot one leaves chunks of zeros out).
+template <int LG, int CH, bool ZERO>
 __global__ void __launch_bounds__(256)
 seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __restrict__ keys, const u32* __restrict__ scan,
                          const int64_t* __restrict__ n_rows, int64_t capacity, int64_t n,
                          const u32* __restrict__ sorted_vals, const float* __restrict__ gx, int64_t* emb_rows, float* emb_grad,
-                         float* partial, float* table, float scale, int hot) {
+                         float* partial, float* table, float scale, int hot, u32 zero, u32 others) {
     constexpr int GPB = 256 / LG;            // lane groups per workgroup
     constexpr int U = LG < 8 ? LG : 8;       // row loads in flight per lane
     const int ch = CH ? CH : short_ch;
@@ -273,6 +280,7 @@ seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __re
     const int64_t n_groups = (int64_t)gridDim.x * GPB;
     const float4* gx4 = reinterpret_cast<const float4*>(gx);
     for (int64_t c = (int64_t)blockIdx.x * GPB + g_in_block; c < n_chunks; c += n_groups) {
+        const u32 spare = ZERO ? zero + ((u32)c & others) : 0u;
         const int64_t cb = c * ch;
         const int cnt = (int)min((int64_t)ch, n - cb);
         if (hot && seg_block_hot(keys, cb / SEG_BLOCK, n)) continue;   // (the other kernel's)
@@ -331,7 +339,10 @@ seg_reduce_chunks_kernel(int D, int F, int short_ch, ValEnc enc, const u32* __re
                     kk[u] = __shfl(k, s0 + u, LG);
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) x[u] = gx4[(int64_t)vv[u] * LG + l];
+                for (int u = 0; u < U; ++u) {
+                    const u32 keep = !ZERO || vv[u] >= zero ? ~0u : 0u;
+                    x[u] = only(gx4[(int64_t)(ZERO ? (vv[u] & keep) | (spare & ~keep) : vv[u]) * LG + l], keep);
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int s = s0 + u;
@@ -400,9 +411,9 @@ __global__ __launch_bounds__(256) void seg_reduce_hot_list_kernel(int F, ValEnc 
         for (int j = 0; j < 4; ++j) list[atomicAdd(&cnt[bucket[j]], 1u)] = (u32)(b * (SEG_BLOCK / SEG_CH) + j);
 }
 // One lane group per listed chunk: its 64 gradient rows, added in order.
-template <int LG>
+template <int LG, bool ZERO>
 __global__ __launch_bounds__(256) void seg_reduce_hot_kernel(int F, ValEnc enc, const u32* __restrict__ vals, const u32* __restrict__ list,
-                                                             const u32* __restrict__ n_list, const float* __restrict__ gx, float* partial) {
+                                                             const u32* __restrict__ n_list, const float* __restrict__ gx, float* partial, u32 zero) {
     constexpr int GPB = 256 / LG, V = SEG_CH / LG > 0 ? SEG_CH / LG : 1, D = 4 * LG;
     constexpr int W = LG < SEG_CH ? LG : SEG_CH;   // lanes of a group that hold values
     const int g = threadIdx.x / LG, l = threadIdx.x % LG;
@@ -425,16 +436,27 @@ __global__ __launch_bounds__(256) void seg_reduce_hot_kernel(int F, ValEnc enc, 
         for (int q = 0; q < V; ++q) r[q] = enc.rshift ? (v[q] >> enc.rshift) * (u32)F + ((v[q] >> enc.pshift) & enc.fmask) : v[q];
         request(i + step);   // (the next chunk's, beside this one's rows)
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        auto sum = [&](auto masked) {
 #pragma unroll
-        for (int q = 0; q < V; ++q)
+            for (int q = 0; q < V; ++q)
 #pragma unroll
-            for (int s0 = 0; s0 < W; s0 += 8) {
-                float4 y[8];
+                for (int s0 = 0; s0 < W; s0 += 8) {
+                    float4 y[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) y[u] = gx4[(int64_t)(u32)__shfl((int)r[q], s0 + u, LG) * LG + l];
+                    for (int u = 0; u < 8; ++u) {
+                        const u32 at = (u32)__shfl((int)r[q], s0 + u, LG), keep = !masked || at >= zero ? ~0u : 0u;
+                        y[u] = only(gx4[(int64_t)(masked ? max(at, zero) : at) * LG + l], keep);
+                    }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) acc = q == 0 && s0 == 0 && u == 0 ? y[0] : add4(acc, y[u]);
+                    for (int u = 0; u < 8; ++u) acc = q == 0 && s0 == 0 && u == 0 ? y[0] : add4(acc, y[u]);
+                }
+        };
+        if constexpr (ZERO) {   // (inside a row the places ascend)
+            if ((u32)__shfl((int)r[V - 1], W - 1, LG) >= zero) {
+                if ((u32)__shfl((int)r[0], 0, LG) >= zero) sum(std::false_type());
+                else sum(std::true_type());
             }
+        } else sum(std::false_type());
         *reinterpret_cast<float4*>(partial + (int64_t)cc * 2 * D + l * 4) = acc;
     }
 }
@@ -565,11 +587,14 @@ __global__ __launch_bounds__(256) void seg_reduce_join_kernel(int ch, const u32*
 }
 
 void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys, const u32* scan, const int64_t* n_rows, int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx,
-                       int64_t* emb_rows, float* emb_grad, float* partial, float* table, float scale, int64_t gx_rows, u32* room) {
+                       int64_t* emb_rows, float* emb_grad, float* partial, float* table, float scale, int64_t gx_rows, int64_t zero_rows, u32* room) {
     if (n <= 0 || capacity <= 0) return;
     const int LG = D / 4, ch = seg_chunk(n, F, D);
     const int64_t n_chunks = (n + ch - 1) / ch;
     const dim3 grid(pool_grid(n_chunks, 256 / LG));
+    const u32 zero = gx_rows > zero_rows ? (u32)(zero_rows * F) : 0u;   // (row * F + field fits 32 bits; without other rows they hold zeros)
+    u32 others = 0;   // places read in the zeros' stead, less one
+    while (2 * (others + 1) <= 65536u && 2 * (int64_t)(others + 1) <= (gx_rows - zero_rows) * F) others = 2 * others + 1;
     const int hot = D >= 32 && D <= 128 && F <= SEG_BUCKETS / 2 && n >= SEG_HOT_N;
     if (hot) {
         int shift = 0;   // samples of a slice, as a power of two
@@ -583,7 +608,8 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
         hipLaunchKernelGGL((seg_reduce_hot_list_kernel<true>), dim3(nb), dim3(256), 0, st, F, enc, keys, sorted_vals, n, shift, slices, at, list);
 #define SEG_HOT(LG_)                                                                                                 \
     case LG_:                                                                                                        \
-        hipLaunchKernelGGL(seg_reduce_hot_kernel<LG_>, dim3(4096), dim3(256), 0, st, F, enc, sorted_vals, list, total, gx, partial); \
+        if (zero) hipLaunchKernelGGL((seg_reduce_hot_kernel<LG_, true>), dim3(4096), dim3(256), 0, st, F, enc, sorted_vals, list, total, gx, partial, zero); \
+        else hipLaunchKernelGGL((seg_reduce_hot_kernel<LG_, false>), dim3(4096), dim3(256), 0, st, F, enc, sorted_vals, list, total, gx, partial, zero); \
         break;
         switch (LG) { SEG_HOT(8) SEG_HOT(16) SEG_HOT(32) default: break; }
 #undef SEG_HOT
@@ -591,8 +617,10 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
     // (the long chunk is a constant of its kernels: 100 tasks x (300 + 300) rows of 32 columns 99 us with a variable length, 90 with 64)
 #define SEG_CHUNKS(LG_, CH_)                                                                                         \
     case LG_:                                                                                                        \
-        hipLaunchKernelGGL((seg_reduce_chunks_kernel<LG_, CH_>), grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
-                           sorted_vals, gx, emb_rows, emb_grad, partial, table, scale, hot);                                          \
+        if (zero) hipLaunchKernelGGL((seg_reduce_chunks_kernel<LG_, CH_, true>), grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
+                                     sorted_vals, gx, emb_rows, emb_grad, partial, table, scale, hot, zero, others);             \
+        else hipLaunchKernelGGL((seg_reduce_chunks_kernel<LG_, CH_, false>), grid, dim3(256), 0, st, D, F, ch, enc, keys, scan, n_rows, capacity, n, \
+                                sorted_vals, gx, emb_rows, emb_grad, partial, table, scale, hot, zero, others);                  \
         break;
     if (ch == SEG_CH) {
         switch (LG) {

@@ -261,7 +261,7 @@ void launch_seg_reduce(hipStream_t st, int D, int F, ValEnc enc, const u32* keys
                        int64_t capacity, int64_t n, const u32* sorted_vals, const float* gx, int64_t* emb_rows,
                        float* emb_grad, float* partial /* seg_reduce_partial_floats(n, D), for D <= 16 with n + radix_hist_words(n, F) more */,
                        float* table /* null, or [all rows, D]: scale * every segment is ADDED to its row instead of listed */, float scale,
-                       int64_t gx_rows /* of gx, each of F * D */, u32* room /* radix_hist_words(n, F) words */);
+                       int64_t gx_rows /* of gx, each of F * D */, int64_t zero_rows /* the first of them, which count as zeros and are not read, unless there are no others */, u32* room /* radix_hist_words(n, F) words */);
 size_t seg_reduce_partial_floats(int64_t n, int D);
 void launch_scatter_add(hipStream_t st, int D, float* table, const int64_t* rows, const float* grad,
                         int64_t n_rows, float scale);

@@ -2067,9 +2067,8 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     launch_copy_matrices(st, mats.data(), (int)mats.size());
     bool theta_summed = false;   // the first wave's sums are stored, later waves' added
     // Gradient w.r.t. the pooled inputs: the query rows are written whole by the outer backward pass; the support rows
-    // are the second-order chain's sum, which starts from zero unless its first product stores instead of adding.
-    const bool gxs_self_init = order == 2 && K > 0;
-    if (FD > 0 && !table && !gxs_self_init) launch_fill_f32(st, b.GX, Ps_tot * (int64_t)FD, 0.f);
+    // are the second-order chain's sum, whose first product stores instead of adding; without a chain they are zeros, and left out.
+    const bool no_chain = order == 1 || K == 0;
     float* task_loss = out->task_loss ? out->task_loss : b.task_loss;
 
     for (const WavePlan& wp : plans) {
@@ -2214,6 +2213,9 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             max_prows = std::max<int>(max_prows, (int)std::max(B.poff_s[t + 1] - B.poff_s[t], B.poff_q[t + 1] - B.poff_q[t]));
         if (K > 0 && F > 0 && max_prows > 2048)
             return fail(c, GM_ERR_CAPACITY, "a task has %d samples in one set; the limit with inner steps is 2048", max_prows);
+        // gradient w.r.t. the pooled inputs: the wave's rows of the batch-wide buffer, or the wave's own buffer
+        float* gxs = table ? w.GX : b.GX + wp.ps0 * (int64_t)FD;
+        float* gxq = table ? w.GX + d.Ps * (int64_t)FD : b.GX + (Ps_tot + wp.pq0) * (int64_t)FD;
         auto hop_out = [&](bool support, const float* y_in, float* y_out, bf16_t* y_bf, float cc) {
             TwoHopOut o;
             memset(&o, 0, sizeof o);
@@ -2341,10 +2343,6 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         if ((rc = join_pairs())) return rc;   // (no inner step took a row hop)
         // outer forward/backward on the query set with the adapted parameters
         if (bf && hops) launch_copy_tail(st, FD, w.Xq0, d.Pq, nullptr, ld0, Xq.b);
-        // gradient w.r.t. the pooled inputs: the wave's rows of the batch-wide buffer, or the wave's own buffer
-        float* gxs = table ? w.GX : b.GX + wp.ps0 * (int64_t)FD;
-        float* gxq = table ? w.GX + d.Ps * (int64_t)FD : b.GX + (Ps_tot + wp.pq0) * (int64_t)FD;
-        if (table && FD > 0 && !gxs_self_init) launch_fill_f32(st, w.GX, d.Ps * (int64_t)FD, 0.f);
         Pass pq{&Xq, &w.Aq, &w.Dq, w.dLq, w.zq};
         forward_backward(c, gq, labels_q, pq, th, thf, thf_stride, w.loss_q, F > 0 ? gxq : nullptr);
         // The query gradient w.r.t. theta' per task starts the second-order chain; without a chain it is only summed
@@ -2423,10 +2421,11 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             const int64_t nw = d.nnz_s + d.nnz_q;
             if (side_table) HIPCHK(c, hipStreamWaitEvent(st, c->ev_side, 0));
             else if (!ordered) global_order(c, B, w.so, r, nullptr, nullptr, nw, nullptr);
+            if (no_chain && d.Pq == 0 && FD > 0) launch_fill_f32(st, w.GX, d.Ps * (int64_t)FD, 0.f);   // (there is nothing but zeros)
             {
                 Prof p(c, "seg_reduce", (double)nw * (4.0 * D + 4), 0);
                 launch_seg_reduce(st, D, F, ordered ? enc : kPlainVals, w.so.keys, w.so.keys_tmp, nullptr, nw, nw, w.so.vals, w.GX,
-                                  nullptr, nullptr, seg_room(c, w.so), row_table, row_scale, d.Ps + d.Pq, w.so.hist);
+                                  nullptr, nullptr, seg_room(c, w.so), row_table, row_scale, d.Ps + d.Pq, no_chain ? d.Ps : 0, w.so.hist);
             }
             if (side_table) HIPCHK(c, hipEventRecord(c->ev_main, st));
         } else if (ordered) {
@@ -2450,10 +2449,11 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
     } else {
         if (side_list) HIPCHK(c, hipStreamWaitEvent(st, c->ev_side, 0));
         else if (!pre && !list_ordered) global_order(c, B, b.so, whole_batch_range(B), nullptr, nullptr, capacity, n_list);
+        if (no_chain && B.poff_q[T] == 0 && FD > 0) launch_fill_f32(st, b.GX, Ps_tot * (int64_t)FD, 0.f);   // (there is nothing but zeros)
         if (F > 0) {
             Prof p(c, "seg_reduce", (double)nnz * (4.0 * D + 4), 0);
             launch_seg_reduce(st, D, F, (pre || list_ordered) ? enc : kPlainVals, b.so.keys, b.so.keys_tmp, n_list, apply ? nnz : capacity, nnz,
-                              b.so.vals, b.GX, out->emb_rows, out->emb_grad, seg_room(c, b.so), row_table, row_scale, Ps_tot + B.poff_q[T], b.so.hist);
+                              b.so.vals, b.GX, out->emb_rows, out->emb_grad, seg_room(c, b.so), row_table, row_scale, Ps_tot + B.poff_q[T], no_chain ? Ps_tot : 0, b.so.hist);
         }
     }
     if (up) up->done = apply;
