@@ -225,11 +225,13 @@ struct PairHopOut {
     int64_t ld;
     float c;
 };
+enum { HOP_SUM = 3 };   // most arrays a hop adds up
 struct PairHopArgs {
     int F, D;
     const uint8_t* mat;
     const int32_t *in_real_off, *in_row_off;  // the in set
-    const float* Z;                           // [rows, ldz], the (field f) block at column f*D
+    const float* Z[HOP_SUM];                  // [rows, ldz] each, the (field f) block at column f*D; Z is the sum of the first n_z
+    int n_z;
     int64_t ldz;
     PairHopOut out[2];                        // support, query
     const u32* task_path;                     // [Tw] only tasks flagged 1 are touched

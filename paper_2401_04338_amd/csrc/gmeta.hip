@@ -293,6 +293,7 @@ struct WaveBufs {
     u32 *tmid_keys = nullptr, *tmid_vals = nullptr;   // more than 512 tasks: the first of the two passes that order the lookups by task
     bool slots_written = true;   // sup_slot / qry_slot hold the slot of every lookup (only the sparse row kernel reads them)
     float *Xs0, *Xq0, *TXf, *dX, *loss_q;
+    float* dX_kept = nullptr;   // (query_sum 3 without a chain: the second step's)
     Theta v;  // direction / query gradient w.r.t. theta'
     // the last weight-gradient products of a call are only ever summed over the tasks: they are taken over COARSE_GROUPS
     // runs of consecutive tasks instead (row offsets of the runs, one sum per run)
@@ -334,8 +335,10 @@ struct WaveDims {
     bool mat_apart = false;                // the matrices' room belongs to the dense side (gm_meta_train: one batch's at a time)
     int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of the tasks beyond HOP_SMALL (the hops' work lists)
     bool table = false;                    // the sparse gradient is reduced wave by wave into a table-shaped output
+    int query_sum = 0;                     // > 1: so many steps' input gradients are kept, and the query set's row update is taken once, from their sum
     int factor_ld = 0;                     // > 0: the chain's direction stays factors (see Factor); rows of the largest task of the batch
 };
+static int query_sum(const gm_ctx* c, int K);
 static int factor_slots(int K) { return 2 * K - 1; }   // most factors of the direction: the query pass's, two of every later step
 
 static Act alloc_act(const gm_ctx* c, Arena& ar, int64_t rows, int ld) {
@@ -442,6 +445,7 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     const bool second = order == 2 && K > 0;
     w.TXf = (second && bf) ? ar.get<float>(d.Ps * ld0) : nullptr;
     w.dX = ar.get<float>(std::max(d.Ps, d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
+    w.dX_kept = d.query_sum > 2 && !second ? ar.get<float>(d.Ps * (int64_t)std::max(c->FD, 1) + 4) : nullptr;
     w.loss_q = ar.get<float>(d.Pq + 1);
     const bool factors = d.factor_ld > 0;
     w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
@@ -803,6 +807,7 @@ extern "C" size_t gm_workspace_bytes(const gm_model_desc* model, int32_t n_tasks
         if (std::max(ns, nq) > 0 && std::max(ns, nq) <= 512) {
             const int64_t ps = (ns + 63) & ~(int64_t)63, pq = (nq + 63) & ~(int64_t)63;
             d.pair = true;
+            d.query_sum = query_sum(&c, inner_steps);
             d.pair_ss = inner_steps >= 2;
             d.pair_sq = order == 2;
             if (std::max(ns, nq) > HOP_SMALL) {
@@ -1717,6 +1722,11 @@ static int factor_rows(const gm_ctx* c, const Batch& B, int bm, int K, int order
     return flops / FACTOR_RATE < bytes / MATRIX_RATE && weights * B.T * 6.0 > FACTOR_CACHE && room < 2.0 * weights * B.T ? most : 0;
 }
 
+// Steps whose input gradients are kept until the last one: the query set's update X - alpha M (Z_0 + .. + Z_k) is then one hop instead of
+// one a step, each of which reads M and X and writes X.  Two steps, or three with bf16 operands: the buffers are ones that nothing
+// uses before (the support rows of the gradient buffer, the chain's fp32 direction) but for one without a chain.
+static int query_sum(const gm_ctx* c, int K) { return K == 2 || (K == 3 && c->mlp_dtype) ? K : 0; }
+
 static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, int bm, int K, int order) {
     WaveDims d;
     d.table = B.table;
@@ -1735,6 +1745,7 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
         d.pair_ss = K >= 2;
         d.pair_sq = order == 2;
         d.pair_bytes = pair_layout(c, B, p, K, d.pair_ss, d.pair_sq, nullptr, nullptr, nullptr, nullptr);
+        d.query_sum = query_sum(c, K);
     }
     d.Tw = p.t1 - p.t0;
     d.Ss = p.s1 - p.s0; d.Sq = p.q1 - p.q0; d.Ps = p.ps1 - p.ps0; d.Pq = p.pq1 - p.pq0;
@@ -2230,19 +2241,25 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             o.y_in = y_in; o.y_out = y_out; o.y_bf = y_bf; o.ld = ld0; o.c = cc;
             return o;
         };
-        auto two_hop = [&](bool in_support, const float* Z, const TwoHopOut* o0, const TwoHopOut* o1) {
+        // (query_sum: the pair-count tasks' query output is left out before the last step, which adds the steps' gradients up)
+        const int n_kept = pair && adapt ? d.query_sum : 0;
+        float* const kept[HOP_SUM] = {w.dX, gxs, second ? w.TXf : w.dX_kept};   // of the last step, the first, the second
+        auto two_hop = [&](bool in_support, const float* Z, const TwoHopOut* o0, const TwoHopOut* o1, bool keep = false) {
             const double bags_ = (o0 ? (double)d.Ss : 0.0) + (o1 ? (double)d.Sq : 0.0);
             const double in_l_ = in_support ? (double)d.nnz_s : (double)d.nnz_q;
             const double out_l_ = (o0 ? (double)d.nnz_s : 0.0) + (o1 ? (double)d.nnz_q : 0.0);
             // algorithmic bytes: Z once per (sample, field), Y read + written per (sample, field), 4 B per lookup and hop
             const double alg_bytes = 4.0 * D * F * (in_support ? d.Ss : d.Sq) + bags_ * F * (8.0 * D + (bf ? 2.0 * D : 0)) + 4.0 * (in_l_ + out_l_);
-            if (pair) {   // o0 is always the support side, o1 the query side
+            const TwoHopOut* const o1_pair = keep && n_kept && o0 ? nullptr : o1;
+            if (pair && (o0 || o1_pair)) {   // o0 is always the support side, o1 the query side
                 PairHopArgs pa;
                 memset(&pa, 0, sizeof pa);
                 pa.F = F; pa.D = D; pa.mat = w.pair_mat; pa.task_path = w.task_path;
                 pa.in_real_off = in_support ? w.real_off_s : w.real_off_q;
                 pa.in_row_off = in_support ? w.row_off_s : w.row_off_q;
-                pa.Z = Z; pa.ldz = FD;
+                pa.Z[0] = Z; pa.n_z = 1; pa.ldz = FD;
+                if (keep && n_kept && !o0)
+                    for (; pa.n_z < n_kept; ++pa.n_z) pa.Z[pa.n_z] = kept[pa.n_z];
                 auto fill = [&](PairHopOut& po, const TwoHopOut& o, bool out_support) {
                     po.enabled = 1;
                     po.mat_off = out_support ? (in_support ? w.pair_off_ss : w.pair_off_sq) : w.pair_off_qs;
@@ -2251,7 +2268,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                     po.y_in = o.y_in; po.y_out = o.y_out; po.y_bf = o.y_bf; po.ld = o.ld; po.c = o.c;
                 };
                 if (o0) fill(pa.out[0], *o0, true);
-                if (o1) fill(pa.out[1], *o1, false);
+                if (o1_pair) fill(pa.out[1], *o1_pair, false);
                 pa.small = w.hop_small; pa.n_small = w.n_hop_small; pa.run = w.hop_run;
                 Prof p(c, "pair_hop", alg_bytes, 0);
                 launch_pair_hop(st, pa, w.hop_tiles, w.hop_longest);
@@ -2294,7 +2311,8 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             s.wL = thf + c->offW[L];
             s.wL_stride = thf_stride;
             Pass p{&s.X, &s.A, &s.Dl, s.dL, s.zL};
-            forward_backward(c, gs, labels_s, p, th, thf, thf_stride, nullptr, F > 0 ? w.dX : nullptr);
+            float* const dX = n_kept && k + 1 < K ? kept[1 + k] : w.dX;
+            forward_backward(c, gs, labels_s, p, th, thf, thf_stride, nullptr, F > 0 ? dX : nullptr);
             // local back-propagation: theta' = theta - alpha dtheta (per task)
             Theta& next = w.thetas[second ? k : 0];
             float* wl_copy = (bf && second && k + 1 < K) ? w.steps[k + 1].wL_copy : nullptr;
@@ -2321,7 +2339,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 const bool last = !more;
                 TwoHopOut os = hop_out(true, xs_cur, bf && k + 2 == K ? nullptr : xs_next, more && bf ? Xn.b : nullptr, -alpha);
                 TwoHopOut oq = hop_out(false, w.Xq0, bf && last ? nullptr : w.Xq0, (bf && last) ? Xq.b : nullptr, -alpha);
-                two_hop(true, w.dX, more ? &os : nullptr, &oq);
+                two_hop(true, dX, more ? &os : nullptr, &oq, true);
                 if (more) {
                     launch_copy_tail(st, FD, xs_cur, d.Ps, bf ? nullptr : (xs_next != xs_cur ? xs_next : nullptr), ld0, bf ? Xn.b : nullptr);
                     xs_cur = xs_next;

@@ -459,21 +459,22 @@ __device__ __forceinline__ void ph_cvt4(u32 x, u32& lo, u32& hi) {
 // one group) and the staging writes (every fourth column, one group) spread over all banks.
 __device__ __forceinline__ int ph_key(int col) { return ((col >> 1) + (col >> 4)) & 7; }
 
-// One workgroup's share of a 64-row chunk of Z: DS/16 rows of four columns per thread.
-template <int DS>
+// One workgroup's share of a 64-row chunk of Z, the sum of NZ arrays: DS/16 rows of four columns per thread.
+template <int DS, int NZ>
 struct HopStage {
     static constexpr int CG = DS / 4;        // float4 column groups of a row of Z
     static constexpr int RPT = CG / 4;       // rows of the 64-row chunk staged per thread (256 threads)
     static constexpr int WORDS = 3 * DS * PH_KC;   // bf16 values of a staged chunk
     int rg, wr_off[4];   // element offsets of this thread's staging writes, per column of its float4
-    const float* Zt;
+    const float* Zt[NZ];
     int64_t ldz;
     int n_in;
-    float4 z[RPT];
-    __device__ __forceinline__ HopStage(const float* Z0, int64_t ldz_, int n_in_) : ldz(ldz_), n_in(n_in_) {
+    float4 z[NZ][RPT];
+    __device__ __forceinline__ HopStage(const PairHopArgs& a, int64_t off, int n_in_) : ldz(a.ldz), n_in(n_in_) {   // off: of the first row's first column
         const int cg = threadIdx.x % CG;
         rg = threadIdx.x / CG;
-        Zt = Z0 + cg * 4;
+#pragma unroll
+        for (int j = 0; j < NZ; ++j) Zt[j] = a.Z[j] + off + cg * 4;
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) {
             const int col = cg * 4 + cc, k0 = rg * RPT;
@@ -483,8 +484,9 @@ struct HopStage {
     __device__ __forceinline__ void load(int kc) {
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {   // branch-free: a row beyond the task reads the task's last row and is zeroed
-            const int row = kc + rg * RPT + r;
-            z[r] = *reinterpret_cast<const float4*>(Zt + (int64_t)min(row, n_in - 1) * ldz);
+            const int64_t at = (int64_t)min(kc + rg * RPT + r, n_in - 1) * ldz;
+#pragma unroll
+            for (int j = 0; j < NZ; ++j) z[j][r] = *reinterpret_cast<const float4*>(Zt[j] + at);
         }
     }
     // splits the loaded rows into their three bf16 pieces and writes them into an LDS buffer
@@ -493,7 +495,10 @@ struct HopStage {
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
             const float keep = kc + rg * RPT + r < n_in ? 1.f : 0.f;
-            const float zz[4] = {z[r].x * keep, z[r].y * keep, z[r].z * keep, z[r].w * keep};
+            float4 x = z[0][r];
+#pragma unroll
+            for (int j = 1; j < NZ; ++j) x = make_float4(x.x + z[j][r].x, x.y + z[j][r].y, x.z + z[j][r].z, x.w + z[j][r].w);
+            const float zz[4] = {x.x * keep, x.y * keep, x.z * keep, x.w * keep};
 #pragma unroll
             for (int cc = 0; cc < 4; ++cc) {
                 const u32 u0 = __builtin_bit_cast(u32, zz[cc]);
@@ -604,8 +609,8 @@ struct HopStrip {
 
 // A tile of up to 64 * NS * 2 out-rows from row0 on.  NS strips per wave, NC column tiles per wave: with fewer than all of
 // them the waves lie side by side along the columns.
-template <int DS, int NS, int NC>
-__device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M, const float* Z0, int64_t ldz, int n_in, int n_out, int row0,
+template <int DS, int NZ, int NS, int NC>
+__device__ __forceinline__ void hop_tile(const PairHopArgs& a, const PairHopOut& out, const uint8_t* M, int64_t z_off, int n_in, int n_out, int row0,
                                          int64_t row_base, int64_t colz, bf16_t* zs) {
     constexpr int WC = DS / 32 / NC;   // waves along the columns
     const int colsP = pad64(n_in);
@@ -613,7 +618,8 @@ __device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M
     const int ct0 = (wv % WC) * NC, row_w = __builtin_amdgcn_readfirstlane(row0 + (wv / WC) * 32 * NS);   // first out-row of this wave
     const bool wave_on = row_w < n_out;               // its strips then lie inside the padded matrix
     const uint8_t* Mw = M + (size_t)(row_w + ln) * colsP + h * 32;
-    HopStage<DS> st(Z0, ldz, n_in);
+    typedef HopStage<DS, NZ> Stage;
+    Stage st(a, z_off, n_in);
     ph_float16 acc[NS][NC];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -646,21 +652,21 @@ __device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M
         st.load(kn);
         load_a(kn, anext);
         __builtin_amdgcn_sched_barrier(0);   // the loads above are consumed only after the multiplication below
-        if (wave_on) hop_multiply<DS, NS, NC>(zs + cur * HopStage<DS>::WORDS, araw, ct0, acc);
+        if (wave_on) hop_multiply<DS, NS, NC>(zs + cur * Stage::WORDS, araw, ct0, acc);
         __builtin_amdgcn_sched_barrier(0);
         cur ^= 1;
-        st.store(zs + cur * HopStage<DS>::WORDS, kn);
+        st.store(zs + cur * Stage::WORDS, kn);
 #pragma unroll
         for (int s = 0; s < NS; ++s) { araw[s][0] = anext[s][0]; araw[s][1] = anext[s][1]; }
         __syncthreads();
     }
     strip.request(0, y[0]);
     __builtin_amdgcn_sched_barrier(0);
-    if (wave_on && colsP > 0) hop_multiply<DS, NS, NC>(zs + cur * HopStage<DS>::WORDS, araw, ct0, acc);
+    if (wave_on && colsP > 0) hop_multiply<DS, NS, NC>(zs + cur * Stage::WORDS, araw, ct0, acc);
     __syncthreads();   // every wave is done with the staged chunks
     if (!wave_on) return;
     float* E = reinterpret_cast<float*>(zs) + wv * HopStrip<NC>::FLOATS;
-    static_assert(4 * HopStrip<NC>::FLOATS * 4 <= 2 * HopStage<DS>::WORDS * 2, "the waves' strips fit the staged chunks' LDS");
+    static_assert(4 * HopStrip<NC>::FLOATS * 4 <= 2 * Stage::WORDS * 2, "the waves' strips fit the staged chunks' LDS");
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         strip.park(E, acc[s]);
@@ -669,10 +675,11 @@ __device__ __forceinline__ void hop_tile(const PairHopOut& out, const uint8_t* M
     }
 }
 
-template <int DS>
+// (a sum of several arrays: a chunk's rows of all of them are on their way together, in registers)
+template <int DS, int NZ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_hop_kernel(PairHopArgs a) {
     constexpr int NCT = DS / 32;      // 32-column tiles
-    __shared__ __attribute__((aligned(16))) bf16_t zs[2 * HopStage<DS>::WORDS];
+    __shared__ __attribute__((aligned(16))) bf16_t zs[2 * HopStage<DS, NZ>::WORDS];
     // workgroups are dealt round-robin to the 8 XCDs; every XCD walks its own list, all (tile, field)s of one task's run in a row
     const int nsl = a.D / DS, fx = a.F * nsl;
     const int xcd = blockIdx.x & 7, k = (int)(blockIdx.x >> 3), e = a.tiles[xcd] + k / a.run;
@@ -706,20 +713,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int n_out = o ? n[1] : n[0];
     const uint8_t* M = a.mat + (o ? mat_off[1] : mat_off[0]) + (size_t)f * pad64(n_out) * pad64(n_in);
     const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
-    const float* Z0 = a.Z + (int64_t)in_row * a.ldz + colz;
+    const int64_t z_off = (int64_t)in_row * a.ldz + colz;
     const int64_t row_base = o ? row_off[1] : row_off[0];
-    if (n_out - row0 > 128) hop_tile<DS, 2, NCT>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
-    else if (n_out - row0 > 64) hop_tile<DS, 1, NCT>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
-    else hop_tile<DS, 1, 1>(out, M, Z0, a.ldz, n_in, n_out, row0, row_base, colz, zs);
+    if (n_out - row0 > 128) hop_tile<DS, NZ, 2, NCT>(a, out, M, z_off, n_in, n_out, row0, row_base, colz, zs);
+    else if (n_out - row0 > 64) hop_tile<DS, NZ, 1, NCT>(a, out, M, z_off, n_in, n_out, row0, row_base, colz, zs);
+    else hop_tile<DS, NZ, 1, 1>(a, out, M, z_off, n_in, n_out, row0, row_base, colz, zs);
 }
 
 // Tasks of at most 64 rows in both sets: one chunk of Z, at most two strips per output.  What is bound here is the chain of
 // dependent reads (task -> offsets -> M, Z and Y -> LDS), so everything is requested at once and half the LDS and registers
 // of the large tiles let twice as many workgroups run side by side.
-template <int DS>
+template <int DS, int NZ>
 __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
     constexpr int NCT = DS / 32;
-    __shared__ __attribute__((aligned(16))) bf16_t zs[HopStage<DS>::WORDS];
+    __shared__ __attribute__((aligned(16))) bf16_t zs[HopStage<DS, NZ>::WORDS];
     const int nsl = a.D / DS, fx = a.F * nsl;
     const int per_xcd = gridDim.x >> 3, wid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);   // neighbouring fields on one XCD
     if (wid >= a.n_small * fx) return;
@@ -748,7 +755,7 @@ __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
         }
     }
     if (n_in > 0) {
-        HopStage<DS> st(a.Z + (int64_t)a.in_row_off[t] * a.ldz + colz, a.ldz, n_in);
+        HopStage<DS, NZ> st(a, (int64_t)a.in_row_off[t] * a.ldz + colz, n_in);
         st.load(0);
         st.store(zs, 0);
     }
@@ -765,7 +772,7 @@ __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
     }
     __syncthreads();   // every wave is done with the staged chunk
     float* E = reinterpret_cast<float*>(zs) + (NCT == 1 ? wv >> 1 : wv) * HopStrip<1>::FLOATS;
-    static_assert(2 * NCT * HopStrip<1>::FLOATS * 4 <= HopStage<DS>::WORDS * 2, "the strips fit the staged chunk's LDS");
+    static_assert(2 * NCT * HopStrip<1>::FLOATS * 4 <= HopStage<DS, NZ>::WORDS * 2, "the strips fit the staged chunk's LDS");
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
         if (!on[o]) continue;
@@ -827,12 +834,21 @@ void launch_pair_hop(hipStream_t st, PairHopArgs a, const int32_t* const tiles[3
     const int ds = a.D % 64 == 0 ? 64 : 32;
     const int64_t fx = (int64_t)a.F * (a.D / ds), n_large = 8 * (int64_t)a.run * longest[kind], n_small = (fx * a.n_small + 7) / 8 * 8;
     if (n_large >= ((int64_t)1 << 31) || n_small >= ((int64_t)1 << 31)) return;   // cannot happen within the library's own limits on a call
-    if (n_large > 0) {
-        if (ds == 64) hipLaunchKernelGGL(pair_hop_kernel<64>, dim3((unsigned)n_large), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(pair_hop_kernel<32>, dim3((unsigned)n_large), dim3(256), 0, st, a);
+#define HOP_LAUNCH(DS_, NZ_)                                                                                                             \
+    do {                                                                                                                                 \
+        if (n_large > 0) hipLaunchKernelGGL((pair_hop_kernel<DS_, NZ_>), dim3((unsigned)n_large), dim3(256), 0, st, a);                  \
+        if (n_small > 0) hipLaunchKernelGGL((pair_hop_small_kernel<DS_, NZ_>), dim3((unsigned)n_small), dim3(256), 0, st, a);            \
+    } while (0)
+#define HOP_WIDTH(NZ_)                                  \
+    do {                                                \
+        if (ds == 64) HOP_LAUNCH(64, NZ_);              \
+        else HOP_LAUNCH(32, NZ_);                       \
+    } while (0)
+    switch (a.n_z) {
+        case 1: HOP_WIDTH(1); break;
+        case 2: HOP_WIDTH(2); break;
+        default: HOP_WIDTH(3); break;
     }
-    if (n_small > 0) {
-        if (ds == 64) hipLaunchKernelGGL(pair_hop_small_kernel<64>, dim3((unsigned)n_small), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(pair_hop_small_kernel<32>, dim3((unsigned)n_small), dim3(256), 0, st, a);
-    }
+#undef HOP_WIDTH
+#undef HOP_LAUNCH
 }
