@@ -336,9 +336,11 @@ struct WaveDims {
     int64_t hop_tiles_s = 0, hop_tiles_q = 0;   // tiles of 256 rows of the tasks beyond HOP_SMALL (the hops' work lists)
     bool table = false;                    // the sparse gradient is reduced wave by wave into a table-shaped output
     int query_sum = 0;                     // > 1: so many steps' input gradients are kept, and the query set's row update is taken once, from their sum
+    bool from_meta = false;                // an inner step's weights are written from the meta parameters and all steps' gradients so far
     int factor_ld = 0;                     // > 0: the chain's direction stays factors (see Factor); rows of the largest task of the batch
 };
 static int query_sum(const gm_ctx* c, int K);
+static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t rows_s, int K, int order);
 static int factor_slots(int K) { return 2 * K - 1; }   // most factors of the direction: the query pass's, two of every later step
 
 static Act alloc_act(const gm_ctx* c, Arena& ar, int64_t rows, int ld) {
@@ -452,10 +454,11 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.vsum = Theta{ar.get<float>((int64_t)most_runs(c) * c->n_theta), c->n_theta, nullptr, 0};
     if (!second) w.v.b = nullptr;  // the direction is a GEMM operand only in the second-order pass
     w.Xs_scratch = Act();
-    if (K > 1 && !second) {
+    const bool keep = second || d.from_meta;   // every step's activations and deltas
+    if (K > 1 && !keep) {
         w.Xs_scratch = alloc_act(c, ar, d.Ps, ld0);
     }
-    const int kept = second ? K : (K > 0 ? 1 : 0);
+    const int kept = keep ? K : (K > 0 ? 1 : 0);
     w.steps.assign(kept, StepState());
     for (int k = 0; k < kept; ++k) {
         StepState& s = w.steps[k];
@@ -799,6 +802,7 @@ extern "C" size_t gm_workspace_bytes(const gm_model_desc* model, int32_t n_tasks
     d.Tw = n_tasks;
     d.Ss = n_support; d.Sq = n_query; d.Ps = Ps; d.Pq = Pq;
     d.nnz_s = nnz_support; d.nnz_q = nnz_query;
+    d.from_meta = theta_from_meta(&c, n_tasks, n_support, inner_steps, order);
     d.mt_s = (int)(Ps / 64 + n_tasks + 1);  // upper bound on m-tiles
     d.mt_q = (int)(Pq / 64 + n_tasks + 1);
     // pair-count matrices, for tasks of equal size (a batch of uneven tasks may need more and then runs in waves)
@@ -1406,6 +1410,7 @@ struct Batch {  // host-side description of one call
     std::vector<int64_t> ls, lq;          // lookup offsets per task (filled when several waves are needed)
     bool table = false;                   // table-shaped sparse output: every wave sorts and reduces its own lookups
     int pair_rows = PAIR_ROWS;            // a task of at most so many rows in each set goes through pair-count matrices
+    bool fp32_master = false;             // first order: no room for every step's activations (theta_from_meta)
     BatchBufs b;
     HostImages images;
 };
@@ -1727,10 +1732,21 @@ static int factor_rows(const gm_ctx* c, const Batch& B, int bm, int K, int order
 // uses before (the support rows of the gradient buffer, the chain's fp32 direction) but for one without a chain.
 static int query_sum(const gm_ctx* c, int K) { return K == 2 || (K == 3 && c->mlp_dtype) ? K : 0; }
 
+// bf16, 2..GEMM_MAX_PAIRS inner steps: every step's weights straight from the meta parameters and the gradients of all steps so far, bf16
+// copy only.  Second order keeps the steps' activations and deltas for the chain anyway.  First order does so where the extra products
+// (k + 1 of step k instead of one) cost less than the fp32 master, written and read again by the next step: 201 tasks of 75..225 rows,
+// 1677-512-256, three steps, the six products of the steps 1110 us with the master, 864 without; a product more costs 60 us there, so K steps
+// of r rows a task break even at K r = 1050.
+static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t rows_s, int K, int order) {
+    if (!c->mlp_dtype || K < 2 || K > GEMM_MAX_PAIRS || !c->theta_from_meta || T <= 0) return false;
+    return order == 2 || (double)K * rows_s < 1050.0 * (double)T;
+}
+
 static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, int bm, int K, int order) {
     WaveDims d;
     d.table = B.table;
     d.factor_ld = factor_rows(c, B, bm, K, order);
+    d.from_meta = !B.fp32_master && theta_from_meta(c, B.T, B.poff_s[B.T], K, order);
     for (int t = p.t0; t < p.t1; ++t) {
         if (task_pair_ok(c, B, t, K)) {
             d.pair = true;
@@ -1831,6 +1847,11 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         }
         if (fits) return GM_OK;
         if (per == 1) {
+            if (!B.fp32_master && order == 1 && theta_from_meta(c, T, B.poff_s[T], K, order)) {
+                B.fp32_master = true;   // (the steps' activations of one task do not fit)
+                n_waves = fewest;
+                continue;
+            }
             if (B.pair_rows == PAIR_ROWS) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
             B.pair_rows = PAIR_ROWS;   // (a large task does not fit with its matrices, not even alone)
             n_waves = fewest;
@@ -2298,14 +2319,12 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         const float* xs_cur = w.Xs0;    // fp32 support input of the current step
         Act Xq = w.Xq;                  // query input as the GEMMs read it
         if (!bf) Xq.f = w.Xq0;          // fp32: the prefetched buffer, updated in place by the overlap update
-        // bf16, second order, 2..GEMM_MAX_PAIRS inner steps: every step's weights straight from the meta parameters
-        // and the gradients of all steps so far (their activations and deltas are kept for the chain anyway)
-        const bool from_theta0 = bf && second && K >= 2 && K <= GEMM_MAX_PAIRS && c->theta_from_meta;
+        const bool from_theta0 = d.from_meta, keep = second || from_theta0;
         std::vector<Factor> v_fac;   // of the direction
         const float* thf0 = thf;
         std::vector<Pass> passes;
         for (int k = 0; k < K; ++k) {
-            StepState& s = w.steps[second ? k : 0];
+            StepState& s = w.steps[keep ? k : 0];
             if (k == 0) s.X = X0s;
             s.th = th;
             s.wL = thf + c->offW[L];
@@ -2328,7 +2347,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             // (overlap update) the query input; a query row that the support set does not touch keeps its meta value
             const bool more = k + 1 < K;
             Act Xn;  // support input of step k+1
-            if (more) Xn = second ? w.steps[k + 1].X : w.Xs_scratch;
+            if (more) Xn = keep ? w.steps[k + 1].X : w.Xs_scratch;
             if (F > 0 && adapt) {
                 if ((rc = join_pairs())) return rc;
                 float* xs_next = nullptr;
@@ -2348,7 +2367,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
                 Xn = s.X;
             }
             if (more) {
-                w.steps[second ? k + 1 : 0].X = Xn;
+                w.steps[keep ? k + 1 : 0].X = Xn;
             }
         }
         // bf16 second order with K > 1: steps k >= 1 read their last-layer weights from the copies taken above
