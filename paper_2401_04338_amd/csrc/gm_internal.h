@@ -40,7 +40,7 @@ struct SetView {
 // (clears the status words first.)  uniform_rows: the number of rows every table has, or -1 when the tables differ in size
 // most_bags: of the largest of the tasks, both sets
 void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, SetView sup, SetView qry, const int64_t* field_base,
-                     int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status);
+                     int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status, bool cleared /* status is clear already */);
 void launch_scan_u32(hipStream_t st, const u32* in, u32* out, int64_t n, u32* tmp /* >= n/1024+2048 */,
                      u32* total /* may be null */);
 size_t scan_tmp_words(int64_t n);
@@ -133,6 +133,7 @@ struct FieldKeysArgs {
     SetView sup, qry;
     const int64_t* field_base;
     const u32 *cnt_s, *cnt_q;        // [Tw * F]
+    u32 *base_s, *base_q;            // [Tw * F] out: exclusive scans of the counts
     u32 *fm_off_s, *fm_off_q;        // [Tw * F] scratch: a (task, field)'s place inside its field's range, per set
     const int32_t *prow_s, *prow_q;  // padded row of every sample (whole sets)
     u32 row0_s, row0_q;              // added to it: the row in the gradient buffer
@@ -140,7 +141,7 @@ struct FieldKeysArgs {
     u32 *keys, *vals;
     const u32 *key_pos, *tot;        // set by the launcher
 };
-void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n /* lookups of the wave, as the passes are given */, int max_bag);
+void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, u32* scan_tmp, int64_t n /* lookups of the wave, as the passes are given */, int max_bag);
 SegTab field_seg_tab(int F, u32* tables);
 size_t field_table_words(int F);
 // chunk_scan: segments that begin in front of every chunk of ch keys; n_rows_out: their number.  With emb_rows or seg_counts:
@@ -423,7 +424,7 @@ struct ExpandJob {
     const int32_t* first;    // [G] or null
     int32_t* out;
 };
-struct ExpandJobs { int n; ExpandJob job[4]; };
+struct ExpandJobs { int n; ExpandJob job[4]; u32* clear = nullptr; int clear_words = 0; };   // (clear: at most 256 words, cleared along with it)
 void launch_expand_tasks(hipStream_t st, int G, const ExpandJobs& jobs);
 enum { MATRIX_JOBS = 12 };   // matrices per launch
 struct MatrixJob {

@@ -1537,7 +1537,7 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
     SetView vs = make_view(B.sup, B.b.toff_s, wp.s0, wp.ls0), vq = make_view(B.qry, B.b.toff_q, wp.q0, wp.lq0);
     {
         Prof p(c, "tf_count", 8.0 * ((wp.s1 - wp.s0) + (wp.q1 - wp.q0)) * F + 4.0 * ((wp.ls1 - wp.ls0) + (wp.lq1 - wp.lq0)), 0);
-        launch_tf_count(st, F, wp.t0, Tw, most_bags(B.sup, B.qry, wp.t0, wp.t1, F), vs, vq, c->d_field_base, B.sup->nnz, B.qry->nnz, uniform_rows(c), w.cnt_s, w.cnt_q, c->d_status);
+        launch_tf_count(st, F, wp.t0, Tw, most_bags(B.sup, B.qry, wp.t0, wp.t1, F), vs, vq, c->d_field_base, B.sup->nnz, B.qry->nnz, uniform_rows(c), w.cnt_s, w.cnt_q, c->d_status, true);
     }
     u32 hs[ST_WORDS];
     int rc = read_status(c, hs);
@@ -1554,7 +1554,6 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
     if (cap > tf_sort_max_cap())
         return fail(c, GM_ERR_CAPACITY, "a (task, field) has %u lookups in one set; the limit is %d", hs[ST_MAX_TF],
                     tf_sort_max_cap());
-    launch_scan_u32_pair(st, w.cnt_s, w.base_s, w.cnt_q, w.base_q, TF, w.scan_tmp);
     const double tf_bytes = 12.0 * ((wp.ls1 - wp.ls0) + (wp.lq1 - wp.lq0));
     // ---- the dictionaries read off the row order of the wave's lookups
     bool join = jr && jr->so && c->index_path != 1;
@@ -1568,9 +1567,11 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
     }
     if (jr && c->index_path == 2 && !join)
         return fail(c, GM_ERR_CAPACITY, "index_path 2: the wave's lookups cannot be ordered as one list of 32-bit bit-field values");
+    const bool by_field = join && c->sort_fields;
+    if (!by_field) launch_scan_u32_pair(st, w.cnt_s, w.base_s, w.cnt_q, w.base_q, TF, w.scan_tmp);
     if (join) {
         SortBufs& so = *jr->so;
-        if (c->sort_fields) {
+        if (by_field) {
             // the keys field after field (the per-(task, field) counts give every lookup its place), then every field's
             // range sorted by its row bits alone
             const int64_t nw = (wp.ls1 - wp.ls0) + (wp.lq1 - wp.lq0);
@@ -1578,10 +1579,10 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
             FieldKeysArgs fa;
             memset(&fa, 0, sizeof fa);
             fa.F = F; fa.t0 = wp.t0; fa.Tw = Tw; fa.sup = vs; fa.qry = vq; fa.field_base = c->d_field_base;
-            fa.cnt_s = w.cnt_s; fa.cnt_q = w.cnt_q; fa.fm_off_s = w.fm_off_s; fa.fm_off_q = w.fm_off_q;
+            fa.cnt_s = w.cnt_s; fa.cnt_q = w.cnt_q; fa.base_s = w.base_s; fa.base_q = w.base_q; fa.fm_off_s = w.fm_off_s; fa.fm_off_q = w.fm_off_q;
             fa.prow_s = B.b.prow_s; fa.prow_q = B.b.prow_q; fa.row0_s = jr->range.row0_s; fa.row0_q = jr->range.row0_q;
             fa.enc = enc; fa.keys = so.keys; fa.vals = so.vals;
-            launch_build_keys_by_field(st, fa, w.field_tab, nw, (int)hs[ST_MAX_BAG]);
+            launch_build_keys_by_field(st, fa, w.field_tab, w.scan_tmp, nw, (int)hs[ST_MAX_BAG]);
             int64_t max_rows = 1;
             for (int f = 0; f < F; ++f) max_rows = std::max(max_rows, c->field_base[f + 1] - c->field_base[f]);
             const SegTab seg = field_seg_tab(F, w.field_tab);
@@ -1935,7 +1936,7 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
     }
     const int rc = up.send(c, B.images);
     if (rc != GM_OK) return rc;
-    launch_expand_tasks(st, d.Tw, ExpandJobs{2, {{nullptr, w.row_off_s, nullptr, w.row_task_s}, {nullptr, w.row_off_q, nullptr, w.row_task_q}}});
+    launch_expand_tasks(st, d.Tw, ExpandJobs{2, {{nullptr, w.row_off_s, nullptr, w.row_task_s}, {nullptr, w.row_off_q, nullptr, w.row_task_q}}, c->d_status, ST_WORDS});
     auto most = [](const std::vector<int32_t>& off) { int32_t m = 0; for (size_t t = 1; t < off.size(); ++t) m = std::max(m, off[t] - off[t - 1]); return (int)m; };
     gs = Grp{w.row_off_s, w.real_off_s, w.row_task_s, w.tile_g_s, w.tile_m_s, d.mt_s, d.Tw, bm, d.Ps, most(ro_s)};
     gq = Grp{w.row_off_q, w.real_off_q, w.row_task_q, w.tile_g_q, w.tile_m_q, d.mt_q, d.Tw, bm, d.Pq, most(ro_q)};
@@ -3238,7 +3239,7 @@ extern "C" int gm_gather_pool(gm_ctx* c, int32_t T, const gm_set* set, const flo
     SetView v = make_view(set, toff, 0, 0);
     if (c->F == 0 || T == 0) launch_fill_u32(st, c->d_status, ST_WORDS, 0);
     else
-        launch_tf_count(st, c->F, 0, T, most_bags(set, set, 0, T, c->F), v, v, c->d_field_base, set->nnz, set->nnz, uniform_rows(c), cnt, cnt + (int64_t)T * c->F + 1, c->d_status);
+        launch_tf_count(st, c->F, 0, T, most_bags(set, set, 0, T, c->F), v, v, c->d_field_base, set->nnz, set->nnz, uniform_rows(c), cnt, cnt + (int64_t)T * c->F + 1, c->d_status, false);
     u32 hs[ST_WORDS];
     rc = read_status(c, hs);
     if (rc != GM_OK) return rc;

@@ -150,14 +150,14 @@ __global__ __launch_bounds__(TC_NT) void tf_count_kernel(int F, int t0, SetView 
 }
 
 void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, SetView sup, SetView qry, const int64_t* field_base,
-                     int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status) {
+                     int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status, bool cleared) {
     if (Tw <= 0) return;
     // A (task, set) is split, down to a bag a thread, while the workgroups are fewer than 128: a few large tasks would leave the chip
     // idle (3 tasks x 32,768 + 32,768 bags).  The largest task decides: the others' spare workgroups have nothing to add, and it
     // alone would be the launch's time (one task of 2048 + 2048 samples and 99 of 2 + 2).
     const int split = (int)std::max<int64_t>(1, std::min<int64_t>(most_bags / TC_NT, 64 / Tw));
     const int64_t counts = split > 1 ? (int64_t)Tw * F : 0;
-    launch_zero(st, ZeroJobs{split > 1 ? 3 : 1, {status, cnt_sup, cnt_qry}, {ST_WORDS, counts, counts}});
+    if (split > 1 || !cleared) launch_zero(st, ZeroJobs{split > 1 ? 3 : 1, {status, cnt_sup, cnt_qry}, {ST_WORDS, counts, counts}});
     hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, 2, split), dim3(TC_NT), F * sizeof(u32), st, F, t0, sup, qry, field_base,
                        nnz_sup, nnz_qry, uniform_rows, cnt_sup, cnt_qry, status);
 }
@@ -793,6 +793,77 @@ __global__ __launch_bounds__(256) void field_table_kernel(int F, const u32* tot,
     }
 }
 
+// Few (task, field)s: the scans of their counts, the fields' offsets and their table by one workgroup instead of three launches that are
+// mostly their latency (4.5 + 4.1 + 3.4 us for 32 of them, and what lies between).  Waves take a field each, a lane a task.  Beyond FP_TF
+// counts they no longer fit the LDS, and there is work for several workgroups.
+#define FP_TF 4096
+#define FP_NT 1024
+__global__ __launch_bounds__(FP_NT) void field_prepare_kernel(int F, int Tw, const u32* __restrict__ cnt_s, const u32* __restrict__ cnt_q, const int64_t* __restrict__ field_base,
+                                                              int tile_keys, u32* base_s, u32* base_q, u32* fm_off_s, u32* fm_off_q, u32* key_pos, u32* tile_base, u32* key_sub, u32* tot) {
+    __shared__ u32 cnt[2][FP_TF], sum[2][FP_TF];   // (F <= F * Tw)
+    __shared__ int sh[FP_NT / WAVE + 2];
+    constexpr int PER = FP_TF / FP_NT;
+    const int TF = F * Tw, lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    for (int i = threadIdx.x; i < TF; i += FP_NT) {
+        cnt[0][i] = cnt_s[i];
+        cnt[1][i] = cnt_q[i];
+    }
+    __syncthreads();
+    for (int set = 0; set < 2; ++set) {
+        u32* const base = set ? base_q : base_s;
+        u32 c[PER];
+        u32 mine = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int i = (int)threadIdx.x * PER + k;
+            c[k] = i < TF ? cnt[set][i] : 0u;
+            mine += c[k];
+        }
+        int all;
+        u32 run = (u32)block_excl_scan((int)mine, sh, &all);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int i = (int)threadIdx.x * PER + k;
+            if (i < TF) base[i] = run;
+            run += c[k];
+        }
+    }
+    for (int i = wv; i < 2 * F; i += FP_NT / WAVE) {   // (field, set)
+        const int set = i & 1, f = i >> 1;
+        u32* const off = set ? fm_off_q : fm_off_s;
+        u32 run = 0;
+        for (int t0 = 0; t0 < Tw; t0 += WAVE) {
+            const int t = t0 + lane;
+            const u32 c = t < Tw ? cnt[set][t * F + f] : 0u;
+            const u32 incl = (u32)wave_incl_scan((int)c);
+            if (t < Tw) off[t * F + f] = run + incl - c;
+            run += (u32)__shfl((int)incl, WAVE - 1, WAVE);
+        }
+        if (lane == 0) {
+            sum[set][f] = run;
+            tot[set * F + f] = run;
+        }
+    }
+    __syncthreads();
+    u32 k = 0, tl = 0;
+    for (int f0 = 0; f0 <= F; f0 += FP_NT) {   // (entry F: the ends)
+        const int f = f0 + (int)threadIdx.x;
+        const u32 nf = f < F ? sum[0][f] + sum[1][f] : 0u;
+        int n_keys, n_tiles;
+        const u32 kx = (u32)block_excl_scan((int)nf, sh, &n_keys);
+        __syncthreads();
+        const u32 tx = (u32)block_excl_scan((int)((nf + (u32)tile_keys - 1) / (u32)tile_keys), sh, &n_tiles);
+        __syncthreads();
+        if (f <= F) {
+            key_pos[f] = k + kx;
+            tile_base[f] = tl + tx;
+            key_sub[f] = f < F ? (u32)field_base[f] : 0u;
+        }
+        k += (u32)n_keys;
+        tl += (u32)n_tiles;
+    }
+}
+
 enum { RS_ITEMS = 8 };   // keys per thread of a radix tile
 static int rs_tile_keys(int64_t n);
 
@@ -908,14 +979,20 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
 }
 
 // tables: 3 (F + 1) words (key_pos, tile_base, key_sub), then 2 F words of totals
-void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, int64_t n, int max_bag) {
+void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, u32* scan_tmp, int64_t n, int max_bag) {
     if (a.F <= 0 || a.Tw <= 0) return;
     u32* key_pos = tables;
     u32* tile_base = key_pos + (a.F + 1);
     u32* key_sub = tile_base + (a.F + 1);
     u32* tot = key_sub + (a.F + 1);
-    hipLaunchKernelGGL(field_offsets_kernel, dim3(a.F), dim3(256), 0, st, a.F, a.Tw, a.cnt_s, a.cnt_q, a.fm_off_s, a.fm_off_q, tot);
-    hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(256), 0, st, a.F, tot, a.field_base, rs_tile_keys(n), key_pos, tile_base, key_sub);
+    if ((int64_t)a.F * a.Tw <= FP_TF) {
+        hipLaunchKernelGGL(field_prepare_kernel, dim3(1), dim3(FP_NT), 0, st, a.F, a.Tw, a.cnt_s, a.cnt_q, a.field_base, rs_tile_keys(n), a.base_s, a.base_q, a.fm_off_s,
+                           a.fm_off_q, key_pos, tile_base, key_sub, tot);
+    } else {
+        launch_scan_u32_pair(st, a.cnt_s, a.base_s, a.cnt_q, a.base_q, (int64_t)a.F * a.Tw, scan_tmp);
+        hipLaunchKernelGGL(field_offsets_kernel, dim3(a.F), dim3(256), 0, st, a.F, a.Tw, a.cnt_s, a.cnt_q, a.fm_off_s, a.fm_off_q, tot);
+        hipLaunchKernelGGL(field_table_kernel, dim3(1), dim3(256), 0, st, a.F, tot, a.field_base, rs_tile_keys(n), key_pos, tile_base, key_sub);
+    }
     a.key_pos = key_pos;
     a.tot = tot;
     const dim3 grid((unsigned)(((int64_t)a.F * a.Tw + 7) / 8 * 8), 2);
@@ -951,13 +1028,15 @@ __device__ __forceinline__ u32 rs_task_of(const TaskOf& m, u32 val) {
 // that ONE exclusive scan over the whole table still yields every (range, digit, tile)'s place in the output; the
 // digit is taken from the key minus the range's key base.  seg.n_seg == 0: one range, the whole list.
 // FEW: few tiles.  The table is [tile][digit] and nobody scans it: every workgroup of the scatter adds up its range's counts itself,
-// beside its first loads (the scan was a launch of one workgroup, RS_FEW_TILES).
+// beside its first loads (the scan was a launch of one workgroup, RS_FEW_TILES).  OWN: so few that it counts the range's other tiles
+// itself, too, and there is no table (RS_OWN_TILES).
+enum { RS_SCAN, RS_FEW, RS_OWN };
 struct RsTile {
     int64_t k0, k1;      // keys of the tile
     u32 key_base;        // subtracted from a key before its digit is taken
     size_t h0;           // count-table index of (digit 0, this tile)
     size_t hstride;      // ... and the distance between digits
-    int64_t pos0;        // the range's first key,
+    int64_t pos0, pos1;  // the range's keys,
     int t0, nt;          // first tile and number of tiles
     bool any;
 };
@@ -971,6 +1050,7 @@ __device__ __forceinline__ RsTile rs_tile(const SegTab& seg, int tile, int nblk,
         t.h0 = FEW ? (size_t)tile * nb : (size_t)tile;
         t.hstride = FEW ? 1 : (size_t)nblk;
         t.pos0 = 0;
+        t.pos1 = n;
         t.t0 = 0;
         t.nt = nblk;
         t.any = tile < nblk;
@@ -990,6 +1070,7 @@ __device__ __forceinline__ RsTile rs_tile(const SegTab& seg, int tile, int nblk,
     t.hstride = FEW ? 1 : (size_t)(te - tb);
     t.h0 = FEW ? (size_t)tile * nb : (size_t)nb * tb + ((u32)tile - tb);
     t.pos0 = (int64_t)seg.key_base_pos[lo];
+    t.pos1 = (int64_t)seg.key_base_pos[lo + 1];
     t.t0 = (int)tb;
     t.nt = (int)(te - tb);
     return t;
@@ -1035,11 +1116,13 @@ __global__ __launch_bounds__(NT) void radix_hist_kernel(const u32* src, int64_t 
 
 // Stable scatter: every wave owns a contiguous 1/4 of the tile and ranks its keys round by round (64
 // consecutive keys per round) with ballot matching, so equal digits keep their input order.
-template <int BITS, bool BYTASK, int NT, bool FEW>
+template <int BITS, bool BYTASK, int NT, int MODE>
 __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const u32* vin, u32* kout, u32* vout, const u32* gofs,
                                      int64_t n_all, int shift, int nblk, TaskOf tk, SegTab seg) {
     constexpr int NB = 1 << BITS, DPT = NB > NT ? NB / NT : 1;   // digits per thread in the per-digit phase
     constexpr int TILE = NT * RS_ITEMS, WAVES = NT / WAVE;
+    constexpr bool FEW = MODE != RS_SCAN, OWN = MODE == RS_OWN;
+    __shared__ u32 others[OWN ? 2 : 1][OWN ? NB : 1];   // keys of a digit in the range's tiles before this one, after it
     __shared__ __attribute__((aligned(16))) uint16_t cnt[WAVES][NB];   // (cleared four bytes at a time)
     __shared__ u32 digstart[NB];
     __shared__ u32 skeys[TILE];
@@ -1064,8 +1147,27 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
         val[r] = vin[idx];
     }
     u32 before[DPT], all[DPT];   // FEW: keys of a thread's digits in the range's tiles before this one, in all of them
-    if constexpr (FEW) {
-        static_assert(NB >= NT, "a thread's digits lie next to each other");
+    static_assert(!FEW || NB >= NT, "a thread's digits lie next to each other");
+    if constexpr (OWN) {
+        for (int i = threadIdx.x; i < 2 * NB; i += NT) others[i / NB][i % NB] = 0;
+        __syncthreads();
+        for (int64_t k0 = T.pos0; k0 < T.pos1; k0 += TILE) {
+            if (k0 == tile0) continue;
+            u32 item[RS_ITEMS];
+#pragma unroll
+            for (int i = 0; i < RS_ITEMS; ++i) item[i] = (BYTASK ? vin : kin)[min(k0 + i * NT + (int64_t)threadIdx.x, T.pos1 - 1)];
+#pragma unroll
+            for (int i = 0; i < RS_ITEMS; ++i)
+                if (k0 + i * NT + (int64_t)threadIdx.x < T.pos1)
+                    atomicAdd(&others[k0 > tile0][((BYTASK ? rs_task_of(tk, item[i]) : item[i] - T.key_base) >> shift) & (NB - 1)], 1u);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < DPT; ++k) {   // (.. and this one's, below)
+            before[k] = others[0][threadIdx.x * DPT + k];
+            all[k] = before[k] + others[1][threadIdx.x * DPT + k];
+        }
+    } else if constexpr (FEW) {
 #pragma unroll
         for (int k = 0; k < DPT; ++k) before[k] = all[k] = 0;
         for (int t0 = 0; t0 < T.nt; t0 += 8) {
@@ -1121,6 +1223,7 @@ __global__ __launch_bounds__(NT) void radix_scatter_kernel(const u32* kin, const
             t += c;
         }
         total[k] = t;
+        if (OWN) all[k] += t;
         mine += t;
     }
     int tile_count;
@@ -1192,20 +1295,23 @@ size_t radix_hist_words(int64_t n, int extra_tiles) {
 // 2,048 lookups 389 / 377 us, 134,000 of 11 fields 486 / 467, 461,000 of 20 fields (245 tiles) 590 / 573, 614,000 of 40 fields (340)
 // 804 / 796, 899,000 of 26 fields (465) 853 / 856: from there on what the workgroups read again outweighs a launch.
 #define RS_FEW_TILES 384
-template <int BITS, bool BYTASK, int NT, bool FEW>
+// Up to RS_OWN_TILES of them the digit counts' launch goes, too: 4,096 lookups 335 / 324 us a step, 12,000 343 / 332, 25,000 (13 tiles) no difference.
+#define RS_OWN_TILES 8
+template <int BITS, bool BYTASK, int NT, int MODE>
 static void radix_pass_nt(hipStream_t st, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist, int nblk,
                           const TaskOf& tk, const SegTab& seg) {
     u32* scan_tmp = hist + ((size_t)512 * nblk + 63) / 64 * 64;
     const dim3 grid((nblk + 7) / 8 * 8);
-    hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK, NT, FEW>), grid, dim3(NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
-    if (!FEW) launch_scan_u32(st, hist, hist, (int64_t)(1 << BITS) * nblk, scan_tmp, nullptr);
-    hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK, NT, FEW>), grid, dim3(NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
+    if (MODE != RS_OWN)
+        hipLaunchKernelGGL((radix_hist_kernel<BITS, BYTASK, NT, MODE == RS_FEW>), grid, dim3(NT), 0, st, BYTASK ? vi : ki, n, shift, hist, nblk, tk, seg);
+    if (MODE == RS_SCAN) launch_scan_u32(st, hist, hist, (int64_t)(1 << BITS) * nblk, scan_tmp, nullptr);
+    hipLaunchKernelGGL((radix_scatter_kernel<BITS, BYTASK, NT, MODE>), grid, dim3(NT), 0, st, ki, vi, ko, vo, hist, n, shift, nblk, tk, seg);
 }
-template <bool BYTASK, int NT, bool FEW>
+template <bool BYTASK, int NT, int MODE>
 static void radix_pass_width(hipStream_t st, int width, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
                              int nblk, const TaskOf& tk, const SegTab& seg) {
-    if (width <= 8) radix_pass_nt<8, BYTASK, NT, FEW>(st, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
-    else radix_pass_nt<9, BYTASK, NT, FEW>(st, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    if (width <= 8) radix_pass_nt<8, BYTASK, NT, MODE>(st, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else radix_pass_nt<9, BYTASK, NT, MODE>(st, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
 }
 template <bool BYTASK>
 static void radix_pass(hipStream_t st, int width, const u32* ki, const u32* vi, u32* ko, u32* vo, int64_t n, int shift, u32* hist,
@@ -1213,9 +1319,10 @@ static void radix_pass(hipStream_t st, int width, const u32* ki, const u32* vi, 
     // ranges: at most one partly filled tile per range beyond the tiles of the whole list (the tiles past the last range's
     // write nothing into the count table: what the table holds there stands behind every count and moves none's place)
     const int tile = rs_tile_keys(n), nblk = (int)((n + tile - 1) / tile) + seg.n_seg;
-    if (rs_long(n)) radix_pass_width<BYTASK, 512, false>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
-    else if (nblk <= RS_FEW_TILES) radix_pass_width<BYTASK, 256, true>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
-    else radix_pass_width<BYTASK, 256, false>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    if (rs_long(n)) radix_pass_width<BYTASK, 512, RS_SCAN>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else if (n <= RS_OWN_TILES * tile) radix_pass_width<BYTASK, 256, RS_OWN>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else if (nblk <= RS_FEW_TILES) radix_pass_width<BYTASK, 256, RS_FEW>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
+    else radix_pass_width<BYTASK, 256, RS_SCAN>(st, width, ki, vi, ko, vo, n, shift, hist, nblk, tk, seg);
 }
 
 // Returns the number of passes made: after an odd number the result is in (keys_tmp, vals_tmp).

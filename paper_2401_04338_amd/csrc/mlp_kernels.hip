@@ -705,6 +705,7 @@ __global__ void expand_tasks_kernel(ExpandJobs jobs) {
     const ExpandJob& j = jobs.job[blockIdx.y];
     const int g = blockIdx.x;
     const int64_t lo = j.off64 ? j.off64[g] : j.off32[g], hi = j.off64 ? j.off64[g + 1] : j.off32[g + 1];
+    if (g == 0 && blockIdx.y == 0 && (int)threadIdx.x < jobs.clear_words) jobs.clear[threadIdx.x] = 0u;
     for (int64_t s = lo + threadIdx.x; s < hi; s += blockDim.x) j.out[s] = j.first ? j.first[g] + (int32_t)(s - lo) : g;
 }
 void launch_expand_tasks(hipStream_t st, int G, const ExpandJobs& jobs) {
