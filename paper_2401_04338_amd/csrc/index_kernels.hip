@@ -883,9 +883,10 @@ __global__ __launch_bounds__(256) void build_keys_fm_kernel(FieldKeysArgs a) {
     __shared__ int sh[8];
     // The fields of a task on one XCD: their bags lie side by side, and their offsets and indices share lines (dealt over all of them
     // 72 million lookups took 337 us instead of 303).
-    const int per_xcd = (int)(gridDim.x >> 3), id = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if (id >= a.F * a.Tw) return;
-    const int t = id / a.F, f = id - t * a.F, set = blockIdx.y;
+    const int per_xcd = (int)(gridDim.x >> 3);
+    const int64_t id = (int64_t)blockIdx.z * gridDim.x + (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (id >= (int64_t)a.F * a.Tw) return;
+    const int t = (int)(id / a.F), f = (int)(id - (int64_t)t * a.F), set = blockIdx.y;
     const SetView& v = set ? a.qry : a.sup;
     const size_t tf = (size_t)t * a.F + f;
     const u32 n_tf = (set ? a.cnt_q : a.cnt_s)[tf];
@@ -995,7 +996,8 @@ void launch_build_keys_by_field(hipStream_t st, FieldKeysArgs a, u32* tables, u3
     }
     a.key_pos = key_pos;
     a.tot = tot;
-    const dim3 grid((unsigned)(((int64_t)a.F * a.Tw + 7) / 8 * 8), 2);
+    const int64_t tf = ((int64_t)a.F * a.Tw + 7) / 8 * 8, nx = std::min<int64_t>(tf, 1 << 22);   // (a launch's threads along x stay below 2^32)
+    const dim3 grid((unsigned)nx, 2, (unsigned)((tf + nx - 1) / nx));
     if (max_bag <= BKF_BAG) hipLaunchKernelGGL(build_keys_fm_kernel<true>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(build_keys_fm_kernel<false>, grid, dim3(256), 0, st, a);
 }
