@@ -77,8 +77,10 @@ __device__ __forceinline__ void pc_barrier() {
 }
 
 // HBITS: log2 of the hot rows of a batch; a lookup's 16 bits hold its bag in the lower 15 - HBITS
+// (at least four waves a SIMD: with registers to spare the four-wave workgroups of small tasks took 189 each, two workgroups a compute
+// unit where the LDS holds four: 700 tasks of a median 32 rows 835 -> 463 us, 64 tasks of 128 + 128 rows 47 -> 32)
 template <int NT, int HBITS>
-__global__ __launch_bounds__(NT) void pair_count_kernel(PairCountArgs a) {
+__global__ __launch_bounds__(NT, 4) void pair_count_kernel(PairCountArgs a) {
     constexpr int HB = 1 << HBITS, HBS = pc_stride(HB), BAG_BITS = 15 - HBITS, BAG_MASK = (1 << BAG_BITS) - 1;
     extern __shared__ __attribute__((aligned(16))) u32 pc_lds[];
     __shared__ int sh_ncold, sh_wave_hot[2][NT / 64];
