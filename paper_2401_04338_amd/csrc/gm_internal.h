@@ -211,11 +211,14 @@ struct PairCountArgs {
     uint8_t* mat;
     int want_ss, want_sq;
     int lds_bytes, n_max, max_tile_rows;      // set by the launcher
+    const int32_t* order;                     // set by the launcher: the launch's tasks
     int cls, small_n;                         // set by the launcher: 0 all, 1 only small (task, field)s, 2 only the others
     u32* task_path;                           // [Tw] only tasks flagged 1 are counted; cleared when a count exceeds 254
     u32* status;
 };
-void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int max_rows, int min_rows, int max_tile_rows);
+// order, rows: the tasks by falling size, and their sizes (samples of the larger set); max_tf: the most lookups any (task, field) of the
+// wave has in one set; max_bag: the longest bag
+void launch_pair_count(hipStream_t st, PairCountArgs a, const int32_t* order, const std::vector<int>& rows, int max_tf, int max_bag, int max_tile_rows);
 struct PairHopOut {
     int enabled;
     const int64_t* mat_off;                   // [Tw]

@@ -317,6 +317,8 @@ struct WaveBufs {
     int64_t *pair_off_ss, *pair_off_qs, *pair_off_sq;
     int32_t *hop_small = nullptr, *hop_tiles[3] = {nullptr, nullptr, nullptr};   // the hops' work lists (HopPlan)
     int hop_longest[3] = {0, 0, 0}, hop_run = 1, n_hop_small = 0;
+    int32_t* count_order = nullptr;   // the tasks whose pairs are counted, by falling size
+    std::vector<int> count_rows;      // their sizes: samples of the larger set
     u32* task_path;   // [Tw] 1: pair-count path, 0: sparse kernel (the counting kernel clears it on overflow)
     // table-shaped sparse output only: the wave's own gradient buffer (support rows, then query rows) and sort
     float* GX = nullptr;
@@ -401,6 +403,7 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.pair_off_ss = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_qs = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
     w.pair_off_sq = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
+    w.count_order = d.pair ? ar.get<int32_t>(d.Tw + 1) : nullptr;
     const int fx = hop_slices(F, c->D);
     if (d.pair) {
         const int64_t es = hop_entries(d.hop_tiles_s, fx), eq = hop_entries(d.hop_tiles_q, fx);
@@ -1925,6 +1928,16 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
         std::vector<HopTask> tasks;
         for (int t = 0; t < d.Tw; ++t)
             if (path[t]) tasks.push_back(HopTask{t, re_s[t + 1] - re_s[t], re_q[t + 1] - re_q[t]});
+        std::vector<HopTask> by_size = tasks;
+        auto size = [](const HopTask& x) { return std::max(x.ns, x.nq); };
+        std::stable_sort(by_size.begin(), by_size.end(), [&](const HopTask& a, const HopTask& b) { return size(a) > size(b); });
+        std::vector<int32_t> order;
+        w.count_rows.clear();
+        for (const HopTask& x : by_size) {
+            order.push_back(x.t);
+            w.count_rows.push_back(size(x));
+        }
+        up.put(w.count_order, order);
         const HopPlan plan = hop_plan(tasks, hop_slices(c->F, c->D));
         w.n_hop_small = (int)plan.small.size();
         w.hop_run = plan.run;
@@ -1951,7 +1964,6 @@ static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& 
                        int max_bag, int max_tf, bool allow_side, bool& pair, bool& any_sparse, bool& pairs_on_side) {
     hipStream_t st = c->stream;
     const int F = c->F, Tw = wp.t1 - wp.t0;
-    const gm_set *sup = B.sup, *qry = B.qry;
     pair = d.pair && tf_cap <= PAIR_MAX_CAP && max_bag <= PAIR_MAX_BAG;
     any_sparse = d.any_sparse || (d.pair && !pair);
     pairs_on_side = false;
@@ -1977,15 +1989,7 @@ static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& 
     }
     {
         Prof p(c, "pair_count", 8.0 * (d.nnz_s + d.nnz_q) + (double)d.pair_bytes, 0, pst, true);
-        int max_rows = 0, min_rows = 1 << 30;
-        for (int t = wp.t0; t < wp.t1; ++t)
-            if (task_pair_ok(c, B, t, K)) {
-                const int r = (int)std::max(sup->task_offsets[t + 1] - sup->task_offsets[t],
-                                            qry->task_offsets[t + 1] - qry->task_offsets[t]);
-                max_rows = std::max(max_rows, r);
-                min_rows = std::min(min_rows, r);
-            }
-        launch_pair_count(pst, pa, Tw, max_tf, max_rows, min_rows, c->pair_tile_rows);
+        launch_pair_count(pst, pa, w.count_order, w.count_rows, max_tf, max_bag, c->pair_tile_rows);
     }
     if (pairs_on_side) {
         HIPCHK(c, hipEventRecord(c->ev_pairs, c->side));

@@ -84,10 +84,9 @@ __global__ __launch_bounds__(NT, 4) void pair_count_kernel(PairCountArgs a) {
     constexpr int HB = 1 << HBITS, HBS = pc_stride(HB), BAG_BITS = 15 - HBITS, BAG_MASK = (1 << BAG_BITS) - 1;
     extern __shared__ __attribute__((aligned(16))) u32 pc_lds[];
     __shared__ int sh_ncold, sh_wave_hot[2][NT / 64];
-    const int f = blockIdx.x, t = blockIdx.y;
-    const bool qs = blockIdx.z == 1;   // 0: support x support, 1: query x support (and its transpose)
-    if (!qs && !a.want_ss) return;
-    if (!a.task_path[t]) return;
+    const int f = blockIdx.x, t = a.order[blockIdx.y];
+    const bool qs = blockIdx.z == 0;   // query x support (and its transpose), 1: support x support
+    if (!a.task_path[t]) return;   // (another field's counts did not fit)
     const size_t tf = (size_t)t * a.F + f;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, ln = lane & 31, h = lane >> 5;
     const int ns = a.real_off_s[t + 1] - a.real_off_s[t], nq = a.real_off_q[t + 1] - a.real_off_q[t];
@@ -370,8 +369,6 @@ __global__ __launch_bounds__(NT, 4) void pair_count_kernel(PairCountArgs a) {
     }
 }
 
-// max_tf: the most lookups any (task, field) of the wave has in one set; max_rows: the most samples any
-// counted task has in one set
 // LDS of a launch: what the largest (task, field) needs for one tile of as many rows as NT threads take
 static size_t pc_lds_need(int NT, int HBITS, int n_max, int max_rows, int max_tile_rows) {
     const int P = pad64(max_rows > 0 ? max_rows : 1);
@@ -380,40 +377,62 @@ static size_t pc_lds_need(int NT, int HBITS, int n_max, int max_rows, int max_ti
 }
 static int pc_n_max(int max_tf) { return (max_tf + 7) / 8 * 8 + 8; }
 
+// n_tasks tasks of a.order, of at most max_rows samples a set and max_tf lookups a (task, field) and set
 template <int NT, int HBITS>
-static void launch_pair_count_nt(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int max_rows) {
+static void launch_pair_count_nt(hipStream_t st, PairCountArgs a, int n_tasks, int max_tf, int max_rows) {
     a.n_max = pc_n_max(max_tf);
     const size_t need = std::min<size_t>(pc_lds_need(NT, HBITS, a.n_max, max_rows, a.max_tile_rows), PAIR_LDS_BYTES);
     a.lds_bytes = (int)(need / 16 * 16);
     auto kern = pair_count_kernel<NT, HBITS>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PAIR_LDS_BYTES);
-    hipLaunchKernelGGL(kern, dim3(a.F, Tw, 2), dim3(NT), (size_t)a.lds_bytes, st, a);
+    hipLaunchKernelGGL(kern, dim3(a.F, n_tasks, a.want_ss ? 2 : 1), dim3(NT), (size_t)a.lds_bytes, st, a);
 }
 
-// max_rows / min_rows: the most / fewest samples any counted task has in one set (the larger of its two sets)
-void launch_pair_count(hipStream_t st, PairCountArgs a, int Tw, int max_tf, int max_rows, int min_rows, int max_tile_rows) {
-    if (Tw <= 0 || a.F <= 0) return;
+// Uneven tasks in up to three launches, over the tasks that each can hold: a workgroup with nothing to do still costs its compute unit
+// (or half of it) the latency of finding out, and a single task of more than 512 rows would send all that share its launch through sixteen
+// waves and batches of 32 hot rows (its bags' numbers take ten of a lookup's 16 bits).  700 tasks of a median 32 rows x
+// 40 fields: all but the small ones 904 us in one launch over all tasks, 421 + 210 so (421: the one or two of more than 512 rows, fewer
+// workgroups than compute units).
+void launch_pair_count(hipStream_t st, PairCountArgs a, const int32_t* order, const std::vector<int>& rows, int max_tf, int max_bag, int max_tile_rows) {
+    if (rows.empty() || a.F <= 0) return;
     a.max_tile_rows = max_tile_rows > 0 ? (max_tile_rows + 31) / 32 * 32 : 1 << 20;
     a.small_n = PC_SMALL_N;
-    // Eight waves where a compute unit's LDS then holds two workgroups, whose phases hide each other's latency; else sixteen,
-    // which take twice the rows a tile.  A single task of more than 512 rows sends all that share its launch (those of more than
-    // PC_SMALL_ROWS) through sixteen waves and batches of 32 hot rows: its bags' numbers take ten of a lookup's 16 bits.
-    auto larger = [&]() {
-        if (max_rows > 512) launch_pair_count_nt<1024, 5>(st, a, Tw, max_tf, max_rows);   // (a bag's number takes ten bits)
-        else if (pc_lds_need(512, 6, pc_n_max(max_tf), max_rows, a.max_tile_rows) <= PC_TWO_LDS) launch_pair_count_nt<512, 6>(st, a, Tw, max_tf, max_rows);
-        else launch_pair_count_nt<1024, 6>(st, a, Tw, max_tf, max_rows);
+    const int n = (int)rows.size(), max_rows = rows.front(), min_rows = rows.back();
+    auto above = [&](int size) {   // tasks of more rows
+        return (int)(std::partition_point(rows.begin(), rows.end(), [&](int r) { return r > size; }) - rows.begin());
     };
+    // Eight waves where a compute unit's LDS then holds two workgroups, whose phases hide each other's latency; else sixteen,
+    // which take twice the rows a tile.
+    auto launch = [&](int t0, int t1) {
+        if (t0 >= t1) return;
+        a.order = order + t0;
+        const int most = rows[t0];
+        // (as long a list as any, for its room for records, where that takes nothing else)
+        const int tf = pc_lds_need(512, 6, pc_n_max(max_tf), most, a.max_tile_rows) <= PC_TWO_LDS ? max_tf : (int)std::min<int64_t>(max_tf, (int64_t)most * max_bag);
+        if (most > 512) launch_pair_count_nt<1024, 5>(st, a, t1 - t0, tf, most);   // (a bag's number takes ten bits)
+        else if (pc_lds_need(512, 6, pc_n_max(tf), most, a.max_tile_rows) <= PC_TWO_LDS) launch_pair_count_nt<512, 6>(st, a, t1 - t0, tf, most);
+        else launch_pair_count_nt<1024, 6>(st, a, t1 - t0, tf, most);
+    };
+    a.order = order;
     if (max_rows <= PC_SMALL_ROWS && max_tf <= PC_SMALL_N) {   // every task is small
         a.cls = 0;
-        launch_pair_count_nt<256, 6>(st, a, Tw, max_tf, max_rows);
-    } else if (max_rows > 2 * PC_SMALL_ROWS && min_rows <= PC_SMALL_ROWS && (int64_t)Tw * a.F >= 32) {   // uneven: two launches, each workgroup checks its class
+        launch_pair_count_nt<256, 6>(st, a, n, max_tf, max_rows);
+    } else if (max_rows > 2 * PC_SMALL_ROWS && min_rows <= PC_SMALL_ROWS && (int64_t)n * a.F >= 32) {   // uneven: each workgroup of the first two checks its class
+        const int large = above(512), mid = above(PC_SMALL_ROWS);
         a.cls = 1;
-        launch_pair_count_nt<256, 6>(st, a, Tw, max_tf < PC_SMALL_N ? max_tf : PC_SMALL_N, PC_SMALL_ROWS);
+        a.order = order + mid;
+        launch_pair_count_nt<256, 6>(st, a, n - mid, std::min<int>(max_tf, PC_SMALL_N), PC_SMALL_ROWS);
         a.cls = 2;
-        larger();
-    } else {
+        // (tasks of few rows but long bags may have (task, field)s that are not small)
+        const int end = above(std::min<int>(PC_SMALL_ROWS, PC_SMALL_N / std::max(max_bag, 1)));
+        launch(large, end);
         a.cls = 0;
-        larger();
+        launch(0, large);
+    } else {
+        const int large = (int64_t)n * a.F >= 32 ? above(512) : 0;
+        a.cls = 0;
+        launch(0, large);
+        launch(large, n);
     }
 }
 
