@@ -295,7 +295,9 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               "coarse_groups"), a wave with a bag or a (task, field) beyond the pair matrices' limits takes the other
  *               row arithmetic whole ("row_path"), and with emb_grad_table every wave adds its own sums to a row.  (A few
  *               tasks of 513 to 1,024 samples may take pair matrices too, which the batch alone decides; only where the
- *               workspace could not hold one of them with its matrices, run by itself, do they take the other row arithmetic.)
+ *               workspace could not hold one of them with its matrices, run by itself, do they take the other row arithmetic.  And
+ *               where it could not hold one task's activations and row gradients of all inner steps, a first-order call in
+ *               bf16 keeps neither: "theta_from_meta" 0, and the query rows' update step by step.)
  *   "pair_tile_rows": most out-rows of a pair-count matrix that the counting kernel holds in LDS at a time
  *               (0 = as many as fit); identical results.
  * Unknown keys or values give GM_ERR_ARG. */

@@ -454,7 +454,7 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.loss_q = ar.get<float>(d.Pq + 1);
     const bool factors = d.factor_ld > 0;
     w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
-    w.vsum = Theta{ar.get<float>((int64_t)most_runs(c) * c->n_theta), c->n_theta, nullptr, 0};
+    w.vsum = Theta{ar.get<float>((int64_t)std::min(most_runs(c), std::max(d.Tw, 1)) * c->n_theta), c->n_theta, nullptr, 0};   // (a run has a task at least)
     if (!second) w.v.b = nullptr;  // the direction is a GEMM operand only in the second-order pass
     w.Xs_scratch = Act();
     const bool keep = second || d.from_meta;   // every step's activations and deltas
@@ -1413,7 +1413,7 @@ struct Batch {  // host-side description of one call
     std::vector<int64_t> ls, lq;          // lookup offsets per task (filled when several waves are needed)
     bool table = false;                   // table-shaped sparse output: every wave sorts and reduces its own lookups
     int pair_rows = PAIR_ROWS;            // a task of at most so many rows in each set goes through pair-count matrices
-    bool fp32_master = false;             // first order: no room for every step's activations (theta_from_meta)
+    bool tight = false;                   // first order: no room for every step's activations (theta_from_meta) or gradients (query_sum)
     BatchBufs b;
     HostImages images;
 };
@@ -1750,7 +1750,7 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
     WaveDims d;
     d.table = B.table;
     d.factor_ld = factor_rows(c, B, bm, K, order);
-    d.from_meta = !B.fp32_master && theta_from_meta(c, B.T, B.poff_s[B.T], K, order);
+    d.from_meta = !B.tight && theta_from_meta(c, B.T, B.poff_s[B.T], K, order);
     for (int t = p.t0; t < p.t1; ++t) {
         if (task_pair_ok(c, B, t, K)) {
             d.pair = true;
@@ -1766,6 +1766,7 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
         d.pair_sq = order == 2;
         d.pair_bytes = pair_layout(c, B, p, K, d.pair_ss, d.pair_sq, nullptr, nullptr, nullptr, nullptr);
         d.query_sum = query_sum(c, K);
+        if (B.tight && d.query_sum > 2) d.query_sum = 0;   // (two steps' need no buffer of their own)
     }
     d.Tw = p.t1 - p.t0;
     d.Ss = p.s1 - p.s0; d.Sq = p.q1 - p.q0; d.Ps = p.ps1 - p.ps0; d.Pq = p.pq1 - p.pq0;
@@ -1851,8 +1852,8 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         }
         if (fits) return GM_OK;
         if (per == 1) {
-            if (!B.fp32_master && order == 1 && theta_from_meta(c, T, B.poff_s[T], K, order)) {
-                B.fp32_master = true;   // (the steps' activations of one task do not fit)
+            if (!B.tight && order == 1 && (theta_from_meta(c, T, B.poff_s[T], K, order) || query_sum(c, K) > 2)) {
+                B.tight = true;
                 n_waves = fewest;
                 continue;
             }

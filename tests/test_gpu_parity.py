@@ -901,6 +901,50 @@ def test_inner_step_weights_from_the_meta_parameters(gm, K):
     ctx.close()
 
 
+@pytest.mark.parametrize("K", [2, 4])
+def test_first_order_weights_from_the_meta_parameters(gm, K):
+    """The same without a chain: with small tasks the default, the fp32 master for comparison."""
+    cfg = SMALL.with_(n_tasks=5, n_support=70, n_query=40, n_fields=4, emb_dim=32, rows_per_field=400, bag_max=5,
+                      layer_dims=(4 * 32 + 13, 96, 48, 1), mlp_dtype=1, inner_lr=0.05)
+    sup, qry, params = _inputs(cfg)
+    ctx = gm.from_config(cfg, workspace_bytes=1 << 30)
+    out, _ = _compare_step(cfg, ctx, sup, qry, params, K, 1, TOL_BF16, f"K={K}, weights from the meta parameters", operand="bf16")
+    a = [x.clone() for x in out["dW"]]
+    ctx.configure("theta_from_meta", 0)
+    out, _ = _compare_step(cfg, ctx, sup, qry, params, K, 1, TOL_BF16, f"K={K}, per-task fp32 master", operand="bf16")
+    for x, y in zip(out["dW"], a):
+        assert max(rel_err(x.cpu().numpy(), y.cpu().numpy())) <= 5e-3
+    ctx.close()
+
+
+def test_first_order_in_any_workspace(gm):
+    """A workspace that does not hold one task's activations of all steps takes the fp32 master, down to what that needs."""
+    from paper_2401_04338_amd.binding import GMetaError
+    cfg = SMALL.with_(n_tasks=2, n_support=340, n_query=40, n_fields=6, emb_dim=64, rows_per_field=400, bag_max=3, layer_dims=(6 * 64 + 13, 256, 64, 1),
+                      mlp_dtype=1, inner_lr=0.05)
+    sup, qry, params = _inputs(cfg)
+    dev = torch.device("cuda", 0)
+    s, q, p = _to_dev(sup, dev), _to_dev(qry, dev), _params_dev(params, dev)
+    got, least = [], []
+    for from_meta in (1, 0):
+        for kib in range(20 << 10, 0, -256):
+            ctx = gm.from_config(cfg, workspace_bytes=kib << 10)
+            ctx.configure("theta_from_meta", from_meta)
+            try:
+                out = ctx.meta_step(s, q, p, cfg.inner_lr, 3, 1)
+            except GMetaError as e:
+                assert e.code == -4, e
+                break
+            finally:
+                ctx.close()
+            got.append([x.clone() for x in out["dW"]])
+        least.append(kib)
+    assert least[0] == least[1]
+    for g in got:
+        for x, y in zip(g, got[0]):
+            assert float((x - y).norm()) <= 5e-3 * float(y.norm())
+
+
 @pytest.mark.parametrize("runs", [1, 7, 32])
 def test_other_numbers_of_task_runs(gm, runs):
     """gm_configure("coarse_groups"): the products only summed over tasks taken over another number of runs of tasks --
