@@ -1,6 +1,6 @@
 """The check of the indices (all that stands before the gathers) finds one bad index wherever it lies.  Tables of one size:
-a workgroup's threads read four indices a trip, `step` = 256 x (workgroups of the task) apart, so the places are the ends of
-each of the four, of the trip after and of the list.  Tables of different sizes: bag by bag.  gm_index_prep checks and does
+a workgroup's threads read eight indices a trip, `step` = 1024 x (workgroups of the (task, set)) apart, so the places are the ends of
+some of the eight, of the trip after and of the list (and of trips of smaller workgroups).  Tables of different sizes: bag by bag.  gm_index_prep checks and does
 not gather."""
 from types import SimpleNamespace
 
@@ -22,7 +22,7 @@ def _set(samples, bag):
 
 
 @pytest.mark.parametrize("uneven", [0, 1])
-@pytest.mark.parametrize("samples,bag,split", [(100, 6, 1), (300, 5, 2), (700, 9, 5)])   # (split: bags of both sets / 512)
+@pytest.mark.parametrize("samples,bag,split", [(100, 6, 1), (300, 5, 2), (700, 9, 5)])   # (step = 256 x split)
 def test_one_bad_index(gm, samples, bag, split, uneven):  # noqa: F811
     from paper_2401_04338_amd import GMetaError
     step, n = 256 * split, samples * F * bag
@@ -60,6 +60,30 @@ def test_one_bad_index_beside_small_tasks(gm, uneven):  # noqa: F811
         for at in (0, 19 * per, 20 * per, 20 * per + 1280, 20 * per + 4 * 1280 - 1, 720 * per - 1, 720 * per, s.nnz - 1):
             good = int(s.indices[at])
             s.indices[at] = -1
+            with pytest.raises(GMetaError) as e:
+                ctx.index_prep(*sets)
+            assert e.value.code == -2, at
+            s.indices[at] = good
+    ctx.index_prep(*sets)
+    ctx.close()
+
+
+@pytest.mark.parametrize("uneven", [0, 1])
+@pytest.mark.parametrize("samples,bag,split", [(400, 25, 1), (700, 14, 2), (1000, 16, 3)])
+def test_one_bad_index_in_a_larger_task(gm, samples, bag, split, uneven):  # noqa: F811
+    """1,024 threads, eight indices a trip (`step` apart), a workgroup a (task, set) or, from 2,048 bags of both sets on, several."""
+    from paper_2401_04338_amd import GMetaError
+    step, n = 1024 * split, samples * F * bag
+    assert split == max(1, 2 * samples * F // 1024) and n > 8 * step
+    ctx = gm(F, [ROWS, ROWS + uneven], 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 26)
+    sets = [_set(samples, bag), _set(samples, bag)]
+    ctx.index_prep(*sets)
+    for s in sets:
+        for at in sorted({k * step + d for k in (0, 1, 7, 8) for d in (-1, 0, 1)} - {-1} | {n - 1}):
+            if at >= n:
+                continue
+            good = int(s.indices[at])
+            s.indices[at] = ROWS + uneven
             with pytest.raises(GMetaError) as e:
                 ctx.index_prep(*sets)
             assert e.value.code == -2, at

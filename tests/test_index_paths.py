@@ -154,3 +154,70 @@ def test_few_tiles(gm, n, rows):
     """Lists of one tile, of several, and around the number of tiles up to which a scatter adds up the digit counts itself (384;
     two of them for the two fields' ranges where the fields are ordered one by one)."""
     test_long_lists(gm, n - (1 << 20), rows)
+
+
+@pytest.mark.parametrize("rows", [300, 200_000])
+@pytest.mark.parametrize("n", [2 * 2048, 5 * 2048 + 7, 8 * 2048, 8 * 2048 + 1, 32768, 32769])
+def test_short_lists(gm, n, rows):
+    """Lists of up to 8 tiles, whose scatters count the other tiles' digits themselves, and one key more; segments counted by one
+    workgroup, up to 32768 keys, and by several."""
+    test_long_lists(gm, n - (1 << 20), rows)
+
+
+def _lists(lens, F, samples, rows, seed, dev="cuda"):
+    """A set of len(lens) / F tasks whose (task, field) i has lens[i] lookups, cut into `samples` bags at random."""
+    gen = torch.Generator().manual_seed(seed)
+    T = len(lens) // F
+    bags = torch.zeros(T, samples, F, dtype=torch.int64)
+    for i, n in enumerate(lens):
+        bags[i // F, :, i % F] = torch.bincount(torch.randint(0, samples, (n,), generator=gen), minlength=samples)
+    off = torch.cat([torch.zeros(1, dtype=torch.int64), bags.flatten().cumsum(0)])
+    n = int(off[-1])
+    return SimpleNamespace(task_offsets=np.arange(T + 1, dtype=np.int64) * samples, bag_offsets=off.to(dev), dense=torch.zeros(T * samples, 1, device=dev),
+                           indices=(torch.rand(n, generator=gen) ** 3 * rows).int().clamp(max=rows - 1).to(dev), labels=torch.zeros(T * samples, device=dev))
+
+
+def _same_dictionaries(gm, sup, qry, F, rows):
+    got = []
+    for path in (1, 2):
+        ctx = gm(F, [rows] * F, 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 30)
+        ctx.configure("index_path", path)
+        got.append({k: v.clone() for k, v in ctx.index_prep(sup, qry).items() if torch.is_tensor(v)})
+        ctx.close()
+    assert len(got[0]) >= 6
+    for k in got[0]:
+        assert torch.equal(got[0][k], got[1][k]), k
+
+
+@pytest.mark.parametrize("rows", [1, 7, 3000])      # one run over all pieces, long ones across the waves' and the pieces' borders, short ones
+@pytest.mark.parametrize("lens", [[1, 63, 64, 65, 255, 256, 257, 511, 512, 513, 0, 1025], [1023, 1024, 1025, 2047, 2048, 2049, 3, 0, 1, 2, 700, 64],
+                                  [4095, 4096, 4097, 8191, 8192, 8193, 1, 0, 15000, 64]], ids=["rounds", "pieces_of_1024", "pieces_of_4096"])
+def test_join_pieces(gm, lens, rows):
+    """(task, field)s that end at, before and behind a wave's round and a workgroup's piece of the join, in each of its three forms (by the
+    lists' mean length), with support and query lookups in every proportion."""
+    sup = [n * (i % 5) // 4 for i, n in enumerate(lens)]
+    _same_dictionaries(gm, _lists(sup, 1, 9, rows, 1), _lists([n - s for n, s in zip(lens, sup)], 1, 11, rows, 2), 1, rows)
+
+
+@pytest.mark.parametrize("longest", [63, 64, 65, 700])
+def test_keys_of_short_and_long_bags(gm, longest):
+    """More bags than are staged at a time and more lookups than are written out at a time; one bag of the longest for which they are, one longer."""
+    gen = torch.Generator().manual_seed(longest)
+    samples, F, rows = 1100, 2, 500
+    sets = []
+    for _ in range(2):
+        lens = torch.randint(0, 16, (2, samples, F), generator=gen)
+        lens[0, 5, 1] = lens[1, samples - 1, 0] = longest
+        off = torch.cat([torch.zeros(1, dtype=torch.int64), lens.flatten().cumsum(0)])
+        n = int(off[-1])
+        sets.append(SimpleNamespace(task_offsets=np.arange(3, dtype=np.int64) * samples, bag_offsets=off.cuda(), dense=torch.zeros(2 * samples, 1, device="cuda"),
+                                    indices=torch.randint(0, rows, (n,), generator=gen, dtype=torch.int32).cuda(), labels=torch.zeros(2 * samples, device="cuda")))
+    _same_dictionaries(gm, *sets, F, rows)
+
+
+@pytest.mark.parametrize("tasks,fields", [(1, 1), (64, 3), (65, 3), (3, 300), (2048, 2), (1366, 3), (4097, 1)])
+def test_numbers_of_task_fields(gm, tasks, fields):
+    """Up to 4096 (task, field)s, whose counts one workgroup scans, and more; tasks up to a wave's lanes and beyond, more fields than waves."""
+    gen = torch.Generator().manual_seed(tasks)
+    sup, qry = (_lists(torch.randint(0, 6, (tasks * fields,), generator=gen).tolist(), fields, 2, 40, w) for w in (3, 4))
+    _same_dictionaries(gm, sup, qry, fields, 40)

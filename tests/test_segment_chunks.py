@@ -110,3 +110,23 @@ def test_chunks_inside_long_segments(gm, dim, fields, lookups, mode):  # noqa: F
     assert abs(scale * T - 1) < 1e-4 or abs(scale - 1) < 1e-4    # (a mean or a sum over the tasks)
     terms = 64 + torch.bincount(row, minlength=fields * R).max().item() / 64 + 8 * dim * fields   # (.. and the logit's own terms)
     assert bool(((got / scale - want).abs() <= terms * 2.0 ** -24 * size + 1e-12).all())
+
+
+@pytest.mark.parametrize("dim,tasks", [(16, 4), (64, 40)])
+@pytest.mark.parametrize("K,order", [(0, 2), (2, 1)])
+def test_no_query_rows(gm, dim, tasks, K, order):  # noqa: F811
+    """Without a chain the support set's lookups have zero gradients, which are not read; with nothing else in the batch they are written."""
+    cfg = small_cfg(n_tasks=tasks, n_fields=2, emb_dim=dim, rows_per_field=50, n_support=30, n_query=4, layer_dims=(2 * dim + 5, 8, 1))
+    sup, _, params = _inputs(cfg, emb_std=0.3)
+    ctx = gm.from_config(cfg, workspace_bytes=1 << 29)
+    ds, dp = _to_dev(sup, ctx.device), _params_dev(params, ctx.device)
+    none = SimpleNamespace(task_offsets=np.zeros(tasks + 1, dtype=np.int64), bag_offsets=torch.zeros(1, dtype=torch.int64, device="cuda"), labels=ds.labels[:0],
+                           indices=ds.indices[:0], dense=ds.dense[:0])
+    for table in (None, torch.ones_like(dp.emb)):
+        out = ctx.meta_step(ds, none, dp, cfg.inner_lr, K, order, emb_grad_table=table)
+        if table is None:
+            n = int(out["n_emb_rows"].item())
+            assert n > 0 and not out["emb_grad"][:n].any()
+        else:
+            assert torch.equal(table, torch.ones_like(table))
+    ctx.close()
