@@ -33,7 +33,7 @@ FAMILIES = {
     # them off the ordered list), the passes by row key to the ordering of the lookups by row
     "tf_sort": r"tf_sort_kernel|tf_join_kernel|radix_(hist|scatter)_kernel<\d+, true",
     "tf_count": r"tf_count_kernel",
-    "global_sort": r"build_keys_kernel|build_keys_fm_kernel|field_(offsets|table)_kernel|radix_(hist|scatter)_kernel<\d+, false|seg_flags_kernel|seg_emit_kernel",
+    "global_sort": r"build_keys_kernel|build_keys_fm_kernel|field_(offsets|table|prepare)_kernel|radix_(hist|scatter)_kernel<\d+, false|seg_(count|scan_one|emit)_kernel",
     "task_colsum": r"task_colsum_(bf16|f32)_kernel",
     "reduce_tasks": r"reduce_tasks_kernel",
     "axpy_gx": r"axpy_kernel",
