@@ -81,7 +81,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
     };
     const RowBuffer mask = buffer(a.mask, has_mask, 0, r0, a.ld_mask, 2);
     const RowBuffer cin = buffer(a.Cin, has_cin, (int64_t)g * a.gCin, 0, a.ldcin, 4);
-    const RowBuffer cacc = buffer(a.Cacc, has_acc, r0 * a.rCacc, 0, a.ldcacc, 4);
+    const RowBuffer cacc = buffer(a.Cacc, has_acc, r0 * a.rCacc, 0, a.ldcacc, 4), csum = buffer(a.Cold ? a.Cold : a.Cacc, has_acc, r0 * a.rCacc, 0, a.ldcacc, 4);
+    const float sum_scale = a.Cold ? a.cacc : 1.f;
     const RowBuffer cf = buffer(a.Cf, fl.cf, (int64_t)g * a.gCf + r0 * a.rCf, 0, a.ldcf, 4);
     const RowBuffer cb = buffer(a.Cb, fl.cb, (int64_t)g * a.gCb + r0 * a.rCb + (fl.epi == EPI_SPLIT ? (int64_t)blockIdx.y * a.ext.slot : 0), 0, a.ldcb, 2);
     float4 bn = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -97,7 +98,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
             const int r = i * 32 + it * RPI;
             if (has_mask) mk[it] = mask.load2(r);
             if (has_cin) ci[it] = cin.load4(r);
-            else if (read_acc) ci[it] = cacc.load4(r);
+            else if (read_acc) ci[it] = csum.load4(r);
             else ci[it] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
     };
@@ -138,7 +139,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmBArgs& a, f32x16 (&acc)[
             if (fl.cf) cf.store<STREAM>(r, x);
             if (has_acc) {
                 const float4 ci = ci_all[i & 1][it];
-                cacc.store(r, make_float4(fmaf(a.cacc, x.x, ci.x), fmaf(a.cacc, x.y, ci.y), fmaf(a.cacc, x.z, ci.z), fmaf(a.cacc, x.w, ci.w)));
+                cacc.store(r, make_float4(fmaf(a.cacc, x.x, sum_scale * ci.x), fmaf(a.cacc, x.y, sum_scale * ci.y), fmaf(a.cacc, x.z, sum_scale * ci.z), fmaf(a.cacc, x.w, sum_scale * ci.w)));
             }
             if (fl.epi == EPI_SPLIT) {
                 const float c = a.ext.c[blockIdx.y];

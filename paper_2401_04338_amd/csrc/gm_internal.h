@@ -360,6 +360,7 @@ struct GemmBArgs {
     bf16_t* Cb; int64_t ldcb, gCb, rCb;    // bf16 output
     float* Cacc; int64_t ldcacc, rCacc; float cacc;  // Cacc[(r0 + m)*ldcacc + n] += cacc * value (not with EPI_AXPBY + Cin)
     int cacc_init;                                   // 1: Cacc is not read, = cacc * value (first term of a sum)
+    const float* Cold;                               // not null: = cacc * Cold + cacc * value, Cold as Cacc lies (may be Cf)
     int most_n;                            // N -1 (EPI_SPLIT): most columns of a product
     GemmExt ext;                           // (64-row tiles only)
 };
