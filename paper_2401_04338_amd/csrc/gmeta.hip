@@ -1963,7 +1963,7 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
 // kernel's limits; a task with a count that does not fit a byte is handed to the sparse kernel (its flag is cleared on
 // the device).  allow_side: the counting may run on the second stream (gm_configure "overlap_pairs"); the caller then
 // joins it before the first row hop.
-static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& w, const WaveDims& d, int K, int tf_cap,
+static int count_pairs(gm_ctx* c, const Batch& B, const WavePlan& wp, WaveBufs& w, const WaveDims& d, int tf_cap,
                        int max_bag, int max_tf, bool allow_side, bool& pair, bool& any_sparse, bool& pairs_on_side) {
     hipStream_t st = c->stream;
     const int F = c->F, Tw = wp.t1 - wp.t0;
@@ -2133,7 +2133,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             pair = pre->pair; any_sparse = pre->any_sparse;
             if (d.mat_apart) {
                 launch_fill_u32(st, c->d_status, ST_WORDS, 0);
-                if ((rc = count_pairs(c, B, wp, w, d, K, tf_cap, max_bag, max_tf, false, pair, any_sparse, pairs_on_side))) return rc;
+                if ((rc = count_pairs(c, B, wp, w, d, tf_cap, max_bag, max_tf, false, pair, any_sparse, pairs_on_side))) return rc;
             }
         } else {
             if ((rc = setup_wave(c, B, wp, bm, K, w, d, gs, gq))) return rc;
@@ -2152,7 +2152,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
             rc = run_index_wave(c, B, wp, w, &tf_cap, &max_bag, &max_tf, &jr);
             if (rc != GM_OK) return rc;
             if (jr.used) { ordered = true; enc = jr.enc; }
-            if ((rc = count_pairs(c, B, wp, w, d, K, tf_cap, max_bag, max_tf, true, pair, any_sparse, pairs_on_side))) return rc;
+            if ((rc = count_pairs(c, B, wp, w, d, tf_cap, max_bag, max_tf, true, pair, any_sparse, pairs_on_side))) return rc;
             if (pairs_on_side) side.active = true;
         }
         // joins the counting on the side stream: the host learns whether a task fell back to the sparse kernel, the main
@@ -2758,7 +2758,7 @@ static int prepare_batch(gm_ctx* c, Arena& ia, int32_t T, const gm_set* sup, con
         if ((rc = run_index_wave(c, B, P.wp, P.w, &P.tf_cap, &P.max_bag, &P.max_tf, &jr))) return rc;
         if (jr.used) P.enc = jr.enc;
         bool on_side = false;
-        if (!mat_apart && (rc = count_pairs(c, B, P.wp, P.w, P.d, K, P.tf_cap, P.max_bag, P.max_tf, false, P.pair, P.any_sparse, on_side))) return rc;
+        if (!mat_apart && (rc = count_pairs(c, B, P.wp, P.w, P.d, P.tf_cap, P.max_bag, P.max_tf, false, P.pair, P.any_sparse, on_side))) return rc;
         if (c->row_path == 2 && P.any_sparse && c->adapt_rows)
             return fail(c, GM_ERR_CAPACITY, "pair-count path forced, but a task, count, bag or (task, field) exceeds its limits");
     }
