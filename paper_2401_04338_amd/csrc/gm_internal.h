@@ -198,6 +198,7 @@ void launch_two_hop(hipStream_t st, TwoHopArgs a, int n_tasks, int max_bags);
 // M[i][j] = number of (lookup of out-bag i, lookup of in-bag j) pairs on one row of the task's support set,
 // stored as bytes, [pad64(n_out)][pad64(n_in)] per field, fields of a task back to back.
 #define PAIR_LDS_BYTES (159 * 1024)   // LDS of the counting kernel: a tile of byte cells, two dense count blocks, the lists
+#define PAIR_BLOCK 4096          // bytes a matrix is a multiple of (64 x 64 counts)
 #define PAIR_MAX_CAP 16384       // lookups of one (task, field) and set that the counting kernel stages
 #define PAIR_MAX_BAG 127         // longest bag for which a (bag, row) count is a non-negative 8-bit integer
 struct PairCountArgs {
@@ -207,7 +208,7 @@ struct PairCountArgs {
     const u32 *base_s, *base_q, *cnt_s, *cnt_q, *n_slots;   // per (task, field)
     const int32_t *slot_start, *qseg_lo, *qseg_hi;
     const int2 *sup_sorted, *qry_sorted;
-    const int64_t *off_ss, *off_qs, *off_sq;  // [Tw] byte offset of the task's first matrix of each kind
+    const u32 *off_ss, *off_qs, *off_sq;      // [Tw] the task's first matrix of each kind, in PAIR_BLOCKs
     uint8_t* mat;
     int want_ss, want_sq;
     int lds_bytes, n_max, max_tile_rows;      // set by the launcher
@@ -221,7 +222,7 @@ struct PairCountArgs {
 void launch_pair_count(hipStream_t st, PairCountArgs a, const int32_t* order, const std::vector<int>& rows, int max_tf, int max_bag, int max_tile_rows);
 struct PairHopOut {
     int enabled;
-    const int64_t* mat_off;                   // [Tw]
+    const u32* mat_off;                       // [Tw] in PAIR_BLOCKs
     const int32_t *real_off, *row_off;        // the out set
     const float* y_in;                        // null: start from zero
     float* y_out;                             // may alias y_in; may be null

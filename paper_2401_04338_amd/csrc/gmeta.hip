@@ -314,7 +314,7 @@ struct WaveBufs {
     float* tdL;
     // pair-count matrices of the wave (null when the sparse kernel does the row arithmetic)
     uint8_t* pair_mat;
-    int64_t *pair_off_ss, *pair_off_qs, *pair_off_sq;
+    u32 *pair_off_ss, *pair_off_qs, *pair_off_sq;
     int32_t *hop_small = nullptr, *hop_tiles[3] = {nullptr, nullptr, nullptr};   // the hops' work lists (HopPlan)
     int hop_longest[3] = {0, 0, 0}, hop_run = 1, n_hop_small = 0;
     int32_t* count_order = nullptr;   // the tasks whose pairs are counted, by falling size
@@ -400,10 +400,15 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.coarse_off_s = ar.get<int32_t>(COARSE_GROUPS + 1);
     w.coarse_off_q = ar.get<int32_t>(COARSE_GROUPS + 1);
     w.task_path = ar.get<u32>(d.Tw + 1);
-    w.pair_off_ss = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
-    w.pair_off_qs = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
-    w.pair_off_sq = d.pair ? ar.get<int64_t>(d.Tw + 1) : nullptr;
-    w.count_order = d.pair ? ar.get<int32_t>(d.Tw + 1) : nullptr;
+    w.pair_off_ss = w.pair_off_qs = w.pair_off_sq = nullptr;
+    w.count_order = nullptr;
+    if (d.pair) {   // (one stretch: four of a task's 32-bit words take what three of 64 bits would, and less)
+        u32* const p = ar.get<u32>(4 * (d.Tw + 1));
+        w.pair_off_ss = p;
+        w.pair_off_qs = p + (d.Tw + 1);
+        w.pair_off_sq = p + 2 * (d.Tw + 1);
+        w.count_order = reinterpret_cast<int32_t*>(p + 3 * (d.Tw + 1));
+    }
     const int fx = hop_slices(F, c->D);
     if (d.pair) {
         const int64_t es = hop_entries(d.hop_tiles_s, fx), eq = hop_entries(d.hop_tiles_q, fx);
@@ -1684,10 +1689,10 @@ static int pair_rows(const gm_ctx* c, const Batch& B) {
     return few > 0 && few <= others ? PAIR_ROWS_FEW : PAIR_ROWS;
 }
 
-// Byte offsets of every task's pair-count matrices (kind by kind, fields back to back; nothing for a task
-// that takes the sparse kernel); returns the total.
+// Where every task's pair-count matrices begin (kind by kind, fields back to back; nothing for a task
+// that takes the sparse kernel), in PAIR_BLOCKs, which every matrix is a whole number of; returns the total in bytes.
 static int64_t pair_layout(const gm_ctx* c, const Batch& B, const WavePlan& p, int K, bool ss, bool sq,
-                           std::vector<int64_t>* off_ss, std::vector<int64_t>* off_qs, std::vector<int64_t>* off_sq,
+                           std::vector<u32>* off_ss, std::vector<u32>* off_qs, std::vector<u32>* off_sq,
                            std::vector<u32>* path) {
     int64_t acc = 0;
     for (int t = p.t0; t < p.t1; ++t) {
@@ -1695,11 +1700,11 @@ static int64_t pair_layout(const gm_ctx* c, const Batch& B, const WavePlan& p, i
         const int64_t ns = ok ? pad64(B.sup->task_offsets[t + 1] - B.sup->task_offsets[t]) : 0;
         const int64_t nq = ok ? pad64(B.qry->task_offsets[t + 1] - B.qry->task_offsets[t]) : 0;
         if (path) path->push_back(ok ? 1u : 0u);
-        if (off_ss) off_ss->push_back(acc);
+        if (off_ss) off_ss->push_back((u32)(acc / PAIR_BLOCK));
         if (ss) acc += c->F * ns * ns;
-        if (off_qs) off_qs->push_back(acc);
+        if (off_qs) off_qs->push_back((u32)(acc / PAIR_BLOCK));
         acc += c->F * nq * ns;
-        if (off_sq) off_sq->push_back(acc);
+        if (off_sq) off_sq->push_back((u32)(acc / PAIR_BLOCK));
         if (sq) acc += c->F * ns * nq;
     }
     return acc;
@@ -1922,7 +1927,7 @@ static int setup_wave(gm_ctx* c, Batch& B, const WavePlan& wp, int bm, int K, Wa
     up.put(w.tile_g_s, tg_s); up.put(w.tile_m_s, tm_s);
     up.put(w.tile_g_q, tg_q); up.put(w.tile_m_q, tm_q);
     up.put(w.coarse_off_s, co_s); up.put(w.coarse_off_q, co_q);
-    std::vector<int64_t> po_ss, po_qs, po_sq;
+    std::vector<u32> po_ss, po_qs, po_sq;
     std::vector<u32> path;
     pair_layout(c, B, wp, K, d.pair_ss, d.pair_sq, &po_ss, &po_qs, &po_sq, &path);
     up.put(w.task_path, path);

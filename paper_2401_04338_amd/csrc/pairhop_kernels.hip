@@ -218,8 +218,8 @@ __global__ __launch_bounds__(NT, 4) void pair_count_kernel(PairCountArgs a) {
     uint8_t* tile = reinterpret_cast<uint8_t*>(pc_lds);
     uint8_t* c_in = tile;
     uint8_t* c_block = tile + (size_t)colsP * HBS;   // of the out bags, where they are another set's
-    uint8_t* M = a.mat + (qs ? a.off_qs[t] : a.off_ss[t]) + (size_t)f * rowsP * colsP;
-    uint8_t* Mt = (qs && a.want_sq) ? a.mat + a.off_sq[t] + (size_t)f * colsP * rowsP : nullptr;  // [colsP rows][rowsP cols]
+    uint8_t* M = a.mat + (size_t)(qs ? a.off_qs[t] : a.off_ss[t]) * PAIR_BLOCK + (size_t)f * rowsP * colsP;
+    uint8_t* Mt = (qs && a.want_sq) ? a.mat + (size_t)a.off_sq[t] * PAIR_BLOCK + (size_t)f * colsP * rowsP : nullptr;  // [colsP rows][rowsP cols]
     const int tiles_c = colsP / 32;
     bool ovf = false;
     for (int i0 = 0; i0 < rowsP; i0 += R) {
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const u32 on = a.task_path[t];
     const int n_in = a.in_real_off[t + 1] - a.in_real_off[t], in_row = a.in_row_off[t];
     int n[2], row_off[2];
-    int64_t mat_off[2];
+    u32 mat_off[2];
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
         n[o] = a.out[o].real_off[t + 1] - a.out[o].real_off[t];
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     if (fs >= fx) return;
     const PairHopOut& out = a.out[o];
     const int n_out = o ? n[1] : n[0];
-    const uint8_t* M = a.mat + (o ? mat_off[1] : mat_off[0]) + (size_t)f * pad64(n_out) * pad64(n_in);
+    const uint8_t* M = a.mat + (size_t)(o ? mat_off[1] : mat_off[0]) * PAIR_BLOCK + (size_t)f * pad64(n_out) * pad64(n_in);
     const int64_t colz = (int64_t)f * a.D + (int64_t)sl * DS;
     const int64_t z_off = (int64_t)in_row * a.ldz + colz;
     const int64_t row_base = o ? row_off[1] : row_off[0];
@@ -770,7 +770,7 @@ __global__ __launch_bounds__(256, 4) void pair_hop_small_kernel(PairHopArgs a) {
         if (!a.out[o].enabled) continue;
         on[o] = row_w < a.out[o].real_off[t + 1] - a.out[o].real_off[t] && ct < NCT;
         if (on[o] && n_in > 0) {
-            const uint4* src = reinterpret_cast<const uint4*>(a.mat + a.out[o].mat_off[t] + ((size_t)f * 64 + row_w + ln) * 64 + h * 32);
+            const uint4* src = reinterpret_cast<const uint4*>(a.mat + (size_t)a.out[o].mat_off[t] * PAIR_BLOCK + ((size_t)f * 64 + row_w + ln) * 64 + h * 32);
             araw[o][0][0] = src[0];
             araw[o][0][1] = src[1];
         }
