@@ -1086,7 +1086,7 @@ static int most_runs(const gm_ctx* c) { return std::max(c->coarse_groups, c->L >
 static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
     if (c->coarse_groups) return std::min(Tw, c->coarse_groups);
     int n = std::min(Tw, 16);
-    if (n < 16 || c->L < 2 || !wgrad_wide_shape(c, c->ld[0], c->ld[1]) || rows / MOST_RUNS < WIDE_LONG) return n;
+    if (n < 16 || c->L < 2 || !c->wgrad_wide || !wgrad_wide_shape(c, c->ld[0], c->ld[1]) || rows / MOST_RUNS < WIDE_LONG) return n;
     const int64_t per = (int64_t)((c->ld[0] + 255) / 256) * (c->ld[1] / 256);
     double best = -1.0;
     for (int k = 12; k <= std::min<int>(MOST_RUNS, Tw); ++k) {

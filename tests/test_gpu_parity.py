@@ -681,6 +681,32 @@ def test_weight_gradient_over_runs_of_tasks_in_wide_tiles(gm):
     ctx.close()
 
 
+def test_runs_counted_for_wide_tiles(gm):
+    """The number of runs that the library picks where 256 x 256 tiles of a long contraction fill the device's rounds: 17 here (5 x 3
+    tiles a run on 256 compute units, two of 34 tasks in each), and 16 where wide tiles are switched off.  The same bits as with that number
+    configured, others than with the next one, and the whole step against the oracle."""
+    from synth import MEDIUM
+    cfg = MEDIUM.with_(n_tasks=34, n_fields=16, rows_per_field=3000, n_support=600, n_query=560, bag_max=2,
+                       layer_dims=(16 * 64 + 13, 768, 64, 1))
+    sup, qry, params = _inputs(cfg)
+    ctx = gm.from_config(cfg, workspace_bytes=4 << 30)
+    dev = ctx.device
+    if torch.cuda.get_device_properties(dev).multi_processor_count != 256:
+        pytest.skip("the counts below are for 256 compute units")
+    ds, dq, dp = _to_dev(sup, dev), _to_dev(qry, dev), _params_dev(params, dev)
+
+    def first_layer(wide, runs):
+        ctx.configure("wgrad_wide", wide)
+        ctx.configure("coarse_groups", runs)
+        return ctx.meta_step(ds, dq, dp, cfg.inner_lr, 1, 2)["dW"][0].clone()
+    for wide, picked, other in ((1, 17, 16), (0, 16, 17)):
+        got = first_layer(wide, 0)
+        assert torch.equal(got, first_layer(wide, picked)) and not torch.equal(got, first_layer(wide, other)), (wide, picked)
+    first_layer(1, 0)
+    _compare_step(cfg, ctx, sup, qry, params, 1, 2, TOL_BF16, "bf16, 17 runs of tasks in wide tiles", operand="bf16")
+    ctx.close()
+
+
 @pytest.mark.parametrize("shape", ["list", "table"])
 def test_sort_on_the_side_stream_gives_the_same_result(gm, shape):
     """gm_configure("overlap_sort", 1): the lookups are ordered by row on a second stream beside the dense phase.  Same
