@@ -279,7 +279,7 @@ enum { MAX_WAVE_TASKS = 32768 };
 static int most_wave_tasks(const gm_ctx* c) { return c->max_wave_tasks > 0 ? std::min<int>(c->max_wave_tasks, MAX_WAVE_TASKS) : MAX_WAVE_TASKS; }
 enum { COARSE_GROUPS = 32 };   // most runs of tasks (gm_configure "coarse_groups" says how many are used)
 
-static int most_runs(const gm_ctx* c);
+static int most_runs(const gm_ctx* c, int Tw, int64_t rows);
 
 struct WaveBufs {
     int32_t *row_off_s, *row_off_q, *real_off_s, *real_off_q;
@@ -450,7 +450,9 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     const bool bf = c->mlp_dtype != 0;
     const int ld0 = c->ld[0];
     if (d.pair && d.mat_apart) w.pair_mat = ar.get<uint8_t>(d.pair_bytes + 64);
-    w.Xs0 = ar.get<float>(d.Ps * ld0);
+    // bf16: the sums over runs of tasks lie where the support set's fp32 input was, which nothing reads after the last inner step
+    const int64_t input = d.Ps * ld0, sums = (int64_t)most_runs(c, d.Tw, std::min(d.Ps, d.Pq)) * c->n_theta;
+    w.Xs0 = ar.get<float>(bf ? std::max(input, sums) : input);
     w.Xq0 = ar.get<float>(d.Pq * ld0);
     const bool second = order == 2 && K > 0;
     w.TXf = (second && bf) ? ar.get<float>(d.Ps * ld0) : nullptr;
@@ -459,7 +461,7 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.loss_q = ar.get<float>(d.Pq + 1);
     const bool factors = d.factor_ld > 0;
     w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
-    w.vsum = Theta{ar.get<float>((int64_t)std::min(most_runs(c), std::max(d.Tw, 1)) * c->n_theta), c->n_theta, nullptr, 0};   // (a run has a task at least)
+    w.vsum = Theta{bf ? w.Xs0 : ar.get<float>(sums), c->n_theta, nullptr, 0};
     if (!second) w.v.b = nullptr;  // the direction is a GEMM operand only in the second-order pass
     w.Xs_scratch = Act();
     const bool keep = second || d.from_meta;   // every step's activations and deltas
@@ -1082,11 +1084,17 @@ static bool wgrad_wide_ok(const gm_ctx* c, int M, int N, int64_t rows, int G) {
 // product can run in 256 x 256 tiles, one workgroup per compute unit: the count in [12, 18] whose tiles fill the
 // last round over the compute units best, the largest run counted (the larger count on a tie).
 enum { MOST_RUNS = 18 };
-static int most_runs(const gm_ctx* c) { return std::max(c->coarse_groups, c->L > 1 && wgrad_wide_shape(c, c->ld[0], c->ld[1]) ? (int)MOST_RUNS : 16); }
+// rows: of the wave's smaller set.  (The sums have the support input's room, as long as it is, and that of 16 runs otherwise.)
+static bool runs_in_wide_tiles(const gm_ctx* c, int64_t rows) {
+    return c->L > 1 && c->wgrad_wide && wgrad_wide_shape(c, c->ld[0], c->ld[1]) && rows / MOST_RUNS >= WIDE_LONG && (MOST_RUNS - 16) * c->n_theta <= rows * c->ld[0];
+}
+static int most_runs(const gm_ctx* c, int Tw, int64_t rows) {   // of a wave (a run has a task at least)
+    return std::min(std::max(Tw, 1), c->coarse_groups ? c->coarse_groups : runs_in_wide_tiles(c, rows) ? (int)MOST_RUNS : 16);
+}
 static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
     if (c->coarse_groups) return std::min(Tw, c->coarse_groups);
     int n = std::min(Tw, 16);
-    if (n < 16 || c->L < 2 || !c->wgrad_wide || !wgrad_wide_shape(c, c->ld[0], c->ld[1]) || rows / MOST_RUNS < WIDE_LONG) return n;
+    if (n < 16 || !runs_in_wide_tiles(c, rows)) return n;
     const int64_t per = (int64_t)((c->ld[0] + 255) / 256) * (c->ld[1] / 256);
     double best = -1.0;
     for (int k = 12; k <= std::min<int>(MOST_RUNS, Tw); ++k) {
