@@ -275,7 +275,8 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               are written as theta - alpha * (the gradients of steps 0..k), one product per step accumulated on the
  *               matrix cores, straight from the meta parameters (every step's activations and deltas are kept for the
  *               second-order chain anyway; first order keeps them where tasks are small enough, up to 1050 support rows of a
- *               task and steps): no per-task fp32 copy of a weight matrix is written or read; 0 = every
+ *               task and steps, and memory that the call has anyway holds them): no per-task fp32 copy of a weight matrix is
+ *               written or read; 0 = every
  *               step updates a per-task fp32 master (theta_{k+1} = theta_k - alpha * gradient_k).  The same values up
  *               to fp32 rounding before the bf16 operand copy is taken.
  *   "chain_factors": bf16 operands, second order: the chain's direction on a task's hidden layers (the query gradient, less
@@ -296,8 +297,8 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *               row arithmetic whole ("row_path"), and with emb_grad_table every wave adds its own sums to a row.  (A few
  *               tasks of 513 to 1,024 samples may take pair matrices too, which the batch alone decides; only where the
  *               workspace could not hold one of them with its matrices, run by itself, do they take the other row arithmetic.  And
- *               where it could not hold one task's activations and row gradients of all inner steps, a first-order call in
- *               bf16 keeps neither: "theta_from_meta" 0, and the query rows' update step by step.)
+ *               where the tasks would run in more waves for what a first-order call in bf16 keeps of its inner steps, it keeps
+ *               nothing: "theta_from_meta" 0, and the query rows' update step by step.)
  *   "pair_tile_rows": most out-rows of a pair-count matrix that the counting kernel holds in LDS at a time
  *               (0 = as many as fit); identical results.
  * Unknown keys or values give GM_ERR_ARG. */

@@ -293,7 +293,7 @@ struct WaveBufs {
     u32 *tmid_keys = nullptr, *tmid_vals = nullptr;   // more than 512 tasks: the first of the two passes that order the lookups by task
     bool slots_written = true;   // sup_slot / qry_slot hold the slot of every lookup (only the sparse row kernel reads them)
     float *Xs0, *Xq0, *TXf, *dX, *loss_q;
-    float* dX_kept = nullptr;   // (query_sum 3 without a chain: the second step's)
+    float* dX_kept = nullptr;   // (query_sum 3 without a chain: the second step's, see Spare)
     Theta v;  // direction / query gradient w.r.t. theta'
     // the last weight-gradient products of a call are only ever summed over the tasks: they are taken over COARSE_GROUPS
     // runs of consecutive tasks instead (row offsets of the runs, one sum per run)
@@ -341,19 +341,78 @@ struct WaveDims {
     bool from_meta = false;                // an inner step's weights are written from the meta parameters and all steps' gradients so far
     int factor_ld = 0;                     // > 0: the chain's direction stays factors (see Factor); rows of the largest task of the batch
 };
+struct FirstOrder { bool grads, acts; };   // what a call without a chain keeps of its inner steps: input gradients (query_sum 3), activations (from_meta)
 static int query_sum(const gm_ctx* c, int K);
-static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t rows_s, int K, int order);
+static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t n_support, int K, int order);
+static FirstOrder first_order_keeps(const gm_ctx* c, int64_t T, int64_t n_support, int64_t Ps, int64_t Pq, int K);
 static int factor_slots(int K) { return 2 * K - 1; }   // most factors of the direction: the query pass's, two of every later step
 
-static Act alloc_act(const gm_ctx* c, Arena& ar, int64_t rows, int ld) {
+// Without a chain the steps' activations and input gradients are dead once the outer pass begins, and until then nothing touches three
+// stretches that the call has anyway: the query set's activations and deltas, its rows of the gradient buffer and the per-task query
+// gradient.  What the steps of such a call keep beyond one step's activations goes there (first_order_keeps).
+struct Spare {
+    Arena part[3];
+    Arena* beyond;   // for what does not fit there
+    template <typename T>
+    T* get(size_t n) {
+        for (Arena& p : part) {
+            Arena a = p;
+            T* const got = a.get<T>(n);
+            if (!a.overflow) { p = a; return got; }
+        }
+        return beyond->get<T>(n);
+    }
+};
+template <typename Mem>   // Arena or Spare
+static Act alloc_act(const gm_ctx* c, Mem& ar, int64_t rows, int ld) {
     Act a;
     a.ld = ld;
     if (c->mlp_dtype == 0) {
-        a.f = ar.get<float>(rows * ld);
+        a.f = ar.template get<float>(rows * ld);
     } else {
-        a.b = ar.get<bf16_t>(rows * ld + 8);
+        a.b = ar.template get<bf16_t>(rows * ld + 8);
     }
     return a;
+}
+// hidden layers' activations and deltas of a step, and its last layer's
+template <typename Mem>
+static void alloc_step(const gm_ctx* c, Mem& ar, StepState& s, int64_t rows) {
+    s.A.assign(c->L, Act());
+    s.Dl.assign(c->L, Act());
+    for (int l = 1; l < c->L; ++l) {
+        s.A[l] = alloc_act(c, ar, rows, c->ld[l]);
+        s.Dl[l] = alloc_act(c, ar, rows, c->ld[l]);
+    }
+    s.dL = ar.template get<float>(rows + 1);
+    s.zL = ar.template get<float>(rows + 1);
+}
+// the query set's activations and deltas of the hidden layers, one stretch
+static size_t alloc_query(const gm_ctx* c, Arena& ar, std::vector<Act>& A, std::vector<Act>& D, int64_t rows) {
+    const size_t from = ar.off;
+    A.assign(c->L, Act());
+    D.assign(c->L, Act());
+    for (int l = 1; l < c->L; ++l) {
+        A[l] = alloc_act(c, ar, rows, c->ld[l]);
+        D[l] = alloc_act(c, ar, rows, c->ld[l]);
+    }
+    return ar.off - from;
+}
+static Spare make_spare(const gm_ctx* c, int64_t Tw, int64_t Pq, void* query, size_t query_bytes, float* query_grad, float* v, Arena* beyond) {
+    Spare s;
+    s.part[0].base = static_cast<char*>(query); s.part[0].cap = query_bytes;
+    s.part[1].base = reinterpret_cast<char*>(query_grad); s.part[1].cap = (size_t)Pq * c->FD * sizeof(float);
+    s.part[2].base = reinterpret_cast<char*>(v); s.part[2].cap = (size_t)Tw * c->n_theta * sizeof(float);
+    s.beyond = beyond;
+    return s;
+}
+// What a call without a chain keeps in spare memory: the second of three steps' input gradients (grads), and every step's activations (acts)
+// but for the first step's and the second one's input, which have the room of two steps' that take turns.
+static void alloc_first_order(const gm_ctx* c, Spare& sp, WaveBufs& w, int64_t rows, int K, bool grads, bool acts) {
+    w.dX_kept = grads ? sp.get<float>(rows * c->FD) : nullptr;
+    for (int k = 1; acts && k < K; ++k) {
+        if (k > 1) w.steps[k].X = alloc_act(c, sp, rows, c->ld[0]);
+        alloc_step(c, sp, w.steps[k], rows);
+    }
 }
 static Theta alloc_theta(const gm_ctx* c, Arena& ar, int Tw, bool need_f) {
     Theta t;
@@ -444,8 +503,9 @@ static void alloc_wave_index(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     w.pair_mat = d.pair && !d.mat_apart ? ar.get<uint8_t>(d.pair_bytes + 64) : nullptr;
 }
 
-// activations, per-task parameters and gradient buffers of a wave
-static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const WaveDims& d, int K, int order) {
+// activations, per-task parameters and gradient buffers of a wave; query_grad: the wave's query rows of the batch-wide gradient buffer
+// (null where sizes are all that is asked, and with the table-shaped output, which has a buffer per wave)
+static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const WaveDims& d, int K, int order, float* query_grad = nullptr) {
     const int L = c->L;
     const bool bf = c->mlp_dtype != 0;
     const int ld0 = c->ld[0];
@@ -457,7 +517,10 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     const bool second = order == 2 && K > 0;
     w.TXf = (second && bf) ? ar.get<float>(d.Ps * ld0) : nullptr;
     w.dX = ar.get<float>(std::max(d.Ps, d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
-    w.dX_kept = d.query_sum > 2 && !second ? ar.get<float>(d.Ps * (int64_t)std::max(c->FD, 1) + 4) : nullptr;
+    if (d.table) {
+        w.GX = ar.get<float>((d.Ps + d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
+        query_grad = w.GX ? w.GX + d.Ps * (int64_t)c->FD : nullptr;
+    }
     w.loss_q = ar.get<float>(d.Pq + 1);
     const bool factors = d.factor_ld > 0;
     w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
@@ -473,18 +536,17 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     for (int k = 0; k < kept; ++k) {
         StepState& s = w.steps[k];
         // fp32: step 0 reads Xs0 itself; later steps (second order) keep their own input
-        if (bf) s.X = alloc_act(c, ar, d.Ps, ld0);
-        else if (k > 0) s.X = alloc_act(c, ar, d.Ps, ld0);
+        const bool here = second || k == 0;   // (not in spare memory)
+        if ((bf || k > 0) && (here || k == 1)) s.X = alloc_act(c, ar, d.Ps, ld0);
         s.X.ld = ld0;
-        s.A.assign(L, Act());
-        s.Dl.assign(L, Act());
-        for (int l = 1; l < L; ++l) {
-            s.A[l] = alloc_act(c, ar, d.Ps, c->ld[l]);
-            s.Dl[l] = alloc_act(c, ar, d.Ps, c->ld[l]);
-        }
-        s.dL = ar.get<float>(d.Ps + 1);
-        s.zL = ar.get<float>(d.Ps + 1);
+        if (here) alloc_step(c, ar, s, d.Ps);
         s.wL_copy = (bf && second && k > 0) ? ar.get<float>((int64_t)d.Tw * c->ld[L - 1]) : nullptr;
+    }
+    const size_t query_bytes = alloc_query(c, ar, w.Aq, w.Dq, d.Pq);
+    w.dX_kept = nullptr;
+    if (!second) {
+        Spare sp = make_spare(c, d.Tw, d.Pq, L > 1 ? w.Aq[1].b : nullptr, bf ? query_bytes : 0, query_grad, w.v.f, &ar);
+        alloc_first_order(c, sp, w, d.Ps, K, d.query_sum > 2, d.from_meta);
     }
     // theta^(k+1), k = 0..K-1.  fp32: one buffer per kept step (the second-order pass needs them all), or one
     // updated in place.  bf16: ONE fp32 master updated in place, and bf16 operand copies per kept step.
@@ -499,12 +561,6 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
         }
     }
     w.Xq = alloc_act(c, ar, d.Pq, ld0);
-    w.Aq.assign(L, Act());
-    w.Dq.assign(L, Act());
-    for (int l = 1; l < L; ++l) {
-        w.Aq[l] = alloc_act(c, ar, d.Pq, c->ld[l]);
-        w.Dq[l] = alloc_act(c, ar, d.Pq, c->ld[l]);
-    }
     w.dLq = ar.get<float>(d.Pq + 1);
     w.zq = ar.get<float>(d.Pq + 1);
     w.TX = Act();
@@ -536,7 +592,6 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
         w.room.S = ar.get<bf16_t>(w.room.slot * factor_slots(K) + 8);
     }
     if (d.table) {
-        w.GX = ar.get<float>((d.Ps + d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
         w.n_rows = ar.get<int64_t>(2);
         alloc_sort(c, ar, w.so, d.nnz_s + d.nnz_q, c->field_base[c->F], 0, true);
     }
@@ -812,7 +867,8 @@ extern "C" size_t gm_workspace_bytes(const gm_model_desc* model, int32_t n_tasks
     d.Tw = n_tasks;
     d.Ss = n_support; d.Sq = n_query; d.Ps = Ps; d.Pq = Pq;
     d.nnz_s = nnz_support; d.nnz_q = nnz_query;
-    d.from_meta = theta_from_meta(&c, n_tasks, n_support, inner_steps, order);
+    const FirstOrder first = first_order_keeps(&c, n_tasks, n_support, Ps, Pq, inner_steps);
+    d.from_meta = order == 1 ? first.acts : theta_from_meta(&c, n_tasks, n_support, inner_steps, order);
     d.mt_s = (int)(Ps / 64 + n_tasks + 1);  // upper bound on m-tiles
     d.mt_q = (int)(Pq / 64 + n_tasks + 1);
     // pair-count matrices, for tasks of equal size (a batch of uneven tasks may need more and then runs in waves)
@@ -822,6 +878,7 @@ extern "C" size_t gm_workspace_bytes(const gm_model_desc* model, int32_t n_tasks
             const int64_t ps = (ns + 63) & ~(int64_t)63, pq = (nq + 63) & ~(int64_t)63;
             d.pair = true;
             d.query_sum = query_sum(&c, inner_steps);
+            if (order == 1 && d.query_sum > 2 && !first.grads) d.query_sum = 0;
             d.pair_ss = inner_steps >= 2;
             d.pair_sq = order == 2;
             if (std::max(ns, nq) > HOP_SMALL) {
@@ -1428,7 +1485,7 @@ struct Batch {  // host-side description of one call
     std::vector<int64_t> ls, lq;          // lookup offsets per task (filled when several waves are needed)
     bool table = false;                   // table-shaped sparse output: every wave sorts and reduces its own lookups
     int pair_rows = PAIR_ROWS;            // a task of at most so many rows in each set goes through pair-count matrices
-    bool tight = false;                   // first order: no room for every step's activations (theta_from_meta) or gradients (query_sum)
+    bool tight = false;                   // a call without a chain keeps no steps' activations or gradients (see first_order_keeps)
     BatchBufs b;
     HostImages images;
 };
@@ -1748,7 +1805,7 @@ static int factor_rows(const gm_ctx* c, const Batch& B, int bm, int K, int order
 
 // Steps whose input gradients are kept until the last one: the query set's update X - alpha M (Z_0 + .. + Z_k) is then one hop instead of
 // one a step, each of which reads M and X and writes X.  Two steps, or three with bf16 operands: the buffers are ones that nothing
-// uses before (the support rows of the gradient buffer, the chain's fp32 direction) but for one without a chain.
+// uses before: the support rows of the gradient buffer, and the chain's fp32 direction or, without a chain, Spare.
 static int query_sum(const gm_ctx* c, int K) { return K == 2 || (K == 3 && c->mlp_dtype) ? K : 0; }
 
 // bf16, 2..GEMM_MAX_PAIRS inner steps: every step's weights straight from the meta parameters and the gradients of all steps so far, bf16
@@ -1756,16 +1813,39 @@ static int query_sum(const gm_ctx* c, int K) { return K == 2 || (K == 3 && c->ml
 // (k + 1 of step k instead of one) cost less than the fp32 master, written and read again by the next step: 201 tasks of 75..225 rows,
 // 1677-512-256, three steps, the six products of the steps 1110 us with the master, 864 without; a product more costs 60 us there, so K steps
 // of r rows a task break even at K r = 1050.
-static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t rows_s, int K, int order) {
+static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t n_support, int K, int order) {
     if (!c->mlp_dtype || K < 2 || K > GEMM_MAX_PAIRS || !c->theta_from_meta || T <= 0) return false;
-    return order == 2 || (double)K * rows_s < 1050.0 * (double)T;
+    return order == 2 || (c->L > 1 && (double)K * n_support < 1050.0 * (double)T);
+}
+
+// What a call without a chain keeps of its inner steps: only what spare memory holds if the batch runs as one wave, so that no call needs
+// more workspace for it (201 tasks of 150 + 243 rows, 1677-512-256, three steps: 0.6 of 6 GB); the input gradients first, which save more.
+// A rule on the batch.  An uneven wave of several may need some beyond the spare memory (then see plan_waves).
+static FirstOrder first_order_keeps(const gm_ctx* c, int64_t T, int64_t n_support, int64_t Ps, int64_t Pq, int K) {
+    auto fits = [&](const FirstOrder& k) {
+        Arena none, query;
+        query.cap = ~(size_t)0 >> 1;
+        std::vector<Act> A, D;
+        Spare sp = make_spare(c, T, Pq, nullptr, alloc_query(c, query, A, D, Pq), nullptr, nullptr, &none);
+        WaveBufs w;
+        w.steps.assign(std::max(K, 1), StepState());
+        alloc_first_order(c, sp, w, Ps, K, k.grads, k.acts);
+        return !none.overflow;
+    };
+    FirstOrder k{query_sum(c, K) > 2 && c->F > 0 && c->D % 32 == 0 && c->adapt_rows && c->row_path != 1, false};
+    if (k.grads && !fits(k)) k.grads = false;
+    k.acts = theta_from_meta(c, T, n_support, K, 1);
+    if (k.acts && !fits(k)) k.acts = false;
+    return k;
 }
 
 static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, int bm, int K, int order) {
     WaveDims d;
     d.table = B.table;
     d.factor_ld = factor_rows(c, B, bm, K, order);
-    d.from_meta = !B.tight && theta_from_meta(c, B.T, B.poff_s[B.T], K, order);
+    FirstOrder first{false, false};
+    if (order == 1 && !B.tight) first = first_order_keeps(c, B.T, B.sup->n_samples, B.poff_s[B.T], B.poff_q[B.T], K);
+    d.from_meta = order == 1 ? first.acts : theta_from_meta(c, B.T, B.sup->n_samples, K, order);
     for (int t = p.t0; t < p.t1; ++t) {
         if (task_pair_ok(c, B, t, K)) {
             d.pair = true;
@@ -1781,7 +1861,7 @@ static WaveDims wave_dims(const gm_ctx* c, const Batch& B, const WavePlan& p, in
         d.pair_sq = order == 2;
         d.pair_bytes = pair_layout(c, B, p, K, d.pair_ss, d.pair_sq, nullptr, nullptr, nullptr, nullptr);
         d.query_sum = query_sum(c, K);
-        if (B.tight && d.query_sum > 2) d.query_sum = 0;   // (two steps' need no buffer of their own)
+        if (order == 1 && d.query_sum > 2 && !first.grads) d.query_sum = 0;   // (two steps' have buffers that nobody else needs)
     }
     d.Tw = p.t1 - p.t0;
     d.Ss = p.s1 - p.s0; d.Sq = p.q1 - p.q0; d.Ps = p.ps1 - p.ps0; d.Pq = p.pq1 - p.pq0;
@@ -1836,6 +1916,7 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
     const int max_per = std::min(std::max(T, 1), most_wave_tasks(c));
     const int fewest = (std::max(T, 1) + max_per - 1) / max_per;
     int n_waves = fewest;
+    const FirstOrder keeps = first_order_keeps(c, T, sup->n_samples, B.poff_s[T], B.poff_q[T], K);
     while (true) {
         const int per = (std::max(T, 1) + n_waves - 1) / n_waves;
         plans.clear();
@@ -1866,12 +1947,10 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
             if (T == 0) break;
         }
         if (fits) return GM_OK;
+        // (a wave less is worth more than what the steps keep)
+        B.tight = order == 1 && !B.tight && (keeps.grads || keeps.acts);
+        if (B.tight) continue;
         if (per == 1) {
-            if (!B.tight && order == 1 && (theta_from_meta(c, T, B.poff_s[T], K, order) || query_sum(c, K) > 2)) {
-                B.tight = true;
-                n_waves = fewest;
-                continue;
-            }
             if (B.pair_rows == PAIR_ROWS) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
             B.pair_rows = PAIR_ROWS;   // (a large task does not fit with its matrices, not even alone)
             n_waves = fewest;
@@ -2132,7 +2211,7 @@ static int meta_step_impl(gm_ctx* c, int32_t T, const gm_set* sup, const gm_set*
         if (pre) w = pre->w;
         const WaveDims d = pre ? pre->d : wave_dims(c, B, wp, bm, K, order);
         if (!pre) alloc_wave_index(c, ar, w, d);
-        alloc_wave_dense(c, ar, w, d, K, order);
+        alloc_wave_dense(c, ar, w, d, K, order, b.GX ? b.GX + (Ps_tot + wp.pq0) * (int64_t)FD : nullptr);
         if (ar.overflow) return fail(c, GM_ERR_WORKSPACE, "internal: wave does not fit");
         Grp gs, gq;
         const bool adapt = c->adapt_rows != 0;
