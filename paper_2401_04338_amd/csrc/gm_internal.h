@@ -38,8 +38,8 @@ struct SetView {
 };
 
 // (clears the status words first.)  uniform_rows: the number of rows every table has, or -1 when the tables differ in size
-// most_bags: of the largest of the tasks, both sets
-void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, SetView sup, SetView qry, const int64_t* field_base,
+// most_bags: of the largest of the tasks, both sets; all_bags: of all of them
+void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, int64_t all_bags, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status, bool cleared /* status is clear already */);
 void launch_scan_u32(hipStream_t st, const u32* in, u32* out, int64_t n, u32* tmp /* >= n/1024+2048 */,
                      u32* total /* may be null */);

@@ -1612,7 +1612,7 @@ static int run_index_wave(gm_ctx* c, Batch& B, const WavePlan& wp, WaveBufs& w, 
     SetView vs = make_view(B.sup, B.b.toff_s, wp.s0, wp.ls0), vq = make_view(B.qry, B.b.toff_q, wp.q0, wp.lq0);
     {
         Prof p(c, "tf_count", 8.0 * ((wp.s1 - wp.s0) + (wp.q1 - wp.q0)) * F + 4.0 * ((wp.ls1 - wp.ls0) + (wp.lq1 - wp.lq0)), 0);
-        launch_tf_count(st, F, wp.t0, Tw, most_bags(B.sup, B.qry, wp.t0, wp.t1, F), vs, vq, c->d_field_base, B.sup->nnz, B.qry->nnz, uniform_rows(c), w.cnt_s, w.cnt_q, c->d_status, true);
+        launch_tf_count(st, F, wp.t0, Tw, most_bags(B.sup, B.qry, wp.t0, wp.t1, F), ((wp.s1 - wp.s0) + (wp.q1 - wp.q0)) * F, vs, vq, c->d_field_base, B.sup->nnz, B.qry->nnz, uniform_rows(c), w.cnt_s, w.cnt_q, c->d_status, true);
     }
     u32 hs[ST_WORDS];
     int rc = read_status(c, hs);
@@ -3341,7 +3341,7 @@ extern "C" int gm_gather_pool(gm_ctx* c, int32_t T, const gm_set* set, const flo
     SetView v = make_view(set, toff, 0, 0);
     if (c->F == 0 || T == 0) launch_fill_u32(st, c->d_status, ST_WORDS, 0);
     else
-        launch_tf_count(st, c->F, 0, T, most_bags(set, set, 0, T, c->F), v, v, c->d_field_base, set->nnz, set->nnz, uniform_rows(c), cnt, cnt + (int64_t)T * c->F + 1, c->d_status, false);
+        launch_tf_count(st, c->F, 0, T, most_bags(set, set, 0, T, c->F), 2 * set->n_samples * c->F, v, v, c->d_field_base, set->nnz, set->nnz, uniform_rows(c), cnt, cnt + (int64_t)T * c->F + 1, c->d_status, false);
     u32 hs[ST_WORDS];
     rc = read_status(c, hs);
     if (rc != GM_OK) return rc;

@@ -149,13 +149,17 @@ __global__ __launch_bounds__(TC_NT) void tf_count_kernel(int F, int t0, SetView 
     }
 }
 
-void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, SetView sup, SetView qry, const int64_t* field_base,
+void launch_tf_count(hipStream_t st, int F, int t0, int Tw, int64_t most_bags, int64_t all_bags, SetView sup, SetView qry, const int64_t* field_base,
                      int64_t nnz_sup, int64_t nnz_qry, int64_t uniform_rows, u32* cnt_sup, u32* cnt_qry, u32* status, bool cleared) {
     if (Tw <= 0) return;
     // A (task, set) is split, down to a bag a thread, while the workgroups are fewer than 128: a few large tasks would leave the chip
-    // idle (3 tasks x 32,768 + 32,768 bags).  The largest task decides: the others' spare workgroups have nothing to add, and it
-    // alone would be the launch's time (one task of 2048 + 2048 samples and 99 of 2 + 2).
-    const int split = (int)std::max<int64_t>(1, std::min<int64_t>(most_bags / TC_NT, 64 / Tw));
+    // idle (3 tasks x 32,768 + 32,768 bags: 57 us whole, 18 in 21 parts).  From there on a part costs as much as it saves (the counts are cleared and
+    // added with atomics: 64 tasks x 3,328 + 3,328 bags 12 us whole, 20 in two; 96 x 6,656 + 6,656 23 and 32) but for parts of 8,192 bags or more:
+    // while the workgroups are fewer than 256 (48 tasks x 32,768 + 32,768 bags 113 us whole, 94 in two), and where one task is larger than the
+    // others and would alone be the launch's time, fewer than 2,048, most of which then find nothing to do (one task of 81,920 + 81,920 bags and 99
+    // of 80 + 80 67 us whole, 31 in ten; 299 70, in three 46; two tasks of 40,960 and 28,000 and 700 of 1,600 56, in two 63).
+    const int64_t most_parts = 4 * all_bags < most_bags * Tw ? 1024 / Tw : 128 / Tw;
+    const int split = (int)std::max<int64_t>({1, std::min<int64_t>(most_bags / TC_NT, 64 / Tw), std::min(most_bags / (2 * 8192), most_parts)});
     const int64_t counts = split > 1 ? (int64_t)Tw * F : 0;
     if (split > 1 || !cleared) launch_zero(st, ZeroJobs{split > 1 ? 3 : 1, {status, cnt_sup, cnt_qry}, {ST_WORDS, counts, counts}});
     hipLaunchKernelGGL(tf_count_kernel, dim3(Tw, 2, split), dim3(TC_NT), F * sizeof(u32), st, F, t0, sup, qry, field_base,

@@ -46,25 +46,35 @@ def test_one_bad_index(gm, samples, bag, split, uneven):  # noqa: F811
 
 
 @pytest.mark.parametrize("uneven", [0, 1])
-def test_one_bad_index_beside_small_tasks(gm, uneven):  # noqa: F811
-    """The largest task decides how many workgroups every task gets: here five, of which the one-sample tasks fill none."""
+@pytest.mark.parametrize("small,large,bag", [(4, 4000, 3), (16, 1500, 9), (40, 16384, 1)])
+def test_one_bad_index_beside_small_tasks(gm, small, large, bag, uneven):  # noqa: F811
+    """The largest task decides how many workgroups every (task, set) gets: several here, of which the one-sample tasks fill one.  Their counts
+    are cleared and added; a bad index is found at the ends of the large task's trips and in the tasks beside it."""
     from paper_2401_04338_amd import GMetaError
-    sizes = [1] * 20 + [700] + [1] * 20
-    ctx = gm(F, [ROWS, ROWS + uneven], 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 26)
-    sets = [_set(sum(sizes), 9), _set(sum(sizes), 9)]
+    sizes = [1] * (small // 2) + [large] + [1] * (small // 2)
+    tasks, most = small + 1, 2 * large * F
+    few, parts = min(most // 1024, 64 // tasks), min(most // 16384, 1024 // tasks)   # (the largest task is more than four times the average)
+    split = max(few, parts)
+    assert split > 1 and 4 * 2 * sum(sizes) * F < most * tasks
+    ctx = gm(F, [ROWS, ROWS + uneven], 4, 1, [F * 4 + 1, 8, 1], 0, workspace_bytes=1 << 27)
+    sets = [_set(sum(sizes), bag), _set(sum(sizes), bag)]
     for s in sets:
         s.task_offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
-    ctx.index_prep(*sets)
-    per = F * 9
+    clean = ctx.index_prep(*sets)
+    per, step = F * bag, 1024 * split
+    first, last = small // 2 * per, (small // 2 + large) * per   # the large task's lookups
+    places = {0, first - 1, first, last - 1, last, sets[0].nnz - 1}
+    places |= {first + k * step + d for k in (1, 7, 8, 9) for d in (-1, 0, 1) if k * step + d < last - first}
     for s in sets:
-        for at in (0, 19 * per, 20 * per, 20 * per + 1280, 20 * per + 4 * 1280 - 1, 720 * per - 1, 720 * per, s.nnz - 1):
+        for at in sorted(places):
             good = int(s.indices[at])
             s.indices[at] = -1
             with pytest.raises(GMetaError) as e:
                 ctx.index_prep(*sets)
             assert e.value.code == -2, at
             s.indices[at] = good
-    ctx.index_prep(*sets)
+    again = ctx.index_prep(*sets)
+    assert all(torch.equal(clean[k], again[k]) for k in clean)
     ctx.close()
 
 
