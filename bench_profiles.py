@@ -108,6 +108,8 @@ def hbm(a):
     cf, cw = copy_reading(fetch), copy_reading(write)
     sf, sw = (known / cf if cf > 0 else 1.0), (known / cw if cw > 0 else 1.0)
     ba = a.bench_args or "<bench arguments>"
+    given = re.search(r"--tasks[ =](\d+)", a.bench_args)   # (a share of the workload's tasks; bench.py counts this run's waves by it)
+    tasks = a.tasks if a.tasks is not None else int(given.group(1)) if given else None
     print(f"# HBM traffic per kernel family, workload {a.workload}")
     print("# commands (from /tmp, TMPDIR=/tmp), one counter per run:")
     print(f"#   rocprofv3 --pmc FETCH_SIZE --output-format csv -d <f> -o p -- python3 /root/repo/bench.py {ba}")
@@ -140,7 +142,7 @@ def hbm(a):
         with open(a.json, "w") as fh:
             json.dump({"workload": a.workload, "unit": "bytes", "scale_fetch": sf, "scale_write": sw,
                        "bytes_per_launch": out, "bytes_per_step": per_step, "steps": a.steps,
-                       "tasks_in_the_profiled_run": a.tasks}, fh, indent=1)
+                       "tasks_in_the_profiled_run": tasks}, fh, indent=1)
 
 
 def mfma(a):
@@ -187,7 +189,7 @@ def main():
     h.add_argument("--workload", required=True)
     h.add_argument("--steps", type=int, default=1, help="meta steps the profiled run made (timed + warm-up + event-timed)")
     h.add_argument("--json", default=None)
-    h.add_argument("--tasks", type=int, default=None, help="tasks of the profiled run (when it was a share of the workload)")
+    h.add_argument("--tasks", type=int, default=None, help="tasks of the profiled run, where --bench-args does not say them")
     h.add_argument("--bench-args", default="")
     m = sub.add_parser("mfma")
     m.add_argument("--csv", required=True)

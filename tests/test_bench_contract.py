@@ -1,6 +1,7 @@
 """bench.py's command line and the one JSON line it prints (the driver's contract)."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -34,6 +35,29 @@ def test_compulsory_bytes_of_the_prefetch():
     qry = one([0, 1, 2], [2, 1, 1, 1], [3, 4, 5, 0, 0])               # task 0: rows (0,3) (0,4) (1,5)
     rows, lookups, bags, samples = 4, 4 + 3, 4 + 2, 2 + 1
     assert compulsory_gather_bytes(cfg, sup, qry, 1) == rows * 16 + lookups * 4 + bags * 8 + samples * 32 * 6
+
+
+@pytest.mark.parametrize("args,tasks", [("--config c5_large --tasks 256 --batches 1", 256), ("--config c3_medium --batches 1", None)])
+def test_counter_summary_names_the_tasks_of_its_run(tmp_path, args, tasks):
+    """A summary of a share of a workload's tasks says so: bench.py divides the whole run's launches by it."""
+    for name in ("FETCH_SIZE", "WRITE_SIZE"):
+        (tmp_path / f"{name}.csv").write_text('"Kernel_Name","Counter_Name","Counter_Value"\n'
+                                              f'"stream_copy_kernel(int)","{name}",1024\n"pair_count_kernel(int)","{name}",512\n')
+    out = tmp_path / "out.json"
+    subprocess.run([sys.executable, os.path.join(ROOT, "bench_profiles.py"), "hbm", "--fetch", str(tmp_path / "FETCH_SIZE.csv"), "--write",
+                    str(tmp_path / "WRITE_SIZE.csv"), "--copy-gib", str(1 / 1024), "--workload", "w", "--json", str(out), "--bench-args", args],
+                   check=True, capture_output=True, timeout=120)
+    d = json.loads(out.read_text())
+    assert d["tasks_in_the_profiled_run"] == tasks and d["bytes_per_step"] == {"pair_count": 2 * 512 * 1024.0}
+
+
+@pytest.mark.parametrize("workload", ["c3_medium", "c5_large"])
+def test_committed_counter_summaries_name_the_tasks_of_their_run(workload):
+    path = os.path.join(ROOT, "profiles", f"hbm_traffic_{workload}")
+    with open(path + ".txt") as fh:
+        given = re.search(r"bench\.py .*--tasks (\d+)", fh.read())
+    with open(path + ".json") as fh:
+        assert json.load(fh)["tasks_in_the_profiled_run"] == (int(given.group(1)) if given else None)
 
 
 @pytest.mark.gpu
