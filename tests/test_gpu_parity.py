@@ -654,7 +654,7 @@ def test_weight_gradient_over_runs_of_tasks_in_wide_tiles(gm):
     per run and a first layer wide enough to fill the device they take the pipelined 256 x 256 tiles, both operands read
     contraction-slowest (gm_configure("wgrad_wide"), on by default).  Every element is accumulated in the same order as
     in 128 x 128 tiles: over the same runs of tasks the results are identical; then the whole step against the oracle
-    with the number of runs the library picks for the wide tiles."""
+    (16 runs; test_runs_counted_for_wide_tiles has another number)."""
     from synth import MEDIUM
     cfg = MEDIUM.with_(n_tasks=40, n_fields=34, rows_per_field=3000, n_support=900, n_query=37, bag_max=3,
                        layer_dims=(34 * 64 + 13, 1024, 64, 1))

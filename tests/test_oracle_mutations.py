@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 
 from oracle import maml_dlrm as O
-from tests.helpers import small_cfg
+from tests.helpers import oracle_model, rel_err, small_cfg
+from tests.test_hop_tiles import THREE_STEPS, THREE_STEPS_TOL, three_steps
 from tests.test_oracle_pins import _fd_check
 
 
@@ -135,3 +136,33 @@ def test_given_gates_ignored_by_a_pass_is_caught(monkeypatch, where):
                             _ORIG(acts, z, y, W, deltas, [a > 0.0 for a in acts[1:]], vW, vb, vx, q))
     with pytest.raises(AssertionError):
         pin(2)
+
+
+@pytest.mark.parametrize("left_out", [0, 1, 2])
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("D,ns,nq", THREE_STEPS)
+def test_a_step_left_out_of_the_query_rows_update_shows(monkeypatch, order, D, ns, nq, left_out):
+    """On the inputs of the three-step hop's test: some output moves by more than 2.5 times that test's tolerance if one step's gradient is
+    missing in the rows that the query set sees."""
+    K = 3
+    cfg, sup, qry, params = three_steps(D, ns, nq)
+    args = (oracle_model(cfg), params.numpy(), sup.numpy(), qry.numpy(), cfg.inner_lr, K, order)
+    gates = {}
+    O.meta_step(*args, operand="bf16", masks_out=gates)
+    want = O.meta_step(*args, relu_masks=gates)
+    pool, task_meta_grad = O.pool, O.task_meta_grad
+
+    def task(*a, **kw):
+        rows = []   # before every step, and the query pass's
+
+        def without(model, E, *rest):
+            rows.append(E)
+            if len(rows) == K + 1:
+                E = E + (rows[left_out] - rows[left_out + 1])
+            return pool(model, E, *rest)
+        monkeypatch.setattr(O, "pool", without)
+        return task_meta_grad(*a, **kw)
+    monkeypatch.setattr(O, "task_meta_grad", task)
+    got = O.meta_step(*args, relu_masks=gates)
+    outputs = lambda r: [r["task_loss"], *r["dW"], *r["db"], r["emb_grad"]]  # noqa: E731
+    assert max(max(rel_err(x, y)) for x, y in zip(outputs(got), outputs(want))) > 2.5 * THREE_STEPS_TOL
