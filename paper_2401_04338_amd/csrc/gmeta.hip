@@ -1163,12 +1163,21 @@ static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
 
 // Whether the query gradient, where the second-order chain's direction starts, is summed over runs of tasks beside being written per
 // task as the chain's bf16 operand, instead of being written in fp32 per task and read again for the sum: one inner step (the chain's
-// next product is summed over runs anyway), and the extra product costs less than eight bytes a weight and task: 128 tasks of 256 rows
-// (1677-512-256) 165 + 41 us to write, 113 to sum, and with the bf16 operand and the runs 102 + 19, 71 + 34, 16; 128 tasks of 512 rows
-// (4109-1024-512-256) 1240 and 490 us against 970, 797 and 63 -- there the product costs more.  The rates are what these show.
-static constexpr double RUNS_RATE = 7.5e14, RUNS_BYTES = 6.6e12;
+// next product is summed over runs anyway), and eight bytes a weight and task cost more than the extra product of a layer -- its operations, its
+// operands, which narrow layers read for few of them, and a launch.  The four figures are the least squares over 69 steps (24 to 300 tasks of 64
+// to 512 query rows; 10, 26, 40 and 64 fields of 64 columns; 128-64 to 1024-512-256).  With the runs and with the fp32 copy: 128 tasks
+// of 128 rows, 1677-512-256 1.46 / 1.58 ms, 4109-1024-512-256 4.35 / 4.81, 653-256-128 0.73 / 0.72; of 256 rows 1.87 / 1.91, 5.66 / 5.95,
+// 0.87 / 0.83; of 512 rows 1677-512-256 2.58 / 2.56, 1677-128-64 1.89 / 1.83; where the rule takes the slower one it is by 1.5 % at most.
+static constexpr double RUNS_BYTES = 6.4e12, RUNS_RATE = 1.6e15, RUNS_OPERANDS = 3.8e12, RUNS_LAUNCH = 4.6e-6;
 static bool query_runs(const gm_ctx* c, int Tw, int64_t rows_q, int n_runs, int K, int order) {
-    return c->mlp_dtype && order == 2 && K == 1 && c->L > 1 && 8.0 * (Tw - n_runs) / RUNS_BYTES > 2.0 * (double)rows_q / RUNS_RATE;
+    if (!c->mlp_dtype || order != 2 || K != 1) return false;
+    double saved = 0, cost = 0;
+    for (int l = 1; l < c->L; ++l) {
+        const double w = (double)c->ld[l - 1] * c->ld[l];
+        saved += 8.0 * (Tw - n_runs) * w / RUNS_BYTES;
+        cost += 2.0 * rows_q * w / RUNS_RATE + 2.0 * rows_q * (c->ld[l - 1] + c->ld[l]) / RUNS_OPERANDS + RUNS_LAUNCH;
+    }
+    return saved > cost;
 }
 
 // fp32 weight gradients of one pass that depend on nothing of each other, collected and launched together

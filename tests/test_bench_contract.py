@@ -110,3 +110,23 @@ def test_json_line_of_a_small_run():
     for key in ("value", "unit", "cores", "kind", "sample"):
         assert key in cpu, key
     assert cpu["kind"] == "oracle" and cpu["value"] > 0 and cpu["cores"] >= 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hidden,runs", [((512, 256), True), ((256, 128), True), ((96, 64), False), ((32,), False), ((), False)])
+def test_query_gradient_over_runs_of_tasks(hidden, runs):
+    """One second-order inner step, bf16: the query gradient summed over runs beside the chain's operand (a launch more per hidden layer) where
+    the layers are wide enough to pay for it, in fp32 per task otherwise; against the oracle either way."""
+    from paper_2401_04338_amd import GMeta
+    from tests.helpers import small_cfg
+    from tests.test_gpu_parity import TOL_BF16, _compare_step, _inputs
+    cfg = small_cfg(n_tasks=64, n_support=16, n_query=40, n_fields=10, emb_dim=64, rows_per_field=200, bag_max=2, mlp_dtype=1,
+                    layer_dims=(10 * 64 + 5,) + hidden + (1,))
+    sup, qry, params = _inputs(cfg)
+    ctx = GMeta.from_config(cfg, workspace_bytes=2 << 30)
+    ctx.configure("chain_factors", 1)   # (the direction as matrices)
+    ctx.profile(True)
+    _compare_step(cfg, ctx, sup, qry, params, 1, 2, TOL_BF16, f"{hidden}, over runs: {runs}", operand="bf16")
+    launches = ctx.profile_report().get("gemm_wgrad", {"launches": 0})["launches"]
+    ctx.close()
+    assert launches == (4 if runs else 3) * len(hidden)   # inner step, query set (twice), tangent pass
