@@ -269,15 +269,15 @@ int gm_index_prep(gm_ctx* ctx, int32_t n_tasks, const gm_set* support, const gm_
  *   "wgrad_wide": 1 (default) = weight-gradient products take 256 x 256 tiles when a group (a task, or
  *               a run of consecutive tasks for the products that are only ever summed over tasks) has at least 192
  *               rows, the layer is at least 1024 wide on the input side and a multiple of 256 on the output side, and
- *               the tiles fill the device at least twice; 0 = always 128 x 128 tiles.  Identical results over the
- *               same groups.
+ *               the tiles fill the device at least twice, or fill 85 % of their rounds over it and a group has at least
+ *               1,024 rows; 0 = always 128 x 128 tiles.  Identical results over the same groups.
  *   "theta_from_meta": bf16 operands, 2 to 4 inner steps: 1 (default) = the weight matrices of inner step k
  *               are written as theta - alpha * (the gradients of steps 0..k), one product per step accumulated on the
  *               matrix cores, straight from the meta parameters (every step's activations and deltas are kept for the
- *               second-order chain anyway; first order keeps them where tasks are small enough, up to 1050 support rows of a
- *               task and steps, and memory that the call has anyway holds them): no per-task fp32 copy of a weight matrix is
- *               written or read; 0 = every
- *               step updates a per-task fp32 master (theta_{k+1} = theta_k - alpha * gradient_k).  The same values up
+ *               second-order chain anyway; first order keeps them where tasks are small, fewer than 800 support rows of a
+ *               task times inner steps on average, and memory that the call has anyway holds them): no per-task fp32 copy of a
+ *               weight matrix is written or read; 0 = every step updates a per-task fp32 master
+ *               (theta_{k+1} = theta_k - alpha * gradient_k).  The same values up
  *               to fp32 rounding before the bf16 operand copy is taken.
  *   "chain_factors": bf16 operands, second order: the chain's direction on a task's hidden layers (the query gradient, less
  *               alpha times a Hessian-vector product per step) is a sum of products of the passes' inputs and deltas over the

@@ -1819,12 +1819,16 @@ static int query_sum(const gm_ctx* c, int K) { return K == 2 || (K == 3 && c->ml
 
 // bf16, 2..GEMM_MAX_PAIRS inner steps: every step's weights straight from the meta parameters and the gradients of all steps so far, bf16
 // copy only.  Second order keeps the steps' activations and deltas for the chain anyway.  First order does so where the extra products
-// (k + 1 of step k instead of one) cost less than the fp32 master, written and read again by the next step: 201 tasks of 75..225 rows,
-// 1677-512-256, three steps, the six products of the steps 1110 us with the master, 864 without; a product more costs 60 us there, so K steps
-// of r rows a task break even at K r = 1050.
+// (k + 1 of step k instead of one) cost less than the fp32 master, written and read again by the next step: with r rows a task
+// r K (K - 1) operations a weight against 8 (K - 1) bytes, so K r decides whatever the layers and the steps.  Whole steps with the master and
+// without, 200 tasks, 1677-512-256: K r = 290 2.62 / 2.47, 3.07 / 2.77 and 3.80 / 3.38 ms with two, three and four steps, 600 3.62 / 3.55, 4.13 / 3.97, 4.63
+// / 4.42, 800 4.56 / 4.53, 4.88 / 4.80, 5.26 / 5.13, 1024 5.32 / 5.33, 5.79 / 5.80, 5.72 / 5.63; 64 tasks, 4109-1024-512-256: 600 4.31 / 4.23, 4.97 / 4.78,
+// 5.75 / 5.46, 800 4.96 / 4.97, 5.95 / 5.93, 6.18 / 6.25, 1024 5.53 / 5.62, 6.37 / 6.46, 6.85 / 6.85, 2000 10.03 / 10.89 (four); 200 tasks,
+// 1677-128-64: 290 1.63 / 1.61, 1.66 / 1.61, 1.95 / 1.87, 600 2.47 / 2.47, 2.52 / 2.50, 2.62 / 2.63, 800 and more within 1 % either way.
+enum { FROM_META_ROWS = 800 };
 static bool theta_from_meta(const gm_ctx* c, int64_t T, int64_t n_support, int K, int order) {
     if (!c->mlp_dtype || K < 2 || K > GEMM_MAX_PAIRS || !c->theta_from_meta || T <= 0) return false;
-    return order == 2 || (c->L > 1 && (double)K * n_support < 1050.0 * (double)T);
+    return order == 2 || (c->L > 1 && (double)K * n_support < FROM_META_ROWS * (double)T);
 }
 
 // What a call without a chain keeps of its inner steps: only what spare memory holds if the batch runs as one wave, so that no call needs

@@ -162,3 +162,23 @@ def test_first_order_whatever_the_workspace_held(n_support, n_query, table):
         step(used, K, 2)
         assert all(torch.equal(x, y) for x, y in zip(step(used, K, 1), want)), K
     used.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,from_meta", [(396, True), (408, False)])
+def test_first_order_weights_on_both_sides_of_the_rule(rows, from_meta):
+    """Two steps of 396 rows a task: below 800, the second step's weights come from the meta parameters; of 408: from the fp32 master, the
+    same bits as with that asked for.  Against the oracle either way."""
+    from paper_2401_04338_amd import GMeta
+    from tests.helpers import small_cfg
+    from tests.test_gpu_parity import TOL_BF16, _compare_step, _inputs
+    cfg = small_cfg(n_tasks=4, n_support=rows, n_query=rows, n_fields=32, emb_dim=16, rows_per_field=300, bag_max=2, mlp_dtype=1,
+                    layer_dims=(32 * 16 + 5, 1024, 256, 1))   # (millions of weights: some round the other way)
+    sup, qry, params = _inputs(cfg)
+    ctx = GMeta.from_config(cfg, workspace_bytes=1 << 30)
+    out, _ = _compare_step(cfg, ctx, sup, qry, params, 2, 1, TOL_BF16, f"{rows} rows", operand="bf16")
+    a = [x.clone() for x in out["dW"]]
+    ctx.configure("theta_from_meta", 0)
+    out, _ = _compare_step(cfg, ctx, sup, qry, params, 2, 1, TOL_BF16, f"{rows} rows, fp32 master", operand="bf16")
+    ctx.close()
+    assert all(torch.equal(x, y) for x, y in zip(a, out["dW"])) != from_meta
