@@ -83,7 +83,7 @@ struct gm_ctx {
     int gemm_tile_n = 0;
     int wgrad_wide = 1;      // weight gradients over runs of tasks in 256 x 256 tiles where the shape allows
     int chain_factors = 0;   // the second-order chain's direction on a task's hidden layers: 0 by size, 1 matrices, 2 factors where they can be (see factor_rows)
-    int theta_from_meta = 1; // bf16, second order, several inner steps: a step's weights from theta and all steps' gradients
+    int theta_from_meta = 1; // bf16, several inner steps: a step's weights from theta and all steps' gradients, in first order where tasks are small
     int coarse_groups = 0;   // runs of tasks for the products only summed over tasks (0: chosen by shape)
     int n_cus = 256;
     int row_path = 0;   // task-local row arithmetic: 0 = choose per wave, 1 = sparse two-hop kernel, 2 = pair-count matrices
@@ -1140,6 +1140,10 @@ static bool wgrad_wide_ok(const gm_ctx* c, int M, int N, int64_t rows, int G) {
 // Runs of consecutive tasks that the products only summed over tasks are taken over.  16, unless the first layer's
 // product can run in 256 x 256 tiles, one workgroup per compute unit: the count in [12, 18] whose tiles fill the
 // last round over the compute units best, the largest run counted (the larger count on a tie).
+// The bound: each run is another set of sums to write and read again, and up to 18 nine in ten numbers of tiles a run (4 to 128) fill 85 % of a
+// round.  Products and sums of 256 or 128 tasks x 256 + 256 rows, 16 and 18 runs: 14 tiles a run (1677 x 512) 499 and 494 us, 24 (1933 x 768) 859 and 865, 44
+// (2573 x 1024) 847 and 884 (17: 869), 68 (4109 x 1024) 1282 and 1284.  More runs gain where a run has few tiles (1037 x 512, ten of them: 24 runs 373, 16 in
+// 128 x 128 tiles 409) and lose beyond (20 to 32 runs of the others: 832..888, 864..904, 1288..1353).
 enum { MOST_RUNS = 18 };
 // rows: of the wave's smaller set.  (The sums have the support input's room, as long as it is, and that of 16 runs otherwise.)
 static bool runs_in_wide_tiles(const gm_ctx* c, int64_t rows) {
@@ -1321,8 +1325,8 @@ static void forward_backward(gm_ctx* c, const Grp& g, const float* labels, const
 // coarse / coarse_out: the hidden layers' weight matrices are summed over runs of tasks instead (c1 times the gradient,
 // nothing added), for a caller that only wants their sum over the tasks -- and, where out has room for bf16 operands, those per
 // task; biases and the last layer stay per task.
-// hist / in0 (bf16 operands, an inner step of a second-order call): the passes of all inner steps so far, this one
-// last, and the meta parameters.  The step's weight matrices are then written as theta - alpha * (sum of the steps'
+// hist / in0 (bf16 operands, an inner step of a call that keeps its steps' activations): the passes of all inner steps so far, this
+// one last, and the meta parameters.  The step's weight matrices are then written as theta - alpha * (sum of the steps'
 // gradients), one product per step accumulated in the matrix cores, from the shared fp32 theta: no per-task fp32
 // master of a weight matrix is written or read (it was most of what a step of small tasks moved); biases and the
 // last layer keep their per-task fp32 chain (in, in_stride).
@@ -1370,9 +1374,9 @@ static void theta_grad(gm_ctx* c, const Grp& g, const Pass& p, Theta& out, const
 // gx_acc (bf16 mode): the support rows of the sparse-gradient buffer, which take -alpha * (tangent of dX) in the
 // layer-1 product itself; need_dx: the tangent of dX is also wanted in w.dX (for the row arithmetic of the next step); gx_init: the sum's
 // first term; gx_old: the first is what w.dX still holds
-// coarse (the chain's last step): the weight matrices' part of H v is not folded into every task's v but summed over
-// runs of tasks into w.vsum (unscaled); the caller adds -alpha times their sum to the reduced v
-// fold: -alpha times it is added to what w.vsum holds
+// coarse (the chain's last step; with factors, every step): the weight matrices' part of H v is not folded into every task's v but summed
+// over runs of tasks into w.vsum.  fold: -alpha times it is added to what w.vsum holds, the query gradient's sums (v's own weight
+// matrices are then not reduced: factors, query_runs); else it is stored unscaled, and the caller adds -alpha times its sum to the reduced v
 static void hvp_step(gm_ctx* c, const Grp& g, const StepState& s, WaveBufs& w, float alpha, bool refresh_v_copies,
                      float* gx_acc, bool need_dx, bool gx_init, bool gx_old, bool tx, const Grp* coarse = nullptr, bool fold = false) {
     hipStream_t st = c->stream;
@@ -1841,7 +1845,7 @@ static FirstOrder first_order_keeps(const gm_ctx* c, int64_t T, int64_t n_suppor
         std::vector<Act> A, D;
         Spare sp = make_spare(c, T, Pq, nullptr, alloc_query(c, query, A, D, Pq), nullptr, nullptr, &none);
         WaveBufs w;
-        w.steps.assign(std::max(K, 1), StepState());
+        w.steps.resize(k.acts ? K : 0);
         alloc_first_order(c, sp, w, Ps, K, k.grads, k.acts);
         return !none.overflow;
     };
