@@ -1168,11 +1168,11 @@ static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
 // Whether the query gradient, where the second-order chain's direction starts, is summed over runs of tasks beside being written per
 // task as the chain's bf16 operand, instead of being written in fp32 per task and read again for the sum: one inner step (the chain's
 // next product is summed over runs anyway), and eight bytes a weight and task cost more than the extra product of a layer -- its operations, its
-// operands, which narrow layers read for few of them, and a launch.  The four figures are the least squares over 69 steps (24 to 300 tasks of 64
-// to 512 query rows; 10, 26, 40 and 64 fields of 64 columns; 128-64 to 1024-512-256).  With the runs and with the fp32 copy: 128 tasks
+// operands, which narrow layers read for few of them, and a launch.  The four figures are the least squares over 70 steps (24 to 300 tasks of 64
+// to 512 query rows, weighted by the power -0.7 of their times; 10, 26, 40 and 64 fields of 64 columns; 128-64 to 1024-512-256).  With the runs and with the fp32 copy: 128 tasks
 // of 128 rows, 1677-512-256 1.46 / 1.58 ms, 4109-1024-512-256 4.35 / 4.81, 653-256-128 0.73 / 0.72; of 256 rows 1.87 / 1.91, 5.66 / 5.95,
-// 0.87 / 0.83; of 512 rows 1677-512-256 2.58 / 2.56, 1677-128-64 1.89 / 1.83; where the rule takes the slower one it is by 1.5 % at most.
-static constexpr double RUNS_BYTES = 6.4e12, RUNS_RATE = 1.6e15, RUNS_OPERANDS = 3.8e12, RUNS_LAUNCH = 4.6e-6;
+// 0.87 / 0.83; of 512 rows 1677-512-256 2.58 / 2.56, 1677-128-64 1.89 / 1.83, 4109-1024-512-256 its products and sums alone 4.25 / 4.14; where the rule takes the slower one it is by 1.5 % at most.
+static constexpr double RUNS_BYTES = 6.45e12, RUNS_RATE = 1.22e15, RUNS_OPERANDS = 5.06e12, RUNS_LAUNCH = 4.84e-6;
 static bool query_runs(const gm_ctx* c, int Tw, int64_t rows_q, int n_runs, int K, int order) {
     if (!c->mlp_dtype || order != 2 || K != 1) return false;
     double saved = 0, cost = 0;
@@ -1933,7 +1933,7 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
     const int max_per = std::min(std::max(T, 1), most_wave_tasks(c));
     const int fewest = (std::max(T, 1) + max_per - 1) / max_per;
     int n_waves = fewest;
-    const FirstOrder keeps = first_order_keeps(c, T, sup->n_samples, B.poff_s[T], B.poff_q[T], K);
+    const FirstOrder keeps = order == 1 ? first_order_keeps(c, T, sup->n_samples, B.poff_s[T], B.poff_q[T], K) : FirstOrder{false, false};
     while (true) {
         const int per = (std::max(T, 1) + n_waves - 1) / n_waves;
         plans.clear();
@@ -1965,7 +1965,7 @@ static int plan_waves(gm_ctx* c, Batch& B, size_t avail, int K, int order, int b
         }
         if (fits) return GM_OK;
         // (a wave less is worth more than what the steps keep)
-        B.tight = order == 1 && !B.tight && (keeps.grads || keeps.acts);
+        B.tight = !B.tight && (keeps.grads || keeps.acts);
         if (B.tight) continue;
         if (per == 1) {
             if (B.pair_rows == PAIR_ROWS) return fail(c, GM_ERR_WORKSPACE, "workspace of %zu bytes cannot hold one task", c->ws_bytes);
