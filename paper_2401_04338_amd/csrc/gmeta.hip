@@ -1168,11 +1168,12 @@ static int coarse_group_count(const gm_ctx* c, int Tw, int64_t rows) {
 // Whether the query gradient, where the second-order chain's direction starts, is summed over runs of tasks beside being written per
 // task as the chain's bf16 operand, instead of being written in fp32 per task and read again for the sum: one inner step (the chain's
 // next product is summed over runs anyway), and eight bytes a weight and task cost more than the extra product of a layer -- its operations, its
-// operands, which narrow layers read for few of them, and a launch.  The four figures are the least squares over 70 steps (24 to 300 tasks of 64
-// to 512 query rows, weighted by the power -0.7 of their times; 10, 26, 40 and 64 fields of 64 columns; 128-64 to 1024-512-256).  With the runs and with the fp32 copy: 128 tasks
-// of 128 rows, 1677-512-256 1.46 / 1.58 ms, 4109-1024-512-256 4.35 / 4.81, 653-256-128 0.73 / 0.72; of 256 rows 1.87 / 1.91, 5.66 / 5.95,
-// 0.87 / 0.83; of 512 rows 1677-512-256 2.58 / 2.56, 1677-128-64 1.89 / 1.83, 4109-1024-512-256 its products and sums alone 4.25 / 4.14; where the rule takes the slower one it is by 1.5 % at most.
-static constexpr double RUNS_BYTES = 6.45e12, RUNS_RATE = 1.22e15, RUNS_OPERANDS = 5.06e12, RUNS_LAUNCH = 4.84e-6;
+// operands, which narrow layers read for few of them, and a launch.  The four figures are the least squares over 81 steps (24 to 512 tasks of 64
+// to 512 query rows, weighted by the power -0.7 of their times; 10, 26, 40 and 64 fields of 64 columns; 128-64 to 1024-512-256).  With the runs
+// and with the fp32 copy: 128 tasks of 128 rows, 1677-512-256 1.46 / 1.58 ms, 4109-1024-512-256 4.35 / 4.81, 653-256-128 0.73 / 0.72; of 256 rows
+// 1.87 / 1.91, 5.66 / 5.95, 0.87 / 0.83; 200 of 384 rows, 4109-1024-512-256 10.76 / 11.00; 256 of 512 rows 15.12 / 15.04, 1677-512-256 4.64 / 4.61; 128
+// of 512, 1677-128-64 1.89 / 1.83.  Where the rule takes the slower one it is by 1.5 % at most.
+static constexpr double RUNS_BYTES = 6.56e12, RUNS_RATE = 1.23e15, RUNS_OPERANDS = 5.81e12, RUNS_LAUNCH = 5.27e-6, RUNS_MARGIN = 1.05;
 static bool query_runs(const gm_ctx* c, int Tw, int64_t rows_q, int n_runs, int K, int order) {
     if (!c->mlp_dtype || order != 2 || K != 1) return false;
     double saved = 0, cost = 0;
@@ -1181,7 +1182,7 @@ static bool query_runs(const gm_ctx* c, int Tw, int64_t rows_q, int n_runs, int 
         saved += 8.0 * (Tw - n_runs) * w / RUNS_BYTES;
         cost += 2.0 * rows_q * w / RUNS_RATE + 2.0 * rows_q * (c->ld[l - 1] + c->ld[l]) / RUNS_OPERANDS + RUNS_LAUNCH;
     }
-    return saved > cost;
+    return saved > RUNS_MARGIN * cost;
 }
 
 // fp32 weight gradients of one pass that depend on nothing of each other, collected and launched together

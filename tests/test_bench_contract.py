@@ -120,7 +120,7 @@ def test_query_gradient_over_runs_of_tasks(hidden, runs):
     from paper_2401_04338_amd import GMeta
     from tests.helpers import small_cfg
     from tests.test_gpu_parity import TOL_BF16, _compare_step, _inputs
-    cfg = small_cfg(n_tasks=64, n_support=16, n_query=40, n_fields=10, emb_dim=64, rows_per_field=200, bag_max=2, mlp_dtype=1,
+    cfg = small_cfg(n_tasks=96, n_support=16, n_query=40, n_fields=10, emb_dim=64, rows_per_field=200, bag_max=2, mlp_dtype=1,
                     layer_dims=(10 * 64 + 5,) + hidden + (1,))
     sup, qry, params = _inputs(cfg)
     ctx = GMeta.from_config(cfg, workspace_bytes=2 << 30)

@@ -22,7 +22,7 @@ def _set(samples, bag):
 
 
 @pytest.mark.parametrize("uneven", [0, 1])
-@pytest.mark.parametrize("samples,bag,split", [(100, 6, 1), (300, 5, 2), (700, 9, 5)])   # (step = 256 x split)
+@pytest.mark.parametrize("samples,bag,split", [(100, 6, 1), (300, 5, 2), (700, 9, 5)])   # (step = 256 x split: workgroups of 256 threads)
 def test_one_bad_index(gm, samples, bag, split, uneven):  # noqa: F811
     from paper_2401_04338_amd import GMetaError
     step, n = 256 * split, samples * F * bag
