@@ -517,10 +517,6 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
     const bool second = order == 2 && K > 0;
     w.TXf = (second && bf) ? ar.get<float>(d.Ps * ld0) : nullptr;
     w.dX = ar.get<float>(std::max(d.Ps, d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
-    if (d.table) {
-        w.GX = ar.get<float>((d.Ps + d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
-        query_grad = w.GX ? w.GX + d.Ps * (int64_t)c->FD : nullptr;
-    }
     w.loss_q = ar.get<float>(d.Pq + 1);
     const bool factors = d.factor_ld > 0;
     w.v = Theta{ar.get<float>((int64_t)d.Tw * c->n_theta), c->n_theta, c->mlp_dtype && !factors ? ar.get<bf16_t>((int64_t)d.Tw * c->n_theta_b) : nullptr, c->n_theta_b};
@@ -543,11 +539,6 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
         s.wL_copy = (bf && second && k > 0) ? ar.get<float>((int64_t)d.Tw * c->ld[L - 1]) : nullptr;
     }
     const size_t query_bytes = alloc_query(c, ar, w.Aq, w.Dq, d.Pq);
-    w.dX_kept = nullptr;
-    if (!second) {
-        Spare sp = make_spare(c, d.Tw, d.Pq, L > 1 ? w.Aq[1].b : nullptr, bf ? query_bytes : 0, query_grad, w.v.f, &ar);
-        alloc_first_order(c, sp, w, d.Ps, K, d.query_sum > 2, d.from_meta);
-    }
     // theta^(k+1), k = 0..K-1.  fp32: one buffer per kept step (the second-order pass needs them all), or one
     // updated in place.  bf16: ONE fp32 master updated in place, and bf16 operand copies per kept step.
     const int n_bufs = second ? K : (K > 0 ? 1 : 0);
@@ -592,8 +583,15 @@ static void alloc_wave_dense(const gm_ctx* c, Arena& ar, WaveBufs& w, const Wave
         w.room.S = ar.get<bf16_t>(w.room.slot * factor_slots(K) + 8);
     }
     if (d.table) {
+        w.GX = ar.get<float>((d.Ps + d.Pq) * (int64_t)std::max(c->FD, 1) + 4);
+        query_grad = w.GX ? w.GX + d.Ps * (int64_t)c->FD : nullptr;
         w.n_rows = ar.get<int64_t>(2);
         alloc_sort(c, ar, w.so, d.nnz_s + d.nnz_q, c->field_base[c->F], 0, true);
+    }
+    w.dX_kept = nullptr;
+    if (!second) {
+        Spare sp = make_spare(c, d.Tw, d.Pq, L > 1 ? w.Aq[1].b : nullptr, bf ? query_bytes : 0, query_grad, w.v.f, &ar);
+        alloc_first_order(c, sp, w, d.Ps, K, d.query_sum > 2, d.from_meta);
     }
 }
 
